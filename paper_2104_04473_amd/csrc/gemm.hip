@@ -5,10 +5,10 @@
 //   mode NT: C[M,N] = A[M,K] B[N,K]^T        input grad   dX = dY W^T
 //   mode TN: C[M,N] = A[K,M]^T B[K,N]        weight grad  dW = X^T dY
 //
-// bf16 path (gfx950): v_mfma_f32_16x16x32_bf16 for NN and NT, v_mfma_f32_32x32x16_bf16 for TN; 256 x 256 block
-// tile, two LDS stages of 64 k filled by direct global->LDS loads.  An operand whose reduction index is the slow
-// memory index (B in NN, both in TN) stays in its memory order in LDS and is gathered into MFMA fragments by
-// transposing LDS reads.
+// bf16 path (gfx950): v_mfma_f32_16x16x32_bf16, 256 x 256 block tile, two LDS stages of 64 k filled by direct
+// global->LDS loads, two groups of waves that alternate between the matrix cores and memory.  An operand whose
+// reduction index is the slow memory index (B in NN, both in TN) stays in its memory order in LDS and is gathered
+// into MFMA fragments by transposing LDS reads.
 // fp32 path: a plain LDS-tiled FMA kernel (correctness configuration only).
 #include "common.h"
 #include <type_traits>
@@ -16,7 +16,6 @@
 namespace ptdp {
 
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8_t;
-typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16_t;
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4_t;
 
 // ------------------------------------------------------------------------------------------------
@@ -69,21 +68,20 @@ gemm_f32_kernel(const float* __restrict__ A, const float* __restrict__ B, float*
 }
 
 // ------------------------------------------------------------------------------------------------
-// bf16 MFMA kernel: global -> LDS without passing through registers (buffer_load ... lds, 16 bytes
-// per lane), 256 x 256 x 64 block tile, 8 waves (2 x 4, 128 x 64 each), two LDS stages.
-// Out-of-range lanes use an offset beyond the buffer's num_records, for which the hardware returns
-// zeros.
+// bf16 MFMA kernel: 256 x 256 x 64 block tile, 8 waves in two groups of four (one wave of each group per SIMD).
 //
-// LDS tile layouts:
-//   k-contiguous operand: [row][8 chunks of 16 B]; chunk c of row r sits in slot c ^ f(r), f chosen
-//     so that 16 neighbouring rows of one fragment read fall into 16 different 16-byte bank groups.
-//   k-slow operand (memory [k][row]): [k][32 chunks of 16 B] (512 B per k); chunk c of k-row k sits in
-//     slot c ^ (4 * (k & 3)) ^ (2 * ((k >> 3) & 1)): the four k-rows that one group of 16 lanes gathers land in
-//     different bank groups, and so do k-rows 8 apart, which the 16x16x32 fragments read in the same cycle.
-//     MFMA fragments are gathered with ds_read_b64_tr_b16: within 16 lanes, lane i receives element (i & 3) of
-//     the 8-byte rows addressed by lanes (i >> 2) + {0, 4, 8, 12}.
+// LDS holds two stages of four half-tiles of 16 KiB (rows 0-127 and 128-255 of each operand, 64 k deep), filled by
+// direct global->LDS loads (buffer_load ... lds, 16 bytes per lane, out-of-range lanes deliver zeros).
+//   k-contiguous operand: [128 rows][8 chunks of 16 B]; chunk c of row r sits in slot c ^ ((r >> 1) & 7), so that the
+//     16 neighbouring rows of one fragment read fall into 16 different 16-byte bank groups.
+//   k-slow operand (memory [k][row]): [64 k][16 chunks of 16 B]; chunk c of k-row k sits in slot
+//     c ^ (2 * (k & 3)) ^ (8 * ((k >> 3) & 1)): the k-rows that one transposing read gathers in a cycle (k & 3 and
+//     (k >> 3) & 1 take all values) land in different bank groups.  MFMA fragments are gathered with
+//     ds_read_b64_tr_b16: within 16 lanes, lane i receives element (i & 3) of the 8-byte rows addressed by lanes
+//     (i >> 2) + {0, 4, 8, 12}.
 // ------------------------------------------------------------------------------------------------
 typedef __attribute__((__vector_size__(4 * sizeof(short)))) short s16x4_t;
+typedef __attribute__((__vector_size__(8 * sizeof(short)))) short s16x8_t;
 typedef __attribute__((address_space(3))) void lds_void_t;
 
 constexpr uint32_t kOob = 0x80000000u;  // beyond any num_records this kernel accepts (< 2 GiB)
@@ -99,152 +97,111 @@ __device__ __forceinline__ uint32_t lds_offset(const char* p) {
   return (uint32_t)reinterpret_cast<uintptr_t>((lds_void_t*)p);
 }
 
-// Global -> LDS loads (16 bytes per lane, lane i lands at dst + 16*i; dst wave-uniform) are written as assembly:
-// the compiler makes every LDS read that it cannot prove disjoint (all transposing reads) wait for every such
-// load in flight, which would cut the distance between request and use from a k-tile to a fraction of one.  The
-// main loops order these loads themselves: an explicit vmcnt(0) wait and a barrier stand between a request and
-// the first read of what it brings, and no other vector-memory access is in flight while one of them is.
+// Global -> LDS loads (lane i lands at dst + 16*i; dst wave-uniform) are written as assembly: the compiler makes
+// every LDS read that it cannot prove disjoint wait for every such load in flight.  The main loop orders these
+// loads itself, by counted vmcnt waits and barriers.
 __device__ __forceinline__ void load_lds_16(rsrc_t r, char* dst, uint32_t voff) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
                :: "s"(lds_offset(dst)), "v"(voff), "s"(r) : "memory", "m0");
 }
-__device__ __forceinline__ void load_lds_4(rsrc_t r, char* dst, uint32_t voff) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, 0 offen lds"
-               :: "s"(lds_offset(dst)), "v"(voff), "s"(r) : "memory", "m0");
-}
-// four wave-loads whose destinations lie 1 KiB apart: the instruction's offset field moves the destination (and
-// the source: the lane offsets passed in are 0, 1024, 2048, 3072 bytes short); soff is added to the source only
-__device__ __forceinline__ void load_lds_16x4(rsrc_t r, char* dst, uint32_t v0, uint32_t v1, uint32_t v2, uint32_t v3,
-                                              uint32_t soff) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\t"
-               "buffer_load_dwordx4 %1, %5, %6 offen lds\n\t"
-               "buffer_load_dwordx4 %2, %5, %6 offen offset:1024 lds\n\t"
-               "buffer_load_dwordx4 %3, %5, %6 offen offset:2048 lds\n\t"
-               "buffer_load_dwordx4 %4, %5, %6 offen offset:3072 lds"
-               :: "s"(lds_offset(dst)), "v"(v0), "v"(v1), "v"(v2), "v"(v3), "s"(r), "s"(soff) : "memory", "m0");
-}
-// two of the four: loads H*2 and H*2+1 of a group (instruction offsets 2048*H and 2048*H + 1024)
-template <int H>
+// two wave-loads whose destinations lie 1 KiB apart: the instruction's offset field moves the destination (and the
+// source: the second lane offset passed in is 1024 bytes short); soff is added to the source only
 __device__ __forceinline__ void load_lds_16x2(rsrc_t r, char* dst, uint32_t v0, uint32_t v1, uint32_t soff) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\t"
-               "buffer_load_dwordx4 %1, %3, %4 offen offset:%5 lds\n\t"
-               "buffer_load_dwordx4 %2, %3, %4 offen offset:%6 lds"
-               :: "s"(lds_offset(dst)), "v"(v0), "v"(v1), "s"(r), "s"(soff), "n"(H * 2048), "n"(H * 2048 + 1024) : "memory", "m0");
+               "buffer_load_dwordx4 %1, %3, %4 offen lds\n\t"
+               "buffer_load_dwordx4 %2, %3, %4 offen offset:1024 lds"
+               :: "s"(lds_offset(dst)), "v"(v0), "v"(v1), "s"(r), "s"(soff) : "memory", "m0");
 }
 
-// One 256-row operand tile of 64 k (32 KiB) is filled by 32 wave-loads of 1 KiB; wave w of NW issues
-// wave-loads w*LPW .. w*LPW+LPW-1.
-// A k-tile that lies inside K whole is requested with as few instructions as the hardware allows, because every
-// one of them takes an issue slot from the MFMAs: the lane offsets are loop constants, the k advance rides in the
-// scalar offset, and the destinations of four consecutive wave-loads differ only in the instruction's offset
-// field (which moves the source too, so it is taken out of the lane offset beforehand); the last, partial k-tile
-// and operands with rows shorter than 256 elements take the general form with its per-lane checks.
 constexpr int BK = 64;
-template <bool KSLOW, int NW> struct TileLoad {
-  static constexpr int LPW = 32 / NW;
-  uint32_t offm[LPW];  // byte offset of the lane's chunk at k-tile 0 minus 1024 * (i % 4), or kOob if its row is out of range
+constexpr int kBM = 256, kBN = 256, kGemmThreads = 512;
+constexpr int kHalfBytes = 128 * BK * 2, kStageBytes = 4 * kHalfBytes, kGemmSmem = 2 * kStageBytes;
+
+// A wave's share of one operand's half-tiles: two wave-loads of 1 KiB each (16 rows, or 8 k-rows, per wave).
+// A k-tile that lies inside K whole is requested with as few instructions as the hardware allows: the lane offsets
+// are loop constants and the k advance rides in the scalar offset (which the descriptor's bounds check excludes);
+// the last, partial k-tile, tiles past the end (all lanes out of range) and operands with short rows take the
+// general form with its per-lane checks.  Either way a call issues two loads: the main loop counts them.
+template <bool KSLOW> struct HalfLoad {
+  uint32_t off[2][2];  // [half][load]: byte offset of the lane's chunk at k-tile 0 minus 1024 * load, or kOob if its row is out of range
   uint32_t kstep;      // byte advance per k-tile
-  int kfirst;          // k of wave-load 0's chunk (k-contiguous: first k of the chunk; k-slow: the k-row)
+  int kpos[2];         // k of the lane's chunk inside the k-tile
   bool plain;          // no offset above goes negative
 
   // the descriptor's base is the block's first row (k-contiguous: base + row0*ld; k-slow: base + row0)
   __device__ __forceinline__ void init(size_t ld, int rows_left, int wave, int lane) {
 #pragma unroll
-    for (int i = 0; i < LPW; ++i) {
-      const int li = wave * LPW + i;
-      const uint32_t imm = (uint32_t)(i & 3) * 1024u;
+    for (int i = 0; i < 2; ++i) {
       if (!KSLOW) {
-        const int row = li * 8 + (lane >> 3);
+        const int row = wave * 16 + i * 8 + (lane >> 3);
         const int chunk = (lane & 7) ^ ((row >> 1) & 7);
-        offm[i] = row < rows_left ? (uint32_t)(((size_t)row * ld + chunk * 8) * 2) - imm : kOob;
+        kpos[i] = chunk * 8;
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+          off[h][i] = h * 128 + row < rows_left ? (uint32_t)(((size_t)(h * 128 + row) * ld + chunk * 8) * 2) - i * 1024u : kOob;
       } else {
-        const int k = li * 2 + (lane >> 5);
-        const int chunk = (lane & 31) ^ (4 * (k & 3)) ^ (2 * ((k >> 3) & 1));
-        offm[i] = chunk * 8 < rows_left ? (uint32_t)(((size_t)k * ld + chunk * 8) * 2) - imm : kOob;
+        const int k = wave * 8 + i * 4 + (lane >> 4);
+        const int chunk = (lane & 15) ^ (2 * (k & 3)) ^ (8 * ((k >> 3) & 1));
+        kpos[i] = k;
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+          off[h][i] = h * 128 + chunk * 8 < rows_left ? (uint32_t)(((size_t)k * ld + h * 128 + chunk * 8) * 2) - i * 1024u : kOob;
       }
     }
     kstep = KSLOW ? (uint32_t)(BK * ld * 2) : (uint32_t)(BK * 2);
-    kfirst = KSLOW ? wave * LPW * 2 + (lane >> 5) : 0;
-    plain = ld >= 256;   // row (or k-row) i of a wave-load starts at least 1024 * (i % 4) bytes into the block
+    plain = ld >= 128;   // row i*8 (k-row i*4) of a wave's share starts at least 1024 * i bytes into the block
   }
-  // k of the lane's data in wave-load i: k-contiguous -> depends on the row's swizzle, recomputed here
-  __device__ __forceinline__ int kpos(int i, int wave, int lane) const {
-    if (KSLOW) return kfirst + 2 * i;
-    const int row = (wave * LPW + i) * 8 + (lane >> 3);
-    return ((lane & 7) ^ ((row >> 1) & 7)) * 8;
-  }
-  // The same request in two instalments (four loads per wave only): H = 0 issues loads 0 and 1, H = 1 loads 2 and 3;
-  // where the lean form does not apply, H = 0 issues everything and H = 1 nothing.
-  template <int H> __device__ __forceinline__ void issue_half(rsrc_t r, char* tile, int wave, int lane, int kt, int K) {
-    static_assert(LPW == 4, "one group of four loads per wave");
-    if (plain && (kt + 1) * BK <= K)
-      load_lds_16x2<H>(r, tile + wave * LPW * 1024, offm[2 * H], offm[2 * H + 1], (uint32_t)kt * kstep);
-    else if (H == 0)
-      issue(r, tile, wave, lane, kt, K);
-  }
-  // k-tiles past the end of K come back as zeros (every lane out of range)
-  __device__ __forceinline__ void issue(rsrc_t r, char* tile, int wave, int lane, int kt, int K) {
-    if (plain && (kt + 1) * BK <= K) {
-      const uint32_t koff = (uint32_t)kt * kstep;
-#pragma unroll
-      for (int i = 0; i < LPW; i += 4)
-        load_lds_16x4(r, tile + (wave * LPW + i) * 1024, offm[i], offm[i + 1], offm[i + 2], offm[i + 3], koff);
+  // LEAN: the caller knows that the k-tile lies inside K whole and that plain is set
+  template <int H, bool LEAN> __device__ __forceinline__ void issue(rsrc_t r, char* half, int wave, int kt, int kend) const {
+    char* dst = half + wave * 2048;
+    if (LEAN) {
+      load_lds_16x2(r, dst, off[H][0], off[H][1], (uint32_t)kt * kstep);
     } else {
 #pragma unroll
-      for (int i = 0; i < LPW; ++i) {
-        const bool ok = offm[i] != kOob && kt * BK + kpos(i, wave, lane) < K;
-        load_lds_16(r, tile + (wave * LPW + i) * 1024, ok ? offm[i] + (uint32_t)(i & 3) * 1024u + (uint32_t)kt * kstep : kOob);
+      for (int i = 0; i < 2; ++i) {
+        const bool ok = off[H][i] != kOob && kt * BK + kpos[i] < kend;
+        load_lds_16(r, dst + i * 1024, ok ? off[H][i] + i * 1024u + (uint32_t)kt * kstep : kOob);
       }
     }
   }
 };
 
-// MFMA operand fragment (row = tile row of this lane, 8 k of k16 step kk) from either layout
-template <bool KSLOW>
-__device__ __forceinline__ bf16x8_t read_frag(const char* tile, int row_base, int kk, int lane) {
-  if (!KSLOW) {
-    const int row = row_base + (lane & 31);
-    const int chunk = (kk * 2 + (lane >> 5)) ^ ((row >> 1) & 7);
-    return *reinterpret_cast<const bf16x8_t*>(tile + row * 128 + chunk * 16);
-  } else {
+// MFMA fragments of v_mfma_f32_16x16x32_bf16 for NB blocks of 16 rows starting at row w0 of a half-tile: lane & 15 is
+// the row inside the block, lane >> 4 selects which 8 of the 32 k of step ks (0, 1) the lane carries.  One LDS address
+// per stage and swizzle pattern; everything else is in the instructions' offset fields.
+#define PTDP_LDS(T, addr) ((__attribute__((address_space(3))) T*)(uintptr_t)(addr))
+template <bool KSLOW, int NB> struct FragRead {
+  uint32_t base[2][KSLOW ? NB : 2];
+  __device__ __forceinline__ void init(const char* smem, int w0, int lane) {
     const int r = lane & 15, G = lane >> 4;
-    const int n0 = row_base + 16 * (G & 1) + 4 * (r & 3);
-    const int k = kk * 16 + 8 * (G >> 1) + (r >> 2);  // (k & 3) == r >> 2 and (k >> 3) & 1 == G >> 1 for both halves
-    const int slot = (n0 >> 3) ^ (4 * (r >> 2)) ^ (2 * (G >> 1));
-    const char* p = tile + k * 512 + slot * 16 + (n0 & 7) * 2;
-    const s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4_t __attribute__((address_space(3)))*)(p));
-    const s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4_t __attribute__((address_space(3)))*)(p + 4 * 512));
-    typedef __attribute__((__vector_size__(8 * sizeof(short)))) short s16x8_t;
-    s16x8_t v = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-    return *reinterpret_cast<bf16x8_t*>(&v);
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+      const uint32_t stage = lds_offset(smem) + s * kStageBytes;
+      if (!KSLOW) {
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks) base[s][ks] = stage + (w0 + r) * 128 + (((ks * 4 + G) ^ (r >> 1)) * 16);
+      } else {
+#pragma unroll
+        for (int i = 0; i < NB; ++i) {
+          const int n0 = w0 + i * 16 + 4 * (r & 3), k = 8 * G + (r >> 2);
+          base[s][i] = stage + k * 256 + (((n0 >> 3) ^ (2 * (r >> 2)) ^ (8 * (G & 1))) * 16) + (n0 & 7) * 2;
+        }
+      }
+    }
   }
-}
-
-// MFMA operand fragment of v_mfma_f32_16x16x32_bf16 from either layout: lane (lane & 15) is the tile row
-// (column of C for the B operand) inside the 16-row block starting at row_base, lane >> 4 selects which 8 of
-// the 32 k of step ks (0, 1) the lane carries.
-template <bool KSLOW>
-__device__ __forceinline__ bf16x8_t read_frag16(const char* tile, int row_base, int ks, int lane) {
-  if (!KSLOW) {
-    const int row = row_base + (lane & 15);
-    const int chunk = (ks * 4 + (lane >> 4)) ^ ((row >> 1) & 7);
-    return *reinterpret_cast<const bf16x8_t*>(tile + row * 128 + chunk * 16);
-  } else {
-    const int r = lane & 15, G = lane >> 4;
-    const int n0 = row_base + 4 * (r & 3);
-    const int k = ks * 32 + 8 * G + (r >> 2);  // (k & 3) == r >> 2 and (k >> 3) & 1 == G & 1 for both halves
-    const int slot = (n0 >> 3) ^ (4 * (r >> 2)) ^ (2 * (G & 1));
-    const char* p = tile + k * 512 + slot * 16 + (n0 & 7) * 2;
-    const s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4_t __attribute__((address_space(3)))*)(p));
-    const s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4_t __attribute__((address_space(3)))*)(p + 4 * 512));
-    typedef __attribute__((__vector_size__(8 * sizeof(short)))) short s16x8_t;
-    s16x8_t v = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-    return *reinterpret_cast<bf16x8_t*>(&v);
+  // S: stage, at: byte offset of the half-tile in the stage
+  template <int S> __device__ __forceinline__ bf16x8_t get(int at, int i, int ks) const {
+    if (!KSLOW) {
+      return *PTDP_LDS(const bf16x8_t, base[S][ks] + at + i * 2048);
+    } else {
+      const uint32_t p = base[S][i] + at + ks * (32 * 256);
+      const s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(PTDP_LDS(s16x4_t, p));
+      const s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(PTDP_LDS(s16x4_t, p + 4 * 256));
+      const s16x8_t v = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+      return __builtin_bit_cast(bf16x8_t, v);
+    }
   }
-}
-
-// s_waitcnt vmcnt(0) only (gfx9 encoding: lgkmcnt and expcnt fields left at their maxima)
-__device__ __forceinline__ void wait_vmcnt0() { __builtin_amdgcn_s_waitcnt(0x0f70); }
+};
 
 // Operands of one GEMM call as the kernels see them.  N is the number of columns this launch covers;
 // ldb / ldc are the row lengths of the full B (k-slow form) and C, so that a launch may cover a column
@@ -259,82 +216,30 @@ struct GemmArgs {
   size_t lda, ldb, ldc;
 };
 
-constexpr int kBM = 256, kBN = 256;
-constexpr int kTileBytes = 256 * BK * 2, kStageBytes = 2 * kTileBytes;
+// One wave's share of a tile: acc[ha][hb] covers rows ha*128 + (wave/4)*64 .. +63 and columns hb*128 + (wave%4)*32
+// .. +31 in blocks of 16 x 16.  The MFMA's A operand is the B fragment, so that a lane holds row lane & 15 of a block
+// and its four columns 4 * (lane >> 4) .. +3: consecutive in memory, written without a trip through LDS.
+typedef f32x4_t TileAcc[2][2][4][2];
 
-// L2 prefetch of operand panels.  In the data-parallel form the 32 workgroups that an XCD runs at a time cover 8 row
-// tiles x 4 column tiles and walk k together, so every line of an A panel is wanted by 4 of them and every line of a
-// B panel by 8, within a fraction of a k-tile.  Panels that the launch streams once (the weights, in forward and data
-// gradient; the activations of a weight gradient) come from HBM, and a request that misses L2 takes longer than the
-// one k-tile by which the main loop requests ahead.  So with its request for k-tile kt each workgroup also touches
-// (4 bytes per 128-byte line, into a scratch corner of LDS) its share of the panels' lines of k-tile kt + kTouchAhead:
-// sharer c of 4 takes a quarter of the A lines, sharer q of 8 an eighth of the B lines; wave 0 touches A, wave 1 B.
-// The demand requests of the next round then hit in L2 (measured at the 1T-shaped layer's shapes: forward and data
-// gradient GEMMs 7 % faster on average, 10-12 % where k = 25600).  `share` = q | c << 8, or -1 for no touching.
-#ifndef PTDP_GEMM_TOUCH_AHEAD
-#define PTDP_GEMM_TOUCH_AHEAD 1
-#endif
-constexpr int kTouchAhead = PTDP_GEMM_TOUCH_AHEAD;   // 0: off
-constexpr int kTouchLdsBytes = 2048;                 // 256 bytes per wave, above the two stages
-template <bool TA, bool TB> struct PanelTouch {
-  uint32_t off, step;
-  bool on, is_a;
-  __device__ __forceinline__ void init(const GemmArgs& g, int m0, int n0, int share, int wave, int lane) {
-    on = kTouchAhead > 0 && !TA && share >= 0 && wave < 2;   // weight gradients (both operands k-slow, 32 k-tiles per tile): 1.5 % slower with it
-    is_a = wave == 0;
-    off = kOob;
-    step = 0;
-    if (!on) return;
-    const int q = share & 0xff, c = (share >> 8) & 3;
-    if (is_a) {
-      if (!TA) {            // k-contiguous: one line per row and k-tile; 64 rows
-        const int row = c * 64 + lane;
-        off = row < g.M - m0 ? (uint32_t)((size_t)row * g.lda * 2) : kOob;
-        step = BK * 2;
-      } else {              // k-slow: four lines per k-row; 16 k-rows
-        const int kr = c * 16 + (lane >> 2), l = lane & 3;
-        off = l * 64 < g.M - m0 ? (uint32_t)(((size_t)kr * g.lda + l * 64) * 2) : kOob;
-        step = (uint32_t)(BK * g.lda * 2);
-      }
-    } else if (lane < 32) {
-      if (!TB) {            // 32 rows
-        const int row = q * 32 + lane;
-        off = row < g.N - n0 ? (uint32_t)((size_t)row * g.ldb * 2) : kOob;
-        step = BK * 2;
-      } else {              // 8 k-rows
-        const int kr = q * 8 + (lane >> 2), l = lane & 3;
-        off = l * 64 < g.N - n0 ? (uint32_t)(((size_t)kr * g.ldb + l * 64) * 2) : kOob;
-        step = (uint32_t)(BK * g.ldb * 2);
-      }
-    }
-  }
-  // kt: the k-tile whose demand request is being issued
-  __device__ __forceinline__ void issue(rsrc_t ra, rsrc_t rb, char* smem, int wave, int kt, int kend) const {
-    if (!on) return;
-    const int kt2 = kt + kTouchAhead;
-    const bool ok = off != kOob && kt2 * BK < kend;
-    load_lds_4(is_a ? ra : rb, smem + 2 * kStageBytes + wave * 256, ok ? off + (uint32_t)kt2 * step : kOob);
-  }
-};
-
-// acc += A[m0.., k] B[n0.., k] over k-tiles kt0 .. kt1-1.  WGM x WGN waves, each (256/WGM) x (256/WGN);
-// two LDS stages.  Fragments are double-buffered in registers: the reads of k16 step kk+1 (or of the
-// next tile's step 0, after the barrier) are issued before the MFMAs of step kk.  The barrier that
-// ends the reads of tile kt's stage sits before the last step's MFMAs, and the loads of tile kt+2
-// into that stage are issued right there (a whole k-tile ahead of their use) with the wave's
-// priority raised, so that the requests leave before the other wave's arithmetic; they go out after the
-// next tile's first fragment reads (measured: +9..14 % over issuing them at the top of the next iteration).
-// Measured on copies of this loop with parts removed (NT, all 256 CUs busy, per k-tile): MFMAs alone 1.28 us
-// (the chip's power limit on changing operands; 0.96 us on a lone CU), fragment reads +0.08, the barrier +0.12,
-// the loads +0.27 in the compiler's form (most of it the issue slots of their address arithmetic: see TileLoad);
-// the loads have always landed when the barrier is reached (dropping the wait changes nothing), so neither more
-// stages nor an earlier request shorten a k-tile.
-template <bool TA, bool TB, int WGM, int WGN>
-__device__ __forceinline__ void gemm_mainloop(f32x16_t (&acc)[kBM / WGM / 32][kBN / WGN / 32], const GemmArgs& g,
-                                              int m0, int n0, int kt0, int kt1, char* smem, int share) {
-  constexpr int NW = WGM * WGN, WM = kBM / WGM, WN = kBN / WGN, TM = WM / 32, TN = WN / 32, NKK = BK / 16;
+// acc += A[m0.., k] B[n0.., k] over k-tiles kt0 .. kt1-1.
+// A k-tile is four phases, one per quadrant of the wave's outputs; a phase is a memory part (the LDS reads the
+// phase needs, two global->LDS loads) and an arithmetic part (16 MFMAs, 256 cycles), with a barrier after each.  The
+// second group of waves enters one barrier later, so that on every SIMD one wave computes while the other reads and
+// requests: neither the requests' issue slots nor the reads' latency idle the matrix cores.  Bound by MFMA issue and the
+// clock that power allows.  Measured against the form in which all eight waves were in the same part at a time (same
+// box, random operands, TFLOP/s): NT 8192^3 1462 -> 1607, NN 1429 -> 1600, NN 2048 x 25600 x 12800 1372 -> 1535, NN
+// 2048 x 12288 x 1536 1009 -> 1151, TN 8192^3 1313 -> 1403.  Touching the panels' lines of a later k-tile into L2 gained
+// 7-12 % there and costs 2-3 % here: a request now has six phases (1.5 k-tiles) to land.
+//   phase:     0             1             2             3
+//   reads      A0(t)         B1(t)         A1(t)         B0(t+1)      (fragments)
+//   requests   A1(t+1)       B0(t+2)       A0(t+2)       B1(t+2)      (half-tiles)
+//   computes   A0 x B0       A0 x B1       A1 x B1       A1 x B0
+// A half-tile is requested one phase after the phase in which every wave has finished reading its predecessor (two
+// tiles older, same place) and is read six phases later; the wait in front of that read leaves the ten younger loads
+// in flight (vmcnt counts loads in order), so the queue never drains inside the loop.
+template <bool TA, bool TB>
+__device__ __forceinline__ void gemm_mainloop(TileAcc& acc, const GemmArgs& g, int m0, int n0, int kt0, int kt1, char* smem) {
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;   // wave-uniform: LDS bases and M0 values stay in scalar registers
-  const int wm0 = (wave / WGN) * WM, wn0 = (wave % WGN) * WN;
   // buffer descriptors start at the block's first row so that lane offsets stay small
   const bf16_t* a_base = TA ? g.A + m0 : g.A + (size_t)m0 * g.lda;
   const bf16_t* b_base = TB ? g.B + n0 : g.B + (size_t)n0 * g.ldb;
@@ -344,369 +249,254 @@ __device__ __forceinline__ void gemm_mainloop(f32x16_t (&acc)[kBM / WGM / 32][kB
   const rsrc_t rb = make_rsrc(b_base, (uint32_t)(b_left < 0x7fffffffu ? b_left : 0x7fffffffu));
   const int kend = min(g.K, kt1 * BK);  // k-tiles from kt1 on read as zeros
 
-  TileLoad<TA, NW> la;
-  TileLoad<TB, NW> lb;
+  HalfLoad<TA> la;
+  HalfLoad<TB> lb;
   la.init(g.lda, g.M - m0, wave, lane);
   lb.init(g.ldb, g.N - n0, wave, lane);
-  PanelTouch<TA, TB> touch;
-  touch.init(g, m0, n0, share, wave, lane);
+  FragRead<TA, 4> fa;
+  FragRead<TB, 2> fb;
+  fa.init(smem, (wave >> 2) * 64, lane);
+  fb.init(smem, (wave & 3) * 32, lane);
+  // byte offsets of the half-tiles in a stage: A0, A1, B0, B1
+  constexpr int kA0 = 0, kA1 = kHalfBytes, kB0 = 2 * kHalfBytes, kB1 = 3 * kHalfBytes;
 
-  __syncthreads();  // LDS may still be read by a slower wave of the previous tile
-  la.issue(ra, smem, wave, lane, kt0, kend);
-  lb.issue(rb, smem + kTileBytes, wave, lane, kt0, kend);
-  wait_vmcnt0();
-  __syncthreads();
+  // the requests of the phases before phase 0 of the first tile, in the loop's order
+  lb.template issue<0, false>(rb, smem + kB0, wave, kt0, kend);
+  la.template issue<0, false>(ra, smem + kA0, wave, kt0, kend);
+  lb.template issue<1, false>(rb, smem + kB1, wave, kt0, kend);
+  la.template issue<1, false>(ra, smem + kA1, wave, kt0, kend);
+  lb.template issue<0, false>(rb, smem + kStageBytes + kB0, wave, kt0 + 1, kend);
+  la.template issue<0, false>(ra, smem + kStageBytes + kA0, wave, kt0 + 1, kend);
+  lb.template issue<1, false>(rb, smem + kStageBytes + kB1, wave, kt0 + 1, kend);
 
-  bf16x8_t af[2][TM], bfr[2][TN];
+  auto barrier = [] {
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("s_barrier" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  auto wait_loads = [] { asm volatile("s_waitcnt vmcnt(10)" ::: "memory"); };
+  auto wait_reads = [] { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); };
+
+  bf16x8_t af[4][2], bfr[2][2][2];   // bfr[t & 1] holds B0 of tile t, the other set B1 and then B0 of tile t+1
+  wait_loads();
+  barrier();
 #pragma unroll
-  for (int i = 0; i < TM; ++i) af[0][i] = read_frag<TA>(smem, wm0 + i * 32, 0, lane);
+  for (int j = 0; j < 2; ++j)
 #pragma unroll
-  for (int j = 0; j < TN; ++j) bfr[0][j] = read_frag<TB>(smem + kTileBytes, wn0 + j * 32, 0, lane);
+    for (int ks = 0; ks < 2; ++ks) bfr[0][j][ks] = fb.template get<0>(kB0, j, ks);
+  if (wave >= 4) barrier();   // the second group runs one part behind the first
 
-  auto request = [&](char* stage, int kt) {
+  auto compute = [&](f32x4_t (&c)[4][2], const bf16x8_t (&b)[2][2]) {
     __builtin_amdgcn_s_setprio(1);
-    la.issue(ra, stage, wave, lane, kt, kend);
-    lb.issue(rb, stage + kTileBytes, wave, lane, kt, kend);
-    touch.issue(ra, rb, smem, wave, kt, kend);
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) c[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[j][ks], af[i][ks], c[i][j], 0, 0, 0);
     __builtin_amdgcn_s_setprio(0);
   };
-  request(smem + kStageBytes, kt0 + 1);
-  for (int kt = kt0; kt < kt1; ++kt) {
-    char* cur = smem + ((kt - kt0) & 1) * kStageBytes;
-    char* nxt = smem + ((kt - kt0 + 1) & 1) * kStageBytes;
+  auto tile = [&](auto parity, auto lean, int t) {
+    constexpr int S = decltype(parity)::value, O = S ^ 1;
+    constexpr bool LEAN = decltype(lean)::value;
+    char* own = smem + S * kStageBytes;
+    char* other = smem + O * kStageBytes;
+    // phase 0
 #pragma unroll
-    for (int kk = 0; kk < NKK; ++kk) {
-      const int c = kk & 1, n = c ^ 1;
-      if (kk + 1 < NKK) {
+    for (int i = 0; i < 4; ++i)
 #pragma unroll
-        for (int i = 0; i < TM; ++i) af[n][i] = read_frag<TA>(cur, wm0 + i * 32, kk + 1, lane);
+      for (int ks = 0; ks < 2; ++ks) af[i][ks] = fa.template get<S>(kA0, i, ks);
+    la.template issue<1, LEAN>(ra, other + kA1, wave, t + 1, kend);
+    wait_loads();
+    barrier();
+    compute(acc[0][0], bfr[S]);
+    barrier();
+    // phase 1
 #pragma unroll
-        for (int j = 0; j < TN; ++j) bfr[n][j] = read_frag<TB>(cur + kTileBytes, wn0 + j * 32, kk + 1, lane);
-      } else {
-        // every fragment of `cur` is in registers: the next tile may be consumed, `cur` may be refilled
-        wait_vmcnt0();
-        __syncthreads();
+    for (int j = 0; j < 2; ++j)
 #pragma unroll
-        for (int i = 0; i < TM; ++i) af[n][i] = read_frag<TA>(nxt, wm0 + i * 32, 0, lane);
+      for (int ks = 0; ks < 2; ++ks) bfr[O][j][ks] = fb.template get<S>(kB1, j, ks);
+    lb.template issue<0, LEAN>(rb, own + kB0, wave, t + 2, kend);
+    wait_loads();
+    barrier();
+    compute(acc[0][1], bfr[O]);
+    barrier();
+    // phase 2
 #pragma unroll
-        for (int j = 0; j < TN; ++j) bfr[n][j] = read_frag<TB>(nxt + kTileBytes, wn0 + j * 32, 0, lane);
-        // the refill goes out after the next tile's first fragment reads (ahead of them: data gradients 1-2 % slower,
-        // the others the same); nothing is requested past the last tile: no load may be in flight when the epilogue
-        // reuses LDS
-        if (kt + 2 < kt1) request(cur, kt + 2);
-      }
+    for (int i = 0; i < 4; ++i)
 #pragma unroll
-      for (int i = 0; i < TM; ++i)
+      for (int ks = 0; ks < 2; ++ks) af[i][ks] = fa.template get<S>(kA1, i, ks);
+    la.template issue<0, LEAN>(ra, own + kA0, wave, t + 2, kend);
+    wait_loads();
+    barrier();
+    compute(acc[1][1], bfr[O]);
+    barrier();
+    // phase 3: its reads are used in the next tile's phase 0, but have to be complete by this phase's end (the place
+    // is refilled from the next tile's phase 1 on)
 #pragma unroll
-        for (int j = 0; j < TN; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[c][i], bfr[c][j], acc[i][j], 0, 0, 0);
-      // Scheduling hint: spread this step's LDS reads between its MFMAs instead of ahead of them (measured:
-      // +2..5 % with two 16-byte reads per two MFMAs when both operands are k-contiguous, +1 % one to one
-      // when B needs transposing reads; when both do - the weight gradients, 12 eight-byte reads for 8 MFMAs -
-      // three reads after each of the first four MFMAs: +1.5..2 % at the 1T-shaped layer's shapes, +4 % at w_o's;
-      // two after each is slower, four the same, six or all twelve up front slower again).
-      if (!TA) {
-        constexpr int per = TB ? 1 : 2;
+    for (int j = 0; j < 2; ++j)
 #pragma unroll
-        for (int q = 0; q < TM * TN / per; ++q) {
-          __builtin_amdgcn_sched_group_barrier(0x008, per, 0);   // MFMA
-          __builtin_amdgcn_sched_group_barrier(0x100, per, 0);   // LDS read
-        }
-      } else {
-#pragma unroll
-        for (int q = 0; q < TM * TN; ++q) {
-          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);   // MFMA
-          __builtin_amdgcn_sched_group_barrier(0x100, 3, 0);   // LDS reads
-        }
-      }
+      for (int ks = 0; ks < 2; ++ks) bfr[O][j][ks] = fb.template get<O>(kB0, j, ks);
+    lb.template issue<1, LEAN>(rb, own + kB1, wave, t + 2, kend);
+    wait_loads();
+    barrier();
+    wait_reads();
+    compute(acc[1][0], bfr[S]);
+    barrier();
+  };
+  constexpr std::integral_constant<int, 0> even{};
+  constexpr std::integral_constant<int, 1> odd{};
+  int t = kt0;
+  if (la.plain && lb.plain)
+    for (; (t + 4) * BK <= kend; t += 2) {   // every tile requested here (up to t + 3) lies inside K whole
+      tile(even, std::true_type{}, t);
+      tile(odd, std::true_type{}, t + 1);
     }
+  for (; t + 1 < kt1; t += 2) {
+    tile(even, std::false_type{}, t);
+    tile(odd, std::false_type{}, t + 1);
   }
+  if (t < kt1) tile(even, std::false_type{}, t);
+  if (wave < 4) barrier();
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the requests past the last k-tile (zeros) have landed
 }
 
-// Output forms.  32x32 accumulator layout: lane holds column (lane & 31), rows 8*(r/4) + 4*(lane/32) + r%4.
-//   Each wave passes its 32-row slabs through its own LDS patch
-//     (the operand stages are free by then) and leaves with 16 consecutive lanes covering one 256-byte
-//     row segment: 16-byte fp32 or 8-byte bf16 accesses instead of scalar ones.
+// Output forms.
 enum { OUT_BF16 = 0, OUT_F32_STORE = 1, OUT_F32_RMW = 2 };
-constexpr int kEpiStride = 72;  // floats per staged row of 64: rows 4 apart land 32 banks apart
-constexpr int kEpiStride16 = 68;  // 16x16 blocks: a store covers rows 0, 4, 8, 12 of a block, which land 16 banks apart
+constexpr size_t kWideRow = (size_t)1 << 23;   // bytes; rows of C from here on take 64-bit addresses
 
-template <int OUT, int WGM, int WGN>
-__device__ __forceinline__ void gemm_epilogue(const f32x16_t (&acc)[kBM / WGM / 32][kBN / WGN / 32], void* Cv, size_t ldc,
-                                              const bf16_t* bias, int M, int N, int m0, int n0, char* smem) {
-  constexpr int WM = kBM / WGM, WN = kBN / WGN, TM = WM / 32, TN = WN / 32;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;   // wave-uniform: LDS bases and M0 values stay in scalar registers
-  const int wm0 = (wave / WGN) * WM, wn0 = (wave % WGN) * WN;
-  static_assert(WN == 64, "staging patch is 32 rows x 64 columns per wave");
-  float* patch = reinterpret_cast<float*>(smem) + wave * (32 * kEpiStride);
-  float bv[TN];
+// Lane-to-memory mapping: with four consecutive columns per lane a block's store would cover 16 rows x 64 bytes (fp32)
+// or 32 bytes (bf16) of each.  bf16: the two column blocks of a 32-column group change lanes (v_permlane16_swap) so
+// that a lane ends up with eight consecutive columns (16 bytes).  fp32: lanes of rows 0-7 and 8-15 change halves (a
+// rotation by 8 inside 16 lanes) so that an access covers 8 rows x 128 bytes: whole lines, which the read-modify-write
+// of the weight gradients needs (25600 x 12800 x 2048: 1431 us with 64-byte segments, 1315 us with whole lines; 1368 us
+// with rows staged through LDS).  All accesses to C go through a buffer descriptor that ends behind the tile's last
+// row (columns past N: an offset beyond it), so the stage is free of branches.
+template <int OUT>
+__device__ __forceinline__ void gemm_epilogue(const TileAcc& acc, void* Cv, size_t ldc, const bf16_t* bias, int M, int N, int m0,
+                                              int n0) {
+  typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
+  typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
+  constexpr uint32_t esz = OUT == OUT_BF16 ? 2 : 4;
+  constexpr int kAux = OUT == OUT_F32_RMW ? 2 : 0;   // gradient accumulators are touched once per launch: non-temporal
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int wm = (wave >> 2) * 64, wn = (wave & 3) * 32, l15 = lane & 15, q = lane >> 4;
+  float bv[2][2][4];
 #pragma unroll
-  for (int j = 0; j < TN; ++j) {
-    const int n = n0 + wn0 + j * 32 + (lane & 31);
-    bv[j] = (bias && n < N) ? bf16_to_f32(bias[n]) : 0.f;
-  }
-  const int c4 = (lane & 15) * 4;            // first of this lane's 4 columns inside the wave's 64
-  const int n = n0 + wn0 + c4;
-  // Gradient accumulators are touched once per launch: stream them past the caches.  The old values of
-  // slab i + 1 are requested before slab i is staged and added, so two slabs of loads are in flight.
-  f32x4_t old[2][8];
-  auto fetch_old = [&](int i, f32x4_t (&dst)[8]) {
+  for (int hb = 0; hb < 2; ++hb)
 #pragma unroll
-    for (int it = 0; it < 8; ++it) {
-      const int m = m0 + wm0 + i * 32 + it * 4 + (lane >> 4);
-      if (m < M && n < N)
-        dst[it] = __builtin_nontemporal_load(reinterpret_cast<const f32x4_t*>(reinterpret_cast<float*>(Cv) + (size_t)m * ldc + n));
+    for (int j = 0; j < 2; ++j) {
+      const int n = n0 + hb * 128 + wn + j * 16 + 4 * q;
+      uint2 w = make_uint2(0u, 0u);
+      if (bias && n < N) w = *reinterpret_cast<const uint2*>(bias + n);
+      bv[hb][j][0] = __uint_as_float(w.x << 16); bv[hb][j][1] = __uint_as_float(w.x & 0xffff0000u);
+      bv[hb][j][2] = __uint_as_float(w.y << 16); bv[hb][j][3] = __uint_as_float(w.y & 0xffff0000u);
     }
-  };
-  if (OUT == OUT_F32_RMW) fetch_old(0, old[0]);
+  if (ldc >= kWideRow / esz) {   // byte offsets inside a tile would not fit 31 bits: plain 64-bit addresses
 #pragma unroll
-  for (int i = 0; i < TM; ++i) {
-    if (OUT == OUT_F32_RMW && i + 1 < TM) fetch_old(i + 1, old[(i + 1) & 1]);
+    for (int b = 0; b < 4; ++b)
 #pragma unroll
-    for (int j = 0; j < TN; ++j)
+      for (int i = 0; i < 4; ++i)
 #pragma unroll
-      for (int r = 0; r < 16; ++r)
-        patch[(8 * (r >> 2) + 4 * (lane >> 5) + (r & 3)) * kEpiStride + j * 32 + (lane & 31)] = acc[i][j][r] + bv[j];
-    __builtin_amdgcn_wave_barrier();
+        for (int j = 0; j < 2; ++j) {
+          const int m = m0 + (b >> 1) * 128 + wm + i * 16 + l15, n = n0 + (b & 1) * 128 + wn + j * 16 + 4 * q;
+          if (m >= M || n >= N) continue;
+          const size_t at = (size_t)m * ldc + n;
 #pragma unroll
-    for (int it = 0; it < 8; ++it) {
-      const int row = it * 4 + (lane >> 4);
-      const int m = m0 + wm0 + i * 32 + row;
-      const float4 v = *reinterpret_cast<const float4*>(patch + row * kEpiStride + c4);
-      if (m < M && n < N) {
-        if (OUT == OUT_BF16) {
-          uint2 o;
-          o.x = pack_bf16x2(v.x, v.y);
-          o.y = pack_bf16x2(v.z, v.w);
-          *reinterpret_cast<uint2*>(reinterpret_cast<bf16_t*>(Cv) + (size_t)m * ldc + n) = o;
-        } else if (OUT == OUT_F32_RMW) {
-          f32x4_t o = old[i & 1][it];
-          o[0] += v.x; o[1] += v.y; o[2] += v.z; o[3] += v.w;
-          __builtin_nontemporal_store(o, reinterpret_cast<f32x4_t*>(reinterpret_cast<float*>(Cv) + (size_t)m * ldc + n));
-        } else {
-          *reinterpret_cast<float4*>(reinterpret_cast<float*>(Cv) + (size_t)m * ldc + n) = v;
+          for (int r = 0; r < 4; ++r) {
+            const float v = acc[b >> 1][b & 1][i][j][r] + bv[b & 1][j][r];
+            if (OUT == OUT_BF16) reinterpret_cast<bf16_t*>(Cv)[at + r] = f32_to_bf16(v);
+            else if (OUT == OUT_F32_RMW) reinterpret_cast<float*>(Cv)[at + r] += v;
+            else reinterpret_cast<float*>(Cv)[at + r] = v;
+          }
         }
-      }
-    }
-    __builtin_amdgcn_wave_barrier();
+    return;
   }
-}
-
-template <int TM, int TN> __device__ __forceinline__ void zero_acc(f32x16_t (&acc)[TM][TN]) {
+  char* origin = reinterpret_cast<char*>(Cv) + ((size_t)m0 * ldc + n0) * esz;
+  const uint32_t pitch = (uint32_t)ldc * esz, records = (uint32_t)(min(kBM, M - m0) - 1) * pitch + (uint32_t)min(kBN, N - n0) * esz;
+  const auto rc = __builtin_amdgcn_make_buffer_rsrc(origin, 0, records, 0x00020000);
+  if (OUT == OUT_BF16) {
+    const int c8 = 16 * (q & 1) + 8 * (q >> 1);   // first of this lane's 8 columns after the exchange
 #pragma unroll
-  for (int i = 0; i < TM; ++i)
+    for (int hb = 0; hb < 2; ++hb) {
+      const int col = hb * 128 + wn + c8;
+      const uint32_t off = n0 + col < N ? (uint32_t)(wm + l15) * pitch + col * esz : kOob;
 #pragma unroll
-    for (int j = 0; j < TN; ++j)
+      for (int ha = 0; ha < 2; ++ha)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-}
-
-// ---- the same main loop and output stage on v_mfma_f32_16x16x32_bf16 -------------------------------------------
-// On operands that change from instruction to instruction the chip sustains about a tenth more with this
-// shape than with 32x32x16 (a register-resident loop: 2.08-2.13 against 1.89 PFLOP/s on random operands; both
-// reach 2.46 on constant ones): a 16x16 accumulator block is read and written half as often per FLOP.  Measured
-// in the kernel: +4..6 % where operand A is k-contiguous (forward, data gradients), -3..6 % for the weight
-// gradients at K = 2048, which therefore stay on 32x32x16.
-template <bool TA, bool TB, int WGM, int WGN>
-__device__ __forceinline__ void gemm_mainloop16(f32x4_t (&acc)[kBM / WGM / 16][kBN / WGN / 16], const GemmArgs& g,
-                                              int m0, int n0, int kt0, int kt1, char* smem, int share) {
-  constexpr int NW = WGM * WGN, WM = kBM / WGM, WN = kBN / WGN, RB = WM / 16, CB = WN / 16;
-  static_assert(RB == 8 && CB == 4, "four phases per k-tile: two k32 steps x two halves of the wave's 8 row blocks");
-  constexpr int HB = RB / 2;   // row blocks per phase
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;   // wave-uniform: LDS bases and M0 values stay in scalar registers
-  const int wm0 = (wave / WGN) * WM, wn0 = (wave % WGN) * WN;
-  // buffer descriptors start at the block's first row so that lane offsets stay small
-  const bf16_t* a_base = TA ? g.A + m0 : g.A + (size_t)m0 * g.lda;
-  const bf16_t* b_base = TB ? g.B + n0 : g.B + (size_t)n0 * g.ldb;
-  const size_t a_left = (size_t)(g.a_end - reinterpret_cast<const char*>(a_base));
-  const size_t b_left = (size_t)(g.b_end - reinterpret_cast<const char*>(b_base));
-  const rsrc_t ra = make_rsrc(a_base, (uint32_t)(a_left < 0x7fffffffu ? a_left : 0x7fffffffu));
-  const rsrc_t rb = make_rsrc(b_base, (uint32_t)(b_left < 0x7fffffffu ? b_left : 0x7fffffffu));
-  const int kend = min(g.K, kt1 * BK);  // k-tiles from kt1 on read as zeros
-
-  TileLoad<TA, NW> la;
-  TileLoad<TB, NW> lb;
-  la.init(g.lda, g.M - m0, wave, lane);
-  lb.init(g.ldb, g.N - n0, wave, lane);
-  PanelTouch<TA, TB> touch;
-  touch.init(g, m0, n0, share, wave, lane);
-
-  __syncthreads();  // LDS may still be read by a slower wave of the previous tile
-  la.issue(ra, smem, wave, lane, kt0, kend);
-  lb.issue(rb, smem + kTileBytes, wave, lane, kt0, kend);
-  wait_vmcnt0();
-  __syncthreads();
-
-  // phase p = 2 * ks + half: the MFMAs of row blocks half*4 .. half*4+3 against all four column blocks at k32 step ks
-  bf16x8_t af[2][HB], bfr[2][CB];
+        for (int i = 0; i < 4; ++i) {
+          uint32_t p[2][2];
 #pragma unroll
-  for (int i = 0; i < HB; ++i) af[0][i] = read_frag16<TA>(smem, wm0 + i * 16, 0, lane);
-#pragma unroll
-  for (int j = 0; j < CB; ++j) bfr[0][j] = read_frag16<TB>(smem + kTileBytes, wn0 + j * 16, 0, lane);
-
-  // A stage is refilled in three instalments - operand A (and the touches) right behind the barrier that frees it,
-  // the two halves of operand B at the start of the next tile's phases 0 and 1 - so that a wave's eight loads do
-  // not queue up behind each other and the seven other waves' (measured against all eight at the barrier: data
-  // gradients +1.5..2.5 %, forward +1 %, -1.5 % at K = 3200; bit-equal).
-  auto request_a = [&](char* stage, int kt) {
-    __builtin_amdgcn_s_setprio(1);
-    la.issue(ra, stage, wave, lane, kt, kend);
-    touch.issue(ra, rb, smem, wave, kt, kend);
-    __builtin_amdgcn_s_setprio(0);
-  };
-  auto request_b = [&](char* stage, int kt, auto half) {
-    __builtin_amdgcn_s_setprio(1);
-    lb.template issue_half<decltype(half)::value>(rb, stage + kTileBytes, wave, lane, kt, kend);
-    __builtin_amdgcn_s_setprio(0);
-  };
-  request_a(smem + kStageBytes, kt0 + 1);
-  lb.issue(rb, smem + kStageBytes + kTileBytes, wave, lane, kt0 + 1, kend);
-  for (int kt = kt0; kt < kt1; ++kt) {
-    char* cur = smem + ((kt - kt0) & 1) * kStageBytes;
-    char* nxt = smem + ((kt - kt0 + 1) & 1) * kStageBytes;
-#pragma unroll
-    for (int p = 0; p < 4; ++p) {
-      const int ks = p >> 1, half = p & 1;
-      if (p == 0 && kt > kt0 && kt + 1 < kt1) request_b(nxt, kt + 1, std::integral_constant<int, 0>{});
-      if (p == 1 && kt > kt0 && kt + 1 < kt1) request_b(nxt, kt + 1, std::integral_constant<int, 1>{});
-      if (p < 3) {
-        const int q = p + 1, qs = q >> 1, qh = q & 1;
-#pragma unroll
-        for (int i = 0; i < HB; ++i) af[q & 1][i] = read_frag16<TA>(cur, wm0 + (qh * HB + i) * 16, qs, lane);
-        if (qh == 0) {
-#pragma unroll
-          for (int j = 0; j < CB; ++j) bfr[qs & 1][j] = read_frag16<TB>(cur + kTileBytes, wn0 + j * 16, qs, lane);
+          for (int j = 0; j < 2; ++j) {
+            const f32x4_t v = acc[ha][hb][i][j];
+            p[j][0] = pack_bf16x2(v[0] + bv[hb][j][0], v[1] + bv[hb][j][1]);
+            p[j][1] = pack_bf16x2(v[2] + bv[hb][j][2], v[3] + bv[hb][j][3]);
+          }
+          const u32x2_t x = __builtin_amdgcn_permlane16_swap(p[0][0], p[1][0], false, false);
+          const u32x2_t y = __builtin_amdgcn_permlane16_swap(p[0][1], p[1][1], false, false);
+          __builtin_amdgcn_raw_buffer_store_b128(u32x4_t{x[0], y[0], x[1], y[1]}, rc, off + (ha * 128 + i * 16) * pitch, 0, 0);
         }
-      } else {
-        // every fragment of `cur` is in registers: the next tile may be consumed, `cur` may be refilled
-        wait_vmcnt0();
-        __syncthreads();
+    }
+  } else {
+    const bool low = l15 < 8;
+    uint32_t off[2];   // after the exchange: rows l15 & 7 (+ 8 for the second access), columns 16 * (l15 / 8) + 4 * q of 32
 #pragma unroll
-        for (int i = 0; i < HB; ++i) af[0][i] = read_frag16<TA>(nxt, wm0 + i * 16, 0, lane);
+    for (int hb = 0; hb < 2; ++hb) {
+      const int col = hb * 128 + wn + (l15 >> 3) * 16 + 4 * q;
+      off[hb] = n0 + col < N ? (uint32_t)(wm + (l15 & 7)) * pitch + col * esz : kOob;
+    }
+    auto at = [&](int b, int i, int half) { return off[b & 1] + ((b >> 1) * 128 + i * 16 + half * 8) * pitch; };
+    // the old values of the next quadrant are requested before the current one is added: two batches of loads in flight
+    u32x4_t old[2][8];
+    auto fetch_old = [&](int b) {
 #pragma unroll
-        for (int j = 0; j < CB; ++j) bfr[0][j] = read_frag16<TB>(nxt + kTileBytes, wn0 + j * 16, 0, lane);
-        // the refill goes out after the next tile's first fragment reads (ahead of them: data gradients 1-2 % slower,
-        // the others the same); nothing is requested past the last tile: no load may be in flight when the epilogue
-        // reuses LDS
-        if (kt + 2 < kt1) request_a(cur, kt + 2);
-      }
+      for (int i = 0; i < 8; ++i) old[b & 1][i] = __builtin_amdgcn_raw_buffer_load_b128(rc, at(b, i >> 1, i & 1), 0, kAux);
+    };
+    if (OUT == OUT_F32_RMW) fetch_old(0);
 #pragma unroll
-      for (int i = 0; i < HB; ++i)
+    for (int b = 0; b < 4; ++b) {
+      if (OUT == OUT_F32_RMW && b + 1 < 4) fetch_old(b + 1);
 #pragma unroll
-        for (int j = 0; j < CB; ++j)
-          acc[half * HB + i][j] =
-              __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[p & 1][i], bfr[ks & 1][j], acc[half * HB + i][j], 0, 0, 0);
-      // Scheduling hint: spread this phase's LDS reads (4 to 12, for 16 MFMAs) between its MFMAs instead of ahead
-      // of them, one after each (measured against one after every two: +2..3 % forward, +5 % at K = 3200,
-      // +1.5..2.5 % data gradients)
-      if (!TA) {
+      for (int i = 0; i < 4; ++i) {
+        f32x4_t v[2];
 #pragma unroll
-        for (int q = 0; q < HB * CB; ++q) {
-          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);   // MFMA
-          __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);   // LDS read
+        for (int r = 0; r < 4; ++r) {
+          const float x = acc[b >> 1][b & 1][i][0][r] + bv[b & 1][0][r], y = acc[b >> 1][b & 1][i][1][r] + bv[b & 1][1][r];
+          const float got = __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, low ? y : x), 0x128, 0xf, 0xf, true));   // row_ror:8
+          v[0][r] = low ? x : got;
+          v[1][r] = low ? got : y;
+        }
+#pragma unroll
+        for (int half = 0; half < 2; ++half) {
+          if (OUT == OUT_F32_RMW) v[half] += __builtin_bit_cast(f32x4_t, old[b & 1][i * 2 + half]);
+          __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, v[half]), rc, at(b, i, half), 0, kAux);
         }
       }
     }
   }
-}
-
-template <int OUT, int WGM, int WGN>
-__device__ __forceinline__ void gemm_epilogue16(const f32x4_t (&acc)[kBM / WGM / 16][kBN / WGN / 16], void* Cv, size_t ldc,
-                                              const bf16_t* bias, int M, int N, int m0, int n0, char* smem) {
-  constexpr int WM = kBM / WGM, WN = kBN / WGN, NS = WM / 32, CB = WN / 16;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;   // wave-uniform: LDS bases and M0 values stay in scalar registers
-  const int wm0 = (wave / WGN) * WM, wn0 = (wave % WGN) * WN;
-  static_assert(WN == 64, "staging patch is 32 rows x 64 columns per wave");
-  float* patch = reinterpret_cast<float*>(smem) + wave * (32 * kEpiStride16);
-  float bv[CB];
-#pragma unroll
-  for (int j = 0; j < CB; ++j) {
-    const int n = n0 + wn0 + j * 16 + (lane & 15);
-    bv[j] = (bias && n < N) ? bf16_to_f32(bias[n]) : 0.f;
-  }
-  const int c4 = (lane & 15) * 4;            // first of this lane's 4 columns inside the wave's 64
-  const int n = n0 + wn0 + c4;
-  // Gradient accumulators are touched once per launch: stream them past the caches.  The old values of
-  // slab i + 1 are requested before slab i is staged and added, so two slabs of loads are in flight.
-  f32x4_t old[2][8];
-  auto fetch_old = [&](int i, f32x4_t (&dst)[8]) {
-#pragma unroll
-    for (int it = 0; it < 8; ++it) {
-      const int m = m0 + wm0 + i * 32 + it * 4 + (lane >> 4);
-      if (m < M && n < N)
-        dst[it] = __builtin_nontemporal_load(reinterpret_cast<const f32x4_t*>(reinterpret_cast<float*>(Cv) + (size_t)m * ldc + n));
-    }
-  };
-  if (OUT == OUT_F32_RMW) fetch_old(0, old[0]);
-#pragma unroll
-  for (int i = 0; i < NS; ++i) {
-    if (OUT == OUT_F32_RMW && i + 1 < NS) fetch_old(i + 1, old[(i + 1) & 1]);
-#pragma unroll
-    for (int b = 0; b < 2; ++b)
-#pragma unroll
-      for (int j = 0; j < CB; ++j)
-#pragma unroll
-        for (int r = 0; r < 4; ++r)
-          patch[(16 * b + 4 * (lane >> 4) + r) * kEpiStride16 + j * 16 + (lane & 15)] = acc[2 * i + b][j][r] + bv[j];
-    __builtin_amdgcn_wave_barrier();
-#pragma unroll
-    for (int it = 0; it < 8; ++it) {
-      const int row = it * 4 + (lane >> 4);
-      const int m = m0 + wm0 + i * 32 + row;
-      const float4 v = *reinterpret_cast<const float4*>(patch + row * kEpiStride16 + c4);
-      if (m < M && n < N) {
-        if (OUT == OUT_BF16) {
-          uint2 o;
-          o.x = pack_bf16x2(v.x, v.y);
-          o.y = pack_bf16x2(v.z, v.w);
-          *reinterpret_cast<uint2*>(reinterpret_cast<bf16_t*>(Cv) + (size_t)m * ldc + n) = o;
-        } else if (OUT == OUT_F32_RMW) {
-          f32x4_t o = old[i & 1][it];
-          o[0] += v.x; o[1] += v.y; o[2] += v.z; o[3] += v.w;
-          __builtin_nontemporal_store(o, reinterpret_cast<f32x4_t*>(reinterpret_cast<float*>(Cv) + (size_t)m * ldc + n));
-        } else {
-          *reinterpret_cast<float4*>(reinterpret_cast<float*>(Cv) + (size_t)m * ldc + n) = v;
-        }
-      }
-    }
-    __builtin_amdgcn_wave_barrier();
-  }
-}
-
-template <int TM, int TN> __device__ __forceinline__ void zero_acc(f32x4_t (&acc)[TM][TN]) {
-#pragma unroll
-  for (int i = 0; i < TM; ++i)
-#pragma unroll
-    for (int j = 0; j < TN; ++j)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) acc[i][j][r] = 0.f;
 }
 
 // One 256 x 256 tile over k-tiles kt0 .. kt1-1, written either in the caller's output form (slab == nullptr) or
-// as a dense 256 x 256 fp32 slab.  The MFMA shape follows operand A's layout (see above).
-template <bool TA, bool TB, int OUT, int WGM, int WGN>
-__device__ __forceinline__ void gemm_tile(const GemmArgs& g, void* Cv, float* slab, int m0, int n0, int kt0, int kt1, char* smem,
-                                          int share) {
-  if constexpr (TA) {
-    f32x16_t acc[kBM / WGM / 32][kBN / WGN / 32];
-    zero_acc(acc);
-    if (kt1 > kt0) gemm_mainloop<TA, TB, WGM, WGN>(acc, g, m0, n0, kt0, kt1, smem, share);
-    if (slab) gemm_epilogue<OUT_F32_STORE, WGM, WGN>(acc, slab, kBN, nullptr, kBM, kBN, 0, 0, smem);
-    else gemm_epilogue<OUT, WGM, WGN>(acc, Cv, g.ldc, g.bias, g.M, g.N, m0, n0, smem);
-  } else {
-    f32x4_t acc[kBM / WGM / 16][kBN / WGN / 16];
-    zero_acc(acc);
-    if (kt1 > kt0) gemm_mainloop16<TA, TB, WGM, WGN>(acc, g, m0, n0, kt0, kt1, smem, share);
-    if (slab) gemm_epilogue16<OUT_F32_STORE, WGM, WGN>(acc, slab, kBN, nullptr, kBM, kBN, 0, 0, smem);
-    else gemm_epilogue16<OUT, WGM, WGN>(acc, Cv, g.ldc, g.bias, g.M, g.N, m0, n0, smem);
-  }
+// as a dense 256 x 256 fp32 slab.
+template <bool TA, bool TB, int OUT>
+__device__ __forceinline__ void gemm_tile(const GemmArgs& g, void* Cv, float* slab, int m0, int n0, int kt0, int kt1, char* smem) {
+  TileAcc acc;
+#pragma unroll
+  for (int b = 0; b < 4; ++b)
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) acc[b >> 1][b & 1][i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  if (kt1 > kt0) gemm_mainloop<TA, TB>(acc, g, m0, n0, kt0, kt1, smem);
+  if (slab) gemm_epilogue<OUT_F32_STORE>(acc, slab, kBN, nullptr, kBM, kBN, 0, 0);
+  else gemm_epilogue<OUT>(acc, Cv, g.ldc, g.bias, g.M, g.N, m0, n0);
 }
 
 // One workgroup per output tile ("data-parallel" form); `id` is the workgroup's index inside its problem.
 // Workgroups are dealt round-robin to the 8 XCDs, each with its own L2.  Each XCD owns the column
 // tiles x, x+8, ... and works through them in groups of up to 8 row tiles, so that the
 // workgroups resident on one XCD share 8 A panels and 4 B panels through that L2.
-template <bool TA, bool TB, int OUT, int WGM, int WGN>
+template <bool TA, bool TB, int OUT>
 __device__ __forceinline__ void gemm_dp_tile(const GemmArgs& g, void* Cv, int id, char* smem) {
   const int tiles_m = (g.M + kBM - 1) / kBM, tiles_n = (g.N + kBN - 1) / kBN;
   const int xcd = id & 7, local = id >> 3;
@@ -716,9 +506,7 @@ __device__ __forceinline__ void gemm_dp_tile(const GemmArgs& g, void* Cv, int id
   const int gm = min(8, tiles_m - grp * 8);         // row tiles in this group
   const int tile_m = grp * 8 + in_grp % gm, tile_n = (in_grp / gm) * 8 + xcd;
   if (tile_n >= tiles_n) return;
-  // place among the workgroups that share this tile's panels: row tile within the group of 8, column tile within the round's 4
-  const int share = (in_grp % gm) | (((in_grp / gm) & 3) << 8);
-  gemm_tile<TA, TB, OUT, WGM, WGN>(g, Cv, nullptr, tile_m * kBM, tile_n * kBN, 0, (g.K + BK - 1) / BK, smem, share);
+  gemm_tile<TA, TB, OUT>(g, Cv, nullptr, tile_m * kBM, tile_n * kBN, 0, (g.K + BK - 1) / BK, smem);
 }
 // workgroups of one problem (a multiple of 8, so that a second problem starts on XCD 0 again)
 static inline int dp_blocks(const GemmArgs& g) {
@@ -726,11 +514,11 @@ static inline int dp_blocks(const GemmArgs& g) {
   return 8 * tiles_m * ((tiles_n + 7) / 8);  // 8 XCD queues of equal length; surplus workgroups exit at once
 }
 
-template <bool TA, bool TB, int OUT, int WGM, int WGN>
-__global__ void __launch_bounds__(WGM * WGN * 64)
+template <bool TA, bool TB, int OUT>
+__global__ void __launch_bounds__(kGemmThreads)
 gemm_bf16_dp_kernel(GemmArgs g, void* Cv) {
   extern __shared__ __attribute__((aligned(1024))) char smem[];
-  gemm_dp_tile<TA, TB, OUT, WGM, WGN>(g, Cv, blockIdx.x, smem);
+  gemm_dp_tile<TA, TB, OUT>(g, Cv, blockIdx.x, smem);
 }
 
 // Up to four independent problems of the same form in one launch: each later problem's tiles fill the CUs that the
@@ -743,8 +531,8 @@ struct MultiArgs {
   int start[kMaxMulti + 1];
   int n;
 };
-template <bool TA, bool TB, int OUT, int WGM, int WGN>
-__global__ void __launch_bounds__(WGM * WGN * 64)
+template <bool TA, bool TB, int OUT>
+__global__ void __launch_bounds__(kGemmThreads)
 gemm_bf16_dp_multi_kernel(MultiArgs a) {
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   const int id = (int)blockIdx.x;
@@ -759,7 +547,7 @@ gemm_bf16_dp_multi_kernel(MultiArgs a) {
       C = a.C[q];
       first = a.start[q];
     }
-  gemm_dp_tile<TA, TB, OUT, WGM, WGN>(g, C, id - first, smem);
+  gemm_dp_tile<TA, TB, OUT>(g, C, id - first, smem);
 }
 
 // Remainder form, for the tiles that do not fill a whole round of the machine.  The remaining tiles are cut into
@@ -787,8 +575,8 @@ struct SplitGroups {
 };
 static inline int split_blocks(int tiles, int parts) { return 8 * ((tiles * parts + 7) / 8); }   // 8 XCD queues of equal length
 
-template <bool TA, bool TB, int OUT, int WGM, int WGN>
-__global__ void __launch_bounds__(WGM * WGN * 64)
+template <bool TA, bool TB, int OUT>
+__global__ void __launch_bounds__(kGemmThreads)
 gemm_bf16_split_kernel(GemmArgs g, void* Cv, float* slabs, SplitGroups sg) {
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   int j = 0;
@@ -805,11 +593,7 @@ gemm_bf16_split_kernel(GemmArgs g, void* Cv, float* slabs, SplitGroups sg) {
   const int m0 = (tile % tiles_m) * kBM, n0 = (tile / tiles_m) * kBN;
   const int nk = (g.K + BK - 1) / BK;
   const int kt0 = (int)((long long)nk * part / parts), kt1 = (int)((long long)nk * (part + 1) / parts);
-  // an XCD's run of units is a run of neighbouring tiles of one part: with 8 row tiles that is 8 x 4 tiles on the same
-  // k range, the sharing pattern of a whole round (other row counts: the touches cover the panels only in part)
-  const int share = ((tile % tiles_m) & 7) | (((tile / tiles_m) & 3) << 8);
-  gemm_tile<TA, TB, OUT, WGM, WGN>(g, Cv, parts == 1 ? nullptr : slabs + (size_t)(sg.slab0[j] + unit) * kSlabFloats, m0, n0, kt0, kt1,
-                                   smem, share);
+  gemm_tile<TA, TB, OUT>(g, Cv, parts == 1 ? nullptr : slabs + (size_t)(sg.slab0[j] + unit) * kSlabFloats, m0, n0, kt0, kt1, smem);
 }
 
 // One workgroup per (tile of a split group, 16-row band): sums the tile's slabs in part order and writes
@@ -861,11 +645,9 @@ gemm_split_reduce_kernel(const float* __restrict__ slabs, void* Cv, const bf16_t
   }
 }
 
-constexpr int kWGM = 2, kWGN = 4, kGemmThreads = kWGM * kWGN * 64, kGemmSmem = 2 * kStageBytes + kTouchLdsBytes;
-
 template <bool TA, bool TB, int OUT>
 static int launch_dp(const GemmArgs& g, void* C, hipStream_t st) {
-  auto kern = gemm_bf16_dp_kernel<TA, TB, OUT, kWGM, kWGN>;
+  auto kern = gemm_bf16_dp_kernel<TA, TB, OUT>;
   static once_flag_t done[kMaxDevices];
   if (set_dynamic_smem(reinterpret_cast<const void*>(kern), kGemmSmem, done) != PTDP_OK) return PTDP_E_HIP;
   hipLaunchKernelGGL(kern, dim3(dp_blocks(g)), dim3(kGemmThreads), kGemmSmem, st, g, C);
@@ -874,7 +656,7 @@ static int launch_dp(const GemmArgs& g, void* C, hipStream_t st) {
 
 template <bool TA, bool TB, int OUT>
 static int launch_split(const GemmArgs& g, void* C, float* slabs, const SplitGroups& sg, int blocks, hipStream_t st) {
-  auto kern = gemm_bf16_split_kernel<TA, TB, OUT, kWGM, kWGN>;
+  auto kern = gemm_bf16_split_kernel<TA, TB, OUT>;
   static once_flag_t done[kMaxDevices];
   if (set_dynamic_smem(reinterpret_cast<const void*>(kern), kGemmSmem, done) != PTDP_OK) return PTDP_E_HIP;
   hipLaunchKernelGGL(kern, dim3(blocks), dim3(kGemmThreads), kGemmSmem, st, g, C, slabs, sg);
@@ -1084,7 +866,7 @@ int launch_gemm_tn_multi(int dtype, int n, const void* const* A, const void* con
     if (j < n) at += dp_blocks(a.g[j]);
   }
   a.start[kMaxMulti] = at;
-  auto kern = gemm_bf16_dp_multi_kernel<true, true, OUT_F32_RMW, kWGM, kWGN>;
+  auto kern = gemm_bf16_dp_multi_kernel<true, true, OUT_F32_RMW>;
   static once_flag_t done[kMaxDevices];
   if (set_dynamic_smem(reinterpret_cast<const void*>(kern), kGemmSmem, done) != PTDP_OK) return PTDP_E_HIP;
   hipLaunchKernelGGL(kern, dim3(at), dim3(kGemmThreads), kGemmSmem, st, a);

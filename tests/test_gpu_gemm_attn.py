@@ -38,6 +38,46 @@ def test_gemm(dtype, mode, M, N, K):
 
 
 @pytest.mark.parametrize("mode", [B.GEMM_NN, B.GEMM_NT, B.GEMM_TN])
+@pytest.mark.parametrize("nk", [1, 2, 3, 4, 5, 6, 7, 8])
+@pytest.mark.parametrize("tail", [0, 8, 56])
+def test_gemm_every_short_pipeline(mode, nk, tail):
+    """1 to 8 whole k-tiles of 64, with and without a partial one: every way into and out of the request pipeline
+    (whose loads run 1.5 k-tiles ahead), with the last tile even and odd."""
+    M, N, K = 264, 264, nk * 64 + tail
+    a = randn((M, K), B.BF16, 1)
+    b = randn((K, N), B.BF16, 2)
+    A = a.t().contiguous() if mode == B.GEMM_TN else a
+    Bm = b.t().contiguous() if mode == B.GEMM_NT else b
+    c = torch.full((M, N), 9.0, dtype=torch.bfloat16, device="cuda")
+    acc = torch.full((M, N), 0.25, dtype=torch.float32, device="cuda")
+    B.check(B.ptdp_gemm(B.BF16, mode, A.data_ptr(), Bm.data_ptr(), c.data_ptr(), None, M, N, K, 0, 0, None, 0, stream()), "gemm")
+    B.check(B.ptdp_gemm(B.BF16, mode, A.data_ptr(), Bm.data_ptr(), acc.data_ptr(), None, M, N, K, 1, 1, None, 0, stream()), "gemm")
+    sync()
+    want = np64(a) @ np64(b)
+    # K products of size <= 1 rounded in fp32 sums: 1e-5 of the result's RMS is 25 times what K = 568 terms give
+    assert_close(np64(acc) - 0.25, want, B.F32, "C +=")
+    assert_close(np64(c), want, B.BF16, "C", 0.2)
+
+
+@pytest.mark.parametrize("out_f32,accumulate", [(0, 0), (1, 0), (1, 1)])
+@pytest.mark.parametrize("N", [(1 << 21) - 8, (1 << 21) + 8, (1 << 22) + 8])
+def test_gemm_rows_of_c_beyond_31_bit_offsets(out_f32, accumulate, N):
+    """Rows of C of 8 MiB and more (fp32: 2^21 columns, bf16: 2^22) take 64-bit addresses inside a tile."""
+    M, K = 24, 8
+    a = randn((M, K), B.BF16, 1)
+    b = randn((K, N), B.BF16, 2)
+    bias = randn((N,), B.BF16, 3)
+    c = torch.full((M, N), 2.0, dtype=torch.float32 if out_f32 else torch.bfloat16, device="cuda")
+    B.check(B.ptdp_gemm(B.BF16, B.GEMM_NN, a.data_ptr(), b.data_ptr(), c.data_ptr(), bias.data_ptr(), M, N, K, out_f32, accumulate,
+                        None, 0, stream()), "gemm")
+    sync()
+    want = a.double() @ b.double() + bias.double() + (2.0 if accumulate else 0.0)
+    err = (c.double() - want).abs()
+    # fp32 sums of 8 products; bf16 rounds to 2^-9 of the value
+    assert bool((err <= (1e-5 if out_f32 else 2.0 ** -8) * want.abs().clamp(min=4.0)).all())
+
+
+@pytest.mark.parametrize("mode", [B.GEMM_NN, B.GEMM_NT, B.GEMM_TN])
 @pytest.mark.parametrize("K,Kpad", [(192, 256), (200, 256), (4096, 4104), (520, 576)])
 def test_gemm_zero_padding_along_k_changes_no_bit(mode, K, Kpad):
     """The same product with the reduction index padded by zeros.  K = 192 -> 256 moves a k-contiguous operand from
