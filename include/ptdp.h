@@ -410,6 +410,8 @@ size_t ptdp_gemm_workspace_bytes(void);
  * group_parts[j] workgroups, part p of which takes the 64-wide k-steps
  * [nk*p/parts, nk*(p+1)/parts) of that tile; tiles x parts never exceeds the
  * number of compute units.  group_tiles / group_parts: two ints each.
+ * Calls with so few 256 x 256 tiles that smaller ones are faster split nothing:
+ * *dp_columns = N, *n_groups = 0.  (out_f32 = 0: an NN or NT call, 1: a TN call.)
  * has_bias / workspace_bytes as in the call being planned.  Returns 0, or
  * PTDP_E_INVALID_ARG / PTDP_E_NULL_PTR. */
 int ptdp_gemm_plan(int M, int N, int K, int out_f32, int accumulate, int has_bias, size_t workspace_bytes,

@@ -113,6 +113,15 @@ __device__ __forceinline__ void load_lds_16x2(rsrc_t r, char* dst, uint32_t v0, 
                :: "s"(lds_offset(dst)), "v"(v0), "v"(v1), "s"(r), "s"(soff) : "memory", "m0");
 }
 
+__device__ __forceinline__ void load_lds_16x4(rsrc_t r, char* dst, uint32_t v0, uint32_t v1, uint32_t v2, uint32_t v3, uint32_t soff) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\t"
+               "buffer_load_dwordx4 %1, %5, %6 offen lds\n\t"
+               "buffer_load_dwordx4 %2, %5, %6 offen offset:1024 lds\n\t"
+               "buffer_load_dwordx4 %3, %5, %6 offen offset:2048 lds\n\t"
+               "buffer_load_dwordx4 %4, %5, %6 offen offset:3072 lds"
+               :: "s"(lds_offset(dst)), "v"(v0), "v"(v1), "v"(v2), "v"(v3), "s"(r), "s"(soff) : "memory", "m0");
+}
+
 constexpr int BK = 64;
 constexpr int kBM = 256, kBN = 256, kGemmThreads = 512;
 constexpr int kHalfBytes = 128 * BK * 2, kStageBytes = 4 * kHalfBytes, kGemmSmem = 2 * kStageBytes;
@@ -216,10 +225,18 @@ struct GemmArgs {
   size_t lda, ldb, ldc;
 };
 
-// One wave's share of a tile: acc[ha][hb] covers rows ha*128 + (wave/4)*64 .. +63 and columns hb*128 + (wave%4)*32
-// .. +31 in blocks of 16 x 16.  The MFMA's A operand is the B fragment, so that a lane holds row lane & 15 of a block
-// and its four columns 4 * (lane >> 4) .. +3: consecutive in memory, written without a trip through LDS.
-typedef f32x4_t TileAcc[2][2][4][2];
+// A wave's outputs are NS strips of RB x 2 blocks of 16 x 16.  The MFMA's A operand is the B fragment, so that a lane
+// holds row lane & 15 of a block and its four columns 4 * (lane >> 4) .. +3: consecutive in memory, written without a
+// trip through LDS.  256 x 256 tile: strip 2*ha + hb covers rows ha*128 + (wave/4)*64 .. +63 and columns hb*128 +
+// (wave%4)*32 .. +31.
+template <int NS, int RB> using StripAcc = f32x4_t[NS][RB][2];
+typedef StripAcc<4, 4> TileAcc;
+template <int NS, int RB> __device__ __forceinline__ void zero_acc(StripAcc<NS, RB>& acc) {
+#pragma unroll
+  for (int b = 0; b < NS; ++b)
+#pragma unroll
+    for (int i = 0; i < RB; ++i) acc[b][i][0] = acc[b][i][1] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+}
 
 // acc += A[m0.., k] B[n0.., k] over k-tiles kt0 .. kt1-1.
 // A k-tile is four phases, one per quadrant of the wave's outputs; a phase is a memory part (the LDS reads the
@@ -309,7 +326,7 @@ __device__ __forceinline__ void gemm_mainloop(TileAcc& acc, const GemmArgs& g, i
     la.template issue<1, LEAN>(ra, other + kA1, wave, t + 1, kend);
     wait_loads();
     barrier();
-    compute(acc[0][0], bfr[S]);
+    compute(acc[0], bfr[S]);
     barrier();
     // phase 1
 #pragma unroll
@@ -319,7 +336,7 @@ __device__ __forceinline__ void gemm_mainloop(TileAcc& acc, const GemmArgs& g, i
     lb.template issue<0, LEAN>(rb, own + kB0, wave, t + 2, kend);
     wait_loads();
     barrier();
-    compute(acc[0][1], bfr[O]);
+    compute(acc[1], bfr[O]);
     barrier();
     // phase 2
 #pragma unroll
@@ -329,7 +346,7 @@ __device__ __forceinline__ void gemm_mainloop(TileAcc& acc, const GemmArgs& g, i
     la.template issue<0, LEAN>(ra, own + kA0, wave, t + 2, kend);
     wait_loads();
     barrier();
-    compute(acc[1][1], bfr[O]);
+    compute(acc[3], bfr[O]);
     barrier();
     // phase 3: its reads are used in the next tile's phase 0, but have to be complete by this phase's end (the place
     // is refilled from the next tile's phase 1 on)
@@ -341,7 +358,7 @@ __device__ __forceinline__ void gemm_mainloop(TileAcc& acc, const GemmArgs& g, i
     wait_loads();
     barrier();
     wait_reads();
-    compute(acc[1][0], bfr[S]);
+    compute(acc[2], bfr[S]);
     barrier();
   };
   constexpr std::integral_constant<int, 0> even{};
@@ -372,39 +389,39 @@ constexpr size_t kWideRow = (size_t)1 << 23;   // bytes; rows of C from here on 
 // of the weight gradients needs (25600 x 12800 x 2048: 1431 us with 64-byte segments, 1315 us with whole lines; 1368 us
 // with rows staged through LDS).  All accesses to C go through a buffer descriptor that ends behind the tile's last
 // row (columns past N: an offset beyond it), so the stage is free of branches.
-template <int OUT>
-__device__ __forceinline__ void gemm_epilogue(const TileAcc& acc, void* Cv, size_t ldc, const bf16_t* bias, int M, int N, int m0,
-                                              int n0) {
+// row[b], col[b]: first row and column of strip b inside the BM x BN tile.
+template <int OUT, int BM, int BN, int NS, int RB>
+__device__ __forceinline__ void gemm_epilogue(const StripAcc<NS, RB>& acc, const int (&row)[NS], const int (&col)[NS], void* Cv, size_t ldc,
+                                              const bf16_t* bias, int M, int N, int m0, int n0) {
   typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
   typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
   constexpr uint32_t esz = OUT == OUT_BF16 ? 2 : 4;
   constexpr int kAux = OUT == OUT_F32_RMW ? 2 : 0;   // gradient accumulators are touched once per launch: non-temporal
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-  const int wm = (wave >> 2) * 64, wn = (wave & 3) * 32, l15 = lane & 15, q = lane >> 4;
-  float bv[2][2][4];
+  const int lane = threadIdx.x & 63, l15 = lane & 15, q = lane >> 4;
+  float bv[NS][2][4];
 #pragma unroll
-  for (int hb = 0; hb < 2; ++hb)
+  for (int b = 0; b < NS; ++b)
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
-      const int n = n0 + hb * 128 + wn + j * 16 + 4 * q;
+      const int n = n0 + col[b] + j * 16 + 4 * q;
       uint2 w = make_uint2(0u, 0u);
       if (bias && n < N) w = *reinterpret_cast<const uint2*>(bias + n);
-      bv[hb][j][0] = __uint_as_float(w.x << 16); bv[hb][j][1] = __uint_as_float(w.x & 0xffff0000u);
-      bv[hb][j][2] = __uint_as_float(w.y << 16); bv[hb][j][3] = __uint_as_float(w.y & 0xffff0000u);
+      bv[b][j][0] = __uint_as_float(w.x << 16); bv[b][j][1] = __uint_as_float(w.x & 0xffff0000u);
+      bv[b][j][2] = __uint_as_float(w.y << 16); bv[b][j][3] = __uint_as_float(w.y & 0xffff0000u);
     }
   if (ldc >= kWideRow / esz) {   // byte offsets inside a tile would not fit 31 bits: plain 64-bit addresses
 #pragma unroll
-    for (int b = 0; b < 4; ++b)
+    for (int b = 0; b < NS; ++b)
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
+      for (int i = 0; i < RB; ++i)
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
-          const int m = m0 + (b >> 1) * 128 + wm + i * 16 + l15, n = n0 + (b & 1) * 128 + wn + j * 16 + 4 * q;
+          const int m = m0 + row[b] + i * 16 + l15, n = n0 + col[b] + j * 16 + 4 * q;
           if (m >= M || n >= N) continue;
           const size_t at = (size_t)m * ldc + n;
 #pragma unroll
           for (int r = 0; r < 4; ++r) {
-            const float v = acc[b >> 1][b & 1][i][j][r] + bv[b & 1][j][r];
+            const float v = acc[b][i][j][r] + bv[b][j][r];
             if (OUT == OUT_BF16) reinterpret_cast<bf16_t*>(Cv)[at + r] = f32_to_bf16(v);
             else if (OUT == OUT_F32_RMW) reinterpret_cast<float*>(Cv)[at + r] += v;
             else reinterpret_cast<float*>(Cv)[at + r] = v;
@@ -413,55 +430,53 @@ __device__ __forceinline__ void gemm_epilogue(const TileAcc& acc, void* Cv, size
     return;
   }
   char* origin = reinterpret_cast<char*>(Cv) + ((size_t)m0 * ldc + n0) * esz;
-  const uint32_t pitch = (uint32_t)ldc * esz, records = (uint32_t)(min(kBM, M - m0) - 1) * pitch + (uint32_t)min(kBN, N - n0) * esz;
+  const uint32_t pitch = (uint32_t)ldc * esz, records = (uint32_t)(min(BM, M - m0) - 1) * pitch + (uint32_t)min(BN, N - n0) * esz;
   const auto rc = __builtin_amdgcn_make_buffer_rsrc(origin, 0, records, 0x00020000);
   if (OUT == OUT_BF16) {
     const int c8 = 16 * (q & 1) + 8 * (q >> 1);   // first of this lane's 8 columns after the exchange
 #pragma unroll
-    for (int hb = 0; hb < 2; ++hb) {
-      const int col = hb * 128 + wn + c8;
-      const uint32_t off = n0 + col < N ? (uint32_t)(wm + l15) * pitch + col * esz : kOob;
+    for (int b = 0; b < NS; ++b) {
+      const int c = col[b] + c8;
+      const uint32_t off = n0 + c < N ? (uint32_t)(row[b] + l15) * pitch + c * esz : kOob;
 #pragma unroll
-      for (int ha = 0; ha < 2; ++ha)
+      for (int i = 0; i < RB; ++i) {
+        uint32_t p[2][2];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          uint32_t p[2][2];
-#pragma unroll
-          for (int j = 0; j < 2; ++j) {
-            const f32x4_t v = acc[ha][hb][i][j];
-            p[j][0] = pack_bf16x2(v[0] + bv[hb][j][0], v[1] + bv[hb][j][1]);
-            p[j][1] = pack_bf16x2(v[2] + bv[hb][j][2], v[3] + bv[hb][j][3]);
-          }
-          const u32x2_t x = __builtin_amdgcn_permlane16_swap(p[0][0], p[1][0], false, false);
-          const u32x2_t y = __builtin_amdgcn_permlane16_swap(p[0][1], p[1][1], false, false);
-          __builtin_amdgcn_raw_buffer_store_b128(u32x4_t{x[0], y[0], x[1], y[1]}, rc, off + (ha * 128 + i * 16) * pitch, 0, 0);
+        for (int j = 0; j < 2; ++j) {
+          const f32x4_t v = acc[b][i][j];
+          p[j][0] = pack_bf16x2(v[0] + bv[b][j][0], v[1] + bv[b][j][1]);
+          p[j][1] = pack_bf16x2(v[2] + bv[b][j][2], v[3] + bv[b][j][3]);
         }
+        const u32x2_t x = __builtin_amdgcn_permlane16_swap(p[0][0], p[1][0], false, false);
+        const u32x2_t y = __builtin_amdgcn_permlane16_swap(p[0][1], p[1][1], false, false);
+        __builtin_amdgcn_raw_buffer_store_b128(u32x4_t{x[0], y[0], x[1], y[1]}, rc, off + i * 16 * pitch, 0, 0);
+      }
     }
   } else {
     const bool low = l15 < 8;
-    uint32_t off[2];   // after the exchange: rows l15 & 7 (+ 8 for the second access), columns 16 * (l15 / 8) + 4 * q of 32
+    uint32_t off[NS];   // after the exchange: rows l15 & 7 (+ 8 for the second access), columns 16 * (l15 / 8) + 4 * q of 32
 #pragma unroll
-    for (int hb = 0; hb < 2; ++hb) {
-      const int col = hb * 128 + wn + (l15 >> 3) * 16 + 4 * q;
-      off[hb] = n0 + col < N ? (uint32_t)(wm + (l15 & 7)) * pitch + col * esz : kOob;
+    for (int b = 0; b < NS; ++b) {
+      const int c = col[b] + (l15 >> 3) * 16 + 4 * q;
+      off[b] = n0 + c < N ? (uint32_t)(row[b] + (l15 & 7)) * pitch + c * esz : kOob;
     }
-    auto at = [&](int b, int i, int half) { return off[b & 1] + ((b >> 1) * 128 + i * 16 + half * 8) * pitch; };
-    // the old values of the next quadrant are requested before the current one is added: two batches of loads in flight
-    u32x4_t old[2][8];
+    auto at = [&](int b, int i, int half) { return off[b] + (i * 16 + half * 8) * pitch; };
+    // the old values of the next strip are requested before the current one is added: two batches of loads in flight
+    u32x4_t old[2][RB * 2];
     auto fetch_old = [&](int b) {
 #pragma unroll
-      for (int i = 0; i < 8; ++i) old[b & 1][i] = __builtin_amdgcn_raw_buffer_load_b128(rc, at(b, i >> 1, i & 1), 0, kAux);
+      for (int i = 0; i < RB * 2; ++i) old[b & 1][i] = __builtin_amdgcn_raw_buffer_load_b128(rc, at(b, i >> 1, i & 1), 0, kAux);
     };
     if (OUT == OUT_F32_RMW) fetch_old(0);
 #pragma unroll
-    for (int b = 0; b < 4; ++b) {
-      if (OUT == OUT_F32_RMW && b + 1 < 4) fetch_old(b + 1);
+    for (int b = 0; b < NS; ++b) {
+      if (OUT == OUT_F32_RMW && b + 1 < NS) fetch_old(b + 1);
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
+      for (int i = 0; i < RB; ++i) {
         f32x4_t v[2];
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          const float x = acc[b >> 1][b & 1][i][0][r] + bv[b & 1][0][r], y = acc[b >> 1][b & 1][i][1][r] + bv[b & 1][1][r];
+          const float x = acc[b][i][0][r] + bv[b][0][r], y = acc[b][i][1][r] + bv[b][1][r];
           const float got = __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, low ? y : x), 0x128, 0xf, 0xf, true));   // row_ror:8
           v[0][r] = low ? x : got;
           v[1][r] = low ? got : y;
@@ -481,15 +496,12 @@ __device__ __forceinline__ void gemm_epilogue(const TileAcc& acc, void* Cv, size
 template <bool TA, bool TB, int OUT>
 __device__ __forceinline__ void gemm_tile(const GemmArgs& g, void* Cv, float* slab, int m0, int n0, int kt0, int kt1, char* smem) {
   TileAcc acc;
-#pragma unroll
-  for (int b = 0; b < 4; ++b)
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-      for (int j = 0; j < 2; ++j) acc[b >> 1][b & 1][i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  zero_acc<4, 4>(acc);
   if (kt1 > kt0) gemm_mainloop<TA, TB>(acc, g, m0, n0, kt0, kt1, smem);
-  if (slab) gemm_epilogue<OUT_F32_STORE>(acc, slab, kBN, nullptr, kBM, kBN, 0, 0);
-  else gemm_epilogue<OUT>(acc, Cv, g.ldc, g.bias, g.M, g.N, m0, n0);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wm = (wave >> 2) * 64, wn = (wave & 3) * 32;
+  const int row[4] = {wm, wm, wm + 128, wm + 128}, col[4] = {wn, wn + 128, wn, wn + 128};
+  if (slab) gemm_epilogue<OUT_F32_STORE, kBM, kBN, 4, 4>(acc, row, col, slab, kBN, nullptr, kBM, kBN, 0, 0);
+  else gemm_epilogue<OUT, kBM, kBN, 4, 4>(acc, row, col, Cv, g.ldc, g.bias, g.M, g.N, m0, n0);
 }
 
 // One workgroup per output tile ("data-parallel" form); `id` is the workgroup's index inside its problem.
@@ -521,6 +533,232 @@ gemm_bf16_dp_kernel(GemmArgs g, void* Cv) {
   gemm_dp_tile<TA, TB, OUT>(g, Cv, blockIdx.x, smem);
 }
 
+// ------------------------------------------------------------------------------------------------
+// Small tiles (BM x BN of 64 or 128, four waves of BM/2 x BN/2 per group), for outputs that give fewer 256 x 256 tiles
+// than the chip has compute units: what counts there is the number of workgroups and the length of the dependent
+// chain of k-tiles.  LDS is a ring of S k-tiles of 64 per group; the fragments of the next k-tile are read while the
+// current one is multiplied (one read after each MFMA; with all reads first the MFMAs wait for the LDS queue: 15-25 %
+// slower), and its place in the ring is refilled at once, so that S - 1 k-tiles are in flight; a k-tile costs one
+// counted wait and one barrier.  KG = 2: two groups of waves take alternate k-tiles and their sums meet in LDS, for
+// calls with at most one workgroup per CU (half the chain).  Bound by that chain (0.3 us per k-tile of a 64 x 64 tile,
+// 0.5 us of a 128 x 128 one: a barrier, the requests' issue, the fragment reads, the MFMAs), not by a rate.  Measured
+// against 256 x 256 tiles with a split k range (us): NN 664 x 512 x 2048 39.7 -> 8.9, NN 664 x 1536 x 512 15.4 -> 5.8,
+// NN 1024 x 2048 x 1024 22.5 -> 9.2, NN 2048 x 4096 x 1024 24.3 -> 19.3, TN += 512 x 2048 x 664 26.9 -> 7.0.
+// Operand layouts as above, with rows of BM (BN) elements for a k-slow operand.
+// ------------------------------------------------------------------------------------------------
+constexpr int kSmallThreads = 256;
+
+// slot of 16-byte chunk c of k-row k in a k-slow tile of ROWS elements per k-row (256 or 128 bytes): the k-rows one
+// transposing read gathers in a cycle land in different bank groups (128-byte rows: k & 1 picks the half by itself)
+template <int ROWS> __device__ __forceinline__ int kslow_swizzle(int k) {
+  return ROWS == 128 ? (2 * (k & 3)) ^ (8 * ((k >> 3) & 1)) : (2 * ((k >> 1) & 1)) ^ (4 * ((k >> 3) & 1));
+}
+
+// a wave's share of a ROWS x 64 operand tile: ROWS / 32 wave-loads of 1 KiB (one or two groups share an M0 value)
+template <bool KSLOW, int ROWS> struct SmallLoad {
+  static constexpr int L = ROWS / 32;
+  uint32_t off[L];
+  uint32_t kstep;
+  bool plain;
+  __device__ __forceinline__ int kpos(int i, int wave, int lane) const {
+    if (!KSLOW) {
+      const int row = (wave * L + i) * 8 + (lane >> 3);
+      return ((lane & 7) ^ ((row >> 1) & 7)) * 8;
+    }
+    constexpr int per = 512 / ROWS;   // k-rows per wave-load
+    return (wave * L + i) * per + lane / (64 / per);
+  }
+  __device__ __forceinline__ void init(size_t ld, int rows_left, int wave, int lane) {
+#pragma unroll
+    for (int i = 0; i < L; ++i) {
+      const int k = kpos(i, wave, lane);
+      if (!KSLOW) {
+        const int row = (wave * L + i) * 8 + (lane >> 3);
+        off[i] = row < rows_left ? (uint32_t)(((size_t)row * ld + k) * 2) - i * 1024u : kOob;
+      } else {
+        const int chunk = (lane & (ROWS / 8 - 1)) ^ kslow_swizzle<ROWS>(k);
+        off[i] = chunk * 8 < rows_left ? (uint32_t)(((size_t)k * ld + chunk * 8) * 2) - i * 1024u : kOob;
+      }
+    }
+    kstep = KSLOW ? (uint32_t)(BK * ld * 2) : (uint32_t)(BK * 2);
+    plain = ld >= 128;
+  }
+  __device__ __forceinline__ void issue(rsrc_t r, char* tile, int wave, int lane, int kt, int kend) const {
+    char* dst = tile + wave * L * 1024;
+    if (plain && (kt + 1) * BK <= kend) {
+      if constexpr (L == 4) load_lds_16x4(r, dst, off[0], off[1], off[2], off[3], (uint32_t)kt * kstep);
+      else load_lds_16x2(r, dst, off[0], off[1], (uint32_t)kt * kstep);
+    } else {
+#pragma unroll
+      for (int i = 0; i < L; ++i) {
+        const bool ok = off[i] != kOob && kt * BK + kpos(i, wave, lane) < kend;
+        load_lds_16(r, dst + i * 1024, ok ? off[i] + i * 1024u + (uint32_t)kt * kstep : kOob);
+      }
+    }
+  }
+};
+
+template <bool KSLOW, int ROWS> struct SmallRead {
+  static constexpr int NB = ROWS / 32;   // blocks of 16 rows per wave
+  uint32_t base[KSLOW ? NB : 2];
+  __device__ __forceinline__ void init(const char* smem, int w0, int lane) {
+    const int r = lane & 15, G = lane >> 4;
+    if (!KSLOW) {
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks) base[ks] = lds_offset(smem) + (w0 + r) * 128 + (((ks * 4 + G) ^ (r >> 1)) * 16);
+    } else {
+#pragma unroll
+      for (int i = 0; i < NB; ++i) {
+        const int n0 = w0 + i * 16 + 4 * (r & 3), k = 8 * G + (r >> 2);
+        base[i] = lds_offset(smem) + k * (ROWS * 2) + (((n0 >> 3) ^ kslow_swizzle<ROWS>(k)) * 16) + (n0 & 7) * 2;
+      }
+    }
+  }
+  __device__ __forceinline__ bf16x8_t get(uint32_t at, int i, int ks) const {
+    if (!KSLOW) {
+      return *PTDP_LDS(const bf16x8_t, base[ks] + at + i * 2048);
+    } else {
+      const uint32_t p = base[i] + at + ks * (32 * ROWS * 2);
+      const s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(PTDP_LDS(s16x4_t, p));
+      const s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(PTDP_LDS(s16x4_t, p + 4 * ROWS * 2));
+      const s16x8_t v = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+      return __builtin_bit_cast(bf16x8_t, v);
+    }
+  }
+};
+
+template <int BM, int BN, int S, int KG> struct SmallGeom {
+  static constexpr int kA = BM * BK * 2, kStage = (BM + BN) * BK * 2, kRing = S * kStage, kSmem = KG * kRing;
+  static constexpr int kThreads = KG * kSmallThreads;
+};
+
+template <bool TA, bool TB, int OUT, int BM, int BN, int S, int KG>
+__device__ __forceinline__ void gemm_small_tile(const GemmArgs& g, void* Cv, int m0, int n0, char* smem) {
+  typedef SmallGeom<BM, BN, S, KG> G;
+  constexpr int NS = BN / 64, RB = BM / 32, kLoads = (BM + BN) / 32;   // strips, row blocks; loads per wave and k-tile
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) & 3;
+  const int kg = KG == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x >> 8);   // group of waves: takes k-tiles kg, kg + KG, ...
+  const int wm = (wave >> 1) * (BM / 2), wn = (wave & 1) * (BN / 2);
+  char* ring = smem + kg * G::kRing;
+  const bf16_t* a_base = TA ? g.A + m0 : g.A + (size_t)m0 * g.lda;
+  const bf16_t* b_base = TB ? g.B + n0 : g.B + (size_t)n0 * g.ldb;
+  const size_t a_left = (size_t)(g.a_end - reinterpret_cast<const char*>(a_base));
+  const size_t b_left = (size_t)(g.b_end - reinterpret_cast<const char*>(b_base));
+  const rsrc_t ra = make_rsrc(a_base, (uint32_t)(a_left < 0x7fffffffu ? a_left : 0x7fffffffu));
+  const rsrc_t rb = make_rsrc(b_base, (uint32_t)(b_left < 0x7fffffffu ? b_left : 0x7fffffffu));
+  const int nk = ((g.K + BK - 1) / BK + KG - 1) / KG;   // steps: k-tile step * KG + kg
+  SmallLoad<TA, BM> la;
+  SmallLoad<TB, BN> lb;
+  la.init(g.lda, g.M - m0, wave, lane);
+  lb.init(g.ldb, g.N - n0, wave, lane);
+  SmallRead<TA, BM> fa;
+  SmallRead<TB, BN> fb;
+  fa.init(ring, wm, lane);
+  fb.init(ring + G::kA, wn, lane);
+  auto request = [&](int stage, int kt) {   // k-tiles past the end come back as zeros: the waits count every request
+    la.issue(ra, ring + stage * G::kStage, wave, lane, kt * KG + kg, g.K);
+    lb.issue(rb, ring + stage * G::kStage + G::kA, wave, lane, kt * KG + kg, g.K);
+  };
+#pragma unroll
+  for (int i = 0; i < S; ++i) request(i, i);
+  StripAcc<NS, RB> acc;
+  zero_acc<NS, RB>(acc);
+  bf16x8_t af[2][2][RB], bfr[2][2][2 * NS];   // [k-tile parity][ks][block]
+  auto read = [&](int par, uint32_t at) {
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) {
+#pragma unroll
+      for (int i = 0; i < RB; ++i) af[par][ks][i] = fa.get(at, i, ks);
+#pragma unroll
+      for (int j = 0; j < 2 * NS; ++j) bfr[par][ks][j] = fb.get(at, j, ks);
+    }
+  };
+  asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" :: "n"((S - 1) * kLoads) : "memory");
+  read(0, 0);
+  int stage = 0;
+  auto step = [&](auto parity, int t) {
+    constexpr int P = decltype(parity)::value;
+    // k-tile t is in every wave's registers and t + 1 has landed: read t + 1, refill t's stage, multiply t
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" :: "n"((S - 2) * kLoads) : "memory");
+    const int next = stage + 1 == S ? 0 : stage + 1;
+    char* own = ring + stage * G::kStage;
+    const uint32_t at = next * G::kStage;
+    stage = next;
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) {
+      if (ks == 0) la.issue(ra, own, wave, lane, (t + S) * KG + kg, g.K);
+      else lb.issue(rb, own + G::kA, wave, lane, (t + S) * KG + kg, g.K);
+#pragma unroll
+      for (int i = 0; i < RB; ++i) af[P ^ 1][ks][i] = fa.get(at, i, ks);
+#pragma unroll
+      for (int j = 0; j < 2 * NS; ++j) bfr[P ^ 1][ks][j] = fb.get(at, j, ks);
+#pragma unroll
+      for (int i = 0; i < RB; ++i)
+#pragma unroll
+        for (int j = 0; j < 2 * NS; ++j)
+          acc[j >> 1][i][j & 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bfr[P][ks][j], af[P][ks][i], acc[j >> 1][i][j & 1], 0, 0, 0);
+      constexpr int kMfma = RB * 2 * NS, kReads = (TA ? 2 : 1) * RB + (TB ? 2 : 1) * 2 * NS, kPer = (kReads + kMfma - 1) / kMfma;
+#pragma unroll
+      for (int q = 0; q < kMfma; ++q) {
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);      // MFMA
+        __builtin_amdgcn_sched_group_barrier(0x100, kPer, 0);   // LDS reads
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  constexpr std::integral_constant<int, 0> even{};
+  constexpr std::integral_constant<int, 1> odd{};
+  int t = 0;
+  for (; t + 1 < nk; t += 2) {
+    step(even, t);
+    step(odd, t + 1);
+  }
+  if (t < nk) step(even, t);
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the requests past the last k-tile (zeros) have landed
+  if constexpr (KG == 2) {   // the second group's sums join the first's through LDS: register r of lane l of wave w at sum[w][r][l]
+    static_assert(G::kSmem >= 4 * NS * RB * 8 * 64 * 4, "the partial sums fit in the operand ring");
+    f32x4_t* sum = reinterpret_cast<f32x4_t*>(smem) + wave * (NS * RB * 2 * 64) + lane;
+    __syncthreads();   // every wave is done with the operands
+    if (kg == 1) {
+#pragma unroll
+      for (int b = 0; b < NS; ++b)
+#pragma unroll
+        for (int i = 0; i < RB * 2; ++i) sum[(b * RB * 2 + i) * 64] = acc[b][i >> 1][i & 1];
+    }
+    __syncthreads();
+    if (kg == 1) return;
+#pragma unroll
+    for (int b = 0; b < NS; ++b)
+#pragma unroll
+      for (int i = 0; i < RB * 2; ++i) acc[b][i >> 1][i & 1] += sum[(b * RB * 2 + i) * 64];
+  }
+  int row[NS], col[NS];
+#pragma unroll
+  for (int b = 0; b < NS; ++b) {
+    row[b] = wm;
+    col[b] = wn + b * 32;
+  }
+  gemm_epilogue<OUT, BM, BN, NS, RB>(acc, row, col, Cv, g.ldc, g.bias, g.M, g.N, m0, n0);
+}
+
+// Tiles are numbered in groups of 8 row tiles, column by column inside a group; each XCD takes one contiguous run, so
+// that its workgroups share operand panels through its L2.
+template <int BM, int BN> static inline int small_blocks(int M, int N) { return 8 * ((((M + BM - 1) / BM) * ((N + BN - 1) / BN) + 7) / 8); }
+template <bool TA, bool TB, int OUT, int BM, int BN, int S, int KG>
+__device__ __forceinline__ void gemm_small_id(const GemmArgs& g, void* Cv, int id, char* smem) {
+  const int tiles_m = (g.M + BM - 1) / BM, tiles_n = (g.N + BN - 1) / BN, tiles = tiles_m * tiles_n;
+  const int per_xcd = (tiles + 7) / 8, t = (id & 7) * per_xcd + (id >> 3);
+  if ((id >> 3) >= per_xcd || t >= tiles) return;
+  const int grp = t / (8 * tiles_n), in_grp = t - grp * 8 * tiles_n, gm = min(8, tiles_m - grp * 8);
+  gemm_small_tile<TA, TB, OUT, BM, BN, S, KG>(g, Cv, (grp * 8 + in_grp % gm) * BM, (in_grp / gm) * BN, smem);
+}
+template <bool TA, bool TB, int OUT, int BM, int BN, int S, int KG>
+__global__ void __launch_bounds__(KG * kSmallThreads, 2)
+gemm_bf16_small_kernel(GemmArgs g, void* Cv) {
+  extern __shared__ __attribute__((aligned(1024))) char smem[];
+  gemm_small_id<TA, TB, OUT, BM, BN, S, KG>(g, Cv, blockIdx.x, smem);
+}
+
 // Up to four independent problems of the same form in one launch: each later problem's tiles fill the CUs that the
 // last, partial round of the ones before it would leave idle.  start[j] = first workgroup index of problem j
 // (multiples of 8, so that every problem starts on XCD 0), start[n] = grid size.
@@ -548,6 +786,24 @@ gemm_bf16_dp_multi_kernel(MultiArgs a) {
       first = a.start[q];
     }
   gemm_dp_tile<TA, TB, OUT>(g, C, id - first, smem);
+}
+
+template <bool TA, bool TB, int OUT, int BM, int BN, int S, int KG>
+__global__ void __launch_bounds__(KG * kSmallThreads, 2)
+gemm_bf16_small_multi_kernel(MultiArgs a) {
+  extern __shared__ __attribute__((aligned(1024))) char smem[];
+  const int id = (int)blockIdx.x;
+  GemmArgs g = a.g[0];
+  void* C = a.C[0];
+  int first = a.start[0];
+#pragma unroll
+  for (int q = 1; q < kMaxMulti; ++q)
+    if (q < a.n && id >= a.start[q]) {
+      g = a.g[q];
+      C = a.C[q];
+      first = a.start[q];
+    }
+  gemm_small_id<TA, TB, OUT, BM, BN, S, KG>(g, C, id - first, smem);
 }
 
 // Remainder form, for the tiles that do not fill a whole round of the machine.  The remaining tiles are cut into
@@ -663,6 +919,43 @@ static int launch_split(const GemmArgs& g, void* C, float* slabs, const SplitGro
   return PTDP_OK;
 }
 
+template <bool TA, bool TB, int OUT, int BM, int BN, int S, int KG>
+static int launch_small(const GemmArgs& g, void* C, hipStream_t st) {
+  auto kern = gemm_bf16_small_kernel<TA, TB, OUT, BM, BN, S, KG>;
+  static once_flag_t done[kMaxDevices];
+  constexpr int smem = SmallGeom<BM, BN, S, KG>::kSmem;
+  if (set_dynamic_smem(reinterpret_cast<const void*>(kern), smem, done) != PTDP_OK) return PTDP_E_HIP;
+  const int blocks = small_blocks<BM, BN>(g.M, g.N);
+  hipLaunchKernelGGL(kern, dim3(blocks), dim3(KG * kSmallThreads), smem, st, g, C);
+  return PTDP_OK;
+}
+template <bool TA, bool TB, int OUT>
+static int launch_small_form(int form, const GemmArgs& g, void* C, hipStream_t st) {
+  switch (form) {
+    case 0: return launch_small<TA, TB, OUT, 128, 128, 2, 1>(g, C, st);
+    case 1: return launch_small<TA, TB, OUT, 128, 128, 2, 2>(g, C, st);
+    case 2: return launch_small<TA, TB, OUT, 128, 64, 3, 2>(g, C, st);
+    case 3: return launch_small<TA, TB, OUT, 64, 64, 4, 2>(g, C, st);
+    default: return launch_small<TA, TB, OUT, 128, 64, 2, 1>(g, C, st);
+  }
+}
+// several problems, see gemm_bf16_dp_multi_kernel; a.start is filled here
+template <int BM, int BN, int S, int KG>
+static int launch_small_multi(MultiArgs& a, hipStream_t st) {
+  auto kern = gemm_bf16_small_multi_kernel<true, true, OUT_F32_RMW, BM, BN, S, KG>;
+  static once_flag_t done[kMaxDevices];
+  constexpr int smem = SmallGeom<BM, BN, S, KG>::kSmem;
+  if (set_dynamic_smem(reinterpret_cast<const void*>(kern), smem, done) != PTDP_OK) return PTDP_E_HIP;
+  int at = 0;
+  for (int j = 0; j < kMaxMulti; ++j) {
+    a.start[j] = at;
+    if (j < a.n) at += small_blocks<BM, BN>(a.g[j].M, a.g[j].N);
+  }
+  a.start[kMaxMulti] = at;
+  hipLaunchKernelGGL(kern, dim3(at), dim3(KG * kSmallThreads), smem, st, a);
+  return PTDP_OK;
+}
+
 static int compute_units() {
   static std::atomic<int> n[kMaxDevices];
   const int d = device_slot();
@@ -678,21 +971,30 @@ static int compute_units() {
 // every split group stores at most one slab per compute unit
 size_t gemm_workspace_bytes() { return (size_t)compute_units() * kMaxSplitGroups * kSlabFloats * sizeof(float); }
 
+// Times in microseconds that decide how a call is cut, fitted to 620 measured calls (M 256 .. 8192, N 256 .. 15360, K 256
+// .. 12288; rms error 6-12 %; picking by them costs 1-4 % over always picking the best).  Outputs in bf16, or += into fp32.
+struct LargeCost {
+  double step, round;                    // 256 x 256 tiles: per k-step, per round (first loads, output)
+  double split_step, split_slab, split_fixed;   // remainder groups: per k-step, per slab, the reduce launch
+};
+static const LargeCost kLargeCost[2] = {{1.10, 10.0, 1.29, 0.10, 3.0}, {1.20, 22.0, 1.50, 0.02, 32.0}};
+
 // How a call is cut: whole rounds of tiles (whole columns of tiles, so that the remainder is fewer tiles than
 // compute units), then the remainder in at most two groups (see gemm_bf16_split_kernel).  A first group of
 // 2^a tiles is taken while one group over all remaining tiles would leave more than a tenth of the
-// compute units idle; the second group takes what is left.  The split is used when a cost model fitted to
-// measurements (1.8 us per k-step; 12 us per group for its first loads and last stores; 0.12 us per slab
-// for its trip through memory, 0.3 us when the sums are added into an fp32 C; 8 us for the reduce launch) puts it
-// below nine tenths of one more round of whole tiles.
-SplitPlan gemm_plan(int M, int N, int K, int out_f32, int accumulate, int has_bias, size_t ws_bytes) {
+// compute units idle; the second group takes what is left.  The split is used when its cost is below that of
+// one more round of whole tiles.  *time: the plan's cost.
+static SplitPlan large_plan(int M, int N, int K, int out_f32, int accumulate, int has_bias, size_t ws_bytes, double* time) {
   const int ncu = compute_units();
   const int tiles_m = (M + kBM - 1) / kBM, tiles_n = (N + kBN - 1) / kBN, nk = (K + BK - 1) / BK;
   const long long tiles = (long long)tiles_m * tiles_n;
+  const LargeCost& cost = kLargeCost[out_f32 && accumulate];
+  const double t_round = cost.step * nk + cost.round;
   SplitPlan P;
   P.dp_cols = tiles_n;
   P.n_groups = 0;
   for (int j = 0; j < kMaxSplitGroups; ++j) P.tiles[j] = P.parts[j] = 0;
+  *time = (double)((tiles + ncu - 1) / ncu) * t_round;
   const bool out_ok = (out_f32 && accumulate && !has_bias) || !out_f32;
   if (tiles % ncu == 0 || !out_ok || ws_bytes < gemm_workspace_bytes() || (out_f32 && nk < 64)) return P;
   // whole columns only: the full rounds' tiles, rounded up to a column boundary
@@ -713,17 +1015,18 @@ SplitPlan gemm_plan(int M, int N, int K, int out_f32, int accumulate, int has_bi
     rem -= take;
     ++n;
   }
-  double t_split = 0.0;
+  double t_split = cost.split_fixed;
   bool any = false;
   for (int j = 0; j < n; ++j) {
-    t_split += 1.8 * ((nk + gp[j] - 1) / gp[j]) + 12.0;
+    t_split += cost.split_step * ((nk + gp[j] - 1) / gp[j]);
     if (gp[j] > 1) {
-      t_split += (out_f32 ? 0.3 : 0.12) * gt[j] * gp[j];
+      t_split += cost.split_slab * gt[j] * gp[j];
       any = true;
     }
   }
-  if (any) t_split += 8.0;
-  if (!any || t_split >= 0.9 * 1.8 * nk) return P;
+  if (!any || t_split >= t_round) return P;
+  // (whole columns: the full rounds may come out as one more, partly filled round)
+  *time = (double)(((long long)dp_cols * tiles_m + ncu - 1) / ncu) * t_round + t_split;
   P.dp_cols = dp_cols;
   P.n_groups = n;
   for (int j = 0; j < n; ++j) {
@@ -733,9 +1036,64 @@ SplitPlan gemm_plan(int M, int N, int K, int out_f32, int accumulate, int has_bi
   return P;
 }
 
+// Small tiles: which form (index into the table, the order of launch_small_form), or -1 for the 256 x 256 kernels.  A
+// call of n problems with `tiles` workgroups and nk k-tiles takes about
+//   fixed + each * w + steps * (pair * (w / 2) + single * (w % 2)),  w = workgroups per CU, steps = ceil(nk / groups)
+// where two workgroups of a form that fits twice on a CU overlap (pair < 2 * single).
+struct SmallCost {
+  int bm, bn, groups, per_cu;
+  double fixed, pair, single, each;
+};
+constexpr int kSmallForms = 5;
+static const SmallCost kSmallCost[2][kSmallForms] = {
+    {{128, 128, 1, 2, 1.5, 0.787, 0.532, 2.3},    // (most calls of 64 to 256 large tiles)
+     {128, 128, 2, 1, 0.0, 0.0, 0.880, 4.7},      // two wave groups share the k range: long k, at most one workgroup per CU
+     {128, 64, 2, 1, 1.4, 0.0, 0.540, 3.3},
+     {64, 64, 2, 1, 2.0, 0.0, 0.326, 2.6},        // the smallest outputs
+     {128, 64, 1, 2, 3.0, 0.545, 0.365, 0.7}},
+    {{128, 128, 1, 2, 0.0, 0.804, 0.547, 6.3},
+     {128, 128, 2, 1, 0.0, 0.0, 0.920, 7.4},
+     {128, 64, 2, 1, 0.9, 0.0, 0.580, 4.8},
+     {64, 64, 2, 1, 1.3, 0.0, 0.377, 3.5},
+     {128, 64, 1, 2, 1.7, 0.578, 0.394, 2.6}}};
+constexpr int kMinStepsForGroups = 8;   // k-tiles from which two wave groups are considered: below, joining their sums costs what they save
+
+static int small_form(int rmw, int n, const int* M, const int* N, int K, double t_large) {
+  const int ncu = compute_units(), nk = (K + BK - 1) / BK;
+  int best = -1;
+  for (int f = 0; f < kSmallForms; ++f) {
+    const SmallCost& c = kSmallCost[rmw][f];
+    if (c.groups > 1 && nk < kMinStepsForGroups) continue;
+    long long tiles = 0;
+    for (int j = 0; j < n; ++j) tiles += (long long)((M[j] + c.bm - 1) / c.bm) * ((N[j] + c.bn - 1) / c.bn);
+    if (tiles > (1 << 30)) continue;
+    const double w = (double)((tiles + ncu - 1) / ncu), steps = (nk + c.groups - 1) / c.groups;
+    const double t = c.fixed + c.each * w + steps * (c.per_cu == 2 ? c.pair * (double)(int)(w / 2) + c.single * (w - 2 * (int)(w / 2)) : c.single * w);
+    if (t < t_large) {
+      t_large = t;
+      best = f;
+    }
+  }
+  return best;
+}
+
+// The whole decision for one call: a small form, or (-1) the plan of the 256 x 256 kernels.  Small forms exist for bf16
+// outputs of NN and NT and for the += of TN: what a layer's calls need.
+static int choose_form(int mode, int M, int N, int K, int out_f32, int accumulate, int has_bias, size_t ws_bytes, SplitPlan* P) {
+  double t;
+  *P = large_plan(M, N, K, out_f32, accumulate, has_bias, ws_bytes, &t);
+  const bool rmw = mode == PTDP_GEMM_TN && out_f32 && accumulate;
+  if (!rmw && (mode == PTDP_GEMM_TN || out_f32)) return -1;
+  return small_form(rmw, 1, &M, &N, K, t);
+}
+
 void gemm_plan_query(int M, int N, int K, int out_f32, int accumulate, int has_bias, size_t ws_bytes, int* dp_cols,
                      int* n_groups, int* tiles, int* parts) {
-  const SplitPlan P = gemm_plan(M, N, K, out_f32, accumulate, has_bias, ws_bytes);
+  SplitPlan P;
+  if (choose_form(out_f32 ? PTDP_GEMM_TN : PTDP_GEMM_NN, M, N, K, out_f32, accumulate, has_bias, ws_bytes, &P) >= 0) {
+    P.dp_cols = (N + kBN - 1) / kBN;   // small tiles: nothing is split
+    P.n_groups = 0;
+  }
   *dp_cols = P.dp_cols;
   *n_groups = P.n_groups;
   for (int j = 0; j < kMaxSplitGroups; ++j) {
@@ -760,7 +1118,13 @@ static int launch_bf16_mode(const void* A, const void* B, void* C, const void* b
   g.ldb = TB ? (size_t)N : (size_t)K;
   g.ldc = (size_t)N;
 
-  const SplitPlan P = gemm_plan(M, N, K, out_f32, accumulate, bias != nullptr, ws != nullptr ? ws_bytes : 0);
+  SplitPlan P;
+  const int form = choose_form(TA ? PTDP_GEMM_TN : (TB ? PTDP_GEMM_NN : PTDP_GEMM_NT), M, N, K, out_f32, accumulate, bias != nullptr,
+                               ws != nullptr ? ws_bytes : 0, &P);
+  if (form >= 0) {
+    constexpr int OUT = TA ? OUT_F32_RMW : OUT_BF16;
+    return launch_small_form<TA, TB, OUT>(form, g, C, st);
+  }
   const int ncu = compute_units();
   const int tiles_m = (M + kBM - 1) / kBM, tiles_n = (N + kBN - 1) / kBN;
   const int n_dp = P.dp_cols < tiles_n ? P.dp_cols * kBN : N;
@@ -866,6 +1230,25 @@ int launch_gemm_tn_multi(int dtype, int n, const void* const* A, const void* con
     if (j < n) at += dp_blocks(a.g[j]);
   }
   a.start[kMaxMulti] = at;
+  double t_large = 0.0;
+  {
+    const LargeCost& cost = kLargeCost[1];
+    long long tiles = 0;
+    for (int j = 0; j < n; ++j) tiles += (long long)((M[j] + kBM - 1) / kBM) * ((N[j] + kBN - 1) / kBN);
+    t_large = (double)((tiles + compute_units() - 1) / compute_units()) * (cost.step * ((K + BK - 1) / BK) + cost.round);
+  }
+  const int form = small_form(1, n, M, N, K, t_large);
+  if (form >= 0) {
+    int rc;
+    switch (form) {
+      case 0: rc = launch_small_multi<128, 128, 2, 1>(a, st); break;
+      case 1: rc = launch_small_multi<128, 128, 2, 2>(a, st); break;
+      case 2: rc = launch_small_multi<128, 64, 3, 2>(a, st); break;
+      case 3: rc = launch_small_multi<64, 64, 4, 2>(a, st); break;
+      default: rc = launch_small_multi<128, 64, 2, 1>(a, st); break;
+    }
+    return rc != PTDP_OK ? rc : L.status();
+  }
   auto kern = gemm_bf16_dp_multi_kernel<true, true, OUT_F32_RMW>;
   static once_flag_t done[kMaxDevices];
   if (set_dynamic_smem(reinterpret_cast<const void*>(kern), kGemmSmem, done) != PTDP_OK) return PTDP_E_HIP;

@@ -59,6 +59,39 @@ def test_gemm_every_short_pipeline(mode, nk, tail):
     assert_close(np64(c), want, B.BF16, "C", 0.2)
 
 
+# each of the five small-tile forms at ragged edges, with k-tile counts that are odd, even and end in a partial tile
+SMALL_FORMS = [(664, 520, 2048 + 8), (72, 1096, 1024), (200, 136, 640),         # 64 x 64, two wave groups
+               (1032, 2056, 4096), (2056, 1000, 2048 + 56),                     # 128 x 64, two wave groups
+               (2040, 1544, 4168), (1544, 2056, 4096),                          # 128 x 128, two wave groups
+               (136, 264, 72), (1000, 2056, 512), (2056, 3064, 448 + 8),        # 128 x 64
+               (2056, 4088, 1024 + 8), (1000, 5128, 2560), (2040, 4104, 192)]   # 128 x 128
+
+
+@pytest.mark.parametrize("mode", [B.GEMM_NN, B.GEMM_NT, B.GEMM_TN])
+@pytest.mark.parametrize("M,N,K", SMALL_FORMS)
+def test_gemm_small_tiles(mode, M, N, K):
+    a = randn((M, K), B.BF16, 1)
+    b = randn((K, N), B.BF16, 2)
+    bias = randn((N,), B.BF16, 3)
+    A = a.t().contiguous() if mode == B.GEMM_TN else a
+    Bm = b.t().contiguous() if mode == B.GEMM_NT else b
+    want = a.double() @ b.double()
+    if mode == B.GEMM_TN:
+        acc = torch.full((M, N), 0.5, dtype=torch.float32, device="cuda")
+        for _ in range(2):
+            B.check(B.ptdp_gemm(B.BF16, mode, A.data_ptr(), Bm.data_ptr(), acc.data_ptr(), None, M, N, K, 1, 1, None, 0, stream()), "gemm")
+        sync()
+        # fp32 sums of up to 4168 products with partial sums of size sqrt(K): error below K^0.5 * 2^-24 * sqrt(K) per sum
+        assert float((acc.double() - 0.5 - 2 * want).abs().max()) <= 2 * 2.0 ** -22 * K
+    else:
+        c = torch.full((M, N), 9.0, dtype=torch.bfloat16, device="cuda")
+        B.check(B.ptdp_gemm(B.BF16, mode, A.data_ptr(), Bm.data_ptr(), c.data_ptr(), bias.data_ptr(), M, N, K, 0, 0, None, 0, stream()), "gemm")
+        sync()
+        want = want + bias.double()
+        # bf16 rounding of the result (2^-9 of its size) plus the fp32 sums' error
+        assert bool(((c.double() - want).abs() <= 2.0 ** -8 * want.abs() + 2.0 ** -22 * K).all())
+
+
 @pytest.mark.parametrize("out_f32,accumulate", [(0, 0), (1, 0), (1, 1)])
 @pytest.mark.parametrize("N", [(1 << 21) - 8, (1 << 21) + 8, (1 << 22) + 8])
 def test_gemm_rows_of_c_beyond_31_bit_offsets(out_f32, accumulate, N):
