@@ -9,7 +9,7 @@
 // bf16 forward: S^T = K Q^T and O^T = V^T P^T on v_mfma_f32_32x32x16_bf16, so that the softmax
 // probabilities leave the first MFMA already in the register layout the second one wants as its
 // B operand.  One wave owns 32 queries; a block of 2 waves shares 64-key K and V tiles in LDS.
-// The "rowwise" kernels are the plain formulation (one wave per row): they are the fp32 path.
+// fp32: the same two-step form on v_mfma_f32_16x16x4_f32, operands straight from memory.
 #include "common.h"
 
 namespace ptdp {
@@ -17,180 +17,286 @@ namespace ptdp {
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8_t;
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16_t;
 
-template <typename T> __device__ __forceinline__ float ld(const T* p);
-template <> __device__ __forceinline__ float ld<float>(const float* p) { return *p; }
-template <> __device__ __forceinline__ float ld<bf16_t>(const bf16_t* p) { return bf16_to_f32(*p); }
-template <typename T> __device__ __forceinline__ void st(T* p, float v);
-template <> __device__ __forceinline__ void st<float>(float* p, float v) { *p = v; }
-template <> __device__ __forceinline__ void st<bf16_t>(bf16_t* p, float v) { *p = f32_to_bf16(v); }
-
-// ------------------------------------------------------------------------------------------------
-// rowwise kernels: grid (s, heads, b), one wave per block; lane owns dims lane, lane+64, ... (dh <= 256)
-// ------------------------------------------------------------------------------------------------
-constexpr int kMaxDimsPerLane = 4;
 // General mask (section 4.2: the fused softmax "with general masking"): a hidden score is replaced
 // by this value before the softmax, so a row without any visible key attends uniformly, and no
 // gradient flows to q and k through a hidden score.  mask is [b, s, s] bytes, nonzero = hidden.
 constexpr float kMaskFill = -10000.f;
+typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4_t;
 
-template <typename T>
-__global__ void __launch_bounds__(64)
-attn_fwd_rowwise(const T* __restrict__ qkv, T* __restrict__ ctx, float* __restrict__ lse, int s, int b, int heads,
-                 int dh, const uint8_t* __restrict__ mask, int causal) {
-  const int i = blockIdx.x, e = blockIdx.y, j = blockIdx.z, lane = threadIdx.x;
-  const int hp = heads * dh;
-  const size_t rs = (size_t)b * 3 * hp;  // token stride
-  const T* base = qkv + (size_t)j * 3 * hp + (size_t)e * dh;
-  const float scale = rsqrtf((float)dh);
-  float q[kMaxDimsPerLane], acc[kMaxDimsPerLane];
+// ------------------------------------------------------------------------------------------------
+// fp32 kernels on v_mfma_f32_16x16x4_f32 (fp32 products and sums).  A workgroup of four waves owns 16 queries (forward,
+// dQ) or 16 keys (dK, dV) of one head; each wave takes every fourth 16-row tile of the other side and the four partial
+// results meet in LDS in a fixed order.  Operands come from memory straight into fragments: lane (c = lane & 15,
+// g = lane >> 4) carries four consecutive dh of row c (elements 16 i + 4 g .. +3 of step i; both factors of a product
+// share that order), and the score tile S^T comes out with column c = the workgroup's row and rows 4 g + r = the tile's,
+// which is the second product's B operand as it stands.  These are small calls (fp32 is the precision of small
+// configurations): what counts is the length of one wave's chain and the number of waves.  128 tokens x 4 heads x 2
+// samples, dh 64: forward 101 -> 15 us, backward 165 -> 32 us against one wave per row that reduced every
+// score across the wave.
+// ND: steps of 16 dh (dh rounded up; the lanes past dh hold zeros).
+// ------------------------------------------------------------------------------------------------
+constexpr int kF32Rows = 16, kF32Waves = 4;
+constexpr int kMaxF32Dh = 256;
+
+template <int ND> struct F32Frag { f32x4_t v[ND]; };
+// four consecutive dh of one row per step; `row` must be readable
+template <int ND> __device__ __forceinline__ void f32_load(F32Frag<ND>& f, const float* __restrict__ row, int g, int dh) {
 #pragma unroll
-  for (int c = 0; c < kMaxDimsPerLane; ++c) {
-    const int d = lane + 64 * c;
-    q[c] = d < dh ? ld(base + (size_t)i * rs + d) : 0.f;
-    acc[c] = 0.f;
+  for (int i = 0; i < ND; ++i) {
+    const int d = 16 * i + 4 * g;
+    f.v[i] = d < dh ? *reinterpret_cast<const f32x4_t*>(row + d) : f32x4_t{0.f, 0.f, 0.f, 0.f};
   }
+}
+// 16 x 16 products of rows a (result rows 4 g + r) and rows b (result column c)
+template <int ND> __device__ __forceinline__ f32x4_t f32_scores(const F32Frag<ND>& a, const F32Frag<ND>& b) {
+  f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int i = 0; i < ND; ++i)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a.v[i][e], b.v[i][e], acc, 0, 0, 0);
+  return acc;
+}
+// acc^T[16 dh rows x 16 columns] += X^T w for the tile rows row0 .. row0 + 15 of X (rows from s on count as zeros; their
+// weights are zero).  Register r of acc[t]: dh 16 t + 4 g + r of column c.
+// A weight that the causal mask hides is zero, but zero times an infinite or undefined element is not: a tile on the
+// diagonal (`vis`: bit r = row 4 g + r is visible to column c) that holds such elements adds its visible rows one by one.
+template <int ND>
+__device__ __forceinline__ void f32_accumulate(f32x4_t (&acc)[ND], f32x4_t w, const float* __restrict__ X, size_t rs, int row0, int s,
+                                               int dh, bool diag, uint32_t vis, int lane) {
+  const int c = lane & 15, g = lane >> 4;
+  auto at = [&](int t, int r) {
+    const int row = row0 + 4 * g + r, d = 16 * t + c;
+    const float x = X[(size_t)min(row, s - 1) * rs + min(d, dh - 1)];
+    return row < s && d < dh ? x : 0.f;
+  };
+  if (diag) {
+    bool finite = true;
+#pragma unroll
+    for (int t = 0; t < ND; ++t)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) finite = finite && fabsf(at(t, r)) < INFINITY;
+    if (!__all(finite)) {
+#pragma unroll
+      for (int row = 0; row < 16; ++row) {
+        const float wr = __shfl(w[row & 3], (row >> 2) * 16 + c, 64);
+        const bool seen = (__shfl((int)vis, (row >> 2) * 16 + c, 64) >> (row & 3)) & 1;
+        if (row0 + row >= s) continue;
+#pragma unroll
+        for (int t = 0; t < ND; ++t)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            const int d = 16 * t + 4 * g + r;
+            if (d < dh && seen) acc[t][r] += wr * X[(size_t)(row0 + row) * rs + d];
+          }
+      }
+      return;
+    }
+  }
+#pragma unroll
+  for (int t = 0; t < ND; ++t)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(at(t, r), w[r], acc[t], 0, 0, 0);
+}
+// waves 1 .. 3 hand their sums to wave 0 (added in that order); returns true in wave 0.  part: 3 * ND * 64 vectors.
+template <int ND> __device__ __forceinline__ bool f32_join(f32x4_t (&acc)[ND], f32x4_t* part, int wave, int lane) {
+  __syncthreads();
+  if (wave > 0) {
+#pragma unroll
+    for (int t = 0; t < ND; ++t) part[((wave - 1) * ND + t) * 64 + lane] = acc[t];
+  }
+  __syncthreads();
+  if (wave > 0) return false;
+#pragma unroll
+  for (int w = 0; w < kF32Waves - 1; ++w)
+#pragma unroll
+    for (int t = 0; t < ND; ++t) acc[t] += part[(w * ND + t) * 64 + lane];
+  return true;
+}
+template <int ND> __device__ __forceinline__ void f32_store(float* row, const f32x4_t (&acc)[ND], int g, int dh) {
+#pragma unroll
+  for (int t = 0; t < ND; ++t)
+    if (16 * t + 4 * g < dh) *reinterpret_cast<f32x4_t*>(row + 16 * t + 4 * g) = acc[t];
+}
+
+template <int ND>
+__global__ void __launch_bounds__(64 * kF32Waves)
+attn_fwd_f32(const float* __restrict__ qkv, float* __restrict__ ctx, float* __restrict__ lse, int s, int b, int heads, int dh,
+             const uint8_t* __restrict__ mask, int causal) {
+  __shared__ f32x4_t part[(kF32Waves - 1) * ND * 64];
+  __shared__ float stat[2][kF32Waves][16];
+  const int e = blockIdx.y, j = blockIdx.z, wave = threadIdx.x >> 6, lane = threadIdx.x & 63, c = lane & 15, g = lane >> 4;
+  const int q0 = ((int)gridDim.x - 1 - (int)blockIdx.x) * kF32Rows, my_q = q0 + c;   // long rows first
+  const int hp = heads * dh;
+  const size_t rs = (size_t)b * 3 * hp;
+  const float* base = qkv + (size_t)j * 3 * hp + (size_t)e * dh;
+  const float scale = rsqrtf((float)dh);
+  F32Frag<ND> q;
+  f32_load<ND>(q, base + (size_t)min(my_q, s - 1) * rs, g, dh);
+  f32x4_t o[ND];
+#pragma unroll
+  for (int t = 0; t < ND; ++t) o[t] = f32x4_t{0.f, 0.f, 0.f, 0.f};
   float m = -INFINITY, l = 0.f;
-  const int kend = causal ? i : s - 1;
-  const uint8_t* mrow = (!causal && mask) ? mask + ((size_t)j * s + i) * s : nullptr;
-  for (int kk = 0; kk <= kend; ++kk) {
-    const T* kr = base + (size_t)kk * rs + hp;
-    const T* vr = kr + hp;
-    float dot = 0.f;
+  const int ntiles = ((causal ? min(q0 + kF32Rows, s) : s) + kF32Rows - 1) / kF32Rows;
+  const uint8_t* mrow = (!causal && mask) ? mask + ((size_t)j * s + min(my_q, s - 1)) * s : nullptr;
+  for (int kt = wave; kt < ntiles; kt += kF32Waves) {
+    const int key0 = kt * kF32Rows;
+    F32Frag<ND> k;
+    f32_load<ND>(k, base + hp + (size_t)min(key0 + c, s - 1) * rs, g, dh);
+    f32x4_t p = f32_scores<ND>(k, q);
+    uint32_t vis = 0;
+    float mx = m;
 #pragma unroll
-    for (int c = 0; c < kMaxDimsPerLane; ++c) {
-      const int d = lane + 64 * c;
-      if (d < dh) dot += q[c] * ld(kr + d);
+    for (int r = 0; r < 4; ++r) {
+      const int key = key0 + 4 * g + r;
+      p[r] *= scale;
+      if (mrow && key < s && mrow[key]) p[r] = kMaskFill;
+      const bool ok = key < s && (!causal || key <= my_q);
+      p[r] = ok ? p[r] : -INFINITY;
+      vis |= (uint32_t)ok << r;
+      mx = fmaxf(mx, p[r]);
     }
-    float sc = wave_sum(dot) * scale;
-    if (mrow && mrow[kk]) sc = kMaskFill;
-    const float mn = fmaxf(m, sc);
-    const float corr = __expf(m - mn), p = __expf(sc - mn);
-    l = l * corr + p;
+    mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
+    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+    const float corr = __expf(m - mx);   // the tile's first key is visible to every row of the workgroup: mx > -inf
+    m = mx;
+    l *= corr;
 #pragma unroll
-    for (int c = 0; c < kMaxDimsPerLane; ++c) {
-      const int d = lane + 64 * c;
-      if (d < dh) acc[c] = acc[c] * corr + p * ld(vr + d);
+    for (int r = 0; r < 4; ++r) {
+      p[r] = __expf(p[r] - mx);
+      l += p[r];
     }
-    m = mn;
-  }
 #pragma unroll
-  for (int c = 0; c < kMaxDimsPerLane; ++c) {
-    const int d = lane + 64 * c;
-    if (d < dh) st(ctx + ((size_t)i * b + j) * hp + (size_t)e * dh + d, acc[c] / l);
+    for (int t = 0; t < ND; ++t) o[t] *= corr;
+    f32_accumulate<ND>(o, p, base + 2 * hp, rs, key0, s, dh, causal && key0 + kF32Rows > q0, vis, lane);
   }
-  if (lane == 0) lse[((size_t)j * heads + e) * s + i] = m + __logf(l);
+  l += __shfl_xor(l, 16, 64);
+  l += __shfl_xor(l, 32, 64);
+  if (g == 0) {
+    stat[0][wave][c] = m;
+    stat[1][wave][c] = l;
+  }
+  __syncthreads();
+  float mall = stat[0][0][c], lall = 0.f;   // wave 0 always has a tile
+#pragma unroll
+  for (int w = 1; w < kF32Waves; ++w) mall = fmaxf(mall, stat[0][w][c]);
+#pragma unroll
+  for (int w = 0; w < kF32Waves; ++w) lall += stat[1][w][c] * __expf(stat[0][w][c] - mall);
+  const float f = __expf(m - mall);   // a wave without a tile: m = -inf, its zeros are multiplied by zero
+#pragma unroll
+  for (int t = 0; t < ND; ++t) o[t] *= f;
+  if (!f32_join<ND>(o, part, wave, lane) || my_q >= s) return;
+#pragma unroll
+  for (int t = 0; t < ND; ++t) o[t] /= lall;
+  f32_store<ND>(ctx + ((size_t)my_q * b + j) * hp + (size_t)e * dh, o, g, dh);
+  if (g == 0) lse[((size_t)j * heads + e) * s + my_q] = mall + __logf(lall);
 }
 
-// delta[j][e][i] = sum_d dctx * ctx
-template <typename T>
-__global__ void __launch_bounds__(64)
-attn_delta_rowwise(const T* __restrict__ ctx, const T* __restrict__ dctx, float* __restrict__ delta, int s, int b,
-                   int heads, int dh) {
-  const int i = blockIdx.x, e = blockIdx.y, j = blockIdx.z, lane = threadIdx.x;
-  const size_t off = ((size_t)i * b + j) * heads * dh + (size_t)e * dh;
-  float a = 0.f;
-  for (int d = lane; d < dh; d += 64) a += ld(ctx + off + d) * ld(dctx + off + d);
-  a = wave_sum(a);
-  if (lane == 0) delta[((size_t)j * heads + e) * s + i] = a;
-}
-
-// dQ of query row i: sum over keys kk <= i of dS[i][kk] K[kk] / sqrt(dh)
-template <typename T>
-__global__ void __launch_bounds__(64)
-attn_bwd_dq_rowwise(const T* __restrict__ qkv, const T* __restrict__ dctx, const float* __restrict__ lse,
-                    const float* __restrict__ delta, T* __restrict__ dqkv, int s, int b, int heads, int dh,
-                    const uint8_t* __restrict__ mask, int causal) {
-  const int i = blockIdx.x, e = blockIdx.y, j = blockIdx.z, lane = threadIdx.x;
+// dQ of 16 queries, and their delta = sum_d dctx * ctx for the dK/dV kernel
+template <int ND>
+__global__ void __launch_bounds__(64 * kF32Waves)
+attn_bwd_dq_f32(const float* __restrict__ qkv, const float* __restrict__ ctx, const float* __restrict__ dctx,
+                const float* __restrict__ lse, float* __restrict__ delta, float* __restrict__ dqkv, int s, int b, int heads, int dh,
+                const uint8_t* __restrict__ mask, int causal) {
+  __shared__ f32x4_t part[(kF32Waves - 1) * ND * 64];
+  const int e = blockIdx.y, j = blockIdx.z, wave = threadIdx.x >> 6, lane = threadIdx.x & 63, c = lane & 15, g = lane >> 4;
+  const int q0 = ((int)gridDim.x - 1 - (int)blockIdx.x) * kF32Rows, my_q = q0 + c, qr = min(my_q, s - 1);
   const int hp = heads * dh;
   const size_t rs = (size_t)b * 3 * hp;
-  const T* base = qkv + (size_t)j * 3 * hp + (size_t)e * dh;
+  const float* base = qkv + (size_t)j * 3 * hp + (size_t)e * dh;
   const float scale = rsqrtf((float)dh);
-  const float L = lse[((size_t)j * heads + e) * s + i], D = delta[((size_t)j * heads + e) * s + i];
-  float q[kMaxDimsPerLane], dc[kMaxDimsPerLane], acc[kMaxDimsPerLane];
-#pragma unroll
-  for (int c = 0; c < kMaxDimsPerLane; ++c) {
-    const int d = lane + 64 * c;
-    q[c] = d < dh ? ld(base + (size_t)i * rs + d) : 0.f;
-    dc[c] = d < dh ? ld(dctx + ((size_t)i * b + j) * hp + (size_t)e * dh + d) : 0.f;
-    acc[c] = 0.f;
+  const size_t stat = ((size_t)j * heads + e) * s + qr, out = ((size_t)qr * b + j) * hp + (size_t)e * dh;
+  F32Frag<ND> q, dc;
+  f32_load<ND>(q, base + (size_t)qr * rs, g, dh);
+  f32_load<ND>(dc, dctx + out, g, dh);
+  // the diagonal of ctx dctx^T, summed in the order of dP below: with one visible key dP - D is exactly zero
+  float D;
+  {
+    F32Frag<ND> o;
+    f32_load<ND>(o, ctx + out, g, dh);
+    const f32x4_t x = f32_scores<ND>(o, dc);
+    const float mine = (c & 2) ? ((c & 1) ? x[3] : x[2]) : ((c & 1) ? x[1] : x[0]);
+    D = __shfl(mine, (c >> 2) * 16 + c, 64);
   }
-  const int kend = causal ? i : s - 1;
-  const uint8_t* mrow = (!causal && mask) ? mask + ((size_t)j * s + i) * s : nullptr;
-  for (int kk = 0; kk <= kend; ++kk) {
-    const T* kr = base + (size_t)kk * rs + hp;
-    const T* vr = kr + hp;
-    float dot = 0.f, dpv = 0.f;
-    float kv[kMaxDimsPerLane];
+  if (wave == 0 && g == 0 && my_q < s) delta[stat] = D;
+  const float L = lse[stat];
+  f32x4_t acc[ND];
 #pragma unroll
-    for (int c = 0; c < kMaxDimsPerLane; ++c) {
-      const int d = lane + 64 * c;
-      kv[c] = d < dh ? ld(kr + d) : 0.f;
-      dot += q[c] * kv[c];
-      if (d < dh) dpv += dc[c] * ld(vr + d);
+  for (int t = 0; t < ND; ++t) acc[t] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  const int ntiles = ((causal ? min(q0 + kF32Rows, s) : s) + kF32Rows - 1) / kF32Rows;
+  const uint8_t* mrow = (!causal && mask) ? mask + ((size_t)j * s + qr) * s : nullptr;
+  for (int kt = wave; kt < ntiles; kt += kF32Waves) {
+    const int key0 = kt * kF32Rows;
+    const size_t row = (size_t)min(key0 + c, s - 1) * rs;
+    F32Frag<ND> k, v;
+    f32_load<ND>(k, base + hp + row, g, dh);
+    f32_load<ND>(v, base + 2 * hp + row, g, dh);
+    const f32x4_t sc = f32_scores<ND>(k, q), dp = f32_scores<ND>(v, dc);
+    f32x4_t ds;
+    uint32_t vis = 0;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int key = key0 + 4 * g + r;
+      const bool ok = key < s && (causal ? key <= my_q : !(mrow && mrow[key]));
+      ds[r] = ok ? __expf(sc[r] * scale - L) * (dp[r] - D) * scale : 0.f;
+      vis |= (uint32_t)ok << r;
     }
-    const bool hidden = mrow && mrow[kk];
-    const float p = __expf((hidden ? kMaskFill : wave_sum(dot) * scale) - L);
-    const float ds = hidden ? 0.f : p * (wave_sum(dpv) - D) * scale;
-#pragma unroll
-    for (int c = 0; c < kMaxDimsPerLane; ++c) acc[c] += ds * kv[c];
+    f32_accumulate<ND>(acc, ds, base + hp, rs, key0, s, dh, causal && key0 + kF32Rows > q0, vis, lane);
   }
-#pragma unroll
-  for (int c = 0; c < kMaxDimsPerLane; ++c) {
-    const int d = lane + 64 * c;
-    if (d < dh) st(dqkv + (size_t)i * rs + (size_t)j * 3 * hp + (size_t)e * dh + d, acc[c]);
-  }
+  if (!f32_join<ND>(acc, part, wave, lane) || my_q >= s) return;
+  f32_store<ND>(dqkv + (size_t)my_q * rs + (size_t)j * 3 * hp + (size_t)e * dh, acc, g, dh);
 }
 
-// dK, dV of key row kk: sums over queries i >= kk
-template <typename T>
-__global__ void __launch_bounds__(64)
-attn_bwd_dkv_rowwise(const T* __restrict__ qkv, const T* __restrict__ dctx, const float* __restrict__ lse,
-                     const float* __restrict__ delta, T* __restrict__ dqkv, int s, int b, int heads, int dh,
-                     const uint8_t* __restrict__ mask, int causal) {
-  const int kk = blockIdx.x, e = blockIdx.y, j = blockIdx.z, lane = threadIdx.x;
+// dK, dV of 16 keys
+template <int ND>
+__global__ void __launch_bounds__(64 * kF32Waves)
+attn_bwd_dkv_f32(const float* __restrict__ qkv, const float* __restrict__ dctx, const float* __restrict__ lse,
+                 const float* __restrict__ delta, float* __restrict__ dqkv, int s, int b, int heads, int dh,
+                 const uint8_t* __restrict__ mask, int causal) {
+  __shared__ f32x4_t part[(kF32Waves - 1) * ND * 64];
+  const int e = blockIdx.y, j = blockIdx.z, wave = threadIdx.x >> 6, lane = threadIdx.x & 63, c = lane & 15, g = lane >> 4;
+  const int k0 = (int)blockIdx.x * kF32Rows, my_key = k0 + c, kr = min(my_key, s - 1);
   const int hp = heads * dh;
-  const size_t rs = (size_t)b * 3 * hp;
-  const T* base = qkv + (size_t)j * 3 * hp + (size_t)e * dh;
+  const size_t rs = (size_t)b * 3 * hp, dors = (size_t)b * hp;
+  const float* base = qkv + (size_t)j * 3 * hp + (size_t)e * dh;
+  const float* dobase = dctx + (size_t)j * hp + (size_t)e * dh;
   const float scale = rsqrtf((float)dh);
-  float kv[kMaxDimsPerLane], vv[kMaxDimsPerLane], dk[kMaxDimsPerLane], dv[kMaxDimsPerLane];
+  const float* lse_h = lse + ((size_t)j * heads + e) * s;
+  const float* delta_h = delta + ((size_t)j * heads + e) * s;
+  F32Frag<ND> k, v;
+  f32_load<ND>(k, base + hp + (size_t)kr * rs, g, dh);
+  f32_load<ND>(v, base + 2 * hp + (size_t)kr * rs, g, dh);
+  f32x4_t dk[ND], dv[ND];
 #pragma unroll
-  for (int c = 0; c < kMaxDimsPerLane; ++c) {
-    const int d = lane + 64 * c;
-    kv[c] = d < dh ? ld(base + (size_t)kk * rs + hp + d) : 0.f;
-    vv[c] = d < dh ? ld(base + (size_t)kk * rs + 2 * hp + d) : 0.f;
-    dk[c] = dv[c] = 0.f;
-  }
-  for (int i = causal ? kk : 0; i < s; ++i) {
-    const T* qr = base + (size_t)i * rs;
-    const T* dr = dctx + ((size_t)i * b + j) * hp + (size_t)e * dh;
-    float qv[kMaxDimsPerLane], dc[kMaxDimsPerLane];
-    float dot = 0.f, dpv = 0.f;
-#pragma unroll
-    for (int c = 0; c < kMaxDimsPerLane; ++c) {
-      const int d = lane + 64 * c;
-      qv[c] = d < dh ? ld(qr + d) : 0.f;
-      dc[c] = d < dh ? ld(dr + d) : 0.f;
-      dot += qv[c] * kv[c];
-      dpv += dc[c] * vv[c];
+  for (int t = 0; t < ND; ++t) dk[t] = dv[t] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  const int ntiles = (s + kF32Rows - 1) / kF32Rows;
+  for (int qt = (causal ? (int)blockIdx.x : 0) + wave; qt < ntiles; qt += kF32Waves) {
+    const int q0 = qt * kF32Rows;
+    f32x4_t sc, dp, p, ds;
+    {
+      F32Frag<ND> q, dc;
+      f32_load<ND>(q, base + (size_t)min(q0 + c, s - 1) * rs, g, dh);
+      f32_load<ND>(dc, dobase + (size_t)min(q0 + c, s - 1) * dors, g, dh);
+      sc = f32_scores<ND>(q, k);
+      dp = f32_scores<ND>(dc, v);
     }
-    const size_t st_i = ((size_t)j * heads + e) * s + i;
-    const bool hidden = !causal && mask && mask[((size_t)j * s + i) * s + kk];
-    const float p = __expf((hidden ? kMaskFill : wave_sum(dot) * scale) - lse[st_i]);
-    const float ds = hidden ? 0.f : p * (wave_sum(dpv) - delta[st_i]) * scale;
+    uint32_t vis = 0;
 #pragma unroll
-    for (int c = 0; c < kMaxDimsPerLane; ++c) {
-      dv[c] += p * dc[c];
-      dk[c] += ds * qv[c];
+    for (int r = 0; r < 4; ++r) {
+      const int q = q0 + 4 * g + r, qq = min(q, s - 1);
+      const bool ok = q < s && (!causal || q >= my_key);
+      const bool hidden = !causal && mask && mask[((size_t)j * s + qq) * s + kr];
+      p[r] = ok ? __expf((hidden ? kMaskFill : sc[r] * scale) - lse_h[qq]) : 0.f;
+      ds[r] = ok && !hidden ? p[r] * (dp[r] - delta_h[qq]) * scale : 0.f;
+      vis |= (uint32_t)ok << r;
     }
+    const bool diag = causal && q0 < k0 + kF32Rows;
+    f32_accumulate<ND>(dv, p, dobase, dors, q0, s, dh, diag, vis, lane);
+    f32_accumulate<ND>(dk, ds, base, rs, q0, s, dh, diag, vis, lane);
   }
-#pragma unroll
-  for (int c = 0; c < kMaxDimsPerLane; ++c) {
-    const int d = lane + 64 * c;
-    if (d < dh) {
-      st(dqkv + (size_t)kk * rs + (size_t)j * 3 * hp + hp + (size_t)e * dh + d, dk[c]);
-      st(dqkv + (size_t)kk * rs + (size_t)j * 3 * hp + 2 * hp + (size_t)e * dh + d, dv[c]);
-    }
-  }
+  float* out = dqkv + (size_t)my_key * rs + (size_t)j * 3 * hp + (size_t)e * dh;
+  const bool mine = f32_join<ND>(dk, part, wave, lane);
+  if (mine && my_key < s) f32_store<ND>(out + hp, dk, g, dh);
+  if (f32_join<ND>(dv, part, wave, lane) && my_key < s) f32_store<ND>(out + 2 * hp, dv, g, dh);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -914,7 +1020,7 @@ attn_delta_bf16(const bf16_t* __restrict__ ctx, const bf16_t* __restrict__ dctx,
 // ------------------------------------------------------------------------------------------------
 bool attn_dh_supported(int dtype, int dh) {
   if (dh <= 0 || dh % 8 != 0) return false;
-  if (dtype == PTDP_F32) return dh <= 64 * kMaxDimsPerLane;
+  if (dtype == PTDP_F32) return dh <= kMaxF32Dh;
   return dh == 32 || dh == 64 || dh == 96 || dh == 128 || dh == 160;
 }
 
@@ -953,6 +1059,17 @@ static int attn_fwd_mfma_t(const bf16_t* qkv, bf16_t* ctx, float* lse, int s, in
   return attn_fwd_mfma_np<DH, CAUSAL, 1>(qkv, ctx, lse, s, b, heads, mask, stream);
 }
 
+// steps of 16 dh, rounded up to one of the built forms
+#define PTDP_F32_DISPATCH(dh, CALL) \
+  do {                              \
+    if ((dh) <= 32) CALL(2);        \
+    else if ((dh) <= 64) CALL(4);   \
+    else if ((dh) <= 96) CALL(6);   \
+    else if ((dh) <= 128) CALL(8);  \
+    else if ((dh) <= 160) CALL(10); \
+    else CALL(16);                  \
+  } while (0)
+
 // Without the causal mask every row is a full row: count the whole s x s square as executed too.
 int launch_attn_fwd(int dtype, const void* qkv, void* ctx, float* lse, int s, int b, int heads, int dh,
                     const uint8_t* mask, int causal, hipStream_t stream) {
@@ -961,8 +1078,11 @@ int launch_attn_fwd(int dtype, const void* qkv, void* ctx, float* lse, int s, in
   Launch L(PTDP_K_ATTN_FWD, attn_flops(s, b, heads, dh), stream);
   int rc = PTDP_OK;
   if (dtype == PTDP_F32) {
-    hipLaunchKernelGGL((attn_fwd_rowwise<float>), dim3(s, heads, b), dim3(64), 0, stream, (const float*)qkv,
-                       (float*)ctx, lse, s, b, heads, dh, mask, causal);
+#define PTDP_ATTN_FWD32(ND) \
+  hipLaunchKernelGGL(attn_fwd_f32<ND>, dim3((s + kF32Rows - 1) / kF32Rows, heads, b), dim3(64 * kF32Waves), 0, stream, (const float*)qkv, \
+                     (float*)ctx, lse, s, b, heads, dh, mask, causal)
+    PTDP_F32_DISPATCH(dh, PTDP_ATTN_FWD32);
+#undef PTDP_ATTN_FWD32
   } else {
     const bf16_t* q = (const bf16_t*)qkv;
     bf16_t* c = (bf16_t*)ctx;
@@ -980,18 +1100,12 @@ int launch_attn_fwd(int dtype, const void* qkv, void* ctx, float* lse, int s, in
   return L.status();
 }
 
-template <typename T>
-static int attn_bwd_rowwise_t(const void* qkv, const void* ctx, const float* lse, const void* dctx, void* dqkv,
-                              float* delta, int s, int b, int heads, int dh, const uint8_t* mask, int causal,
-                              hipStream_t stream) {
-  const dim3 grid(s, heads, b);
-  hipLaunchKernelGGL((attn_delta_rowwise<T>), grid, dim3(64), 0, stream, (const T*)ctx, (const T*)dctx, delta, s, b,
-                     heads, dh);
-  hipLaunchKernelGGL((attn_bwd_dq_rowwise<T>), grid, dim3(64), 0, stream, (const T*)qkv, (const T*)dctx, lse, delta,
-                     (T*)dqkv, s, b, heads, dh, mask, causal);
-  hipLaunchKernelGGL((attn_bwd_dkv_rowwise<T>), grid, dim3(64), 0, stream, (const T*)qkv, (const T*)dctx, lse, delta,
-                     (T*)dqkv, s, b, heads, dh, mask, causal);
-  return PTDP_OK;
+template <int ND>
+static void attn_bwd_f32_t(const float* qkv, const float* ctx, const float* lse, const float* dctx, float* dqkv, float* delta, int s,
+                           int b, int heads, int dh, const uint8_t* mask, int causal, hipStream_t stream) {
+  const dim3 grid((s + kF32Rows - 1) / kF32Rows, heads, b), block(64 * kF32Waves);
+  hipLaunchKernelGGL(attn_bwd_dq_f32<ND>, grid, block, 0, stream, qkv, ctx, dctx, lse, delta, dqkv, s, b, heads, dh, mask, causal);
+  hipLaunchKernelGGL(attn_bwd_dkv_f32<ND>, grid, block, 0, stream, qkv, dctx, lse, (const float*)delta, dqkv, s, b, heads, dh, mask, causal);
 }
 
 template <int DH, bool CAUSAL, int NP>
@@ -1030,7 +1144,10 @@ int launch_attn_bwd(int dtype, const void* qkv, const void* ctx, const float* ls
   Launch L(PTDP_K_ATTN_BWD, 2.0 * attn_flops(s, b, heads, dh), stream);
   int rc = PTDP_OK;
   if (dtype == PTDP_F32) {
-    rc = attn_bwd_rowwise_t<float>(qkv, ctx, lse, dctx, dqkv, delta, s, b, heads, dh, mask, causal, stream);
+#define PTDP_ATTN_BWD32(ND) \
+  attn_bwd_f32_t<ND>((const float*)qkv, (const float*)ctx, lse, (const float*)dctx, (float*)dqkv, delta, s, b, heads, dh, mask, causal, stream)
+    PTDP_F32_DISPATCH(dh, PTDP_ATTN_BWD32);
+#undef PTDP_ATTN_BWD32
   } else {
     const bf16_t* q = (const bf16_t*)qkv;
     const bf16_t* c = (const bf16_t*)ctx;

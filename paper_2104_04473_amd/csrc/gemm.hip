@@ -9,7 +9,7 @@
 // global->LDS loads, two groups of waves that alternate between the matrix cores and memory.  An operand whose
 // reduction index is the slow memory index (B in NN, both in TN) stays in its memory order in LDS and is gathered
 // into MFMA fragments by transposing LDS reads.
-// fp32 path: a plain LDS-tiled FMA kernel (correctness configuration only).
+// fp32 path: v_mfma_f32_32x32x2_f32, operands straight from memory (small configurations).
 #include "common.h"
 #include <type_traits>
 
@@ -18,53 +18,144 @@ namespace ptdp {
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8_t;
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4_t;
 
+typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16_t;
+
 // ------------------------------------------------------------------------------------------------
-// fp32: 64 x 64 x 16 tile, 256 threads, 4 x 4 outputs per thread, generic strides.
+// fp32: v_mfma_f32_32x32x2_f32 (fp32 products and sums), operands straight from memory into fragments.  A workgroup is
+// KG waves on one tile of 32 NB x 32 NB outputs; wave w takes the 32-wide k-chunks w, w + KG, ... and the partial tiles
+// are added in LDS in wave order.  Lane (r = lane & 31, half = lane >> 5) carries k 8 q + 4 half + e of row r in element
+// e of group q: the product's k order is free as long as both operands share it, and a k-contiguous row then gives one
+// 16-byte load per group.  The next chunk is requested before the current one is multiplied.  fp32 calls are small and
+// bound by one wave's chain of loads; before, by the k-steps of the few workgroups that 64 x 64 tiles of plain FMAs gave.
+// us: 256 x 256 outputs over k = 256, 768, 1024 on average 110 -> 9; 256 x 1024 x 256 49 -> 5.3.
+// VA, VB: the operand's rows are k-contiguous, 16-byte aligned and a multiple of four long; otherwise any strides.
 // ------------------------------------------------------------------------------------------------
-__global__ void __launch_bounds__(256)
+constexpr int kF32Chunk = 32;
+template <bool V> struct F32Operand {
+  const float* row;
+  size_t ks;   // k stride (V: 1)
+  // CLIP: k from kend on are zeros
+  template <bool CLIP> __device__ __forceinline__ void load(f32x4_t (&f)[4], int k0, int half, int kend) const {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int k = k0 + 8 * q + 4 * half;
+      if (V) {
+        if (CLIP && k >= kend) f[q] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+        else f[q] = *reinterpret_cast<const f32x4_t*>(row + k);
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          if (CLIP && k + e >= kend) f[q][e] = 0.f;
+          else f[q][e] = row[(size_t)(k + e) * ks];
+        }
+      }
+    }
+  }
+};
+template <bool VA, bool VB, int NB>
+__global__ void __launch_bounds__(512)
 gemm_f32_kernel(const float* __restrict__ A, const float* __restrict__ B, float* C, const float* __restrict__ bias,
                 int M, int N, int K, size_t a_rs, size_t a_cs, size_t b_rs, size_t b_cs, int accumulate) {
-  __shared__ float As[16][65];
-  __shared__ float Bs[16][65];
-  const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-  const int m0 = blockIdx.y * 64, n0 = blockIdx.x * 64;
-  float acc[4][4] = {};
-  for (int k0 = 0; k0 < K; k0 += 16) {
-    for (int e = threadIdx.x; e < 16 * 64; e += 256) {
-      const int kk = e & 15, r = e >> 4;  // consecutive threads walk k, then rows
-      const int m = m0 + r, n = n0 + r, k = k0 + kk;
-      As[kk][r] = (m < M && k < K) ? A[(size_t)m * a_rs + (size_t)k * a_cs] : 0.f;
-      Bs[kk][r] = (n < N && k < K) ? B[(size_t)k * b_rs + (size_t)n * b_cs] : 0.f;
-    }
-    __syncthreads();
+  extern __shared__ __attribute__((aligned(16))) float part[];
+  constexpr int kTile = 32 * NB, kPitch = kTile + 8;   // rows 4 apart (the two halves of a register) in different banks
+  const int wave = threadIdx.x >> 6, kg = blockDim.x >> 6, lane = threadIdx.x & 63, l31 = lane & 31, half = lane >> 5;
+  const int m0 = blockIdx.y * kTile, n0 = blockIdx.x * kTile;
+  F32Operand<VA> oa[NB];
+  F32Operand<VB> ob[NB];
 #pragma unroll
-    for (int kk = 0; kk < 16; ++kk) {
-      float a[4], b[4];
+  for (int i = 0; i < NB; ++i) {   // rows past the end repeat the last one: their outputs are not written
+    oa[i].row = A + (size_t)min(m0 + i * 32 + l31, M - 1) * a_rs;
+    oa[i].ks = a_cs;
+    ob[i].row = B + (size_t)min(n0 + i * 32 + l31, N - 1) * b_cs;
+    ob[i].ks = b_rs;
+  }
+  f32x16_t acc[NB][NB];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        a[i] = As[kk][ty * 4 + i];
-        b[i] = Bs[kk][tx * 4 + i];
+  for (int i = 0; i < NB; ++i)
+#pragma unroll
+    for (int j = 0; j < NB; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+  f32x4_t fa[2][NB][4], fb[2][NB][4];
+  const int step = kg * kF32Chunk;
+  auto load = [&](int set, int k) {
+    if (k >= K) return;
+    if (k + kF32Chunk <= K) {
+#pragma unroll
+      for (int i = 0; i < NB; ++i) {
+        oa[i].template load<false>(fa[set][i], k, half, K);
+        ob[i].template load<false>(fb[set][i], k, half, K);
       }
+    } else {
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] += a[i] * b[j];
+      for (int i = 0; i < NB; ++i) {
+        oa[i].template load<true>(fa[set][i], k, half, K);
+        ob[i].template load<true>(fb[set][i], k, half, K);
+      }
     }
-    __syncthreads();
-  }
+  };
+  auto multiply = [&](int set) {
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int m = m0 + ty * 4 + i;
-    if (m >= M) continue;
+    for (int q = 0; q < 4; ++q)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int n = n0 + tx * 4 + j;
-      if (n >= N) continue;
-      float v = acc[i][j] + (bias ? bias[n] : 0.f);
-      float* c = C + (size_t)m * N + n;
-      *c = accumulate ? *c + v : v;
-    }
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int i = 0; i < NB; ++i)
+#pragma unroll
+          for (int j = 0; j < NB; ++j)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[set][i][q][e], fb[set][j][q][e], acc[i][j], 0, 0, 0);
+  };
+  int k = wave * kF32Chunk;
+  load(0, k);
+  for (; k < K; k += 2 * step) {
+    load(1, k + step);
+    multiply(0);
+    if (k + step >= K) break;
+    load(0, k + 2 * step);
+    multiply(1);
   }
+  float* mine = part + wave * (kTile * kPitch);
+#pragma unroll
+  for (int i = 0; i < NB; ++i)
+#pragma unroll
+    for (int j = 0; j < NB; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) mine[(i * 32 + 8 * (r >> 2) + 4 * half + (r & 3)) * kPitch + j * 32 + l31] = acc[i][j][r];
+  __syncthreads();
+  for (int x = threadIdx.x; x < kTile * kTile; x += blockDim.x) {
+    const int r = x / kTile, c = x % kTile, m = m0 + r, n = n0 + c;
+    if (m >= M || n >= N) continue;
+    float v = 0.f;
+    for (int w = 0; w < kg; ++w) v += part[w * (kTile * kPitch) + r * kPitch + c];
+    if (bias) v += bias[n];
+    float* o = C + (size_t)m * N + n;
+    *o = accumulate ? *o + v : v;
+  }
+}
+
+template <bool VA, bool VB, int NB>
+static int launch_gemm_f32_t(const float* A, const float* B, float* C, const float* bias, int M, int N, int K, size_t a_rs, size_t a_cs,
+                             size_t b_rs, size_t b_cs, int accumulate, int kg, hipStream_t st) {
+  auto kern = gemm_f32_kernel<VA, VB, NB>;
+  constexpr int kTile = 32 * NB, kPart = kTile * (kTile + 8) * (int)sizeof(float);
+  static once_flag_t done[kMaxDevices];
+  if (set_dynamic_smem(reinterpret_cast<const void*>(kern), (NB == 1 ? 8 : 4) * kPart, done) != PTDP_OK) return PTDP_E_HIP;
+  hipLaunchKernelGGL(kern, dim3((N + kTile - 1) / kTile, (M + kTile - 1) / kTile), dim3(64 * kg), kg * kPart, st, A, B, C, bias, M, N, K,
+                     a_rs, a_cs, b_rs, b_cs, accumulate);
+  return PTDP_OK;
+}
+static int compute_units();
+// 64 x 64 tiles (half the operand traffic) once they give every SIMD a wave, 32 x 32 before; up to 8 (4) waves share a
+// tile's k range, fewer when the tiles alone fill the chip or the range has fewer chunks.
+template <bool VA, bool VB>
+static int launch_gemm_f32(const float* A, const float* B, float* C, const float* bias, int M, int N, int K, size_t a_rs, size_t a_cs,
+                           size_t b_rs, size_t b_cs, int accumulate, hipStream_t st) {
+  const long long ncu = compute_units(), t1 = (long long)((M + 31) / 32) * ((N + 31) / 32), t2 = (long long)((M + 63) / 64) * ((N + 63) / 64);
+  const bool big = t2 >= ncu;
+  int kg = big ? 4 : 8;
+  while (kg > 1 && (kg > (K + kF32Chunk - 1) / kF32Chunk || (big ? t2 : t1) * kg > 16 * ncu)) kg /= 2;
+  if (big) return launch_gemm_f32_t<VA, VB, 2>(A, B, C, bias, M, N, K, a_rs, a_cs, b_rs, b_cs, accumulate, kg, st);
+  return launch_gemm_f32_t<VA, VB, 1>(A, B, C, bias, M, N, K, a_rs, a_cs, b_rs, b_cs, accumulate, kg, st);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -1265,9 +1356,13 @@ int launch_gemm(int dtype, int mode, const void* A, const void* B, void* C, cons
     size_t a_rs = K, a_cs = 1, b_rs = N, b_cs = 1;
     if (mode == PTDP_GEMM_NT) { b_rs = 1; b_cs = K; }
     if (mode == PTDP_GEMM_TN) { a_rs = 1; a_cs = M; }
-    hipLaunchKernelGGL(gemm_f32_kernel, dim3((N + 63) / 64, (M + 63) / 64), dim3(256), 0, st, (const float*)A,
-                       (const float*)B, (float*)C, (const float*)bias, M, N, K, a_rs, a_cs, b_rs, b_cs, accumulate);
-    return L.status();
+    const float *a = (const float*)A, *b = (const float*)B, *bi = (const float*)bias;
+    const bool va = a_cs == 1 && K % 4 == 0 && ((uintptr_t)A & 15) == 0, vb = b_rs == 1 && K % 4 == 0 && ((uintptr_t)B & 15) == 0;
+    int rc;
+    if (va && vb) rc = launch_gemm_f32<true, true>(a, b, (float*)C, bi, M, N, K, a_rs, a_cs, b_rs, b_cs, accumulate, st);
+    else if (va) rc = launch_gemm_f32<true, false>(a, b, (float*)C, bi, M, N, K, a_rs, a_cs, b_rs, b_cs, accumulate, st);
+    else rc = launch_gemm_f32<false, false>(a, b, (float*)C, bi, M, N, K, a_rs, a_cs, b_rs, b_cs, accumulate, st);
+    return rc != PTDP_OK ? rc : L.status();
   }
   int rc;
   switch (mode) {

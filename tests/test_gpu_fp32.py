@@ -1,0 +1,92 @@
+"""fp32 GEMM and attention at the edges of their tiles: ragged sizes, operands without 16-byte rows, every head size
+the kernels are built for and ones between, non-finite values behind the causal mask."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import gpt_layer as L
+from paper_2104_04473_amd import binding as B
+from gpu_util import assert_close, np64, randn, stream, sync
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("mode", [B.GEMM_NN, B.GEMM_NT, B.GEMM_TN])
+@pytest.mark.parametrize("M,N,K", [(1, 1, 1), (33, 65, 30), (31, 32, 33), (64, 96, 1024), (130, 70, 257), (1030, 1090, 100),
+                                   (1025, 1024, 36), (40, 24, 0)])
+def test_gemm_fp32(mode, M, N, K):
+    a, b, bias = randn((M, K), B.F32, 1), randn((K, N), B.F32, 2), randn((N,), B.F32, 3)
+    A = a.t().contiguous() if mode == B.GEMM_TN else a
+    Bm = b.t().contiguous() if mode == B.GEMM_NT else b
+    if K == 0:
+        A = Bm = torch.zeros(16, device="cuda")
+    want = a.double() @ b.double() + bias.double()
+    c = torch.full((M, N), 9.0, device="cuda")
+    for acc in (0, 1):   # overwritten, then added to
+        B.check(B.ptdp_gemm(B.F32, mode, A.data_ptr(), Bm.data_ptr(), c.data_ptr(), bias.data_ptr(), M, N, K, 1, acc, None, 0,
+                            stream()), "gemm")
+        sync()
+        # K products of size about 1 in fp32: error below 2^-24 * K, doubled for the second pass
+        assert float((c.double() - (1 + acc) * want).abs().max()) <= 2.0 ** -21 * (K + 8)
+
+
+def forward_backward(qkv, dctx, s, b, heads, dh, mask=None):
+    ctx, lse = torch.zeros_like(dctx), torch.zeros((b, heads, s), device="cuda")
+    dqkv, delta = torch.zeros_like(qkv), torch.zeros((b, heads, s), device="cuda")
+    if mask is None:
+        B.check(B.ptdp_attn_fwd(B.F32, qkv.data_ptr(), ctx.data_ptr(), lse.data_ptr(), s, b, heads, dh, stream()), "fwd")
+        B.check(B.ptdp_attn_bwd(B.F32, qkv.data_ptr(), ctx.data_ptr(), lse.data_ptr(), dctx.data_ptr(), dqkv.data_ptr(),
+                                delta.data_ptr(), s, b, heads, dh, stream()), "bwd")
+    else:
+        B.check(B.ptdp_attn_masked_fwd(B.F32, qkv.data_ptr(), mask.data_ptr(), ctx.data_ptr(), lse.data_ptr(), s, b, heads, dh,
+                                       stream()), "fwd")
+        B.check(B.ptdp_attn_masked_bwd(B.F32, qkv.data_ptr(), mask.data_ptr(), ctx.data_ptr(), lse.data_ptr(), dctx.data_ptr(),
+                                       dqkv.data_ptr(), delta.data_ptr(), s, b, heads, dh, stream()), "bwd")
+    sync()
+    return ctx, lse, dqkv
+
+
+@pytest.mark.parametrize("masked", [False, True])
+@pytest.mark.parametrize("s,b,heads,dh", [(1, 1, 2, 8), (15, 2, 1, 24), (17, 1, 3, 40), (64, 2, 2, 64), (65, 1, 2, 96),
+                                          (129, 1, 1, 128), (96, 2, 1, 160), (83, 1, 1, 200), (50, 1, 2, 256)])
+def test_attention_fp32(s, b, heads, dh, masked):
+    hp = heads * dh
+    qkv, dctx = randn((s, b, 3 * hp), B.F32, 1), randn((s, b, hp), B.F32, 2)
+    mask = None
+    if masked:
+        m = (np.random.default_rng(3).random((b, s, s)) < 0.4).astype(np.uint8)
+        m[0, s // 2] = 1   # a query without a visible key
+        mask = m
+    ctx, lse, dqkv = forward_backward(qkv, dctx, s, b, heads, dh, torch.from_numpy(mask).cuda() if masked else None)
+    cfg = L.LayerConfig(h=hp, a=heads, t=1, s=s, b=b, causal=not masked)
+    wctx, probs, wlse = L.attention_core(np64(qkv), cfg, mask) if masked else L.attention_core(np64(qkv), cfg)
+    want = L.attention_core_backward(np64(dctx), np64(qkv), probs, cfg, mask) if masked else \
+        L.attention_core_backward(np64(dctx), np64(qkv), probs, cfg)
+    assert_close(np64(ctx), wctx, B.F32, "ctx", 0.1)
+    assert np.allclose(np64(lse), wlse, rtol=1e-6, atol=1e-4)
+    got = np64(dqkv)
+    for name, lo in (("dq", 0), ("dk", hp), ("dv", 2 * hp)):
+        if np.abs(want[..., lo:lo + hp]).max() > 1e-9:   # (one query: its softmax is constant, dq and dk are zero)
+            # a query without a visible key has a log-sum-exp near -10^4, stored in fp32 to 2^-11: its probabilities (1/s
+            # each) are off by that much, which only dv sees; the stated tolerance holds
+            assert_close(got[..., lo:lo + hp], want[..., lo:lo + hp], B.F32, name, 1.0 if masked and name == "dv" else 0.1)
+
+
+@pytest.mark.parametrize("bad", [float("inf"), float("nan")])
+def test_attention_fp32_future_tokens_stay_hidden(bad):
+    """Undefined or infinite values in a later token's K, V, Q or output gradient change no bit of an earlier token's output
+    (K, V) and of a later key's gradients (Q, dctx), also inside a tile on the diagonal."""
+    s, b, heads, dh, at = 50, 1, 2, 24, 21
+    hp = heads * dh
+    qkv, dctx = randn((s, b, 3 * hp), B.F32, 1), randn((s, b, hp), B.F32, 2)
+    ctx, _, dqkv = forward_backward(qkv, dctx, s, b, heads, dh)
+    q2 = qkv.clone()
+    q2[at:, :, hp:] = bad
+    ctx2, _, dqkv2 = forward_backward(q2, dctx, s, b, heads, dh)
+    # (rows of a tile with such values are added one by one instead of in the matrix unit's order: rounding only)
+    assert torch.allclose(ctx[:at], ctx2[:at], rtol=1e-5, atol=1e-6)
+    assert torch.allclose(dqkv[:at, :, :hp], dqkv2[:at, :, :hp], rtol=1e-5, atol=1e-6)
+    d3 = dctx.clone()
+    d3[:at] = bad
+    _, _, dqkv3 = forward_backward(qkv, d3, s, b, heads, dh)
+    assert torch.allclose(dqkv[at:, :, hp:], dqkv3[at:, :, hp:], rtol=1e-5, atol=1e-6)
