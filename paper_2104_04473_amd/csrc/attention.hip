@@ -660,8 +660,8 @@ attn_fwd_mfma(const bf16_t* __restrict__ qkv, bf16_t* __restrict__ ctx, float* _
 // tiles of its own in LDS and pair 1 hands its sums to pair 0 at the end (see the dK/dV kernel below for when).
 template <int DH, bool CAUSAL, int NP>
 __global__ void __launch_bounds__(NP * kAttnThreads, DH >= 96 ? 1 : 2)
-attn_bwd_dq_mfma(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ dctx, const float* __restrict__ lse,
-                 const float* __restrict__ delta, bf16_t* __restrict__ dqkv, int s, int b, int heads,
+attn_bwd_dq_mfma(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ ctx, const bf16_t* __restrict__ dctx,
+                 const float* __restrict__ lse, float* __restrict__ delta, bf16_t* __restrict__ dqkv, int s, int b, int heads,
                  const uint8_t* __restrict__ mask) {
   constexpr int NKK = DH / 16, NDT = DH / 32;
   extern __shared__ __attribute__((aligned(16))) char smem_all[];
@@ -684,15 +684,29 @@ attn_bwd_dq_mfma(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ dctx
   const float scale = rsqrtf((float)DH), c2 = scale * 1.4426950408889634f;
   const size_t stat = ((size_t)j * heads + e) * s + my_q;
   const float L2 = valid ? lse[stat] * 1.4426950408889634f : 0.f;
-  const float D = valid ? delta[stat] : 0.f;
 
   bf16x8_t qf[NKK], dof[NKK];
-  const bf16_t* dorow = dctx + ((size_t)min(my_q, s - 1) * b + j) * hp + (size_t)e * DH;
+  const size_t out_row = ((size_t)min(my_q, s - 1) * b + j) * hp + (size_t)e * DH;
 #pragma unroll
   for (int kk = 0; kk < NKK; ++kk) {
     qf[kk] = frag_global(base + (size_t)min(my_q, s - 1) * rs, valid, kk, half);
-    dof[kk] = frag_global(dorow, valid, kk, half);
+    dof[kk] = frag_global(dctx + out_row, valid, kk, half);
   }
+  // delta = sum_d dctx * ctx: the diagonal of ctx dctx^T, summed in the order of dP below (with one visible key dP - D is
+  // exactly zero); the dK/dV kernel, launched next, reads it from memory.  In a launch of its own it took 8 to 61 us.
+  float D;
+  {
+    f32x16_t x = zero16();
+#pragma unroll
+    for (int kk = 0; kk < NKK; ++kk)
+      x = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_global(ctx + out_row, valid, kk, half), dof[kk], x, 0, 0, 0);
+    // row l31 of column l31: register (l31 & 3) + 4 * (l31 >> 3) of the lane of half (l31 >> 2) & 1
+    float mine = x[0];
+#pragma unroll
+    for (int r = 1; r < 16; ++r) mine = (l31 & 3) + 4 * (l31 >> 3) == r ? x[r] : mine;
+    D = __shfl(mine, ((l31 >> 2) & 1) * 32 + l31, 64);
+  }
+  if (pair == 0 && half == 0 && valid) delta[stat] = D;
   f32x16_t acc[NDT];
 #pragma unroll
   for (int d = 0; d < NDT; ++d) acc[d] = zero16();
@@ -796,6 +810,33 @@ attn_bwd_dq_mfma(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ dctx
 
 constexpr int kMaskLdsStride = 68;   // bytes per key row of the staged mask tile ([key][query], padded)
 
+// A 64 x 64 tile of the mask on its way to LDS as [key][query], so that a lane reads four queries of its key at once.  A
+// thread carries two blocks of 4 queries x 4 keys: four words of four keys, turned by byte permutes into four words of
+// four queries (byte loads and stores, one per element: 98 us for the kernel at 4 samples x 16 heads x 512, now 35).
+struct MaskTile {
+  uint32_t v[2][4];
+  __device__ __forceinline__ void load(const uint8_t* __restrict__ mask_j, int q0, int key0, int s, bool aligned, int tid) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int blk = tid + i * kAttnThreads, key = key0 + 4 * (blk & 15), q = q0 + 4 * (blk >> 4);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) v[i][r] = mask_word(mask_j + (size_t)min(q + r, s - 1) * s, key, s, aligned);
+    }
+  }
+  __device__ __forceinline__ void store(uint8_t* lds, int tid) const {
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int blk = tid + i * kAttnThreads, key = 4 * (blk & 15), ql = 4 * (blk >> 4);
+      const uint32_t a = __builtin_amdgcn_perm(v[i][1], v[i][0], 0x05010400u), b = __builtin_amdgcn_perm(v[i][1], v[i][0], 0x07030602u);
+      const uint32_t c = __builtin_amdgcn_perm(v[i][3], v[i][2], 0x05010400u), d = __builtin_amdgcn_perm(v[i][3], v[i][2], 0x07030602u);
+      const uint32_t t[4] = {__builtin_amdgcn_perm(c, a, 0x05040100u), __builtin_amdgcn_perm(c, a, 0x07060302u),
+                             __builtin_amdgcn_perm(d, b, 0x05040100u), __builtin_amdgcn_perm(d, b, 0x07060302u)};
+#pragma unroll
+      for (int k = 0; k < 4; ++k) *reinterpret_cast<uint32_t*>(lds + (key + k) * kMaskLdsStride + ql) = t[k];
+    }
+  }
+};
+
 // dK/dV: a workgroup owns 64 keys; wave w of a pair owns keys 32 w .. 32 w + 31.  NP = 1: one pair of waves walks all
 // 64-query tiles.  NP = 2: two pairs; pair p walks every second tile (first + p, first + p + 2, ...) with tiles of its
 // own in LDS, and at the end pair 1 hands its sums to pair 0 through LDS, added in that fixed order.  The workgroup
@@ -860,8 +901,12 @@ attn_bwd_dkv_mfma(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ dct
   TileMap<kPrefetch ? DH : 32> qmap, domap;
   TileRegs<kPrefetch ? DH : 32> qr, dor;
   float lse_r = 0.f, delta_r = 0.f;
+  MaskTile mt;
+  const uint8_t* mask_j = use_mask ? mask + (size_t)j * s * s : nullptr;
+  const bool aligned = (s & 3) == 0;
   auto fetch = [&](int q0) {
     if constexpr (kPrefetch) {
+      if (use_mask) mt.load(mask_j, q0, kblk * kBQ, s, aligned, tid);
       qmap.load(qr, base, rs, q0, s);
       domap.load(dor, dobase, dors, q0, s);
       if (tid < kBKV) {
@@ -903,12 +948,9 @@ attn_bwd_dkv_mfma(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ dct
           delta_lds[tid] = q < s ? delta_h[q] : 0.f;
         }
       }
-      if (use_mask) {   // this tile of the mask, transposed to [key][query] so that a lane reads 4 queries at once
-        for (int idx = tid; idx < kBKV * kBQ; idx += kAttnThreads) {
-          const int ql = idx / kBQ, kl = idx % kBQ;
-          const int q = q0 + ql, key = kblk * kBQ + kl;
-          mask_lds[kl * kMaskLdsStride + ql] = (q < s && key < s) ? mask[((size_t)j * s + q) * s + key] : (uint8_t)0;
-        }
+      if (use_mask) {
+        if constexpr (!kPrefetch) mt.load(mask_j, q0, kblk * kBQ, s, aligned, tid);
+        mt.store(mask_lds, tid);
       }
     }
     __syncthreads();
@@ -985,34 +1027,6 @@ attn_bwd_dkv_mfma(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ dct
     store_cols<NDT>(out + hp, dk, scale, half);
     store_cols<NDT>(out + 2 * hp, dv, 1.f, half);
   }
-}
-
-// delta[j][e][i] = sum_d dctx[i][j][e][d] * ctx[i][j][e][d]; one wave per (token, head), 4 per block
-__global__ void __launch_bounds__(256)
-attn_delta_bf16(const bf16_t* __restrict__ ctx, const bf16_t* __restrict__ dctx, float* __restrict__ delta, int s, int b,
-                int heads, int dh) {
-  const int lane = threadIdx.x & 63;
-  const size_t row = (size_t)blockIdx.x * 4 + (threadIdx.x >> 6);  // (token, head) pair index
-  const size_t nrows = (size_t)s * b * heads;
-  if (row >= nrows) return;
-  const size_t tok = row / heads;
-  const int e = (int)(row % heads);
-  const int i = (int)(tok / b), j = (int)(tok % b);
-  const bf16_t* c = ctx + row * dh;
-  const bf16_t* d = dctx + row * dh;
-  float a = 0.f;
-  for (int v = lane; v < dh / 8; v += 64) {
-    Vec16<bf16_t> x, y;
-    float xf[8], yf[8];
-    x.load(c + v * 8);
-    y.load(d + v * 8);
-    x.unpack(xf);
-    y.unpack(yf);
-#pragma unroll
-    for (int t = 0; t < 8; ++t) a += xf[t] * yf[t];
-  }
-  a = wave_sum(a);
-  if (lane == 0) delta[((size_t)j * heads + e) * s + i] = a;
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -1109,8 +1123,8 @@ static void attn_bwd_f32_t(const float* qkv, const float* ctx, const float* lse,
 }
 
 template <int DH, bool CAUSAL, int NP>
-static int attn_bwd_mfma_np(const bf16_t* qkv, const bf16_t* dctx, const float* lse, const float* delta, bf16_t* dqkv, int s,
-                            int b, int heads, const uint8_t* mask, hipStream_t stream) {
+static int attn_bwd_mfma_np(const bf16_t* qkv, const bf16_t* ctx, const bf16_t* dctx, const float* lse, float* delta, bf16_t* dqkv,
+                            int s, int b, int heads, const uint8_t* mask, hipStream_t stream) {
   constexpr int smem_dq = NP * 2 * TileGeom<DH>::BYTES;   // (NP = 2: the final sums, 2 x DH x 256 bytes, fit in the tiles)
   constexpr int smem_dkv = NP == 2 ? DkvLds<DH, CAUSAL>::kBytes2 : DkvLds<DH, CAUSAL>::kPair;
   static once_flag_t done_dq[kMaxDevices], done_dkv[kMaxDevices];
@@ -1118,23 +1132,21 @@ static int attn_bwd_mfma_np(const bf16_t* qkv, const bf16_t* dctx, const float* 
       set_dynamic_smem(reinterpret_cast<const void*>(attn_bwd_dkv_mfma<DH, CAUSAL, NP>), smem_dkv, done_dkv) != PTDP_OK)
     return PTDP_E_HIP;
   const dim3 grid(attn_grid((s + kBQ - 1) / kBQ, heads, b));
-  hipLaunchKernelGGL((attn_bwd_dkv_mfma<DH, CAUSAL, NP>), grid, dim3(NP * kAttnThreads), smem_dkv, stream, qkv, dctx, lse, delta,
+  // dQ first: it writes delta
+  hipLaunchKernelGGL((attn_bwd_dq_mfma<DH, CAUSAL, NP>), grid, dim3(NP * kAttnThreads), smem_dq, stream, qkv, ctx, dctx, lse, delta,
                      dqkv, s, b, heads, mask);
-  hipLaunchKernelGGL((attn_bwd_dq_mfma<DH, CAUSAL, NP>), grid, dim3(NP * kAttnThreads), smem_dq, stream, qkv, dctx, lse, delta,
-                     dqkv, s, b, heads, mask);
+  hipLaunchKernelGGL((attn_bwd_dkv_mfma<DH, CAUSAL, NP>), grid, dim3(NP * kAttnThreads), smem_dkv, stream, qkv, dctx, lse,
+                     (const float*)delta, dqkv, s, b, heads, mask);
   return PTDP_OK;
 }
 template <int DH, bool CAUSAL>
 static int attn_bwd_mfma_t(const bf16_t* qkv, const bf16_t* ctx, const float* lse, const bf16_t* dctx, bf16_t* dqkv,
                            float* delta, int s, int b, int heads, const uint8_t* mask, hipStream_t stream) {
-  const size_t nrows = (size_t)s * b * heads;
-  hipLaunchKernelGGL(attn_delta_bf16, dim3((unsigned)((nrows + 3) / 4)), dim3(256), 0, stream, ctx, dctx, delta, s, b,
-                     heads, DH);
   // few workgroups: the longest one sets the time, so split its walk over two pairs of waves
   const long long wgs = (long long)((s + kBQ - 1) / kBQ) * heads * b;
   if (wgs <= attn_resident_pairs())
-    return attn_bwd_mfma_np<DH, CAUSAL, 2>(qkv, dctx, lse, delta, dqkv, s, b, heads, mask, stream);
-  return attn_bwd_mfma_np<DH, CAUSAL, 1>(qkv, dctx, lse, delta, dqkv, s, b, heads, mask, stream);
+    return attn_bwd_mfma_np<DH, CAUSAL, 2>(qkv, ctx, dctx, lse, delta, dqkv, s, b, heads, mask, stream);
+  return attn_bwd_mfma_np<DH, CAUSAL, 1>(qkv, ctx, dctx, lse, delta, dqkv, s, b, heads, mask, stream);
 }
 
 int launch_attn_bwd(int dtype, const void* qkv, const void* ctx, const float* lse, const void* dctx, void* dqkv,
