@@ -668,7 +668,7 @@ struct LmLayout {
 LmLayout lm_layout(const ptdp_layer_cfg* c, int vrows) {
   const Dims d = dims_of(c);
   size_t sz[LM_N];
-  sz[LM_U] = sz[LM_DU] = d.T * d.h * d.esz;   // LM_DU doubles as the masked gradient of the embedding backward
+  sz[LM_U] = sz[LM_DU] = d.T * d.h * d.esz;
   sz[LM_MU] = sz[LM_RSTD] = d.T * sizeof(float);
   sz[LM_LOGITS] = (size_t)d.T * vrows * d.esz;
   sz[LM_COLSUM] = layernorm_bwd_scratch_bytes((int)d.T, (int)d.h);
@@ -716,9 +716,8 @@ int ptdp_embedding_backward(const ptdp_layer_cfg* cfg, int vocab_first, int voca
   PTDP_TRY(lm_check(cfg, vocab_first, vocab_rows));
   if (!tokens || !dx || !d_e_word || !d_e_pos || !workspace) return PTDP_E_NULL_PTR;
   if (microbatch < 0) return PTDP_E_INVALID_ARG;
-  const LmLayout L = lm_layout(cfg, vocab_rows);
-  return launch_embed_bwd(cfg->dtype, tokens, dx, (char*)workspace + L.off[LM_DU], d_e_word, d_e_pos, cfg->s, cfg->b,
-                          cfg->h, vocab_first, vocab_rows, cfg->p_hidden,
+  return launch_embed_bwd(cfg->dtype, tokens, dx, d_e_word, d_e_pos, cfg->s, cfg->b, cfg->h,
+                          vocab_first, vocab_rows, cfg->p_hidden,
                           dropout_key(cfg->seed, PTDP_EMBED_LAYER, 0, (uint64_t)microbatch), (hipStream_t)stream);
 }
 

@@ -192,8 +192,7 @@ bool attn_dh_supported(int dtype, int dh);
 // first / last stage extras (lm_stage.hip)
 int launch_embed_fwd(int dtype, const int32_t* tokens, const void* e_word, const void* e_pos, void* x, int s, int b,
                      int h, int v0, int vrows, float p, uint64_t key, hipStream_t st);
-int launch_embed_bwd(int dtype, const int32_t* tokens, const void* dx, void* dmasked, float* d_e_word, float* d_e_pos,
-                     int s, int b, int h, int v0, int vrows, float p, uint64_t key, hipStream_t st);
+int launch_embed_bwd(int dtype, const int32_t* tokens, const void* dx, float* d_e_word, float* d_e_pos, int s, int b, int h, int v0, int vrows, float p, uint64_t key, hipStream_t st);
 int launch_xent(int dtype, void* logits, const int32_t* targets, float* token_loss, float* loss, int rows, int vrows,
                 int v0, float grad_scale, hipStream_t st);
 

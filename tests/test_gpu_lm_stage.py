@@ -69,6 +69,14 @@ def test_embedding_forward_backward(dtype, s, b, h, V, v0, rows, p):
     assert torch.equal(dw, dw2) and torch.equal(dp, dp2)
 
 
+# more tokens than one round of the backward takes (8192), nearly all of them of a few rows; one row of columns beyond a
+# wave's slice; one workgroup's rows exactly and nine of them
+@pytest.mark.parametrize("dtype,s,b,h,V,v0,rows,p", [(B.BF16, 8200, 1, 64, 24, 8, 8, 0.1), (B.F32, 3000, 3, 64, 80, 0, 72, 0.1),
+                                                     (B.BF16, 65, 1, 4160, 16, 0, 8, 0.0)])
+def test_embedding_many_tokens(dtype, s, b, h, V, v0, rows, p):
+    test_embedding_forward_backward(dtype, s, b, h, V, v0, rows, p)
+
+
 @pytest.mark.parametrize("dtype,s,b,h,V,v0,rows,p", CASES)
 def test_head_step(dtype, s, b, h, V, v0, rows, p):
     cfg = B.make_cfg(h=h, a=h // 64, t=1, s=s, b=b, dtype=dtype, p_hidden=p, seed=3)
