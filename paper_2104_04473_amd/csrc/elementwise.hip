@@ -96,13 +96,205 @@ __global__ void layernorm_fwd_kernel(const T* __restrict__ x, const T* __restric
 // LayerNorm backward: input gradient and the partial sums of the gain / bias gradients in one pass.
 //   xhat = (x-mu)*rstd, dxhat = du*gain, dx = resid + rstd*(dxhat - mean(dxhat) - xhat*mean(dxhat*xhat)),
 //   dgain[c] = sum_r du*xhat, dbias[c] = sum_r du.
-// A block walks `rpb` consecutive rows; each row of du and x is read once and waits in registers in storage
-// form (fp32 copies of both would not fit next to the column accumulators) while the two row means are reduced;
-// every lane keeps the running column sums of its own VPT*N columns and stores them once, as row blockIdx.x of
-// part[][2*width] (gain part first).  dx may alias du: a lane overwrites only elements it has read itself.
+// A block of eight waves walks `rpb` consecutive rows, eight / GW of them at a time: GW waves share a row, so that
+// narrow rows cost little or no waiting on other waves and several are under way at once.  Each row of du, x and the
+// residual is read once, requested while the previous row is reduced and kept in storage form (fp32 copies would not fit
+// next to the column accumulators); every lane keeps the running column sums of its own VPT*N columns.  The groups' sums
+// meet in LDS and the block stores them once, as row blockIdx.x of part[][2*width] (gain part first).  dx may alias du or
+// resid: a lane overwrites only elements it has read itself.
+// Bound by memory for wide rows, by one row's round trip for narrow ones.  us before (one row per block at a time) and
+// now, bf16 with residual: 8192 rows x 2048 58 -> 31, 2048 x 4096 26 -> 21.5, 2048 x 12288 58 -> 53, 1024 x 2048
+// 11.3 -> 9.9.
+constexpr int kLnBwdThreads = 512, kLnBwdWaves = kLnBwdThreads / 64;
+template <typename T, int VPT, int GW>
+__global__ void __launch_bounds__(kLnBwdThreads)
+layernorm_bwd_kernel(const T* du, const T* __restrict__ x, const T* __restrict__ gain, const float* __restrict__ mu,
+                     const float* __restrict__ rstd, const T* resid, T* dx, float* __restrict__ part, int rows, int width,
+                     int rpb) {
+  constexpr int N = Vec16<T>::N, NG = kLnBwdWaves / GW;
+  extern __shared__ __attribute__((aligned(16))) char ln_smem[];
+  T* gain_s = reinterpret_cast<T*>(ln_smem);   // the gain row, read twice per row of the block
+  __shared__ float red[2][2][kLnBwdWaves];
+  const int nvec = width / N, wave = threadIdx.x >> 6, grp = NG == 1 ? 0 : wave / GW, tid = threadIdx.x - grp * GW * 64;
+  for (int c = threadIdx.x; c < nvec; c += kLnBwdThreads) {
+    Vec16<T> g;
+    g.load(gain + (size_t)c * N);
+    g.store(gain_s + (size_t)c * N);
+  }
+  float ag[VPT][N], ab[VPT][N];
+#pragma unroll
+  for (int i = 0; i < VPT; ++i)
+#pragma unroll
+    for (int j = 0; j < N; ++j) ag[i][j] = ab[i][j] = 0.f;
+  const int r0 = blockIdx.x * rpb, r1 = min(rows, r0 + rpb);
+  // the residual gradient is only wanted after the reduction, but requested with the rest: one round trip per row
+  typedef Vec16<T> Row[VPT];
+  auto load = [&](int r, Row& pa, Row& pb, Row& pr, float& pm, float& prs) {
+    if (r >= r1) return;
+    const size_t base = (size_t)r * width;
+    pm = mu[r];
+    prs = rstd[r];
+#pragma unroll
+    for (int i = 0; i < VPT; ++i) {
+      const int c = tid + i * GW * 64;
+      if (c < nvec) {
+        pa[i].load(du + base + (size_t)c * N);
+        pb[i].load(x + base + (size_t)c * N);
+        if (resid) pr[i].load(resid + base + (size_t)c * N);
+      }
+    }
+  };
+  auto process = [&](int t, Row& a, Row& b, Row& rr, float m, float rs) {
+    const int r = r0 + t * NG + grp;
+    const bool have = NG == 1 || r < r1;
+    float s1 = 0.f, s2 = 0.f;
+    if (have) {
+#pragma unroll
+      for (int i = 0; i < VPT; ++i) {
+        const int c = tid + i * GW * 64;
+        if (c < nvec) {
+          Vec16<T> g;
+          float af[N], xf[N], gf[N];
+          g.load(gain_s + (size_t)c * N);
+          a[i].unpack(af);
+          b[i].unpack(xf);
+          g.unpack(gf);
+#pragma unroll
+          for (int j = 0; j < N; ++j) {
+            const float xh = (xf[j] - m) * rs, dxh = af[j] * gf[j];
+            s1 += dxh;
+            s2 += dxh * xh;
+            ag[i][j] += af[j] * xh;
+            ab[i][j] += af[j];
+          }
+        }
+      }
+    }
+    s1 = wave_sum(s1);
+    s2 = wave_sum(s2);
+    if constexpr (GW > 1) {   // both row sums through one barrier; alternating places, so that none is needed behind the reads
+      float (&place)[2][kLnBwdWaves] = red[t & 1];
+      if ((threadIdx.x & 63) == 0) {
+        place[0][wave] = s1;
+        place[1][wave] = s2;
+      }
+      __syncthreads();
+      s1 = s2 = 0.f;
+#pragma unroll
+      for (int w = 0; w < GW; ++w) {
+        s1 += place[0][grp * GW + w];
+        s2 += place[1][grp * GW + w];
+      }
+    }
+    const float c1 = s1 / (float)width, c2 = s2 / (float)width;
+    // the second pass unpacks the stored row again: keeping the first pass's fp32 values alive across the
+    // reduction instead would cost two more registers per element and spill
+#pragma unroll
+    for (int i = 0; i < VPT; ++i) {
+      asm volatile("" : "+v"(a[i].raw.x), "+v"(a[i].raw.y), "+v"(a[i].raw.z), "+v"(a[i].raw.w));
+      asm volatile("" : "+v"(b[i].raw.x), "+v"(b[i].raw.y), "+v"(b[i].raw.z), "+v"(b[i].raw.w));
+    }
+    if (have) {
+      const size_t base = (size_t)r * width;
+#pragma unroll
+      for (int i = 0; i < VPT; ++i) {
+        const int c = tid + i * GW * 64;
+        if (c < nvec) {
+          Vec16<T> g, o;
+          float af[N], xf[N], gf[N], of[N];
+          g.load(gain_s + (size_t)c * N);
+          a[i].unpack(af);
+          b[i].unpack(xf);
+          g.unpack(gf);
+          if (resid) {
+            rr[i].unpack(of);
+          } else {
+#pragma unroll
+            for (int j = 0; j < N; ++j) of[j] = 0.f;
+          }
+#pragma unroll
+          for (int j = 0; j < N; ++j) of[j] += rs * (af[j] * gf[j] - c1 - (xf[j] - m) * rs * c2);
+          o.pack(of);
+          o.store(dx + base + (size_t)c * N);
+        }
+      }
+    }
+  };
+  const int steps = (r1 - r0 + NG - 1) / NG;   // the same for every group: the barriers are the block's
+  __syncthreads();   // gain row visible
+  Row a, b, rr, na, nb, nr;
+  float m = 0.f, rs = 0.f, nm = 0.f, nrs = 0.f;
+  load(r0 + grp, a, b, rr, m, rs);
+  for (int t = 0; t < steps; ++t) {
+    load(r0 + (t + 1) * NG + grp, na, nb, nr, nm, nrs);
+    process(t, a, b, rr, m, rs);
+#pragma unroll
+    for (int i = 0; i < VPT; ++i) {
+      a[i] = na[i];
+      b[i] = nb[i];
+      rr[i] = nr[i];
+    }
+    m = nm;
+    rs = nrs;
+  }
+  // the upper half of the groups hands its sums to the lower half until one is left
+  if constexpr (NG > 1) {
+    float* sums = reinterpret_cast<float*>(ln_smem);   // [group][gain, bias][column]: the gain row is done with
+#pragma unroll
+    for (int live = NG / 2; live > 0; live /= 2) {
+      __syncthreads();
+      if (grp >= live && grp < 2 * live) {
+        float* o = sums + (size_t)(grp - live) * 2 * width;
+#pragma unroll
+        for (int i = 0; i < VPT; ++i) {
+          const int c = tid + i * GW * 64;
+          if (c < nvec) {
+#pragma unroll
+            for (int j = 0; j < N; ++j) {
+              o[(size_t)j * nvec + c] = ag[i][j];   // [j][c]: neighbouring lanes in neighbouring banks
+              o[(size_t)(N + j) * nvec + c] = ab[i][j];
+            }
+          }
+        }
+      }
+      __syncthreads();
+      if (grp < live) {
+        const float* o = sums + (size_t)grp * 2 * width;
+#pragma unroll
+        for (int i = 0; i < VPT; ++i) {
+          const int c = tid + i * GW * 64;
+          if (c < nvec) {
+#pragma unroll
+            for (int j = 0; j < N; ++j) {
+              ag[i][j] += o[(size_t)j * nvec + c];
+              ab[i][j] += o[(size_t)(N + j) * nvec + c];
+            }
+          }
+        }
+      }
+    }
+    if (grp > 0) return;
+  }
+  float* prow = part + (size_t)blockIdx.x * 2 * width;
+#pragma unroll
+  for (int i = 0; i < VPT; ++i) {
+    const int c = tid + i * GW * 64;
+    if (c < nvec) {
+#pragma unroll
+      for (int j = 0; j < N; ++j) {
+        prow[(size_t)c * N + j] = ag[i][j];
+        prow[(size_t)width + (size_t)c * N + j] = ab[i][j];
+      }
+    }
+  }
+}
+
+// The same for rows whose next row does not fit the registers beside the current one (more than four vectors per lane of
+// eight waves): one row at a time, requested when its turn comes.  Bound by memory (25600 columns: 12 bytes per element
+// of three reads and a write at 3.3 TB/s); the form above spills there and takes 180 instead of 127 us.
 template <typename T, int VPT>
 __global__ void __launch_bounds__(512)
-layernorm_bwd_kernel(const T* du, const T* __restrict__ x, const T* __restrict__ gain, const float* __restrict__ mu,
+layernorm_bwd_wide_kernel(const T* du, const T* __restrict__ x, const T* __restrict__ gain, const float* __restrict__ mu,
                      const float* __restrict__ rstd, const T* resid, T* dx, float* __restrict__ part, int rows, int width,
                      int rpb) {
   constexpr int N = Vec16<T>::N;
@@ -574,34 +766,66 @@ size_t layernorm_bwd_scratch_bytes(int rows, int width) {
   return (size_t)((rows + rpb - 1) / rpb) * 2 * (size_t)width * sizeof(float);
 }
 
+template <typename T, int VPT, int GW>
+static int ln_bwd_launch(const void* du, const void* x, const void* gain, const float* mu, const float* rstd, const void* resid,
+                         void* dx, float* part, int rows, int width, int rpb, int nblk, hipStream_t st) {
+  constexpr int NG = kLnBwdWaves / GW;
+  const size_t gain_bytes = (size_t)width * sizeof(T), sum_bytes = (size_t)(NG / 2) * 2 * width * sizeof(float);
+  constexpr int kMost = VPT * GW * 64 * Vec16<T>::N * (int)(NG > 1 ? NG * sizeof(float) : sizeof(T));   // at the widest row of this form
+  auto kern = layernorm_bwd_kernel<T, VPT, GW>;
+  static once_flag_t done[kMaxDevices];
+  if (set_dynamic_smem(reinterpret_cast<const void*>(kern), kMost, done) != PTDP_OK) return PTDP_E_HIP;
+  hipLaunchKernelGGL(kern, dim3(nblk), dim3(kLnBwdThreads), gain_bytes > sum_bytes ? gain_bytes : sum_bytes, st, (const T*)du,
+                     (const T*)x, (const T*)gain, mu, rstd, (const T*)resid, (T*)dx, part, rows, width, rpb);
+  return PTDP_OK;
+}
+template <typename T, int VPT>
+static int ln_bwd_wide_launch(const void* du, const void* x, const void* gain, const float* mu, const float* rstd, const void* resid,
+                              void* dx, float* part, int rows, int width, int rpb, int nblk, hipStream_t st) {
+  hipLaunchKernelGGL((layernorm_bwd_wide_kernel<T, VPT>), dim3(nblk), dim3(512), (size_t)width * sizeof(T), st, (const T*)du,
+                     (const T*)x, (const T*)gain, mu, rstd, (const T*)resid, (T*)dx, part, rows, width, rpb);
+  return PTDP_OK;
+}
 template <typename T>
 static int ln_bwd_t(const void* du, const void* x, const void* gain, const float* mu, const float* rstd,
                     const void* resid, void* dx, float* dgain, float* dbias, void* scratch, int rows, int width,
                     hipStream_t st, ColsumBatch* defer) {
   constexpr int N = Vec16<T>::N;
-  int vpt;
-  const int threads = ln_threads(width / N, &vpt);
-  if (vpt > 8) return PTDP_E_UNSUPPORTED;
-  vpt = (width / N + threads - 1) / threads;   // exact count: every vector slot costs two column accumulators
+  const int slots = (width / N + 63) / 64;   // 64-vector pieces of a row
+  if (slots > 8 * kLnBwdWaves) return PTDP_E_UNSUPPORTED;
   float* part = (float*)scratch;
   const int rpb = ln_bwd_rows_per_block(rows), nblk = (rows + rpb - 1) / rpb;
   {
     const double bytes = (double)rows * width * sizeof(T) * (resid ? 4 : 3);
     Launch L(PTDP_K_LN_BWD, bytes, st);
-#define PTDP_LN_BWD(V)                                                                                        \
-  hipLaunchKernelGGL((layernorm_bwd_kernel<T, V>), dim3(nblk), dim3(threads), (size_t)width * sizeof(T), st, (const T*)du, (const T*)x, \
-                     (const T*)gain, mu, rstd, (const T*)resid, (T*)dx, part, rows, width, rpb)
-    switch (vpt) {
-      case 1: PTDP_LN_BWD(1); break;
-      case 2: PTDP_LN_BWD(2); break;
-      case 3: PTDP_LN_BWD(3); break;
-      case 4: PTDP_LN_BWD(4); break;
-      case 5: PTDP_LN_BWD(5); break;
-      case 6: PTDP_LN_BWD(6); break;
-      case 7: PTDP_LN_BWD(7); break;
-      default: PTDP_LN_BWD(8); break;
+    int rc;
+#define PTDP_LN_BWD_WIDE(V) rc = ln_bwd_wide_launch<T, V>(du, x, gain, mu, rstd, resid, dx, part, rows, width, rpb, nblk, st)
+#define PTDP_LN_BWD(V, G) rc = ln_bwd_launch<T, V, G>(du, x, gain, mu, rstd, resid, dx, part, rows, width, rpb, nblk, st)
+    // Waves per row: doubled while a lane would hold more than two vectors (2048 columns, 8192 rows: four 50, two 46, one
+    // 51 us with the finishing launch) and while a block has fewer rows than groups (their sums' way through LDS costs
+    // more than it saves: 1024 rows x 2048 27.7 -> 24.2).  Eight waves hold up to four vectors a lane, beyond that one row at a time.
+    int gw = 1;
+    while (gw < kLnBwdWaves && (slots > 2 * gw || kLnBwdWaves / gw > rpb)) gw *= 2;
+    const int v = (slots + gw - 1) / gw;
+    switch (gw * 16 + v) {
+      case 16 + 1: PTDP_LN_BWD(1, 1); break;
+      case 16 + 2: PTDP_LN_BWD(2, 1); break;
+      case 32 + 1: PTDP_LN_BWD(1, 2); break;
+      case 32 + 2: PTDP_LN_BWD(2, 2); break;
+      case 64 + 1: PTDP_LN_BWD(1, 4); break;
+      case 64 + 2: PTDP_LN_BWD(2, 4); break;
+      case 128 + 1: PTDP_LN_BWD(1, 8); break;
+      case 128 + 2: PTDP_LN_BWD(2, 8); break;
+      case 128 + 3: PTDP_LN_BWD(3, 8); break;
+      case 128 + 4: PTDP_LN_BWD(4, 8); break;
+      case 128 + 5: PTDP_LN_BWD_WIDE(5); break;
+      case 128 + 6: PTDP_LN_BWD_WIDE(6); break;
+      case 128 + 7: PTDP_LN_BWD_WIDE(7); break;
+      default: PTDP_LN_BWD_WIDE(8); break;
     }
 #undef PTDP_LN_BWD
+#undef PTDP_LN_BWD_WIDE
+    if (rc != PTDP_OK) return rc;
     if (L.status() != PTDP_OK) return L.status();
   }
   return colsum_finish(part, nblk, 2 * width, dgain, dbias, width, st, defer);
