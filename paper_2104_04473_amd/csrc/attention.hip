@@ -312,19 +312,19 @@ typedef __attribute__((__vector_size__(4 * sizeof(short)))) short s16x4_t;
 
 // bytes per LDS tile row: padded so that both the 16-byte fragment reads of 16 neighbouring rows and
 // the 4-row x 32-byte gathers of the transposing reads spread over the banks
-template <int DH> struct TileGeom {
+template <int DH, int THREADS = kAttnThreads> struct TileGeom {
   static constexpr int STRIDE = DH * 2 + (DH == 128 ? 32 : 16);
   static constexpr int BYTES = kBKV * STRIDE;
-  static constexpr int NCH = kBKV * (DH / 8) / kAttnThreads;  // 16-byte chunks per thread and tile
+  static constexpr int NCH = kBKV * (DH / 8) / THREADS;  // 16-byte chunks per thread and tile
 };
 
 // One 64-row tile of one head on its way global -> registers -> LDS (rows >= s read as zeros).
-template <int DH> struct TileRegs {
-  uint4 v[TileGeom<DH>::NCH];
+template <int DH, int THREADS = kAttnThreads> struct TileRegs {
+  uint4 v[TileGeom<DH, THREADS>::NCH];
   __device__ __forceinline__ void load(const bf16_t* __restrict__ src, size_t rs, int row0, int s) {
 #pragma unroll
-    for (int i = 0; i < TileGeom<DH>::NCH; ++i) {
-      const int c = (threadIdx.x & (kAttnThreads - 1)) + i * kAttnThreads;
+    for (int i = 0; i < TileGeom<DH, THREADS>::NCH; ++i) {
+      const int c = (threadIdx.x & (THREADS - 1)) + i * THREADS;
       const int row = c / (DH / 8), ch = c % (DH / 8);
       // branch-free: read a clamped (always valid) row, then blank it if it is past the end, so that
       // the loads of a tile are issued back to back
@@ -336,8 +336,8 @@ template <int DH> struct TileRegs {
   }
   __device__ __forceinline__ void store(char* lds) const {
 #pragma unroll
-    for (int i = 0; i < TileGeom<DH>::NCH; ++i) {
-      const int c = (threadIdx.x & (kAttnThreads - 1)) + i * kAttnThreads;
+    for (int i = 0; i < TileGeom<DH, THREADS>::NCH; ++i) {
+      const int c = (threadIdx.x & (THREADS - 1)) + i * THREADS;
       const int row = c / (DH / 8), ch = c % (DH / 8);
       *reinterpret_cast<uint4*>(lds + row * TileGeom<DH>::STRIDE + ch * 16) = v[i];
     }
@@ -347,32 +347,32 @@ template <int DH> struct TileRegs {
 // This thread's chunk positions inside a tile, computed once: element offsets for the loads (rows rs
 // apart) and byte offsets for the LDS stores.  A tile that lies wholly inside the sequence is then
 // loaded with one add per chunk; the last, ragged tile takes TileRegs::load.
-template <int DH> struct TileMap {
-  uint32_t src[TileGeom<DH>::NCH];
-  uint32_t dst[TileGeom<DH>::NCH];
+template <int DH, int THREADS = kAttnThreads> struct TileMap {
+  uint32_t src[TileGeom<DH, THREADS>::NCH];
+  uint32_t dst[TileGeom<DH, THREADS>::NCH];
   __device__ __forceinline__ void init(size_t rs) {
 #pragma unroll
-    for (int i = 0; i < TileGeom<DH>::NCH; ++i) {
-      const int c = (threadIdx.x & (kAttnThreads - 1)) + i * kAttnThreads;
+    for (int i = 0; i < TileGeom<DH, THREADS>::NCH; ++i) {
+      const int c = (threadIdx.x & (THREADS - 1)) + i * THREADS;
       const int row = c / (DH / 8), ch = c % (DH / 8);
       src[i] = (uint32_t)(row * rs + ch * 8);
       dst[i] = (uint32_t)(row * TileGeom<DH>::STRIDE + ch * 16);
     }
   }
   // rows row0 .. row0+63 of src (row pitch rs); s = number of valid rows
-  __device__ __forceinline__ void load(TileRegs<DH>& t, const bf16_t* __restrict__ src_base, size_t rs, int row0,
+  __device__ __forceinline__ void load(TileRegs<DH, THREADS>& t, const bf16_t* __restrict__ src_base, size_t rs, int row0,
                                        int s) const {
     if (row0 + kBKV <= s) {
       const bf16_t* p = src_base + (size_t)row0 * rs;
 #pragma unroll
-      for (int i = 0; i < TileGeom<DH>::NCH; ++i) t.v[i] = *reinterpret_cast<const uint4*>(p + src[i]);
+      for (int i = 0; i < TileGeom<DH, THREADS>::NCH; ++i) t.v[i] = *reinterpret_cast<const uint4*>(p + src[i]);
     } else {
       t.load(src_base, rs, row0, s);
     }
   }
-  __device__ __forceinline__ void store(const TileRegs<DH>& t, char* lds) const {
+  __device__ __forceinline__ void store(const TileRegs<DH, THREADS>& t, char* lds) const {
 #pragma unroll
-    for (int i = 0; i < TileGeom<DH>::NCH; ++i) *reinterpret_cast<uint4*>(lds + dst[i]) = t.v[i];
+    for (int i = 0; i < TileGeom<DH, THREADS>::NCH; ++i) *reinterpret_cast<uint4*>(lds + dst[i]) = t.v[i];
   }
 };
 
@@ -810,55 +810,57 @@ attn_bwd_dq_mfma(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ ctx,
 
 constexpr int kMaskLdsStride = 68;   // bytes per key row of the staged mask tile ([key][query], padded)
 
-// A 64 x 64 tile of the mask on its way to LDS as [key][query], so that a lane reads four queries of its key at once.  A
-// thread carries two blocks of 4 queries x 4 keys: four words of four keys, turned by byte permutes into four words of
+// A 64 x 64 tile of the mask on its way to LDS as [key][query], so that a lane reads four queries of its key at once.  Blocks
+// of 4 queries x 4 keys, one or two per thread: four words of four keys, turned by byte permutes into four words of
 // four queries (byte loads and stores, one per element: 98 us for the kernel at 4 samples x 16 heads x 512, now 35).
-struct MaskTile {
-  uint32_t v[2][4];
+template <int THREADS> struct MaskTile {
+  static constexpr int NB = 256 / THREADS;   // blocks per thread
+  uint32_t v[NB][4];
   __device__ __forceinline__ void load(const uint8_t* __restrict__ mask_j, int q0, int key0, int s, bool aligned, int tid) {
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      const int blk = tid + i * kAttnThreads, key = key0 + 4 * (blk & 15), q = q0 + 4 * (blk >> 4);
+    for (int i = 0; i < NB; ++i) {
+      const int blk = tid + i * THREADS, key = key0 + 4 * (blk & 15), q = q0 + 4 * (blk >> 4);
 #pragma unroll
       for (int r = 0; r < 4; ++r) v[i][r] = mask_word(mask_j + (size_t)min(q + r, s - 1) * s, key, s, aligned);
     }
   }
   __device__ __forceinline__ void store(uint8_t* lds, int tid) const {
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      const int blk = tid + i * kAttnThreads, key = 4 * (blk & 15), ql = 4 * (blk >> 4);
+    for (int i = 0; i < NB; ++i) {
+      const int blk = tid + i * THREADS, key = 4 * (blk & 15), ql = 4 * (blk >> 4);
       const uint32_t a = __builtin_amdgcn_perm(v[i][1], v[i][0], 0x05010400u), b = __builtin_amdgcn_perm(v[i][1], v[i][0], 0x07030602u);
       const uint32_t c = __builtin_amdgcn_perm(v[i][3], v[i][2], 0x05010400u), d = __builtin_amdgcn_perm(v[i][3], v[i][2], 0x07030602u);
       const uint32_t t[4] = {__builtin_amdgcn_perm(c, a, 0x05040100u), __builtin_amdgcn_perm(c, a, 0x07060302u),
                              __builtin_amdgcn_perm(d, b, 0x05040100u), __builtin_amdgcn_perm(d, b, 0x07060302u)};
 #pragma unroll
-      for (int k = 0; k < 4; ++k) *reinterpret_cast<uint32_t*>(lds + (key + k) * kMaskLdsStride + ql) = t[k];
+      for (int r = 0; r < 4; ++r) *reinterpret_cast<uint32_t*>(lds + (key + r) * kMaskLdsStride + ql) = t[r];
     }
   }
 };
 
-// dK/dV: a workgroup owns 64 keys; wave w of a pair owns keys 32 w .. 32 w + 31.  NP = 1: one pair of waves walks all
-// 64-query tiles.  NP = 2: two pairs; pair p walks every second tile (first + p, first + p + 2, ...) with tiles of its
-// own in LDS, and at the end pair 1 hands its sums to pair 0 through LDS, added in that fixed order.  The workgroup
-// that owns the first keys of a causal head walks all query tiles and the launch lasts at least as long as it does:
-// two pairs halve that path, at the price of one barrier domain per CU instead of two independent ones.  The launch
-// code takes NP = 2 when all workgroups of the one-pair form would be resident at once (the longest one then sets
-// the time: GPT-3-shaped shard, 12 heads: backward 0.213 -> 0.152 ms) and NP = 1 otherwise (1T-shaped shard, 20
-// heads of 160: 0.331 against 0.343 ms).
-template <int DH, bool CAUSAL> struct DkvLds {
+// dK/dV: a workgroup owns 64 keys; wave w of a pair owns keys 32 w .. 32 w + 31 and computes both results.  NP = 1: one
+// pair of waves walks all 64-query tiles.  NP = 2: two pairs; pair p walks every second tile (first + p, first + p + 2,
+// ...) with tiles of its own in LDS, and at the end pair 1 hands its sums to pair 0 through LDS, added in that fixed order.
+// The workgroup that owns the first keys of a causal head walks all query tiles and the launch lasts at least as long as
+// it does: two pairs halve that path, at the price of one barrier domain per CU instead of two independent ones.  The
+// launch code takes NP = 2 when all workgroups of the one-pair form would be resident at once (the longest one then sets
+// the time: GPT-3-shaped shard, 12 heads: backward 0.213 -> 0.152 ms) and NP = 1 otherwise (1T-shaped shard, 20 heads of
+// 160: 0.331 against 0.343 ms).
+// For heads of 32, 64 and 160; 96 and 128 take the form below.
+template <int DH, bool CAUSAL> struct DkvBothLds {
   static constexpr int kPair = 2 * TileGeom<DH>::BYTES + 2 * kBKV * (int)sizeof(float) + (CAUSAL ? 0 : kBQ * kMaskLdsStride);
   static constexpr int kSum = 2 * (DH / 32) * 16 * 64 * (int)sizeof(float);   // one wave's dK and dV
   static constexpr int kBytes2 = 2 * kPair > 2 * kSum ? 2 * kPair : 2 * kSum;
 };
 template <int DH, bool CAUSAL, int NP>
 __global__ void __launch_bounds__(NP * kAttnThreads)
-attn_bwd_dkv_mfma(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ dctx, const float* __restrict__ lse,
+attn_bwd_dkv_both_mfma(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ dctx, const float* __restrict__ lse,
                   const float* __restrict__ delta, bf16_t* __restrict__ dqkv, int s, int b, int heads,
                   const uint8_t* __restrict__ mask) {
   constexpr int NKK = DH / 16, NDT = DH / 32;
   extern __shared__ __attribute__((aligned(16))) char smem_all[];
   const int pair = NP == 2 ? threadIdx.x >> 7 : 0, tid = threadIdx.x & (kAttnThreads - 1);
-  char* smem = smem_all + pair * DkvLds<DH, CAUSAL>::kPair;
+  char* smem = smem_all + pair * DkvBothLds<DH, CAUSAL>::kPair;
   char* q_lds = smem;                           // Q  [query][dh]: S = Q K^T directly, dK^T = Q^T dS through tr reads
   char* do_lds = smem + TileGeom<DH>::BYTES;    // dO [query][dh]: dP = dO V^T directly, dV^T = dO^T P through tr reads
   float* lse_lds = reinterpret_cast<float*>(smem + 2 * TileGeom<DH>::BYTES);  // lse * log2(e), +inf past the end
@@ -901,7 +903,7 @@ attn_bwd_dkv_mfma(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ dct
   TileMap<kPrefetch ? DH : 32> qmap, domap;
   TileRegs<kPrefetch ? DH : 32> qr, dor;
   float lse_r = 0.f, delta_r = 0.f;
-  MaskTile mt;
+  MaskTile<kAttnThreads> mt;
   const uint8_t* mask_j = use_mask ? mask + (size_t)j * s * s : nullptr;
   const bool aligned = (s & 3) == 0;
   auto fetch = [&](int q0) {
@@ -1029,6 +1031,175 @@ attn_bwd_dkv_mfma(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ dct
   }
 }
 
+// The same, split by result: a group of four waves, of which two (32 keys each) compute S, dP and dK and two S and dV.  S
+// twice is a quarter more matrix work, but a wave then holds one result and fits 256 registers: two waves per SIMD cover
+// each other's waits where both results in one wave leave one (half of its time went to waiting for LDS and barriers).
+// Which waves take which result alternates with the workgroup, so that every SIMD gets both.  us, both results in a wave
+// and split: dh 128, 4 samples x 16 heads x 2048 371 -> 319, 12 heads x 2048 90 -> 87, 8 heads x 1024 38 -> 35; dh 96 with
+// dQ, 4 x 16 x 2048 459 -> 447, 12 heads x 2048 115 -> 118, 8 heads x 1024 54 -> 52; but dh 64, 4 x 16 x 512 with mask 34.7
+// -> 36.0 and dh 32, 128 heads x 2048 191 -> 259, where several waves fit a SIMD as it is.  NP = 2: two groups of four
+// waves, as above.
+constexpr int kDkvThreads = 2 * kAttnThreads;
+template <int DH, bool CAUSAL> struct DkvLds {
+  static constexpr int kPair = 2 * TileGeom<DH>::BYTES + 2 * kBKV * (int)sizeof(float) + (CAUSAL ? 0 : kBQ * kMaskLdsStride);
+  static constexpr int kSum = (DH / 32) * 16 * 64 * (int)sizeof(float);   // one wave's dK or dV
+  static constexpr int kBytes2 = 2 * kPair > 4 * kSum ? 2 * kPair : 4 * kSum;
+};
+template <int DH, bool CAUSAL, int NP>
+__global__ void __launch_bounds__(NP * kDkvThreads, 2)
+attn_bwd_dkv_mfma(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ dctx, const float* __restrict__ lse,
+                  const float* __restrict__ delta, bf16_t* __restrict__ dqkv, int s, int b, int heads,
+                  const uint8_t* __restrict__ mask) {
+  constexpr int NKK = DH / 16, NDT = DH / 32;
+  extern __shared__ __attribute__((aligned(16))) char smem_all[];
+  const int pair = NP == 2 ? threadIdx.x >> 8 : 0, tid = threadIdx.x & (kDkvThreads - 1);
+  char* smem = smem_all + pair * DkvLds<DH, CAUSAL>::kPair;
+  char* q_lds = smem;                           // Q  [query][dh]: S = Q K^T directly, dK^T = Q^T dS through tr reads
+  char* do_lds = smem + TileGeom<DH>::BYTES;    // dO [query][dh]: dP = dO V^T directly, dV^T = dO^T P through tr reads
+  float* lse_lds = reinterpret_cast<float*>(smem + 2 * TileGeom<DH>::BYTES);  // lse * log2(e), +inf past the end
+  float* delta_lds = lse_lds + kBKV;
+  uint8_t* mask_lds = reinterpret_cast<uint8_t*>(delta_lds + kBKV);   // general mask only: [64 keys][68]
+  const bool use_mask = !CAUSAL && mask != nullptr;
+  const float fill = kMaskFill * sqrtf((float)DH);
+
+  int kblk, e, j;  // the first key blocks see the most queries and start first
+  if (!attn_map(blockIdx.x, (s + kBQ - 1) / kBQ, heads, b, &kblk, &e, &j)) return;
+  const int wave4 = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) & 3, wave = wave4 & 1;
+  const bool want_dk = ((wave4 >> 1) ^ (blockIdx.x >> 8)) & 1;
+  const int lane = threadIdx.x & 63, half = lane >> 5, l31 = lane & 31;
+  const int hp = heads * DH;
+  const size_t rs = (size_t)b * 3 * hp;
+  const bf16_t* base = qkv + (size_t)j * 3 * hp + (size_t)e * DH;
+  const bf16_t* dobase = dctx + (size_t)j * hp + (size_t)e * DH;
+  const size_t dors = (size_t)b * hp;
+  const int key_first = kblk * kBQ + wave * 32;
+  const int my_key = key_first + l31;
+  const bool valid = my_key < s;
+  const float scale = rsqrtf((float)DH), c2 = scale * 1.4426950408889634f;
+  const float* lse_h = lse + ((size_t)j * heads + e) * s;
+  const float* delta_h = delta + ((size_t)j * heads + e) * s;
+
+  bf16x8_t kf[NKK], vf[NKK];
+#pragma unroll
+  for (int kk = 0; kk < NKK; ++kk) {
+    kf[kk] = frag_global(base + (size_t)min(my_key, s - 1) * rs + hp, valid, kk, half);
+    vf[kk] = frag_global(base + (size_t)min(my_key, s - 1) * rs + 2 * hp, valid, kk, half);
+  }
+  f32x16_t acc[NDT];   // dK or dV
+#pragma unroll
+  for (int d = 0; d < NDT; ++d) acc[d] = zero16();
+  const int nq_tiles = (s + kBKV - 1) / kBKV;
+  // the next Q and dO tiles (and their lse, delta, mask) travel in registers while this step's arithmetic runs
+  TileMap<DH, kDkvThreads> qmap, domap;
+  TileRegs<DH, kDkvThreads> qr, dor;
+  float lse_r = 0.f, delta_r = 0.f;
+  MaskTile<kDkvThreads> mt;
+  const uint8_t* mask_j = use_mask ? mask + (size_t)j * s * s : nullptr;
+  const bool aligned = (s & 3) == 0;
+  auto fetch = [&](int q0) {
+    if (use_mask) mt.load(mask_j, q0, kblk * kBQ, s, aligned, tid);
+    qmap.load(qr, base, rs, q0, s);
+    domap.load(dor, dobase, dors, q0, s);
+    if (tid < kBKV) {
+      const int q = q0 + tid;
+      lse_r = q < s ? lse_h[q] * 1.4426950408889634f : INFINITY;
+      delta_r = q < s ? delta_h[q] : 0.f;
+    }
+  };
+  const int qt_first = CAUSAL ? (kblk * kBQ) / kBKV : 0;
+  qmap.init(rs);
+  domap.init(dors);
+  if (qt_first + pair < nq_tiles) fetch((qt_first + pair) * kBKV);
+  // both groups take the same number of steps (the barriers are the workgroup's); a group without a tile idles
+  for (int qt0 = qt_first; qt0 < nq_tiles; qt0 += NP) {
+    const int qt = qt0 + pair;
+    const bool have = qt < nq_tiles;
+    const int q0 = qt * kBKV;
+    __syncthreads();
+    if (have) {
+      qmap.store(qr, q_lds);
+      domap.store(dor, do_lds);
+      if (tid < kBKV) {
+        lse_lds[tid] = lse_r;
+        delta_lds[tid] = delta_r;
+      }
+      if (use_mask) mt.store(mask_lds, tid);
+    }
+    __syncthreads();
+    if (!have) continue;
+    if (qt + NP < nq_tiles) fetch(q0 + NP * kBKV);
+    if (CAUSAL && q0 + kBKV - 1 < key_first) continue;  // every query of the tile precedes this wave's keys
+    const bool diag = CAUSAL && q0 < key_first + 32;    // some query of the tile precedes some key of this wave
+    bf16x8_t wf[2][2];   // P or dS
+#pragma unroll
+    for (int sub = 0; sub < 2; ++sub) {
+      f32x16_t sacc = zero16(), dp = zero16();
+#pragma unroll
+      for (int kk = 0; kk < NKK; ++kk)
+        sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_direct<DH>(q_lds, sub, kk, l31, half), kf[kk], sacc, 0, 0, 0);
+      if (want_dk) {
+#pragma unroll
+        for (int kk = 0; kk < NKK; ++kk)
+          dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_direct<DH>(do_lds, sub, kk, l31, half), vf[kk], dp, 0, 0, 0);
+      }
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        const int ql = sub * 32 + 8 * g + 4 * half;  // local index of the first of 4 consecutive queries
+        const float4 L4 = *reinterpret_cast<const float4*>(lse_lds + ql);
+        const float Ls[4] = {L4.x, L4.y, L4.z, L4.w};
+        const uint32_t mw = use_mask ? *reinterpret_cast<const uint32_t*>(mask_lds + (wave * 32 + l31) * kMaskLdsStride + ql) : 0u;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int r = 4 * g + i;
+          const bool hidden = (mw >> (8 * i)) & 0xffu;
+          const float p = __builtin_amdgcn_exp2f((hidden ? fill : sacc[r]) * c2 - Ls[i]);   // lse = +inf past the end gives 0
+          sacc[r] = diag && my_key > q0 + ql + i ? 0.f : p;
+        }
+        if (want_dk) {
+          const float4 D4 = *reinterpret_cast<const float4*>(delta_lds + ql);
+          const float Ds[4] = {D4.x, D4.y, D4.z, D4.w};
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const bool hidden = (mw >> (8 * i)) & 0xffu;
+            sacc[4 * g + i] = hidden ? 0.f : sacc[4 * g + i] * (dp[4 * g + i] - Ds[i]);
+          }
+        }
+      }
+      wf[sub][0] = pack_frag(sacc, 0);
+      wf[sub][1] = pack_frag(sacc, 1);
+    }
+    const char* tr = want_dk ? q_lds : do_lds;
+#pragma unroll
+    for (int d = 0; d < NDT; ++d)
+#pragma unroll
+      for (int sub = 0; sub < 2; ++sub)
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks)
+          acc[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_tr<DH>(tr, d, sub, ks, lane), wf[sub][ks], acc[d], 0, 0, 0);
+  }
+  if constexpr (NP == 2) {
+    // group 1's sums join group 0's: register r of lane l of wave w at sum[w][r][l]
+    __syncthreads();   // every wave is done with the tiles
+    float* sum = reinterpret_cast<float*>(smem_all) + wave4 * (NDT * 16 * 64) + lane;
+    if (pair == 1) {
+#pragma unroll
+      for (int d = 0; d < NDT; ++d)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) sum[(d * 16 + r) * 64] = acc[d][r];
+    }
+    __syncthreads();
+    if (pair == 1) return;
+#pragma unroll
+    for (int d = 0; d < NDT; ++d)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[d][r] += sum[(d * 16 + r) * 64];
+  }
+  if (valid) {
+    bf16_t* out = dqkv + (size_t)my_key * rs + (size_t)j * 3 * hp + (size_t)e * DH;
+    store_cols<NDT>(out + (want_dk ? hp : 2 * hp), acc, want_dk ? scale : 1.f, half);
+  }
+}
+
 // ------------------------------------------------------------------------------------------------
 // host launchers
 // ------------------------------------------------------------------------------------------------
@@ -1126,17 +1297,25 @@ template <int DH, bool CAUSAL, int NP>
 static int attn_bwd_mfma_np(const bf16_t* qkv, const bf16_t* ctx, const bf16_t* dctx, const float* lse, float* delta, bf16_t* dqkv,
                             int s, int b, int heads, const uint8_t* mask, hipStream_t stream) {
   constexpr int smem_dq = NP * 2 * TileGeom<DH>::BYTES;   // (NP = 2: the final sums, 2 x DH x 256 bytes, fit in the tiles)
-  constexpr int smem_dkv = NP == 2 ? DkvLds<DH, CAUSAL>::kBytes2 : DkvLds<DH, CAUSAL>::kPair;
   static once_flag_t done_dq[kMaxDevices], done_dkv[kMaxDevices];
-  if (set_dynamic_smem(reinterpret_cast<const void*>(attn_bwd_dq_mfma<DH, CAUSAL, NP>), smem_dq, done_dq) != PTDP_OK ||
-      set_dynamic_smem(reinterpret_cast<const void*>(attn_bwd_dkv_mfma<DH, CAUSAL, NP>), smem_dkv, done_dkv) != PTDP_OK)
-    return PTDP_E_HIP;
+  if (set_dynamic_smem(reinterpret_cast<const void*>(attn_bwd_dq_mfma<DH, CAUSAL, NP>), smem_dq, done_dq) != PTDP_OK) return PTDP_E_HIP;
   const dim3 grid(attn_grid((s + kBQ - 1) / kBQ, heads, b));
   // dQ first: it writes delta
   hipLaunchKernelGGL((attn_bwd_dq_mfma<DH, CAUSAL, NP>), grid, dim3(NP * kAttnThreads), smem_dq, stream, qkv, ctx, dctx, lse, delta,
                      dqkv, s, b, heads, mask);
-  hipLaunchKernelGGL((attn_bwd_dkv_mfma<DH, CAUSAL, NP>), grid, dim3(NP * kAttnThreads), smem_dkv, stream, qkv, dctx, lse,
-                     (const float*)delta, dqkv, s, b, heads, mask);
+  if constexpr (DH < 96 || DH > 128) {
+    constexpr int smem_dkv = NP == 2 ? DkvBothLds<DH, CAUSAL>::kBytes2 : DkvBothLds<DH, CAUSAL>::kPair;
+    if (set_dynamic_smem(reinterpret_cast<const void*>(attn_bwd_dkv_both_mfma<DH, CAUSAL, NP>), smem_dkv, done_dkv) != PTDP_OK)
+      return PTDP_E_HIP;
+    hipLaunchKernelGGL((attn_bwd_dkv_both_mfma<DH, CAUSAL, NP>), grid, dim3(NP * kAttnThreads), smem_dkv, stream, qkv, dctx, lse,
+                       (const float*)delta, dqkv, s, b, heads, mask);
+  } else {
+    constexpr int smem_dkv = NP == 2 ? DkvLds<DH, CAUSAL>::kBytes2 : DkvLds<DH, CAUSAL>::kPair;
+    if (set_dynamic_smem(reinterpret_cast<const void*>(attn_bwd_dkv_mfma<DH, CAUSAL, NP>), smem_dkv, done_dkv) != PTDP_OK)
+      return PTDP_E_HIP;
+    hipLaunchKernelGGL((attn_bwd_dkv_mfma<DH, CAUSAL, NP>), grid, dim3(NP * kDkvThreads), smem_dkv, stream, qkv, dctx, lse,
+                       (const float*)delta, dqkv, s, b, heads, mask);
+  }
   return PTDP_OK;
 }
 template <int DH, bool CAUSAL>
