@@ -146,7 +146,8 @@ constexpr int kColsumRegions = 6;
 static size_t colsum_region_bytes(const Dims& d, int i) {
   size_t b = 0;
   switch (i) {
-    case 0: case 3: b = colsum_scratch_bytes((int)d.T, (int)d.h); break;
+    case 0: b = colsum_scratch_bytes((int)d.T, (int)d.h); break;
+    case 3: b = layernorm_bwd_drop_scratch_bytes((int)d.T, (int)d.h); break;
     case 1: b = colsum_scratch_bytes((int)d.T, (int)d.fp); break;
     case 4: b = colsum_scratch_bytes((int)d.T, (int)(3 * d.hp)); break;
     default: b = layernorm_bwd_scratch_bytes((int)d.T, (int)d.h); break;
@@ -390,11 +391,10 @@ int ptdp_layer_backward(ptdp_chunk* ch, int layer, int64_t microbatch, const voi
   PTDP_TRY(launch_gemm(dt, PTDP_GEMM_NT, wf(WS_DMO), P.w_2, wf(WS_BIG), nullptr, T, fp, h, 0, 0, sk, skb, st));
   PTDP_TRY(launch_bias_gelu_bwd(dt, c.gelu_mode, wf(WS_BIG), sf(PTDP_STASH_Z), P.b_1, wf(WS_BIG), G.b_1, csr[1], T, fp, st, &sums));
   PTDP_TRY(launch_gemm(dt, PTDP_GEMM_NT, wf(WS_BIG), P.w_1, wf(WS_H2), nullptr, T, h, fp, 0, 0, sk, skb, st));
-  PTDP_TRY(launch_layernorm_bwd(dt, wf(WS_H2), sf(PTDP_STASH_X1), P.ln2_g, (const float*)sf(PTDP_STASH_MU2),
-                                (const float*)sf(PTDP_STASH_RSTD2), dy, wf(WS_X1), G.ln2_g, G.ln2_b, csr[2], T, h, st, &sums));
-  // attention block
-  PTDP_TRY(launch_bda_bwd(dt, wf(WS_X1), wf(WS_H1), G.b_o, csr[3], T, h, c.p_hidden,
-                          dropout_key(c.seed, gl, 0, (uint64_t)microbatch), st, &sums));
+  // LayerNorm 2, then the attention block's dropout on the same gradient
+  PTDP_TRY(launch_layernorm_bwd_drop(dt, wf(WS_H2), sf(PTDP_STASH_X1), P.ln2_g, (const float*)sf(PTDP_STASH_MU2),
+                                     (const float*)sf(PTDP_STASH_RSTD2), dy, wf(WS_X1), G.ln2_g, G.ln2_b, csr[2], wf(WS_H1), G.b_o,
+                                     csr[3], c.p_hidden, dropout_key(c.seed, gl, 0, (uint64_t)microbatch), T, h, st, &sums));
   PTDP_TRY(launch_gemm(dt, PTDP_GEMM_NT, wf(WS_H1), P.w_o, wf(WS_CTX), nullptr, T, hp, h, 0, 0, sk, skb, st));
   PTDP_TRY(launch_attn_bwd(dt, sf(PTDP_STASH_QKV), sf(PTDP_STASH_CTX), (const float*)sf(PTDP_STASH_LSE), wf(WS_CTX),
                            wf(WS_QKV), (float*)wf(WS_DELTA), c.s, c.b, (int)d.al, (int)d.dh, ch->mask, c.causal, st));

@@ -152,6 +152,12 @@ int launch_layernorm_fwd(int dtype, const void* x, const void* gain, const void*
 int launch_layernorm_bwd(int dtype, const void* du, const void* x, const void* gain, const float* mu,
                          const float* rstd, const void* resid, void* dx, float* dgain, float* dbias,
                          void* scratch, int rows, int width, hipStream_t st, ColsumBatch* defer = nullptr);
+// the same, followed by din = Drop'(dx) and dbias_in += column sums of din (launch_bda_bwd), in one pass where rows are
+// narrow enough; scratch_in: layernorm_bwd_drop_scratch_bytes
+int launch_layernorm_bwd_drop(int dtype, const void* du, const void* x, const void* gain, const float* mu, const float* rstd,
+                              const void* resid, void* dx, float* dgain, float* dbias, void* scratch, void* din, float* dbias_in,
+                              void* scratch_in, float p, uint64_t key, int rows, int width, hipStream_t st,
+                              ColsumBatch* defer = nullptr);
 int launch_bias_gelu_fwd(int dtype, int mode, const void* z, const void* bias, void* g, int rows, int width,
                          hipStream_t st);
 int launch_bias_gelu_bwd(int dtype, int mode, const void* dg, const void* z, const void* bias, void* dz,
@@ -168,6 +174,7 @@ bool profiling_enabled();
 int launch_dropout_mask(uint8_t* keep, int64_t n, float p, uint64_t key, hipStream_t st);
 size_t colsum_scratch_bytes(int rows, int width);
 size_t layernorm_bwd_scratch_bytes(int rows, int width);   // scratch of launch_layernorm_bwd
+size_t layernorm_bwd_drop_scratch_bytes(int rows, int width);
 // out[width] (fp32) += column sums of in[rows, width]
 int launch_colsum(int dtype, const void* in, float* out, void* scratch, int rows, int width, hipStream_t st,
                   ColsumBatch* defer = nullptr);

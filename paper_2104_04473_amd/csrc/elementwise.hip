@@ -105,13 +105,23 @@ __global__ void layernorm_fwd_kernel(const T* __restrict__ x, const T* __restric
 // Bound by memory for wide rows, by one row's round trip for narrow ones.  us before (one row per block at a time) and
 // now, bf16 with residual: 8192 rows x 2048 58 -> 31, 2048 x 4096 26 -> 21.5, 2048 x 12288 58 -> 53, 1024 x 2048
 // 11.3 -> 9.9.
+// DROP: the gradient dx, as stored, also goes through the dropout in front of this residual sum, din = Drop'(dx), with the
+// column sums of din (what bda_bwd_kernel does in a pass of its own): one read of dx and a launch less.  us for the two
+// passes and for one: 8192 x 2048 45 -> 38, 2048 x 12288 77 -> 62, 666 x 512 11.5 -> 5.9.
+template <typename T> struct LnDrop {
+  T* din;
+  float* part;   // [blocks][width]
+  uint64_t key;
+  uint32_t thr;
+  float scale;
+};
 constexpr int kLnBwdThreads = 512, kLnBwdWaves = kLnBwdThreads / 64;
-template <typename T, int VPT, int GW>
+template <typename T, int VPT, int GW, bool DROP>
 __global__ void __launch_bounds__(kLnBwdThreads)
 layernorm_bwd_kernel(const T* du, const T* __restrict__ x, const T* __restrict__ gain, const float* __restrict__ mu,
                      const float* __restrict__ rstd, const T* resid, T* dx, float* __restrict__ part, int rows, int width,
-                     int rpb) {
-  constexpr int N = Vec16<T>::N, NG = kLnBwdWaves / GW;
+                     int rpb, LnDrop<T> drop) {
+  constexpr int N = Vec16<T>::N, NG = kLnBwdWaves / GW, SUMS = DROP ? 3 : 2;
   extern __shared__ __attribute__((aligned(16))) char ln_smem[];
   T* gain_s = reinterpret_cast<T*>(ln_smem);   // the gain row, read twice per row of the block
   __shared__ float red[2][2][kLnBwdWaves];
@@ -126,6 +136,11 @@ layernorm_bwd_kernel(const T* du, const T* __restrict__ x, const T* __restrict__
   for (int i = 0; i < VPT; ++i)
 #pragma unroll
     for (int j = 0; j < N; ++j) ag[i][j] = ab[i][j] = 0.f;
+  float ad[DROP ? VPT : 1][N];
+#pragma unroll
+  for (int i = 0; i < (DROP ? VPT : 1); ++i)
+#pragma unroll
+    for (int j = 0; j < N; ++j) ad[i][j] = 0.f;
   const int r0 = blockIdx.x * rpb, r1 = min(rows, r0 + rpb);
   // the residual gradient is only wanted after the reduction, but requested with the rest: one round trip per row
   typedef Vec16<T> Row[VPT];
@@ -216,6 +231,19 @@ layernorm_bwd_kernel(const T* du, const T* __restrict__ x, const T* __restrict__
           for (int j = 0; j < N; ++j) of[j] += rs * (af[j] * gf[j] - c1 - (xf[j] - m) * rs * c2);
           o.pack(of);
           o.store(dx + base + (size_t)c * N);
+          if constexpr (DROP) {
+            const size_t off = base + (size_t)c * N;
+            bool keep[N];
+            o.unpack(of);
+            keep_flags<N>(drop.key, (uint64_t)off, drop.thr, keep);
+#pragma unroll
+            for (int j = 0; j < N; ++j) {
+              of[j] = keep[j] ? of[j] * drop.scale : 0.f;
+              ad[i][j] += of[j];
+            }
+            o.pack(of);
+            o.store(drop.din + off);
+          }
         }
       }
     }
@@ -239,12 +267,12 @@ layernorm_bwd_kernel(const T* du, const T* __restrict__ x, const T* __restrict__
   }
   // the upper half of the groups hands its sums to the lower half until one is left
   if constexpr (NG > 1) {
-    float* sums = reinterpret_cast<float*>(ln_smem);   // [group][gain, bias][column]: the gain row is done with
+    float* sums = reinterpret_cast<float*>(ln_smem);   // [group][gain, bias (, din)][column]: the gain row is done with
 #pragma unroll
     for (int live = NG / 2; live > 0; live /= 2) {
       __syncthreads();
       if (grp >= live && grp < 2 * live) {
-        float* o = sums + (size_t)(grp - live) * 2 * width;
+        float* o = sums + (size_t)(grp - live) * SUMS * width;
 #pragma unroll
         for (int i = 0; i < VPT; ++i) {
           const int c = tid + i * GW * 64;
@@ -253,13 +281,14 @@ layernorm_bwd_kernel(const T* du, const T* __restrict__ x, const T* __restrict__
             for (int j = 0; j < N; ++j) {
               o[(size_t)j * nvec + c] = ag[i][j];   // [j][c]: neighbouring lanes in neighbouring banks
               o[(size_t)(N + j) * nvec + c] = ab[i][j];
+              if constexpr (DROP) o[(size_t)(2 * N + j) * nvec + c] = ad[i][j];
             }
           }
         }
       }
       __syncthreads();
       if (grp < live) {
-        const float* o = sums + (size_t)grp * 2 * width;
+        const float* o = sums + (size_t)grp * SUMS * width;
 #pragma unroll
         for (int i = 0; i < VPT; ++i) {
           const int c = tid + i * GW * 64;
@@ -268,6 +297,7 @@ layernorm_bwd_kernel(const T* du, const T* __restrict__ x, const T* __restrict__
             for (int j = 0; j < N; ++j) {
               ag[i][j] += o[(size_t)j * nvec + c];
               ab[i][j] += o[(size_t)(N + j) * nvec + c];
+              if constexpr (DROP) ad[i][j] += o[(size_t)(2 * N + j) * nvec + c];
             }
           }
         }
@@ -284,6 +314,7 @@ layernorm_bwd_kernel(const T* du, const T* __restrict__ x, const T* __restrict__
       for (int j = 0; j < N; ++j) {
         prow[(size_t)c * N + j] = ag[i][j];
         prow[(size_t)width + (size_t)c * N + j] = ab[i][j];
+        if constexpr (DROP) drop.part[(size_t)blockIdx.x * width + (size_t)c * N + j] = ad[i][j];
       }
     }
   }
@@ -766,17 +797,17 @@ size_t layernorm_bwd_scratch_bytes(int rows, int width) {
   return (size_t)((rows + rpb - 1) / rpb) * 2 * (size_t)width * sizeof(float);
 }
 
-template <typename T, int VPT, int GW>
+template <typename T, int VPT, int GW, bool DROP>
 static int ln_bwd_launch(const void* du, const void* x, const void* gain, const float* mu, const float* rstd, const void* resid,
-                         void* dx, float* part, int rows, int width, int rpb, int nblk, hipStream_t st) {
-  constexpr int NG = kLnBwdWaves / GW;
-  const size_t gain_bytes = (size_t)width * sizeof(T), sum_bytes = (size_t)(NG / 2) * 2 * width * sizeof(float);
-  constexpr int kMost = VPT * GW * 64 * Vec16<T>::N * (int)(NG > 1 ? NG * sizeof(float) : sizeof(T));   // at the widest row of this form
-  auto kern = layernorm_bwd_kernel<T, VPT, GW>;
+                         void* dx, float* part, int rows, int width, int rpb, int nblk, const LnDrop<T>& drop, hipStream_t st) {
+  constexpr int NG = kLnBwdWaves / GW, SUMS = DROP ? 3 : 2;
+  const size_t gain_bytes = (size_t)width * sizeof(T), sum_bytes = (size_t)(NG / 2) * SUMS * width * sizeof(float);
+  constexpr int kMost = VPT * GW * 64 * Vec16<T>::N * (int)(NG > 1 ? (NG / 2) * SUMS * sizeof(float) : sizeof(T));   // at the widest row of this form
+  auto kern = layernorm_bwd_kernel<T, VPT, GW, DROP>;
   static once_flag_t done[kMaxDevices];
   if (set_dynamic_smem(reinterpret_cast<const void*>(kern), kMost, done) != PTDP_OK) return PTDP_E_HIP;
   hipLaunchKernelGGL(kern, dim3(nblk), dim3(kLnBwdThreads), gain_bytes > sum_bytes ? gain_bytes : sum_bytes, st, (const T*)du,
-                     (const T*)x, (const T*)gain, mu, rstd, (const T*)resid, (T*)dx, part, rows, width, rpb);
+                     (const T*)x, (const T*)gain, mu, rstd, (const T*)resid, (T*)dx, part, rows, width, rpb, drop);
   return PTDP_OK;
 }
 template <typename T, int VPT>
@@ -789,18 +820,20 @@ static int ln_bwd_wide_launch(const void* du, const void* x, const void* gain, c
 template <typename T>
 static int ln_bwd_t(const void* du, const void* x, const void* gain, const float* mu, const float* rstd,
                     const void* resid, void* dx, float* dgain, float* dbias, void* scratch, int rows, int width,
-                    hipStream_t st, ColsumBatch* defer) {
+                    hipStream_t st, ColsumBatch* defer, LnDrop<T>* drop = nullptr) {
   constexpr int N = Vec16<T>::N;
   const int slots = (width / N + 63) / 64;   // 64-vector pieces of a row
   if (slots > 8 * kLnBwdWaves) return PTDP_E_UNSUPPORTED;
   float* part = (float*)scratch;
   const int rpb = ln_bwd_rows_per_block(rows), nblk = (rows + rpb - 1) / rpb;
   {
-    const double bytes = (double)rows * width * sizeof(T) * (resid ? 4 : 3);
+    const double bytes = (double)rows * width * sizeof(T) * ((resid ? 4 : 3) + (drop ? 1 : 0));
     Launch L(PTDP_K_LN_BWD, bytes, st);
     int rc;
 #define PTDP_LN_BWD_WIDE(V) rc = ln_bwd_wide_launch<T, V>(du, x, gain, mu, rstd, resid, dx, part, rows, width, rpb, nblk, st)
-#define PTDP_LN_BWD(V, G) rc = ln_bwd_launch<T, V, G>(du, x, gain, mu, rstd, resid, dx, part, rows, width, rpb, nblk, st)
+#define PTDP_LN_BWD(V, G)                                                                                                       \
+  rc = drop ? ln_bwd_launch<T, V, G, true>(du, x, gain, mu, rstd, resid, dx, part, rows, width, rpb, nblk, *drop, st)          \
+            : ln_bwd_launch<T, V, G, false>(du, x, gain, mu, rstd, resid, dx, part, rows, width, rpb, nblk, LnDrop<T>{}, st)
     // Waves per row: doubled while a lane would hold more than two vectors (2048 columns, 8192 rows: four 50, two 46, one
     // 51 us with the finishing launch) and while a block has fewer rows than groups (their sums' way through LDS costs
     // more than it saves: 1024 rows x 2048 27.7 -> 24.2).  Eight waves hold up to four vectors a lane, beyond that one row at a time.
@@ -817,7 +850,7 @@ static int ln_bwd_t(const void* du, const void* x, const void* gain, const float
       case 128 + 1: PTDP_LN_BWD(1, 8); break;
       case 128 + 2: PTDP_LN_BWD(2, 8); break;
       case 128 + 3: PTDP_LN_BWD(3, 8); break;
-      case 128 + 4: PTDP_LN_BWD(4, 8); break;
+      case 128 + 4: rc = ln_bwd_launch<T, 4, 8, false>(du, x, gain, mu, rstd, resid, dx, part, rows, width, rpb, nblk, LnDrop<T>{}, st); break;
       case 128 + 5: PTDP_LN_BWD_WIDE(5); break;
       case 128 + 6: PTDP_LN_BWD_WIDE(6); break;
       case 128 + 7: PTDP_LN_BWD_WIDE(7); break;
@@ -838,6 +871,38 @@ int launch_layernorm_bwd(int dtype, const void* du, const void* x, const void* g
   return dtype == PTDP_BF16
              ? ln_bwd_t<bf16_t>(du, x, gain, mu, rstd, resid, dx, dgain, dbias, scratch, rows, width, st, defer)
              : ln_bwd_t<float>(du, x, gain, mu, rstd, resid, dx, dgain, dbias, scratch, rows, width, st, defer);
+}
+
+// Rows of up to 24 x 64 vectors (12288 bf16 elements): beyond, the third set of column sums does not fit the registers.
+template <typename T>
+static int ln_bwd_drop_t(const void* du, const void* x, const void* gain, const float* mu, const float* rstd, const void* resid,
+                         void* dx, float* dgain, float* dbias, void* scratch, void* din, float* dbias_in, void* scratch_in, float p,
+                         uint64_t key, int rows, int width, hipStream_t st, ColsumBatch* defer) {
+  if (width / Vec16<T>::N > 24 * 64) {
+    const int rc = ln_bwd_t<T>(du, x, gain, mu, rstd, resid, dx, dgain, dbias, scratch, rows, width, st, defer);
+    if (rc != PTDP_OK) return rc;
+    return launch_bda_bwd(sizeof(T) == 2 ? PTDP_BF16 : PTDP_F32, dx, din, dbias_in, scratch_in, rows, width, p, key, st, defer);
+  }
+  LnDrop<T> drop{(T*)din, (float*)scratch_in, key, p > 0.f ? dropout_threshold(p) : 0u, 1.0f / (1.0f - p)};
+  const int rc = ln_bwd_t<T>(du, x, gain, mu, rstd, resid, dx, dgain, dbias, scratch, rows, width, st, defer, &drop);
+  if (rc != PTDP_OK) return rc;
+  const int rpb = ln_bwd_rows_per_block(rows), nblk = (rows + rpb - 1) / rpb;
+  return colsum_finish(drop.part, nblk, width, dbias_in, nullptr, width, st, defer);
+}
+
+size_t layernorm_bwd_drop_scratch_bytes(int rows, int width) {
+  const size_t a = colsum_scratch_bytes(rows, width), b = layernorm_bwd_scratch_bytes(rows, width) / 2;
+  return a > b ? a : b;
+}
+
+int launch_layernorm_bwd_drop(int dtype, const void* du, const void* x, const void* gain, const float* mu, const float* rstd,
+                              const void* resid, void* dx, float* dgain, float* dbias, void* scratch, void* din, float* dbias_in,
+                              void* scratch_in, float p, uint64_t key, int rows, int width, hipStream_t st, ColsumBatch* defer) {
+  if (rows == 0) return PTDP_OK;
+  return dtype == PTDP_BF16 ? ln_bwd_drop_t<bf16_t>(du, x, gain, mu, rstd, resid, dx, dgain, dbias, scratch, din, dbias_in, scratch_in,
+                                                    p, key, rows, width, st, defer)
+                            : ln_bwd_drop_t<float>(du, x, gain, mu, rstd, resid, dx, dgain, dbias, scratch, din, dbias_in, scratch_in,
+                                                   p, key, rows, width, st, defer);
 }
 
 static inline int stream_grid(size_t total_vec) {

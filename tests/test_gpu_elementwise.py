@@ -63,6 +63,15 @@ def test_layernorm_forward_backward(dtype, rows, width):
     assert_close(np64(du2), wdx, dtype, "dx in place")
 
 
+# the backward kernel's forms: 1, 2, 4 or 8 waves per row (512, 1024, 2048, 4096 bf16 columns each, up to 16384), one row to
+# sixteen rows per block, ragged last groups
+@pytest.mark.parametrize("dtype", DTYPES)
+@pytest.mark.parametrize("rows,width", [(2100, 504), (1100, 1024), (1025, 1032), (700, 2056), (515, 4096), (300, 4104), (258, 8200),
+                                        (3, 12296), (5, 16384)])
+def test_layernorm_backward_forms(dtype, rows, width):
+    test_layernorm_forward_backward(dtype, rows, width)
+
+
 @pytest.mark.parametrize("dtype", DTYPES)
 @pytest.mark.parametrize("mode", [B.GELU_ERF, B.GELU_TANH])
 @pytest.mark.parametrize("rows,width", [(1, 8), (70, 264), (257, 1024), (33, 12800), (3, 1032), (35, 520)])
