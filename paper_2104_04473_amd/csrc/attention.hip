@@ -31,7 +31,7 @@ typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4_t;
 // share that order), and the score tile S^T comes out with column c = the workgroup's row and rows 4 g + r = the tile's,
 // which is the second product's B operand as it stands.  These are small calls (fp32 is the precision of small
 // configurations): what counts is the length of one wave's chain and the number of waves.  128 tokens x 4 heads x 2
-// samples, dh 64: forward 101 -> 15 us, backward 165 -> 32 us against one wave per row that reduced every
+// samples, dh 64: forward 68 -> 9 us, backward 155 -> 25 us against one wave per row that reduced every
 // score across the wave.
 // ND: steps of 16 dh (dh rounded up; the lanes past dh hold zeros).
 // ------------------------------------------------------------------------------------------------
@@ -58,8 +58,9 @@ template <int ND> __device__ __forceinline__ f32x4_t f32_scores(const F32Frag<ND
 }
 // acc^T[16 dh rows x 16 columns] += X^T w for the tile rows row0 .. row0 + 15 of X (rows from s on count as zeros; their
 // weights are zero).  Register r of acc[t]: dh 16 t + 4 g + r of column c.
-// A weight that the causal mask hides is zero, but zero times an infinite or undefined element is not: a tile on the
-// diagonal (`vis`: bit r = row 4 g + r is visible to column c) that holds such elements adds its visible rows one by one.
+// A weight that the causal mask hides is zero, but zero times an infinite or undefined element is not: in a tile on the
+// diagonal (`vis`: bit r = row 4 g + r is visible to column c) such elements enter the product as zeros and are added
+// afterwards to the columns that see them, so that no bit of the other columns depends on them.
 template <int ND>
 __device__ __forceinline__ void f32_accumulate(f32x4_t (&acc)[ND], f32x4_t w, const float* __restrict__ X, size_t rs, int row0, int s,
                                                int dh, bool diag, uint32_t vis, int lane) {
@@ -69,33 +70,39 @@ __device__ __forceinline__ void f32_accumulate(f32x4_t (&acc)[ND], f32x4_t w, co
     const float x = X[(size_t)min(row, s - 1) * rs + min(d, dh - 1)];
     return row < s && d < dh ? x : 0.f;
   };
-  if (diag) {
-    bool finite = true;
+  if (!diag) {
 #pragma unroll
     for (int t = 0; t < ND; ++t)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) finite = finite && fabsf(at(t, r)) < INFINITY;
-    if (!__all(finite)) {
-#pragma unroll
-      for (int row = 0; row < 16; ++row) {
-        const float wr = __shfl(w[row & 3], (row >> 2) * 16 + c, 64);
-        const bool seen = (__shfl((int)vis, (row >> 2) * 16 + c, 64) >> (row & 3)) & 1;
-        if (row0 + row >= s) continue;
-#pragma unroll
-        for (int t = 0; t < ND; ++t)
-#pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            const int d = 16 * t + 4 * g + r;
-            if (d < dh && seen) acc[t][r] += wr * X[(size_t)(row0 + row) * rs + d];
-          }
-      }
-      return;
-    }
+      for (int r = 0; r < 4; ++r) acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(at(t, r), w[r], acc[t], 0, 0, 0);
+    return;
   }
+  bool finite = true;
 #pragma unroll
   for (int t = 0; t < ND; ++t)
 #pragma unroll
-    for (int r = 0; r < 4; ++r) acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(at(t, r), w[r], acc[t], 0, 0, 0);
+    for (int r = 0; r < 4; ++r) {
+      const float x = at(t, r);
+      const bool ok = fabsf(x) < INFINITY;
+      finite = finite && ok;
+      acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(ok ? x : 0.f, w[r], acc[t], 0, 0, 0);
+    }
+  if (__all(finite)) return;
+#pragma unroll 1
+  for (int row = 0; row < 16 && row0 + row < s; ++row) {
+    const int src = (row >> 2) * 16 + c, k = row & 3;
+    const float wr = __shfl(k & 2 ? (k & 1 ? w[3] : w[2]) : (k & 1 ? w[1] : w[0]), src, 64);
+    const bool seen = (__shfl((int)vis, src, 64) >> k) & 1;
+    const float* x = X + (size_t)(row0 + row) * rs + 4 * g;
+#pragma unroll
+    for (int t = 0; t < ND; ++t)
+      if (16 * t + 4 * g < dh) {
+        const f32x4_t v = *reinterpret_cast<const f32x4_t*>(x + 16 * t);
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          if (seen && !(fabsf(v[r]) < INFINITY)) acc[t][r] += wr * v[r];
+      }
+  }
 }
 // waves 1 .. 3 hand their sums to wave 0 (added in that order); returns true in wave 0.  part: 3 * ND * 64 vectors.
 template <int ND> __device__ __forceinline__ bool f32_join(f32x4_t (&acc)[ND], f32x4_t* part, int wave, int lane) {

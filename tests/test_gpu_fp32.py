@@ -83,10 +83,10 @@ def test_attention_fp32_future_tokens_stay_hidden(bad):
     q2 = qkv.clone()
     q2[at:, :, hp:] = bad
     ctx2, _, dqkv2 = forward_backward(q2, dctx, s, b, heads, dh)
-    # (rows of a tile with such values are added one by one instead of in the matrix unit's order: rounding only)
-    assert torch.allclose(ctx[:at], ctx2[:at], rtol=1e-5, atol=1e-6)
-    assert torch.allclose(dqkv[:at, :, :hp], dqkv2[:at, :, :hp], rtol=1e-5, atol=1e-6)
+    assert torch.equal(ctx[:at], ctx2[:at])
+    assert torch.equal(dqkv[:at, :, :hp], dqkv2[:at, :, :hp])
+    assert not bool(torch.isfinite(ctx2[at:]).any())   # the tokens that see such a value do not lose it
     d3 = dctx.clone()
     d3[:at] = bad
     _, _, dqkv3 = forward_backward(qkv, d3, s, b, heads, dh)
-    assert torch.allclose(dqkv[at:, :, hp:], dqkv3[at:, :, hp:], rtol=1e-5, atol=1e-6)
+    assert torch.equal(dqkv[at:, :, hp:], dqkv3[at:, :, hp:])
