@@ -164,12 +164,13 @@ attn_fwd_f32(const float* __restrict__ qkv, float* __restrict__ ctx, float* __re
     }
     mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
     mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-    const float corr = __expf(m - mx);   // the tile's first key is visible to every row of the workgroup: mx > -inf
+    const float ref = mx == -INFINITY ? 0.f : mx;   // only scores of -inf so far: weights of zero, not exp(-inf + inf)
+    const float corr = __expf(m - ref);
     m = mx;
     l *= corr;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      p[r] = __expf(p[r] - mx);
+      p[r] = __expf(p[r] - ref);
       l += p[r];
     }
 #pragma unroll

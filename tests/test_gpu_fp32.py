@@ -90,3 +90,26 @@ def test_attention_fp32_future_tokens_stay_hidden(bad):
     d3[:at] = bad
     _, _, dqkv3 = forward_backward(qkv, d3, s, b, heads, dh)
     assert torch.equal(dqkv[at:, :, hp:], dqkv3[at:, :, hp:])
+
+
+@pytest.mark.parametrize("causal", [True, False])
+def test_attention_fp32_scores_of_minus_infinity(causal):
+    """A score of -inf has probability zero, also where it is the only one (causal: query 16 and key 16) or all of those (16 keys,
+    no mask) that a wave sees in its first tile; the key in front of them is finite for every query."""
+    s, b, heads, dh = 40, 1, 2, 24
+    hp = heads * dh
+    qkv = randn((s, b, 3 * hp), B.F32, 1)
+    qkv[..., 0:hp:dh] = qkv[..., 0:hp:dh].abs() + 0.1            # first element of every query positive
+    qkv[16:17 if causal else 32, :, hp:2 * hp:dh] = -float("inf")    # first element of those keys
+    ctx, lse = torch.zeros((s, b, hp), device="cuda"), torch.zeros((b, heads, s), device="cuda")
+    if causal:
+        B.check(B.ptdp_attn_fwd(B.F32, qkv.data_ptr(), ctx.data_ptr(), lse.data_ptr(), s, b, heads, dh, stream()), "fwd")
+    else:
+        B.check(B.ptdp_attn_masked_fwd(B.F32, qkv.data_ptr(), None, ctx.data_ptr(), lse.data_ptr(), s, b, heads, dh, stream()), "fwd")
+    sync()
+    cfg = L.LayerConfig(h=hp, a=heads, t=1, s=s, b=b, causal=causal)
+    wctx, _, wlse = L.attention_core(np64(qkv), cfg)
+    assert np.isfinite(wctx).all()
+    assert_close(np64(ctx), wctx, B.F32, "ctx", 0.1)
+    assert np.allclose(np64(lse), wlse, rtol=1e-6, atol=1e-4)
+
