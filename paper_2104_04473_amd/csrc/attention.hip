@@ -47,14 +47,21 @@ template <int ND> __device__ __forceinline__ void f32_load(F32Frag<ND>& f, const
     f.v[i] = d < dh ? *reinterpret_cast<const f32x4_t*>(row + d) : f32x4_t{0.f, 0.f, 0.f, 0.f};
   }
 }
-// 16 x 16 products of rows a (result rows 4 g + r) and rows b (result column c)
-template <int ND> __device__ __forceinline__ f32x4_t f32_scores(const F32Frag<ND>& a, const F32Frag<ND>& b) {
-  f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
+// 16 x 16 products of rows a (result rows 4 g + r) and rows b (result column c): MFMAs FIRST .. FIRST + N - 1 of 4 dh each
+// (of 4 ND), added up as a tree whose leaves are chains of kF32Leaf.
+// One chain over dh had up to twice the error of the tree.
+template <int ND, int FIRST = 0, int N = 4 * ND>
+__device__ __forceinline__ f32x4_t f32_scores(const F32Frag<ND>& a, const F32Frag<ND>& b) {
+  constexpr int kF32Leaf = ND > 10 ? 8 : 4;   // (heads beyond 160: a shorter chain's registers would spill)
+  if constexpr (N > kF32Leaf) {
+    constexpr int kHalf = (N / kF32Leaf + 1) / 2 * kF32Leaf;
+    return f32_scores<ND, FIRST, kHalf>(a, b) + f32_scores<ND, FIRST + kHalf, N - kHalf>(a, b);
+  } else {
+    f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-  for (int i = 0; i < ND; ++i)
-#pragma unroll
-    for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a.v[i][e], b.v[i][e], acc, 0, 0, 0);
-  return acc;
+    for (int i = FIRST; i < FIRST + N; ++i) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a.v[i / 4][i % 4], b.v[i / 4][i % 4], acc, 0, 0, 0);
+    return acc;
+  }
 }
 // acc^T[16 dh rows x 16 columns] += X^T w for the tile rows row0 .. row0 + 15 of X (rows from s on count as zeros; their
 // weights are zero).  Register r of acc[t]: dh 16 t + 4 g + r of column c.
