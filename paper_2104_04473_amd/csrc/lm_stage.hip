@@ -41,23 +41,31 @@ __global__ void embed_fwd_kernel(const int32_t* __restrict__ tokens, const T* __
 
 // Backward: d = Drop'(dx), d_pos[i, :] += sum_j d[i, j, :] (j in order) and d_word[r, :] += sum over the tokens with id
 // v0 + r of d[token, :] in token order, in one launch.  The first row_blocks workgroups take kEmbedRows vocabulary rows
-// each: they read the token ids once, note in LDS which tokens name which of their rows (one bit per token, 64 ids per
-// ballot) and add up the rows that any token names, each wave its own slices of 64 column vectors: no atomics, no two
-// waves touch the same element, rows that no token names are left untouched.  The other workgroups walk the positions.
-// Dropping out again from dx costs a hash per four elements and saves writing d and reading it back.  Bound by the
-// read-modify-write of d_pos.  Before: a launch that wrote d (50 us) and one workgroup per row whose four waves each read
-// all ids twice, one load at a time (81 us; 2048 tokens x 12288, 6400 rows); now about 58 us together.
-constexpr int kEmbedThreads = 512, kEmbedRows = 8, kEmbedChunks = 128;   // tokens per round: 64 * kEmbedChunks
+// each: they read the token ids once, list the tokens that name one of their rows, row by row in token order, in LDS, and
+// add them up, each wave its own slices of 64 column vectors: no atomics, no two waves touch the same element, rows that no
+// token names are left untouched.  The other workgroups walk the positions.
+// Dropping out again from dx costs a hash per four elements and saves writing d and reading it back.
+// Bound by the read-modify-write of d_pos where ids are spread evenly, and by the chain of hashes and additions of the most
+// frequent row otherwise (0.2 us a token).  us, before (a launch that wrote d and one workgroup per row whose waves read all
+// ids twice, one load at a time) and now, bf16, even ids / ids with frequency 1 / rank: 2048 tokens x 12288, 6400 rows
+// 116 / 519 -> 45 / 221; 8192 x 1024, 128 rows 52 / 376 -> 17 / 283; 48 x 1024, 50000 rows 14.9 / 14.5 -> 13.8 / 13.4.
+// Batches of 8 gain 15 % on frequent ids and lose 5 % on even ones.
+constexpr int kEmbedThreads = 512, kEmbedWaves = kEmbedThreads / 64, kEmbedRows = 8;
+constexpr int kEmbedChunks = 128;   // tokens per round: 64 * kEmbedChunks
+constexpr int kEmbedBatch = 4;      // tokens of a row requested together
+static_assert(kEmbedRows == kEmbedWaves && kEmbedChunks == 128, "a wave lists one row, two words per lane");
+// acc += Drop'(a); z = key + kGolden * (index of a's first element / 4), as in keep_flags
 template <typename T>
-__device__ __forceinline__ void embed_drop(const T* __restrict__ dx, size_t v, uint64_t key, uint32_t thr, float scale, float* af) {
+__device__ __forceinline__ void embed_add(const Vec16<T>& a, uint64_t z, uint32_t thr, float scale, float (&acc)[Vec16<T>::N]) {
   constexpr int N = Vec16<T>::N;
-  Vec16<T> a;
-  bool keep[N];
-  a.load(dx + v * N);
+  float af[N];
   a.unpack(af);
-  keep_flags<N>(key, (uint64_t)v * N, thr, keep);
 #pragma unroll
-  for (int e = 0; e < N; ++e) af[e] = keep[e] ? af[e] * scale : 0.f;
+  for (int w = 0; w < N / 4; ++w) {
+    const uint64_t r = mix64(z + kGolden * w);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) acc[4 * w + j] = fmaf((uint32_t)((r >> (16 * j)) & 0xffffu) >= thr ? af[4 * w + j] : 0.f, scale, acc[4 * w + j]);
+  }
 }
 template <typename T>
 __global__ void __launch_bounds__(kEmbedThreads)
@@ -73,10 +81,10 @@ embed_bwd_kernel(const int32_t* __restrict__ tokens, const T* __restrict__ dx, f
 #pragma unroll
       for (int e = 0; e < N; ++e) acc[e] = 0.f;
       for (int j = 0; j < b; ++j) {
-        float af[N];
-        embed_drop<T>(dx, (pos * b + j) * nvec_row + c, key, thr, scale, af);
-#pragma unroll
-        for (int e = 0; e < N; ++e) acc[e] += af[e];
+        const size_t v = (pos * b + j) * nvec_row + c;
+        Vec16<T> a;
+        a.load(dx + v * N);
+        embed_add<T>(a, key + kGolden * (v * (N / 4)), thr, scale, acc);
       }
       float* o = d_pos + i * N;
 #pragma unroll
@@ -84,55 +92,99 @@ embed_bwd_kernel(const int32_t* __restrict__ tokens, const T* __restrict__ dx, f
     }
     return;
   }
-  __shared__ unsigned long long named[kEmbedRows][kEmbedChunks];
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, row0 = (int)blockIdx.x * kEmbedRows, rows = min(kEmbedRows, vrows - row0);
-  const int id0 = v0 + row0, ntok = s * b;
+  __shared__ unsigned long long named[kEmbedRows][kEmbedChunks];   // bit t of word ch: token 64 ch + t of the round names the row
+  __shared__ uint16_t list[64 * kEmbedChunks];                     // the tokens of row 0, of row 1, ..
+  __shared__ int count[kEmbedRows];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  // rows blockIdx.x, blockIdx.x + row_blocks, ..: frequent ids are often neighbours
+  const int row0 = (int)blockIdx.x, rows = (vrows - row0 + row_blocks - 1) / row_blocks, ntok = s * b, slices = (nvec_row + 63) / 64;
   for (int base = 0; base < ntok; base += 64 * kEmbedChunks) {
-    __syncthreads();   // `named` of the previous round no longer read
+    const int chunks = min(kEmbedChunks, (ntok - base + 63) / 64);
 #pragma unroll 4
-    for (int ch = wave; ch < kEmbedChunks; ch += kEmbedThreads / 64) {
+    for (int ch = wave; ch < chunks; ch += kEmbedWaves) {
       const int t = base + ch * 64 + lane;
-      const uint32_t local = t < ntok ? (uint32_t)tokens[t] - (uint32_t)id0 : ~0u;
+      const uint32_t local = t < ntok ? (uint32_t)tokens[t] - (uint32_t)v0 : ~0u;
       unsigned long long mine = 0;
-      if (__any(local < (uint32_t)rows)) {
 #pragma unroll
-        for (int r = 0; r < kEmbedRows; ++r) {
-          const unsigned long long m = __ballot(local == (uint32_t)r);
-          if (lane == r) mine = m;
-        }
+      for (int r = 0; r < kEmbedRows; ++r) {   // (rows past the last one: read by nobody)
+        const unsigned long long m = __ballot(local == (uint32_t)(row0 + r * row_blocks));
+        if (lane == r) mine = m;
       }
       if (lane < kEmbedRows) named[lane][ch] = mine;
     }
     __syncthreads();
-    for (int r = 0; r < rows; ++r) {
-      static_assert(kEmbedChunks == 128, "two words per lane");
-      const unsigned long long full[2] = {__ballot(named[r][lane] != 0), __ballot(named[r][64 + lane] != 0)};
-      if ((full[0] | full[1]) == 0) continue;
-      for (int c = wave * 64 + lane; c - lane < nvec_row; c += kEmbedThreads) {
-        const bool col_ok = c < nvec_row;
-        float acc[N];
+    // wave r counts row r: `before` = the row's tokens ahead of this lane's two words
+    unsigned long long word[2];
+    int mine = 0, before = 0;
+    if (wave < rows) {
+      // lane l takes words 2 l and 2 l + 1: tokens in order across the lanes
 #pragma unroll
-        for (int e = 0; e < N; ++e) acc[e] = 0.f;
+      for (int h = 0; h < 2; ++h) {
+        word[h] = 2 * lane + h < chunks ? named[wave][2 * lane + h] : 0;
+        mine += __popcll(word[h]);
+      }
+      before = mine;
 #pragma unroll
-        for (int w = 0; w < 2; ++w)
-          for (unsigned long long f = full[w]; f; f &= f - 1) {
-            const int ch = w * 64 + __ffsll((long long)f) - 1;
-            for (unsigned long long m = named[r][ch]; m; m &= m - 1) {
-              const size_t t = (size_t)base + ch * 64 + __ffsll((long long)m) - 1;
-              if (!col_ok) continue;
-              float af[N];
-              embed_drop<T>(dx, t * nvec_row + c, key, thr, scale, af);
+      for (int d = 1; d < 64; d *= 2) {
+        const int up = __shfl_up(before, d, 64);
+        if (lane >= d) before += up;
+      }
+      if (lane == 63) count[wave] = before;
+      before -= mine;
+    } else if (lane == 63) {
+      count[wave] = 0;
+    }
+    __syncthreads();
+    int total = 0;
 #pragma unroll
-              for (int e = 0; e < N; ++e) acc[e] += af[e];
+    for (int r = 0; r < kEmbedRows; ++r) {
+      if (r == wave) before += total;
+      total += count[r];
+    }
+    if (total > 0) {
+      if (wave < rows) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+          for (unsigned long long m = word[h]; m; m &= m - 1)
+            list[before++] = (uint16_t)((2 * lane + h) * 64 + __ffsll((long long)m) - 1);
+      }
+      __syncthreads();
+      int first = 0;
+      for (int r = 0; r < rows; ++r) {
+        const int n = __builtin_amdgcn_readfirstlane(count[r]);
+        // the rows' slices go round the waves in one sequence: a row of few slices leaves the other waves to the next rows
+        for (int sl = (wave - r * slices) & (kEmbedWaves - 1); n > 0 && sl < slices; sl += kEmbedWaves) {
+          const int c = sl * 64 + lane, cc = min(c, nvec_row - 1);
+          const uint64_t z_lane = key + kGolden * ((uint64_t)cc * (N / 4));
+          float acc[N];
+#pragma unroll
+          for (int e = 0; e < N; ++e) acc[e] = 0.f;
+          for (int i = 0; i < n; i += 64) {
+            const int m = min(64, n - i), toks = list[first + i + min(lane, m - 1)];
+            for (int k0 = 0; k0 < m; k0 += kEmbedBatch) {
+              Vec16<T> a[kEmbedBatch];
+              uint64_t z[kEmbedBatch];   // a token's share of z: the same in every lane, so that a lane is left with two products
+#pragma unroll
+              for (int k = 0; k < kEmbedBatch; ++k) {   // (past the end: the last token again, not added)
+                const size_t v = (size_t)(base + __builtin_amdgcn_readlane(toks, min(k0 + k, m - 1))) * nvec_row;
+                a[k].load(dx + (v + cc) * N);
+                z[k] = kGolden * (v * (N / 4));
+              }
+#pragma unroll
+              for (int k = 0; k < kEmbedBatch; ++k)
+                if (k0 + k < m) embed_add<T>(a[k], z_lane + z[k], thr, scale, acc);
             }
           }
-        if (col_ok) {
-          float* o = d_word + ((size_t)(row0 + r) * nvec_row + c) * N;
+          if (c < nvec_row) {
+            float* o = d_word + ((size_t)(row0 + r * row_blocks) * nvec_row + c) * N;
 #pragma unroll
-          for (int e = 0; e < N; ++e) o[e] += acc[e];
+            for (int e = 0; e < N; ++e) o[e] += acc[e];
+          }
         }
+        first += n;
       }
     }
+    __syncthreads();   // `named`, `count` and `list` are free again
   }
 }
 
