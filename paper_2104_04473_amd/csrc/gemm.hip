@@ -27,7 +27,7 @@ typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16_t;
 // e of group q: the product's k order is free as long as both operands share it, and a k-contiguous row then gives one
 // 16-byte load per group.  The next chunk is requested before the current one is multiplied.  fp32 calls are small and
 // bound by one wave's chain of loads; before, by the k-steps of the few workgroups that 64 x 64 tiles of plain FMAs gave.
-// us: 256 x 256 outputs over k = 256, 768, 1024 on average 110 -> 9; 256 x 1024 x 256 49 -> 5.3.
+// us: 256 x 256 x 256 40 -> 4.2, x 1024 148 -> 12; 1024 x 1024 x 1024 191 -> 30; 4096 x 4096 x 1024 730 -> 358.
 // VA, VB: the operand's rows are k-contiguous, 16-byte aligned and a multiple of four long; otherwise any strides.
 // ------------------------------------------------------------------------------------------------
 constexpr int kF32Chunk = 32;
@@ -52,8 +52,9 @@ template <bool V> struct F32Operand {
     }
   }
 };
+constexpr int f32_most_waves(int nb) { return nb == 1 ? 8 : 4; }   // waves that share a tile's k range
 template <bool VA, bool VB, int NB>
-__global__ void __launch_bounds__(512)
+__global__ void __launch_bounds__(64 * f32_most_waves(NB))
 gemm_f32_kernel(const float* __restrict__ A, const float* __restrict__ B, float* C, const float* __restrict__ bias,
                 int M, int N, int K, size_t a_rs, size_t a_cs, size_t b_rs, size_t b_cs, int accumulate) {
   extern __shared__ __attribute__((aligned(16))) float part[];
@@ -139,20 +140,22 @@ static int launch_gemm_f32_t(const float* A, const float* B, float* C, const flo
   auto kern = gemm_f32_kernel<VA, VB, NB>;
   constexpr int kTile = 32 * NB, kPart = kTile * (kTile + 8) * (int)sizeof(float);
   static once_flag_t done[kMaxDevices];
-  if (set_dynamic_smem(reinterpret_cast<const void*>(kern), (NB == 1 ? 8 : 4) * kPart, done) != PTDP_OK) return PTDP_E_HIP;
+  if (set_dynamic_smem(reinterpret_cast<const void*>(kern), f32_most_waves(NB) * kPart, done) != PTDP_OK) return PTDP_E_HIP;
   hipLaunchKernelGGL(kern, dim3((N + kTile - 1) / kTile, (M + kTile - 1) / kTile), dim3(64 * kg), kg * kPart, st, A, B, C, bias, M, N, K,
                      a_rs, a_cs, b_rs, b_cs, accumulate);
   return PTDP_OK;
 }
 static int compute_units();
 // 64 x 64 tiles (half the operand traffic) once they give every SIMD a wave, 32 x 32 before; up to 8 (4) waves share a
-// tile's k range, fewer when the tiles alone fill the chip or the range has fewer chunks.
+// tile's k range, fewer when the tiles alone fill the chip or the range has fewer chunks.  us with 32 x 32 and 64 x 64: 1024 x
+// 1024 (256 tiles of 64 x 64) over k = 256 13.6, 13.2, over 1024 45, 29; 768 x 768 (144 tiles) 10.5, 13.0 and 33, 28.  16 waves
+// per CU or 4: 512 x 512 x 1024 12.6, 11.4; 2048 x 2048 x 256 47, 36; 1536 x 1536 x 1024 81, 92; 3072 x 3072 x 1024 264, 264.
 template <bool VA, bool VB>
 static int launch_gemm_f32(const float* A, const float* B, float* C, const float* bias, int M, int N, int K, size_t a_rs, size_t a_cs,
                            size_t b_rs, size_t b_cs, int accumulate, hipStream_t st) {
   const long long ncu = compute_units(), t1 = (long long)((M + 31) / 32) * ((N + 31) / 32), t2 = (long long)((M + 63) / 64) * ((N + 63) / 64);
   const bool big = t2 >= ncu;
-  int kg = big ? 4 : 8;
+  int kg = f32_most_waves(big ? 2 : 1);
   while (kg > 1 && (kg > (K + kF32Chunk - 1) / kF32Chunk || (big ? t2 : t1) * kg > 16 * ncu)) kg /= 2;
   if (big) return launch_gemm_f32_t<VA, VB, 2>(A, B, C, bias, M, N, K, a_rs, a_cs, b_rs, b_cs, accumulate, kg, st);
   return launch_gemm_f32_t<VA, VB, 1>(A, B, C, bias, M, N, K, a_rs, a_cs, b_rs, b_cs, accumulate, kg, st);
