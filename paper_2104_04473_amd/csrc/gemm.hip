@@ -473,7 +473,11 @@ __device__ __forceinline__ void gemm_mainloop(TileAcc& acc, const GemmArgs& g, i
 }
 
 // Output forms.
-enum { OUT_BF16 = 0, OUT_F32_STORE = 1, OUT_F32_RMW = 2 };
+enum { OUT_BF16 = 0, OUT_F32_STORE = 1, OUT_F32_RMW = 2, OUT_F32_RMW_LINES = 3 };
+// Gradient accumulators are touched once per launch: non-temporal accesses (.._LINES) where the rows of C start on a line of 128
+// bytes.  Elsewhere the two parts of a line belong to different accesses and the second would fetch it again: us for += 7016
+// x 9080 x 248 non-temporal 194, plain 151 (8192 x 8200 x 2048 323, 309); 25600 x 12800 x 2048 the other way round, 1296, 1408.
+static inline bool whole_lines(size_t ldc) { return ldc * sizeof(float) % 128 == 0; }
 constexpr size_t kWideRow = (size_t)1 << 23;   // bytes; rows of C from here on take 64-bit addresses
 
 // Lane-to-memory mapping: with four consecutive columns per lane a block's store would cover 16 rows x 64 bytes (fp32)
@@ -490,7 +494,8 @@ __device__ __forceinline__ void gemm_epilogue(const StripAcc<NS, RB>& acc, const
   typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
   typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
   constexpr uint32_t esz = OUT == OUT_BF16 ? 2 : 4;
-  constexpr int kAux = OUT == OUT_F32_RMW ? 2 : 0;   // gradient accumulators are touched once per launch: non-temporal
+  constexpr bool kRmw = OUT == OUT_F32_RMW || OUT == OUT_F32_RMW_LINES;
+  constexpr int kAux = OUT == OUT_F32_RMW_LINES ? 2 : 0;
   const int lane = threadIdx.x & 63, l15 = lane & 15, q = lane >> 4;
   float bv[NS][2][4];
 #pragma unroll
@@ -517,7 +522,7 @@ __device__ __forceinline__ void gemm_epilogue(const StripAcc<NS, RB>& acc, const
           for (int r = 0; r < 4; ++r) {
             const float v = acc[b][i][j][r] + bv[b][j][r];
             if (OUT == OUT_BF16) reinterpret_cast<bf16_t*>(Cv)[at + r] = f32_to_bf16(v);
-            else if (OUT == OUT_F32_RMW) reinterpret_cast<float*>(Cv)[at + r] += v;
+            else if (kRmw) reinterpret_cast<float*>(Cv)[at + r] += v;
             else reinterpret_cast<float*>(Cv)[at + r] = v;
           }
         }
@@ -561,10 +566,10 @@ __device__ __forceinline__ void gemm_epilogue(const StripAcc<NS, RB>& acc, const
 #pragma unroll
       for (int i = 0; i < RB * 2; ++i) old[b & 1][i] = __builtin_amdgcn_raw_buffer_load_b128(rc, at(b, i >> 1, i & 1), 0, kAux);
     };
-    if (OUT == OUT_F32_RMW) fetch_old(0);
+    if (kRmw) fetch_old(0);
 #pragma unroll
     for (int b = 0; b < NS; ++b) {
-      if (OUT == OUT_F32_RMW && b + 1 < NS) fetch_old(b + 1);
+      if (kRmw && b + 1 < NS) fetch_old(b + 1);
 #pragma unroll
       for (int i = 0; i < RB; ++i) {
         f32x4_t v[2];
@@ -577,7 +582,7 @@ __device__ __forceinline__ void gemm_epilogue(const StripAcc<NS, RB>& acc, const
         }
 #pragma unroll
         for (int half = 0; half < 2; ++half) {
-          if (OUT == OUT_F32_RMW) v[half] += __builtin_bit_cast(f32x4_t, old[b & 1][i * 2 + half]);
+          if (kRmw) v[half] += __builtin_bit_cast(f32x4_t, old[b & 1][i * 2 + half]);
           __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, v[half]), rc, at(b, i, half), 0, kAux);
         }
       }
@@ -1034,9 +1039,9 @@ static int launch_small_form(int form, const GemmArgs& g, void* C, hipStream_t s
   }
 }
 // several problems, see gemm_bf16_dp_multi_kernel; a.start is filled here
-template <int BM, int BN, int S, int KG>
+template <int OUT, int BM, int BN, int S, int KG>
 static int launch_small_multi(MultiArgs& a, hipStream_t st) {
-  auto kern = gemm_bf16_small_multi_kernel<true, true, OUT_F32_RMW, BM, BN, S, KG>;
+  auto kern = gemm_bf16_small_multi_kernel<true, true, OUT, BM, BN, S, KG>;
   static once_flag_t done[kMaxDevices];
   constexpr int smem = SmallGeom<BM, BN, S, KG>::kSmem;
   if (set_dynamic_smem(reinterpret_cast<const void*>(kern), smem, done) != PTDP_OK) return PTDP_E_HIP;
@@ -1216,8 +1221,8 @@ static int launch_bf16_mode(const void* A, const void* B, void* C, const void* b
   const int form = choose_form(TA ? PTDP_GEMM_TN : (TB ? PTDP_GEMM_NN : PTDP_GEMM_NT), M, N, K, out_f32, accumulate, bias != nullptr,
                                ws != nullptr ? ws_bytes : 0, &P);
   if (form >= 0) {
-    constexpr int OUT = TA ? OUT_F32_RMW : OUT_BF16;
-    return launch_small_form<TA, TB, OUT>(form, g, C, st);
+    if constexpr (TA) return whole_lines(g.ldc) ? launch_small_form<TA, TB, OUT_F32_RMW_LINES>(form, g, C, st) : launch_small_form<TA, TB, OUT_F32_RMW>(form, g, C, st);
+    else return launch_small_form<TA, TB, OUT_BF16>(form, g, C, st);
   }
   const int ncu = compute_units();
   const int tiles_m = (M + kBM - 1) / kBM, tiles_n = (N + kBN - 1) / kBN;
@@ -1227,7 +1232,7 @@ static int launch_bf16_mode(const void* A, const void* B, void* C, const void* b
     d.N = n_dp;
     int rc;
     if (!out_f32) rc = launch_dp<TA, TB, OUT_BF16>(d, C, st);
-    else if (accumulate) rc = launch_dp<TA, TB, OUT_F32_RMW>(d, C, st);
+    else if (accumulate) rc = whole_lines(g.ldc) ? launch_dp<TA, TB, OUT_F32_RMW_LINES>(d, C, st) : launch_dp<TA, TB, OUT_F32_RMW>(d, C, st);
     else rc = launch_dp<TA, TB, OUT_F32_STORE>(d, C, st);
     if (rc != PTDP_OK) return rc;
   }
@@ -1257,7 +1262,8 @@ static int launch_bf16_mode(const void* A, const void* B, void* C, const void* b
     if (tile0 != tiles_m * ((r.N + kBN - 1) / kBN)) return PTDP_E_STATE;   // the groups cover the remainder exactly
     int rc;
     if (!out_f32) rc = launch_split<TA, TB, OUT_BF16>(r, Cr, (float*)ws, sg, blocks, st);
-    else if (accumulate) rc = launch_split<TA, TB, OUT_F32_RMW>(r, Cr, (float*)ws, sg, blocks, st);
+    else if (accumulate) rc = whole_lines(g.ldc) ? launch_split<TA, TB, OUT_F32_RMW_LINES>(r, Cr, (float*)ws, sg, blocks, st)
+                                                 : launch_split<TA, TB, OUT_F32_RMW>(r, Cr, (float*)ws, sg, blocks, st);
     else rc = launch_split<TA, TB, OUT_F32_STORE>(r, Cr, (float*)ws, sg, blocks, st);
     if (rc != PTDP_OK) return rc;
     // one reduce launch over the groups that were split (they are adjacent: a group with one part comes last, if at all)
@@ -1292,6 +1298,22 @@ static GemmArgs tn_args(const void* A, const void* B, int M, int N, int K) {
   g.ldb = (size_t)N;
   g.ldc = (size_t)N;
   return g;
+}
+
+template <int OUT> static int launch_tn_multi(int form, MultiArgs& a, hipStream_t st) {
+  switch (form) {
+    case 0: return launch_small_multi<OUT, 128, 128, 2, 1>(a, st);
+    case 1: return launch_small_multi<OUT, 128, 128, 2, 2>(a, st);
+    case 2: return launch_small_multi<OUT, 128, 64, 3, 2>(a, st);
+    case 3: return launch_small_multi<OUT, 64, 64, 4, 2>(a, st);
+    case 4: return launch_small_multi<OUT, 128, 64, 2, 1>(a, st);
+    default: break;
+  }
+  auto kern = gemm_bf16_dp_multi_kernel<true, true, OUT>;
+  static once_flag_t done[kMaxDevices];
+  if (set_dynamic_smem(reinterpret_cast<const void*>(kern), kGemmSmem, done) != PTDP_OK) return PTDP_E_HIP;
+  hipLaunchKernelGGL(kern, dim3(a.start[kMaxMulti]), dim3(kGemmThreads), kGemmSmem, st, a);
+  return PTDP_OK;
 }
 
 // C_j[M_j,N_j] += A_j^T B_j for j < n <= 4 (fp32 C, both operands [K, .]), sharing K: weight gradients whose inputs
@@ -1332,22 +1354,10 @@ int launch_gemm_tn_multi(int dtype, int n, const void* const* A, const void* con
     t_large = (double)((tiles + compute_units() - 1) / compute_units()) * (cost.step * ((K + BK - 1) / BK) + cost.round);
   }
   const int form = small_form(1, n, M, N, K, t_large);
-  if (form >= 0) {
-    int rc;
-    switch (form) {
-      case 0: rc = launch_small_multi<128, 128, 2, 1>(a, st); break;
-      case 1: rc = launch_small_multi<128, 128, 2, 2>(a, st); break;
-      case 2: rc = launch_small_multi<128, 64, 3, 2>(a, st); break;
-      case 3: rc = launch_small_multi<64, 64, 4, 2>(a, st); break;
-      default: rc = launch_small_multi<128, 64, 2, 1>(a, st); break;
-    }
-    return rc != PTDP_OK ? rc : L.status();
-  }
-  auto kern = gemm_bf16_dp_multi_kernel<true, true, OUT_F32_RMW>;
-  static once_flag_t done[kMaxDevices];
-  if (set_dynamic_smem(reinterpret_cast<const void*>(kern), kGemmSmem, done) != PTDP_OK) return PTDP_E_HIP;
-  hipLaunchKernelGGL(kern, dim3(at), dim3(kGemmThreads), kGemmSmem, st, a);
-  return L.status();
+  bool lines = true;
+  for (int j = 0; j < n; ++j) lines = lines && whole_lines(N[j]);
+  const int rc = lines ? launch_tn_multi<OUT_F32_RMW_LINES>(form, a, st) : launch_tn_multi<OUT_F32_RMW>(form, a, st);
+  return rc != PTDP_OK ? rc : L.status();
 }
 
 int launch_gemm(int dtype, int mode, const void* A, const void* B, void* C, const void* bias, int M, int N, int K,

@@ -110,6 +110,25 @@ def test_gemm_rows_of_c_beyond_31_bit_offsets(out_f32, accumulate, N):
     assert bool((err <= (1e-5 if out_f32 else 2.0 ** -8) * want.abs().clamp(min=4.0)).all())
 
 
+def test_gemm_accumulates_as_fast_into_rows_that_start_inside_a_line():
+    """+= into rows of 9080 floats (36320 bytes, not a multiple of 128) against 9088: the part of a line that another access
+    takes next has to be found in the cache.  1.15 for noise; with non-temporal accesses it is 1.3 times as long."""
+    M, K, best = 7016, 248, []
+    for N in (9080, 9088):
+        a, b, c = randn((K, M), B.BF16, 1), randn((K, N), B.BF16, 2), torch.zeros((M, N), device="cuda")
+        times = []
+        for _ in range(8):
+            e = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+            e[0].record()
+            for _ in range(4):
+                B.check(B.ptdp_gemm(B.BF16, B.GEMM_TN, a.data_ptr(), b.data_ptr(), c.data_ptr(), None, M, N, K, 1, 1, None, 0, stream()), "gemm")
+            e[1].record()
+            sync()
+            times.append(e[0].elapsed_time(e[1]))
+        best.append(min(times))
+    assert best[0] <= 1.15 * best[1], best
+
+
 @pytest.mark.parametrize("mode", [B.GEMM_NN, B.GEMM_NT, B.GEMM_TN])
 @pytest.mark.parametrize("K,Kpad", [(192, 256), (200, 256), (4096, 4104), (520, 576)])
 def test_gemm_zero_padding_along_k_changes_no_bit(mode, K, Kpad):
