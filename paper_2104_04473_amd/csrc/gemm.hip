@@ -1070,30 +1070,43 @@ static int compute_units() {
 // every split group stores at most one slab per compute unit
 size_t gemm_workspace_bytes() { return (size_t)compute_units() * kMaxSplitGroups * kSlabFloats * sizeof(float); }
 
-// Times in microseconds that decide how a call is cut, fitted to 620 measured calls (M 256 .. 8192, N 256 .. 15360, K 256
-// .. 12288; rms error 6-12 %; picking by them costs 1-4 % over always picking the best).  Outputs in bf16, or += into fp32.
+// Times in microseconds that decide how a call is cut (outputs in bf16, or += into fp32), fitted to measured calls: see
+// profiles/gemm_forms.txt for the calls, each fit's error and what picking by these numbers costs.
 struct LargeCost {
-  double step, round;                    // 256 x 256 tiles: per k-step, per round (first loads, output)
-  double split_step, split_slab, split_fixed;   // remainder groups: per k-step, per slab, the reduce launch
+  double fixed, step, step_alone, round, round_alone;   // 256 x 256 tiles: per k-step and per round (first loads, output), full chip and one tile
+  double split_fixed, split_step, split_slab, split_part, split_reduce;   // remainder groups: per k-step, per slab; reduce: per slab of one tile or, if more, of all
 };
-static const LargeCost kLargeCost[2] = {{1.10, 10.0, 1.29, 0.10, 3.0}, {1.20, 22.0, 1.50, 0.02, 32.0}};
+static const LargeCost kLargeCost[2] = {{3.9, 1.28, 0.78, 8.4, 2.8, 11.5, 1.28, 0.050, 0.26, 0.020},
+                                        {5.7, 1.33, 1.12, 24.4, 8.7, 3.3, 1.56, 0.023, 0.50, 0.069}};
+
+// Whole tiles: full rounds, then one that fills part of the chip.  An XCD owns the column tiles x, x + 8, .. (gemm_dp_tile): the
+// one with the most tiles (`busiest`) sets the number of rounds.  whole: the share of the tiles' outputs that exist.
+constexpr int kMixedRounds = 12;   // rounds from which the compute units no longer run in step and one's output overlaps another's products
+static double large_time(const LargeCost& c, long long tiles, long long busiest, double whole, int nk) {
+  const int ncu = compute_units(), per_xcd = ncu >= 8 ? ncu / 8 : 1;
+  const long long rounds = (busiest + per_xcd - 1) / per_xcd, left = tiles - (rounds - 1) * ncu;
+  const double fill = left >= ncu ? 1.0 : (left > 1 ? (double)left : 1.0) / ncu;
+  const double t = c.fixed + (double)(rounds - 1) * (c.step * nk + c.round * whole) + (c.step_alone + (c.step - c.step_alone) * fill) * nk +
+                   (c.round_alone + (c.round - c.round_alone) * fill) * whole;
+  return rounds >= kMixedRounds ? 0.95 * t : t;
+}
+static long long busiest_xcd(long long tiles_m, long long tiles_n) { return tiles_m * ((tiles_n + 7) / 8); }
 
 // How a call is cut: whole rounds of tiles (whole columns of tiles, so that the remainder is fewer tiles than
 // compute units), then the remainder in at most two groups (see gemm_bf16_split_kernel).  A first group of
 // 2^a tiles is taken while one group over all remaining tiles would leave more than a tenth of the
 // compute units idle; the second group takes what is left.  The split is used when its cost is below that of
-// one more round of whole tiles.  *time: the plan's cost.
+// whole tiles.  *time: the plan's cost.
 static SplitPlan large_plan(int M, int N, int K, int out_f32, int accumulate, int has_bias, size_t ws_bytes, double* time) {
   const int ncu = compute_units();
   const int tiles_m = (M + kBM - 1) / kBM, tiles_n = (N + kBN - 1) / kBN, nk = (K + BK - 1) / BK;
   const long long tiles = (long long)tiles_m * tiles_n;
   const LargeCost& cost = kLargeCost[out_f32 && accumulate];
-  const double t_round = cost.step * nk + cost.round;
   SplitPlan P;
   P.dp_cols = tiles_n;
   P.n_groups = 0;
   for (int j = 0; j < kMaxSplitGroups; ++j) P.tiles[j] = P.parts[j] = 0;
-  *time = (double)((tiles + ncu - 1) / ncu) * t_round;
+  *time = large_time(cost, tiles, busiest_xcd(tiles_m, tiles_n), (double)M * N / ((double)tiles * kBM * kBN), nk);
   const bool out_ok = (out_f32 && accumulate && !has_bias) || !out_f32;
   if (tiles % ncu == 0 || !out_ok || ws_bytes < gemm_workspace_bytes() || (out_f32 && nk < 64)) return P;
   // whole columns only: the full rounds' tiles, rounded up to a column boundary
@@ -1115,17 +1128,18 @@ static SplitPlan large_plan(int M, int N, int K, int out_f32, int accumulate, in
     ++n;
   }
   double t_split = cost.split_fixed;
-  bool any = false;
+  int most = 0, slabs = 0;
   for (int j = 0; j < n; ++j) {
     t_split += cost.split_step * ((nk + gp[j] - 1) / gp[j]);
-    if (gp[j] > 1) {
-      t_split += cost.split_slab * gt[j] * gp[j];
-      any = true;
-    }
+    if (gp[j] <= 1) continue;
+    slabs += gt[j] * gp[j];
+    if (gp[j] > most) most = gp[j];
   }
-  if (!any || t_split >= t_round) return P;
+  t_split += cost.split_slab * slabs + (cost.split_part * most > cost.split_reduce * slabs ? cost.split_part * most : cost.split_reduce * slabs);
   // (whole columns: the full rounds may come out as one more, partly filled round)
-  *time = (double)(((long long)dp_cols * tiles_m + ncu - 1) / ncu) * t_round + t_split;
+  if (dp_cols > 0) t_split += large_time(cost, (long long)dp_cols * tiles_m, busiest_xcd(tiles_m, dp_cols), 1.0, nk);
+  if (most == 0 || t_split >= *time) return P;
+  *time = t_split;
   P.dp_cols = dp_cols;
   P.n_groups = n;
   for (int j = 0; j < n; ++j) {
@@ -1136,26 +1150,29 @@ static SplitPlan large_plan(int M, int N, int K, int out_f32, int accumulate, in
 }
 
 // Small tiles: which form (index into the table, the order of launch_small_form), or -1 for the 256 x 256 kernels.  A
-// call of n problems with `tiles` workgroups and nk k-tiles takes about
-//   fixed + each * w + steps * (pair * (w / 2) + single * (w % 2)),  w = workgroups per CU, steps = ceil(nk / groups)
+// call of n problems with `tiles` workgroups, nk k-tiles and `mb` MB of operands takes about
+//   fixed + each * w + steps * (pair * (w / 2) + single * (w % 2)) + per_mb * mb,  w = workgroups per CU, steps = ceil(nk / groups)
 // where two workgroups of a form that fits twice on a CU overlap (pair < 2 * single).
 struct SmallCost {
   int bm, bn, groups, per_cu;
-  double fixed, pair, single, each;
+  double fixed, pair, single, each, per_mb;
 };
 constexpr int kSmallForms = 5;
 static const SmallCost kSmallCost[2][kSmallForms] = {
-    {{128, 128, 1, 2, 1.5, 0.787, 0.532, 2.3},    // (most calls of 64 to 256 large tiles)
-     {128, 128, 2, 1, 0.0, 0.0, 0.880, 4.7},      // two wave groups share the k range: long k, at most one workgroup per CU
-     {128, 64, 2, 1, 1.4, 0.0, 0.540, 3.3},
-     {64, 64, 2, 1, 2.0, 0.0, 0.326, 2.6},        // the smallest outputs
-     {128, 64, 1, 2, 3.0, 0.545, 0.365, 0.7}},
-    {{128, 128, 1, 2, 0.0, 0.804, 0.547, 6.3},
-     {128, 128, 2, 1, 0.0, 0.0, 0.920, 7.4},
-     {128, 64, 2, 1, 0.9, 0.0, 0.580, 4.8},
-     {64, 64, 2, 1, 1.3, 0.0, 0.377, 3.5},
-     {128, 64, 1, 2, 1.7, 0.578, 0.394, 2.6}}};
+    {{128, 128, 1, 2, 1.9, 0.741, 0.515, 2.1, 0.135},    // (most calls of 64 to 256 large tiles)
+     {128, 128, 2, 1, 0.0, 0.0, 0.992, 3.1, 0.102},      // two wave groups share the k range: long k, at most one workgroup per CU
+     {128, 64, 2, 1, 0.0, 0.0, 0.576, 3.9, 0.079},
+     {64, 64, 2, 1, 0.7, 0.0, 0.372, 2.7, 0.103},        // the smallest outputs
+     {128, 64, 1, 2, 2.4, 0.548, 0.422, 0.9, 0.157}},
+    {{128, 128, 1, 2, 0.0, 0.742, 0.570, 5.8, 0.163},
+     {128, 128, 2, 1, 0.0, 0.0, 0.995, 6.6, 0.127},
+     {128, 64, 2, 1, 0.4, 0.0, 0.573, 4.7, 0.072},
+     {64, 64, 2, 1, 0.9, 0.0, 0.388, 3.4, 0.087},
+     {128, 64, 1, 2, 1.4, 0.510, 0.356, 2.8, 0.159}}};
 constexpr int kMinStepsForGroups = 8;   // k-tiles from which two wave groups are considered: below, joining their sums costs what they save
+// Not considered with that many workgroups per CU over that many k-tiles: the panels no longer stay in the caches and the time is
+// up to 1.6 times the above (128 x 64, 16 workgroups, 100 k-tiles).
+constexpr int kManyRounds = 16, kManySteps = 32;
 
 static int small_form(int rmw, int n, const int* M, const int* N, int K, double t_large) {
   const int ncu = compute_units(), nk = (K + BK - 1) / BK;
@@ -1164,10 +1181,15 @@ static int small_form(int rmw, int n, const int* M, const int* N, int K, double 
     const SmallCost& c = kSmallCost[rmw][f];
     if (c.groups > 1 && nk < kMinStepsForGroups) continue;
     long long tiles = 0;
-    for (int j = 0; j < n; ++j) tiles += (long long)((M[j] + c.bm - 1) / c.bm) * ((N[j] + c.bn - 1) / c.bn);
+    double mb = 0.0;
+    for (int j = 0; j < n; ++j) {
+      tiles += (long long)((M[j] + c.bm - 1) / c.bm) * ((N[j] + c.bn - 1) / c.bn);
+      mb += 2e-6 * ((double)M[j] + N[j]) * K;
+    }
     if (tiles > (1 << 30)) continue;
+    if (tiles > (long long)(kManyRounds - 1) * ncu && nk >= kManySteps) continue;
     const double w = (double)((tiles + ncu - 1) / ncu), steps = (nk + c.groups - 1) / c.groups;
-    const double t = c.fixed + c.each * w + steps * (c.per_cu == 2 ? c.pair * (double)(int)(w / 2) + c.single * (w - 2 * (int)(w / 2)) : c.single * w);
+    const double t = c.fixed + c.each * w + c.per_mb * mb + steps * (c.per_cu == 2 ? c.pair * (double)(int)(w / 2) + c.single * (w - 2 * (int)(w / 2)) : c.single * w);
     if (t < t_large) {
       t_large = t;
       best = f;
@@ -1346,13 +1368,15 @@ int launch_gemm_tn_multi(int dtype, int n, const void* const* A, const void* con
     if (j < n) at += dp_blocks(a.g[j]);
   }
   a.start[kMaxMulti] = at;
-  double t_large = 0.0;
-  {
-    const LargeCost& cost = kLargeCost[1];
-    long long tiles = 0;
-    for (int j = 0; j < n; ++j) tiles += (long long)((M[j] + kBM - 1) / kBM) * ((N[j] + kBN - 1) / kBN);
-    t_large = (double)((tiles + compute_units() - 1) / compute_units()) * (cost.step * ((K + BK - 1) / BK) + cost.round);
+  long long tiles = 0, busiest = 0;
+  double outputs = 0.0;
+  for (int j = 0; j < n; ++j) {
+    const long long tm = (M[j] + kBM - 1) / kBM, tn = (N[j] + kBN - 1) / kBN;
+    tiles += tm * tn;
+    busiest += busiest_xcd(tm, tn);
+    outputs += (double)M[j] * N[j];
   }
+  const double t_large = large_time(kLargeCost[1], tiles, busiest, outputs / ((double)tiles * kBM * kBN), (K + BK - 1) / BK);
   const int form = small_form(1, n, M, N, K, t_large);
   bool lines = true;
   for (int j = 0; j < n; ++j) lines = lines && whole_lines(N[j]);

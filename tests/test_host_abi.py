@@ -208,6 +208,15 @@ def test_gemm_remainder_split_covers_every_tile_and_k_step_once():
     assert _plan(2048, 3200, 25600) == (0, [(64, 4), (40, 6)])
 
 
+def test_gemm_plan_of_few_tiles():
+    """One or two 256 x 256 tiles: splitting k costs a second launch that adds up to one slab per k-step, small tiles are two to
+    five times as fast.  With more tiles and a long k the split is the faster one (64 x 3160 x 14928: 40 against 63 us)."""
+    for M, N, K in ((160, 232, 216), (504, 72, 232), (88, 208, 1968), (184, 72, 2304), (176, 216, 1504), (56, 96, 7800), (16, 192, 6872)):
+        assert _plan(M, N, K) == (N, []), (M, N, K)
+    for M, N, K in ((64, 3160, 14928), (1368, 2272, 11792), (1016, 7384, 9232)):
+        assert _plan(M, N, K)[1], (M, N, K)
+
+
 def test_cfg_refuses_operands_beyond_the_gemm_offset_range():
     big = B.make_cfg(h=25600, a=160, t=1, s=2048, b=1, dtype=B.BF16)    # w_1 is 5.2 GB
     assert B.ptdp_cfg_validate(C.byref(big)) == B.E_UNSUPPORTED
