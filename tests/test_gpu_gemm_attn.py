@@ -112,7 +112,8 @@ def test_gemm_rows_of_c_beyond_31_bit_offsets(out_f32, accumulate, N):
 
 def test_gemm_accumulates_as_fast_into_rows_that_start_inside_a_line():
     """+= into rows of 9080 floats (36320 bytes, not a multiple of 128) against 9088: the part of a line that another access
-    takes next has to be found in the cache.  1.15 for noise; with non-temporal accesses it is 1.3 times as long."""
+    takes next has to be found in the cache.  Plain accesses take up to 1.15 times as long as the non-temporal ones of whole
+    lines, non-temporal ones here 1.45 times: the bound lies halfway."""
     M, K, best = 7016, 248, []
     for N in (9080, 9088):
         a, b, c = randn((K, M), B.BF16, 1), randn((K, N), B.BF16, 2), torch.zeros((M, N), device="cuda")
@@ -126,7 +127,7 @@ def test_gemm_accumulates_as_fast_into_rows_that_start_inside_a_line():
             sync()
             times.append(e[0].elapsed_time(e[1]))
         best.append(min(times))
-    assert best[0] <= 1.15 * best[1], best
+    assert best[0] <= 1.3 * best[1], best
 
 
 @pytest.mark.parametrize("mode", [B.GEMM_NN, B.GEMM_NT, B.GEMM_TN])
