@@ -730,7 +730,6 @@ attn_bwd_dq_mfma(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ ctx,
   const int ntiles = CAUSAL ? q_last_blk / kBKV + 1 : (s + kBKV - 1) / kBKV;
   const uint8_t* mrow = (!CAUSAL && mask) ? mask + ((size_t)j * s + min(my_q, s - 1)) * s : nullptr;
   const bool aligned = (s & 3) == 0;
-  const float fill = kMaskFill * sqrtf((float)DH);
   // the next K and V tiles travel in registers while this step's arithmetic runs
   TileMap<DH> map;
   map.init(rs);
@@ -861,10 +860,10 @@ template <int THREADS> struct MaskTile {
 // launch code takes NP = 2 when all workgroups of the one-pair form would be resident at once (the longest one then sets
 // the time: GPT-3-shaped shard, 12 heads: backward 0.213 -> 0.152 ms) and NP = 1 otherwise (1T-shaped shard, 20 heads of
 // 160: 0.331 against 0.343 ms).
-// For heads of 32, 64 and 160; 96 and 128 take the form below.
-template <int DH, bool CAUSAL> struct DkvBothLds {
+// For the calls that kDkvSplit, below, leaves.
+template <int DH, bool CAUSAL> struct DkvLds {
   static constexpr int kPair = 2 * TileGeom<DH>::BYTES + 2 * kBKV * (int)sizeof(float) + (CAUSAL ? 0 : kBQ * kMaskLdsStride);
-  static constexpr int kSum = 2 * (DH / 32) * 16 * 64 * (int)sizeof(float);   // one wave's dK and dV
+  static constexpr int kSum = 2 * (DH / 32) * 16 * 64 * (int)sizeof(float);   // dK and dV of one wave (both forms: of 32 keys)
   static constexpr int kBytes2 = 2 * kPair > 2 * kSum ? 2 * kPair : 2 * kSum;
 };
 template <int DH, bool CAUSAL, int NP>
@@ -875,7 +874,7 @@ attn_bwd_dkv_both_mfma(const bf16_t* __restrict__ qkv, const bf16_t* __restrict_
   constexpr int NKK = DH / 16, NDT = DH / 32;
   extern __shared__ __attribute__((aligned(16))) char smem_all[];
   const int pair = NP == 2 ? threadIdx.x >> 7 : 0, tid = threadIdx.x & (kAttnThreads - 1);
-  char* smem = smem_all + pair * DkvBothLds<DH, CAUSAL>::kPair;
+  char* smem = smem_all + pair * DkvLds<DH, CAUSAL>::kPair;
   char* q_lds = smem;                           // Q  [query][dh]: S = Q K^T directly, dK^T = Q^T dS through tr reads
   char* do_lds = smem + TileGeom<DH>::BYTES;    // dO [query][dh]: dP = dO V^T directly, dV^T = dO^T P through tr reads
   float* lse_lds = reinterpret_cast<float*>(smem + 2 * TileGeom<DH>::BYTES);  // lse * log2(e), +inf past the end
@@ -1049,17 +1048,15 @@ attn_bwd_dkv_both_mfma(const bf16_t* __restrict__ qkv, const bf16_t* __restrict_
 // The same, split by result: a group of four waves, of which two (32 keys each) compute S, dP and dK and two S and dV.  S
 // twice is a quarter more matrix work, but a wave then holds one result and fits 256 registers: two waves per SIMD cover
 // each other's waits where both results in one wave leave one (half of its time went to waiting for LDS and barriers).
-// Which waves take which result alternates with the workgroup, so that every SIMD gets both.  us, both results in a wave
-// and split: dh 128, 4 samples x 16 heads x 2048 371 -> 319, 12 heads x 2048 90 -> 87, 8 heads x 1024 38 -> 35; dh 96 with
-// dQ, 4 x 16 x 2048 459 -> 447, 12 heads x 2048 115 -> 118, 8 heads x 1024 54 -> 52; but dh 64, 4 x 16 x 512 with mask 34.7
-// -> 36.0 and dh 32, 128 heads x 2048 191 -> 259, where several waves fit a SIMD as it is.  NP = 2: two groups of four
-// waves, as above.
+// Which waves take which result alternates with the workgroup, so that every SIMD gets both.  NP = 2: two groups of four
+// waves, as above.  Taken where it measured faster; us for the backward with both results in a wave and split:
+//   dh 128 causal   4 samples x 16 heads x 2048 545, 502; 20 heads x 2048 233, 207; 12 x 2048 143, 142; 8 x 1024 64.6, 62.9
+//   dh 128 no mask  983, 1033; 484, 462; 295, 299; 73.8, 76.4 (general mask alike): the form's 256 registers spill there
+//   dh 96 causal    433, 407; 188, 169; 113.6, 113.8; 51.9, 50.7; no mask 834, 831; 402, 372; 249, 243; 63.0, 63.2
+// Heads of 64 with a mask (4 x 16 x 512: 34.7, 36.0 for this kernel alone) and of 32 (128 heads x 2048: 191, 259) are faster with
+// both results in a wave.
+template <int DH, bool CAUSAL> constexpr bool kDkvSplit = DH == 96 || (DH == 128 && CAUSAL);
 constexpr int kDkvThreads = 2 * kAttnThreads;
-template <int DH, bool CAUSAL> struct DkvLds {
-  static constexpr int kPair = 2 * TileGeom<DH>::BYTES + 2 * kBKV * (int)sizeof(float) + (CAUSAL ? 0 : kBQ * kMaskLdsStride);
-  static constexpr int kSum = (DH / 32) * 16 * 64 * (int)sizeof(float);   // one wave's dK or dV
-  static constexpr int kBytes2 = 2 * kPair > 4 * kSum ? 2 * kPair : 4 * kSum;
-};
 template <int DH, bool CAUSAL, int NP>
 __global__ void __launch_bounds__(NP * kDkvThreads, 2)
 attn_bwd_dkv_mfma(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ dctx, const float* __restrict__ lse,
@@ -1318,8 +1315,8 @@ static int attn_bwd_mfma_np(const bf16_t* qkv, const bf16_t* ctx, const bf16_t* 
   // dQ first: it writes delta
   hipLaunchKernelGGL((attn_bwd_dq_mfma<DH, CAUSAL, NP>), grid, dim3(NP * kAttnThreads), smem_dq, stream, qkv, ctx, dctx, lse, delta,
                      dqkv, s, b, heads, mask);
-  if constexpr (DH < 96 || DH > 128) {
-    constexpr int smem_dkv = NP == 2 ? DkvBothLds<DH, CAUSAL>::kBytes2 : DkvBothLds<DH, CAUSAL>::kPair;
+  if constexpr (!kDkvSplit<DH, CAUSAL>) {
+    constexpr int smem_dkv = NP == 2 ? DkvLds<DH, CAUSAL>::kBytes2 : DkvLds<DH, CAUSAL>::kPair;
     if (set_dynamic_smem(reinterpret_cast<const void*>(attn_bwd_dkv_both_mfma<DH, CAUSAL, NP>), smem_dkv, done_dkv) != PTDP_OK)
       return PTDP_E_HIP;
     hipLaunchKernelGGL((attn_bwd_dkv_both_mfma<DH, CAUSAL, NP>), grid, dim3(NP * kAttnThreads), smem_dkv, stream, qkv, dctx, lse,

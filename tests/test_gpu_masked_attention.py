@@ -35,6 +35,12 @@ CASES = [  # dtype, s, b, heads, dh, masked?, empty rows
     # more than 512 (query block, sample, head) triples: one-pair form of the backward kernels
     (B.BF16, 130, 6, 30, 64, True, [(2, 129)]),
     (B.BF16, 140, 4, 44, 160, True, []),
+    (B.BF16, 130, 6, 30, 96, True, [(3, 64)]),
+    (B.BF16, 200, 5, 27, 128, True, [(4, 199)]),
+    (B.BF16, 257, 3, 36, 128, False, []),
+    # heads of 96 and 128 in both forms of the dK/dV kernel, two pairs
+    (B.BF16, 257, 1, 2, 96, True, [(0, 256)]),
+    (B.BF16, 300, 2, 3, 128, False, []),
 ]
 
 
