@@ -417,6 +417,12 @@ size_t ptdp_gemm_workspace_bytes(void);
 int ptdp_gemm_plan(int M, int N, int K, int out_f32, int accumulate, int has_bias, size_t workspace_bytes,
                    int* dp_columns, int* n_groups, int* group_tiles, int* group_parts);
 
+/* Host only: the tiles of the bf16 call ptdp_gemm(mode, ...) with these arguments.  A workgroup computes *tile_m x *tile_n
+ * outputs; with *wave_groups = 2 two groups of its waves take alternate 64-wide k-steps and their sums are added at the
+ * end.  256, 256, 1 for the calls that ptdp_gemm_plan describes.  Returns 0, PTDP_E_INVALID_ARG or PTDP_E_NULL_PTR. */
+int ptdp_gemm_form(int mode, int M, int N, int K, int out_f32, int accumulate, int has_bias, size_t workspace_bytes,
+                   int* tile_m, int* tile_n, int* wave_groups);
+
 /* Fused causal attention over qkv [s, b, 3hp] (scale 1/sqrt(dh), implicit
  * causal mask, softmax, times V; section 4.2's scale+mask+softmax fusion
  * extended over both batched GEMMs): ctx [s, b, hp], lse [b, heads, s] fp32. */

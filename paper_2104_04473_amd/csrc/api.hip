@@ -846,6 +846,14 @@ int ptdp_gemm_plan(int M, int N, int K, int out_f32, int accumulate, int has_bia
   return PTDP_OK;
 }
 
+int ptdp_gemm_form(int mode, int M, int N, int K, int out_f32, int accumulate, int has_bias, size_t workspace_bytes, int* tile_m,
+                   int* tile_n, int* wave_groups) {
+  if (!tile_m || !tile_n || !wave_groups) return PTDP_E_NULL_PTR;
+  if (mode < PTDP_GEMM_NN || mode > PTDP_GEMM_TN || M <= 0 || N <= 0 || K <= 0 || M % 8 || N % 8 || K % 8) return PTDP_E_INVALID_ARG;
+  gemm_form_query(mode, M, N, K, out_f32, accumulate, has_bias, workspace_bytes, tile_m, tile_n, wave_groups);
+  return PTDP_OK;
+}
+
 int ptdp_dropout_mask(uint8_t* keep, int64_t n, float p, uint64_t seed, uint32_t layer, uint32_t site,
                       uint64_t microbatch, void* stream) {
   if (n < 0 || !(p >= 0.f && p < 1.f) || site > 1) return PTDP_E_INVALID_ARG;

@@ -184,6 +184,9 @@ size_t gemm_workspace_bytes();
 // tiles, group j giving each of its tiles[j] tiles to parts[j] workgroups that split the k range evenly
 void gemm_plan_query(int M, int N, int K, int out_f32, int accumulate, int has_bias, size_t ws_bytes, int* dp_cols,
                      int* n_groups, int* tiles, int* parts);
+// the tile of a bf16 call's workgroups and how many wave groups share its k range (host only)
+void gemm_form_query(int mode, int M, int N, int K, int out_f32, int accumulate, int has_bias, size_t ws_bytes, int* tile_m,
+                     int* tile_n, int* groups);
 int launch_gemm(int dtype, int mode, const void* A, const void* B, void* C, const void* bias, int M, int N,
                 int K, int out_f32, int accumulate, void* ws, size_t ws_bytes, hipStream_t st);
 // up to four fp32-accumulating weight gradients C_j += A_j^T B_j with the same K (bf16: one launch)

@@ -1223,6 +1223,16 @@ void gemm_plan_query(int M, int N, int K, int out_f32, int accumulate, int has_b
   }
 }
 
+void gemm_form_query(int mode, int M, int N, int K, int out_f32, int accumulate, int has_bias, size_t ws_bytes, int* tile_m,
+                     int* tile_n, int* groups) {
+  SplitPlan P;
+  const int f = choose_form(mode, M, N, K, out_f32, accumulate, has_bias, ws_bytes, &P);
+  const SmallCost& c = kSmallCost[0][f >= 0 ? f : 0];
+  *tile_m = f >= 0 ? c.bm : kBM;
+  *tile_n = f >= 0 ? c.bn : kBN;
+  *groups = f >= 0 ? c.groups : 1;
+}
+
 template <bool TA, bool TB>
 static int launch_bf16_mode(const void* A, const void* B, void* C, const void* bias, int M, int N, int K, int out_f32,
                             int accumulate, void* ws, size_t ws_bytes, hipStream_t st) {

@@ -1,4 +1,6 @@
 """GPU parity of the GEMM and attention kernels against their plain definitions (oracle side)."""
+import ctypes as C
+
 import numpy as np
 import pytest
 import torch
@@ -8,6 +10,22 @@ from paper_2104_04473_amd import binding as B
 from gpu_util import assert_close, np64, randn, stream, sync, tdt
 
 pytestmark = pytest.mark.gpu
+
+
+def form(mode, M, N, K, out_f32, accumulate, has_bias=0, ws_bytes=0):
+    """(tile_m, tile_n, wave groups) of the call."""
+    v = [C.c_int() for _ in range(3)]
+    B.check(B.ptdp_gemm_form(mode, M, N, K, out_f32, accumulate, has_bias, ws_bytes, *[C.byref(x) for x in v]), "form")
+    return tuple(x.value for x in v)
+
+
+def split_groups(M, N, K, out_f32, accumulate, has_bias):
+    cols, n = C.c_int(), C.c_int()
+    tiles, parts = (C.c_int * 2)(), (C.c_int * 2)()
+    B.check(B.ptdp_gemm_plan(M, N, K, out_f32, accumulate, has_bias, B.ptdp_gemm_workspace_bytes(), C.byref(cols), C.byref(n), tiles,
+                             parts), "plan")
+    return n.value
+
 
 SHAPES = [(8, 8, 8), (136, 264, 72), (256, 256, 64), (520, 776, 200), (1032, 264, 1096), (264, 1032, 520),
           (264, 136, 128), (72, 520, 136), (136, 72, 192)]     # 1, 2, 3 and more k-steps, whole and ragged
@@ -59,17 +77,20 @@ def test_gemm_every_short_pipeline(mode, nk, tail):
     assert_close(np64(c), want, B.BF16, "C", 0.2)
 
 
-# each of the five small-tile forms at ragged edges, with k-tile counts that are odd, even and end in a partial tile
-SMALL_FORMS = [(664, 520, 2048 + 8), (72, 1096, 1024), (200, 136, 640),         # 64 x 64, two wave groups
-               (1032, 2056, 4096), (2056, 1000, 2048 + 56),                     # 128 x 64, two wave groups
-               (2040, 1544, 4168), (1544, 2056, 4096),                          # 128 x 128, two wave groups
-               (136, 264, 72), (1000, 2056, 512), (2056, 3064, 448 + 8),        # 128 x 64
-               (2056, 4088, 1024 + 8), (1000, 5128, 2560), (2040, 4104, 192)]   # 128 x 128
+# each of the five small-tile forms at ragged edges, with step counts that are odd, even and end in a partial k-tile
+SMALL_FORMS = {(64, 64, 2): [(664, 520, 2048 + 8), (72, 1096, 1024), (200, 136, 640)],
+               (128, 64, 2): [(1000, 2040, 4168), (520, 3080, 2056), (1000, 1992, 1096), (1000, 2040, 4096)],
+               (128, 128, 2): [(1032, 2056, 4096), (2056, 1000, 2048 + 56), (2040, 1544, 4168), (1544, 2056, 4096)],
+               (128, 64, 1): [(136, 264, 72), (2040, 4104, 192)],
+               (128, 128, 1): [(2056, 3064, 448 + 8), (1000, 5128, 2560)],
+               None: [(1000, 2056, 512), (2056, 4088, 1024 + 8)]}      # a form of its own in each mode
 
 
 @pytest.mark.parametrize("mode", [B.GEMM_NN, B.GEMM_NT, B.GEMM_TN])
-@pytest.mark.parametrize("M,N,K", SMALL_FORMS)
-def test_gemm_small_tiles(mode, M, N, K):
+@pytest.mark.parametrize("tile,M,N,K", [(tile, *shape) for tile, shapes in SMALL_FORMS.items() for shape in shapes])
+def test_gemm_small_tiles(mode, tile, M, N, K):
+    tn = int(mode == B.GEMM_TN)
+    assert tile is None or form(mode, M, N, K, tn, tn, 1 - tn) == tile
     a = randn((M, K), B.BF16, 1)
     b = randn((K, N), B.BF16, 2)
     bias = randn((N,), B.BF16, 3)
@@ -131,13 +152,17 @@ def test_gemm_accumulates_as_fast_into_rows_that_start_inside_a_line():
 
 
 @pytest.mark.parametrize("mode", [B.GEMM_NN, B.GEMM_NT, B.GEMM_TN])
-@pytest.mark.parametrize("K,Kpad", [(192, 256), (200, 256), (4096, 4104), (520, 576)])
+@pytest.mark.parametrize("K,Kpad", [(64, 128), (120, 184), (192, 256), (200, 256), (4096, 4104), (520, 576)])
 def test_gemm_zero_padding_along_k_changes_no_bit(mode, K, Kpad):
-    """The same product with the reduction index padded by zeros.  K = 192 -> 256 moves a k-contiguous operand from
-    rows shorter than 256 elements (every operand request in the general form, with per-lane checks) to rows of 256
-    (whole k-tiles requested in the lean form); 4096 -> 4104 and 520 -> 576 add or remove a partial last k-tile.
-    Every output element adds the same products in the same order plus exact zeros: the results agree bit for bit."""
+    """The same product with the reduction index padded by zeros.  K = 64 -> 128 and 120 -> 184 move a k-contiguous operand
+    from rows shorter than 128 elements (every request of the small tiles in the general form, with per-lane checks) to rows of
+    128 and more (whole k-tiles requested in the lean form); the others add a k-tile or add or remove a partial last one.
+    Every output element adds the same products in the same order plus exact zeros: the results agree bit for bit.  C in bf16
+    takes small tiles (TN: 256 x 256), += the other way round."""
     M, N = 520, 264
+    for out_f32 in (0, 1):
+        assert form(mode, M, N, K, out_f32, out_f32) == form(mode, M, N, Kpad, out_f32, out_f32)
+        assert (form(mode, M, N, K, out_f32, out_f32) == (256, 256, 1)) == (out_f32 == (mode != B.GEMM_TN))
     a = randn((M, K), B.BF16, 1)
     b = randn((K, N), B.BF16, 2)
     ap = torch.zeros((M, Kpad), dtype=torch.bfloat16, device="cuda"); ap[:, :K] = a
@@ -158,16 +183,51 @@ def test_gemm_zero_padding_along_k_changes_no_bit(mode, K, Kpad):
 
 
 @pytest.mark.parametrize("mode", [B.GEMM_NN, B.GEMM_NT, B.GEMM_TN])
-@pytest.mark.parametrize("M,N,K", [(520, 776, 4168), (264, 4104, 4096), (2048, 1288, 4160), (2048, 10248, 4096),
-                                   (14336, 1792, 4096)])   # 56 row tiles: do not divide the compute-unit count
-def test_gemm_split_along_k(mode, M, N, K):
+@pytest.mark.parametrize("K", [512 + 8, 320])
+def test_gemm_zero_padding_of_short_rows_changes_no_bit(mode, K):
+    """A k-slow operand (B in NN, both in TN) with rows of 120 elements, all of whose requests take the general form, against the
+    same one padded to 128, whose whole k-tiles take the lean form, in the 256 x 256 kernels (+=; TN: bf16) and in small tiles."""
+    for (M, N, Mp, Np) in ((520, 120, 520, 128), (120, 520, 128, 520)):
+        a, b = randn((M, K), B.BF16, 1), randn((K, N), B.BF16, 2)
+        ap = torch.zeros((Mp, K), dtype=torch.bfloat16, device="cuda"); ap[:M] = a
+        bp = torch.zeros((K, Np), dtype=torch.bfloat16, device="cuda"); bp[:, :N] = b
+        for out_f32 in (0, 1):
+            assert form(mode, M, N, K, out_f32, out_f32) == form(mode, Mp, Np, K, out_f32, out_f32)
+            assert (form(mode, M, N, K, out_f32, out_f32) == (256, 256, 1)) == (out_f32 == (mode != B.GEMM_TN))
+            outs = []
+            for (x, y, m, n) in ((a, b, M, N), (ap, bp, Mp, Np)):
+                A = x.t().contiguous() if mode == B.GEMM_TN else x
+                Bm = y.t().contiguous() if mode == B.GEMM_NT else y
+                c = torch.full((m, n), 0.25, dtype=torch.float32 if out_f32 else torch.bfloat16, device="cuda")
+                B.check(B.ptdp_gemm(B.BF16, mode, A.data_ptr(), Bm.data_ptr(), c.data_ptr(), None, m, n, K, out_f32, out_f32, None, 0,
+                                    stream()), "gemm")
+                sync()
+                outs.append(c[:M, :N])
+            assert torch.equal(*outs)
+            assert_close(np64(outs[0]) - (0.25 if out_f32 else 0.0), np64(a) @ np64(b), B.BF16, "C")
+
+
+# (M, N, K, split): split calls with one and two groups, row tiles that do not divide the number of compute units (3, 9), ragged
+# edges, whole rounds in front; and calls that are given a workspace and do not need it
+SPLIT_SHAPES = [(2128, 64, 10976, True), (136, 10928, 7400, True), (536, 3592, 10064, True), (1848, 8720, 4176, True),
+                (520, 776, 4168, False), (264, 4104, 4096, False), (2048, 1288, 4160, False), (2048, 10248, 4096, False),
+                (14336, 1792, 4096, False)]
+
+
+@pytest.mark.parametrize("mode", [B.GEMM_NN, B.GEMM_NT, B.GEMM_TN])
+@pytest.mark.parametrize("M,N,K,split", SPLIT_SHAPES)
+def test_gemm_split_along_k(mode, M, N, K, split):
     """Tile counts that do not fill the compute units: the remaining tiles are split along k through the
     workspace and reduced in a fixed order (bf16 output, or += into the fp32 accumulator)."""
+    if split:   # bf16 output with a bias, and +=, in every mode (the plan of += is that of TN)
+        for out_f32 in (0, 1):
+            assert split_groups(M, N, K, out_f32, out_f32, 1 - out_f32) > 0
+            assert form(mode, M, N, K, out_f32, out_f32, 1 - out_f32, B.ptdp_gemm_workspace_bytes()) == (256, 256, 1)
     dtype = B.BF16
     a = randn((M, K), dtype, 1)
     b = randn((K, N), dtype, 2)
     bias = randn((N,), dtype, 3)
-    want = np64(a) @ np64(b)
+    want = (a.double() @ b.double()).cpu().numpy()
     A = a.t().contiguous() if mode == B.GEMM_TN else a
     Bm = b.t().contiguous() if mode == B.GEMM_NT else b
     ws = torch.full((B.ptdp_gemm_workspace_bytes() // 4,), 7.0, dtype=torch.float32, device="cuda")   # garbage on entry

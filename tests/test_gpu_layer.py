@@ -66,6 +66,21 @@ def test_layer_variants(kw):
     check_layer(B.make_cfg(**kw))
 
 
+# LayerNorm backward with the attention half's dropout in the same pass: 1, 2 and 4 waves per row with one and two vectors a lane, rows
+# that do not fill the last block's groups
+@pytest.mark.parametrize("kw", [
+    dict(h=512, a=8, t=1, s=301, b=7, dtype=B.BF16, p_hidden=0.1, seed=6),           # one wave, one vector
+    dict(h=1024, a=8, t=4, s=301, b=7, dtype=B.BF16, p_hidden=0.1, seed=7),          # one wave, two
+    dict(h=256, a=4, t=1, s=301, b=7, dtype=B.F32, p_hidden=0.1, seed=8),
+    dict(h=512, a=8, t=4, s=301, b=7, dtype=B.F32, p_hidden=0.1, seed=9),
+    dict(h=512, a=8, t=1, s=259, b=4, dtype=B.BF16, p_hidden=0.1, seed=10),          # two waves, one vector
+    dict(h=2048, a=16, t=8, s=259, b=4, dtype=B.BF16, p_hidden=0.1, seed=11),        # two waves, two vectors
+    dict(h=2304, a=24, t=8, s=259, b=4, dtype=B.BF16, p_hidden=0.1, seed=12),        # four waves
+])
+def test_layer_rows_shared_by_few_waves(kw):
+    check_layer(B.make_cfg(**kw))
+
+
 def test_chunk_of_layers_and_gradient_accumulation():
     cfg = B.make_cfg(h=256, a=4, t=1, s=40, b=2, dtype=B.F32, p_hidden=0.1, seed=9)
     check_layer(cfg, n_layers=3, first_layer=4, microbatches=(0, 3))

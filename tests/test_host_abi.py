@@ -217,6 +217,20 @@ def test_gemm_plan_of_few_tiles():
         assert _plan(M, N, K)[1], (M, N, K)
 
 
+def test_gemm_form_errors_and_agreement_with_the_plan():
+    v = [C.c_int(-1) for _ in range(3)]
+    ref = [C.byref(x) for x in v]
+    assert B.ptdp_gemm_form(3, 8, 8, 8, 0, 0, 0, 0, *ref) == B.E_INVALID_ARG
+    assert B.ptdp_gemm_form(B.GEMM_NN, 8, 8, 12, 0, 0, 0, 0, *ref) == B.E_INVALID_ARG
+    assert B.ptdp_gemm_form(B.GEMM_NN, 8, 8, 8, 0, 0, 0, 0, ref[0], ref[1], None) == B.E_NULL_PTR
+    assert [x.value for x in v] == [-1, -1, -1]
+    ws = B.ptdp_gemm_workspace_bytes()
+    for M, N, K in ((160, 232, 216), (64, 3160, 14928), (2048, 12800, 25600), (8192, 8192, 8192), (1024, 2048, 1024)):
+        assert B.ptdp_gemm_form(B.GEMM_NN, M, N, K, 0, 0, 0, ws, *ref) == B.OK
+        whole = [x.value for x in v] == [256, 256, 1]
+        assert whole or _plan(M, N, K) == (N, []), (M, N, K)      # only 256 x 256 tiles are ever split
+
+
 def test_cfg_refuses_operands_beyond_the_gemm_offset_range():
     big = B.make_cfg(h=25600, a=160, t=1, s=2048, b=1, dtype=B.BF16)    # w_1 is 5.2 GB
     assert B.ptdp_cfg_validate(C.byref(big)) == B.E_UNSUPPORTED
