@@ -321,8 +321,10 @@ layernorm_bwd_kernel(const T* du, const T* __restrict__ x, const T* __restrict__
 }
 
 // The same for rows whose next row does not fit the registers beside the current one (more than four vectors per lane of
-// eight waves): one row at a time, requested when its turn comes.  Bound by memory (25600 columns: 12 bytes per element
-// of three reads and a write at 3.3 TB/s); the form above spills there and takes 180 instead of 127 us.
+// eight waves): one row at a time, requested when its turn comes.  Bound by memory latency: a workgroup of eight waves fills
+// the compute unit's registers, so nothing is in flight during a row's reduction (2048 x 25600 bf16: 8 bytes per element of
+// three reads and a write, 420 MB in 123 us = 3.4 TB/s).  In bf16 the widest two forms spill (7 vectors per lane: 5
+// registers, 8: 59); the form above would spill far more at these widths and takes 180 instead of 127 us.
 template <typename T, int VPT>
 __global__ void __launch_bounds__(512)
 layernorm_bwd_wide_kernel(const T* du, const T* __restrict__ x, const T* __restrict__ gain, const float* __restrict__ mu,

@@ -79,7 +79,7 @@ def main():
         scratch = torch.empty(max(B.ptdp_layernorm_bwd_scratch_bytes(T, h), B.ptdp_colsum_scratch_bytes(T, max(h, fp))), dtype=torch.uint8, device=dev)
         B.ptdp_layernorm_fwd(B.BF16, xs[0].data_ptr(), g.data_ptr(), be.data_ptr(), us[0].data_ptr(), mu.data_ptr(),
                              rstd.data_ptr(), None, T, h, 1e-5, sh)
-        report("layernorm_bwd (dx + parameter gradients, with residual)", T * h * 12, "GB/s",
+        report("layernorm_bwd (dx + parameter gradients, with residual)", T * h * 8, "GB/s",
                [lambda i=i: B.ptdp_layernorm_bwd(B.BF16, us[i].data_ptr(), xs[i].data_ptr(), g.data_ptr(), mu.data_ptr(),
                                                  rstd.data_ptr(), xs[(i + 1) % n].data_ptr(), us[i].data_ptr(), dg.data_ptr(),
                                                  db.data_ptr(), scratch.data_ptr(), T, h, sh) for i in range(n)])
