@@ -1092,11 +1092,17 @@ static double large_time(const LargeCost& c, long long tiles, long long busiest,
 }
 static long long busiest_xcd(long long tiles_m, long long tiles_n) { return tiles_m * ((tiles_n + 7) / 8); }
 
+// A call that is all remainder is split where that promises to be so much faster: the fit is too low for remainders of half a
+// round and more (2048 x 6144 x 12288 whole 241 us, split 256; 2048 x 6400 x 25600 497, 508).  Of the factors 1 to 1.15 the one that
+// loses least over the measured calls (438 us in 839, 464 without).  Behind whole rounds the split pays as
+// computed (2048 x 12288 x 4608, 384 tiles: 191 us whole, 186 split; 2048 x 25600 x 3200 284, 271).
+constexpr double kSplitMargin = 1.06;
+
 // How a call is cut: whole rounds of tiles (whole columns of tiles, so that the remainder is fewer tiles than
 // compute units), then the remainder in at most two groups (see gemm_bf16_split_kernel).  A first group of
 // 2^a tiles is taken while one group over all remaining tiles would leave more than a tenth of the
 // compute units idle; the second group takes what is left.  The split is used when its cost is below that of
-// whole tiles.  *time: the plan's cost.
+// whole tiles (less kSplitMargin).  *time: the plan's cost.
 static SplitPlan large_plan(int M, int N, int K, int out_f32, int accumulate, int has_bias, size_t ws_bytes, double* time) {
   const int ncu = compute_units();
   const int tiles_m = (M + kBM - 1) / kBM, tiles_n = (N + kBN - 1) / kBN, nk = (K + BK - 1) / BK;
@@ -1138,7 +1144,7 @@ static SplitPlan large_plan(int M, int N, int K, int out_f32, int accumulate, in
   t_split += cost.split_slab * slabs + (cost.split_part * most > cost.split_reduce * slabs ? cost.split_part * most : cost.split_reduce * slabs);
   // (whole columns: the full rounds may come out as one more, partly filled round)
   if (dp_cols > 0) t_split += large_time(cost, (long long)dp_cols * tiles_m, busiest_xcd(tiles_m, dp_cols), 1.0, nk);
-  if (most == 0 || t_split >= *time) return P;
+  if (most == 0 || t_split * (dp_cols > 0 ? 1.0 : kSplitMargin) >= *time) return P;
   *time = t_split;
   P.dp_cols = dp_cols;
   P.n_groups = n;

@@ -217,6 +217,13 @@ def test_gemm_plan_of_few_tiles():
         assert _plan(M, N, K)[1], (M, N, K)
 
 
+def test_gemm_plan_of_most_of_a_round():
+    """Three quarters of a round of long products: whole tiles are 2 to 6 % faster than two groups of parts; half a round is split."""
+    for M, N, K in ((2048, 6144, 12288), (2048, 6400, 25600)):
+        assert _plan(M, N, K) == (N, []), (M, N, K)
+    assert _plan(2048, 4096, 8192) == (0, [(128, 2)])
+
+
 def test_gemm_form_errors_and_agreement_with_the_plan():
     v = [C.c_int(-1) for _ in range(3)]
     ref = [C.byref(x) for x in v]
