@@ -8,7 +8,7 @@
 //
 // bf16 forward: S^T = K Q^T and O^T = V^T P^T on v_mfma_f32_32x32x16_bf16, so that the softmax
 // probabilities leave the first MFMA already in the register layout the second one wants as its
-// B operand.  One wave owns 32 queries; a block of 2 waves shares 64-key K and V tiles in LDS.
+// B operand.  One wave owns 32 queries; the waves of a block share K and V tiles in LDS.
 // fp32: the same two-step form on v_mfma_f32_16x16x4_f32, operands straight from memory.
 #include "common.h"
 
@@ -484,181 +484,357 @@ inline int attn_grid(int nblk, int heads, int b) {
   return 8 * (whole * nblk + (rest * nblk + 7) / 8);
 }
 
-// Forward: S^T = K Q^T and O^T = V^T P^T, so that the probabilities leave the first MFMA in the register
-// layout the second one takes as its B operand.  One tile's worth of registers carries V of the
-// current step (requested before the score MFMAs, stored to LDS after the softmax) and then K of the
-// next step (requested before the P V MFMAs), so both loads overlap arithmetic.  The loop is bound by
-// vector ALU work, not by MFMA: the output is rescaled only when some row's running maximum moved,
-// the mask is applied only on tiles that touch the diagonal, and exponentials and bf16 conversions
-// are single instructions.
-// NP = 2: the workgroup is two pairs of waves; pair p walks every second key tile with tiles of its own in LDS, and
-// at the end pair 0 merges pair 1's running maximum, sum and output into its own (the usual rescaling of two
-// partial softmax results).  For launches with so few workgroups that the longest one sets the time.
-template <int DH, bool CAUSAL, int NP>
-__global__ void __launch_bounds__(NP * kAttnThreads, DH > 128 ? 1 : 2)
-attn_fwd_mfma(const bf16_t* __restrict__ qkv, bf16_t* __restrict__ ctx, float* __restrict__ lse, int s, int b,
-              int heads, const uint8_t* __restrict__ mask) {
-  constexpr int NKK = DH / 16, NDT = DH / 32;
-  extern __shared__ __attribute__((aligned(16))) char smem_all[];
-  const int pair = NP == 2 ? threadIdx.x >> 7 : 0;
-  char* smem = smem_all + pair * 2 * TileGeom<DH>::BYTES;
-  char* k_lds = smem;
-  char* v_lds = smem + TileGeom<DH>::BYTES;
+// The same for the causal kernels on tiles from LDS, whose blocks differ in length: an XCD takes block `blk` of all its pairs
+// before block blk + 1 of any, so that the longest walks start first whatever pair they belong to (pair by pair, the last
+// pair's longest block starts when most others are done).  Eight block levels at a time; the last heads * b mod 8 pairs
+// are dealt block by block.  Fewer than eight blocks: as above.
+__device__ __forceinline__ bool attn_map_levels(int id, int nblk, int heads, int b, int* blk, int* e, int* j) {
+  if (nblk < 8) return attn_map(id, nblk, heads, b, blk, e, j);
+  const int xcd = id & 7, local = id >> 3;
+  const int pairs = heads * b, whole = pairs >> 3, rest = pairs & 7;
+  const int chunk = local / pairs, r = local % pairs;
+  int pair;
+  if (r < rest) {
+    const int g = (chunk * rest + r) * 8 + xcd;   // index into the remaining pairs' blocks, block-major
+    if (g >= rest * nblk) return false;
+    pair = 8 * whole + g % rest;
+    *blk = g / rest;
+  } else {
+    *blk = 8 * chunk + (r - rest) / whole;
+    if (*blk >= nblk) return false;
+    pair = xcd + 8 * ((r - rest) % whole);
+  }
+  *e = pair % heads;
+  *j = pair / heads;
+  return true;
+}
+inline int attn_grid_levels(int nblk, int heads, int b) {
+  return nblk < 8 ? attn_grid(nblk, heads, b) : 8 * heads * b * ((nblk + 7) / 8);
+}
 
-  const int nqb = (s + kBQ - 1) / kBQ;
+// ------------------------------------------------------------------------------------------------
+// Tiles of 64 rows that travel from memory straight to LDS (buffer_load ... lds), one tile ahead of the arithmetic.
+// LDS image: blocks of 32 dh, [block][64 rows][64 bytes]; the 16-byte chunk c of row r sits in slot c ^ ((r >> 2) & 3),
+// so that 16 rows of a fragment read and the 8 rows of a transposing read fall into different bank groups.
+// ------------------------------------------------------------------------------------------------
+typedef uint32_t attn_rsrc_t __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ uint32_t attn_lds_offset(const char* p) {
+  return (uint32_t)reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) void*)p);
+}
+// lane i's 16 bytes land at lds + 16 i.  Assembly, because the compiler makes every LDS read wait for all such loads in
+// flight; s_nop 4: the descriptor may have been written by the vector ALU just before, which the compiler cannot see here.
+__device__ __forceinline__ void attn_load_lds(attn_rsrc_t r, uint32_t lds, uint32_t voff) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" :: "s"(lds), "v"(voff), "s"(r) : "memory", "m0");
+}
+// A group of W waves loads a tile of KT rows; wave w takes the 16-row slices w, w + W, .. of every block.
+template <int DH, int W, int KT> struct TileDma {
+  static_assert(KT / 16 % W == 0, "every wave takes the same slices of every block");
+  static constexpr int NDT = DH / 32, kBytes = KT * DH * 2;
+  uint32_t off;   // the lane's chunk inside a slice's first block
+  size_t rs;
+  __device__ __forceinline__ void init(size_t row_elements, int lane) {
+    rs = row_elements;
+    off = (uint32_t)((lane >> 2) * row_elements * 2) + (((lane & 3) ^ (lane >> 4)) * 16);
+  }
+  // rows row0 .. row0 + KT - 1 of a head whose row 0 starts at p; rows from s on are zeros
+  __device__ __forceinline__ void issue(const bf16_t* __restrict__ p, int row0, int s, uint32_t lds, int w) const {
+#pragma unroll
+    for (int g = 0; g < KT / 16 / W; ++g) {
+      const int slice = w + W * g, first = row0 + 16 * slice, rows = min(s - first, 16);
+      const uint64_t a = reinterpret_cast<uint64_t>(p + (size_t)first * rs);
+      const attn_rsrc_t r = {(uint32_t)a, (uint32_t)(a >> 32) & 0xffffu, rows > 0 ? (uint32_t)((rows - 1) * rs * 2 + DH * 2) : 0u, 0x00020000u};
+#pragma unroll
+      for (int d = 0; d < NDT; ++d) attn_load_lds(r, lds + d * (KT * 64) + slice * 1024, off + d * 64);
+    }
+  }
+};
+typedef __attribute__((address_space(3))) const bf16x8_t lds_frag_t;
+typedef __attribute__((address_space(3))) s16x4_t lds_tr_t;
+// fragment with the tile row as the MFMA row: row sub * 32 + (lane & 31), eight dh of k16 step kk
+template <int KT> struct FragDirect {
+  uint32_t base[2];
+  __device__ __forceinline__ void init(uint32_t tile, int l31, int half) {
+#pragma unroll
+    for (int p = 0; p < 2; ++p) base[p] = tile + l31 * 64 + (((2 * p + half) ^ ((l31 >> 2) & 3)) * 16);
+  }
+  // moved by a stage: the sum is kept in the base registers, so that everything else is in the instructions' offset fields
+  __device__ __forceinline__ FragDirect at(uint32_t stage) const {
+    FragDirect f{{base[0] + stage, base[1] + stage}};
+    asm volatile("" : "+v"(f.base[0]), "+v"(f.base[1]));
+    return f;
+  }
+  __device__ __forceinline__ bf16x8_t get(int sub, int kk) const {
+    return *(lds_frag_t*)(uintptr_t)(base[kk & 1] + (kk >> 1) * (KT * 64) + sub * 2048);
+  }
+};
+// fragment with dh as the MFMA row (d * 32 + (lane & 31)) and tile rows as the contraction index, in the order of the 32x32
+// accumulator rows that feed the other operand: rows 16 * ks + 4 * half + 0..3 and 16 * ks + 8 + 4 * half + 0..3 of
+// 32-row half `sub`.  ds_read_b64_tr_b16: within 16 lanes, lane i receives element (i & 3) of the 8-byte rows addressed by
+// lanes (i >> 2) + {0, 4, 8, 12}.
+template <int KT> struct FragTr {
+  uint32_t lo, hi;
+  __device__ __forceinline__ void init(uint32_t tile, int lane) {
+    const int r = lane & 15, G = lane >> 4, row = 4 * (G >> 1) + (r >> 2), c = (2 * (G & 1) + ((r & 3) >> 1)) ^ (G >> 1);
+    lo = tile + row * 64 + c * 16 + (r & 1) * 8;
+    hi = tile + (row + 8) * 64 + (c ^ 2) * 16 + (r & 1) * 8;
+  }
+  __device__ __forceinline__ FragTr at(uint32_t stage) const {
+    FragTr f{lo + stage, hi + stage};
+    asm volatile("" : "+v"(f.lo), "+v"(f.hi));
+    return f;
+  }
+  __device__ __forceinline__ bf16x8_t get(int d, int sub, int ks) const {
+    const uint32_t o = d * (KT * 64) + sub * 2048 + ks * 1024;
+    const s16x4_t a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_tr_t*)(uintptr_t)(lo + o));
+    const s16x4_t b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_tr_t*)(uintptr_t)(hi + o));
+    typedef __attribute__((__vector_size__(8 * sizeof(short)))) short s16x8_t;
+    const s16x8_t v = __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7);
+    return __builtin_bit_cast(bf16x8_t, v);
+  }
+};
+// every request of this wave has landed, every LDS read has returned, and the same holds for the workgroup's other waves
+__device__ __forceinline__ void attn_tiles_ready() { asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+// order of a scheduling region's MFMAs and LDS reads: the reads of the first kAhead MFMAs, then one MFMA and the reads of one
+template <int MFMAS, int READS> __device__ __forceinline__ void sched_reads_ahead() {
+  constexpr int kAhead = 4 < MFMAS ? 4 : MFMAS;
+  __builtin_amdgcn_sched_group_barrier(0x100, kAhead * READS, 0);
+#pragma unroll
+  for (int i = 0; i < MFMAS; ++i) {
+    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+    __builtin_amdgcn_sched_group_barrier(0x100, READS, 0);
+  }
+}
+// MFMAs with the reads of one more and a share of VALU vector instructions behind each
+template <int MFMAS, int READS, int VALU> __device__ __forceinline__ void sched_mixed() {
+#pragma unroll
+  for (int i = 0; i < MFMAS; ++i) {
+    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+    __builtin_amdgcn_sched_group_barrier(0x100, READS, 0);
+    __builtin_amdgcn_sched_group_barrier(0x402, (VALU + MFMAS - 1) / MFMAS, 0);
+  }
+}
+
+// A lane's words of one general-mask tile: its query's flags of keys sub * 32 + 8 g + 4 * half .. + 3.  They are requested a
+// tile ahead; take() is where the compiler waits for them: behind attn_tiles_ready, when nothing else is in flight, and before
+// the next tile's requests.
+template <int SUBS> struct MaskWords {
+  uint32_t next[SUBS][4], now[SUBS][4];
+  __device__ __forceinline__ void load(const uint8_t* __restrict__ mrow, int key0, int s, int half) {
+#pragma unroll
+    for (int sub = 0; sub < SUBS; ++sub)
+#pragma unroll
+      for (int g = 0; g < 4; ++g) next[sub][g] = mask_word(mrow, key0 + sub * 32 + 8 * g + 4 * half, s, (s & 3) == 0);
+  }
+  __device__ __forceinline__ void take() {
+#pragma unroll
+    for (int sub = 0; sub < SUBS; ++sub)
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        now[sub][g] = next[sub][g];
+        asm volatile("" : "+v"(now[sub][g]));
+      }
+  }
+  __device__ __forceinline__ bool hidden(int sub, int r) const { return (now[sub][r >> 2] >> (8 * (r & 3))) & 0xffu; }
+};
+template <bool CAUSAL> __device__ __forceinline__ bool attn_map_tiles(int id, int nblk, int heads, int b, int* blk, int* e, int* j) {
+  if (!(CAUSAL ? attn_map_levels(id, nblk, heads, b, blk, e, j) : attn_map(id, nblk, heads, b, blk, e, j))) return false;
+  *blk = __builtin_amdgcn_readfirstlane(*blk);
+  *e = __builtin_amdgcn_readfirstlane(*e);
+  *j = __builtin_amdgcn_readfirstlane(*j);
+  return true;
+}
+
+// Forward: S^T = K Q^T and O^T = V^T P^T, so that the probabilities leave the first MFMA in the register layout the second
+// one takes as its B operand.  A workgroup owns 32 QW queries, 32 to a wave; K and V stream through two LDS stages of KT
+// keys, requested one tile ahead, with one barrier per tile.  What bounds it: with two waves per SIMD the matrix cores are
+// busy 37 % of the cycles and the vector ALU a quarter; the rest is the two waves waiting on each other's phases.  Hence:
+//   reads of fragments run four MFMAs ahead of their use (left to the compiler, every MFMA waits for its own read);
+//   the second 32 keys' exponentials are spread between the first 32 keys' products;
+//   long rows start first over all pairs of an XCD (attn_map_levels): 1.07 -> 1.43 waves per SIMD on average;
+//   the output is rescaled only when some row's running maximum moved, the mask touches only tiles on the diagonal.
+// NP = 2: two groups of QW waves take alternate tiles, with stages of their own, and their partial results are merged at the
+// end: for launches with too few workgroups to fill the chip.
+// us before (tiles through registers, two barriers per tile) and now, causal, s = 2048 unless given: 4 x 16 heads of 128 143 ->
+// 87; 12 heads of 128 52 -> 30; 8 heads 39 -> 29, at s = 1024 21.6 -> 16.3; 20 heads of 160 98 -> 54; 32 of 64 54 -> 32; 128
+// of 32 104 -> 67; without the mask 16 heads of 128 58 -> 43.
+template <int DH, bool CAUSAL, int QW, int NP, int KT>
+__global__ void __launch_bounds__(64 * QW * NP, 2)
+attn_fwd_tiles(const bf16_t* __restrict__ qkv, bf16_t* __restrict__ ctx, float* __restrict__ lse, int s, int b, int heads,
+               const uint8_t* __restrict__ mask) {
+  constexpr int NKK = DH / 16, NDT = DH / 32, kQ = 32 * QW, SUBS = KT / 32;
+  constexpr uint32_t kTile = TileDma<DH, QW, KT>::kBytes, kStage = 2 * kTile;
+  extern __shared__ __attribute__((aligned(1024))) char smem_all[];
+  const int wave_all = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), grp = NP == 1 ? 0 : wave_all / QW, wave = wave_all % QW;
+  const uint32_t lds0 = attn_lds_offset(smem_all) + grp * 2 * kStage;
+
+  const int nqb = (s + kQ - 1) / kQ;
   int qblk, e, j;
-  if (!attn_map(blockIdx.x, nqb, heads, b, &qblk, &e, &j)) return;
-  qblk = nqb - 1 - qblk;  // long rows first
-  const int wave = (threadIdx.x >> 6) & 1, lane = threadIdx.x & 63, half = lane >> 5, l31 = lane & 31;
+  if (!attn_map_tiles<CAUSAL>(blockIdx.x, nqb, heads, b, &qblk, &e, &j)) return;
+  qblk = nqb - 1 - qblk;   // long rows first
+  const int lane = threadIdx.x & 63, half = lane >> 5, l31 = lane & 31;
   const int hp = heads * DH;
   const size_t rs = (size_t)b * 3 * hp;
   const bf16_t* base = qkv + (size_t)j * 3 * hp + (size_t)e * DH;
-  const int q_first = qblk * kBQ + wave * 32;  // first query of this wave
+  const int q_first = qblk * kQ + wave * 32;
   const int my_q = q_first + l31;
   const float c2 = rsqrtf((float)DH) * 1.4426950408889634f;  // scale * log2(e)
+
+  const int q_last_blk = min(s, (qblk + 1) * kQ) - 1;
+  const int ntiles = CAUSAL ? q_last_blk / KT + 1 : (s + KT - 1) / KT;
+  TileDma<DH, QW, KT> dma;
+  dma.init(rs, lane);
+  auto request = [&](int kt, uint32_t stage) {
+    dma.issue(base + hp, kt * KT, s, lds0 + stage, wave);
+    dma.issue(base + 2 * hp, kt * KT, s, lds0 + stage + kTile, wave);
+  };
+  request(grp, 0);
 
   bf16x8_t qf[NKK];
 #pragma unroll
   for (int kk = 0; kk < NKK; ++kk) qf[kk] = frag_global(base + (size_t)min(my_q, s - 1) * rs, my_q < s, kk, half);
-
+  FragDirect<KT> fk;
+  FragTr<KT> fv;
+  fk.init(lds0, l31, half);
+  fv.init(lds0 + kTile, lane);
   f32x16_t o[NDT];
 #pragma unroll
   for (int d = 0; d < NDT; ++d) o[d] = zero16();
   float m_run = -INFINITY, l_run = 0.f;
-
-  const int q_last_blk = min(s, (qblk + 1) * kBQ) - 1;
-  const int ntiles = CAUSAL ? q_last_blk / kBKV + 1 : (s + kBKV - 1) / kBKV;
   const uint8_t* mrow = (!CAUSAL && mask) ? mask + ((size_t)j * s + min(my_q, s - 1)) * s : nullptr;
-  const bool aligned = (s & 3) == 0;
   const float fill = kMaskFill * sqrtf((float)DH);   // times 1/sqrt(dh) gives the fill value
-  TileMap<DH> map;
-  map.init(rs);
-  TileRegs<DH> tr;
-  if (pair < ntiles) {
-    map.load(tr, base + hp, rs, pair * kBKV, s);
-    map.store(tr, k_lds);
-  }
-  __syncthreads();
-  // both pairs take the same number of steps (the barriers are the workgroup's); a pair without a tile idles
-  for (int kt0 = 0; kt0 < ntiles; kt0 += NP) {
-    const int kt = kt0 + pair;
-    const bool have = kt < ntiles;
-    const int key0 = kt * kBKV;
-    const bool active = have && (!CAUSAL || key0 <= q_first + 31);  // else every key of the tile is in this wave's future
-    if (have) map.load(tr, base + 2 * hp, rs, key0, s);
-    uint32_t mw[2][4];
-    if (!CAUSAL && mrow) {
-#pragma unroll
-      for (int sub = 0; sub < 2; ++sub)
-#pragma unroll
-        for (int g = 0; g < 4; ++g) mw[sub][g] = mask_word(mrow, key0 + sub * 32 + 8 * g + 4 * half, s, aligned);
-    }
+  MaskWords<SUBS> mw;
+  if (!CAUSAL && mrow) mw.load(mrow, grp * KT, s, half);
 
-    bf16x8_t pf[2][2];
-    if (active) {
-      f32x16_t sacc[2];
+  uint32_t stage = 0;
+  // all groups take the same number of steps (the barriers are the workgroup's); a group without a tile idles
+  for (int kt0 = 0; kt0 < ntiles; kt0 += NP, stage ^= kStage) {
+    const int kt = kt0 + grp, key0 = kt * KT;
+    attn_tiles_ready();
+    if (!CAUSAL && mrow) mw.take();
+    if (kt0 + NP < ntiles) {
+      if (!CAUSAL && mrow) mw.load(mrow, key0 + NP * KT, s, half);
+      request(kt + NP, stage ^ kStage);
+    }
+    if (kt >= ntiles || (CAUSAL && key0 > q_first + 31)) continue;   // (every key of the tile is in this wave's future)
+
+    f32x16_t sacc[SUBS];
 #pragma unroll
-      for (int sub = 0; sub < 2; ++sub) {
-        sacc[sub] = zero16();
+    for (int sub = 0; sub < SUBS; ++sub) sacc[sub] = zero16();
+    const FragDirect<KT> fks = fk.at(stage);
 #pragma unroll
-        for (int kk = 0; kk < NKK; ++kk)
-          sacc[sub] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_direct<DH>(k_lds, sub, kk, l31, half), qf[kk],
-                                                              sacc[sub], 0, 0, 0);
+    for (int kk = 0; kk < NKK; ++kk)
+#pragma unroll
+      for (int sub = 0; sub < SUBS; ++sub) sacc[sub] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fks.get(sub, kk), qf[kk], sacc[sub], 0, 0, 0);
+    sched_reads_ahead<SUBS * NKK, 1>();
+    if (CAUSAL) {
+      // causal mask (also hides keys >= s, which are > every valid query); only tiles on the diagonal need it
+      if (key0 + KT - 1 > q_first) {
+#pragma unroll
+        for (int sub = 0; sub < SUBS; ++sub)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            const int key = key0 + sub * 32 + 8 * (r >> 2) + 4 * half + (r & 3);
+            sacc[sub][r] = key > my_q ? -INFINITY : sacc[sub][r];
+          }
       }
-      if (CAUSAL) {
-        // causal mask (also hides keys >= s, which are > every valid query); only tiles on the diagonal need it
-        if (key0 + kBKV - 1 > q_first) {
+    } else {
+      if (mrow) {
 #pragma unroll
-          for (int sub = 0; sub < 2; ++sub)
+        for (int sub = 0; sub < SUBS; ++sub)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-              const int key = key0 + sub * 32 + 8 * (r >> 2) + 4 * half + (r & 3);
-              sacc[sub][r] = key > my_q ? -INFINITY : sacc[sub][r];
-            }
-        }
-      } else {
-        if (mrow) {
-#pragma unroll
-          for (int sub = 0; sub < 2; ++sub)
-#pragma unroll
-            for (int r = 0; r < 16; ++r)
-              sacc[sub][r] = ((mw[sub][r >> 2] >> (8 * (r & 3))) & 0xffu) ? fill : sacc[sub][r];
-        }
-        if (key0 + kBKV > s) {   // keys past the end of the sequence do not exist
-#pragma unroll
-          for (int sub = 0; sub < 2; ++sub)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-              const int key = key0 + sub * 32 + 8 * (r >> 2) + 4 * half + (r & 3);
-              sacc[sub][r] = key >= s ? -INFINITY : sacc[sub][r];
-            }
-        }
+          for (int r = 0; r < 16; ++r) sacc[sub][r] = mw.hidden(sub, r) ? fill : sacc[sub][r];
       }
-      float mx = m_run;
+      if (key0 + KT > s) {   // keys past the end of the sequence do not exist
 #pragma unroll
-      for (int sub = 0; sub < 2; ++sub)
+        for (int sub = 0; sub < SUBS; ++sub)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) mx = fmaxf(mx, sacc[sub][r]);
-      mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-      if (__any(mx > m_run)) {   // some row's maximum moved: rescale what has been accumulated
-        const float corr = __builtin_amdgcn_exp2f((m_run - mx) * c2);
-        m_run = mx;
-        l_run *= corr;
+          for (int r = 0; r < 16; ++r) {
+            const int key = key0 + sub * 32 + 8 * (r >> 2) + 4 * half + (r & 3);
+            sacc[sub][r] = key >= s ? -INFINITY : sacc[sub][r];
+          }
+      }
+    }
+    float mx = m_run;
+#pragma unroll
+    for (int sub = 0; sub < SUBS; ++sub)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) mx = fmaxf(mx, sacc[sub][r]);
+    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+    if (__any(mx > m_run)) {   // some row's maximum moved: rescale what has been accumulated
+      const float corr = __builtin_amdgcn_exp2f((m_run - mx) * c2);
+      m_run = mx;
+      l_run *= corr;
+#pragma unroll
+      for (int d = 0; d < NDT; ++d)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) o[d][r] *= corr;
+    }
+    const float mc = mx * c2;
+    bf16x8_t pf[SUBS][2], vr[2][NDT];
+    auto weights = [&](int sub) {
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        sacc[sub][r] = __builtin_amdgcn_exp2f(sacc[sub][r] * c2 - mc);
+        l_run += sacc[sub][r];
+      }
+      pf[sub][0] = pack_frag(sacc[sub], 0);
+      pf[sub][1] = pack_frag(sacc[sub], 1);
+    };
+    const FragTr<KT> fvs = fv.at(stage);
+    auto read_v = [&](int u) {
+#pragma unroll
+      for (int d = 0; d < NDT; ++d) vr[u & 1][d] = fvs.get(d, u >> 1, u & 1);
+    };
+    auto multiply = [&](int u) {
+#pragma unroll
+      for (int d = 0; d < NDT; ++d) o[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vr[u & 1][d], pf[u >> 1][u & 1], o[d], 0, 0, 0);
+    };
+    read_v(0);
+    weights(0);
+    __builtin_amdgcn_sched_barrier(0);
+    if constexpr (SUBS == 2) {   // the second half's exponentials between the first half's products
+      read_v(1);
+      multiply(0);
+      read_v(2);
+      multiply(1);
+      weights(1);
+      sched_mixed<2 * NDT, 2, 56>();
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    read_v(2 * SUBS - 1);
+    multiply(2 * SUBS - 2);
+    multiply(2 * SUBS - 1);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  l_run += __shfl_xor(l_run, 32, 64);
+  if constexpr (NP > 1) {
+    // the other groups' partial results join group 0's in order: value v of lane l of wave w at part[w][v][l]
+    float* part = reinterpret_cast<float*>(smem_all) + wave * ((2 + NDT * 16) * 64) + lane;
+#pragma unroll 1
+    for (int from = 1; from < NP; ++from) {
+      __syncthreads();   // every wave is done with the tiles, the last partial result has been read
+      if (grp == from) {
+        part[0] = m_run;
+        part[64] = l_run;
 #pragma unroll
         for (int d = 0; d < NDT; ++d)
 #pragma unroll
-          for (int r = 0; r < 16; ++r) o[d][r] *= corr;
+          for (int r = 0; r < 16; ++r) part[(2 + d * 16 + r) * 64] = o[d][r];
       }
-      const float mc = mx * c2;
+      __syncthreads();
+      if (grp == 0) {
+        const float m1 = part[0], l1 = part[64];
+        const float m = fmaxf(m_run, m1);   // group 0 always has tile 0, whose key 0 every query sees: m_run is finite
+        const float a0 = __builtin_amdgcn_exp2f((m_run - m) * c2), a1 = __builtin_amdgcn_exp2f((m1 - m) * c2);
+        l_run = l_run * a0 + l1 * a1;
+        m_run = m;
 #pragma unroll
-      for (int sub = 0; sub < 2; ++sub) {
+        for (int d = 0; d < NDT; ++d)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          sacc[sub][r] = __builtin_amdgcn_exp2f(sacc[sub][r] * c2 - mc);
-          l_run += sacc[sub][r];
-        }
-        pf[sub][0] = pack_frag(sacc[sub], 0);
-        pf[sub][1] = pack_frag(sacc[sub], 1);
+          for (int r = 0; r < 16; ++r) o[d][r] = o[d][r] * a0 + part[(2 + d * 16 + r) * 64] * a1;
       }
     }
-    if (have) map.store(tr, v_lds);
-    __syncthreads();   // V visible; every wave is done with K of this step
-    if (kt + NP < ntiles) map.load(tr, base + hp, rs, key0 + NP * kBKV, s);
-    if (active) {
-#pragma unroll
-      for (int d = 0; d < NDT; ++d)
-#pragma unroll
-        for (int sub = 0; sub < 2; ++sub)
-#pragma unroll
-          for (int ks = 0; ks < 2; ++ks)
-            o[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_tr<DH>(v_lds, d, sub, ks, lane), pf[sub][ks], o[d], 0, 0, 0);
-    }
-    if (kt + NP < ntiles) map.store(tr, k_lds);
-    __syncthreads();   // next K visible; every wave is done with V of this step
-  }
-  l_run += __shfl_xor(l_run, 32, 64);
-  if constexpr (NP == 2) {
-    // pair 1's partial result joins pair 0's: value v of lane l of wave w at part[w][v][l]
-    float* part = reinterpret_cast<float*>(smem_all) + wave * ((2 + NDT * 16) * 64) + lane;
-    if (pair == 1) {
-      part[0] = m_run;
-      part[64] = l_run;
-#pragma unroll
-      for (int d = 0; d < NDT; ++d)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) part[(2 + d * 16 + r) * 64] = o[d][r];
-    }
-    __syncthreads();
-    if (pair == 1) return;
-    const float m1 = part[0], l1 = part[64];
-    const float m = fmaxf(m_run, m1);   // pair 0 always has tile 0, whose key 0 every query sees: m_run is finite
-    const float a0 = __builtin_amdgcn_exp2f((m_run - m) * c2), a1 = __builtin_amdgcn_exp2f((m1 - m) * c2);
-    l_run = l_run * a0 + l1 * a1;
-    m_run = m;
-#pragma unroll
-    for (int d = 0; d < NDT; ++d)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) o[d][r] = o[d][r] * a0 + part[(2 + d * 16 + r) * 64] * a1;
+    if (grp > 0) return;
   }
   if (my_q < s) {
     store_cols<NDT>(ctx + ((size_t)my_q * b + j) * hp + (size_t)e * DH, o, 1.f / l_run, half);
@@ -1221,10 +1397,21 @@ bool attn_dh_supported(int dtype, int dh) {
   return dh == 32 || dh == 64 || dh == 96 || dh == 128 || dh == 160;
 }
 
+template <int DH, bool CAUSAL, int QW, int NP, int KT>
+static int attn_fwd_tiles_np(const bf16_t* qkv, bf16_t* ctx, float* lse, int s, int b, int heads, const uint8_t* mask, hipStream_t stream) {
+  constexpr int tiles = NP * 4 * TileDma<DH, QW, KT>::kBytes, part = NP > 1 ? QW * (2 + DH / 2) * 64 * (int)sizeof(float) : 0;
+  constexpr int smem = tiles > part ? tiles : part;
+  static once_flag_t done[kMaxDevices];
+  if (set_dynamic_smem(reinterpret_cast<const void*>(attn_fwd_tiles<DH, CAUSAL, QW, NP, KT>), smem, done) != PTDP_OK) return PTDP_E_HIP;
+  const int nblk = (s + 32 * QW - 1) / (32 * QW);
+  const dim3 grid(CAUSAL ? attn_grid_levels(nblk, heads, b) : attn_grid(nblk, heads, b));
+  hipLaunchKernelGGL((attn_fwd_tiles<DH, CAUSAL, QW, NP, KT>), grid, dim3(64 * QW * NP), smem, stream, qkv, ctx, lse, s, b, heads, mask);
+  return PTDP_OK;
+}
+
 static inline double attn_flops(int s, int b, int heads, int dh) { return 4.0 * b * heads * (double)s * s * dh; }
 
-// resident workgroups of the one-pair kernels: two per CU (one wave per SIMD each)
-static int attn_resident_pairs() {
+static int attn_compute_units() {
   static std::atomic<int> cached[kMaxDevices];   // per device, looked up once
   const int d = device_slot();
   if (d >= 0 && cached[d].load(std::memory_order_relaxed) > 0) return cached[d].load(std::memory_order_relaxed);
@@ -1233,27 +1420,25 @@ static int attn_resident_pairs() {
     int v = 0;
     if (hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && v > 0) cu = v;
   }
-  if (d >= 0) cached[d].store(2 * cu, std::memory_order_relaxed);
-  return 2 * cu;
+  if (d >= 0) cached[d].store(cu, std::memory_order_relaxed);
+  return cu;
 }
-template <int DH, bool CAUSAL, int NP>
-static int attn_fwd_mfma_np(const bf16_t* qkv, bf16_t* ctx, float* lse, int s, int b, int heads, const uint8_t* mask,
-                            hipStream_t stream) {
-  constexpr int smem = NP * 2 * TileGeom<DH>::BYTES;   // (NP = 2: the partial results, (2 + DH / 2) x 512 bytes, fit in the tiles)
-  static once_flag_t done[kMaxDevices];
-  if (set_dynamic_smem(reinterpret_cast<const void*>(attn_fwd_mfma<DH, CAUSAL, NP>), smem, done) != PTDP_OK) return PTDP_E_HIP;
-  const dim3 grid(attn_grid((s + kBQ - 1) / kBQ, heads, b));
-  hipLaunchKernelGGL((attn_fwd_mfma<DH, CAUSAL, NP>), grid, dim3(NP * kAttnThreads), smem, stream, qkv, ctx, lse, s, b, heads,
-                     mask);
-  return PTDP_OK;
-}
+// Which form: QW waves of queries, NP groups, KT keys per tile.  The walk is split in two while one group per workgroup would
+// leave the chip's 2048 wave slots half empty, with 64 queries per workgroup as long as about every compute unit gets
+// one (heads of 64 and less: two fit), else 128.  us for (2, 2, 64), (4, 2, 64), (4, 1, 64): 8 heads of 128 x 2048 28.5, 34, 41; 12
+// heads 30, 36, 43; 16 heads without the mask 61, 43, 50; 32 heads of 64 35, 32, 35; 64 heads of 128 151, 102, 87.  Heads of
+// 160: two groups' stages of 64 keys would take all LDS, so tiles of 32: (2, 2, 32), (4, 1, 64): 20 heads 54, 57.
 template <int DH, bool CAUSAL>
 static int attn_fwd_mfma_t(const bf16_t* qkv, bf16_t* ctx, float* lse, int s, int b, int heads, const uint8_t* mask,
                            hipStream_t stream) {
-  // few workgroups: the longest one sets the time, so split its walk over two pairs of waves
-  const long long wgs = (long long)((s + kBQ - 1) / kBQ) * heads * b;
-  if (wgs <= attn_resident_pairs()) return attn_fwd_mfma_np<DH, CAUSAL, 2>(qkv, ctx, lse, s, b, heads, mask, stream);
-  return attn_fwd_mfma_np<DH, CAUSAL, 1>(qkv, ctx, lse, s, b, heads, mask, stream);
+  const long long blocks64 = (long long)((s + 63) / 64) * heads * b, ncu = attn_compute_units();
+  if (blocks64 > 4 * ncu) return attn_fwd_tiles_np<DH, CAUSAL, 4, 1, 64>(qkv, ctx, lse, s, b, heads, mask, stream);
+  if constexpr (DH > 128) {
+    return attn_fwd_tiles_np<DH, CAUSAL, 2, 2, 32>(qkv, ctx, lse, s, b, heads, mask, stream);
+  } else {
+    if (blocks64 <= (DH > 64 ? ncu * 3 / 2 : ncu * 2)) return attn_fwd_tiles_np<DH, CAUSAL, 2, 2, 64>(qkv, ctx, lse, s, b, heads, mask, stream);
+    return attn_fwd_tiles_np<DH, CAUSAL, 4, 2, 64>(qkv, ctx, lse, s, b, heads, mask, stream);
+  }
 }
 
 // steps of 16 dh, rounded up to one of the built forms
@@ -1335,7 +1520,8 @@ static int attn_bwd_mfma_t(const bf16_t* qkv, const bf16_t* ctx, const float* ls
                            float* delta, int s, int b, int heads, const uint8_t* mask, hipStream_t stream) {
   // few workgroups: the longest one sets the time, so split its walk over two pairs of waves
   const long long wgs = (long long)((s + kBQ - 1) / kBQ) * heads * b;
-  if (wgs <= attn_resident_pairs())
+  if (wgs <= 2 * attn_compute_units())   // all resident at once: two per compute unit, one wave per SIMD each
+   
     return attn_bwd_mfma_np<DH, CAUSAL, 2>(qkv, ctx, dctx, lse, delta, dqkv, s, b, heads, mask, stream);
   return attn_bwd_mfma_np<DH, CAUSAL, 1>(qkv, ctx, dctx, lse, delta, dqkv, s, b, heads, mask, stream);
 }

@@ -299,6 +299,15 @@ def test_attention_forward_backward(dtype, s, b, heads, dh):
         assert_close(got[..., lo:lo + hp], want[..., lo:lo + hp], dtype, name)
 
 
+# The forms of the causal kernels on 64-row (32-row) tiles and the assignment of their blocks: workgroups of 64 and 128 rows, the
+# walk split in two or whole, fewer and more than eight blocks per head, a last block of one to six rows, and numbers of
+# (sample, head) pairs that leave 5, 6 and 7 of them over after dealing eight at a time.
+@pytest.mark.parametrize("s,b,heads,dh", [(1026, 1, 13, 64), (518, 1, 62, 32), (1025, 1, 37, 64), (1030, 1, 61, 32),
+                                          (515, 1, 47, 128), (897, 1, 7, 160), (449, 2, 67, 160), (70, 1, 5, 96)])
+def test_attention_forms(s, b, heads, dh):
+    test_attention_forward_backward(B.BF16, s, b, heads, dh)
+
+
 def test_attention_sharp_softmax_bf16():
     # logits with standard deviation ~10, as N(0, 0.02) weights give at h = 25600
     s, b, heads, dh = 256, 1, 2, 160
