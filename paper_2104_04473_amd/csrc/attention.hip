@@ -11,6 +11,7 @@
 // B operand.  One wave owns 32 queries; the waves of a block share K and V tiles in LDS.
 // fp32: the same two-step form on v_mfma_f32_16x16x4_f32, operands straight from memory.
 #include "common.h"
+#include <type_traits>
 
 namespace ptdp {
 
@@ -616,23 +617,49 @@ template <int MFMAS, int READS, int VALU> __device__ __forceinline__ void sched_
 
 // A lane's words of one general-mask tile: its query's flags of keys sub * 32 + 8 g + 4 * half .. + 3.  They are requested a
 // tile ahead; take() is where the compiler waits for them: behind attn_tiles_ready, when nothing else is in flight, and before
-// the next tile's requests.
+// the next tile's requests.  A tile inside the mask row travels as 16 SUBS consecutive bytes per lane (word by word it took
+// four times the address cycles, more than the tile's products: dQ of 4 x 16 heads of 64 x 512 27 us); the two lanes of a row
+// then exchange every other word.
 template <int SUBS> struct MaskWords {
-  uint32_t next[SUBS][4], now[SUBS][4];
+  uint32_t next[SUBS * 4], now[SUBS][4];
+  bool wide;
   __device__ __forceinline__ void load(const uint8_t* __restrict__ mrow, int key0, int s, int half) {
+    typedef uint32_t words_t __attribute__((ext_vector_type(4), aligned(4)));
+    wide = key0 + 32 * SUBS <= s && (s & 3) == 0;
+    if (wide) {
+      const words_t* p = reinterpret_cast<const words_t*>(mrow + key0 + half * (16 * SUBS));
 #pragma unroll
-    for (int sub = 0; sub < SUBS; ++sub)
+      for (int i = 0; i < SUBS; ++i) {
+        const words_t w = p[i];
 #pragma unroll
-      for (int g = 0; g < 4; ++g) next[sub][g] = mask_word(mrow, key0 + sub * 32 + 8 * g + 4 * half, s, (s & 3) == 0);
+        for (int k = 0; k < 4; ++k) next[4 * i + k] = w[k];
+      }
+    } else {
+#pragma unroll
+      for (int sub = 0; sub < SUBS; ++sub)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) next[sub * 4 + g] = mask_word(mrow, key0 + sub * 32 + 8 * g + 4 * half, s, (s & 3) == 0);
+    }
   }
   __device__ __forceinline__ void take() {
 #pragma unroll
-    for (int sub = 0; sub < SUBS; ++sub)
+    for (int i = 0; i < 4 * SUBS; ++i) asm volatile("" : "+v"(next[i]));
+    if (wide) {   // words 2 i, 2 i + 1 of the lower lane's and of the upper lane's bytes: even ones belong below, odd ones above
 #pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        now[sub][g] = next[sub][g];
-        asm volatile("" : "+v"(now[sub][g]));
+      for (int i = 0; i < 2 * SUBS; ++i) {
+        const auto w = __builtin_amdgcn_permlane32_swap(next[2 * i], next[2 * i + 1], false, false);
+        if constexpr (SUBS == 2) {
+          now[0][i] = w[0];
+          now[1][i] = w[1];
+        } else {
+          now[0][i] = w[0];
+          now[0][2 + i] = w[1];
+        }
       }
+    } else {
+#pragma unroll
+      for (int i = 0; i < 4 * SUBS; ++i) now[i >> 2][i & 3] = next[i];
+    }
   }
   __device__ __forceinline__ bool hidden(int sub, int r) const { return (now[sub][r >> 2] >> (8 * (r & 3))) & 0xffu; }
 };
@@ -700,19 +727,20 @@ attn_fwd_tiles(const bf16_t* __restrict__ qkv, bf16_t* __restrict__ ctx, float* 
 #pragma unroll
   for (int d = 0; d < NDT; ++d) o[d] = zero16();
   float m_run = -INFINITY, l_run = 0.f;
-  const uint8_t* mrow = (!CAUSAL && mask) ? mask + ((size_t)j * s + min(my_q, s - 1)) * s : nullptr;
+  const bool use_mask = !CAUSAL && mask != nullptr;
+  const uint8_t* mrow = mask + ((size_t)j * s + min(my_q, s - 1)) * s;   // (read if use_mask)
   const float fill = kMaskFill * sqrtf((float)DH);   // times 1/sqrt(dh) gives the fill value
   MaskWords<SUBS> mw;
-  if (!CAUSAL && mrow) mw.load(mrow, grp * KT, s, half);
+  if (use_mask) mw.load(mrow, grp * KT, s, half);
 
   uint32_t stage = 0;
   // all groups take the same number of steps (the barriers are the workgroup's); a group without a tile idles
   for (int kt0 = 0; kt0 < ntiles; kt0 += NP, stage ^= kStage) {
     const int kt = kt0 + grp, key0 = kt * KT;
     attn_tiles_ready();
-    if (!CAUSAL && mrow) mw.take();
+    if (use_mask) mw.take();
     if (kt0 + NP < ntiles) {
-      if (!CAUSAL && mrow) mw.load(mrow, key0 + NP * KT, s, half);
+      if (use_mask) mw.load(mrow, key0 + NP * KT, s, half);
       request(kt + NP, stage ^ kStage);
     }
     if (kt >= ntiles || (CAUSAL && key0 > q_first + 31)) continue;   // (every key of the tile is in this wave's future)
@@ -738,7 +766,7 @@ attn_fwd_tiles(const bf16_t* __restrict__ qkv, bf16_t* __restrict__ ctx, float* 
           }
       }
     } else {
-      if (mrow) {
+      if (use_mask) {
 #pragma unroll
         for (int sub = 0; sub < SUBS; ++sub)
 #pragma unroll
@@ -847,35 +875,49 @@ attn_fwd_tiles(const bf16_t* __restrict__ qkv, bf16_t* __restrict__ ctx, float* 
 // needs atomics: one owns 64 queries and produces dQ, one owns 64 keys and produces dK and dV.
 //   dP = dO V^T, dS = P o (dP - delta), dQ = dS K / sqrt(dh), dK = dS^T Q / sqrt(dh), dV = P^T dO
 // ------------------------------------------------------------------------------------------------
-// dQ: a workgroup owns 64 queries.  NP = 2: it is two pairs of waves; pair p walks every second 64-key tile with
-// tiles of its own in LDS and pair 1 hands its sums to pair 0 at the end (see the dK/dV kernel below for when).
-template <int DH, bool CAUSAL, int NP>
-__global__ void __launch_bounds__(NP * kAttnThreads, DH >= 96 ? 1 : 2)
-attn_bwd_dq_mfma(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ ctx, const bf16_t* __restrict__ dctx,
-                 const float* __restrict__ lse, float* __restrict__ delta, bf16_t* __restrict__ dqkv, int s, int b, int heads,
-                 const uint8_t* __restrict__ mask) {
-  constexpr int NKK = DH / 16, NDT = DH / 32;
-  extern __shared__ __attribute__((aligned(16))) char smem_all[];
-  const int pair = NP == 2 ? threadIdx.x >> 7 : 0;
-  char* smem = smem_all + pair * 2 * TileGeom<DH>::BYTES;
-  char* k_lds = smem;                          // K [key][dh]: S^T = K Q^T directly, dQ^T = K^T dS^T through tr reads
-  char* v_lds = smem + TileGeom<DH>::BYTES;    // V [key][dh]: dP^T = V dO^T
+// dQ of 32 QW queries, as the forward kernel walks them: K and V stream through two LDS stages of KT keys (K is read twice,
+// as rows for S and transposed for dQ).  NP = 2: two groups take alternate tiles and their sums are added at the end.  A wave
+// holds Q, dO and dQ and fits two to a SIMD (tiles on their way through registers had left one), so that one's
+// exponentials run under the other's products.  Error against 64 bits unchanged.
+// us before and now, causal, s = 2048 unless given: 4 x 16 heads of 128 216 -> 106; 12 heads of 128 61 -> 38; 8 heads 48 -> 34, at
+// s = 1024 27 -> 20; 20 heads of 160 121 -> 56; 32 of 64 62 -> 36; 128 of 32 112 -> 76; 16 of 128 without the mask 147 -> 61; 4 x 16
+// heads of 64 x 512 under a general mask 23 -> 16.
+template <int DH, bool CAUSAL, int QW, int NP, int KT>
+__global__ void __launch_bounds__(64 * QW * NP, 2)
+attn_bwd_dq_tiles(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ ctx, const bf16_t* __restrict__ dctx,
+                  const float* __restrict__ lse, float* __restrict__ delta, bf16_t* __restrict__ dqkv, int s, int b, int heads,
+                  const uint8_t* __restrict__ mask) {
+  constexpr int NKK = DH / 16, NDT = DH / 32, kQ = 32 * QW, SUBS = KT / 32;
+  constexpr uint32_t kTile = TileDma<DH, QW, KT>::kBytes, kStage = 2 * kTile;
+  extern __shared__ __attribute__((aligned(1024))) char smem_all[];
+  const int wave_all = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), grp = NP == 1 ? 0 : wave_all / QW, wave = wave_all % QW;
+  const uint32_t lds0 = attn_lds_offset(smem_all) + grp * 2 * kStage;
 
-  const int nqb = (s + kBQ - 1) / kBQ;
+  const int nqb = (s + kQ - 1) / kQ;
   int qblk, e, j;
-  if (!attn_map(blockIdx.x, nqb, heads, b, &qblk, &e, &j)) return;
-  qblk = nqb - 1 - qblk;
-  const int wave = (threadIdx.x >> 6) & 1, lane = threadIdx.x & 63, half = lane >> 5, l31 = lane & 31;
+  if (!attn_map_tiles<CAUSAL>(blockIdx.x, nqb, heads, b, &qblk, &e, &j)) return;
+  qblk = nqb - 1 - qblk;   // long rows first
+  const int lane = threadIdx.x & 63, half = lane >> 5, l31 = lane & 31;
   const int hp = heads * DH;
   const size_t rs = (size_t)b * 3 * hp;
   const bf16_t* base = qkv + (size_t)j * 3 * hp + (size_t)e * DH;
-  const int q_first = qblk * kBQ + wave * 32;
+  const int q_first = qblk * kQ + wave * 32;
   const int my_q = q_first + l31;
   const bool valid = my_q < s;
   const float scale = rsqrtf((float)DH), c2 = scale * 1.4426950408889634f;
   const size_t stat = ((size_t)j * heads + e) * s + my_q;
-  const float L2 = valid ? lse[stat] * 1.4426950408889634f : 0.f;
 
+  const int q_last_blk = min(s, (qblk + 1) * kQ) - 1;
+  const int ntiles = CAUSAL ? q_last_blk / KT + 1 : (s + KT - 1) / KT;
+  TileDma<DH, QW, KT> dma;
+  dma.init(rs, lane);
+  auto request = [&](int kt, uint32_t stage) {
+    dma.issue(base + hp, kt * KT, s, lds0 + stage, wave);
+    dma.issue(base + 2 * hp, kt * KT, s, lds0 + stage + kTile, wave);
+  };
+  request(grp, 0);
+
+  const float L2 = valid ? lse[stat] * 1.4426950408889634f : 0.f;
   bf16x8_t qf[NKK], dof[NKK];
   const size_t out_row = ((size_t)min(my_q, s - 1) * b + j) * hp + (size_t)e * DH;
 #pragma unroll
@@ -897,103 +939,93 @@ attn_bwd_dq_mfma(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ ctx,
     for (int r = 1; r < 16; ++r) mine = (l31 & 3) + 4 * (l31 >> 3) == r ? x[r] : mine;
     D = __shfl(mine, ((l31 >> 2) & 1) * 32 + l31, 64);
   }
-  if (pair == 0 && half == 0 && valid) delta[stat] = D;
+  if (grp == 0 && half == 0 && valid) delta[stat] = D;
+  FragDirect<KT> fk, fv;
+  FragTr<KT> ft;
+  fk.init(lds0, l31, half);
+  fv.init(lds0 + kTile, l31, half);
+  ft.init(lds0, lane);
   f32x16_t acc[NDT];
 #pragma unroll
   for (int d = 0; d < NDT; ++d) acc[d] = zero16();
+  const bool use_mask = !CAUSAL && mask != nullptr;
+  const uint8_t* mrow = mask + ((size_t)j * s + min(my_q, s - 1)) * s;   // (read if use_mask)
+  MaskWords<SUBS> mw;
+  if (use_mask) mw.load(mrow, grp * KT, s, half);
 
-  const int q_last_blk = min(s, (qblk + 1) * kBQ) - 1;
-  const int ntiles = CAUSAL ? q_last_blk / kBKV + 1 : (s + kBKV - 1) / kBKV;
-  const uint8_t* mrow = (!CAUSAL && mask) ? mask + ((size_t)j * s + min(my_q, s - 1)) * s : nullptr;
-  const bool aligned = (s & 3) == 0;
-  // the next K and V tiles travel in registers while this step's arithmetic runs
-  TileMap<DH> map;
-  map.init(rs);
-  TileRegs<DH> kr, vr;
-  if (pair < ntiles) {
-    map.load(kr, base + hp, rs, pair * kBKV, s);
-    map.load(vr, base + 2 * hp, rs, pair * kBKV, s);
-  }
-  // both pairs take the same number of steps (the barriers are the workgroup's); a pair without a tile idles
-  for (int kt0 = 0; kt0 < ntiles; kt0 += NP) {
-    const int kt = kt0 + pair;
-    const bool have = kt < ntiles;
-    const int key0 = kt * kBKV;
-    __syncthreads();
-    if (have) {
-      map.store(kr, k_lds);
-      map.store(vr, v_lds);
+  uint32_t stage = 0;
+  // all groups take the same number of steps (the barriers are the workgroup's); a group without a tile idles
+  for (int kt0 = 0; kt0 < ntiles; kt0 += NP, stage ^= kStage) {
+    const int kt = kt0 + grp, key0 = kt * KT;
+    attn_tiles_ready();
+    if (use_mask) mw.take();
+    if (kt0 + NP < ntiles) {
+      if (use_mask) mw.load(mrow, key0 + NP * KT, s, half);
+      request(kt + NP, stage ^ kStage);
     }
-    __syncthreads();
-    if (!have) continue;
-    if (kt + NP < ntiles) {
-      map.load(kr, base + hp, rs, key0 + NP * kBKV, s);
-      map.load(vr, base + 2 * hp, rs, key0 + NP * kBKV, s);
-    }
-    if (CAUSAL && key0 > q_first + 31) continue;
-    const bool diag = key0 + kBKV - 1 > q_first;   // only tiles on the diagonal need the causal mask
-    bf16x8_t dsf[2][2];
+    if (kt >= ntiles || (CAUSAL && key0 > q_first + 31)) continue;   // (every key of the tile is in this wave's future)
+
+    const FragDirect<KT> fks = fk.at(stage), fvs = fv.at(stage);
+    const FragTr<KT> fts = ft.at(stage);
+    // some score of the tile is hidden (under the causal mask only in tiles on the diagonal)
+    const bool hide = CAUSAL ? key0 + KT - 1 > q_first : use_mask || key0 + KT > s;
 #pragma unroll
-    for (int sub = 0; sub < 2; ++sub) {
-      uint32_t mw[4] = {0u, 0u, 0u, 0u};
-      if (!CAUSAL && mrow) {
-#pragma unroll
-        for (int g = 0; g < 4; ++g) mw[g] = mask_word(mrow, key0 + sub * 32 + 8 * g + 4 * half, s, aligned);
-      }
+    for (int sub = 0; sub < SUBS; ++sub) {
       f32x16_t sacc = zero16(), dp = zero16();
 #pragma unroll
       for (int kk = 0; kk < NKK; ++kk) {
-        sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_direct<DH>(k_lds, sub, kk, l31, half), qf[kk], sacc, 0, 0, 0);
-        dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_direct<DH>(v_lds, sub, kk, l31, half), dof[kk], dp, 0, 0, 0);
+        sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fks.get(sub, kk), qf[kk], sacc, 0, 0, 0);
+        dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fvs.get(sub, kk), dof[kk], dp, 0, 0, 0);
       }
-      if (!CAUSAL) {
-        // a hidden score is the constant fill: its probability counts (through D) but it passes no gradient;
-        // keys past the end do not exist (an empty row's lse is so low that their exp2 would overflow)
-        const bool tail = key0 + kBKV > s;
+      sched_reads_ahead<2 * NKK, 1>();
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int key = key0 + sub * 32 + 8 * (r >> 2) + 4 * half + (r & 3);
-          const bool hidden = ((mw[r >> 2] >> (8 * (r & 3))) & 0xffu) || (tail && key >= s);
-          sacc[r] = hidden ? 0.f : __builtin_amdgcn_exp2f(sacc[r] * c2 - L2) * (dp[r] - D);
+      for (int r = 0; r < 16; ++r) sacc[r] = __builtin_amdgcn_exp2f(sacc[r] * c2 - L2) * (dp[r] - D);
+      if (hide) {
+        // without the causal mask a hidden score is the constant fill: its probability counts (through D) but it passes no
+        // gradient; keys past the end do not exist (an empty row's lse is so low that their exp2 would overflow)
+        if (CAUSAL || key0 + KT > s) {
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            const int key = key0 + sub * 32 + 8 * (r >> 2) + 4 * half + (r & 3);
+            sacc[r] = (CAUSAL ? key > my_q : key >= s) ? 0.f : sacc[r];
+          }
         }
-      } else if (diag) {
+        if (use_mask) {
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int key = key0 + sub * 32 + 8 * (r >> 2) + 4 * half + (r & 3);
-          const float p = __builtin_amdgcn_exp2f(sacc[r] * c2 - L2);
-          sacc[r] = key > my_q ? 0.f : p * (dp[r] - D);
+          for (int r = 0; r < 16; ++r) sacc[r] = mw.hidden(sub, r) ? 0.f : sacc[r];
         }
-      } else {
-#pragma unroll
-        for (int r = 0; r < 16; ++r) sacc[r] = __builtin_amdgcn_exp2f(sacc[r] * c2 - L2) * (dp[r] - D);
       }
-      dsf[sub][0] = pack_frag(sacc, 0);
-      dsf[sub][1] = pack_frag(sacc, 1);
+      const bf16x8_t dsf[2] = {pack_frag(sacc, 0), pack_frag(sacc, 1)};
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+        for (int d = 0; d < NDT; ++d) acc[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fts.get(d, sub, ks), dsf[ks], acc[d], 0, 0, 0);
+      sched_reads_ahead<2 * NDT, 2>();
+      __builtin_amdgcn_sched_barrier(0);
     }
-#pragma unroll
-    for (int d = 0; d < NDT; ++d)
-#pragma unroll
-      for (int sub = 0; sub < 2; ++sub)
-#pragma unroll
-        for (int ks = 0; ks < 2; ++ks)
-          acc[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_tr<DH>(k_lds, d, sub, ks, lane), dsf[sub][ks], acc[d], 0, 0, 0);
   }
-  if constexpr (NP == 2) {
-    // pair 1's sums join pair 0's: register r of lane l of wave w at sum[w][r][l]
-    __syncthreads();   // every wave is done with the tiles
+  if constexpr (NP > 1) {
+    // the other groups' sums join group 0's in order: register r of lane l of wave w at sum[w][r][l]
     float* sum = reinterpret_cast<float*>(smem_all) + wave * (NDT * 16 * 64) + lane;
-    if (pair == 1) {
+#pragma unroll 1
+    for (int from = 1; from < NP; ++from) {
+      __syncthreads();   // every wave is done with the tiles, the last sums have been read
+      if (grp == from) {
 #pragma unroll
-      for (int d = 0; d < NDT; ++d)
+        for (int d = 0; d < NDT; ++d)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) sum[(d * 16 + r) * 64] = acc[d][r];
+          for (int r = 0; r < 16; ++r) sum[(d * 16 + r) * 64] = acc[d][r];
+      }
+      __syncthreads();
+      if (grp == 0) {
+#pragma unroll
+        for (int d = 0; d < NDT; ++d)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) acc[d][r] += sum[(d * 16 + r) * 64];
+      }
     }
-    __syncthreads();
-    if (pair == 1) return;
-#pragma unroll
-    for (int d = 0; d < NDT; ++d)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[d][r] += sum[(d * 16 + r) * 64];
+    if (grp > 0) return;
   }
   if (valid) store_cols<NDT>(dqkv + (size_t)my_q * rs + (size_t)j * 3 * hp + (size_t)e * DH, acc, scale, half);
 }
@@ -1490,40 +1522,63 @@ static void attn_bwd_f32_t(const float* qkv, const float* ctx, const float* lse,
   hipLaunchKernelGGL(attn_bwd_dkv_f32<ND>, grid, block, 0, stream, qkv, dctx, lse, (const float*)delta, dqkv, s, b, heads, dh, mask, causal);
 }
 
-template <int DH, bool CAUSAL, int NP>
-static int attn_bwd_mfma_np(const bf16_t* qkv, const bf16_t* ctx, const bf16_t* dctx, const float* lse, float* delta, bf16_t* dqkv,
-                            int s, int b, int heads, const uint8_t* mask, hipStream_t stream) {
-  constexpr int smem_dq = NP * 2 * TileGeom<DH>::BYTES;   // (NP = 2: the final sums, 2 x DH x 256 bytes, fit in the tiles)
-  static once_flag_t done_dq[kMaxDevices], done_dkv[kMaxDevices];
-  if (set_dynamic_smem(reinterpret_cast<const void*>(attn_bwd_dq_mfma<DH, CAUSAL, NP>), smem_dq, done_dq) != PTDP_OK) return PTDP_E_HIP;
-  const dim3 grid(attn_grid((s + kBQ - 1) / kBQ, heads, b));
-  // dQ first: it writes delta
-  hipLaunchKernelGGL((attn_bwd_dq_mfma<DH, CAUSAL, NP>), grid, dim3(NP * kAttnThreads), smem_dq, stream, qkv, ctx, dctx, lse, delta,
+template <int DH, bool CAUSAL, int QW, int NP, int KT>
+static int attn_bwd_dq_tiles_np(const bf16_t* qkv, const bf16_t* ctx, const bf16_t* dctx, const float* lse, float* delta, bf16_t* dqkv,
+                                int s, int b, int heads, const uint8_t* mask, hipStream_t stream) {
+  constexpr int tiles = NP * 4 * TileDma<DH, QW, KT>::kBytes, sums = NP > 1 ? QW * (DH / 2) * 64 * (int)sizeof(float) : 0;
+  constexpr int smem = tiles > sums ? tiles : sums;
+  static once_flag_t done[kMaxDevices];
+  if (set_dynamic_smem(reinterpret_cast<const void*>(attn_bwd_dq_tiles<DH, CAUSAL, QW, NP, KT>), smem, done) != PTDP_OK) return PTDP_E_HIP;
+  const int nblk = (s + 32 * QW - 1) / (32 * QW);
+  const dim3 grid(CAUSAL ? attn_grid_levels(nblk, heads, b) : attn_grid(nblk, heads, b));
+  hipLaunchKernelGGL((attn_bwd_dq_tiles<DH, CAUSAL, QW, NP, KT>), grid, dim3(64 * QW * NP), smem, stream, qkv, ctx, dctx, lse, delta,
                      dqkv, s, b, heads, mask);
+  return PTDP_OK;
+}
+
+// Which form: as for the forward kernel.  us for (2, 2, 32), (2, 2, 64), (4, 2, 64), (4, 1, 64): 8 heads of 128 x 2048 34, 33, 43, 49; 16
+// heads 42, 46, 50, 53; 24 heads 52, 69, 54, 58; 32 heads 68, 87, 65, 64; 64 heads 122, 172, 129, 106; 32 heads of 64 36, 42, 40, 44;
+// 128 heads of 32 94, 102, 87, 76; 20 and 40 heads of 160 (first and last) 56, 69 and 101, 88; 16 heads of 128 without the mask 61,
+// 80, 56, 60.
+template <int DH, bool CAUSAL>
+static int attn_bwd_dq_t(const bf16_t* qkv, const bf16_t* ctx, const bf16_t* dctx, const float* lse, float* delta, bf16_t* dqkv, int s,
+                         int b, int heads, const uint8_t* mask, hipStream_t stream) {
+  const long long blocks64 = (long long)((s + 63) / 64) * heads * b;
+  if (blocks64 > (DH > 64 ? 3 : 4) * attn_compute_units())
+    return attn_bwd_dq_tiles_np<DH, CAUSAL, 4, 1, 64>(qkv, ctx, dctx, lse, delta, dqkv, s, b, heads, mask, stream);
+  return attn_bwd_dq_tiles_np<DH, CAUSAL, 2, 2, 32>(qkv, ctx, dctx, lse, delta, dqkv, s, b, heads, mask, stream);
+}
+
+template <int DH, bool CAUSAL, int NP>
+static int attn_bwd_dkv_np(const bf16_t* qkv, const bf16_t* dctx, const float* lse, const float* delta, bf16_t* dqkv, int s, int b, int heads,
+                           const uint8_t* mask, hipStream_t stream) {
+  static once_flag_t done_dkv[kMaxDevices];
+  const dim3 grid(attn_grid((s + kBQ - 1) / kBQ, heads, b));
   if constexpr (!kDkvSplit<DH, CAUSAL>) {
     constexpr int smem_dkv = NP == 2 ? DkvLds<DH, CAUSAL>::kBytes2 : DkvLds<DH, CAUSAL>::kPair;
     if (set_dynamic_smem(reinterpret_cast<const void*>(attn_bwd_dkv_both_mfma<DH, CAUSAL, NP>), smem_dkv, done_dkv) != PTDP_OK)
       return PTDP_E_HIP;
     hipLaunchKernelGGL((attn_bwd_dkv_both_mfma<DH, CAUSAL, NP>), grid, dim3(NP * kAttnThreads), smem_dkv, stream, qkv, dctx, lse,
-                       (const float*)delta, dqkv, s, b, heads, mask);
+                       delta, dqkv, s, b, heads, mask);
   } else {
     constexpr int smem_dkv = NP == 2 ? DkvLds<DH, CAUSAL>::kBytes2 : DkvLds<DH, CAUSAL>::kPair;
     if (set_dynamic_smem(reinterpret_cast<const void*>(attn_bwd_dkv_mfma<DH, CAUSAL, NP>), smem_dkv, done_dkv) != PTDP_OK)
       return PTDP_E_HIP;
     hipLaunchKernelGGL((attn_bwd_dkv_mfma<DH, CAUSAL, NP>), grid, dim3(NP * kDkvThreads), smem_dkv, stream, qkv, dctx, lse,
-                       (const float*)delta, dqkv, s, b, heads, mask);
+                       delta, dqkv, s, b, heads, mask);
   }
   return PTDP_OK;
 }
 template <int DH, bool CAUSAL>
 static int attn_bwd_mfma_t(const bf16_t* qkv, const bf16_t* ctx, const float* lse, const bf16_t* dctx, bf16_t* dqkv,
                            float* delta, int s, int b, int heads, const uint8_t* mask, hipStream_t stream) {
+  const int rc = attn_bwd_dq_t<DH, CAUSAL>(qkv, ctx, dctx, lse, delta, dqkv, s, b, heads, mask, stream);   // first: it writes delta
+  if (rc != PTDP_OK) return rc;
   // few workgroups: the longest one sets the time, so split its walk over two pairs of waves
   const long long wgs = (long long)((s + kBQ - 1) / kBQ) * heads * b;
   if (wgs <= 2 * attn_compute_units())   // all resident at once: two per compute unit, one wave per SIMD each
-   
-    return attn_bwd_mfma_np<DH, CAUSAL, 2>(qkv, ctx, dctx, lse, delta, dqkv, s, b, heads, mask, stream);
-  return attn_bwd_mfma_np<DH, CAUSAL, 1>(qkv, ctx, dctx, lse, delta, dqkv, s, b, heads, mask, stream);
+    return attn_bwd_dkv_np<DH, CAUSAL, 2>(qkv, dctx, lse, delta, dqkv, s, b, heads, mask, stream);
+  return attn_bwd_dkv_np<DH, CAUSAL, 1>(qkv, dctx, lse, delta, dqkv, s, b, heads, mask, stream);
 }
 
 int launch_attn_bwd(int dtype, const void* qkv, const void* ctx, const float* lse, const void* dctx, void* dqkv,

@@ -76,6 +76,14 @@ def test_masked_attention_forward_backward(dtype, s, b, heads, dh, masked, empty
         assert np.all(got[q, j, :hp] == 0.0)      # no gradient reaches the query of an empty row
 
 
+# Mask rows that travel whole (s a multiple of 4: tiles inside the row), word by word (the last tile) and byte by byte (any other
+# s), in the forms of the kernels for few and many workgroups.
+@pytest.mark.parametrize("s,b,heads,dh", [(196, 1, 3, 64), (132, 2, 3, 160), (132, 8, 43, 32), (131, 8, 43, 32), (192, 4, 65, 128),
+                                          (256, 2, 35, 96)])
+def test_masked_attention_forms(s, b, heads, dh):
+    test_masked_attention_forward_backward(B.BF16, s, b, heads, dh, True, [(0, s - 1)])
+
+
 def test_upper_triangular_mask_equals_the_causal_kernels():
     s, b, heads, dh = 192, 1, 2, 128
     hp = heads * dh
