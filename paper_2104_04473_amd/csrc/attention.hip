@@ -316,104 +316,13 @@ attn_bwd_dkv_f32(const float* __restrict__ qkv, const float* __restrict__ dctx, 
 }
 
 // ------------------------------------------------------------------------------------------------
-// bf16 MFMA kernels.  A workgroup is 2 waves and owns 64 queries (forward, dQ) or 64 keys (dK/dV); the
-// other side streams through LDS in tiles of 64 rows kept in memory order [row][dh].  Operands whose
-// contraction index is the tile row (V^T, K^T, Q^T, dO^T) are gathered from those same tiles with
-// transposing LDS reads, so nothing is transposed in registers and every tile is stored once.
+// bf16 MFMA kernels.  A wave owns 32 queries (forward, dQ) or 32 keys (dK/dV); the other side streams through LDS in
+// tiles of 32 or 64 rows kept in memory order [row][dh].  Operands whose contraction index is the tile row (V^T, K^T,
+// Q^T, dO^T) are gathered from those same tiles with transposing LDS reads, so nothing is transposed in registers
+// and every tile is stored once.
 // ------------------------------------------------------------------------------------------------
-constexpr int kBQ = 64;            // rows owned by a workgroup (2 waves x 32)
-constexpr int kBKV = 64;           // rows per streamed LDS tile
-constexpr int kAttnThreads = 128;
 typedef __attribute__((__vector_size__(4 * sizeof(short)))) short s16x4_t;
 
-// bytes per LDS tile row: padded so that both the 16-byte fragment reads of 16 neighbouring rows and
-// the 4-row x 32-byte gathers of the transposing reads spread over the banks
-template <int DH, int THREADS = kAttnThreads> struct TileGeom {
-  static constexpr int STRIDE = DH * 2 + (DH == 128 ? 32 : 16);
-  static constexpr int BYTES = kBKV * STRIDE;
-  static constexpr int NCH = kBKV * (DH / 8) / THREADS;  // 16-byte chunks per thread and tile
-};
-
-// One 64-row tile of one head on its way global -> registers -> LDS (rows >= s read as zeros).
-template <int DH, int THREADS = kAttnThreads> struct TileRegs {
-  uint4 v[TileGeom<DH, THREADS>::NCH];
-  __device__ __forceinline__ void load(const bf16_t* __restrict__ src, size_t rs, int row0, int s) {
-#pragma unroll
-    for (int i = 0; i < TileGeom<DH, THREADS>::NCH; ++i) {
-      const int c = (threadIdx.x & (THREADS - 1)) + i * THREADS;
-      const int row = c / (DH / 8), ch = c % (DH / 8);
-      // branch-free: read a clamped (always valid) row, then blank it if it is past the end, so that
-      // the loads of a tile are issued back to back
-      const int rr = min(row0 + row, s - 1);
-      const uint4 t = *reinterpret_cast<const uint4*>(src + (size_t)rr * rs + ch * 8);
-      const bool ok = row0 + row < s;
-      v[i] = make_uint4(ok ? t.x : 0u, ok ? t.y : 0u, ok ? t.z : 0u, ok ? t.w : 0u);
-    }
-  }
-  __device__ __forceinline__ void store(char* lds) const {
-#pragma unroll
-    for (int i = 0; i < TileGeom<DH, THREADS>::NCH; ++i) {
-      const int c = (threadIdx.x & (THREADS - 1)) + i * THREADS;
-      const int row = c / (DH / 8), ch = c % (DH / 8);
-      *reinterpret_cast<uint4*>(lds + row * TileGeom<DH>::STRIDE + ch * 16) = v[i];
-    }
-  }
-};
-
-// This thread's chunk positions inside a tile, computed once: element offsets for the loads (rows rs
-// apart) and byte offsets for the LDS stores.  A tile that lies wholly inside the sequence is then
-// loaded with one add per chunk; the last, ragged tile takes TileRegs::load.
-template <int DH, int THREADS = kAttnThreads> struct TileMap {
-  uint32_t src[TileGeom<DH, THREADS>::NCH];
-  uint32_t dst[TileGeom<DH, THREADS>::NCH];
-  __device__ __forceinline__ void init(size_t rs) {
-#pragma unroll
-    for (int i = 0; i < TileGeom<DH, THREADS>::NCH; ++i) {
-      const int c = (threadIdx.x & (THREADS - 1)) + i * THREADS;
-      const int row = c / (DH / 8), ch = c % (DH / 8);
-      src[i] = (uint32_t)(row * rs + ch * 8);
-      dst[i] = (uint32_t)(row * TileGeom<DH>::STRIDE + ch * 16);
-    }
-  }
-  // rows row0 .. row0+63 of src (row pitch rs); s = number of valid rows
-  __device__ __forceinline__ void load(TileRegs<DH, THREADS>& t, const bf16_t* __restrict__ src_base, size_t rs, int row0,
-                                       int s) const {
-    if (row0 + kBKV <= s) {
-      const bf16_t* p = src_base + (size_t)row0 * rs;
-#pragma unroll
-      for (int i = 0; i < TileGeom<DH, THREADS>::NCH; ++i) t.v[i] = *reinterpret_cast<const uint4*>(p + src[i]);
-    } else {
-      t.load(src_base, rs, row0, s);
-    }
-  }
-  __device__ __forceinline__ void store(const TileRegs<DH, THREADS>& t, char* lds) const {
-#pragma unroll
-    for (int i = 0; i < TileGeom<DH, THREADS>::NCH; ++i) *reinterpret_cast<uint4*>(lds + dst[i]) = t.v[i];
-  }
-};
-
-// MFMA fragment with the tile row as the MFMA row: row = sub*32 + (lane & 31), eight consecutive dh of k16 step kk.
-template <int DH>
-__device__ __forceinline__ bf16x8_t frag_direct(const char* lds, int sub, int kk, int l31, int half) {
-  return *reinterpret_cast<const bf16x8_t*>(lds + (sub * 32 + l31) * TileGeom<DH>::STRIDE + (kk * 2 + half) * 16);
-}
-// MFMA fragment with dh as the MFMA row (d*32 + (lane & 31)) and tile rows as the contraction index, taken in
-// the order of the 32x32 accumulator rows that feed the other operand: rows 16*ks + 4*half + 0..3 and
-// 16*ks + 8 + 4*half + 0..3 of 32-row half `sub`.  ds_read_b64_tr_b16: within 16 lanes, lane i receives
-// element (i & 3) of the 8-byte rows addressed by lanes (i >> 2) + {0, 4, 8, 12}.
-template <int DH>
-__device__ __forceinline__ bf16x8_t frag_tr(const char* lds, int d, int sub, int ks, int lane) {
-  const int r = lane & 15, G = lane >> 4;
-  const int dh0 = d * 32 + 16 * (G & 1) + 4 * (r & 3);
-  const int row = sub * 32 + ks * 16 + 4 * (G >> 1) + (r >> 2);
-  const char* p = lds + row * TileGeom<DH>::STRIDE + dh0 * 2;
-  const s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4_t __attribute__((address_space(3)))*)(p));
-  const s16x4_t hi =
-      __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4_t __attribute__((address_space(3)))*)(p + 8 * TileGeom<DH>::STRIDE));
-  typedef __attribute__((__vector_size__(8 * sizeof(short)))) short s16x8_t;
-  s16x8_t v = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-  return *reinterpret_cast<bf16x8_t*>(&v);
-}
 // Registers 8*ks .. 8*ks+7 of a 32x32 accumulator as a bf16 B-operand fragment.
 __device__ __forceinline__ bf16x8_t pack_frag(const f32x16_t& a, int ks) {
   uint4 t = make_uint4(pack_bf16x2(a[ks * 8 + 0], a[ks * 8 + 1]), pack_bf16x2(a[ks * 8 + 2], a[ks * 8 + 3]),
@@ -564,8 +473,8 @@ template <int KT> struct FragDirect {
     asm volatile("" : "+v"(f.base[0]), "+v"(f.base[1]));
     return f;
   }
-  __device__ __forceinline__ bf16x8_t get(int sub, int kk) const {
-    return *(lds_frag_t*)(uintptr_t)(base[kk & 1] + (kk >> 1) * (KT * 64) + sub * 2048);
+  __device__ __forceinline__ bf16x8_t get(int sub, int kk, int tile = 0) const {
+    return *(lds_frag_t*)(uintptr_t)(base[kk & 1] + (kk >> 1) * (KT * 64) + sub * 2048 + tile);
   }
 };
 // fragment with dh as the MFMA row (d * 32 + (lane & 31)) and tile rows as the contraction index, in the order of the 32x32
@@ -584,8 +493,8 @@ template <int KT> struct FragTr {
     asm volatile("" : "+v"(f.lo), "+v"(f.hi));
     return f;
   }
-  __device__ __forceinline__ bf16x8_t get(int d, int sub, int ks) const {
-    const uint32_t o = d * (KT * 64) + sub * 2048 + ks * 1024;
+  __device__ __forceinline__ bf16x8_t get(int d, int sub, int ks, int tile = 0) const {
+    const uint32_t o = d * (KT * 64) + sub * 2048 + ks * 1024 + tile;
     const s16x4_t a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_tr_t*)(uintptr_t)(lo + o));
     const s16x4_t b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_tr_t*)(uintptr_t)(hi + o));
     typedef __attribute__((__vector_size__(8 * sizeof(short)))) short s16x8_t;
@@ -1030,393 +939,238 @@ attn_bwd_dq_tiles(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ ctx
   if (valid) store_cols<NDT>(dqkv + (size_t)my_q * rs + (size_t)j * 3 * hp + (size_t)e * DH, acc, scale, half);
 }
 
-constexpr int kMaskLdsStride = 68;   // bytes per key row of the staged mask tile ([key][query], padded)
-
-// A 64 x 64 tile of the mask on its way to LDS as [key][query], so that a lane reads four queries of its key at once.  Blocks
-// of 4 queries x 4 keys, one or two per thread: four words of four keys, turned by byte permutes into four words of
-// four queries (byte loads and stores, one per element: 98 us for the kernel at 4 samples x 16 heads x 512, now 35).
-template <int THREADS> struct MaskTile {
-  static constexpr int NB = 256 / THREADS;   // blocks per thread
-  uint32_t v[NB][4];
+// The hidden flags of a tile of KEYS keys x QT queries on their way to LDS as one bit each, [key][query]: a lane reads the bits of
+// its key at once.  A thread turns 8 queries x 4 keys: eight words of four keys, whose nonzero bytes' flags are shifted
+// into one byte per key.
+template <int THREADS, int KEYS, int QT> struct MaskBits {
+  static constexpr int kRow = QT / 8, kBytes = KEYS * kRow, NB = (KEYS / 4) * kRow;   // NB: blocks, at most one per thread
+  static_assert(NB <= THREADS);
+  uint32_t v[8];
   __device__ __forceinline__ void load(const uint8_t* __restrict__ mask_j, int q0, int key0, int s, bool aligned, int tid) {
+    if (tid >= NB) return;
+    const int key = key0 + 4 * (tid % (KEYS / 4)), q = q0 + 8 * (tid / (KEYS / 4));
 #pragma unroll
-    for (int i = 0; i < NB; ++i) {
-      const int blk = tid + i * THREADS, key = key0 + 4 * (blk & 15), q = q0 + 4 * (blk >> 4);
-#pragma unroll
-      for (int r = 0; r < 4; ++r) v[i][r] = mask_word(mask_j + (size_t)min(q + r, s - 1) * s, key, s, aligned);
-    }
+    for (int r = 0; r < 8; ++r) v[r] = mask_word(mask_j + (size_t)min(q + r, s - 1) * s, key, s, aligned);
   }
-  __device__ __forceinline__ void store(uint8_t* lds, int tid) const {
+  __device__ __forceinline__ void store(char* lds, int tid) const {
+    if (tid >= NB) return;
+    uint32_t bits = 0;
 #pragma unroll
-    for (int i = 0; i < NB; ++i) {
-      const int blk = tid + i * THREADS, key = 4 * (blk & 15), ql = 4 * (blk >> 4);
-      const uint32_t a = __builtin_amdgcn_perm(v[i][1], v[i][0], 0x05010400u), b = __builtin_amdgcn_perm(v[i][1], v[i][0], 0x07030602u);
-      const uint32_t c = __builtin_amdgcn_perm(v[i][3], v[i][2], 0x05010400u), d = __builtin_amdgcn_perm(v[i][3], v[i][2], 0x07030602u);
-      const uint32_t t[4] = {__builtin_amdgcn_perm(c, a, 0x05040100u), __builtin_amdgcn_perm(c, a, 0x07060302u),
-                             __builtin_amdgcn_perm(d, b, 0x05040100u), __builtin_amdgcn_perm(d, b, 0x07060302u)};
+    for (int r = 0; r < 8; ++r) bits = (bits >> 1) | ((((v[r] & 0x7f7f7f7fu) + 0x7f7f7f7fu) | v[r]) & 0x80808080u);
+    const int key = 4 * (tid % (KEYS / 4)), q8 = tid / (KEYS / 4);
 #pragma unroll
-      for (int r = 0; r < 4; ++r) *reinterpret_cast<uint32_t*>(lds + (key + r) * kMaskLdsStride + ql) = t[r];
-    }
+    for (int k = 0; k < 4; ++k) lds[(key + k) * kRow + q8] = (char)(bits >> (8 * k));
   }
 };
 
-// dK/dV: a workgroup owns 64 keys; wave w of a pair owns keys 32 w .. 32 w + 31 and computes both results.  NP = 1: one
-// pair of waves walks all 64-query tiles.  NP = 2: two pairs; pair p walks every second tile (first + p, first + p + 2,
-// ...) with tiles of its own in LDS, and at the end pair 1 hands its sums to pair 0 through LDS, added in that fixed order.
-// The workgroup that owns the first keys of a causal head walks all query tiles and the launch lasts at least as long as
-// it does: two pairs halve that path, at the price of one barrier domain per CU instead of two independent ones.  The
-// launch code takes NP = 2 when all workgroups of the one-pair form would be resident at once (the longest one then sets
-// the time: GPT-3-shaped shard, 12 heads: backward 0.213 -> 0.152 ms) and NP = 1 otherwise (1T-shaped shard, 20 heads of
-// 160: 0.331 against 0.343 ms).
-// For the calls that kDkvSplit, below, leaves.
-template <int DH, bool CAUSAL> struct DkvLds {
-  static constexpr int kPair = 2 * TileGeom<DH>::BYTES + 2 * kBKV * (int)sizeof(float) + (CAUSAL ? 0 : kBQ * kMaskLdsStride);
-  static constexpr int kSum = 2 * (DH / 32) * 16 * 64 * (int)sizeof(float);   // dK and dV of one wave (both forms: of 32 keys)
-  static constexpr int kBytes2 = 2 * kPair > 2 * kSum ? 2 * kPair : 2 * kSum;
+// dK, dV of 32 KW keys; Q and dO stream through two LDS stages of QT queries, requested one tile ahead, with one barrier per tile,
+// and are read twice each: as rows for S = Q K^T and dP = dO V^T, transposed for dK and dV.  The queries' lse and delta (and the
+// general mask) travel in registers and are written to the next stage behind the arithmetic.
+// SPLIT: KW waves compute S, dP and dK and KW waves S and dV: S twice is a quarter more matrix work, but both results of heads of
+// 160 do not fit the 256 registers that leave two waves on a SIMD (50 to 90 spilled), and short walks are cut once more.
+// What bounds it: every product reads its own fragment from LDS, which at full rate takes as long as the products, and
+// the two waves of a SIMD wait on each other's phases: 29 % of the matrix rate at 64 heads of 128.
+// us for this kernel before (tiles through registers, two barriers per tile, one wave per SIMD where both results were in
+// one wave) and now, causal, s = 2048: 4 x 16 heads of 128 297 -> 192, 12 heads 88 -> 65, 20 heads of 160 201 -> 113, 20 of 96 90 -> 49,
+// 32 of 64 90 -> 57, 128 of 32 168 -> 122; 4 x 16 heads of 64 x 512 under a general mask 35 -> 22.
+template <int DH, bool CAUSAL, int KW, int NP, int QT, bool SPLIT> struct DkvGeom {
+  static constexpr int kWaves = SPLIT ? 2 * KW : KW, kThreads = 64 * kWaves;   // of a group
+  static constexpr int kTile = QT * DH * 2, kStats = 2 * kTile, kMask = kStats + 2 * QT * (int)sizeof(float);
+  static constexpr int stage_bytes(bool masked) {   // kept a multiple of 128 bytes
+    return ((masked ? kMask + MaskBits<kThreads, 32 * KW, QT>::kBytes : kMask) + 127) / 128 * 128;
+  }
+  static constexpr int kSums = NP > 1 ? KW * 2 * (DH / 2) * 64 * (int)sizeof(float) : 0;
+  static constexpr int lds_bytes(bool masked) { return NP * 2 * stage_bytes(masked) > kSums ? NP * 2 * stage_bytes(masked) : kSums; }
 };
-template <int DH, bool CAUSAL, int NP>
-__global__ void __launch_bounds__(NP * kAttnThreads)
-attn_bwd_dkv_both_mfma(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ dctx, const float* __restrict__ lse,
-                  const float* __restrict__ delta, bf16_t* __restrict__ dqkv, int s, int b, int heads,
-                  const uint8_t* __restrict__ mask) {
-  constexpr int NKK = DH / 16, NDT = DH / 32;
-  extern __shared__ __attribute__((aligned(16))) char smem_all[];
-  const int pair = NP == 2 ? threadIdx.x >> 7 : 0, tid = threadIdx.x & (kAttnThreads - 1);
-  char* smem = smem_all + pair * DkvLds<DH, CAUSAL>::kPair;
-  char* q_lds = smem;                           // Q  [query][dh]: S = Q K^T directly, dK^T = Q^T dS through tr reads
-  char* do_lds = smem + TileGeom<DH>::BYTES;    // dO [query][dh]: dP = dO V^T directly, dV^T = dO^T P through tr reads
-  float* lse_lds = reinterpret_cast<float*>(smem + 2 * TileGeom<DH>::BYTES);  // lse * log2(e), +inf past the end
-  float* delta_lds = lse_lds + kBKV;
-  uint8_t* mask_lds = reinterpret_cast<uint8_t*>(delta_lds + kBKV);   // general mask only: [64 keys][68]
+template <int DH, bool CAUSAL, int KW, int NP, int QT, bool SPLIT>
+__global__ void __launch_bounds__(64 * KW * (SPLIT ? 2 : 1) * NP, 2)
+attn_bwd_dkv_tiles(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ dctx, const float* __restrict__ lse,
+                   const float* __restrict__ delta, bf16_t* __restrict__ dqkv, int s, int b, int heads,
+                   const uint8_t* __restrict__ mask) {
+  using Geom = DkvGeom<DH, CAUSAL, KW, NP, QT, SPLIT>;
+  constexpr int NKK = DH / 16, NDT = DH / 32, kKeys = 32 * KW, SUBS = QT / 32, GW = Geom::kWaves, kTile = Geom::kTile;
+  constexpr int NR = SPLIT ? 1 : 2;   // results of a wave
+  extern __shared__ __attribute__((aligned(1024))) char smem_all[];
   const bool use_mask = !CAUSAL && mask != nullptr;
-  const float fill = kMaskFill * sqrtf((float)DH);
+  const uint32_t stage_bytes = Geom::stage_bytes(!CAUSAL && use_mask);
+  const int wave_all = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), grp = NP == 1 ? 0 : wave_all / GW, wave = wave_all % GW;
+  const int kw = wave % KW, tid = threadIdx.x & (Geom::kThreads - 1);
+  static_assert((Geom::kThreads & (Geom::kThreads - 1)) == 0 && QT <= Geom::kThreads);
+  char* smem = smem_all + grp * 2 * stage_bytes;
+  const uint32_t lds0 = attn_lds_offset(smem);
 
-  int kblk, e, j;  // the first key blocks see the most queries and start first
-  if (!attn_map(blockIdx.x, (s + kBQ - 1) / kBQ, heads, b, &kblk, &e, &j)) return;
-  const int wave = (threadIdx.x >> 6) & 1, lane = threadIdx.x & 63, half = lane >> 5, l31 = lane & 31;
-  const int hp = heads * DH;
-  const size_t rs = (size_t)b * 3 * hp;
-  const bf16_t* base = qkv + (size_t)j * 3 * hp + (size_t)e * DH;
-  const bf16_t* dobase = dctx + (size_t)j * hp + (size_t)e * DH;
-  const size_t dors = (size_t)b * hp;
-  const int key_first = kblk * kBQ + wave * 32;
-  const int my_key = key_first + l31;
-  const bool valid = my_key < s;
-  const float scale = rsqrtf((float)DH), c2 = scale * 1.4426950408889634f;
-  const float* lse_h = lse + ((size_t)j * heads + e) * s;
-  const float* delta_h = delta + ((size_t)j * heads + e) * s;
-
-  bf16x8_t kf[NKK], vf[NKK];
-#pragma unroll
-  for (int kk = 0; kk < NKK; ++kk) {
-    kf[kk] = frag_global(base + (size_t)min(my_key, s - 1) * rs + hp, valid, kk, half);
-    vf[kk] = frag_global(base + (size_t)min(my_key, s - 1) * rs + 2 * hp, valid, kk, half);
-  }
-  f32x16_t dk[NDT], dv[NDT];
-#pragma unroll
-  for (int d = 0; d < NDT; ++d) {
-    dk[d] = zero16();
-    dv[d] = zero16();
-  }
-  const int nq_tiles = (s + kBKV - 1) / kBKV;
-  // the next Q and dO tiles (and their lse, delta) travel in registers while this step's arithmetic runs
-  // (not for the largest head size: the tiles would not fit the register file next to dK and dV)
-  constexpr bool kPrefetch = DH <= 128;
-  TileMap<kPrefetch ? DH : 32> qmap, domap;
-  TileRegs<kPrefetch ? DH : 32> qr, dor;
-  float lse_r = 0.f, delta_r = 0.f;
-  MaskTile<kAttnThreads> mt;
-  const uint8_t* mask_j = use_mask ? mask + (size_t)j * s * s : nullptr;
-  const bool aligned = (s & 3) == 0;
-  auto fetch = [&](int q0) {
-    if constexpr (kPrefetch) {
-      if (use_mask) mt.load(mask_j, q0, kblk * kBQ, s, aligned, tid);
-      qmap.load(qr, base, rs, q0, s);
-      domap.load(dor, dobase, dors, q0, s);
-      if (tid < kBKV) {
-        const int q = q0 + tid;
-        lse_r = q < s ? lse_h[q] * 1.4426950408889634f : INFINITY;
-        delta_r = q < s ? delta_h[q] : 0.f;
-      }
-    }
-  };
-  const int qt_first = CAUSAL ? (kblk * kBQ) / kBKV : 0;
-  if constexpr (kPrefetch) {
-    qmap.init(rs);
-    domap.init(dors);
-    if (qt_first + pair < nq_tiles) fetch((qt_first + pair) * kBKV);
-  }
-  // both pairs take the same number of steps (the barriers are the workgroup's); a pair without a tile idles
-  for (int qt0 = qt_first; qt0 < nq_tiles; qt0 += NP) {
-    const int qt = qt0 + pair;
-    const bool have = qt < nq_tiles;
-    const int q0 = qt * kBKV;
-    __syncthreads();
-    if (have) {
-      if constexpr (kPrefetch) {
-        qmap.store(qr, q_lds);
-        domap.store(dor, do_lds);
-        if (tid < kBKV) {
-          lse_lds[tid] = lse_r;
-          delta_lds[tid] = delta_r;
-        }
-      } else {
-        TileRegs<DH> t;
-        t.load(base, rs, q0, s);
-        t.store(q_lds);
-        t.load(dobase, dors, q0, s);
-        t.store(do_lds);
-        if (tid < kBKV) {
-          const int q = q0 + tid;
-          lse_lds[tid] = q < s ? lse_h[q] * 1.4426950408889634f : INFINITY;
-          delta_lds[tid] = q < s ? delta_h[q] : 0.f;
-        }
-      }
-      if (use_mask) {
-        if constexpr (!kPrefetch) mt.load(mask_j, q0, kblk * kBQ, s, aligned, tid);
-        mt.store(mask_lds, tid);
-      }
-    }
-    __syncthreads();
-    if (!have) continue;
-    if (qt + NP < nq_tiles) fetch(q0 + NP * kBKV);
-    if (CAUSAL && q0 + kBKV - 1 < key_first) continue;  // every query of the tile precedes this wave's keys
-    const bool diag = CAUSAL && q0 < key_first + 32;    // some query of the tile precedes some key of this wave
-    bf16x8_t pf[2][2], dsf[2][2];
-#pragma unroll
-    for (int sub = 0; sub < 2; ++sub) {
-      f32x16_t sacc = zero16(), dp = zero16();
-#pragma unroll
-      for (int kk = 0; kk < NKK; ++kk) {
-        sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_direct<DH>(q_lds, sub, kk, l31, half), kf[kk], sacc, 0, 0, 0);
-        dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_direct<DH>(do_lds, sub, kk, l31, half), vf[kk], dp, 0, 0, 0);
-      }
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const int ql = sub * 32 + 8 * g + 4 * half;  // local index of the first of 4 consecutive queries
-        const float4 L4 = *reinterpret_cast<const float4*>(lse_lds + ql);
-        const float4 D4 = *reinterpret_cast<const float4*>(delta_lds + ql);
-        const float Ls[4] = {L4.x, L4.y, L4.z, L4.w}, Ds[4] = {D4.x, D4.y, D4.z, D4.w};
-        const uint32_t mw = use_mask ? *reinterpret_cast<const uint32_t*>(mask_lds + (wave * 32 + l31) * kMaskLdsStride + ql) : 0u;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int r = 4 * g + i;
-          const bool hidden = (mw >> (8 * i)) & 0xffu;
-          float p = __builtin_amdgcn_exp2f((hidden ? fill : sacc[r]) * c2 - Ls[i]);   // lse = +inf past the end gives 0
-          if (diag) p = my_key > q0 + ql + i ? 0.f : p;
-          sacc[r] = p;
-          dp[r] = hidden ? 0.f : p * (dp[r] - Ds[i]);
-        }
-      }
-      pf[sub][0] = pack_frag(sacc, 0);
-      pf[sub][1] = pack_frag(sacc, 1);
-      dsf[sub][0] = pack_frag(dp, 0);
-      dsf[sub][1] = pack_frag(dp, 1);
-    }
-#pragma unroll
-    for (int d = 0; d < NDT; ++d)
-#pragma unroll
-      for (int sub = 0; sub < 2; ++sub)
-#pragma unroll
-        for (int ks = 0; ks < 2; ++ks) {
-          dv[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_tr<DH>(do_lds, d, sub, ks, lane), pf[sub][ks], dv[d], 0, 0, 0);
-          dk[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_tr<DH>(q_lds, d, sub, ks, lane), dsf[sub][ks], dk[d], 0, 0, 0);
-        }
-  }
-  if constexpr (NP == 2) {
-    // pair 1's sums join pair 0's: register r of lane l of wave w at sum[w][r][l]
-    __syncthreads();   // every wave is done with the tiles
-    float* sum = reinterpret_cast<float*>(smem_all) + wave * (2 * NDT * 16 * 64) + lane;
-    if (pair == 1) {
-#pragma unroll
-      for (int d = 0; d < NDT; ++d)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          sum[(d * 16 + r) * 64] = dk[d][r];
-          sum[((NDT + d) * 16 + r) * 64] = dv[d][r];
-        }
-    }
-    __syncthreads();
-    if (pair == 1) return;
-#pragma unroll
-    for (int d = 0; d < NDT; ++d)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        dk[d][r] += sum[(d * 16 + r) * 64];
-        dv[d][r] += sum[((NDT + d) * 16 + r) * 64];
-      }
-  }
-  if (valid) {
-    bf16_t* out = dqkv + (size_t)my_key * rs + (size_t)j * 3 * hp + (size_t)e * DH;
-    store_cols<NDT>(out + hp, dk, scale, half);
-    store_cols<NDT>(out + 2 * hp, dv, 1.f, half);
-  }
-}
-
-// The same, split by result: a group of four waves, of which two (32 keys each) compute S, dP and dK and two S and dV.  S
-// twice is a quarter more matrix work, but a wave then holds one result and fits 256 registers: two waves per SIMD cover
-// each other's waits where both results in one wave leave one (half of its time went to waiting for LDS and barriers).
-// Which waves take which result alternates with the workgroup, so that every SIMD gets both.  NP = 2: two groups of four
-// waves, as above.  Taken where it measured faster; us for the backward with both results in a wave and split:
-//   dh 128 causal   4 samples x 16 heads x 2048 545, 502; 20 heads x 2048 233, 207; 12 x 2048 143, 142; 8 x 1024 64.6, 62.9
-//   dh 128 no mask  983, 1033; 484, 462; 295, 299; 73.8, 76.4 (general mask alike): the form's 256 registers spill there
-//   dh 96 causal    433, 407; 188, 169; 113.6, 113.8; 51.9, 50.7; no mask 834, 831; 402, 372; 249, 243; 63.0, 63.2
-// Heads of 64 with a mask (4 x 16 x 512: 34.7, 36.0 for this kernel alone) and of 32 (128 heads x 2048: 191, 259) are faster with
-// both results in a wave.
-template <int DH, bool CAUSAL> constexpr bool kDkvSplit = DH == 96 || (DH == 128 && CAUSAL);
-constexpr int kDkvThreads = 2 * kAttnThreads;
-template <int DH, bool CAUSAL, int NP>
-__global__ void __launch_bounds__(NP * kDkvThreads, 2)
-attn_bwd_dkv_mfma(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ dctx, const float* __restrict__ lse,
-                  const float* __restrict__ delta, bf16_t* __restrict__ dqkv, int s, int b, int heads,
-                  const uint8_t* __restrict__ mask) {
-  constexpr int NKK = DH / 16, NDT = DH / 32;
-  extern __shared__ __attribute__((aligned(16))) char smem_all[];
-  const int pair = NP == 2 ? threadIdx.x >> 8 : 0, tid = threadIdx.x & (kDkvThreads - 1);
-  char* smem = smem_all + pair * DkvLds<DH, CAUSAL>::kPair;
-  char* q_lds = smem;                           // Q  [query][dh]: S = Q K^T directly, dK^T = Q^T dS through tr reads
-  char* do_lds = smem + TileGeom<DH>::BYTES;    // dO [query][dh]: dP = dO V^T directly, dV^T = dO^T P through tr reads
-  float* lse_lds = reinterpret_cast<float*>(smem + 2 * TileGeom<DH>::BYTES);  // lse * log2(e), +inf past the end
-  float* delta_lds = lse_lds + kBKV;
-  uint8_t* mask_lds = reinterpret_cast<uint8_t*>(delta_lds + kBKV);   // general mask only: [64 keys][68]
-  const bool use_mask = !CAUSAL && mask != nullptr;
-  const float fill = kMaskFill * sqrtf((float)DH);
-
-  int kblk, e, j;  // the first key blocks see the most queries and start first
-  if (!attn_map(blockIdx.x, (s + kBQ - 1) / kBQ, heads, b, &kblk, &e, &j)) return;
-  const int wave4 = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) & 3, wave = wave4 & 1;
-  const bool want_dk = ((wave4 >> 1) ^ (blockIdx.x >> 8)) & 1;
+  const int nkb = (s + kKeys - 1) / kKeys;
+  int kblk, e, j;   // the first key blocks see the most queries and start first
+  if (!attn_map_tiles<CAUSAL>(blockIdx.x, nkb, heads, b, &kblk, &e, &j)) return;
+  // which half of a group takes dK alternates, so that every SIMD gets both (KW = 4: it does anyway)
+  const bool want_dk = !SPLIT || ((wave / KW) ^ (KW == 4 ? 0 : NP == 2 ? grp : (int)(blockIdx.x >> 8))) & 1;
   const int lane = threadIdx.x & 63, half = lane >> 5, l31 = lane & 31;
   const int hp = heads * DH;
-  const size_t rs = (size_t)b * 3 * hp;
+  const size_t rs = (size_t)b * 3 * hp, dors = (size_t)b * hp;
   const bf16_t* base = qkv + (size_t)j * 3 * hp + (size_t)e * DH;
   const bf16_t* dobase = dctx + (size_t)j * hp + (size_t)e * DH;
-  const size_t dors = (size_t)b * hp;
-  const int key_first = kblk * kBQ + wave * 32;
+  const int key_first = kblk * kKeys + kw * 32;
   const int my_key = key_first + l31;
   const bool valid = my_key < s;
   const float scale = rsqrtf((float)DH), c2 = scale * 1.4426950408889634f;
+  const float fill = kMaskFill * sqrtf((float)DH);
   const float* lse_h = lse + ((size_t)j * heads + e) * s;
   const float* delta_h = delta + ((size_t)j * heads + e) * s;
+  const uint8_t* mask_j = mask + (size_t)j * s * s;   // (read if use_mask)
+  const bool aligned = (s & 3) == 0;
 
+  // every wave loads a share of both tiles, or one half of the waves Q and the other dO
+  constexpr int kSlices = QT / 16, DW = GW > kSlices ? kSlices : GW;
+  static_assert(GW <= 2 * kSlices);
+  TileDma<DH, DW, QT> dma_q, dma_do;
+  dma_q.init(rs, lane);
+  dma_do.init(dors, lane);
+  auto request = [&](int qt, uint32_t at) {
+    if (GW == DW || wave < DW) dma_q.issue(base, qt * QT, s, lds0 + at, wave % DW);
+    if (GW == DW || wave >= DW) dma_do.issue(dobase, qt * QT, s, lds0 + at + kTile, wave % DW);
+  };
+  float lse_r = 0.f, delta_r = 0.f;
+  MaskBits<Geom::kThreads, kKeys, QT> mb;
+  auto fetch = [&](int qt) {
+    const int q = qt * QT + tid;
+    if (tid < QT) {
+      lse_r = q < s ? lse_h[q] * 1.4426950408889634f : INFINITY;   // p is zero past the end
+      delta_r = q < s ? delta_h[q] : 0.f;
+    }
+    if (use_mask) mb.load(mask_j, qt * QT, kblk * kKeys, s, aligned, tid);
+  };
+  auto put = [&](uint32_t at) {
+    if (tid < QT) {
+      float* st = reinterpret_cast<float*>(smem + at + Geom::kStats);
+      st[tid] = lse_r;
+      st[QT + tid] = delta_r;
+    }
+    if (use_mask) mb.store(smem + at + Geom::kMask, tid);
+  };
+  const int nqt = (s + QT - 1) / QT, qt_first = CAUSAL ? kblk * kKeys / QT : 0;
+  if (qt_first + grp < nqt) {
+    request(qt_first + grp, 0);
+    fetch(qt_first + grp);
+    put(0);
+  }
   bf16x8_t kf[NKK], vf[NKK];
 #pragma unroll
   for (int kk = 0; kk < NKK; ++kk) {
     kf[kk] = frag_global(base + (size_t)min(my_key, s - 1) * rs + hp, valid, kk, half);
     vf[kk] = frag_global(base + (size_t)min(my_key, s - 1) * rs + 2 * hp, valid, kk, half);
   }
-  f32x16_t acc[NDT];   // dK or dV
+  FragDirect<QT> f0;
+  FragTr<QT> t0;
+  f0.init(lds0, l31, half);
+  t0.init(lds0, lane);
+  f32x16_t acc[NR][NDT];   // dV and dK, or one of them
 #pragma unroll
-  for (int d = 0; d < NDT; ++d) acc[d] = zero16();
-  const int nq_tiles = (s + kBKV - 1) / kBKV;
-  // the next Q and dO tiles (and their lse, delta, mask) travel in registers while this step's arithmetic runs
-  TileMap<DH, kDkvThreads> qmap, domap;
-  TileRegs<DH, kDkvThreads> qr, dor;
-  float lse_r = 0.f, delta_r = 0.f;
-  MaskTile<kDkvThreads> mt;
-  const uint8_t* mask_j = use_mask ? mask + (size_t)j * s * s : nullptr;
-  const bool aligned = (s & 3) == 0;
-  auto fetch = [&](int q0) {
-    if (use_mask) mt.load(mask_j, q0, kblk * kBQ, s, aligned, tid);
-    qmap.load(qr, base, rs, q0, s);
-    domap.load(dor, dobase, dors, q0, s);
-    if (tid < kBKV) {
-      const int q = q0 + tid;
-      lse_r = q < s ? lse_h[q] * 1.4426950408889634f : INFINITY;
-      delta_r = q < s ? delta_h[q] : 0.f;
+  for (int r = 0; r < NR; ++r)
+#pragma unroll
+    for (int d = 0; d < NDT; ++d) acc[r][d] = zero16();
+
+  uint32_t stage = 0;
+  // all groups take the same number of steps (the barriers are the workgroup's); a group without a tile idles
+  for (int qt0 = qt_first; qt0 < nqt; qt0 += NP, stage ^= stage_bytes) {
+    const int qt = qt0 + grp, q0 = qt * QT;
+    attn_tiles_ready();
+    const bool more = qt + NP < nqt;
+    if (more) {
+      fetch(qt + NP);
+      request(qt + NP, stage ^ stage_bytes);
     }
-  };
-  const int qt_first = CAUSAL ? (kblk * kBQ) / kBKV : 0;
-  qmap.init(rs);
-  domap.init(dors);
-  if (qt_first + pair < nq_tiles) fetch((qt_first + pair) * kBKV);
-  // both groups take the same number of steps (the barriers are the workgroup's); a group without a tile idles
-  for (int qt0 = qt_first; qt0 < nq_tiles; qt0 += NP) {
-    const int qt = qt0 + pair;
-    const bool have = qt < nq_tiles;
-    const int q0 = qt * kBKV;
-    __syncthreads();
-    if (have) {
-      qmap.store(qr, q_lds);
-      domap.store(dor, do_lds);
-      if (tid < kBKV) {
-        lse_lds[tid] = lse_r;
-        delta_lds[tid] = delta_r;
-      }
-      if (use_mask) mt.store(mask_lds, tid);
-    }
-    __syncthreads();
-    if (!have) continue;
-    if (qt + NP < nq_tiles) fetch(q0 + NP * kBKV);
-    if (CAUSAL && q0 + kBKV - 1 < key_first) continue;  // every query of the tile precedes this wave's keys
-    const bool diag = CAUSAL && q0 < key_first + 32;    // some query of the tile precedes some key of this wave
-    bf16x8_t wf[2][2];   // P or dS
+    // (skipped if every query of the tile precedes this wave's keys)
+    if (qt < nqt && !(CAUSAL && q0 + QT - 1 < key_first)) {
+      const FragDirect<QT> fs = f0.at(stage);
+      const FragTr<QT> ts = t0.at(stage);
+      const char* stats = smem + stage + Geom::kStats;
+      const bool diag = CAUSAL && q0 < key_first + 31;   // some query of the tile precedes some key of this wave
 #pragma unroll
-    for (int sub = 0; sub < 2; ++sub) {
-      f32x16_t sacc = zero16(), dp = zero16();
+      for (int sub = 0; sub < SUBS; ++sub) {
+        f32x16_t sacc = zero16(), dp = zero16();
+        if (!SPLIT || want_dk) {
 #pragma unroll
-      for (int kk = 0; kk < NKK; ++kk)
-        sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_direct<DH>(q_lds, sub, kk, l31, half), kf[kk], sacc, 0, 0, 0);
-      if (want_dk) {
+          for (int kk = 0; kk < NKK; ++kk) {
+            sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fs.get(sub, kk), kf[kk], sacc, 0, 0, 0);
+            dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fs.get(sub, kk, kTile), vf[kk], dp, 0, 0, 0);
+          }
+          sched_reads_ahead<2 * NKK, 1>();
+        } else {
 #pragma unroll
-        for (int kk = 0; kk < NKK; ++kk)
-          dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_direct<DH>(do_lds, sub, kk, l31, half), vf[kk], dp, 0, 0, 0);
-      }
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const int ql = sub * 32 + 8 * g + 4 * half;  // local index of the first of 4 consecutive queries
-        const float4 L4 = *reinterpret_cast<const float4*>(lse_lds + ql);
-        const float Ls[4] = {L4.x, L4.y, L4.z, L4.w};
-        const uint32_t mw = use_mask ? *reinterpret_cast<const uint32_t*>(mask_lds + (wave * 32 + l31) * kMaskLdsStride + ql) : 0u;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int r = 4 * g + i;
-          const bool hidden = (mw >> (8 * i)) & 0xffu;
-          const float p = __builtin_amdgcn_exp2f((hidden ? fill : sacc[r]) * c2 - Ls[i]);   // lse = +inf past the end gives 0
-          sacc[r] = diag && my_key > q0 + ql + i ? 0.f : p;
+          for (int kk = 0; kk < NKK; ++kk) sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fs.get(sub, kk), kf[kk], sacc, 0, 0, 0);
+          sched_reads_ahead<NKK, 1>();
         }
-        if (want_dk) {
-          const float4 D4 = *reinterpret_cast<const float4*>(delta_lds + ql);
-          const float Ds[4] = {D4.x, D4.y, D4.z, D4.w};
+        __builtin_amdgcn_sched_barrier(0);
+        uint32_t mw = 0;   // bit 8 g + i: query 8 g + 4 half + i of this half of the tile is hidden from my_key
+        if (use_mask) mw = *reinterpret_cast<const uint32_t*>(smem + stage + Geom::kMask + (kw * 32 + l31) * (QT / 8) + sub * 4) >> (4 * half);
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          const int ql = sub * 32 + 8 * g + 4 * half;   // local index of the first of 4 consecutive queries
+          const f32x4_t Ls = *reinterpret_cast<const f32x4_t*>(stats + ql * 4), Ds = *reinterpret_cast<const f32x4_t*>(stats + (QT + ql) * 4);
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
-            const bool hidden = (mw >> (8 * i)) & 0xffu;
-            sacc[4 * g + i] = hidden ? 0.f : sacc[4 * g + i] * (dp[4 * g + i] - Ds[i]);
+            const int r = 4 * g + i;
+            const bool hidden = !CAUSAL && (mw >> (8 * g + i)) & 1u;
+            float p = __builtin_amdgcn_exp2f((hidden ? fill : sacc[r]) * c2 - Ls[i]);
+            if (CAUSAL && diag) p = my_key > q0 + ql + i ? 0.f : p;
+            sacc[r] = p;
+            dp[r] = hidden ? 0.f : p * (dp[r] - Ds[i]);
           }
         }
+        const bf16x8_t pf[2] = {pack_frag(sacc, 0), pack_frag(sacc, 1)}, dsf[2] = {pack_frag(dp, 0), pack_frag(dp, 1)};
+        if constexpr (SPLIT) {
+          // Q^T or dO^T; P or dS
+          const uint32_t tile = want_dk ? 0 : kTile;
+          const FragTr<QT> tw{ts.lo + tile, ts.hi + tile};
+#pragma unroll
+          for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+            for (int d = 0; d < NDT; ++d) acc[0][d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(tw.get(d, sub, ks), want_dk ? dsf[ks] : pf[ks], acc[0][d], 0, 0, 0);
+          sched_reads_ahead<2 * NDT, 2>();
+        } else {
+#pragma unroll
+          for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+            for (int d = 0; d < NDT; ++d) {
+              acc[0][d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ts.get(d, sub, ks, kTile), pf[ks], acc[0][d], 0, 0, 0);
+              acc[1][d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ts.get(d, sub, ks), dsf[ks], acc[1][d], 0, 0, 0);
+            }
+          sched_reads_ahead<4 * NDT, 2>();
+        }
+        __builtin_amdgcn_sched_barrier(0);
       }
-      wf[sub][0] = pack_frag(sacc, 0);
-      wf[sub][1] = pack_frag(sacc, 1);
     }
-    const char* tr = want_dk ? q_lds : do_lds;
-#pragma unroll
-    for (int d = 0; d < NDT; ++d)
-#pragma unroll
-      for (int sub = 0; sub < 2; ++sub)
-#pragma unroll
-        for (int ks = 0; ks < 2; ++ks)
-          acc[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_tr<DH>(tr, d, sub, ks, lane), wf[sub][ks], acc[d], 0, 0, 0);
+    if (more) put(stage ^ stage_bytes);
   }
-  if constexpr (NP == 2) {
-    // group 1's sums join group 0's: register r of lane l of wave w at sum[w][r][l]
+  if constexpr (NP > 1) {
+    // the second group's sums join the first's: register r of lane l of the wave with keys kw (and one result) at sum[..][r][l]
+    float* sum = reinterpret_cast<float*>(smem_all) + (SPLIT ? (want_dk ? KW : 0) + kw : 2 * kw) * (NDT * 16 * 64) + lane;
     __syncthreads();   // every wave is done with the tiles
-    float* sum = reinterpret_cast<float*>(smem_all) + wave4 * (NDT * 16 * 64) + lane;
-    if (pair == 1) {
+    if (grp == 1) {
+#pragma unroll
+      for (int x = 0; x < NR; ++x)
+#pragma unroll
+        for (int d = 0; d < NDT; ++d)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) sum[((x * NDT + d) * 16 + r) * 64] = acc[x][d][r];
+    }
+    __syncthreads();
+    if (grp == 1) return;
+#pragma unroll
+    for (int x = 0; x < NR; ++x)
 #pragma unroll
       for (int d = 0; d < NDT; ++d)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) sum[(d * 16 + r) * 64] = acc[d][r];
-    }
-    __syncthreads();
-    if (pair == 1) return;
-#pragma unroll
-    for (int d = 0; d < NDT; ++d)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[d][r] += sum[(d * 16 + r) * 64];
+        for (int r = 0; r < 16; ++r) acc[x][d][r] += sum[((x * NDT + d) * 16 + r) * 64];
   }
   if (valid) {
     bf16_t* out = dqkv + (size_t)my_key * rs + (size_t)j * 3 * hp + (size_t)e * DH;
-    store_cols<NDT>(out + (want_dk ? hp : 2 * hp), acc, want_dk ? scale : 1.f, half);
+    if constexpr (SPLIT) {
+      store_cols<NDT>(out + (want_dk ? hp : 2 * hp), acc[0], want_dk ? scale : 1.f, half);
+    } else {
+      store_cols<NDT>(out + 2 * hp, acc[0], 1.f, half);
+      store_cols<NDT>(out + hp, acc[1], scale, half);
+    }
   }
 }
 
@@ -1549,36 +1303,47 @@ static int attn_bwd_dq_t(const bf16_t* qkv, const bf16_t* ctx, const bf16_t* dct
   return attn_bwd_dq_tiles_np<DH, CAUSAL, 2, 2, 32>(qkv, ctx, dctx, lse, delta, dqkv, s, b, heads, mask, stream);
 }
 
-template <int DH, bool CAUSAL, int NP>
-static int attn_bwd_dkv_np(const bf16_t* qkv, const bf16_t* dctx, const float* lse, const float* delta, bf16_t* dqkv, int s, int b, int heads,
-                           const uint8_t* mask, hipStream_t stream) {
-  static once_flag_t done_dkv[kMaxDevices];
-  const dim3 grid(attn_grid((s + kBQ - 1) / kBQ, heads, b));
-  if constexpr (!kDkvSplit<DH, CAUSAL>) {
-    constexpr int smem_dkv = NP == 2 ? DkvLds<DH, CAUSAL>::kBytes2 : DkvLds<DH, CAUSAL>::kPair;
-    if (set_dynamic_smem(reinterpret_cast<const void*>(attn_bwd_dkv_both_mfma<DH, CAUSAL, NP>), smem_dkv, done_dkv) != PTDP_OK)
-      return PTDP_E_HIP;
-    hipLaunchKernelGGL((attn_bwd_dkv_both_mfma<DH, CAUSAL, NP>), grid, dim3(NP * kAttnThreads), smem_dkv, stream, qkv, dctx, lse,
-                       delta, dqkv, s, b, heads, mask);
-  } else {
-    constexpr int smem_dkv = NP == 2 ? DkvLds<DH, CAUSAL>::kBytes2 : DkvLds<DH, CAUSAL>::kPair;
-    if (set_dynamic_smem(reinterpret_cast<const void*>(attn_bwd_dkv_mfma<DH, CAUSAL, NP>), smem_dkv, done_dkv) != PTDP_OK)
-      return PTDP_E_HIP;
-    hipLaunchKernelGGL((attn_bwd_dkv_mfma<DH, CAUSAL, NP>), grid, dim3(NP * kDkvThreads), smem_dkv, stream, qkv, dctx, lse,
-                       delta, dqkv, s, b, heads, mask);
-  }
+template <int DH, bool CAUSAL, int KW, int NP, int QT, bool SPLIT>
+static int attn_bwd_dkv_tiles_np(const bf16_t* qkv, const bf16_t* dctx, const float* lse, const float* delta, bf16_t* dqkv, int s, int b,
+                                 int heads, const uint8_t* mask, hipStream_t stream) {
+  using Geom = DkvGeom<DH, CAUSAL, KW, NP, QT, SPLIT>;
+  static once_flag_t done[kMaxDevices];
+  const auto kernel = attn_bwd_dkv_tiles<DH, CAUSAL, KW, NP, QT, SPLIT>;
+  if (set_dynamic_smem(reinterpret_cast<const void*>(kernel), Geom::lds_bytes(!CAUSAL), done) != PTDP_OK) return PTDP_E_HIP;
+  const int nblk = (s + 32 * KW - 1) / (32 * KW);
+  const dim3 grid(CAUSAL ? attn_grid_levels(nblk, heads, b) : attn_grid(nblk, heads, b));
+  hipLaunchKernelGGL(kernel, grid, dim3(Geom::kThreads * NP), Geom::lds_bytes(!CAUSAL && mask != nullptr), stream, qkv, dctx, lse, delta, dqkv,
+                     s, b, heads, mask);
   return PTDP_OK;
+}
+// Which form.  us for the whole backward with (4, 1, 64), (2, 2, 32), (2, 2, 64) and, split by result, (2, 1, 32), (2, 2, 32), (2, 2, 64):
+//   heads x s     dh 128 8 x 2048 146, 104, 103, 118, 95, 92; 12 x 2048 155, 116, 111, 130, 106, 103; 24 x 2048 186, 148, 186, 154, 177, 175;
+//                 32 x 2048 215, 188, 236, 196, 225, 224; 64 x 2048 327, 344, 444, 350, 422, 415; without the mask 16 x 2048 211, 181, 260,
+//                 188, 206, 201, 64 x 2048 572, 613, 932, 620, 727, 709
+//                 dh 160 (no room for the last; both results spill) 16 x 1001 147, 96, -, 76, 66; 20 x 2048 323, 260, -, 169, 180
+//                 dh 96 8 x 1024 59, 45, 43; 20 x 2048 127, 102, 122; 64 x 2048 246, 257, 322; 64 x 1024 under a general mask 144, 154, 188
+//                 dh 64 16 x 333 25, 19.6, 19.2; 64 x 512 under a general mask 44, 40, 38; 32 x 2048 122, 101, 110; 64 x 2048 equal
+//                 dh 32 32 x 512 23, 18.3, 17.7; 32 x 2048 88, 70, 68; 128 x 2048 212, 225, 223
+template <int DH, bool CAUSAL>
+static int attn_bwd_dkv_t(const bf16_t* qkv, const bf16_t* dctx, const float* lse, const float* delta, bf16_t* dqkv, int s, int b, int heads,
+                          const uint8_t* mask, hipStream_t stream) {
+  const long long blocks64 = (long long)((s + 63) / 64) * heads * b, ncu = attn_compute_units();
+  if constexpr (DH > 128) {
+    if (blocks64 <= 2 * ncu) return attn_bwd_dkv_tiles_np<DH, CAUSAL, 2, 2, 32, true>(qkv, dctx, lse, delta, dqkv, s, b, heads, mask, stream);
+    return attn_bwd_dkv_tiles_np<DH, CAUSAL, 2, 1, 32, true>(qkv, dctx, lse, delta, dqkv, s, b, heads, mask, stream);
+  } else {
+    if (blocks64 > (CAUSAL ? 6 : 3) * ncu) return attn_bwd_dkv_tiles_np<DH, CAUSAL, 4, 1, 64, false>(qkv, dctx, lse, delta, dqkv, s, b, heads, mask, stream);
+    if (blocks64 <= (DH == 128 ? ncu * 3 / 2 : DH == 96 ? ncu : 2 * ncu))
+      return attn_bwd_dkv_tiles_np<DH, CAUSAL, 2, 2, 64, DH == 128>(qkv, dctx, lse, delta, dqkv, s, b, heads, mask, stream);
+    return attn_bwd_dkv_tiles_np<DH, CAUSAL, 2, 2, 32, false>(qkv, dctx, lse, delta, dqkv, s, b, heads, mask, stream);
+  }
 }
 template <int DH, bool CAUSAL>
 static int attn_bwd_mfma_t(const bf16_t* qkv, const bf16_t* ctx, const float* lse, const bf16_t* dctx, bf16_t* dqkv,
                            float* delta, int s, int b, int heads, const uint8_t* mask, hipStream_t stream) {
   const int rc = attn_bwd_dq_t<DH, CAUSAL>(qkv, ctx, dctx, lse, delta, dqkv, s, b, heads, mask, stream);   // first: it writes delta
   if (rc != PTDP_OK) return rc;
-  // few workgroups: the longest one sets the time, so split its walk over two pairs of waves
-  const long long wgs = (long long)((s + kBQ - 1) / kBQ) * heads * b;
-  if (wgs <= 2 * attn_compute_units())   // all resident at once: two per compute unit, one wave per SIMD each
-    return attn_bwd_dkv_np<DH, CAUSAL, 2>(qkv, dctx, lse, delta, dqkv, s, b, heads, mask, stream);
-  return attn_bwd_dkv_np<DH, CAUSAL, 1>(qkv, dctx, lse, delta, dqkv, s, b, heads, mask, stream);
+  return attn_bwd_dkv_t<DH, CAUSAL>(qkv, dctx, lse, delta, dqkv, s, b, heads, mask, stream);
 }
 
 int launch_attn_bwd(int dtype, const void* qkv, const void* ctx, const float* lse, const void* dctx, void* dqkv,

@@ -303,7 +303,11 @@ def test_attention_forward_backward(dtype, s, b, heads, dh):
 # walk split in two or whole, fewer and more than eight blocks per head, a last block of one to six rows, and numbers of
 # (sample, head) pairs that leave 5, 6 and 7 of them over after dealing eight at a time.
 @pytest.mark.parametrize("s,b,heads,dh", [(1026, 1, 13, 64), (518, 1, 62, 32), (1025, 1, 37, 64), (1030, 1, 61, 32),
-                                          (515, 1, 47, 128), (897, 1, 7, 160), (449, 2, 67, 160), (70, 1, 5, 96)])
+                                          (515, 1, 47, 128), (897, 1, 7, 160), (449, 2, 67, 160), (70, 1, 5, 96),
+                                          # dK/dV: the walk whole, 128 keys to a workgroup, for every head size that has it; the
+                                          # remaining forms of heads of 96 and 128
+                                          (130, 3, 172, 32), (129, 4, 130, 64), (131, 2, 258, 96), (197, 4, 97, 128), (321, 1, 50, 96),
+                                          (327, 1, 5, 128)])
 def test_attention_forms(s, b, heads, dh):
     test_attention_forward_backward(B.BF16, s, b, heads, dh)
 

@@ -79,7 +79,7 @@ def test_masked_attention_forward_backward(dtype, s, b, heads, dh, masked, empty
 # Mask rows that travel whole (s a multiple of 4: tiles inside the row), word by word (the last tile) and byte by byte (any other
 # s), in the forms of the kernels for few and many workgroups.
 @pytest.mark.parametrize("s,b,heads,dh", [(196, 1, 3, 64), (132, 2, 3, 160), (132, 8, 43, 32), (131, 8, 43, 32), (192, 4, 65, 128),
-                                          (256, 2, 35, 96)])
+                                          (256, 2, 35, 96), (130, 5, 53, 96), (132, 5, 53, 64), (132, 4, 43, 32), (133, 3, 90, 64)])
 def test_masked_attention_forms(s, b, heads, dh):
     test_masked_attention_forward_backward(B.BF16, s, b, heads, dh, True, [(0, s - 1)])
 
