@@ -317,11 +317,10 @@ int ptdp_chunk_bind_grads(ptdp_chunk* chunk, int layer, const ptdp_layer_grads* 
     if (rc__ != PTDP_OK) return rc__; \
   } while (0)
 
-int ptdp_layer_forward(ptdp_chunk* ch, int layer, int64_t microbatch, const void* x, void* y, void* stash,
-                       void* workspace, void* stream) {
-  if (!ch || !x || !y || !stash || !workspace) return PTDP_E_NULL_PTR;
-  if (layer < 0 || layer >= ch->n_layers || microbatch < 0 || x == y) return PTDP_E_INVALID_ARG;
-  if (!ch->have_params[layer]) return PTDP_E_STATE;
+// One layer.  `ln1_done`: U, MU1, RSTD1 and X of its stash are there already.  `next`: the stash of the following layer of the
+// same pass (y is its X), whose first LayerNorm then runs in this layer's last launch; NULL: there is none.
+static int layer_forward(ptdp_chunk* ch, int layer, int64_t microbatch, const void* x, void* y, void* stash, void* workspace,
+                         void* stream, bool ln1_done, void* next) {
   const ptdp_layer_cfg& c = ch->cfg;
   const ptdp_layer_params& P = ch->params[layer];
   const Dims d = dims_of(&c);
@@ -336,24 +335,34 @@ int ptdp_layer_forward(ptdp_chunk* ch, int layer, int64_t microbatch, const void
   const size_t skb = ws_field_bytes(ch->wl, WS_SPLITK);
   void* x_copy = (x == sf(PTDP_STASH_X)) ? nullptr : sf(PTDP_STASH_X);
 
-  PTDP_TRY(launch_layernorm_fwd(c.dtype, x, P.ln1_g, P.ln1_b, sf(PTDP_STASH_U), (float*)sf(PTDP_STASH_MU1),
-                                (float*)sf(PTDP_STASH_RSTD1), x_copy, T, h, c.ln_eps, st));
+  if (!ln1_done)
+    PTDP_TRY(launch_layernorm_fwd(c.dtype, x, P.ln1_g, P.ln1_b, sf(PTDP_STASH_U), (float*)sf(PTDP_STASH_MU1),
+                                  (float*)sf(PTDP_STASH_RSTD1), x_copy, T, h, c.ln_eps, st));
   PTDP_TRY(launch_gemm(c.dtype, PTDP_GEMM_NN, sf(PTDP_STASH_U), P.w_qkv, sf(PTDP_STASH_QKV), P.b_qkv, T, 3 * hp, h, 0,
                        0, sk, skb, st));
   PTDP_TRY(launch_attn_fwd(c.dtype, sf(PTDP_STASH_QKV), sf(PTDP_STASH_CTX), (float*)sf(PTDP_STASH_LSE), c.s, c.b,
                            (int)d.al, (int)d.dh, ch->mask, c.causal, st));
   PTDP_TRY(launch_gemm(c.dtype, PTDP_GEMM_NN, sf(PTDP_STASH_CTX), P.w_o, o, nullptr, T, h, hp, 0, 0, sk, skb, st));
-  PTDP_TRY(launch_bda_fwd(c.dtype, o, P.b_o, x, sf(PTDP_STASH_X1), T, h, c.p_hidden,
-                          dropout_key(c.seed, gl, 0, (uint64_t)microbatch), st));
-  PTDP_TRY(launch_layernorm_fwd(c.dtype, sf(PTDP_STASH_X1), P.ln2_g, P.ln2_b, sf(PTDP_STASH_U2),
-                                (float*)sf(PTDP_STASH_MU2), (float*)sf(PTDP_STASH_RSTD2), nullptr, T, h, c.ln_eps,
-                                st));
+  PTDP_TRY(launch_bda_layernorm_fwd(c.dtype, o, P.b_o, x, sf(PTDP_STASH_X1), c.p_hidden,
+                                    dropout_key(c.seed, gl, 0, (uint64_t)microbatch), P.ln2_g, P.ln2_b, sf(PTDP_STASH_U2),
+                                    (float*)sf(PTDP_STASH_MU2), (float*)sf(PTDP_STASH_RSTD2), T, h, c.ln_eps, st));
   PTDP_TRY(launch_gemm(c.dtype, PTDP_GEMM_NN, sf(PTDP_STASH_U2), P.w_1, sf(PTDP_STASH_Z), nullptr, T, fp, h, 0, 0, sk, skb, st));
   PTDP_TRY(launch_bias_gelu_fwd(c.dtype, c.gelu_mode, sf(PTDP_STASH_Z), P.b_1, sf(PTDP_STASH_G), T, fp, st));
   PTDP_TRY(launch_gemm(c.dtype, PTDP_GEMM_NN, sf(PTDP_STASH_G), P.w_2, o, nullptr, T, h, fp, 0, 0, sk, skb, st));
-  PTDP_TRY(launch_bda_fwd(c.dtype, o, P.b_2, sf(PTDP_STASH_X1), y, T, h, c.p_hidden,
-                          dropout_key(c.seed, gl, 1, (uint64_t)microbatch), st));
-  return PTDP_OK;
+  const uint64_t key = dropout_key(c.seed, gl, 1, (uint64_t)microbatch);
+  if (!next) return launch_bda_fwd(c.dtype, o, P.b_2, sf(PTDP_STASH_X1), y, T, h, c.p_hidden, key, st);
+  auto nf = [&](int f) { return (void*)((char*)next + ch->sl.off[f]); };
+  const ptdp_layer_params& Q = ch->params[layer + 1];
+  return launch_bda_layernorm_fwd(c.dtype, o, P.b_2, sf(PTDP_STASH_X1), y, c.p_hidden, key, Q.ln1_g, Q.ln1_b, nf(PTDP_STASH_U),
+                                  (float*)nf(PTDP_STASH_MU1), (float*)nf(PTDP_STASH_RSTD1), T, h, c.ln_eps, st);
+}
+
+int ptdp_layer_forward(ptdp_chunk* ch, int layer, int64_t microbatch, const void* x, void* y, void* stash,
+                       void* workspace, void* stream) {
+  if (!ch || !x || !y || !stash || !workspace) return PTDP_E_NULL_PTR;
+  if (layer < 0 || layer >= ch->n_layers || microbatch < 0 || x == y) return PTDP_E_INVALID_ARG;
+  if (!ch->have_params[layer]) return PTDP_E_STATE;
+  return layer_forward(ch, layer, microbatch, x, y, stash, workspace, stream, false, nullptr);
 }
 
 int ptdp_layer_backward(ptdp_chunk* ch, int layer, int64_t microbatch, const void* dy, void* dx, const void* stash,
@@ -423,8 +432,9 @@ int ptdp_chunk_forward(ptdp_chunk* ch, int64_t microbatch, const void* x, void* 
   const void* cur = x;
   for (int l = 0; l < ch->n_layers; ++l) {
     // a layer's output is written straight into the next layer's stash slot for X
-    void* out = (l + 1 < ch->n_layers) ? (void*)(S + (size_t)(l + 1) * ch->sl.total + ch->sl.off[PTDP_STASH_X]) : y;
-    PTDP_TRY(ptdp_layer_forward(ch, l, microbatch, cur, out, S + (size_t)l * ch->sl.total, workspace, stream));
+    char* next = l + 1 < ch->n_layers ? S + (size_t)(l + 1) * ch->sl.total : nullptr;
+    void* out = next ? (void*)(next + ch->sl.off[PTDP_STASH_X]) : y;
+    PTDP_TRY(layer_forward(ch, l, microbatch, cur, out, S + (size_t)l * ch->sl.total, workspace, stream, l > 0, next));
     cur = out;
   }
   return PTDP_OK;
@@ -467,8 +477,9 @@ static int segment_forward(ptdp_chunk* ch, int l0, int l1, int64_t mb, const voi
                            void* workspace, void* stream) {
   const void* cur = x;
   for (int l = l0; l < l1; ++l) {
-    void* y = (l + 1 < l1) ? (void*)(seg_stash + (size_t)(l + 1 - l0) * ch->sl.total + ch->sl.off[PTDP_STASH_X]) : out;
-    PTDP_TRY(ptdp_layer_forward(ch, l, mb, cur, y, seg_stash + (size_t)(l - l0) * ch->sl.total, workspace, stream));
+    char* next = l + 1 < l1 ? seg_stash + (size_t)(l + 1 - l0) * ch->sl.total : nullptr;
+    void* y = next ? (void*)(next + ch->sl.off[PTDP_STASH_X]) : out;
+    PTDP_TRY(layer_forward(ch, l, mb, cur, y, seg_stash + (size_t)(l - l0) * ch->sl.total, workspace, stream, l > l0, next));
     cur = y;
   }
   return PTDP_OK;

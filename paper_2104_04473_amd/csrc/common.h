@@ -149,6 +149,10 @@ int launch_colsum_batch(const ColsumBatch& batch, hipStream_t st);
 // kernels (defined in the .hip files; all arguments validated by the callers in api.hip)
 int launch_layernorm_fwd(int dtype, const void* x, const void* gain, const void* bias, void* u, float* mu,
                          float* rstd, void* x_copy, int rows, int width, float eps, hipStream_t st);
+// bias + dropout + add, then LayerNorm of its result, in one launch: out = resid + Drop(in + bias_in), u = LN(out)
+int launch_bda_layernorm_fwd(int dtype, const void* in, const void* bias_in, const void* resid, void* out, float p, uint64_t key,
+                             const void* gain, const void* bias, void* u, float* mu, float* rstd, int rows, int width, float eps,
+                             hipStream_t st);
 int launch_layernorm_bwd(int dtype, const void* du, const void* x, const void* gain, const float* mu,
                          const float* rstd, const void* resid, void* dx, float* dgain, float* dbias,
                          void* scratch, int rows, int width, hipStream_t st, ColsumBatch* defer = nullptr);

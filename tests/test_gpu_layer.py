@@ -206,3 +206,26 @@ def test_chunk_forward_backward_replays_from_a_hip_graph():
     for l in range(2):
         for k in B.PARAM_NAMES:
             assert torch.equal(rig.grads[l][k], eager3[l][k]), (l, k)
+
+
+# The LayerNorms that run in the launch of the residual sum in front of them (inside a layer, and across two layers of a chunk)
+# give the bits of the op by itself on the stored row.  Widths: one, two, four and eight vectors per thread, the last ones partly used.
+@pytest.mark.parametrize("dtype,h,a,t", [(B.F32, 256, 4, 1), (B.F32, 2176, 34, 2), (B.BF16, 256, 4, 1), (B.BF16, 4608, 48, 8),
+                                         (B.BF16, 12288, 96, 8), (B.BF16, 25600, 160, 8)])
+def test_layernorm_behind_a_residual_sum(dtype, h, a, t):
+    s, b, n = 5, 1, 2
+    cfg = B.make_cfg(h=h, a=a, t=t, s=s, b=b, dtype=dtype, p_hidden=0.1, seed=3)
+    rig = LayerRig(cfg, n)
+    x, y = randn((s, b, h), dtype, 4), torch.empty((s, b, h), dtype=tdt(dtype), device="cuda")
+    B.check(rig.chunk.forward(0, x.data_ptr(), y.data_ptr(), rig.stash.data_ptr(), rig.ws.data_ptr()), "forward")
+    sync()
+    for l in range(n):
+        for src, dst, mean, rstd, norm in (("X", "U", "MU1", "RSTD1", "ln1"), ("X1", "U2", "MU2", "RSTD2", "ln2")):
+            row, P = rig.field(l, src, (s, b, h)), rig.params[l]
+            u, mu, rs = torch.empty_like(row), torch.empty(s * b, device="cuda"), torch.empty(s * b, device="cuda")
+            B.check(B.ptdp_layernorm_fwd(dtype, row.data_ptr(), P[norm + "_g"].data_ptr(), P[norm + "_b"].data_ptr(), u.data_ptr(),
+                                         mu.data_ptr(), rs.data_ptr(), None, s * b, h, cfg.ln_eps, stream()), "layernorm_fwd")
+            sync()
+            assert torch.equal(u, rig.field(l, dst, (s, b, h)))
+            assert torch.equal(mu, rig.field(l, mean, (s * b,), torch.float32))
+            assert torch.equal(rs, rig.field(l, rstd, (s * b,), torch.float32))
