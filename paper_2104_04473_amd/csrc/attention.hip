@@ -666,13 +666,11 @@ attn_fwd_tiles(const bf16_t* __restrict__ qkv, bf16_t* __restrict__ ctx, float* 
     if (CAUSAL) {
       // causal mask (also hides keys >= s, which are > every valid query); only tiles on the diagonal need it
       if (key0 + KT - 1 > q_first) {
+        const int seen = my_q - key0 - 4 * half;   // local keys above it are hidden
 #pragma unroll
         for (int sub = 0; sub < SUBS; ++sub)
 #pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            const int key = key0 + sub * 32 + 8 * (r >> 2) + 4 * half + (r & 3);
-            sacc[sub][r] = key > my_q ? -INFINITY : sacc[sub][r];
-          }
+          for (int r = 0; r < 16; ++r) sacc[sub][r] = sub * 32 + 8 * (r >> 2) + (r & 3) > seen ? -INFINITY : sacc[sub][r];
       }
     } else {
       if (use_mask) {
@@ -894,11 +892,9 @@ attn_bwd_dq_tiles(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ ctx
         // without the causal mask a hidden score is the constant fill: its probability counts (through D) but it passes no
         // gradient; keys past the end do not exist (an empty row's lse is so low that their exp2 would overflow)
         if (CAUSAL || key0 + KT > s) {
+          const int seen = (CAUSAL ? my_q : s - 1) - key0 - sub * 32 - 4 * half;   // local keys above it are hidden
 #pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            const int key = key0 + sub * 32 + 8 * (r >> 2) + 4 * half + (r & 3);
-            sacc[r] = (CAUSAL ? key > my_q : key >= s) ? 0.f : sacc[r];
-          }
+          for (int r = 0; r < 16; ++r) sacc[r] = 8 * (r >> 2) + (r & 3) > seen ? 0.f : sacc[r];
         }
         if (use_mask) {
 #pragma unroll
@@ -1101,8 +1097,13 @@ attn_bwd_dkv_tiles(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ dc
           sched_reads_ahead<NKK, 1>();
         }
         __builtin_amdgcn_sched_barrier(0);
+        // hidden scores in branches of their own: few tiles have any, and selects in every tile were a third of the vector instructions
         uint32_t mw = 0;   // bit 8 g + i: query 8 g + 4 half + i of this half of the tile is hidden from my_key
-        if (use_mask) mw = *reinterpret_cast<const uint32_t*>(smem + stage + Geom::kMask + (kw * 32 + l31) * (QT / 8) + sub * 4) >> (4 * half);
+        if (use_mask) {
+          mw = *reinterpret_cast<const uint32_t*>(smem + stage + Geom::kMask + (kw * 32 + l31) * (QT / 8) + sub * 4) >> (4 * half);
+#pragma unroll
+          for (int r = 0; r < 16; ++r) sacc[r] = (mw >> (8 * (r >> 2) + (r & 3))) & 1u ? fill : sacc[r];
+        }
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
           const int ql = sub * 32 + 8 * g + 4 * half;   // local index of the first of 4 consecutive queries
@@ -1110,11 +1111,22 @@ attn_bwd_dkv_tiles(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ dc
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
             const int r = 4 * g + i;
-            const bool hidden = !CAUSAL && (mw >> (8 * g + i)) & 1u;
-            float p = __builtin_amdgcn_exp2f((hidden ? fill : sacc[r]) * c2 - Ls[i]);
-            if (CAUSAL && diag) p = my_key > q0 + ql + i ? 0.f : p;
+            const float p = __builtin_amdgcn_exp2f(sacc[r] * c2 - Ls[i]);
             sacc[r] = p;
-            dp[r] = hidden ? 0.f : p * (dp[r] - Ds[i]);
+            dp[r] = p * (dp[r] - Ds[i]);
+          }
+        }
+        if (use_mask) {   // no gradient through a hidden score
+#pragma unroll
+          for (int r = 0; r < 16; ++r) dp[r] = (mw >> (8 * (r >> 2) + (r & 3))) & 1u ? 0.f : dp[r];
+        }
+        if (diag) {
+          const int before = my_key - q0 - sub * 32 - 4 * half;   // local queries below it precede my_key
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            const bool gone = 8 * (r >> 2) + (r & 3) < before;
+            sacc[r] = gone ? 0.f : sacc[r];
+            dp[r] = gone ? 0.f : dp[r];
           }
         }
         const bf16x8_t pf[2] = {pack_frag(sacc, 0), pack_frag(sacc, 1)}, dsf[2] = {pack_frag(dp, 0), pack_frag(dp, 1)};
