@@ -8,12 +8,14 @@ namespace ptdp {
 
 static constexpr int kColRows = 32;  // rows per block in the column-sum producers
 
-// The column-sum producers (bias+GeLU backward, bias+dropout+add backward, plain column sums) run 256-thread
-// workgroups of 64 column groups (16 bytes each) x 4 row lanes: wave w takes rows r0 + w, r0 + w + 4, ... of
-// the block's kColRows rows, a whole 1 KiB run of one row per access, eight rows per thread in flight, and
-// width / 512 x rows / 32 workgroups per launch (one thread walking all 32 rows left a 6144-wide bf16 gradient
-// with 192 workgroups for 256 CUs).  The four waves' sums meet in LDS and wave 0 adds them in a fixed order.
-static constexpr int kColLanes = 4;
+// The column-sum producers (bias+GeLU backward, bias+dropout+add backward, plain column sums) run workgroups of 64
+// column groups (16 bytes each) x 16 row lanes: wave w takes rows r0 + w and r0 + w + 16 of the block's kColRows
+// rows, a whole 1 KiB run of one row per access, and width / 512 x rows / 32 workgroups per launch.  The waves' sums
+// meet in LDS and wave 0 adds them in a fixed order.  Bound by memory for large calls, by one wave's chain for small ones.
+// us with 4 row lanes of eight rows each and now, with the finishing launch: bias+GeLU backward 666 x 2048 8.9 -> 8.1, 2048 x
+// 4096 14.9 -> 13.9, 2048 x 12288 28.6 -> 29.0, 8192 x 8192 84 -> 75; bias+dropout+add backward 666 x 512 7.3 -> 6.5, 2048 x 25600
+// 37.6 -> 36.6, 8192 x 8192 57 -> 47.
+static constexpr int kColLanes = 16;
 static inline dim3 colsum_grid(int nvec, int rows) { return dim3((nvec + 63) / 64, (rows + kColRows - 1) / kColRows); }
 template <int N>
 __device__ __forceinline__ void colsum_block_store(float (&acc)[N], float* __restrict__ part, int width, int c, bool valid) {
@@ -26,8 +28,15 @@ __device__ __forceinline__ void colsum_block_store(float (&acc)[N], float* __res
   __syncthreads();
   if (w == 0 && valid) {
 #pragma unroll
-    for (int j = 0; j < N; ++j)
-      part[(size_t)blockIdx.y * width + (size_t)c * N + j] = (acc[j] + red[0][j][lane]) + (red[1][j][lane] + red[2][j][lane]);
+    for (int j = 0; j < N; ++j) {
+      float t[kColLanes / 4];   // four waves at a time, then the fours in order
+#pragma unroll
+      for (int k = 0; k < kColLanes / 4; ++k)
+        t[k] = ((k == 0 ? acc[j] : red[4 * k - 1][j][lane]) + red[4 * k][j][lane]) + (red[4 * k + 1][j][lane] + red[4 * k + 2][j][lane]);
+#pragma unroll
+      for (int k = 1; k < kColLanes / 4; ++k) t[0] += t[k];
+      part[(size_t)blockIdx.y * width + (size_t)c * N + j] = t[0];
+    }
   }
 }
 
@@ -631,7 +640,7 @@ __global__ void bias_gelu_fwd_kernel(const T* __restrict__ z, const T* __restric
 
 // grid (slabs of 64 column groups, row tiles of kColRows); thread owns one 16-byte column group of every fourth row.
 template <typename T, int MODE>
-__global__ void __launch_bounds__(256)
+__global__ void __launch_bounds__(64 * kColLanes)
 bias_gelu_bwd_kernel(const T* dg, const T* __restrict__ z, const T* __restrict__ bias, T* dz,
                      float* __restrict__ part, int rows, int width) {
   constexpr int N = Vec16<T>::N;
@@ -694,7 +703,7 @@ __global__ void bda_fwd_kernel(const T* __restrict__ in, const T* __restrict__ b
 }
 
 template <typename T>
-__global__ void __launch_bounds__(256)
+__global__ void __launch_bounds__(64 * kColLanes)
 bda_bwd_kernel(const T* __restrict__ dout, T* __restrict__ din, float* __restrict__ part, int rows,
                int width, uint64_t key, uint32_t thr, float scale) {
   constexpr int N = Vec16<T>::N;
@@ -729,7 +738,7 @@ bda_bwd_kernel(const T* __restrict__ dout, T* __restrict__ din, float* __restric
 // part[blockIdx.y][c] = sum of in[r][c] over the block's kColRows rows (first stage of a bias gradient
 // whose producer lives in another kernel, e.g. the QKV bias).
 template <typename T>
-__global__ void __launch_bounds__(256)
+__global__ void __launch_bounds__(64 * kColLanes)
 colsum_rows_kernel(const T* __restrict__ in, float* __restrict__ part, int rows, int width) {
   constexpr int N = Vec16<T>::N;
   const int c = blockIdx.x * 64 + (threadIdx.x & 63);
@@ -1013,10 +1022,10 @@ static int gelu_bwd_t(int mode, const void* dg, const void* z, const void* bias,
   {
     Launch L(PTDP_K_GELU_BWD, (double)rows * width * sizeof(T) * 3, st);
     if (mode == PTDP_GELU_TANH)
-      hipLaunchKernelGGL((bias_gelu_bwd_kernel<T, PTDP_GELU_TANH>), grid, dim3(256), 0, st, (const T*)dg,
+      hipLaunchKernelGGL((bias_gelu_bwd_kernel<T, PTDP_GELU_TANH>), grid, dim3(64 * kColLanes), 0, st, (const T*)dg,
                          (const T*)z, (const T*)bias, (T*)dz, part, rows, width);
     else
-      hipLaunchKernelGGL((bias_gelu_bwd_kernel<T, PTDP_GELU_ERF>), grid, dim3(256), 0, st, (const T*)dg,
+      hipLaunchKernelGGL((bias_gelu_bwd_kernel<T, PTDP_GELU_ERF>), grid, dim3(64 * kColLanes), 0, st, (const T*)dg,
                          (const T*)z, (const T*)bias, (T*)dz, part, rows, width);
     if (L.status() != PTDP_OK) return L.status();
   }
@@ -1057,7 +1066,7 @@ static int bda_bwd_t(const void* dout, void* din, float* dbias, void* scratch, i
   float* part = (float*)scratch;
   {
     Launch L(PTDP_K_BDA_BWD, (double)rows * width * sizeof(T) * 2, st);
-    hipLaunchKernelGGL((bda_bwd_kernel<T>), grid, dim3(256), 0, st, (const T*)dout, (T*)din, part, rows, width, key,
+    hipLaunchKernelGGL((bda_bwd_kernel<T>), grid, dim3(64 * kColLanes), 0, st, (const T*)dout, (T*)din, part, rows, width, key,
                        p > 0.f ? dropout_threshold(p) : 0u, 1.0f / (1.0f - p));
     if (L.status() != PTDP_OK) return L.status();
   }
@@ -1108,7 +1117,7 @@ static int colsum_t(const void* in, float* out, void* scratch, int rows, int wid
   float* part = (float*)scratch;
   {
     Launch L(PTDP_K_COLSUM, (double)rows * width * sizeof(T), st);
-    hipLaunchKernelGGL((colsum_rows_kernel<T>), grid, dim3(256), 0, st, (const T*)in, part, rows, width);
+    hipLaunchKernelGGL((colsum_rows_kernel<T>), grid, dim3(64 * kColLanes), 0, st, (const T*)in, part, rows, width);
     if (L.status() != PTDP_OK) return L.status();
   }
   return colsum_finish(part, grid.y, width, out, nullptr, width, st, defer);
