@@ -27,7 +27,7 @@ typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16_t;
 // e of group q: the product's k order is free as long as both operands share it, and a k-contiguous row then gives one
 // 16-byte load per group.  The next chunk is requested before the current one is multiplied.  fp32 calls are small and
 // bound by one wave's chain of loads; before, by the k-steps of the few workgroups that 64 x 64 tiles of plain FMAs gave.
-// us: 256 x 256 x 256 40 -> 4.2, x 1024 148 -> 12; 1024 x 1024 x 1024 191 -> 30; 4096 x 4096 x 1024 730 -> 358.
+// us: 256 x 256 x 256 40 -> 4.2; 1024 x 1024 x 1024 191 -> 30; 4096 x 4096 x 1024 730 -> 358.
 // VA, VB: the operand's rows are k-contiguous, 16-byte aligned and a multiple of four long; otherwise any strides.
 // ------------------------------------------------------------------------------------------------
 constexpr int kF32Chunk = 32;
@@ -134,6 +134,72 @@ gemm_f32_kernel(const float* __restrict__ A, const float* __restrict__ B, float*
   }
 }
 
+// The same on one 16 x 16 tile (v_mfma_f32_16x16x4_f32), for outputs of fewer 32 x 32 tiles than the chip has compute units, where
+// the matrix work of a tile is what its compute unit takes: four times as many workgroups.  Lane (r = lane & 15, q = lane >> 4)
+// carries k 16 g + 4 q + e of row r in element e of group g.  Four k-chunks of a wave are requested at a time.
+// us before and now, NN: 256 x 256 x 768 9.0 -> 4.5, x 1024 11.3 -> 5.2, 48 x 1536 x 512 6.8 -> 5.3, 128 x 512 x 2048 20.6 -> 8.5, 333 x 320 x
+// 1280 14.2 -> 10.4.  Errors against 64 bits are the same.
+template <bool V> struct F32Operand16 {
+  const float* row;
+  size_t ks;   // k stride (V: 1)
+  __device__ __forceinline__ void load(f32x4_t (&f)[2], int k0, int q, int K) const {   // k from K on are zeros
+#pragma unroll
+    for (int g = 0; g < 2; ++g) {
+      const int k = k0 + 16 * g + 4 * q;
+      if (V) {
+        f[g] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+        if (k < K) f[g] = *reinterpret_cast<const f32x4_t*>(row + k);
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) f[g][e] = k + e < K ? row[(size_t)(k + e) * ks] : 0.f;
+      }
+    }
+  }
+};
+constexpr int kF32TinyWaves = 8, kF32TinyAhead = 4;
+template <bool VA, bool VB>
+__global__ void __launch_bounds__(64 * kF32TinyWaves)
+gemm_f32_tiny_kernel(const float* __restrict__ A, const float* __restrict__ B, float* C, const float* __restrict__ bias,
+                     int M, int N, int K, size_t a_rs, size_t a_cs, size_t b_rs, size_t b_cs, int accumulate) {
+  __shared__ float part[kF32TinyWaves][16][17];
+  const int wave = threadIdx.x >> 6, kg = blockDim.x >> 6, lane = threadIdx.x & 63, l15 = lane & 15, q = lane >> 4;
+  const int m0 = blockIdx.y * 16, n0 = blockIdx.x * 16;
+  // rows past the end repeat the last one: their outputs are not written
+  const F32Operand16<VA> oa{A + (size_t)min(m0 + l15, M - 1) * a_rs, a_cs};
+  const F32Operand16<VB> ob{B + (size_t)min(n0 + l15, N - 1) * b_cs, b_rs};
+  f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
+  const int step = kg * kF32Chunk;
+  for (int k = wave * kF32Chunk; k < K; k += kF32TinyAhead * step) {
+    f32x4_t fa[kF32TinyAhead][2], fb[kF32TinyAhead][2];
+#pragma unroll
+    for (int u = 0; u < kF32TinyAhead; ++u) {
+      if (k + u * step < K) {
+        oa.load(fa[u], k + u * step, q, K);
+        ob.load(fb[u], k + u * step, q, K);
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < kF32TinyAhead; ++u) {
+      if (k + u * step < K) {
+#pragma unroll
+        for (int g = 0; g < 2; ++g)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(fa[u][g][e], fb[u][g][e], acc, 0, 0, 0);
+      }
+    }
+  }
+#pragma unroll
+  for (int r = 0; r < 4; ++r) part[wave][4 * q + r][l15] = acc[r];
+  __syncthreads();
+  const int x = threadIdx.x, m = m0 + (x >> 4), n = n0 + (x & 15);
+  if (x >= 256 || m >= M || n >= N) return;
+  float v = 0.f;
+  for (int w = 0; w < kg; ++w) v += part[w][x >> 4][x & 15];
+  if (bias) v += bias[n];
+  float* o = C + (size_t)m * N + n;
+  *o = accumulate ? *o + v : v;
+}
+
 template <bool VA, bool VB, int NB>
 static int launch_gemm_f32_t(const float* A, const float* B, float* C, const float* bias, int M, int N, int K, size_t a_rs, size_t a_cs,
                              size_t b_rs, size_t b_cs, int accumulate, int kg, hipStream_t st) {
@@ -150,10 +216,18 @@ static int compute_units();
 // tile's k range, fewer when the tiles alone fill the chip or the range has fewer chunks.  us with 32 x 32 and 64 x 64: 1024 x
 // 1024 (256 tiles of 64 x 64) over k = 256 13.6, 13.2, over 1024 45, 29; 768 x 768 (144 tiles) 10.5, 13.0 and 33, 28.  16 waves
 // per CU or 4: 512 x 512 x 1024 12.6, 11.4; 2048 x 2048 x 256 47, 36; 1536 x 1536 x 1024 81, 92; 3072 x 3072 x 1024 264, 264.
+// 16 x 16 tiles up to two per compute unit, where a 32 x 32 tile's waves would have more than one k-chunk: 256 x 512 x 1024 (512
+// tiles of 16 x 16) 11.6 -> 8.8; 500 x 288 x 1152 (576) 13.5 and 12.5 NN, 13.7 and 16.9 TN; 256 x 256 x 256 4.4 either way.
 template <bool VA, bool VB>
 static int launch_gemm_f32(const float* A, const float* B, float* C, const float* bias, int M, int N, int K, size_t a_rs, size_t a_cs,
                            size_t b_rs, size_t b_cs, int accumulate, hipStream_t st) {
   const long long ncu = compute_units(), t1 = (long long)((M + 31) / 32) * ((N + 31) / 32), t2 = (long long)((M + 63) / 64) * ((N + 63) / 64);
+  const long long t16 = (long long)((M + 15) / 16) * ((N + 15) / 16);
+  if (t16 <= 2 * ncu && K > kF32TinyWaves * kF32Chunk) {
+    hipLaunchKernelGGL((gemm_f32_tiny_kernel<VA, VB>), dim3((N + 15) / 16, (M + 15) / 16), dim3(64 * kF32TinyWaves), 0, st, A, B, C, bias, M, N, K,
+                       a_rs, a_cs, b_rs, b_cs, accumulate);
+    return PTDP_OK;
+  }
   const bool big = t2 >= ncu;
   int kg = f32_most_waves(big ? 2 : 1);
   while (kg > 1 && (kg > (K + kF32Chunk - 1) / kF32Chunk || (big ? t2 : t1) * kg > 16 * ncu)) kg /= 2;

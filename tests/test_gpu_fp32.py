@@ -13,7 +13,10 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("mode", [B.GEMM_NN, B.GEMM_NT, B.GEMM_TN])
 @pytest.mark.parametrize("M,N,K", [(1, 1, 1), (33, 65, 30), (31, 32, 33), (64, 96, 1024), (130, 70, 257), (1030, 1090, 100),
-                                   (1025, 1024, 36), (40, 24, 0)])
+                                   (1025, 1024, 36), (40, 24, 0),
+                                   # tiles of 16 x 16: one and four requests of a wave's k-chunks and one more, ragged
+                                   # everywhere, the most tiles and one more column of them
+                                   (17, 15, 257), (33, 50, 1024), (31, 16, 1056), (250, 509, 1300), (256, 512, 288), (256, 513, 288)])
 def test_gemm_fp32(mode, M, N, K):
     a, b, bias = randn((M, K), B.F32, 1), randn((K, N), B.F32, 2), randn((N,), B.F32, 3)
     A = a.t().contiguous() if mode == B.GEMM_TN else a
