@@ -318,7 +318,8 @@ int ptdp_chunk_bind_grads(ptdp_chunk* chunk, int layer, const ptdp_layer_grads* 
   } while (0)
 
 // One layer.  `ln1_done`: U, MU1, RSTD1 and X of its stash are there already.  `next`: the stash of the following layer of the
-// same pass (y is its X), whose first LayerNorm then runs in this layer's last launch; NULL: there is none.
+// same pass (y is its X), whose first LayerNorm then runs in this layer's last launch; NULL: there is none.  y NULL: only the
+// stash is wanted (the layer's output is in no later layer's gradients).
 static int layer_forward(ptdp_chunk* ch, int layer, int64_t microbatch, const void* x, void* y, void* stash, void* workspace,
                          void* stream, bool ln1_done, void* next) {
   const ptdp_layer_cfg& c = ch->cfg;
@@ -348,6 +349,7 @@ static int layer_forward(ptdp_chunk* ch, int layer, int64_t microbatch, const vo
                                     (float*)sf(PTDP_STASH_MU2), (float*)sf(PTDP_STASH_RSTD2), T, h, c.ln_eps, st));
   PTDP_TRY(launch_gemm(c.dtype, PTDP_GEMM_NN, sf(PTDP_STASH_U2), P.w_1, sf(PTDP_STASH_Z), nullptr, T, fp, h, 0, 0, sk, skb, st));
   PTDP_TRY(launch_bias_gelu_fwd(c.dtype, c.gelu_mode, sf(PTDP_STASH_Z), P.b_1, sf(PTDP_STASH_G), T, fp, st));
+  if (!y) return PTDP_OK;
   PTDP_TRY(launch_gemm(c.dtype, PTDP_GEMM_NN, sf(PTDP_STASH_G), P.w_2, o, nullptr, T, h, fp, 0, 0, sk, skb, st));
   const uint64_t key = dropout_key(c.seed, gl, 1, (uint64_t)microbatch);
   if (!next) return launch_bda_fwd(c.dtype, o, P.b_2, sf(PTDP_STASH_X1), y, T, h, c.p_hidden, key, st);
@@ -472,7 +474,7 @@ int ptdp_chunk_n_checkpoints(const ptdp_chunk* ch, int seg_layers) {
 }
 
 // Forward of layers [l0, l1) of a chunk with layer l's stash at seg_stash slot (l - l0).  The
-// segment's output goes to `out`.
+// segment's output goes to `out`; NULL: it is not made.
 static int segment_forward(ptdp_chunk* ch, int l0, int l1, int64_t mb, const void* x, void* out, char* seg_stash,
                            void* workspace, void* stream) {
   const void* cur = x;
@@ -519,11 +521,9 @@ int ptdp_chunk_backward_ckpt(ptdp_chunk* ch, int64_t microbatch, const void* dy,
   const void* cur = dy;
   for (int sg = n_seg - 1; sg >= 0; --sg) {
     const int l0 = sg * seg_layers, l1 = l0 + seg_layers < n ? l0 + seg_layers : n;
-    // Rerun the segment.  Its output is not needed again: the last segment's goes to the gradient
-    // chain buffer (idle until the first backward), an inner segment's rewrites the next checkpoint
-    // with the bits it already holds.
-    void* out = l1 < n ? (void*)((char*)ckpt + (size_t)(sg + 1) * cb) : chain;
-    PTDP_TRY(segment_forward(ch, l0, l1, microbatch, (const char*)ckpt + (size_t)sg * cb, out, S, workspace, stream));
+    // Rerun the segment.  Its output is not needed again (an inner segment's is the next checkpoint, which is there already),
+    // and no gradient needs what only it needs: the last layer stops in front of its second MLP product.
+    PTDP_TRY(segment_forward(ch, l0, l1, microbatch, (const char*)ckpt + (size_t)sg * cb, nullptr, S, workspace, stream));
     for (int l = l1 - 1; l >= l0; --l) {
       void* o = l > 0 ? chain : dx;
       PTDP_TRY(ptdp_layer_backward(ch, l, microbatch, cur, o, S + (size_t)(l - l0) * ch->sl.total, workspace, stream));
