@@ -965,10 +965,10 @@ template <int THREADS, int KEYS, int QT> struct MaskBits {
 // SPLIT: KW waves compute S, dP and dK and KW waves S and dV: S twice is a quarter more matrix work, but both results of heads of
 // 160 do not fit the 256 registers that leave two waves on a SIMD (50 to 90 spilled), and short walks are cut once more.
 // What bounds it: every product reads its own fragment from LDS, which at full rate takes as long as the products, and
-// the two waves of a SIMD wait on each other's phases: 29 % of the matrix rate at 64 heads of 128.
+// the two waves of a SIMD wait on each other's phases: 35 % of the matrix rate at 64 heads of 128.
 // us for this kernel before (tiles through registers, two barriers per tile, one wave per SIMD where both results were in
-// one wave) and now, causal, s = 2048: 4 x 16 heads of 128 297 -> 192, 12 heads 88 -> 65, 20 heads of 160 201 -> 113, 20 of 96 90 -> 49,
-// 32 of 64 90 -> 57, 128 of 32 168 -> 122; 4 x 16 heads of 64 x 512 under a general mask 35 -> 22.
+// one wave) and now, causal, s = 2048: 4 x 16 heads of 128 316 -> 157, 12 heads 83 -> 54, 20 heads of 160 219 -> 96, 128 of 32 180 -> 101;
+// 16 heads of 64 x 333 11.2 -> 9.9; 4 x 16 heads of 64 x 512 under a general mask 36 -> 23.
 template <int DH, bool CAUSAL, int KW, int NP, int QT, bool SPLIT> struct DkvGeom {
   static constexpr int kWaves = SPLIT ? 2 * KW : KW, kThreads = 64 * kWaves;   // of a group
   static constexpr int kTile = QT * DH * 2, kStats = 2 * kTile, kMask = kStats + 2 * QT * (int)sizeof(float);
@@ -1328,7 +1328,8 @@ static int attn_bwd_dkv_tiles_np(const bf16_t* qkv, const bf16_t* dctx, const fl
                      s, b, heads, mask);
   return PTDP_OK;
 }
-// Which form.  us for the whole backward with (4, 1, 64), (2, 2, 32), (2, 2, 64) and, split by result, (2, 1, 32), (2, 2, 32), (2, 2, 64):
+// Which form.  us for the whole backward (measured with hidden scores selected in every tile: all forms 6-10 % slower than now)
+// with (4, 1, 64), (2, 2, 32), (2, 2, 64) and, split by result, (2, 1, 32), (2, 2, 32), (2, 2, 64):
 //   heads x s     dh 128 8 x 2048 146, 104, 103, 118, 95, 92; 12 x 2048 155, 116, 111, 130, 106, 103; 24 x 2048 186, 148, 186, 154, 177, 175;
 //                 32 x 2048 215, 188, 236, 196, 225, 224; 64 x 2048 327, 344, 444, 350, 422, 415; without the mask 16 x 2048 211, 181, 260,
 //                 188, 206, 201, 64 x 2048 572, 613, 932, 620, 727, 709
