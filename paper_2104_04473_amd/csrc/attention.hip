@@ -389,8 +389,8 @@ __device__ __forceinline__ bool attn_map(int id, int nblk, int heads, int b, int
   *j = pair / heads;
   return true;
 }
-inline int attn_grid(int nblk, int heads, int b) {
-  const int pairs = heads * b, whole = pairs >> 3, rest = pairs & 7;
+inline long long attn_grid(long long nblk, int heads, int b) {
+  const long long pairs = (long long)heads * b, whole = pairs >> 3, rest = pairs & 7;
   return 8 * (whole * nblk + (rest * nblk + 7) / 8);
 }
 
@@ -418,8 +418,8 @@ __device__ __forceinline__ bool attn_map_levels(int id, int nblk, int heads, int
   *j = pair / heads;
   return true;
 }
-inline int attn_grid_levels(int nblk, int heads, int b) {
-  return nblk < 8 ? attn_grid(nblk, heads, b) : 8 * heads * b * ((nblk + 7) / 8);
+inline long long attn_grid_levels(long long nblk, int heads, int b) {
+  return nblk < 8 ? attn_grid(nblk, heads, b) : (long long)heads * b * (8 * ((nblk + 7) / 8));
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -436,18 +436,44 @@ __device__ __forceinline__ uint32_t attn_lds_offset(const char* p) {
 __device__ __forceinline__ void attn_load_lds(attn_rsrc_t r, uint32_t lds, uint32_t voff) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" :: "s"(lds), "v"(voff), "s"(r) : "memory", "m0");
 }
+// A slice is addressed from its first row with 32-bit byte offsets; they reach the end of its sixteenth row up to this pitch.
+constexpr bool attn_slice_fits(uint64_t row_elements, int dh) {
+  return row_elements < (1ull << 31) && 15 * row_elements * 2 + 2 * (uint64_t)dh <= 0xffffffffull;
+}
+typedef uint32_t attn_chunk_t __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) attn_chunk_t lds_chunk_t;
 // A group of W waves loads a tile of KT rows; wave w takes the 16-row slices w, w + W, .. of every block.
-template <int DH, int W, int KT> struct TileDma {
+// WIDE: any row pitch: 64-bit addresses, through registers, to the same places.
+template <int DH, int W, int KT, bool WIDE> struct TileDma {
   static_assert(KT / 16 % W == 0, "every wave takes the same slices of every block");
   static constexpr int NDT = DH / 32, kBytes = KT * DH * 2;
-  uint32_t off;   // the lane's chunk inside a slice's first block
+  uint32_t off;   // the lane's chunk inside a slice's first block (WIDE: inside the lane's row)
+  uint32_t lane;
   size_t rs;
-  __device__ __forceinline__ void init(size_t row_elements, int lane) {
+  __device__ __forceinline__ void init(size_t row_elements, int lane_id) {
     rs = row_elements;
-    off = (uint32_t)((lane >> 2) * row_elements * 2) + (((lane & 3) ^ (lane >> 4)) * 16);
+    lane = lane_id;
+    off = (WIDE ? 0u : (uint32_t)((lane >> 2) * row_elements * 2)) + (((lane & 3) ^ (lane >> 4)) * 16);
   }
   // rows row0 .. row0 + KT - 1 of a head whose row 0 starts at p; rows from s on are zeros
   __device__ __forceinline__ void issue(const bf16_t* __restrict__ p, int row0, int s, uint32_t lds, int w) const {
+    if constexpr (WIDE) {
+#pragma unroll
+      for (int g = 0; g < KT / 16 / W; ++g) {
+        const int slice = w + W * g, row = row0 + 16 * slice + (int)(lane >> 2);
+        const bool ok = row < s;
+        const char* a = reinterpret_cast<const char*>(p + (size_t)min(row, s - 1) * rs) + off;
+        const uint32_t to = lds + slice * 1024 + lane * 16;
+#pragma unroll
+        for (int d = 0; d < NDT; ++d) {
+          attn_chunk_t t = *reinterpret_cast<const attn_chunk_t*>(a + d * 64);
+#pragma unroll
+          for (int i = 0; i < 4; ++i) t[i] = ok ? t[i] : 0u;
+          *(lds_chunk_t*)(uintptr_t)(to + d * (KT * 64)) = t;
+        }
+      }
+      return;
+    }
 #pragma unroll
     for (int g = 0; g < KT / 16 / W; ++g) {
       const int slice = w + W * g, first = row0 + 16 * slice, rows = min(s - first, 16);
@@ -572,8 +598,8 @@ template <int SUBS> struct MaskWords {
   }
   __device__ __forceinline__ bool hidden(int sub, int r) const { return (now[sub][r >> 2] >> (8 * (r & 3))) & 0xffu; }
 };
-template <bool CAUSAL> __device__ __forceinline__ bool attn_map_tiles(int id, int nblk, int heads, int b, int* blk, int* e, int* j) {
-  if (!(CAUSAL ? attn_map_levels(id, nblk, heads, b, blk, e, j) : attn_map(id, nblk, heads, b, blk, e, j))) return false;
+template <bool LEVELS> __device__ __forceinline__ bool attn_map_tiles(int id, int nblk, int heads, int b, int* blk, int* e, int* j) {
+  if (!(LEVELS ? attn_map_levels(id, nblk, heads, b, blk, e, j) : attn_map(id, nblk, heads, b, blk, e, j))) return false;
   *blk = __builtin_amdgcn_readfirstlane(*blk);
   *e = __builtin_amdgcn_readfirstlane(*e);
   *j = __builtin_amdgcn_readfirstlane(*j);
@@ -593,19 +619,19 @@ template <bool CAUSAL> __device__ __forceinline__ bool attn_map_tiles(int id, in
 // us before (tiles through registers, two barriers per tile) and now, causal, s = 2048 unless given: 4 x 16 heads of 128 143 ->
 // 87; 12 heads of 128 52 -> 30; 8 heads 39 -> 29, at s = 1024 21.6 -> 16.3; 20 heads of 160 98 -> 54; 32 of 64 54 -> 32; 128
 // of 32 104 -> 67; without the mask 16 heads of 128 58 -> 43.
-template <int DH, bool CAUSAL, int QW, int NP, int KT>
+template <int DH, bool CAUSAL, int QW, int NP, int KT, bool WIDE>
 __global__ void __launch_bounds__(64 * QW * NP, 2)
 attn_fwd_tiles(const bf16_t* __restrict__ qkv, bf16_t* __restrict__ ctx, float* __restrict__ lse, int s, int b, int heads,
                const uint8_t* __restrict__ mask) {
   constexpr int NKK = DH / 16, NDT = DH / 32, kQ = 32 * QW, SUBS = KT / 32;
-  constexpr uint32_t kTile = TileDma<DH, QW, KT>::kBytes, kStage = 2 * kTile;
+  constexpr uint32_t kTile = TileDma<DH, QW, KT, WIDE>::kBytes, kStage = 2 * kTile;
   extern __shared__ __attribute__((aligned(1024))) char smem_all[];
   const int wave_all = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), grp = NP == 1 ? 0 : wave_all / QW, wave = wave_all % QW;
   const uint32_t lds0 = attn_lds_offset(smem_all) + grp * 2 * kStage;
 
   const int nqb = (s + kQ - 1) / kQ;
   int qblk, e, j;
-  if (!attn_map_tiles<CAUSAL>(blockIdx.x, nqb, heads, b, &qblk, &e, &j)) return;
+  if (!attn_map_tiles<CAUSAL && !WIDE>(blockIdx.x, nqb, heads, b, &qblk, &e, &j)) return;
   qblk = nqb - 1 - qblk;   // long rows first
   const int lane = threadIdx.x & 63, half = lane >> 5, l31 = lane & 31;
   const int hp = heads * DH;
@@ -617,7 +643,7 @@ attn_fwd_tiles(const bf16_t* __restrict__ qkv, bf16_t* __restrict__ ctx, float* 
 
   const int q_last_blk = min(s, (qblk + 1) * kQ) - 1;
   const int ntiles = CAUSAL ? q_last_blk / KT + 1 : (s + KT - 1) / KT;
-  TileDma<DH, QW, KT> dma;
+  TileDma<DH, QW, KT, WIDE> dma;
   dma.init(rs, lane);
   auto request = [&](int kt, uint32_t stage) {
     dma.issue(base + hp, kt * KT, s, lds0 + stage, wave);
@@ -789,20 +815,20 @@ attn_fwd_tiles(const bf16_t* __restrict__ qkv, bf16_t* __restrict__ ctx, float* 
 // us before and now, causal, s = 2048 unless given: 4 x 16 heads of 128 216 -> 106; 12 heads of 128 61 -> 38; 8 heads 48 -> 34, at
 // s = 1024 27 -> 20; 20 heads of 160 121 -> 56; 32 of 64 62 -> 36; 128 of 32 112 -> 76; 16 of 128 without the mask 147 -> 61; 4 x 16
 // heads of 64 x 512 under a general mask 23 -> 16.
-template <int DH, bool CAUSAL, int QW, int NP, int KT>
+template <int DH, bool CAUSAL, int QW, int NP, int KT, bool WIDE>
 __global__ void __launch_bounds__(64 * QW * NP, 2)
 attn_bwd_dq_tiles(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ ctx, const bf16_t* __restrict__ dctx,
                   const float* __restrict__ lse, float* __restrict__ delta, bf16_t* __restrict__ dqkv, int s, int b, int heads,
                   const uint8_t* __restrict__ mask) {
   constexpr int NKK = DH / 16, NDT = DH / 32, kQ = 32 * QW, SUBS = KT / 32;
-  constexpr uint32_t kTile = TileDma<DH, QW, KT>::kBytes, kStage = 2 * kTile;
+  constexpr uint32_t kTile = TileDma<DH, QW, KT, WIDE>::kBytes, kStage = 2 * kTile;
   extern __shared__ __attribute__((aligned(1024))) char smem_all[];
   const int wave_all = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), grp = NP == 1 ? 0 : wave_all / QW, wave = wave_all % QW;
   const uint32_t lds0 = attn_lds_offset(smem_all) + grp * 2 * kStage;
 
   const int nqb = (s + kQ - 1) / kQ;
   int qblk, e, j;
-  if (!attn_map_tiles<CAUSAL>(blockIdx.x, nqb, heads, b, &qblk, &e, &j)) return;
+  if (!attn_map_tiles<CAUSAL && !WIDE>(blockIdx.x, nqb, heads, b, &qblk, &e, &j)) return;
   qblk = nqb - 1 - qblk;   // long rows first
   const int lane = threadIdx.x & 63, half = lane >> 5, l31 = lane & 31;
   const int hp = heads * DH;
@@ -816,7 +842,7 @@ attn_bwd_dq_tiles(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ ctx
 
   const int q_last_blk = min(s, (qblk + 1) * kQ) - 1;
   const int ntiles = CAUSAL ? q_last_blk / KT + 1 : (s + KT - 1) / KT;
-  TileDma<DH, QW, KT> dma;
+  TileDma<DH, QW, KT, WIDE> dma;
   dma.init(rs, lane);
   auto request = [&](int kt, uint32_t stage) {
     dma.issue(base + hp, kt * KT, s, lds0 + stage, wave);
@@ -980,8 +1006,8 @@ template <int DH, bool CAUSAL, int KW, int NP, int QT, bool SPLIT> struct DkvGeo
 };
 // Causal heads of 64 in tiles of 32: 168 registers instead of 171 (three spilled) leave three waves on a SIMD (whole backward of 32 heads x 2048 93 ->
 // 87 us; in tiles of 64 30 heads x 4 x 777 83 -> 86, and without the causal mask it spills).
-template <int DH, bool CAUSAL, int KW, int NP, int QT, bool SPLIT>
-__global__ void __launch_bounds__(64 * KW * (SPLIT ? 2 : 1) * NP, CAUSAL && DH == 64 && QT == 32 ? 3 : 2)
+template <int DH, bool CAUSAL, int KW, int NP, int QT, bool SPLIT, bool WIDE>
+__global__ void __launch_bounds__(64 * KW * (SPLIT ? 2 : 1) * NP, WIDE ? 1 : CAUSAL && DH == 64 && QT == 32 ? 3 : 2)
 attn_bwd_dkv_tiles(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ dctx, const float* __restrict__ lse,
                    const float* __restrict__ delta, bf16_t* __restrict__ dqkv, int s, int b, int heads,
                    const uint8_t* __restrict__ mask) {
@@ -999,7 +1025,7 @@ attn_bwd_dkv_tiles(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ dc
 
   const int nkb = (s + kKeys - 1) / kKeys;
   int kblk, e, j;   // the first key blocks see the most queries and start first
-  if (!attn_map_tiles<CAUSAL>(blockIdx.x, nkb, heads, b, &kblk, &e, &j)) return;
+  if (!attn_map_tiles<CAUSAL && !WIDE>(blockIdx.x, nkb, heads, b, &kblk, &e, &j)) return;
   // which half of a group takes dK alternates, so that every SIMD gets both (KW = 4: it does anyway)
   const bool want_dk = !SPLIT || ((wave / KW) ^ (KW == 4 ? 0 : NP == 2 ? grp : (int)(blockIdx.x >> 8))) & 1;
   const int lane = threadIdx.x & 63, half = lane >> 5, l31 = lane & 31;
@@ -1020,7 +1046,7 @@ attn_bwd_dkv_tiles(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ dc
   // every wave loads a share of both tiles, or one half of the waves Q and the other dO
   constexpr int kSlices = QT / 16, DW = GW > kSlices ? kSlices : GW;
   static_assert(GW <= 2 * kSlices);
-  TileDma<DH, DW, QT> dma_q, dma_do;
+  TileDma<DH, DW, QT, WIDE> dma_q, dma_do;
   dma_q.init(rs, lane);
   dma_do.init(dors, lane);
   auto request = [&](int qt, uint32_t at) {
@@ -1197,15 +1223,15 @@ bool attn_dh_supported(int dtype, int dh) {
   return dh == 32 || dh == 64 || dh == 96 || dh == 128 || dh == 160;
 }
 
-template <int DH, bool CAUSAL, int QW, int NP, int KT>
+template <int DH, bool CAUSAL, int QW, int NP, int KT, bool WIDE = false>
 static int attn_fwd_tiles_np(const bf16_t* qkv, bf16_t* ctx, float* lse, int s, int b, int heads, const uint8_t* mask, hipStream_t stream) {
-  constexpr int tiles = NP * 4 * TileDma<DH, QW, KT>::kBytes, part = NP > 1 ? QW * (2 + DH / 2) * 64 * (int)sizeof(float) : 0;
+  constexpr int tiles = NP * 4 * TileDma<DH, QW, KT, WIDE>::kBytes, part = NP > 1 ? QW * (2 + DH / 2) * 64 * (int)sizeof(float) : 0;
   constexpr int smem = tiles > part ? tiles : part;
   static once_flag_t done[kMaxDevices];
-  if (set_dynamic_smem(reinterpret_cast<const void*>(attn_fwd_tiles<DH, CAUSAL, QW, NP, KT>), smem, done) != PTDP_OK) return PTDP_E_HIP;
+  if (set_dynamic_smem(reinterpret_cast<const void*>(attn_fwd_tiles<DH, CAUSAL, QW, NP, KT, WIDE>), smem, done) != PTDP_OK) return PTDP_E_HIP;
   const int nblk = (s + 32 * QW - 1) / (32 * QW);
-  const dim3 grid(CAUSAL ? attn_grid_levels(nblk, heads, b) : attn_grid(nblk, heads, b));
-  hipLaunchKernelGGL((attn_fwd_tiles<DH, CAUSAL, QW, NP, KT>), grid, dim3(64 * QW * NP), smem, stream, qkv, ctx, lse, s, b, heads, mask);
+  const dim3 grid(CAUSAL && !WIDE ? attn_grid_levels(nblk, heads, b) : attn_grid(nblk, heads, b));
+  hipLaunchKernelGGL((attn_fwd_tiles<DH, CAUSAL, QW, NP, KT, WIDE>), grid, dim3(64 * QW * NP), smem, stream, qkv, ctx, lse, s, b, heads, mask);
   return PTDP_OK;
 }
 
@@ -1223,20 +1249,44 @@ static int attn_compute_units() {
   if (d >= 0) cached[d].store(cu, std::memory_order_relaxed);
   return cu;
 }
-// Which form: QW waves of queries, NP groups, KT keys per tile.  The walk is split in two while one group per workgroup would
+// The form of a kernel that a call takes.  w: a workgroup's queries (dK/dV: keys) / 32; groups: how many groups of waves share its
+// walk; tile: rows per tile; split: one result per wave (dK/dV).
+// wide: the row pitch b * 3 * heads * dh is too large for slices with 32-bit offsets (attn_slice_fits), or so many workgroups of
+// the form that a launch cannot number their threads: tiles with 64-bit addresses, workgroups of two waves.
+struct AttnForm {
+  int w, groups, tile;
+  bool split, wide;
+};
+static AttnForm attn_wide_or(AttnForm f, AttnForm wide, bool causal, int s, int b, int heads, int dh) {
+  const uint64_t pairs = (uint64_t)b * heads;
+  const int nblk = (s + 32 * f.w - 1) / (32 * f.w), threads = 64 * f.w * (f.split ? 2 : 1) * f.groups;
+  const long long blocks = causal ? attn_grid_levels(nblk, heads, b) : attn_grid(nblk, heads, b);
+  const bool fits = pairs < (1ull << 31) && attn_slice_fits(pairs * 3 * dh, dh) && blocks < (1ll << 32) / threads;
+  return fits ? f : wide;
+}
+// The walk is split in two while one group per workgroup would
 // leave the chip's 2048 wave slots half empty, with 64 queries per workgroup as long as about every compute unit gets
 // one (heads of 64 and less: two fit), else 128.  us for (2, 2, 64), (4, 2, 64), (4, 1, 64): 8 heads of 128 x 2048 28.5, 34, 41; 12
 // heads 30, 36, 43; 16 heads without the mask 61, 43, 50; 32 heads of 64 35, 32, 35; 64 heads of 128 151, 102, 87.  Heads of
 // 160: two groups' stages of 64 keys would take all LDS, so tiles of 32: (2, 2, 32), (4, 1, 64): 20 heads 54, 57.
+static AttnForm attn_fwd_form(int dh, bool causal, int s, int b, int heads) {
+  const long long blocks64 = (long long)((s + 63) / 64) * heads * b, ncu = attn_compute_units();
+  AttnForm f = {4, 2, 64, false, false};
+  if (blocks64 > 4 * ncu) f = {4, 1, 64, false, false};
+  else if (dh > 128) f = {2, 2, 32, false, false};
+  else if (blocks64 <= (dh > 64 ? ncu * 3 / 2 : ncu * 2)) f = {2, 2, 64, false, false};
+  return attn_wide_or(f, {2, 1, 64, false, true}, causal, s, b, heads, dh);
+}
 template <int DH, bool CAUSAL>
 static int attn_fwd_mfma_t(const bf16_t* qkv, bf16_t* ctx, float* lse, int s, int b, int heads, const uint8_t* mask,
                            hipStream_t stream) {
-  const long long blocks64 = (long long)((s + 63) / 64) * heads * b, ncu = attn_compute_units();
-  if (blocks64 > 4 * ncu) return attn_fwd_tiles_np<DH, CAUSAL, 4, 1, 64>(qkv, ctx, lse, s, b, heads, mask, stream);
+  const AttnForm f = attn_fwd_form(DH, CAUSAL, s, b, heads);
+  if (f.wide) return attn_fwd_tiles_np<DH, CAUSAL, 2, 1, 64, true>(qkv, ctx, lse, s, b, heads, mask, stream);
+  if (f.groups == 1) return attn_fwd_tiles_np<DH, CAUSAL, 4, 1, 64>(qkv, ctx, lse, s, b, heads, mask, stream);
   if constexpr (DH > 128) {
     return attn_fwd_tiles_np<DH, CAUSAL, 2, 2, 32>(qkv, ctx, lse, s, b, heads, mask, stream);
   } else {
-    if (blocks64 <= (DH > 64 ? ncu * 3 / 2 : ncu * 2)) return attn_fwd_tiles_np<DH, CAUSAL, 2, 2, 64>(qkv, ctx, lse, s, b, heads, mask, stream);
+    if (f.w == 2) return attn_fwd_tiles_np<DH, CAUSAL, 2, 2, 64>(qkv, ctx, lse, s, b, heads, mask, stream);
     return attn_fwd_tiles_np<DH, CAUSAL, 4, 2, 64>(qkv, ctx, lse, s, b, heads, mask, stream);
   }
 }
@@ -1290,16 +1340,16 @@ static void attn_bwd_f32_t(const float* qkv, const float* ctx, const float* lse,
   hipLaunchKernelGGL(attn_bwd_dkv_f32<ND>, grid, block, 0, stream, qkv, dctx, lse, (const float*)delta, dqkv, s, b, heads, dh, mask, causal);
 }
 
-template <int DH, bool CAUSAL, int QW, int NP, int KT>
+template <int DH, bool CAUSAL, int QW, int NP, int KT, bool WIDE = false>
 static int attn_bwd_dq_tiles_np(const bf16_t* qkv, const bf16_t* ctx, const bf16_t* dctx, const float* lse, float* delta, bf16_t* dqkv,
                                 int s, int b, int heads, const uint8_t* mask, hipStream_t stream) {
-  constexpr int tiles = NP * 4 * TileDma<DH, QW, KT>::kBytes, sums = NP > 1 ? QW * (DH / 2) * 64 * (int)sizeof(float) : 0;
+  constexpr int tiles = NP * 4 * TileDma<DH, QW, KT, WIDE>::kBytes, sums = NP > 1 ? QW * (DH / 2) * 64 * (int)sizeof(float) : 0;
   constexpr int smem = tiles > sums ? tiles : sums;
   static once_flag_t done[kMaxDevices];
-  if (set_dynamic_smem(reinterpret_cast<const void*>(attn_bwd_dq_tiles<DH, CAUSAL, QW, NP, KT>), smem, done) != PTDP_OK) return PTDP_E_HIP;
+  if (set_dynamic_smem(reinterpret_cast<const void*>(attn_bwd_dq_tiles<DH, CAUSAL, QW, NP, KT, WIDE>), smem, done) != PTDP_OK) return PTDP_E_HIP;
   const int nblk = (s + 32 * QW - 1) / (32 * QW);
-  const dim3 grid(CAUSAL ? attn_grid_levels(nblk, heads, b) : attn_grid(nblk, heads, b));
-  hipLaunchKernelGGL((attn_bwd_dq_tiles<DH, CAUSAL, QW, NP, KT>), grid, dim3(64 * QW * NP), smem, stream, qkv, ctx, dctx, lse, delta,
+  const dim3 grid(CAUSAL && !WIDE ? attn_grid_levels(nblk, heads, b) : attn_grid(nblk, heads, b));
+  hipLaunchKernelGGL((attn_bwd_dq_tiles<DH, CAUSAL, QW, NP, KT, WIDE>), grid, dim3(64 * QW * NP), smem, stream, qkv, ctx, dctx, lse, delta,
                      dqkv, s, b, heads, mask);
   return PTDP_OK;
 }
@@ -1308,24 +1358,30 @@ static int attn_bwd_dq_tiles_np(const bf16_t* qkv, const bf16_t* ctx, const bf16
 // heads 42, 46, 50, 53; 24 heads 52, 69, 54, 58; 32 heads 68, 87, 65, 64; 64 heads 122, 172, 129, 106; 32 heads of 64 36, 42, 40, 44;
 // 128 heads of 32 94, 102, 87, 76; 20 and 40 heads of 160 (first and last) 56, 69 and 101, 88; 16 heads of 128 without the mask 61,
 // 80, 56, 60.
+static AttnForm attn_dq_form(int dh, bool causal, int s, int b, int heads) {
+  const long long blocks64 = (long long)((s + 63) / 64) * heads * b;
+  AttnForm f = {2, 2, 32, false, false};
+  if (blocks64 > (dh > 64 ? 3 : 4) * attn_compute_units()) f = {4, 1, 64, false, false};
+  return attn_wide_or(f, {2, 1, 64, false, true}, causal, s, b, heads, dh);
+}
 template <int DH, bool CAUSAL>
 static int attn_bwd_dq_t(const bf16_t* qkv, const bf16_t* ctx, const bf16_t* dctx, const float* lse, float* delta, bf16_t* dqkv, int s,
                          int b, int heads, const uint8_t* mask, hipStream_t stream) {
-  const long long blocks64 = (long long)((s + 63) / 64) * heads * b;
-  if (blocks64 > (DH > 64 ? 3 : 4) * attn_compute_units())
-    return attn_bwd_dq_tiles_np<DH, CAUSAL, 4, 1, 64>(qkv, ctx, dctx, lse, delta, dqkv, s, b, heads, mask, stream);
+  const AttnForm f = attn_dq_form(DH, CAUSAL, s, b, heads);
+  if (f.wide) return attn_bwd_dq_tiles_np<DH, CAUSAL, 2, 1, 64, true>(qkv, ctx, dctx, lse, delta, dqkv, s, b, heads, mask, stream);
+  if (f.groups == 1) return attn_bwd_dq_tiles_np<DH, CAUSAL, 4, 1, 64>(qkv, ctx, dctx, lse, delta, dqkv, s, b, heads, mask, stream);
   return attn_bwd_dq_tiles_np<DH, CAUSAL, 2, 2, 32>(qkv, ctx, dctx, lse, delta, dqkv, s, b, heads, mask, stream);
 }
 
-template <int DH, bool CAUSAL, int KW, int NP, int QT, bool SPLIT>
+template <int DH, bool CAUSAL, int KW, int NP, int QT, bool SPLIT, bool WIDE = false>
 static int attn_bwd_dkv_tiles_np(const bf16_t* qkv, const bf16_t* dctx, const float* lse, const float* delta, bf16_t* dqkv, int s, int b,
                                  int heads, const uint8_t* mask, hipStream_t stream) {
   using Geom = DkvGeom<DH, CAUSAL, KW, NP, QT, SPLIT>;
   static once_flag_t done[kMaxDevices];
-  const auto kernel = attn_bwd_dkv_tiles<DH, CAUSAL, KW, NP, QT, SPLIT>;
+  const auto kernel = attn_bwd_dkv_tiles<DH, CAUSAL, KW, NP, QT, SPLIT, WIDE>;
   if (set_dynamic_smem(reinterpret_cast<const void*>(kernel), Geom::lds_bytes(!CAUSAL), done) != PTDP_OK) return PTDP_E_HIP;
   const int nblk = (s + 32 * KW - 1) / (32 * KW);
-  const dim3 grid(CAUSAL ? attn_grid_levels(nblk, heads, b) : attn_grid(nblk, heads, b));
+  const dim3 grid(CAUSAL && !WIDE ? attn_grid_levels(nblk, heads, b) : attn_grid(nblk, heads, b));
   hipLaunchKernelGGL(kernel, grid, dim3(Geom::kThreads * NP), Geom::lds_bytes(!CAUSAL && mask != nullptr), stream, qkv, dctx, lse, delta, dqkv,
                      s, b, heads, mask);
   return PTDP_OK;
@@ -1339,19 +1395,35 @@ static int attn_bwd_dkv_tiles_np(const bf16_t* qkv, const bf16_t* dctx, const fl
 //                 dh 96 8 x 1024 59, 45, 43; 20 x 2048 127, 102, 122; 64 x 2048 246, 257, 322; 64 x 1024 under a general mask 144, 154, 188
 //                 dh 64 16 x 333 25, 19.6, 19.2; 64 x 512 under a general mask 44, 40, 38; 32 x 2048 122, 101, 110; 64 x 2048 equal
 //                 dh 32 32 x 512 23, 18.3, 17.7; 32 x 2048 88, 70, 68; 128 x 2048 212, 225, 223
+static AttnForm attn_dkv_form(int dh, bool causal, int s, int b, int heads) {
+  const long long blocks64 = (long long)((s + 63) / 64) * heads * b, ncu = attn_compute_units();
+  AttnForm f = {2, 2, 32, false, false};
+  if (dh > 128) f = {2, blocks64 <= 2 * ncu ? 2 : 1, 32, true, false};
+  else if (blocks64 > (causal ? 6 : 3) * ncu) f = {4, 1, 64, false, false};
+  else if (blocks64 <= (dh == 128 ? ncu * 3 / 2 : dh == 96 ? ncu : 2 * ncu)) f = {2, 2, 64, dh == 128, false};
+  return attn_wide_or(f, {2, 1, 32, false, true}, causal, s, b, heads, dh);
+}
 template <int DH, bool CAUSAL>
 static int attn_bwd_dkv_t(const bf16_t* qkv, const bf16_t* dctx, const float* lse, const float* delta, bf16_t* dqkv, int s, int b, int heads,
                           const uint8_t* mask, hipStream_t stream) {
-  const long long blocks64 = (long long)((s + 63) / 64) * heads * b, ncu = attn_compute_units();
+  const AttnForm f = attn_dkv_form(DH, CAUSAL, s, b, heads);
+  if (f.wide) return attn_bwd_dkv_tiles_np<DH, CAUSAL, 2, 1, 32, false, true>(qkv, dctx, lse, delta, dqkv, s, b, heads, mask, stream);
   if constexpr (DH > 128) {
-    if (blocks64 <= 2 * ncu) return attn_bwd_dkv_tiles_np<DH, CAUSAL, 2, 2, 32, true>(qkv, dctx, lse, delta, dqkv, s, b, heads, mask, stream);
+    if (f.groups == 2) return attn_bwd_dkv_tiles_np<DH, CAUSAL, 2, 2, 32, true>(qkv, dctx, lse, delta, dqkv, s, b, heads, mask, stream);
     return attn_bwd_dkv_tiles_np<DH, CAUSAL, 2, 1, 32, true>(qkv, dctx, lse, delta, dqkv, s, b, heads, mask, stream);
   } else {
-    if (blocks64 > (CAUSAL ? 6 : 3) * ncu) return attn_bwd_dkv_tiles_np<DH, CAUSAL, 4, 1, 64, false>(qkv, dctx, lse, delta, dqkv, s, b, heads, mask, stream);
-    if (blocks64 <= (DH == 128 ? ncu * 3 / 2 : DH == 96 ? ncu : 2 * ncu))
-      return attn_bwd_dkv_tiles_np<DH, CAUSAL, 2, 2, 64, DH == 128>(qkv, dctx, lse, delta, dqkv, s, b, heads, mask, stream);
+    if (f.w == 4) return attn_bwd_dkv_tiles_np<DH, CAUSAL, 4, 1, 64, false>(qkv, dctx, lse, delta, dqkv, s, b, heads, mask, stream);
+    if (f.tile == 64) return attn_bwd_dkv_tiles_np<DH, CAUSAL, 2, 2, 64, DH == 128>(qkv, dctx, lse, delta, dqkv, s, b, heads, mask, stream);
     return attn_bwd_dkv_tiles_np<DH, CAUSAL, 2, 2, 32, false>(qkv, dctx, lse, delta, dqkv, s, b, heads, mask, stream);
   }
+}
+void attn_form_query(int kernel, int causal, int s, int b, int heads, int dh, int* rows, int* groups, int* tile, int* wide) {
+  const AttnForm f = kernel == PTDP_ATTN_KERNEL_FWD ? attn_fwd_form(dh, causal != 0, s, b, heads)
+                     : kernel == PTDP_ATTN_KERNEL_DQ ? attn_dq_form(dh, causal != 0, s, b, heads) : attn_dkv_form(dh, causal != 0, s, b, heads);
+  *rows = 32 * f.w;
+  *groups = f.groups;
+  *tile = f.tile;
+  *wide = f.wide;
 }
 template <int DH, bool CAUSAL>
 static int attn_bwd_mfma_t(const bf16_t* qkv, const bf16_t* ctx, const float* lse, const bf16_t* dctx, bf16_t* dqkv,

@@ -312,6 +312,52 @@ def test_attention_forms(s, b, heads, dh):
     test_attention_forward_backward(B.BF16, s, b, heads, dh)
 
 
+# Row pitches at which the sixteenth row of a slice lies more than 2^32 bytes behind the first (9 to 20 GB of qkv): one tile and two, partly
+# filled, under each kind of mask.  Compared at the first, the last and some other samples.
+@pytest.mark.parametrize("kind,s,heads,dh", [("causal", 70, 16, 128), ("causal", 33, 4, 32), ("mask", 36, 16, 64), ("mask", 33, 7, 96),
+                                             ("none", 40, 16, 160)])
+def test_attention_rows_beyond_32_bit_offsets(kind, s, heads, dh):
+    hp = heads * dh
+    b = (2 ** 32 - 1 - 2 * dh) // 30 // (3 * hp) + 1
+    causal = int(kind == "causal")
+    for kernel in range(3):
+        v = [C.c_int() for _ in range(4)]
+        B.check(B.ptdp_attn_form(kernel, causal, s, b, heads, dh, *[C.byref(x) for x in v]), "form")
+        assert v[3].value == 1
+    gen = torch.Generator(device="cuda"); gen.manual_seed(s + dh)
+    rand = lambda *shape: torch.empty(shape, dtype=torch.bfloat16, device="cuda").normal_(generator=gen)
+    qkv, dctx = rand(s, b, 3 * hp), rand(s, b, hp)
+    mask = None
+    if kind == "mask":
+        mask = (torch.rand((b, s, s), device="cuda", generator=gen) < 0.3).to(torch.uint8)
+        mask[:, range(s), range(s)] = 0
+    mp = mask.data_ptr() if mask is not None else None
+    ctx = torch.zeros_like(dctx); dqkv = torch.zeros_like(qkv)
+    lse = torch.zeros((b, heads, s), device="cuda"); delta = torch.zeros_like(lse)
+    if causal:
+        B.check(B.ptdp_attn_fwd(B.BF16, qkv.data_ptr(), ctx.data_ptr(), lse.data_ptr(), s, b, heads, dh, stream()), "fwd")
+        B.check(B.ptdp_attn_bwd(B.BF16, qkv.data_ptr(), ctx.data_ptr(), lse.data_ptr(), dctx.data_ptr(), dqkv.data_ptr(), delta.data_ptr(), s, b,
+                                heads, dh, stream()), "bwd")
+    else:
+        B.check(B.ptdp_attn_masked_fwd(B.BF16, qkv.data_ptr(), mp, ctx.data_ptr(), lse.data_ptr(), s, b, heads, dh, stream()), "fwd")
+        B.check(B.ptdp_attn_masked_bwd(B.BF16, qkv.data_ptr(), mp, ctx.data_ptr(), lse.data_ptr(), dctx.data_ptr(), dqkv.data_ptr(),
+                                       delta.data_ptr(), s, b, heads, dh, stream()), "bwd")
+    sync()
+    pick = sorted({0, 1, b // 3, b // 2, b - 2, b - 1})
+    idx = torch.tensor(pick, device="cuda")
+    cfg = L.LayerConfig(h=hp, a=heads, t=1, s=s, b=len(pick), causal=bool(causal))
+    q64, d64 = np64(qkv[:, idx]), np64(dctx[:, idx])
+    m = mask[idx].cpu().numpy() if mask is not None else None
+    wctx, probs, wlse = L.attention_core(q64, cfg, m)
+    assert_close(np64(ctx[:, idx]), wctx, B.BF16, "ctx")
+    assert np.allclose(np64(lse[idx]), wlse, rtol=0, atol=3e-2)
+    want, got = L.attention_core_backward(d64, q64, probs, cfg, m), np64(dqkv[:, idx])
+    for name, lo in (("dq", 0), ("dk", hp), ("dv", 2 * hp)):
+        assert_close(got[..., lo:lo + hp], want[..., lo:lo + hp], B.BF16, name)
+    del qkv, dctx, ctx, dqkv
+    torch.cuda.empty_cache()
+
+
 def test_attention_sharp_softmax_bf16():
     # logits with standard deviation ~10, as N(0, 0.02) weights give at h = 25600
     s, b, heads, dh = 256, 1, 2, 160

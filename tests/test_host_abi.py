@@ -238,6 +238,45 @@ def test_gemm_form_errors_and_agreement_with_the_plan():
         assert whole or _plan(M, N, K) == (N, []), (M, N, K)      # only 256 x 256 tiles are ever split
 
 
+def _attn_form(kernel, causal, s, b, heads, dh):
+    """(rows, groups, tile, wide) of the call."""
+    v = [C.c_int(-1) for _ in range(4)]
+    assert B.ptdp_attn_form(kernel, causal, s, b, heads, dh, *[C.byref(x) for x in v]) == B.OK
+    return tuple(x.value for x in v)
+
+
+def test_attn_form_errors():
+    v = [C.c_int(-1) for _ in range(4)]
+    ref = [C.byref(x) for x in v]
+    for args in ((3, 1, 8, 1, 1, 64), (-1, 1, 8, 1, 1, 64), (0, 1, 0, 1, 1, 64), (0, 1, 8, 0, 1, 64), (0, 1, 8, 1, 0, 64), (0, 1, 8, 1, 1, 36)):
+        assert B.ptdp_attn_form(*args, *ref) == B.E_INVALID_ARG
+    assert B.ptdp_attn_form(0, 1, 8, 1, 1, 40, *ref) == B.E_UNSUPPORTED
+    assert B.ptdp_attn_form(0, 1, 8, 1, 1, 64, ref[0], ref[1], ref[2], None) == B.E_NULL_PTR
+    assert [x.value for x in v] == [-1] * 4
+
+
+@pytest.mark.parametrize("heads,dh", [(16, 32), (1, 64), (13, 96), (16, 128), (7, 160)])
+def test_attention_rows_beyond_32_bit_offsets(heads, dh):
+    """A slice of 16 rows is read with 32-bit byte offsets from its first row only where every one of them fits."""
+    most = ((2 ** 32 - 1 - 2 * dh) // 30) // (3 * heads * dh)      # the largest b whose sixteenth row still ends inside
+    for s in (2, 16, 40, 300):
+        for b in (1, most // 3, most - 1, most, most + 1, 2 * most + 1, 17 * most):
+            pitch = b * 3 * heads * dh
+            exact = all(r * pitch * 2 + 2 * dh < 2 ** 32 for r in range(16))
+            for causal in (0, 1):
+                for kernel in range(3):
+                    wide = _attn_form(kernel, causal, s, b, heads, dh)[3]
+                    assert exact or wide, (s, b, causal, kernel)
+                    assert not exact or not wide, (s, b, causal, kernel)
+
+
+def test_attention_grids_within_the_launch_limit():
+    """Fewer than 2^32 threads, also where the rows are narrow enough for 32-bit offsets: 1.05 million heads of 32 x 1025."""
+    for kernel in range(3):
+        assert _attn_form(kernel, 1, 1025, 1 << 16, 16, 32) == (64, 1, 32 if kernel == 2 else 64, 1)
+        assert _attn_form(kernel, 1, 1024, 1 << 16, 16, 32)[3] == 0
+
+
 def test_cfg_refuses_operands_beyond_the_gemm_offset_range():
     big = B.make_cfg(h=25600, a=160, t=1, s=2048, b=1, dtype=B.BF16)    # w_1 is 5.2 GB
     assert B.ptdp_cfg_validate(C.byref(big)) == B.E_UNSUPPORTED
