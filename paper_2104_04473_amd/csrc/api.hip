@@ -885,11 +885,11 @@ int ptdp_gemm(int dtype, int mode, const void* A, const void* B, void* C, const 
                      (hipStream_t)stream);
 }
 
-int ptdp_attn_form(int kernel, int causal, int s, int b, int heads, int dh, int* rows, int* groups, int* tile, int* wide) {
+int ptdp_attn_form(int kernel, int causal, int masked, int s, int b, int heads, int dh, int* rows, int* groups, int* tile, int* wide) {
   if (!rows || !groups || !tile || !wide) return PTDP_E_NULL_PTR;
   if (kernel < PTDP_ATTN_KERNEL_FWD || kernel > PTDP_ATTN_KERNEL_DKV || s <= 0 || b <= 0 || heads <= 0 || dh <= 0 || dh % 8) return PTDP_E_INVALID_ARG;
   if (!attn_dh_supported(PTDP_BF16, dh)) return PTDP_E_UNSUPPORTED;
-  attn_form_query(kernel, causal, s, b, heads, dh, rows, groups, tile, wide);
+  attn_form_query(kernel, causal, masked, s, b, heads, dh, rows, groups, tile, wide);
   return PTDP_OK;
 }
 

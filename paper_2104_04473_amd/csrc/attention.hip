@@ -678,7 +678,8 @@ attn_fwd_tiles(const bf16_t* __restrict__ qkv, bf16_t* __restrict__ ctx, float* 
       if (use_mask) mw.load(mrow, key0 + NP * KT, s, half);
       request(kt + NP, stage ^ kStage);
     }
-    if (kt >= ntiles || (CAUSAL && key0 > q_first + 31)) continue;   // (every key of the tile is in this wave's future)
+    // (no query of the wave exists, or every key of the tile is in its future)
+    if (kt >= ntiles || q_first >= s || (CAUSAL && key0 > q_first + 31)) continue;
 
     f32x16_t sacc[SUBS];
 #pragma unroll
@@ -896,7 +897,8 @@ attn_bwd_dq_tiles(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ ctx
       if (use_mask) mw.load(mrow, key0 + NP * KT, s, half);
       request(kt + NP, stage ^ kStage);
     }
-    if (kt >= ntiles || (CAUSAL && key0 > q_first + 31)) continue;   // (every key of the tile is in this wave's future)
+    // (no query of the wave exists, or every key of the tile is in its future)
+    if (kt >= ntiles || q_first >= s || (CAUSAL && key0 > q_first + 31)) continue;
 
     const FragDirect<KT> fks = fk.at(stage), fvs = fv.at(stage);
     const FragTr<KT> fts = ft.at(stage);
@@ -1103,8 +1105,8 @@ attn_bwd_dkv_tiles(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ dc
       fetch(qt + NP);
       request(qt + NP, stage ^ stage_bytes);
     }
-    // (skipped if every query of the tile precedes this wave's keys)
-    if (qt < nqt && !(CAUSAL && q0 + QT - 1 < key_first)) {
+    // (skipped if no key of the wave exists, or every query of the tile precedes its keys)
+    if (qt < nqt && key_first < s && !(CAUSAL && q0 + QT - 1 < key_first)) {
       const FragDirect<QT> fs = f0.at(stage);
       const FragTr<QT> ts = t0.at(stage);
       const char* stats = smem + stage + Geom::kStats;
@@ -1264,28 +1266,55 @@ static AttnForm attn_wide_or(AttnForm f, AttnForm wide, bool causal, int s, int 
   const bool fits = pairs < (1ull << 31) && attn_slice_fits(pairs * 3 * dh, dh) && blocks < (1ll << 32) / threads;
   return fits ? f : wide;
 }
-// The walk is split in two while one group per workgroup would
-// leave the chip's 2048 wave slots half empty, with 64 queries per workgroup as long as about every compute unit gets
-// one (heads of 64 and less: two fit), else 128.  us for (2, 2, 64), (4, 2, 64), (4, 1, 64): 8 heads of 128 x 2048 28.5, 34, 41; 12
-// heads 30, 36, 43; 16 heads without the mask 61, 43, 50; 32 heads of 64 35, 32, 35; 64 heads of 128 151, 102, 87.  Heads of
-// 160: two groups' stages of 64 keys would take all LDS, so tiles of 32: (2, 2, 32), (4, 1, 64): 20 heads 54, 57.
-static AttnForm attn_fwd_form(int dh, bool causal, int s, int b, int heads) {
-  const long long blocks64 = (long long)((s + 63) / 64) * heads * b, ncu = attn_compute_units();
-  AttnForm f = {4, 2, 64, false, false};
-  if (blocks64 > 4 * ncu) f = {4, 1, 64, false, false};
-  else if (dh > 128) f = {2, 2, 32, false, false};
-  else if (blocks64 <= (dh > 64 ? ncu * 3 / 2 : ncu * 2)) f = {2, 2, 64, false, false};
+// Forward.  Long walks (seven blocks of 64 rows and more) are split in two while one group per workgroup would leave the chip's
+// 2048 wave slots half empty, with 64 queries per workgroup as long as about every compute unit gets one (heads of 64 and less:
+// two fit), else with 128, for heads of 96 and 128 up to two blocks of 64 per compute unit unless a long causal walk is to be cut.
+// us for (2, 2, 64), (4, 2, 64), (4, 1, 64): 8 heads of 128 x 2048 28.5, 34, 41; 12 heads 30, 36, 43; 16 heads without the mask
+// 58, 41, 47, 20 heads 101, 77, 66; 32 heads of 64 35, 32, 35; 64 heads of 128 151, 102, 87.  Heads of 160: two groups' stages of
+// 64 keys would take all LDS, so tiles of 32: (2, 2, 32), (4, 1, 64): 20 heads 54, 57.
+// Short walks are not worth a merge once every compute unit has work, and stages of 64 keys then keep workgroups off the chip:
+//   one block: (2, 1, 32).  us for it, (2, 2, 64), (4, 2, 64), (4, 1, 64): 1024 heads of 128 x 64 15.2, 26.3, 28.3, 16.1; of 64
+//     7.2, 9.9, 10.8, 7.0; 64 heads of 64 4.5, 4.5, 4.6, 4.5;
+//   three, the last on one wave: 128 queries would leave three waves idle in half of the workgroups.  (2, 1, 32), (4, 1, 64): 4096
+//     heads of 32 x 129 44, 57, of 128 153, 173;
+//   up to six: (4, 1, 64) and (2, 2, 64), (4, 2, 64): 64 heads of 128 x 320 10.3, -, 14.7, without the mask 12.0, -, 17.9.
+// A general mask whose rows are not a multiple of four bytes is read byte by byte, which with one tile of 32 keys ahead hides
+// better: (2, 2, 32) and (2, 2, 64), (4, 2, 64), (4, 1, 64): 32 heads of 96 x 577 36, 53, 36, 48; 256 of 64 x 1030 454, 598, 490, 590.
+static AttnForm attn_fwd_form(int dh, bool causal, bool masked, int s, int b, int heads) {
+  const int n = (s + 63) / 64;
+  const long long blocks64 = (long long)n * heads * b, ncu = attn_compute_units();
+  const bool bytes = masked && (s & 3), one_wave_left = s % 128 > 0 && s % 128 <= 32;
+  const AttnForm small = {2, 1, 32, false, false}, split32 = {2, 2, 32, false, false}, split64 = {2, 2, 64, false, false};
+  const AttnForm split128 = {4, 2, 64, false, false};
+  AttnForm f = {4, 1, 64, false, false};
+  if (dh > 128) {
+    if (blocks64 <= 4 * ncu) f = split32;
+  } else if (bytes && n <= 2 && (blocks64 <= 2 * ncu || (dh <= 64 && s > 96))) {
+    f = split32;
+  } else if (n == 1) {
+    f = small;
+  } else if (bytes && n >= 3 && (n <= 5 || blocks64 > ncu)) {
+    f = blocks64 > 2 * ncu && ((dh >= 64 && n == 3) || (dh == 128 && n <= 6)) ? small : split32;
+  } else if (blocks64 <= (dh <= 64 ? n <= 3 ? ncu * 3 / 2 : ncu * 2 : causal && n > 6 ? ncu * 3 / 2 : ncu)) {
+    f = split64;
+  } else if (n > 6 && blocks64 <= (dh > 64 && (!causal || n <= 16) ? 2 : 4) * ncu) {
+    f = split128;
+  } else if (n == 3 && one_wave_left) {
+    f = small;
+  }
   return attn_wide_or(f, {2, 1, 64, false, true}, causal, s, b, heads, dh);
 }
 template <int DH, bool CAUSAL>
 static int attn_fwd_mfma_t(const bf16_t* qkv, bf16_t* ctx, float* lse, int s, int b, int heads, const uint8_t* mask,
                            hipStream_t stream) {
-  const AttnForm f = attn_fwd_form(DH, CAUSAL, s, b, heads);
+  const AttnForm f = attn_fwd_form(DH, CAUSAL, !CAUSAL && mask != nullptr, s, b, heads);
   if (f.wide) return attn_fwd_tiles_np<DH, CAUSAL, 2, 1, 64, true>(qkv, ctx, lse, s, b, heads, mask, stream);
-  if (f.groups == 1) return attn_fwd_tiles_np<DH, CAUSAL, 4, 1, 64>(qkv, ctx, lse, s, b, heads, mask, stream);
+  if (f.w == 4 && f.groups == 1) return attn_fwd_tiles_np<DH, CAUSAL, 4, 1, 64>(qkv, ctx, lse, s, b, heads, mask, stream);
   if constexpr (DH > 128) {
     return attn_fwd_tiles_np<DH, CAUSAL, 2, 2, 32>(qkv, ctx, lse, s, b, heads, mask, stream);
   } else {
+    if (f.groups == 1) return attn_fwd_tiles_np<DH, CAUSAL, 2, 1, 32>(qkv, ctx, lse, s, b, heads, mask, stream);
+    if (f.tile == 32) return attn_fwd_tiles_np<DH, CAUSAL, 2, 2, 32>(qkv, ctx, lse, s, b, heads, mask, stream);
     if (f.w == 2) return attn_fwd_tiles_np<DH, CAUSAL, 2, 2, 64>(qkv, ctx, lse, s, b, heads, mask, stream);
     return attn_fwd_tiles_np<DH, CAUSAL, 4, 2, 64>(qkv, ctx, lse, s, b, heads, mask, stream);
   }
@@ -1358,10 +1387,19 @@ static int attn_bwd_dq_tiles_np(const bf16_t* qkv, const bf16_t* ctx, const bf16
 // heads 42, 46, 50, 53; 24 heads 52, 69, 54, 58; 32 heads 68, 87, 65, 64; 64 heads 122, 172, 129, 106; 32 heads of 64 36, 42, 40, 44;
 // 128 heads of 32 94, 102, 87, 76; 20 and 40 heads of 160 (first and last) 56, 69 and 101, 88; 16 heads of 128 without the mask 61,
 // 80, 56, 60.
+// One block of 64 rows, or three (all causal calls, and where the last one is one wave's): workgroups of 128 rows would be half empty.
+// us for the whole backward with (2, 1, 32), (4, 1, 64): 4096 heads of 32 x 129, causal, 154, 183; of 128 x 129 692, 788; 1024 of 64 x 64
+// 27.7, 29.8.
+static bool attn_bwd_small(int dh, bool causal, int s, long long blocks64, long long ncu) {
+  const int n = (s + 63) / 64;
+  return dh <= 128 && ((n == 1 && blocks64 > 2 * ncu) || (n == 3 && blocks64 > (causal && dh == 64 ? 2 : 3) * ncu && (causal || (s % 128 > 0 && s % 128 <= 32))));
+}
 static AttnForm attn_dq_form(int dh, bool causal, int s, int b, int heads) {
-  const long long blocks64 = (long long)((s + 63) / 64) * heads * b;
+  const int n = (s + 63) / 64;
+  const long long blocks64 = (long long)n * heads * b, ncu = attn_compute_units();
   AttnForm f = {2, 2, 32, false, false};
-  if (blocks64 > (dh > 64 ? 3 : 4) * attn_compute_units()) f = {4, 1, 64, false, false};
+  if (attn_bwd_small(dh, causal, s, blocks64, ncu)) f = {2, 1, 32, false, false};
+  else if (blocks64 > (dh > 64 || (causal && n <= 6) ? 3 : 4) * ncu) f = {4, 1, 64, false, false};
   return attn_wide_or(f, {2, 1, 64, false, true}, causal, s, b, heads, dh);
 }
 template <int DH, bool CAUSAL>
@@ -1369,6 +1407,8 @@ static int attn_bwd_dq_t(const bf16_t* qkv, const bf16_t* ctx, const bf16_t* dct
                          int b, int heads, const uint8_t* mask, hipStream_t stream) {
   const AttnForm f = attn_dq_form(DH, CAUSAL, s, b, heads);
   if (f.wide) return attn_bwd_dq_tiles_np<DH, CAUSAL, 2, 1, 64, true>(qkv, ctx, dctx, lse, delta, dqkv, s, b, heads, mask, stream);
+  if constexpr (DH <= 128)
+    if (f.w == 2 && f.groups == 1) return attn_bwd_dq_tiles_np<DH, CAUSAL, 2, 1, 32>(qkv, ctx, dctx, lse, delta, dqkv, s, b, heads, mask, stream);
   if (f.groups == 1) return attn_bwd_dq_tiles_np<DH, CAUSAL, 4, 1, 64>(qkv, ctx, dctx, lse, delta, dqkv, s, b, heads, mask, stream);
   return attn_bwd_dq_tiles_np<DH, CAUSAL, 2, 2, 32>(qkv, ctx, dctx, lse, delta, dqkv, s, b, heads, mask, stream);
 }
@@ -1395,11 +1435,16 @@ static int attn_bwd_dkv_tiles_np(const bf16_t* qkv, const bf16_t* dctx, const fl
 //                 dh 96 8 x 1024 59, 45, 43; 20 x 2048 127, 102, 122; 64 x 2048 246, 257, 322; 64 x 1024 under a general mask 144, 154, 188
 //                 dh 64 16 x 333 25, 19.6, 19.2; 64 x 512 under a general mask 44, 40, 38; 32 x 2048 122, 101, 110; 64 x 2048 equal
 //                 dh 32 32 x 512 23, 18.3, 17.7; 32 x 2048 88, 70, 68; 128 x 2048 212, 225, 223
+// Few blocks per head, as for dQ: (2, 1, 64) for heads of up to 64, (2, 1, 32) for others.  us for the whole backward with (2, 1, 64),
+// (2, 1, 32), (4, 1, 64), (2, 2, 32): causal 4096 heads of 64 x 129 329, 329, 402, 360; 1024 of 64 x 64 27.0, 27.7, 29.1, 31.1; 4096 of 128 x 129
+// 682, 584, 789, 663; 256 of 64 x 200 31.2, 30.9, 30.0, 36.1.
 static AttnForm attn_dkv_form(int dh, bool causal, int s, int b, int heads) {
-  const long long blocks64 = (long long)((s + 63) / 64) * heads * b, ncu = attn_compute_units();
+  const int n = (s + 63) / 64;
+  const long long blocks64 = (long long)n * heads * b, ncu = attn_compute_units();
   AttnForm f = {2, 2, 32, false, false};
   if (dh > 128) f = {2, blocks64 <= 2 * ncu ? 2 : 1, 32, true, false};
-  else if (blocks64 > (causal ? 6 : 3) * ncu) f = {4, 1, 64, false, false};
+  else if (attn_bwd_small(dh, causal, s, blocks64, ncu)) f = {2, 1, dh <= 64 ? 64 : 32, false, false};
+  else if (blocks64 > (causal && n > 6 ? 6 : 3) * ncu) f = {4, 1, 64, false, false};
   else if (blocks64 <= (dh == 128 ? ncu * 3 / 2 : dh == 96 ? ncu : 2 * ncu)) f = {2, 2, 64, dh == 128, false};
   return attn_wide_or(f, {2, 1, 32, false, true}, causal, s, b, heads, dh);
 }
@@ -1412,13 +1457,15 @@ static int attn_bwd_dkv_t(const bf16_t* qkv, const bf16_t* dctx, const float* ls
     if (f.groups == 2) return attn_bwd_dkv_tiles_np<DH, CAUSAL, 2, 2, 32, true>(qkv, dctx, lse, delta, dqkv, s, b, heads, mask, stream);
     return attn_bwd_dkv_tiles_np<DH, CAUSAL, 2, 1, 32, true>(qkv, dctx, lse, delta, dqkv, s, b, heads, mask, stream);
   } else {
+    if (f.w == 2 && f.groups == 1)
+      return attn_bwd_dkv_tiles_np<DH, CAUSAL, 2, 1, DH <= 64 ? 64 : 32, false>(qkv, dctx, lse, delta, dqkv, s, b, heads, mask, stream);
     if (f.w == 4) return attn_bwd_dkv_tiles_np<DH, CAUSAL, 4, 1, 64, false>(qkv, dctx, lse, delta, dqkv, s, b, heads, mask, stream);
     if (f.tile == 64) return attn_bwd_dkv_tiles_np<DH, CAUSAL, 2, 2, 64, DH == 128>(qkv, dctx, lse, delta, dqkv, s, b, heads, mask, stream);
     return attn_bwd_dkv_tiles_np<DH, CAUSAL, 2, 2, 32, false>(qkv, dctx, lse, delta, dqkv, s, b, heads, mask, stream);
   }
 }
-void attn_form_query(int kernel, int causal, int s, int b, int heads, int dh, int* rows, int* groups, int* tile, int* wide) {
-  const AttnForm f = kernel == PTDP_ATTN_KERNEL_FWD ? attn_fwd_form(dh, causal != 0, s, b, heads)
+void attn_form_query(int kernel, int causal, int masked, int s, int b, int heads, int dh, int* rows, int* groups, int* tile, int* wide) {
+  const AttnForm f = kernel == PTDP_ATTN_KERNEL_FWD ? attn_fwd_form(dh, causal != 0, !causal && masked, s, b, heads)
                      : kernel == PTDP_ATTN_KERNEL_DQ ? attn_dq_form(dh, causal != 0, s, b, heads) : attn_dkv_form(dh, causal != 0, s, b, heads);
   *rows = 32 * f.w;
   *groups = f.groups;

@@ -307,22 +307,26 @@ def test_attention_forward_backward(dtype, s, b, heads, dh):
                                           # dK/dV: the walk whole, 128 keys to a workgroup, for every head size that has it; the
                                           # remaining forms of heads of 96 and 128
                                           (130, 3, 172, 32), (129, 4, 130, 64), (131, 2, 258, 96), (197, 4, 97, 128), (321, 1, 50, 96),
-                                          (327, 1, 5, 128)])
+                                          (327, 1, 5, 128),
+                                          # one and two blocks of 64 rows, the last of one to 33 rows
+                                          (65, 13, 31, 32), (65, 13, 31, 64), (65, 1, 403, 96), (389, 5, 13, 96), (33, 5, 103, 128)])
 def test_attention_forms(s, b, heads, dh):
     test_attention_forward_backward(B.BF16, s, b, heads, dh)
 
 
 # Row pitches at which the sixteenth row of a slice lies more than 2^32 bytes behind the first (9 to 20 GB of qkv): one tile and two, partly
 # filled, under each kind of mask.  Compared at the first, the last and some other samples.
-@pytest.mark.parametrize("kind,s,heads,dh", [("causal", 70, 16, 128), ("causal", 33, 4, 32), ("mask", 36, 16, 64), ("mask", 33, 7, 96),
-                                             ("none", 40, 16, 160)])
+@pytest.mark.parametrize("kind,s,heads,dh", [("causal", 70, 16, 128), ("causal", 33, 4, 32), ("causal", 34, 16, 64), ("causal", 17, 13, 96),
+                                             ("causal", 40, 7, 160), ("mask", 36, 16, 64), ("mask", 33, 7, 96), ("mask", 40, 16, 32),
+                                             ("mask", 37, 16, 128), ("mask", 36, 20, 160), ("none", 40, 16, 160), ("none", 33, 16, 128),
+                                             ("none", 68, 12, 64), ("none", 16, 16, 32), ("none", 35, 16, 96)])
 def test_attention_rows_beyond_32_bit_offsets(kind, s, heads, dh):
     hp = heads * dh
     b = (2 ** 32 - 1 - 2 * dh) // 30 // (3 * hp) + 1
     causal = int(kind == "causal")
     for kernel in range(3):
         v = [C.c_int() for _ in range(4)]
-        B.check(B.ptdp_attn_form(kernel, causal, s, b, heads, dh, *[C.byref(x) for x in v]), "form")
+        B.check(B.ptdp_attn_form(kernel, causal, int(kind == "mask"), s, b, heads, dh, *[C.byref(x) for x in v]), "form")
         assert v[3].value == 1
     gen = torch.Generator(device="cuda"); gen.manual_seed(s + dh)
     rand = lambda *shape: torch.empty(shape, dtype=torch.bfloat16, device="cuda").normal_(generator=gen)

@@ -79,9 +79,27 @@ def test_masked_attention_forward_backward(dtype, s, b, heads, dh, masked, empty
 # Mask rows that travel whole (s a multiple of 4: tiles inside the row), word by word (the last tile) and byte by byte (any other
 # s), in the forms of the kernels for few and many workgroups.
 @pytest.mark.parametrize("s,b,heads,dh", [(196, 1, 3, 64), (132, 2, 3, 160), (132, 8, 43, 32), (131, 8, 43, 32), (192, 4, 65, 128),
-                                          (256, 2, 35, 96), (130, 5, 53, 96), (132, 5, 53, 64), (132, 4, 43, 32), (133, 3, 90, 64)])
+                                          (256, 2, 35, 96), (130, 5, 53, 96), (132, 5, 53, 64), (132, 4, 43, 32), (133, 3, 90, 64),
+                                          # the forms that the lists above leave out, rows of whole words
+                                          (68, 1, 1, 32), (68, 5, 103, 32), (452, 5, 13, 32), (68, 1, 257, 64), (68, 5, 103, 64), (452, 5, 13, 64),
+                                          (36, 1, 1, 96), (68, 1, 1, 96), (36, 5, 103, 96), (68, 13, 31, 96), (388, 5, 8, 96), (36, 1, 1, 128),
+                                          (36, 5, 103, 128), (388, 5, 8, 128), (36, 10, 103, 160),
+                                          # and of single bytes
+                                          (33, 1, 1, 32), (327, 1, 3, 32), (65, 1, 257, 32), (33, 5, 103, 32), (65, 5, 103, 32), (33, 1, 1, 64),
+                                          (327, 1, 3, 64), (65, 5, 103, 64), (327, 1, 3, 96), (65, 13, 31, 96), (327, 1, 3, 128),
+                                          (33, 5, 103, 128), (65, 1, 257, 128), (65, 13, 31, 128), (33, 10, 103, 160)])
 def test_masked_attention_forms(s, b, heads, dh):
     test_masked_attention_forward_backward(B.BF16, s, b, heads, dh, True, [(0, s - 1)])
+
+
+# No mask at all, in every form.
+@pytest.mark.parametrize("s,b,heads,dh", [(33, 1, 1, 32), (65, 1, 1, 32), (33, 5, 103, 32), (65, 1, 257, 32), (65, 5, 103, 32), (449, 5, 13, 32),
+                                          (33, 1, 1, 64), (65, 1, 1, 64), (33, 5, 103, 64), (65, 1, 257, 64), (65, 5, 103, 64), (449, 5, 13, 64),
+                                          (33, 1, 1, 96), (65, 3, 43, 96), (33, 5, 103, 96), (65, 13, 31, 96), (389, 5, 8, 96),
+                                          (33, 1, 1, 128), (33, 5, 103, 128), (65, 13, 31, 128), (389, 5, 8, 128),
+                                          (33, 1, 1, 160), (33, 10, 103, 160)])
+def test_unmasked_attention_forms(s, b, heads, dh):
+    test_masked_attention_forward_backward(B.BF16, s, b, heads, dh, False, [])
 
 
 def test_upper_triangular_mask_equals_the_causal_kernels():

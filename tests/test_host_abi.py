@@ -238,20 +238,21 @@ def test_gemm_form_errors_and_agreement_with_the_plan():
         assert whole or _plan(M, N, K) == (N, []), (M, N, K)      # only 256 x 256 tiles are ever split
 
 
-def _attn_form(kernel, causal, s, b, heads, dh):
+def _attn_form(kernel, causal, s, b, heads, dh, masked=0):
     """(rows, groups, tile, wide) of the call."""
     v = [C.c_int(-1) for _ in range(4)]
-    assert B.ptdp_attn_form(kernel, causal, s, b, heads, dh, *[C.byref(x) for x in v]) == B.OK
+    assert B.ptdp_attn_form(kernel, causal, masked, s, b, heads, dh, *[C.byref(x) for x in v]) == B.OK
     return tuple(x.value for x in v)
 
 
 def test_attn_form_errors():
     v = [C.c_int(-1) for _ in range(4)]
     ref = [C.byref(x) for x in v]
-    for args in ((3, 1, 8, 1, 1, 64), (-1, 1, 8, 1, 1, 64), (0, 1, 0, 1, 1, 64), (0, 1, 8, 0, 1, 64), (0, 1, 8, 1, 0, 64), (0, 1, 8, 1, 1, 36)):
+    for args in ((3, 1, 0, 8, 1, 1, 64), (-1, 1, 0, 8, 1, 1, 64), (0, 1, 0, 0, 1, 1, 64), (0, 1, 0, 8, 0, 1, 64), (0, 1, 0, 8, 1, 0, 64),
+                 (0, 1, 0, 8, 1, 1, 36)):
         assert B.ptdp_attn_form(*args, *ref) == B.E_INVALID_ARG
-    assert B.ptdp_attn_form(0, 1, 8, 1, 1, 40, *ref) == B.E_UNSUPPORTED
-    assert B.ptdp_attn_form(0, 1, 8, 1, 1, 64, ref[0], ref[1], ref[2], None) == B.E_NULL_PTR
+    assert B.ptdp_attn_form(0, 1, 0, 8, 1, 1, 40, *ref) == B.E_UNSUPPORTED
+    assert B.ptdp_attn_form(0, 1, 0, 8, 1, 1, 64, ref[0], ref[1], ref[2], None) == B.E_NULL_PTR
     assert [x.value for x in v] == [-1] * 4
 
 
