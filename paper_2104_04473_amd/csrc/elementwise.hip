@@ -42,7 +42,9 @@ __device__ __forceinline__ void colsum_block_store(float (&acc)[N], float* __res
 
 // ------------------------------------------------------------------------------------------------
 // LayerNorm forward: one block per row, the row lives in registers (VPT 16-byte vectors per thread).  Gain and bias are
-// requested with the row (up to four vectors): behind the two reductions they cost one more round trip.
+// requested with the row (without BDA up to 16 values of it per thread, with it up to four vectors): behind the two reductions
+// they cost one more round trip, but their registers cost waves.  us for one row alone behind and with, bf16: 2048 x 6144 10.9, 10.2; 666 x
+// 12288 7.2, 8.4; 2048 x 12288 17.8, 19.0.
 // BDA: the row is first made, x = resid + Drop(in + bias_in), and stored as x_copy (what bda_fwd_kernel does in a pass of its
 // own): one read of x and a launch less.  Statistics and output are those of the stored row.  Bound by memory; for small calls by
 // the launch and one row's round trips.  us for the two passes and for one, inside a layer: 256 x 256 fp32 7.0 -> 3.5, 2048 x 1024 10.6 -> 6.6,
@@ -61,7 +63,7 @@ layernorm_fwd_kernel(const T* __restrict__ x, const T* __restrict__ gain, const 
                      T* __restrict__ u, float* __restrict__ mu, float* __restrict__ rstd,
                      T* __restrict__ x_copy, int width, float eps, LnBda<T> bda) {
   constexpr int N = Vec16<T>::N;
-  constexpr bool kEarly = VPT <= 4;
+  constexpr bool kEarly = BDA ? VPT <= 4 : VPT * N <= 16;
   __shared__ float red[16];
   const int nvec = width / N;
   const size_t row = blockIdx.x;
