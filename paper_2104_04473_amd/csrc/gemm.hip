@@ -217,13 +217,15 @@ static int compute_units();
 // 1024 (256 tiles of 64 x 64) over k = 256 13.6, 13.2, over 1024 45, 29; 768 x 768 (144 tiles) 10.5, 13.0 and 33, 28.  16 waves
 // per CU or 4: 512 x 512 x 1024 12.6, 11.4; 2048 x 2048 x 256 47, 36; 1536 x 1536 x 1024 81, 92; 3072 x 3072 x 1024 264, 264.
 // 16 x 16 tiles up to two per compute unit, where a 32 x 32 tile's waves would have more than one k-chunk: 256 x 512 x 1024 (512
-// tiles of 16 x 16) 11.6 -> 8.8; 500 x 288 x 1152 (576) 13.5 and 12.5 NN, 13.7 and 16.9 TN; 256 x 256 x 256 4.4 either way.
+// tiles of 16 x 16) 11.6 -> 8.8; 500 x 288 x 1152 (576) 13.5 and 12.5 NN, 13.7 and 16.9 TN; 256 x 256 x 256 4.4 either way.  More than
+// one per compute unit only for outputs of more than 64 rows and columns (thinner ones read the long operand in shorter pieces and save
+// little: 1 x 8192 x 1024 10.8, 13.0; 4096 x 32 x 2048 TN 21, 26) and k up to 4096 (119 x 812 x 7783 TN 75, 81; 688 x 168 x 8664 NT 179, 187).
 template <bool VA, bool VB>
 static int launch_gemm_f32(const float* A, const float* B, float* C, const float* bias, int M, int N, int K, size_t a_rs, size_t a_cs,
                            size_t b_rs, size_t b_cs, int accumulate, hipStream_t st) {
   const long long ncu = compute_units(), t1 = (long long)((M + 31) / 32) * ((N + 31) / 32), t2 = (long long)((M + 63) / 64) * ((N + 63) / 64);
   const long long t16 = (long long)((M + 15) / 16) * ((N + 15) / 16);
-  if (t16 <= 2 * ncu && K > kF32TinyWaves * kF32Chunk) {
+  if (K > kF32TinyWaves * kF32Chunk && (t16 <= ncu || (t16 <= 2 * ncu && M > 64 && N > 64 && K <= 4096))) {
     hipLaunchKernelGGL((gemm_f32_tiny_kernel<VA, VB>), dim3((N + 15) / 16, (M + 15) / 16), dim3(64 * kF32TinyWaves), 0, st, A, B, C, bias, M, N, K,
                        a_rs, a_cs, b_rs, b_cs, accumulate);
     return PTDP_OK;

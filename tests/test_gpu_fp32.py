@@ -16,7 +16,9 @@ pytestmark = pytest.mark.gpu
                                    (1025, 1024, 36), (40, 24, 0),
                                    # tiles of 16 x 16: one and four requests of a wave's k-chunks and one more, ragged
                                    # everywhere, the most tiles and one more column of them
-                                   (17, 15, 257), (33, 50, 1024), (31, 16, 1056), (250, 509, 1300), (256, 512, 288), (256, 513, 288)])
+                                   (17, 15, 257), (33, 50, 1024), (31, 16, 1056), (250, 509, 1300), (256, 512, 288), (256, 513, 288),
+                                   # thin outputs and long k ranges of 257 to 512 such tiles
+                                   (1, 8190, 300), (65, 1613, 300), (64, 2046, 300), (70, 1600, 4100)])
 def test_gemm_fp32(mode, M, N, K):
     a, b, bias = randn((M, K), B.F32, 1), randn((K, N), B.F32, 2), randn((N,), B.F32, 3)
     A = a.t().contiguous() if mode == B.GEMM_TN else a
