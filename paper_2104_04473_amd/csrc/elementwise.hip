@@ -12,9 +12,11 @@ static constexpr int kColRows = 32;  // rows per block in the column-sum produce
 // column groups (16 bytes each) x 16 row lanes: wave w takes rows r0 + w and r0 + w + 16 of the block's kColRows
 // rows, a whole 1 KiB run of one row per access, and width / 512 x rows / 32 workgroups per launch.  The waves' sums
 // meet in LDS and wave 0 adds them in a fixed order.  Bound by memory for large calls, by one wave's chain for small ones.
-// us with 4 row lanes of eight rows each and now, with the finishing launch: bias+GeLU backward 666 x 2048 8.9 -> 8.1, 2048 x
-// 4096 14.9 -> 13.9, 2048 x 12288 28.6 -> 29.0, 8192 x 8192 84 -> 75; bias+dropout+add backward 666 x 512 7.3 -> 6.5, 2048 x 25600
-// 37.6 -> 36.6, 8192 x 8192 57 -> 47.
+// A wave's two rows go one after the other: sixteen waves hide each other's trips, and both at once (or a loop unrolled for
+// more rows) take registers: bias+dropout+add backward 2048 x 12288 22.3 with both requested first, 20.3 so.
+// us with 4 row lanes of eight rows each and now, with the finishing launch: bias+GeLU backward 666 x 2048 8.7 -> 7.7, 2048 x
+// 4096 15.0 -> 13.6, 2048 x 12288 28.4 -> 28.2, 8192 x 8192 86 -> 76; bias+dropout+add backward 666 x 512 7.1 -> 6.0, 2048 x 25600
+// 38.3 -> 36.6, 8192 x 8192 52 -> 46; one row of 1024 4.2 -> 4.4 (waves without a row).
 static constexpr int kColLanes = 16;
 static inline dim3 colsum_grid(int nvec, int rows) { return dim3((nvec + 63) / 64, (rows + kColRows - 1) / kColRows); }
 template <int N>
@@ -640,7 +642,7 @@ __global__ void bias_gelu_fwd_kernel(const T* __restrict__ z, const T* __restric
   }
 }
 
-// grid (slabs of 64 column groups, row tiles of kColRows); thread owns one 16-byte column group of every fourth row.
+// grid (slabs of 64 column groups, row tiles of kColRows); thread owns one 16-byte column group of every sixteenth row.
 template <typename T, int MODE>
 __global__ void __launch_bounds__(64 * kColLanes)
 bias_gelu_bwd_kernel(const T* dg, const T* __restrict__ z, const T* __restrict__ bias, T* dz,
@@ -656,7 +658,7 @@ bias_gelu_bwd_kernel(const T* dg, const T* __restrict__ z, const T* __restrict__
     b.load(bias + (size_t)c * N);
     b.unpack(bf);
     const int r0 = blockIdx.y * kColRows + (threadIdx.x >> 6), r1 = min(rows, (int)(blockIdx.y + 1) * kColRows);
-#pragma unroll 8
+#pragma unroll 1
     for (int r = r0; r < r1; r += kColLanes) {
       const size_t off = (size_t)r * width + (size_t)c * N;
       Vec16<T> a, zz;
@@ -716,7 +718,7 @@ bda_bwd_kernel(const T* __restrict__ dout, T* __restrict__ din, float* __restric
   for (int j = 0; j < N; ++j) acc[j] = 0.f;
   if (valid) {
     const int r0 = blockIdx.y * kColRows + (threadIdx.x >> 6), r1 = min(rows, (int)(blockIdx.y + 1) * kColRows);
-#pragma unroll 8
+#pragma unroll 1
     for (int r = r0; r < r1; r += kColLanes) {
       const size_t off = (size_t)r * width + (size_t)c * N;
       Vec16<T> a;
@@ -750,7 +752,7 @@ colsum_rows_kernel(const T* __restrict__ in, float* __restrict__ part, int rows,
   for (int j = 0; j < N; ++j) acc[j] = 0.f;
   if (valid) {
     const int r0 = blockIdx.y * kColRows + (threadIdx.x >> 6), r1 = min(rows, (int)(blockIdx.y + 1) * kColRows);
-#pragma unroll 8
+#pragma unroll 1
     for (int r = r0; r < r1; r += kColLanes) {
       Vec16<T> a;
       float af[N];
