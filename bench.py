@@ -10,8 +10,9 @@ one device, 2 chunks x 8 microbatches).  Inputs, parameters, gradient accumulato
 workspace are resident in HBM before the timed region.  Prints ONE JSON line.
 
 value       model TFLOP/s = 3 x (24 b s h^2 + 4 b s^2 h)/t per layer and microbatch (paper appendix) / wall
-            time.  The paper's factor 4 is used only with --recompute, where the rerun forward is really
-            executed; --stage last adds the logit layer's 6 b s h V / t.  Both carry their own metric name.
+            time.  With --recompute the rerun forward is counted as executed: a fourth time the forward, without the
+            second MLP product (8 b s h^2 / t) of every rerun segment's last layer, which no gradient needs; --stage last
+            adds the logit layer's 6 b s h V / t.  Both carry their own metric name.
 roofline    the GEMM family with the largest share of the step, timed live with HIP events on the
             launch stream in a second pass over the same steps (event pairs around every launch)
 cpu_baseline the fp64 numpy oracle, one full layer forward+backward at the workload's shape (one of the
@@ -41,6 +42,16 @@ WORKLOADS = {
 }
 
 
+def executed_flops(w, seg, passes):
+    """FLOPs of `passes` forward and backward passes over the workload's layers, with checkpoints every seg layers if seg."""
+    forward = (24 * w["b"] * w["s"] * w["h"] ** 2 + 4 * w["b"] * w["s"] ** 2 * w["h"]) // w["t"]
+    flops = 3 * w["layers"] * forward
+    if seg:
+        segments = (w["layers"] + seg - 1) // seg
+        flops += w["layers"] * forward - segments * (8 * w["b"] * w["s"] * w["h"] ** 2 // w["t"])
+    return flops * passes
+
+
 def main():
     ap = argparse.ArgumentParser()
     ap.add_argument("--gpus", type=int, default=1)
@@ -49,8 +60,8 @@ def main():
     ap.add_argument("--workload", default="c4", choices=sorted(WORKLOADS))
     ap.add_argument("--no-cpu-baseline", action="store_true")
     ap.add_argument("--recompute", type=int, default=0, metavar="SEG",
-                    help="activation recomputation with a checkpoint every SEG layers (section 3.5); the rerun "
-                         "forward is executed and counted: FLOP factor 4 instead of 3.  Not the default metric.")
+                    help="activation recomputation with a checkpoint every SEG layers (section 3.5); what the rerun "
+                         "forward executes is counted.  Not the default metric.")
     ap.add_argument("--stage", default="middle", choices=["middle", "first", "last"],
                     help="first: embedding forward/backward around the layers; last: final LayerNorm, logit layer "
                          "(V=51200 split over t) and loss after them.  Not the default metric.")
@@ -179,8 +190,8 @@ def main():
                                                   d_e_pos.data_ptr(), lm_ws.data_ptr(), 0, sh), "embedding_backward")
         passes_per_step = 1
 
-    flop_factor = 4 if seg else 3
-    flops_step = flop_factor * B.ptdp_layer_flops_fwd(C.byref(cfg)) * w["layers"] * passes_per_step
+    flops_step = executed_flops(w, seg, passes_per_step)
+    flop_factor = round(flops_step / (B.ptdp_layer_flops_fwd(C.byref(cfg)) * w["layers"] * passes_per_step), 4)
     if args.stage == "last":
         flops_step += 3 * B.ptdp_logit_flops_fwd(C.byref(cfg), 51200 // w["t"])      # 6 b s h V / t
     torch.cuda.synchronize()
