@@ -162,6 +162,7 @@ __global__ void __launch_bounds__(64 * kF32TinyWaves)
 gemm_f32_tiny_kernel(const float* __restrict__ A, const float* __restrict__ B, float* C, const float* __restrict__ bias,
                      int M, int N, int K, size_t a_rs, size_t a_cs, size_t b_rs, size_t b_cs, int accumulate) {
   __shared__ float part[kF32TinyWaves][16][17];
+  // kg is kF32TinyWaves, read from the launch: as a constant the loops come out 1.5 % slower (a fp32 layer of 66 x 768)
   const int wave = threadIdx.x >> 6, kg = blockDim.x >> 6, lane = threadIdx.x & 63, l15 = lane & 15, q = lane >> 4;
   const int m0 = blockIdx.y * 16, n0 = blockIdx.x * 16;
   // rows past the end repeat the last one: their outputs are not written
@@ -217,15 +218,19 @@ static int compute_units();
 // 1024 (256 tiles of 64 x 64) over k = 256 13.6, 13.2, over 1024 45, 29; 768 x 768 (144 tiles) 10.5, 13.0 and 33, 28.  16 waves
 // per CU or 4: 512 x 512 x 1024 12.6, 11.4; 2048 x 2048 x 256 47, 36; 1536 x 1536 x 1024 81, 92; 3072 x 3072 x 1024 264, 264.
 // 16 x 16 tiles up to two per compute unit, where a 32 x 32 tile's waves would have more than one k-chunk: 256 x 512 x 1024 (512
-// tiles of 16 x 16) 11.6 -> 8.8; 500 x 288 x 1152 (576) 13.5 and 12.5 NN, 13.7 and 16.9 TN; 256 x 256 x 256 4.4 either way.  More than
-// one per compute unit only for outputs of more than 64 rows and columns (thinner ones read the long operand in shorter pieces and save
-// little: 1 x 8192 x 1024 10.8, 13.0; 4096 x 32 x 2048 TN 21, 26) and k up to 4096 (119 x 812 x 7783 TN 75, 81; 688 x 168 x 8664 NT 179, 187).
+// tiles of 16 x 16) 11.6 -> 8.8; 500 x 288 x 1152 (576) 13.5 and 12.5 NN, 13.7 and 16.9 TN; 256 x 256 x 256 4.4 either way.  With more
+// than one tile per compute unit smaller tiles pay only where they do not just read the long side of a thin output in shorter pieces:
+// 1260 random calls with 257 to 512 tiles, time with 16 x 16 over time with 32 x 32 tiles, averages of outputs with a short side of
+// up to 32, 33 to 64, 65 to 100:  NN with no more columns than rows 0.83, 0.88, 0.87;  others with k up to 512 0.92, 0.84, 0.86;  to 1024 NN
+// and NT 1.00, 0.89, 0.88, TN 1.17, 0.99, 0.92;  to 4096 1.08, 1.02, 0.98;  beyond 1.08, 1.02, 0.95 (wider: 119 x 812 x 7783 TN 75, 81 us).
 template <bool VA, bool VB>
 static int launch_gemm_f32(const float* A, const float* B, float* C, const float* bias, int M, int N, int K, size_t a_rs, size_t a_cs,
                            size_t b_rs, size_t b_cs, int accumulate, hipStream_t st) {
   const long long ncu = compute_units(), t1 = (long long)((M + 31) / 32) * ((N + 31) / 32), t2 = (long long)((M + 63) / 64) * ((N + 63) / 64);
   const long long t16 = (long long)((M + 15) / 16) * ((N + 15) / 16);
-  if (K > kF32TinyWaves * kF32Chunk && (t16 <= ncu || (t16 <= 2 * ncu && M > 64 && N > 64 && K <= 4096))) {
+  const int thin = M < N ? M : N;
+  const bool two_rounds = (VA && !VB && N <= M) || (thin > 64 && K <= 4096) || (thin > 32 && K <= (VA ? 1024 : 512));
+  if (K > kF32TinyWaves * kF32Chunk && (t16 <= ncu || (t16 <= 2 * ncu && two_rounds))) {
     hipLaunchKernelGGL((gemm_f32_tiny_kernel<VA, VB>), dim3((N + 15) / 16, (M + 15) / 16), dim3(64 * kF32TinyWaves), 0, st, A, B, C, bias, M, N, K,
                        a_rs, a_cs, b_rs, b_cs, accumulate);
     return PTDP_OK;
