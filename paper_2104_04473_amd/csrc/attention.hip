@@ -608,11 +608,12 @@ template <bool LEVELS> __device__ __forceinline__ bool attn_map_tiles(int id, in
 
 // Forward: S^T = K Q^T and O^T = V^T P^T, so that the probabilities leave the first MFMA in the register layout the second
 // one takes as its B operand.  A workgroup owns 32 QW queries, 32 to a wave; K and V stream through two LDS stages of KT
-// keys, requested one tile ahead, with one barrier per tile.  What bounds it: with two waves per SIMD the matrix cores are
-// busy 37 % of the cycles and the vector ALU a quarter; the rest is the two waves waiting on each other's phases.  Hence:
+// keys, requested one tile ahead, with one barrier per tile.  What bounds it: at 64 heads of 128 x 2048 the matrix cores are
+// busy 35 % of the cycles and the vector ALU issues in 31 % (profiles/c4_kernel_counters.txt); the rest is the two waves of a SIMD
+// waiting on each other's phases.  Hence:
 //   reads of fragments run four MFMAs ahead of their use (left to the compiler, every MFMA waits for its own read);
 //   the second 32 keys' exponentials are spread between the first 32 keys' products;
-//   long rows start first over all pairs of an XCD (attn_map_levels): 1.07 -> 1.43 waves per SIMD on average;
+//   long rows start first over all pairs of an XCD (attn_map_levels): 1.5 waves run on a SIMD on average;
 //   the output is rescaled only when some row's running maximum moved, the mask touches only tiles on the diagonal.
 // NP = 2: two groups of QW waves take alternate tiles, with stages of their own, and their partial results are merged at the
 // end: for launches with too few workgroups to fill the chip.
@@ -993,7 +994,9 @@ template <int THREADS, int KEYS, int QT> struct MaskBits {
 // SPLIT: KW waves compute S, dP and dK and KW waves S and dV: S twice is a quarter more matrix work, but both results of heads of
 // 160 do not fit the 256 registers that leave two waves on a SIMD (50 to 90 spilled), and short walks are cut once more.
 // What bounds it: every product reads its own fragment from LDS, which at full rate takes as long as the products, and
-// the two waves of a SIMD wait on each other's phases: 35 % of the matrix rate at 64 heads of 128.
+// the two waves of a SIMD wait on each other's phases: 35 % of the matrix rate at 64 heads of 128 x 2048 (the same file).
+// Heads of 128 with both results in a wave spill: without the causal mask 32 registers (92 bytes of scratch a lane) in (4, 1, 64) and
+// 20 in tiles of 32, with it up to 3.  Where the launcher takes them they are still the faster forms (its table).
 // us for this kernel before (tiles through registers, two barriers per tile, one wave per SIMD where both results were in
 // one wave) and now, causal, s = 2048: 4 x 16 heads of 128 316 -> 157, 12 heads 83 -> 54, 20 heads of 160 219 -> 96, 128 of 32 180 -> 101;
 // 16 heads of 64 x 333 11.2 -> 9.9; 4 x 16 heads of 64 x 512 under a general mask 36 -> 23.
@@ -1028,8 +1031,9 @@ attn_bwd_dkv_tiles(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ dc
   const int nkb = (s + kKeys - 1) / kKeys;
   int kblk, e, j;   // the first key blocks see the most queries and start first
   if (!attn_map_tiles<CAUSAL && !WIDE>(blockIdx.x, nkb, heads, b, &kblk, &e, &j)) return;
-  // which half of a group takes dK alternates, so that every SIMD gets both (KW = 4: it does anyway)
-  const bool want_dk = !SPLIT || ((wave / KW) ^ (KW == 4 ? 0 : NP == 2 ? grp : (int)(blockIdx.x >> 8))) & 1;
+  static_assert(!SPLIT || KW == 2);
+  // which half of a group takes dK alternates, so that every SIMD gets both
+  const bool want_dk = !SPLIT || ((wave / KW) ^ (NP == 2 ? grp : (int)(blockIdx.x >> 8))) & 1;
   const int lane = threadIdx.x & 63, half = lane >> 5, l31 = lane & 31;
   const int hp = heads * DH;
   const size_t rs = (size_t)b * 3 * hp, dors = (size_t)b * hp;
