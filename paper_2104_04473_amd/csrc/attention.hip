@@ -466,9 +466,8 @@ template <int DH, int W, int KT, bool WIDE> struct TileDma {
         const uint32_t to = lds + slice * 1024 + lane * 16;
 #pragma unroll
         for (int d = 0; d < NDT; ++d) {
-          attn_chunk_t t = *reinterpret_cast<const attn_chunk_t*>(a + d * 64);
-#pragma unroll
-          for (int i = 0; i < 4; ++i) t[i] = ok ? t[i] : 0u;
+          attn_chunk_t t = {0u, 0u, 0u, 0u};
+          if (ok) t = *reinterpret_cast<const attn_chunk_t*>(a + d * 64);
           *(lds_chunk_t*)(uintptr_t)(to + d * (KT * 64)) = t;
         }
       }
@@ -1259,6 +1258,8 @@ static int attn_compute_units() {
 // walk; tile: rows per tile; split: one result per wave (dK/dV).
 // wide: the row pitch b * 3 * heads * dh is too large for slices with 32-bit offsets (attn_slice_fits), or so many workgroups of
 // the form that a launch cannot number their threads: tiles with 64-bit addresses, workgroups of two waves.
+// us with tiles through registers as these calls had them before 32-bit offsets and so (63 rows and less): 24576 samples x 16 heads of
+// 128, causal, 16 rows forward 2640, 2430, backward 10870, 8930; 40 rows 5390, 5790 and 22000, 22200.
 struct AttnForm {
   int w, groups, tile;
   bool split, wide;
@@ -1306,13 +1307,13 @@ static AttnForm attn_fwd_form(int dh, bool causal, bool masked, int s, int b, in
   } else if (n == 3 && one_wave_left) {
     f = small;
   }
-  return attn_wide_or(f, {2, 1, 64, false, true}, causal, s, b, heads, dh);
+  return attn_wide_or(f, {2, 1, 32, false, true}, causal, s, b, heads, dh);
 }
 template <int DH, bool CAUSAL>
 static int attn_fwd_mfma_t(const bf16_t* qkv, bf16_t* ctx, float* lse, int s, int b, int heads, const uint8_t* mask,
                            hipStream_t stream) {
   const AttnForm f = attn_fwd_form(DH, CAUSAL, !CAUSAL && mask != nullptr, s, b, heads);
-  if (f.wide) return attn_fwd_tiles_np<DH, CAUSAL, 2, 1, 64, true>(qkv, ctx, lse, s, b, heads, mask, stream);
+  if (f.wide) return attn_fwd_tiles_np<DH, CAUSAL, 2, 1, 32, true>(qkv, ctx, lse, s, b, heads, mask, stream);
   if (f.w == 4 && f.groups == 1) return attn_fwd_tiles_np<DH, CAUSAL, 4, 1, 64>(qkv, ctx, lse, s, b, heads, mask, stream);
   if constexpr (DH > 128) {
     return attn_fwd_tiles_np<DH, CAUSAL, 2, 2, 32>(qkv, ctx, lse, s, b, heads, mask, stream);
@@ -1404,13 +1405,13 @@ static AttnForm attn_dq_form(int dh, bool causal, int s, int b, int heads) {
   AttnForm f = {2, 2, 32, false, false};
   if (attn_bwd_small(dh, causal, s, blocks64, ncu)) f = {2, 1, 32, false, false};
   else if (blocks64 > (dh > 64 || (causal && n <= 6) ? 3 : 4) * ncu) f = {4, 1, 64, false, false};
-  return attn_wide_or(f, {2, 1, 64, false, true}, causal, s, b, heads, dh);
+  return attn_wide_or(f, {2, 1, 32, false, true}, causal, s, b, heads, dh);
 }
 template <int DH, bool CAUSAL>
 static int attn_bwd_dq_t(const bf16_t* qkv, const bf16_t* ctx, const bf16_t* dctx, const float* lse, float* delta, bf16_t* dqkv, int s,
                          int b, int heads, const uint8_t* mask, hipStream_t stream) {
   const AttnForm f = attn_dq_form(DH, CAUSAL, s, b, heads);
-  if (f.wide) return attn_bwd_dq_tiles_np<DH, CAUSAL, 2, 1, 64, true>(qkv, ctx, dctx, lse, delta, dqkv, s, b, heads, mask, stream);
+  if (f.wide) return attn_bwd_dq_tiles_np<DH, CAUSAL, 2, 1, 32, true>(qkv, ctx, dctx, lse, delta, dqkv, s, b, heads, mask, stream);
   if constexpr (DH <= 128)
     if (f.w == 2 && f.groups == 1) return attn_bwd_dq_tiles_np<DH, CAUSAL, 2, 1, 32>(qkv, ctx, dctx, lse, delta, dqkv, s, b, heads, mask, stream);
   if (f.groups == 1) return attn_bwd_dq_tiles_np<DH, CAUSAL, 4, 1, 64>(qkv, ctx, dctx, lse, delta, dqkv, s, b, heads, mask, stream);
