@@ -425,7 +425,9 @@ int ptdp_gemm_form(int mode, int M, int N, int K, int out_f32, int accumulate, i
 
 /* Fused causal attention over qkv [s, b, 3hp] (scale 1/sqrt(dh), implicit
  * causal mask, softmax, times V; section 4.2's scale+mask+softmax fusion
- * extended over both batched GEMMs): ctx [s, b, hp], lse [b, heads, s] fp32. */
+ * extended over both batched GEMMs): ctx [s, b, hp], lse [b, heads, s] fp32.
+ * bf16: PTDP_E_UNSUPPORTED if 128 threads for every 64 rows of every head of
+ * every sample come to 2^32 or more (the forms below too). */
 int ptdp_attn_fwd(int dtype, const void* qkv, void* ctx, float* lse, int s, int b, int heads, int dh,
                   void* stream);
 /* The same with a general mask instead of the causal one (mask as in

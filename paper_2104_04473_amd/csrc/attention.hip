@@ -1267,9 +1267,9 @@ struct AttnForm {
 static AttnForm attn_wide_or(AttnForm f, AttnForm wide, bool causal, int s, int b, int heads, int dh) {
   const uint64_t pairs = (uint64_t)b * heads;
   const int nblk = (s + 32 * f.w - 1) / (32 * f.w), threads = 64 * f.w * (f.split ? 2 : 1) * f.groups;
+  if (pairs >= (1ull << 31) || !attn_slice_fits(pairs * 3 * dh, dh)) return wide;
   const long long blocks = causal ? attn_grid_levels(nblk, heads, b) : attn_grid(nblk, heads, b);
-  const bool fits = pairs < (1ull << 31) && attn_slice_fits(pairs * 3 * dh, dh) && blocks < (1ll << 32) / threads;
-  return fits ? f : wide;
+  return blocks < (1ll << 32) / threads ? f : wide;
 }
 // Forward.  Long walks (seven blocks of 64 rows and more) are split in two while one group per workgroup would leave the chip's
 // 2048 wave slots half empty, with 64 queries per workgroup as long as about every compute unit gets one (heads of 64 and less:
@@ -1325,6 +1325,12 @@ static int attn_fwd_mfma_t(const bf16_t* qkv, bf16_t* ctx, float* lse, int s, in
   }
 }
 
+// a launch numbers its threads with 32 bits: the form of the smallest workgroups (wide) has to fit
+static bool attn_sizes_fit(int s, int b, int heads) {
+  const uint64_t pairs = (uint64_t)b * heads;
+  return pairs < (1ull << 31) && attn_grid((s + 63) / 64, heads, b) < (1ll << 32) / 128;
+}
+
 // steps of 16 dh, rounded up to one of the built forms
 #define PTDP_F32_DISPATCH(dh, CALL) \
   do {                              \
@@ -1340,7 +1346,7 @@ static int attn_fwd_mfma_t(const bf16_t* qkv, bf16_t* ctx, float* lse, int s, in
 int launch_attn_fwd(int dtype, const void* qkv, void* ctx, float* lse, int s, int b, int heads, int dh,
                     const uint8_t* mask, int causal, hipStream_t stream) {
   if (s == 0 || b == 0 || heads == 0) return PTDP_OK;
-  if (!attn_dh_supported(dtype, dh)) return PTDP_E_UNSUPPORTED;
+  if (!attn_dh_supported(dtype, dh) || (dtype == PTDP_BF16 && !attn_sizes_fit(s, b, heads))) return PTDP_E_UNSUPPORTED;
   Launch L(PTDP_K_ATTN_FWD, attn_flops(s, b, heads, dh), stream);
   int rc = PTDP_OK;
   if (dtype == PTDP_F32) {
@@ -1488,7 +1494,7 @@ static int attn_bwd_mfma_t(const bf16_t* qkv, const bf16_t* ctx, const float* ls
 int launch_attn_bwd(int dtype, const void* qkv, const void* ctx, const float* lse, const void* dctx, void* dqkv,
                     float* delta, int s, int b, int heads, int dh, const uint8_t* mask, int causal, hipStream_t stream) {
   if (s == 0 || b == 0 || heads == 0) return PTDP_OK;
-  if (!attn_dh_supported(dtype, dh)) return PTDP_E_UNSUPPORTED;
+  if (!attn_dh_supported(dtype, dh) || (dtype == PTDP_BF16 && !attn_sizes_fit(s, b, heads))) return PTDP_E_UNSUPPORTED;
   Launch L(PTDP_K_ATTN_BWD, 2.0 * attn_flops(s, b, heads, dh), stream);
   int rc = PTDP_OK;
   if (dtype == PTDP_F32) {

@@ -278,6 +278,16 @@ def test_attention_grids_within_the_launch_limit():
         assert _attn_form(kernel, 1, 1024, 1 << 16, 16, 32)[3] == 0
 
 
+@pytest.mark.parametrize("s,b,heads", [(1, 1 << 25, 1), (1, (1 << 20) + 1, 1 << 12), (65, 1 << 20, 16), (1, 2 ** 31 - 1, 2 ** 31 - 1)])
+def test_attention_refuses_more_heads_than_a_launch_numbers(s, b, heads):
+    """(sample, head) pairs whose workgroups pass 2^32 threads are refused before any device work, not cut to what 32 bits hold."""
+    p = 1 << 20
+    assert B.ptdp_attn_fwd(B.BF16, p, p, p, s, b, heads, 32, None) == B.E_UNSUPPORTED
+    assert B.ptdp_attn_masked_fwd(B.BF16, p, None, p, p, s, b, heads, 32, None) == B.E_UNSUPPORTED
+    assert B.ptdp_attn_bwd(B.BF16, p, p, p, p, p, p, s, b, heads, 32, None) == B.E_UNSUPPORTED
+    assert B.ptdp_attn_masked_bwd(B.BF16, p, p, p, p, p, p, p, s, b, heads, 32, None) == B.E_UNSUPPORTED
+
+
 def test_cfg_refuses_operands_beyond_the_gemm_offset_range():
     big = B.make_cfg(h=25600, a=160, t=1, s=2048, b=1, dtype=B.BF16)    # w_1 is 5.2 GB
     assert B.ptdp_cfg_validate(C.byref(big)) == B.E_UNSUPPORTED
