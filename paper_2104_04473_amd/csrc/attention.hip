@@ -1280,8 +1280,8 @@ static AttnForm attn_wide_or(AttnForm f, AttnForm wide, bool causal, int s, int 
 // Short walks are not worth a merge once every compute unit has work, and stages of 64 keys then keep workgroups off the chip:
 //   one block: (2, 1, 32).  us for it, (2, 2, 64), (4, 2, 64), (4, 1, 64): 1024 heads of 128 x 64 15.2, 26.3, 28.3, 16.1; of 64
 //     7.2, 9.9, 10.8, 7.0; 64 heads of 64 4.5, 4.5, 4.6, 4.5;
-//   three, the last on one wave: 128 queries would leave three waves idle in half of the workgroups.  (2, 1, 32), (4, 1, 64): 4096
-//     heads of 32 x 129 44, 57, of 128 153, 173;
+//   three: 128 queries would leave three waves idle in half of the workgroups, or two, which only very many heads hide.
+//     (2, 1, 32), (4, 1, 64): 4096 heads of 32 x 129 44, 57, of 128 153, 173; 672 heads of 128 x 164 without the mask 0.87 of the time;
 //   up to six: (4, 1, 64) and (2, 2, 64), (4, 2, 64): 64 heads of 128 x 320 10.3, -, 14.7, without the mask 12.0, -, 17.9.
 // A general mask whose rows are not a multiple of four bytes is read byte by byte, which with one tile of 32 keys ahead hides
 // better: (2, 2, 32) and (2, 2, 64), (4, 2, 64), (4, 1, 64): 32 heads of 96 x 577 36, 53, 36, 48; 256 of 64 x 1030 454, 598, 490, 590.
@@ -1304,7 +1304,7 @@ static AttnForm attn_fwd_form(int dh, bool causal, bool masked, int s, int b, in
     f = split64;
   } else if (n > 6 && blocks64 <= (dh > 64 && (!causal || n <= 16) ? 2 : 4) * ncu) {
     f = split128;
-  } else if (n == 3 && one_wave_left) {
+  } else if (n == 3 && (one_wave_left || (blocks64 > 3 * ncu && blocks64 <= 10 * ncu))) {
     f = small;
   }
   return attn_wide_or(f, {2, 1, 32, false, true}, causal, s, b, heads, dh);
@@ -1398,25 +1398,28 @@ static int attn_bwd_dq_tiles_np(const bf16_t* qkv, const bf16_t* ctx, const bf16
 // heads 42, 46, 50, 53; 24 heads 52, 69, 54, 58; 32 heads 68, 87, 65, 64; 64 heads 122, 172, 129, 106; 32 heads of 64 36, 42, 40, 44;
 // 128 heads of 32 94, 102, 87, 76; 20 and 40 heads of 160 (first and last) 56, 69 and 101, 88; 16 heads of 128 without the mask 61,
 // 80, 56, 60.
-// One block of 64 rows, or three (all causal calls, and where the last one is one wave's): workgroups of 128 rows would be half empty.
+// One block of 64 rows, or three (all causal calls, where the last one is one wave's, and heads of up to 64 unless very many):
+// workgroups of 128 rows would be half empty.
 // us for the whole backward with (2, 1, 32), (4, 1, 64): 4096 heads of 32 x 129, causal, 154, 183; of 128 x 129 692, 788; 1024 of 64 x 64
 // 27.7, 29.8.
 static bool attn_bwd_small(int dh, bool causal, int s, long long blocks64, long long ncu) {
   const int n = (s + 63) / 64;
-  return dh <= 128 && ((n == 1 && blocks64 > 2 * ncu) || (n == 3 && blocks64 > (causal && dh == 64 ? 2 : 3) * ncu && (causal || (s % 128 > 0 && s % 128 <= 32))));
+  return dh <= 128 && ((n == 1 && blocks64 > 2 * ncu) || (n == 3 && blocks64 > (causal && dh == 64 ? 2 : 3) * ncu &&
+                                                                      (causal || (s % 128 > 0 && s % 128 <= 32) || (dh <= 64 && blocks64 <= 10 * ncu))));
 }
-static AttnForm attn_dq_form(int dh, bool causal, int s, int b, int heads) {
+// Heads of 32 under a mask read byte by byte stay in two groups: 512 heads x 333 196, (4, 1, 64) 232.
+static AttnForm attn_dq_form(int dh, bool causal, bool masked, int s, int b, int heads) {
   const int n = (s + 63) / 64;
   const long long blocks64 = (long long)n * heads * b, ncu = attn_compute_units();
   AttnForm f = {2, 2, 32, false, false};
   if (attn_bwd_small(dh, causal, s, blocks64, ncu)) f = {2, 1, 32, false, false};
-  else if (blocks64 > (dh > 64 || (causal && n <= 6) ? 3 : 4) * ncu) f = {4, 1, 64, false, false};
+  else if (blocks64 > (dh > 64 || (causal && n <= 6) ? 3 : 4) * ncu && !(dh == 32 && masked && (s & 3))) f = {4, 1, 64, false, false};
   return attn_wide_or(f, {2, 1, 32, false, true}, causal, s, b, heads, dh);
 }
 template <int DH, bool CAUSAL>
 static int attn_bwd_dq_t(const bf16_t* qkv, const bf16_t* ctx, const bf16_t* dctx, const float* lse, float* delta, bf16_t* dqkv, int s,
                          int b, int heads, const uint8_t* mask, hipStream_t stream) {
-  const AttnForm f = attn_dq_form(DH, CAUSAL, s, b, heads);
+  const AttnForm f = attn_dq_form(DH, CAUSAL, !CAUSAL && mask != nullptr, s, b, heads);
   if (f.wide) return attn_bwd_dq_tiles_np<DH, CAUSAL, 2, 1, 32, true>(qkv, ctx, dctx, lse, delta, dqkv, s, b, heads, mask, stream);
   if constexpr (DH <= 128)
     if (f.w == 2 && f.groups == 1) return attn_bwd_dq_tiles_np<DH, CAUSAL, 2, 1, 32>(qkv, ctx, dctx, lse, delta, dqkv, s, b, heads, mask, stream);
@@ -1477,7 +1480,7 @@ static int attn_bwd_dkv_t(const bf16_t* qkv, const bf16_t* dctx, const float* ls
 }
 void attn_form_query(int kernel, int causal, int masked, int s, int b, int heads, int dh, int* rows, int* groups, int* tile, int* wide) {
   const AttnForm f = kernel == PTDP_ATTN_KERNEL_FWD ? attn_fwd_form(dh, causal != 0, !causal && masked, s, b, heads)
-                     : kernel == PTDP_ATTN_KERNEL_DQ ? attn_dq_form(dh, causal != 0, s, b, heads) : attn_dkv_form(dh, causal != 0, s, b, heads);
+                     : kernel == PTDP_ATTN_KERNEL_DQ ? attn_dq_form(dh, causal != 0, !causal && masked, s, b, heads) : attn_dkv_form(dh, causal != 0, s, b, heads);
   *rows = 32 * f.w;
   *groups = f.groups;
   *tile = f.tile;
