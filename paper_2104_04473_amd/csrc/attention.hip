@@ -1008,8 +1008,8 @@ template <int DH, bool CAUSAL, int KW, int NP, int QT, bool SPLIT> struct DkvGeo
   static constexpr int kSums = NP > 1 ? KW * 2 * (DH / 2) * 64 * (int)sizeof(float) : 0;
   static constexpr int lds_bytes(bool masked) { return NP * 2 * stage_bytes(masked) > kSums ? NP * 2 * stage_bytes(masked) : kSums; }
 };
-// Causal heads of 64 in tiles of 32: 168 registers instead of 171 (three spilled) leave three waves on a SIMD (whole backward of 32 heads x 2048 93 ->
-// 87 us; in tiles of 64 30 heads x 4 x 777 83 -> 86, and without the causal mask it spills).
+// Causal heads of 64 in tiles of 32: 168 registers instead of 171 (three spilled) leave three waves on a SIMD (whole backward of 32 heads x 2048 98 ->
+// 89 us, 24 heads 75, 76, 60 x 777 40.5, 38.8; in tiles of 64 30 heads x 4 x 777 83 -> 86, and without the causal mask it spills).
 template <int DH, bool CAUSAL, int KW, int NP, int QT, bool SPLIT, bool WIDE>
 __global__ void __launch_bounds__(64 * KW * (SPLIT ? 2 : 1) * NP, WIDE ? 1 : CAUSAL && DH == 64 && QT == 32 ? 3 : 2)
 attn_bwd_dkv_tiles(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ dctx, const float* __restrict__ lse,
