@@ -748,24 +748,26 @@ template <bool KSLOW, int ROWS> struct SmallLoad {
     constexpr int per = 512 / ROWS;   // k-rows per wave-load
     return (wave * L + i) * per + lane / (64 / per);
   }
-  __device__ __forceinline__ void init(size_t ld, int rows_left, int wave, int lane) {
+  // row0: first row of the tile in the block that the descriptor starts at
+  __device__ __forceinline__ void init(size_t ld, int rows_left, int wave, int lane, int row0 = 0) {
 #pragma unroll
     for (int i = 0; i < L; ++i) {
       const int k = kpos(i, wave, lane);
       if (!KSLOW) {
-        const int row = (wave * L + i) * 8 + (lane >> 3);
+        const int row = row0 + (wave * L + i) * 8 + (lane >> 3);
         off[i] = row < rows_left ? (uint32_t)(((size_t)row * ld + k) * 2) - i * 1024u : kOob;
       } else {
         const int chunk = (lane & (ROWS / 8 - 1)) ^ kslow_swizzle<ROWS>(k);
-        off[i] = chunk * 8 < rows_left ? (uint32_t)(((size_t)k * ld + chunk * 8) * 2) - i * 1024u : kOob;
+        off[i] = row0 + chunk * 8 < rows_left ? (uint32_t)(((size_t)k * ld + row0 + chunk * 8) * 2) - i * 1024u : kOob;
       }
     }
     kstep = KSLOW ? (uint32_t)(BK * ld * 2) : (uint32_t)(BK * 2);
     plain = ld >= 128;
   }
-  __device__ __forceinline__ void issue(rsrc_t r, char* tile, int wave, int lane, int kt, int kend) const {
+  // LEAN: the caller knows that the k-tile lies inside K whole and that plain is set
+  template <bool LEAN = false> __device__ __forceinline__ void issue(rsrc_t r, char* tile, int wave, int lane, int kt, int kend) const {
     char* dst = tile + wave * L * 1024;
-    if (plain && (kt + 1) * BK <= kend) {
+    if (LEAN || (plain && (kt + 1) * BK <= kend)) {
       if constexpr (L == 4) load_lds_16x4(r, dst, off[0], off[1], off[2], off[3], (uint32_t)kt * kstep);
       else load_lds_16x2(r, dst, off[0], off[1], (uint32_t)kt * kstep);
     } else {
@@ -792,6 +794,14 @@ template <bool KSLOW, int ROWS> struct SmallRead {
         const int n0 = w0 + i * 16 + 4 * (r & 3), k = 8 * G + (r >> 2);
         base[i] = lds_offset(smem) + k * (ROWS * 2) + (((n0 >> 3) ^ kslow_swizzle<ROWS>(k)) * 16) + (n0 & 7) * 2;
       }
+    }
+  }
+  // to another stage; opaque, so that what follows stays in the reads' offset fields
+  __device__ __forceinline__ void move(int bytes) {
+#pragma unroll
+    for (int i = 0; i < (KSLOW ? NB : 2); ++i) {
+      base[i] += bytes;
+      asm("" : "+v"(base[i]));
     }
   }
   __device__ __forceinline__ bf16x8_t get(uint32_t at, int i, int ks) const {
@@ -919,6 +929,203 @@ __device__ __forceinline__ void gemm_small_tile(const GemmArgs& g, void* Cv, int
     col[b] = wn + b * 32;
   }
   gemm_epilogue<OUT, BM, BN, NS, RB>(acc, row, col, Cv, g.ldc, g.bias, g.M, g.N, m0, n0);
+}
+
+// ------------------------------------------------------------------------------------------------
+// 256 x 128 tiles (NN and NT), for outputs that give about one or two of them per compute unit and too few of 256 x 256.
+// Two groups of four waves take alternate k-tiles of 64, 128 x 64 outputs to a wave as in the 256 x 256 kernel (64 x 64
+// to a wave, as in 128 x 128 tiles, reads a third more from LDS per product and cannot keep up with the MFMAs), and
+// their sums meet in LDS at the end.  A k-tile is the 256 x 256 kernel's four phases, each a memory part and an
+// arithmetic part with a barrier behind it; the second group runs kWideLag parts behind the first, so that on every SIMD
+// one wave computes while the other reads and requests.
+// Three k-tiles of 48 KiB are in LDS; k-tile t is in stage t % 3 and belongs to group t % 2.  A half-tile's place is
+// free once its group has read it, and the group refills it a phase later, with the same half-tile of k-tile t + 3:
+//   phase:     0             1             2             3
+//   reads      A0(t)         B1(t)         A1(t)         B0(t+2)      (fragments)
+//   requests   B0(t+3)       A0(t+3)       B1(t+3)       A1(t+3)      (half-tiles: 2, 4, 2, 4 loads a wave)
+//   computes   A0 x B0       A0 x B1       A1 x B1       A1 x B0
+// The other group reads it 6 + kWideLag parts after the request (first group; 14 - kWideLag for the second): the last
+// memory part in front of that which the requesting wave has is four phases, twelve loads, after the request, so each
+// waits for all but its twelve youngest loads.
+// Bound by MFMA issue on few compute units (0.53 us per k-tile, operands in the caches), by the clock that power allows and
+// the way from L2 to LDS with all of them (0.73, operands from memory 0.80), against 0.83 and 1.0 for two 128 x 128 tiles.
+// us, operands from memory, before (128 x 128 tiles; the last split along k) and now: 2048 x 4096 x 4096 NN 69.4 -> 59.0, NT 67.4 -> 58.4;
+// 2048 x 3072 x 4096 67.7 -> 57.9; 1008 x 5120 x 2560 42.8 -> 36.8; 1008 x 7680 x 5120 78.4 -> 72.8.
+// ------------------------------------------------------------------------------------------------
+constexpr int kWideM = 256, kWideN = 128, kWideLag = 3;
+constexpr int kWideStage = (kWideM + kWideN) * BK * 2, kWideSmem = 3 * kWideStage;
+template <bool TB>
+__device__ __forceinline__ void gemm_wide_tile(const GemmArgs& g, void* Cv, int m0, int n0, char* smem) {
+  const int lane = threadIdx.x & 63, wave8 = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wave = wave8 & 3, grp = wave8 >> 2;
+  const bf16_t* a_base = g.A + (size_t)m0 * g.lda;
+  const bf16_t* b_base = TB ? g.B + n0 : g.B + (size_t)n0 * g.ldb;
+  const size_t a_left = (size_t)(g.a_end - reinterpret_cast<const char*>(a_base));
+  const size_t b_left = (size_t)(g.b_end - reinterpret_cast<const char*>(b_base));
+  const rsrc_t ra = make_rsrc(a_base, (uint32_t)(a_left < 0x7fffffffu ? a_left : 0x7fffffffu));
+  const rsrc_t rb = make_rsrc(b_base, (uint32_t)(b_left < 0x7fffffffu ? b_left : 0x7fffffffu));
+  const int steps = ((g.K + BK - 1) / BK + 1) / 2;   // group grp takes k-tiles 2 * step + grp; past the end they are zeros
+
+  SmallLoad<false, 128> la[2];
+  SmallLoad<TB, 64> lb[2];
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    la[h].init(g.lda, g.M - m0, wave, lane, h * 128);
+    lb[h].init(g.ldb, g.N - n0, wave, lane, h * 64);
+  }
+  SmallRead<false, 128> fa;
+  SmallRead<TB, 64> fb;
+  fa.init(smem, (wave >> 1) * 64, lane);
+  fb.init(smem, (wave & 1) * 32, lane);
+  // byte offsets of the half-tiles in a stage: A0, A1 (128 rows), B0, B1 (64)
+  constexpr int kA = 128 * BK * 2, kB = 64 * BK * 2, kB0 = 2 * kA;
+
+  auto barrier = [] {
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("s_barrier" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  auto wait_loads = [] { asm volatile("s_waitcnt vmcnt(12)" ::: "memory"); };   // all but the youngest k-tile's
+  auto request = [&](int kt, int stage) {
+    char* at = smem + stage * kWideStage;
+    lb[0].template issue<false>(rb, at + kB0, wave, lane, kt, g.K);
+    la[0].template issue<false>(ra, at, wave, lane, kt, g.K);
+    lb[1].template issue<false>(rb, at + kB0 + kB, wave, lane, kt, g.K);
+    la[1].template issue<false>(ra, at + kA, wave, lane, kt, g.K);
+  };
+  StripAcc<4, 4> acc;
+  zero_acc<4, 4>(acc);
+  bf16x8_t af[4][2], bfr[2][2][2];
+  auto read_a = [&](uint32_t at) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks) af[i][ks] = fa.get(at, i, ks);
+  };
+  auto read_b = [&](bf16x8_t (&f)[2][2], uint32_t at) {
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks) f[j][ks] = fb.get(at, j, ks);
+  };
+  auto compute = [&](f32x4_t (&c)[4][2], const bf16x8_t (&b)[2][2]) {
+    __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) c[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[j][ks], af[i][ks], c[i][j], 0, 0, 0);
+    __builtin_amdgcn_s_setprio(0);
+  };
+
+  // as if by the k-tiles in front of the first: the group refills what the other one reads next
+  if (grp == 1) {
+    request(0, 0);
+    request(2, 2);
+    wait_loads();   // k-tile 0
+  } else {
+    request(1, 1);
+  }
+  barrier();
+  if (grp == 1) {
+#pragma unroll
+    for (int i = 0; i < kWideLag; ++i) barrier();
+  }
+  int stage = grp;   // of the group's current k-tile
+  fa.move(stage * kWideStage);
+  fb.move(stage * kWideStage);
+  read_b(bfr[0], kB0);
+  auto tile = [&](auto parity, auto lean, int kt) {
+    constexpr int S = decltype(parity)::value, O = S ^ 1;
+    constexpr bool LEAN = decltype(lean)::value;
+    char* own = smem + stage * kWideStage;
+    const int step = stage == 0 ? 2 * kWideStage : -kWideStage;   // to the stage of the group's next k-tile
+    stage = stage == 0 ? 2 : stage - 1;
+    // phase 0
+    read_a(0);
+    lb[0].template issue<LEAN>(rb, own + kB0, wave, lane, kt + 3, g.K);
+    wait_loads();
+    barrier();
+    compute(acc[0], bfr[S]);
+    barrier();
+    // phase 1
+    read_b(bfr[O], kB0 + kB);
+    la[0].template issue<LEAN>(ra, own, wave, lane, kt + 3, g.K);
+    wait_loads();
+    barrier();
+    compute(acc[1], bfr[O]);
+    barrier();
+    // phase 2
+    read_a(kA);
+    fa.move(step);
+    lb[1].template issue<LEAN>(rb, own + kB0 + kB, wave, lane, kt + 3, g.K);
+    wait_loads();
+    barrier();
+    compute(acc[3], bfr[O]);
+    barrier();
+    // phase 3
+    fb.move(step);
+    read_b(bfr[O], kB0);
+    la[1].template issue<LEAN>(ra, own + kA, wave, lane, kt + 3, g.K);
+    wait_loads();
+    barrier();
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    compute(acc[2], bfr[S]);
+    barrier();
+  };
+  constexpr std::integral_constant<int, 0> even{};
+  constexpr std::integral_constant<int, 1> odd{};
+  // every k-tile requested here (up to 2 i + 6) lies inside K whole
+  const int lean = la[0].plain && lb[0].plain ? max(0, min((g.K / BK - 6 + 3) / 4 * 2, steps / 2 * 2)) : 0;
+  int i = 0;
+  for (; i < lean; i += 2) {
+    tile(even, std::true_type{}, 2 * i + grp);
+    tile(odd, std::true_type{}, 2 * i + 2 + grp);
+  }
+  for (; i + 1 < steps; i += 2) {
+    tile(even, std::false_type{}, 2 * i + grp);
+    tile(odd, std::false_type{}, 2 * i + 2 + grp);
+  }
+  if (i < steps) tile(even, std::false_type{}, 2 * i + grp);
+  if (grp == 0) {
+#pragma unroll
+    for (int q = 0; q < kWideLag; ++q) barrier();
+  }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the requests past the last k-tile (zeros) have landed
+  __syncthreads();
+  // the groups' sums meet in LDS: group 0 finishes strips 0 and 1, group 1 strips 2 and 3; register r of lane l of wave w at sum[w][r][l]
+  f32x4_t* sum = reinterpret_cast<f32x4_t*>(smem) + lane;
+  f32x4_t mine[2][4][2];
+#pragma unroll
+  for (int b = 0; b < 2; ++b)
+#pragma unroll
+    for (int r = 0; r < 8; ++r) {
+      const f32x4_t lo = acc[b][r >> 1][r & 1], hi = acc[2 + b][r >> 1][r & 1];
+      sum[(((grp ^ 1) * 4 + wave) * 16 + b * 8 + r) * 64] = grp == 0 ? hi : lo;
+      mine[b][r >> 1][r & 1] = grp == 0 ? lo : hi;
+    }
+  __syncthreads();
+#pragma unroll
+  for (int b = 0; b < 2; ++b)
+#pragma unroll
+    for (int r = 0; r < 8; ++r) {
+      const f32x4_t other = sum[((grp * 4 + wave) * 16 + b * 8 + r) * 64];
+      mine[b][r >> 1][r & 1] += other;
+    }
+  const int rm = grp * 128 + (wave >> 1) * 64, cn = (wave & 1) * 32;
+  const int row[2] = {rm, rm}, col[2] = {cn, cn + 64};
+  gemm_epilogue<OUT_BF16, kWideM, kWideN, 2, 4>(mine, row, col, Cv, g.ldc, g.bias, g.M, g.N, m0, n0);
+}
+
+template <bool TB>
+__global__ void __launch_bounds__(kGemmThreads)
+gemm_bf16_wide_kernel(GemmArgs g, void* Cv) {
+  extern __shared__ __attribute__((aligned(1024))) char smem[];
+  const int tiles_m = (g.M + kWideM - 1) / kWideM, tiles_n = (g.N + kWideN - 1) / kWideN, tiles = tiles_m * tiles_n;
+  const int id = blockIdx.x, per_xcd = (tiles + 7) / 8, t = (id & 7) * per_xcd + (id >> 3);   // numbered as below
+  if ((id >> 3) >= per_xcd || t >= tiles) return;
+  const int grp = t / (8 * tiles_n), in_grp = t - grp * 8 * tiles_n, gm = min(8, tiles_m - grp * 8);
+  gemm_wide_tile<TB>(g, Cv, (grp * 8 + in_grp % gm) * kWideM, (in_grp / gm) * kWideN, smem);
 }
 
 // Tiles are numbered in groups of 8 row tiles, column by column inside a group; each XCD takes one contiguous run, so
@@ -1109,6 +1316,14 @@ static int launch_small(const GemmArgs& g, void* C, hipStream_t st) {
   hipLaunchKernelGGL(kern, dim3(blocks), dim3(KG * kSmallThreads), smem, st, g, C);
   return PTDP_OK;
 }
+template <bool TB>
+static int launch_wide(const GemmArgs& g, void* C, hipStream_t st) {
+  auto kern = gemm_bf16_wide_kernel<TB>;
+  static once_flag_t done[kMaxDevices];
+  if (set_dynamic_smem(reinterpret_cast<const void*>(kern), kWideSmem, done) != PTDP_OK) return PTDP_E_HIP;
+  hipLaunchKernelGGL(kern, dim3(small_blocks<kWideM, kWideN>(g.M, g.N)), dim3(kGemmThreads), kWideSmem, st, g, C);
+  return PTDP_OK;
+}
 template <bool TA, bool TB, int OUT>
 static int launch_small_form(int form, const GemmArgs& g, void* C, hipStream_t st) {
   switch (form) {
@@ -1116,7 +1331,10 @@ static int launch_small_form(int form, const GemmArgs& g, void* C, hipStream_t s
     case 1: return launch_small<TA, TB, OUT, 128, 128, 2, 2>(g, C, st);
     case 2: return launch_small<TA, TB, OUT, 128, 64, 3, 2>(g, C, st);
     case 3: return launch_small<TA, TB, OUT, 64, 64, 4, 2>(g, C, st);
-    default: return launch_small<TA, TB, OUT, 128, 64, 2, 1>(g, C, st);
+    case 4: return launch_small<TA, TB, OUT, 128, 64, 2, 1>(g, C, st);
+    default:
+      if constexpr (!TA) return launch_wide<TB>(g, C, st);
+      else return PTDP_E_STATE;   // small_form offers it to NN and NT alone
   }
 }
 // several problems, see gemm_bf16_dp_multi_kernel; a.start is filled here
@@ -1244,19 +1462,26 @@ struct SmallCost {
   int bm, bn, groups, per_cu;
   double fixed, pair, single, each, per_mb;
 };
-constexpr int kSmallForms = 5;
+constexpr int kSmallForms = 6;   // TN has no 256 x 128 tiles: with += they are slower than both neighbours (4096 x 4096 x 2048 90 us, 80 and 81)
 static const SmallCost kSmallCost[2][kSmallForms] = {
-    {{128, 128, 1, 2, 1.9, 0.741, 0.515, 2.1, 0.135},    // (most calls of 64 to 256 large tiles)
+    {{128, 128, 1, 2, 1.9, 0.741, 0.515, 2.1, 0.135},    // (most calls of 64 to 256 large tiles with short k ranges)
      {128, 128, 2, 1, 0.0, 0.0, 0.992, 3.1, 0.102},      // two wave groups share the k range: long k, at most one workgroup per CU
      {128, 64, 2, 1, 0.0, 0.0, 0.576, 3.9, 0.079},
      {64, 64, 2, 1, 0.7, 0.0, 0.372, 2.7, 0.103},        // the smallest outputs
-     {128, 64, 1, 2, 2.4, 0.548, 0.422, 0.9, 0.157}},
+     {128, 64, 1, 2, 2.4, 0.548, 0.422, 0.9, 0.157},
+     {256, 128, 2, 1, 2.3, 0.0, 1.48, 7.2, 0.03}},       // 80 to 128 large tiles (about one workgroup per CU), and the like in more rounds
     {{128, 128, 1, 2, 0.0, 0.742, 0.570, 5.8, 0.163},
      {128, 128, 2, 1, 0.0, 0.0, 0.995, 6.6, 0.127},
      {128, 64, 2, 1, 0.4, 0.0, 0.573, 4.7, 0.072},
      {64, 64, 2, 1, 0.9, 0.0, 0.388, 3.4, 0.087},
-     {128, 64, 1, 2, 1.4, 0.510, 0.356, 2.8, 0.159}}};
+     {128, 64, 1, 2, 1.4, 0.510, 0.356, 2.8, 0.159},
+     {256, 128, 2, 1, 0.0, 0.0, 0.0, 0.0, 0.0}}};
 constexpr int kMinStepsForGroups = 8;   // k-tiles from which two wave groups are considered: below, joining their sums costs what they save
+// k-tiles up to which 256 x 128 tiles are considered: longer products are faster on 256 x 256 tiles whose k range is split (us for
+// 256 x 128 and split: 2048 x 4096 x 12288 NT 168, 163; x 16384 NN 211, 209, NT 215, 206).  Of 1409 calls (those of
+// profiles/gemm_forms.txt and layers of 48 to 8192 tokens) they are picked in 45 and take 0.86 of the time of the form picked
+// before on average, 0.985 at most.
+constexpr int kWideSteps = 120;
 // Not considered with that many workgroups per CU over that many k-tiles: the panels no longer stay in the caches and the time is
 // up to 1.6 times the above (128 x 64, 16 workgroups, 100 k-tiles).
 constexpr int kManyRounds = 16, kManySteps = 32;
@@ -1264,9 +1489,10 @@ constexpr int kManyRounds = 16, kManySteps = 32;
 static int small_form(int rmw, int n, const int* M, const int* N, int K, double t_large) {
   const int ncu = compute_units(), nk = (K + BK - 1) / BK;
   int best = -1;
-  for (int f = 0; f < kSmallForms; ++f) {
+  for (int f = 0; f < (rmw ? kSmallForms - 1 : kSmallForms); ++f) {
     const SmallCost& c = kSmallCost[rmw][f];
     if (c.groups > 1 && nk < kMinStepsForGroups) continue;
+    if (c.bm == kWideM && nk > kWideSteps) continue;
     long long tiles = 0;
     double mb = 0.0;
     for (int j = 0; j < n; ++j) {

@@ -113,6 +113,30 @@ def test_gemm_small_tiles(mode, tile, M, N, K):
         assert bool(((c.double() - want).abs() <= 2.0 ** -8 * want.abs() + 2.0 ** -22 * K).all())
 
 
+# 256 x 128 tiles: whole tiles, a few rows or columns in the last one, k-tiles per group of waves odd and even, the last one whole,
+# partial and missing, requests in the lean form up to the end and not
+WIDE_TILES = [(2048, 4096, 3072), (2040, 4088, 4104), (1000, 7656, 4168), (264, 16376, 1544), (264, 16376, 1736), (520, 10248, 1920 - 8)]
+
+
+@pytest.mark.parametrize("mode", [B.GEMM_NN, B.GEMM_NT])
+@pytest.mark.parametrize("M,N,K", WIDE_TILES)
+def test_gemm_wide_tiles(mode, M, N, K):
+    assert form(mode, M, N, K, 0, 0, 1, B.ptdp_gemm_workspace_bytes()) == (256, 128, 2)
+    a, b, bias = randn((M, K), B.BF16, 1), randn((K, N), B.BF16, 2), randn((N,), B.BF16, 3)
+    Bm = b.t().contiguous() if mode == B.GEMM_NT else b
+    guard = torch.full((M + 2, N), 9.0, dtype=torch.bfloat16, device="cuda")   # rows in front of and behind C stay as they are
+    c = guard[1:M + 1]
+    ws = torch.zeros(B.ptdp_gemm_workspace_bytes(), dtype=torch.uint8, device="cuda")
+    for _ in range(2):
+        B.check(B.ptdp_gemm(B.BF16, mode, a.data_ptr(), Bm.data_ptr(), c.data_ptr(), bias.data_ptr(), M, N, K, 0, 0, ws.data_ptr(),
+                            ws.numel(), stream()), "gemm")
+    sync()
+    want = a.double() @ b.double() + bias.double()
+    # bf16 rounding of the result (2^-9 of its size) plus the fp32 sums' error, as for the small tiles
+    assert bool(((c.double() - want).abs() <= 2.0 ** -8 * want.abs() + 2.0 ** -22 * K).all())
+    assert bool((guard[0] == 9.0).all()) and bool((guard[M + 1] == 9.0).all())
+
+
 @pytest.mark.parametrize("out_f32,accumulate", [(0, 0), (1, 0), (1, 1)])
 @pytest.mark.parametrize("N", [(1 << 21) - 8, (1 << 21) + 8, (1 << 22) + 8])
 def test_gemm_rows_of_c_beyond_31_bit_offsets(out_f32, accumulate, N):
