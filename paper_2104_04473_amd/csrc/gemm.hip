@@ -53,14 +53,14 @@ template <bool V> struct F32Operand {
   }
 };
 constexpr int f32_most_waves(int nb) { return nb == 1 ? 8 : 4; }   // waves that share a tile's k range
+// One tile by the workgroup's first kg waves (the others only take part in the end).
 template <bool VA, bool VB, int NB>
-__global__ void __launch_bounds__(64 * f32_most_waves(NB))
-gemm_f32_kernel(const float* __restrict__ A, const float* __restrict__ B, float* C, const float* __restrict__ bias,
-                int M, int N, int K, size_t a_rs, size_t a_cs, size_t b_rs, size_t b_cs, int accumulate) {
-  extern __shared__ __attribute__((aligned(16))) float part[];
+__device__ __forceinline__ void gemm_f32_tile(const float* __restrict__ A, const float* __restrict__ B, float* C, const float* __restrict__ bias,
+                                              int M, int N, int K, size_t a_rs, size_t a_cs, size_t b_rs, size_t b_cs, int accumulate,
+                                              int tile_m, int tile_n, int kg, float* part) {
   constexpr int kTile = 32 * NB, kPitch = kTile + 8;   // rows 4 apart (the two halves of a register) in different banks
-  const int wave = threadIdx.x >> 6, kg = blockDim.x >> 6, lane = threadIdx.x & 63, l31 = lane & 31, half = lane >> 5;
-  const int m0 = blockIdx.y * kTile, n0 = blockIdx.x * kTile;
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, l31 = lane & 31, half = lane >> 5;
+  const int m0 = tile_m * kTile, n0 = tile_n * kTile;
   F32Operand<VA> oa[NB];
   F32Operand<VB> ob[NB];
 #pragma unroll
@@ -106,7 +106,7 @@ gemm_f32_kernel(const float* __restrict__ A, const float* __restrict__ B, float*
           for (int j = 0; j < NB; ++j)
             acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[set][i][q][e], fb[set][j][q][e], acc[i][j], 0, 0, 0);
   };
-  int k = wave * kF32Chunk;
+  int k = wave < kg ? wave * kF32Chunk : K;
   load(0, k);
   for (; k < K; k += 2 * step) {
     load(1, k + step);
@@ -116,12 +116,14 @@ gemm_f32_kernel(const float* __restrict__ A, const float* __restrict__ B, float*
     multiply(1);
   }
   float* mine = part + wave * (kTile * kPitch);
+  if (wave < kg) {
 #pragma unroll
-  for (int i = 0; i < NB; ++i)
+    for (int i = 0; i < NB; ++i)
 #pragma unroll
-    for (int j = 0; j < NB; ++j)
+      for (int j = 0; j < NB; ++j)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) mine[(i * 32 + 8 * (r >> 2) + 4 * half + (r & 3)) * kPitch + j * 32 + l31] = acc[i][j][r];
+        for (int r = 0; r < 16; ++r) mine[(i * 32 + 8 * (r >> 2) + 4 * half + (r & 3)) * kPitch + j * 32 + l31] = acc[i][j][r];
+  }
   __syncthreads();
   for (int x = threadIdx.x; x < kTile * kTile; x += blockDim.x) {
     const int r = x / kTile, c = x % kTile, m = m0 + r, n = n0 + c;
@@ -132,6 +134,13 @@ gemm_f32_kernel(const float* __restrict__ A, const float* __restrict__ B, float*
     float* o = C + (size_t)m * N + n;
     *o = accumulate ? *o + v : v;
   }
+}
+template <bool VA, bool VB, int NB>
+__global__ void __launch_bounds__(64 * f32_most_waves(NB))
+gemm_f32_kernel(const float* __restrict__ A, const float* __restrict__ B, float* C, const float* __restrict__ bias,
+                int M, int N, int K, size_t a_rs, size_t a_cs, size_t b_rs, size_t b_cs, int accumulate) {
+  extern __shared__ __attribute__((aligned(16))) float part[];
+  gemm_f32_tile<VA, VB, NB>(A, B, C, bias, M, N, K, a_rs, a_cs, b_rs, b_cs, accumulate, blockIdx.y, blockIdx.x, blockDim.x >> 6, part);
 }
 
 // The same on one 16 x 16 tile (v_mfma_f32_16x16x4_f32), for outputs of fewer 32 x 32 tiles than the chip has compute units, where
@@ -158,13 +167,12 @@ template <bool V> struct F32Operand16 {
 };
 constexpr int kF32TinyWaves = 8, kF32TinyAhead = 4;
 template <bool VA, bool VB>
-__global__ void __launch_bounds__(64 * kF32TinyWaves)
-gemm_f32_tiny_kernel(const float* __restrict__ A, const float* __restrict__ B, float* C, const float* __restrict__ bias,
-                     int M, int N, int K, size_t a_rs, size_t a_cs, size_t b_rs, size_t b_cs, int accumulate) {
-  __shared__ float part[kF32TinyWaves][16][17];
+__device__ __forceinline__ void gemm_f32_tiny_tile(const float* __restrict__ A, const float* __restrict__ B, float* C, const float* __restrict__ bias,
+                                                   int M, int N, int K, size_t a_rs, size_t a_cs, size_t b_rs, size_t b_cs, int accumulate,
+                                                   int tile_m, int tile_n, float (*part)[16][17]) {
   // kg is kF32TinyWaves, read from the launch: as a constant the loops come out 1.5 % slower (a fp32 layer of 66 x 768)
   const int wave = threadIdx.x >> 6, kg = blockDim.x >> 6, lane = threadIdx.x & 63, l15 = lane & 15, q = lane >> 4;
-  const int m0 = blockIdx.y * 16, n0 = blockIdx.x * 16;
+  const int m0 = tile_m * 16, n0 = tile_n * 16;
   // rows past the end repeat the last one: their outputs are not written
   const F32Operand16<VA> oa{A + (size_t)min(m0 + l15, M - 1) * a_rs, a_cs};
   const F32Operand16<VB> ob{B + (size_t)min(n0 + l15, N - 1) * b_cs, b_rs};
@@ -200,6 +208,45 @@ gemm_f32_tiny_kernel(const float* __restrict__ A, const float* __restrict__ B, f
   float* o = C + (size_t)m * N + n;
   *o = accumulate ? *o + v : v;
 }
+template <bool VA, bool VB>
+__global__ void __launch_bounds__(64 * kF32TinyWaves)
+gemm_f32_tiny_kernel(const float* __restrict__ A, const float* __restrict__ B, float* C, const float* __restrict__ bias,
+                     int M, int N, int K, size_t a_rs, size_t a_cs, size_t b_rs, size_t b_cs, int accumulate) {
+  __shared__ float part[kF32TinyWaves][16][17];
+  gemm_f32_tiny_tile<VA, VB>(A, B, C, bias, M, N, K, a_rs, a_cs, b_rs, b_cs, accumulate, blockIdx.y, blockIdx.x, part);
+}
+
+// Weight gradients of one layer (C_j[M_j, N_j] += A_j^T B_j, sharing K) whose tiles have the same size as one launch: alone each is a
+// few microseconds of a part of the chip.  A workgroup's tile, the number of waves that share its k range (kg) and so every bit of
+// the result are those of a launch of its own.  A layer of 256 x 256 tokens: four launches 21.9 us, one 12.5 (the pass 130.3 -> 124.4).
+constexpr int kMaxMultiF32 = 4;
+struct MultiF32 {
+  const float *A[kMaxMultiF32], *B[kMaxMultiF32];
+  float* C[kMaxMultiF32];
+  int M[kMaxMultiF32], N[kMaxMultiF32], kg[kMaxMultiF32], start[kMaxMultiF32], n, K;   // start: first workgroup
+};
+template <bool TINY>
+__global__ void __launch_bounds__(64 * f32_most_waves(1))
+gemm_f32_multi_kernel(MultiF32 a) {
+  constexpr int kTile = TINY ? 16 : 32;
+  extern __shared__ __attribute__((aligned(16))) float part[];
+  const int id = (int)blockIdx.x;
+  // constant indices only: the arguments stay in scalar registers
+  const float *A = a.A[0], *B = a.B[0];
+  float* C = a.C[0];
+  int M = a.M[0], N = a.N[0], kg = a.kg[0], first = 0;
+#pragma unroll
+  for (int q = 1; q < kMaxMultiF32; ++q)
+    if (q < a.n && id >= a.start[q]) {
+      A = a.A[q]; B = a.B[q]; C = a.C[q];
+      M = a.M[q]; N = a.N[q]; kg = a.kg[q]; first = a.start[q];
+    }
+  const int tiles_n = (N + kTile - 1) / kTile, t = id - first;
+  if constexpr (TINY)
+    gemm_f32_tiny_tile<false, false>(A, B, C, nullptr, M, N, a.K, 1, M, N, 1, 1, t / tiles_n, t % tiles_n, reinterpret_cast<float (*)[16][17]>(part));
+  else
+    gemm_f32_tile<false, false, 1>(A, B, C, nullptr, M, N, a.K, 1, M, N, 1, 1, t / tiles_n, t % tiles_n, kg, part);
+}
 
 template <bool VA, bool VB, int NB>
 static int launch_gemm_f32_t(const float* A, const float* B, float* C, const float* bias, int M, int N, int K, size_t a_rs, size_t a_cs,
@@ -223,23 +270,81 @@ static int compute_units();
 // 1260 random calls with 257 to 512 tiles, time with 16 x 16 over time with 32 x 32 tiles, averages of outputs with a short side of
 // up to 32, 33 to 64, 65 to 100:  NN with no more columns than rows 0.83, 0.88, 0.87;  others with k up to 512 0.92, 0.84, 0.86;  to 1024 NN
 // and NT 1.00, 0.89, 0.88, TN 1.17, 0.99, 0.92;  to 4096 1.08, 1.02, 0.98;  beyond 1.08, 1.02, 0.95 (wider: 119 x 812 x 7783 TN 75, 81 us).
-template <bool VA, bool VB>
-static int launch_gemm_f32(const float* A, const float* B, float* C, const float* bias, int M, int N, int K, size_t a_rs, size_t a_cs,
-                           size_t b_rs, size_t b_cs, int accumulate, hipStream_t st) {
+struct F32Form {
+  int tile, kg;   // 16, 32 or 64 rows and columns; waves of a workgroup
+};
+static F32Form f32_form(bool va, bool vb, int M, int N, int K) {
   const long long ncu = compute_units(), t1 = (long long)((M + 31) / 32) * ((N + 31) / 32), t2 = (long long)((M + 63) / 64) * ((N + 63) / 64);
   const long long t16 = (long long)((M + 15) / 16) * ((N + 15) / 16);
   const int thin = M < N ? M : N;
-  const bool two_rounds = (VA && !VB && N <= M) || (thin > 64 && K <= 4096) || (thin > 32 && K <= (VA ? 1024 : 512));
-  if (K > kF32TinyWaves * kF32Chunk && (t16 <= ncu || (t16 <= 2 * ncu && two_rounds))) {
+  const bool two_rounds = (va && !vb && N <= M) || (thin > 64 && K <= 4096) || (thin > 32 && K <= (va ? 1024 : 512));
+  if (K > kF32TinyWaves * kF32Chunk && (t16 <= ncu || (t16 <= 2 * ncu && two_rounds))) return {16, kF32TinyWaves};
+  const bool big = t2 >= ncu;
+  int kg = f32_most_waves(big ? 2 : 1);
+  while (kg > 1 && (kg > (K + kF32Chunk - 1) / kF32Chunk || (big ? t2 : t1) * kg > 16 * ncu)) kg /= 2;
+  return {big ? 64 : 32, kg};
+}
+template <bool VA, bool VB>
+static int launch_gemm_f32(const float* A, const float* B, float* C, const float* bias, int M, int N, int K, size_t a_rs, size_t a_cs,
+                           size_t b_rs, size_t b_cs, int accumulate, hipStream_t st) {
+  const F32Form f = f32_form(VA, VB, M, N, K);
+  if (f.tile == 16) {
     hipLaunchKernelGGL((gemm_f32_tiny_kernel<VA, VB>), dim3((N + 15) / 16, (M + 15) / 16), dim3(64 * kF32TinyWaves), 0, st, A, B, C, bias, M, N, K,
                        a_rs, a_cs, b_rs, b_cs, accumulate);
     return PTDP_OK;
   }
-  const bool big = t2 >= ncu;
-  int kg = f32_most_waves(big ? 2 : 1);
-  while (kg > 1 && (kg > (K + kF32Chunk - 1) / kF32Chunk || (big ? t2 : t1) * kg > 16 * ncu)) kg /= 2;
-  if (big) return launch_gemm_f32_t<VA, VB, 2>(A, B, C, bias, M, N, K, a_rs, a_cs, b_rs, b_cs, accumulate, kg, st);
-  return launch_gemm_f32_t<VA, VB, 1>(A, B, C, bias, M, N, K, a_rs, a_cs, b_rs, b_cs, accumulate, kg, st);
+  if (f.tile == 64) return launch_gemm_f32_t<VA, VB, 2>(A, B, C, bias, M, N, K, a_rs, a_cs, b_rs, b_cs, accumulate, f.kg, st);
+  return launch_gemm_f32_t<VA, VB, 1>(A, B, C, bias, M, N, K, a_rs, a_cs, b_rs, b_cs, accumulate, f.kg, st);
+}
+
+template <bool TINY> static int launch_f32_multi(const MultiF32& a, int blocks, hipStream_t st) {
+  constexpr int kPart = (TINY ? 16 * 17 : 32 * 40) * (int)sizeof(float);   // a wave's partial tile
+  static once_flag_t done[kMaxDevices];
+  if (set_dynamic_smem(reinterpret_cast<const void*>(gemm_f32_multi_kernel<TINY>), f32_most_waves(1) * kPart, done) != PTDP_OK) return PTDP_E_HIP;
+  int kg = 1;
+  for (int j = 0; j < a.n; ++j) kg = a.kg[j] > kg ? a.kg[j] : kg;
+  hipLaunchKernelGGL(gemm_f32_multi_kernel<TINY>, dim3(blocks), dim3(64 * kg), kg * kPart, st, a);
+  return PTDP_OK;
+}
+// Weight gradients of a layer: those of 16 x 16 tiles and those of 32 x 32 tiles as one launch each, 64 x 64 tiles (which fill the
+// chip) one by one.
+static int launch_f32_tn_multi(int n, const void* const* A, const void* const* B, float* const* C, const int* M, const int* N, int K,
+                               hipStream_t st) {
+  MultiF32 m[2];
+  long long blocks[2] = {0, 0};
+  for (int x = 0; x < 2; ++x) {
+    m[x].n = 0;
+    m[x].K = K;
+  }
+  for (int j = 0; j < n; ++j) {
+    if (M[j] == 0 || N[j] == 0) continue;
+    const float *a = (const float*)A[j], *b = (const float*)B[j];
+    const F32Form f = f32_form(false, false, M[j], N[j], K);
+    if (f.tile == 64) {
+      const int rc = launch_gemm_f32_t<false, false, 2>(a, b, C[j], nullptr, M[j], N[j], K, 1, M[j], N[j], 1, 1, f.kg, st);
+      if (rc != PTDP_OK) return rc;
+      continue;
+    }
+    const int x = f.tile == 16 ? 0 : 1, q = m[x].n++;
+    m[x].A[q] = a;
+    m[x].B[q] = b;
+    m[x].C[q] = C[j];
+    m[x].M[q] = M[j];
+    m[x].N[q] = N[j];
+    m[x].kg[q] = f.kg;
+    m[x].start[q] = (int)blocks[x];
+    blocks[x] += (long long)((M[j] + f.tile - 1) / f.tile) * ((N[j] + f.tile - 1) / f.tile);
+  }
+  for (int x = 0; x < 2; ++x) {
+    if (m[x].n == 0) continue;
+    for (int q = m[x].n; q < kMaxMultiF32; ++q) {   // unused slots repeat the first (never selected)
+      m[x].A[q] = m[x].A[0]; m[x].B[q] = m[x].B[0]; m[x].C[q] = m[x].C[0];
+      m[x].M[q] = m[x].M[0]; m[x].N[q] = m[x].N[0]; m[x].kg[q] = m[x].kg[0]; m[x].start[q] = 0;
+    }
+    const int rc = x == 0 ? launch_f32_multi<true>(m[x], (int)blocks[x], st) : launch_f32_multi<false>(m[x], (int)blocks[x], st);
+    if (rc != PTDP_OK) return rc;
+  }
+  return PTDP_OK;
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -1666,10 +1771,10 @@ template <int OUT> static int launch_tn_multi(int form, MultiArgs& a, hipStream_
 int launch_gemm_tn_multi(int dtype, int n, const void* const* A, const void* const* B, float* const* C, const int* M,
                          const int* N, int K, hipStream_t st) {
   if (n <= 0 || n > kMaxMulti) return PTDP_E_INVALID_ARG;
-  bool one_by_one = dtype == PTDP_F32;
+  bool one_by_one = false;
   double flops = 0.0;
   for (int j = 0; j < n; ++j) {
-    if (M[j] == 0 || N[j] == 0 || (size_t)M[j] * K * 2 >= 0x7fffffffull || (size_t)N[j] * K * 2 >= 0x7fffffffull) one_by_one = true;
+    if (dtype == PTDP_BF16 && (M[j] == 0 || N[j] == 0 || (size_t)M[j] * K * 2 >= 0x7fffffffull || (size_t)N[j] * K * 2 >= 0x7fffffffull)) one_by_one = true;
     flops += 2.0 * K * (double)M[j] * N[j];
   }
   if (one_by_one) {
@@ -1680,6 +1785,10 @@ int launch_gemm_tn_multi(int dtype, int n, const void* const* A, const void* con
     return PTDP_OK;
   }
   Launch L(PTDP_K_GEMM_TN, flops, st);
+  if (dtype == PTDP_F32) {
+    const int rc = launch_f32_tn_multi(n, A, B, C, M, N, K, st);
+    return rc != PTDP_OK ? rc : L.status();
+  }
   MultiArgs a;
   a.n = n;
   int at = 0;

@@ -6,6 +6,7 @@ import torch
 
 from oracle import gpt_layer as L
 from paper_2104_04473_amd import binding as B
+from paper_2104_04473_amd import synth
 from gpu_util import assert_close, np64, randn, rel_l2, stream, sync
 
 pytestmark = pytest.mark.gpu
@@ -75,6 +76,33 @@ def test_attention_fp32(s, b, heads, dh, masked):
             # a query without a visible key has a log-sum-exp near -10^4, stored in fp32 to 2^-11: its probabilities (1/s
             # each) are off by that much, which only dv sees; the stated tolerance holds
             assert_close(got[..., lo:lo + hp], want[..., lo:lo + hp], B.F32, name, 1.0 if masked and name == "dv" else 0.1)
+
+
+# weight gradients in tiles of 16, of 32, of both sizes, of 32 with eight waves each, of 32 and 64
+@pytest.mark.parametrize("h,a,t,s,b", [(96, 3, 1, 300, 1), (64, 2, 1, 37, 3), (256, 8, 8, 300, 1), (256, 4, 1, 128, 2), (512, 8, 1, 65, 1)])
+def test_weight_gradients_fp32_together_and_one_by_one(h, a, t, s, b):
+    """A layer's four weight gradients run in shared launches: every bit is that of a call of its own with the same operands."""
+    hp, fp, T = h // t, 4 * h // t, s * b
+    cfg = B.make_cfg(h=h, a=a, t=t, s=s, b=b, dtype=B.F32, p_hidden=0.1, seed=5)
+    P, G = synth.layer_params(h, a, t, B.F32, seed=1, device="cuda"), synth.zero_grads(h, a, t, "cuda")
+    ch = B.Chunk(cfg, 1, 0)
+    ch.bind(0, P, G)
+    x, dy = synth.activations(s, b, h, B.F32, 2, "cuda"), synth.activations(s, b, h, B.F32, 3, "cuda")
+    y, dx = torch.empty_like(x), torch.empty_like(x)
+    stash = torch.empty(ch.stash_bytes(), dtype=torch.uint8, device="cuda")
+    ws = torch.empty(ch.workspace_bytes(), dtype=torch.uint8, device="cuda")
+    for g in G.values():
+        g.fill_(0.25)   # += : the old value counts
+    B.check(ch.forward(0, x.data_ptr(), y.data_ptr(), stash.data_ptr(), ws.data_ptr()), "forward")
+    B.check(ch.backward(0, dy.data_ptr(), dx.data_ptr(), stash.data_ptr(), ws.data_ptr()), "backward")
+    sync()
+    at, wat = B.stash_offsets(cfg), B.workspace_offsets(cfg)
+    for name, A, Bm, M, N in (("w_2", stash[at["G"]:], ws[wat["DMO"]:], fp, h), ("w_1", stash[at["U2"]:], ws[wat["DZ"]:], h, fp),
+                              ("w_qkv", stash[at["U"]:], ws[wat["DQKV"]:], h, 3 * hp), ("w_o", stash[at["CTX"]:], ws[wat["DO"]:], hp, h)):
+        want = torch.full((M, N), 0.25, device="cuda")
+        B.check(B.ptdp_gemm(B.F32, B.GEMM_TN, A.data_ptr(), Bm.data_ptr(), want.data_ptr(), None, M, N, T, 1, 1, None, 0, stream()), name)
+        sync()
+        assert torch.equal(G[name].view(M, N), want), name
 
 
 @pytest.mark.parametrize("bad", [float("inf"), float("nan")])
