@@ -207,15 +207,28 @@ attn_fwd_f32(const float* __restrict__ qkv, float* __restrict__ ctx, float* __re
   if (g == 0) lse[((size_t)j * heads + e) * s + my_q] = mall + __logf(lall);
 }
 
-// dQ of 16 queries, and their delta = sum_d dctx * ctx for the dK/dV kernel
+// delta = sum_d dctx * ctx of 16 rows (o, dc): the diagonal of ctx dctx^T, summed in the order of dP below: with one visible key
+// dP - delta is exactly zero.  Lane (c, g) holds it for row c if the tile's rows are columns, for rows 4 g + r otherwise.
+template <int ND> __device__ __forceinline__ float f32_delta_column(const F32Frag<ND>& o, const F32Frag<ND>& dc, int c) {
+  const f32x4_t x = f32_scores<ND>(o, dc);
+  const float mine = (c & 2) ? ((c & 1) ? x[3] : x[2]) : ((c & 1) ? x[1] : x[0]);
+  return __shfl(mine, (c >> 2) * 16 + c, 64);
+}
+template <int ND> __device__ __forceinline__ f32x4_t f32_delta_rows(const F32Frag<ND>& o, const F32Frag<ND>& dc, int g) {
+  const f32x4_t x = f32_scores<ND>(o, dc);
+  f32x4_t d;
+#pragma unroll
+  for (int r = 0; r < 4; ++r) d[r] = __shfl(x[r], 16 * g + 4 * g + r, 64);
+  return d;
+}
+
+// dQ of 16 queries, and (delta not NULL) their delta for the dK/dV kernel
 template <int ND>
-__global__ void __launch_bounds__(64 * kF32Waves)
-attn_bwd_dq_f32(const float* __restrict__ qkv, const float* __restrict__ ctx, const float* __restrict__ dctx,
-                const float* __restrict__ lse, float* __restrict__ delta, float* __restrict__ dqkv, int s, int b, int heads, int dh,
-                const uint8_t* __restrict__ mask, int causal) {
-  __shared__ f32x4_t part[(kF32Waves - 1) * ND * 64];
+__device__ __forceinline__ void f32_dq_block(const float* __restrict__ qkv, const float* __restrict__ ctx, const float* __restrict__ dctx,
+                                             const float* __restrict__ lse, float* __restrict__ delta, float* __restrict__ dqkv, int s, int b,
+                                             int heads, int dh, const uint8_t* __restrict__ mask, int causal, int blk, f32x4_t* part) {
   const int e = blockIdx.y, j = blockIdx.z, wave = threadIdx.x >> 6, lane = threadIdx.x & 63, c = lane & 15, g = lane >> 4;
-  const int q0 = ((int)gridDim.x - 1 - (int)blockIdx.x) * kF32Rows, my_q = q0 + c, qr = min(my_q, s - 1);
+  const int q0 = blk * kF32Rows, my_q = q0 + c, qr = min(my_q, s - 1);
   const int hp = heads * dh;
   const size_t rs = (size_t)b * 3 * hp;
   const float* base = qkv + (size_t)j * 3 * hp + (size_t)e * dh;
@@ -224,16 +237,13 @@ attn_bwd_dq_f32(const float* __restrict__ qkv, const float* __restrict__ ctx, co
   F32Frag<ND> q, dc;
   f32_load<ND>(q, base + (size_t)qr * rs, g, dh);
   f32_load<ND>(dc, dctx + out, g, dh);
-  // the diagonal of ctx dctx^T, summed in the order of dP below: with one visible key dP - D is exactly zero
   float D;
   {
     F32Frag<ND> o;
     f32_load<ND>(o, ctx + out, g, dh);
-    const f32x4_t x = f32_scores<ND>(o, dc);
-    const float mine = (c & 2) ? ((c & 1) ? x[3] : x[2]) : ((c & 1) ? x[1] : x[0]);
-    D = __shfl(mine, (c >> 2) * 16 + c, 64);
+    D = f32_delta_column<ND>(o, dc, c);
   }
-  if (wave == 0 && g == 0 && my_q < s) delta[stat] = D;
+  if (delta && wave == 0 && g == 0 && my_q < s) delta[stat] = D;
   const float L = lse[stat];
   f32x4_t acc[ND];
 #pragma unroll
@@ -262,22 +272,21 @@ attn_bwd_dq_f32(const float* __restrict__ qkv, const float* __restrict__ ctx, co
   f32_store<ND>(dqkv + (size_t)my_q * rs + (size_t)j * 3 * hp + (size_t)e * dh, acc, g, dh);
 }
 
-// dK, dV of 16 keys
-template <int ND>
-__global__ void __launch_bounds__(64 * kF32Waves)
-attn_bwd_dkv_f32(const float* __restrict__ qkv, const float* __restrict__ dctx, const float* __restrict__ lse,
-                 const float* __restrict__ delta, float* __restrict__ dqkv, int s, int b, int heads, int dh,
-                 const uint8_t* __restrict__ mask, int causal) {
-  __shared__ f32x4_t part[(kF32Waves - 1) * ND * 64];
+// dK, dV of 16 keys.  OWN_DELTA: the queries' delta is computed here as well (ctx), not read (delta).
+template <int ND, bool OWN_DELTA>
+__device__ __forceinline__ void f32_dkv_block(const float* __restrict__ qkv, const float* __restrict__ ctx, const float* __restrict__ dctx,
+                                              const float* __restrict__ lse, const float* __restrict__ delta, float* __restrict__ dqkv, int s,
+                                              int b, int heads, int dh, const uint8_t* __restrict__ mask, int causal, int blk, f32x4_t* part) {
   const int e = blockIdx.y, j = blockIdx.z, wave = threadIdx.x >> 6, lane = threadIdx.x & 63, c = lane & 15, g = lane >> 4;
-  const int k0 = (int)blockIdx.x * kF32Rows, my_key = k0 + c, kr = min(my_key, s - 1);
+  const int k0 = blk * kF32Rows, my_key = k0 + c, kr = min(my_key, s - 1);
   const int hp = heads * dh;
   const size_t rs = (size_t)b * 3 * hp, dors = (size_t)b * hp;
   const float* base = qkv + (size_t)j * 3 * hp + (size_t)e * dh;
   const float* dobase = dctx + (size_t)j * hp + (size_t)e * dh;
   const float scale = rsqrtf((float)dh);
   const float* lse_h = lse + ((size_t)j * heads + e) * s;
-  const float* delta_h = delta + ((size_t)j * heads + e) * s;
+  const float* delta_h = delta + ((size_t)j * heads + e) * s;   // (read unless OWN_DELTA)
+  const float* cbase = ctx + (size_t)j * hp + (size_t)e * dh;     // (read if OWN_DELTA)
   F32Frag<ND> k, v;
   f32_load<ND>(k, base + hp + (size_t)kr * rs, g, dh);
   f32_load<ND>(v, base + 2 * hp + (size_t)kr * rs, g, dh);
@@ -285,13 +294,18 @@ attn_bwd_dkv_f32(const float* __restrict__ qkv, const float* __restrict__ dctx, 
 #pragma unroll
   for (int t = 0; t < ND; ++t) dk[t] = dv[t] = f32x4_t{0.f, 0.f, 0.f, 0.f};
   const int ntiles = (s + kF32Rows - 1) / kF32Rows;
-  for (int qt = (causal ? (int)blockIdx.x : 0) + wave; qt < ntiles; qt += kF32Waves) {
+  for (int qt = (causal ? blk : 0) + wave; qt < ntiles; qt += kF32Waves) {
     const int q0 = qt * kF32Rows;
-    f32x4_t sc, dp, p, ds;
+    f32x4_t sc, dp, p, ds, own = {0.f, 0.f, 0.f, 0.f};
     {
       F32Frag<ND> q, dc;
       f32_load<ND>(q, base + (size_t)min(q0 + c, s - 1) * rs, g, dh);
       f32_load<ND>(dc, dobase + (size_t)min(q0 + c, s - 1) * dors, g, dh);
+      if constexpr (OWN_DELTA) {
+        F32Frag<ND> o;
+        f32_load<ND>(o, cbase + (size_t)min(q0 + c, s - 1) * dors, g, dh);
+        own = f32_delta_rows<ND>(o, dc, g);
+      }
       sc = f32_scores<ND>(q, k);
       dp = f32_scores<ND>(dc, v);
     }
@@ -302,7 +316,7 @@ attn_bwd_dkv_f32(const float* __restrict__ qkv, const float* __restrict__ dctx, 
       const bool ok = q < s && (!causal || q >= my_key);
       const bool hidden = !causal && mask && mask[((size_t)j * s + qq) * s + kr];
       p[r] = ok ? __expf((hidden ? kMaskFill : sc[r] * scale) - lse_h[qq]) : 0.f;
-      ds[r] = ok && !hidden ? p[r] * (dp[r] - delta_h[qq]) * scale : 0.f;
+      ds[r] = ok && !hidden ? p[r] * (dp[r] - (OWN_DELTA ? own[r] : delta_h[qq])) * scale : 0.f;
       vis |= (uint32_t)ok << r;
     }
     const bool diag = causal && q0 < k0 + kF32Rows;
@@ -313,6 +327,34 @@ attn_bwd_dkv_f32(const float* __restrict__ qkv, const float* __restrict__ dctx, 
   const bool mine = f32_join<ND>(dk, part, wave, lane);
   if (mine && my_key < s) f32_store<ND>(out + hp, dk, g, dh);
   if (f32_join<ND>(dv, part, wave, lane) && my_key < s) f32_store<ND>(out + 2 * hp, dv, g, dh);
+}
+
+template <int ND>
+__global__ void __launch_bounds__(64 * kF32Waves)
+attn_bwd_dq_f32(const float* __restrict__ qkv, const float* __restrict__ ctx, const float* __restrict__ dctx,
+                const float* __restrict__ lse, float* __restrict__ delta, float* __restrict__ dqkv, int s, int b, int heads, int dh,
+                const uint8_t* __restrict__ mask, int causal) {
+  __shared__ f32x4_t part[(kF32Waves - 1) * ND * 64];
+  // long rows first
+  f32_dq_block<ND>(qkv, ctx, dctx, lse, delta, dqkv, s, b, heads, dh, mask, causal, (int)gridDim.x - 1 - (int)blockIdx.x, part);
+}
+template <int ND>
+__global__ void __launch_bounds__(64 * kF32Waves)
+attn_bwd_dkv_f32(const float* __restrict__ qkv, const float* __restrict__ dctx, const float* __restrict__ lse,
+                 const float* __restrict__ delta, float* __restrict__ dqkv, int s, int b, int heads, int dh,
+                 const uint8_t* __restrict__ mask, int causal) {
+  __shared__ f32x4_t part[(kF32Waves - 1) * ND * 64];
+  f32_dkv_block<ND, false>(qkv, nullptr, dctx, lse, delta, dqkv, s, b, heads, dh, mask, causal, blockIdx.x, part);
+}
+// Both in one launch: dK/dV computes the delta of its queries itself, so that neither waits for the other.
+template <int ND>
+__global__ void __launch_bounds__(64 * kF32Waves)
+attn_bwd_f32(const float* __restrict__ qkv, const float* __restrict__ ctx, const float* __restrict__ dctx, const float* __restrict__ lse,
+             float* __restrict__ dqkv, int s, int b, int heads, int dh, const uint8_t* __restrict__ mask, int causal) {
+  __shared__ f32x4_t part[(kF32Waves - 1) * ND * 64];
+  const int n = (int)gridDim.x / 2, x = (int)blockIdx.x;
+  if (x < n) f32_dkv_block<ND, true>(qkv, ctx, dctx, lse, nullptr, dqkv, s, b, heads, dh, mask, causal, x, part);
+  else f32_dq_block<ND>(qkv, ctx, dctx, lse, nullptr, dqkv, s, b, heads, dh, mask, causal, 2 * n - 1 - x, part);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -1372,10 +1414,24 @@ int launch_attn_fwd(int dtype, const void* qkv, void* ctx, float* lse, int s, in
   return L.status();
 }
 
+// Workgroups of 16 rows up to which dQ and dK/dV run in one launch: while both fit the chip side by side.  With more, the delta
+// computed once per block of keys and the larger of the two kernels' registers for both cost more than the second launch: us of
+// two launches and one, causal, 6 workgroups of dh 64 15.8, 9.2; 64 of dh 32 15.9, 9.2, of 64 25.8, 16.1 (a layer of 256 tokens 124.4 -> 114.7), of 128 48, 30, of 160 58, 36; 256 of 32 25,
+// 20, of 64 45, 41, of 96 66, 63, of 128 87, 120; 512 of 32 62, 55, of 64 114, 144.
+static long long f32_bwd_together(int dh, int causal) {
+  const long long ncu = attn_compute_units();
+  return dh <= 32 && causal ? 2 * ncu : dh <= 96 ? ncu : ncu / 2;
+}
 template <int ND>
 static void attn_bwd_f32_t(const float* qkv, const float* ctx, const float* lse, const float* dctx, float* dqkv, float* delta, int s,
                            int b, int heads, int dh, const uint8_t* mask, int causal, hipStream_t stream) {
   const dim3 grid((s + kF32Rows - 1) / kF32Rows, heads, b), block(64 * kF32Waves);
+  if constexpr (ND <= 10) {   // (heads beyond 160 spill)
+    if ((long long)grid.x * heads * b <= f32_bwd_together(dh, causal)) {
+      hipLaunchKernelGGL(attn_bwd_f32<ND>, dim3(2 * grid.x, heads, b), block, 0, stream, qkv, ctx, dctx, lse, dqkv, s, b, heads, dh, mask, causal);
+      return;
+    }
+  }
   hipLaunchKernelGGL(attn_bwd_dq_f32<ND>, grid, block, 0, stream, qkv, ctx, dctx, lse, delta, dqkv, s, b, heads, dh, mask, causal);
   hipLaunchKernelGGL(attn_bwd_dkv_f32<ND>, grid, block, 0, stream, qkv, dctx, lse, (const float*)delta, dqkv, s, b, heads, dh, mask, causal);
 }

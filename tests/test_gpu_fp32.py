@@ -78,6 +78,21 @@ def test_attention_fp32(s, b, heads, dh, masked):
             assert_close(got[..., lo:lo + hp], want[..., lo:lo + hp], B.F32, name, 1.0 if masked and name == "dv" else 0.1)
 
 
+@pytest.mark.parametrize("causal", [True, False])
+@pytest.mark.parametrize("s,heads,dh,many", [(17, 8, 32, 70), (33, 8, 64, 14), (16, 4, 96, 70), (49, 4, 128, 12), (31, 2, 160, 40)])
+def test_attention_fp32_backward_in_one_and_in_two_launches(s, heads, dh, many, causal):
+    """Few workgroups run dQ and dK/dV in one launch, in which dK/dV computes the queries' delta itself; more run them one after
+    the other.  A sample's gradients have the same bits alone and among `many` (280 to 680 and more workgroups)."""
+    hp = heads * dh
+    qkv, dctx = randn((s, many, 3 * hp), B.F32, 1), randn((s, many, hp), B.F32, 2)
+    mask = None if causal else torch.from_numpy((np.random.default_rng(3).random((many, s, s)) < 0.3).astype(np.uint8)).cuda()
+    _, _, all_of_them = forward_backward(qkv, dctx, s, many, heads, dh, mask)
+    for j in (0, many // 2, many - 1):
+        one = mask[j:j + 1].clone() if mask is not None else None
+        _, _, alone = forward_backward(qkv[:, j:j + 1].contiguous(), dctx[:, j:j + 1].contiguous(), s, 1, heads, dh, one)
+        assert torch.equal(alone, all_of_them[:, j:j + 1]), j
+
+
 # weight gradients in tiles of 16, of 32, of both sizes, of 32 with eight waves each, of 32 and 64
 @pytest.mark.parametrize("h,a,t,s,b", [(96, 3, 1, 300, 1), (64, 2, 1, 37, 3), (256, 8, 8, 300, 1), (256, 4, 1, 128, 2), (512, 8, 1, 65, 1)])
 def test_weight_gradients_fp32_together_and_one_by_one(h, a, t, s, b):
