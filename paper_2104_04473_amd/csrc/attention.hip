@@ -851,6 +851,21 @@ attn_fwd_tiles(const bf16_t* __restrict__ qkv, bf16_t* __restrict__ ctx, float* 
 // needs atomics: one owns 64 queries and produces dQ, one owns 64 keys and produces dK and dV.
 //   dP = dO V^T, dS = P o (dP - delta), dQ = dS K / sqrt(dh), dK = dS^T Q / sqrt(dh), dV = P^T dO
 // ------------------------------------------------------------------------------------------------
+// delta = sum_d dctx * ctx of 32 rows, one to a lane and its neighbour 32 lanes on: the diagonal of ctx dctx^T, summed in the order of dP
+// in the kernels below (with one visible key dP - D is exactly zero).  `row`: the lane's row of ctx, readable.
+template <int DH>
+__device__ __forceinline__ float attn_delta_of(const bf16_t* __restrict__ row, const bf16x8_t (&dof)[DH / 16], bool valid, int lane) {
+  const int half = lane >> 5, l31 = lane & 31;
+  f32x16_t x = zero16();
+#pragma unroll
+  for (int kk = 0; kk < DH / 16; ++kk) x = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_global(row, valid, kk, half), dof[kk], x, 0, 0, 0);
+  // row l31 of column l31: register (l31 & 3) + 4 * (l31 >> 3) of the lane of half (l31 >> 2) & 1
+  float mine = x[0];
+#pragma unroll
+  for (int r = 1; r < 16; ++r) mine = (l31 & 3) + 4 * (l31 >> 3) == r ? x[r] : mine;
+  return __shfl(mine, ((l31 >> 2) & 1) * 32 + l31, 64);
+}
+
 // dQ of 32 QW queries, as the forward kernel walks them: K and V stream through two LDS stages of KT keys (K is read twice,
 // as rows for S and transposed for dQ).  NP = 2: two groups take alternate tiles and their sums are added at the end.  A wave
 // holds Q, dO and dQ and fits two to a SIMD (tiles on their way through registers had left one), so that one's
@@ -858,20 +873,19 @@ attn_fwd_tiles(const bf16_t* __restrict__ qkv, bf16_t* __restrict__ ctx, float* 
 // us before and now, causal, s = 2048 unless given: 4 x 16 heads of 128 216 -> 106; 12 heads of 128 61 -> 38; 8 heads 48 -> 34, at
 // s = 1024 27 -> 20; 20 heads of 160 121 -> 56; 32 of 64 62 -> 36; 128 of 32 112 -> 76; 16 of 128 without the mask 147 -> 61; 4 x 16
 // heads of 64 x 512 under a general mask 23 -> 16.
-template <int DH, bool CAUSAL, int QW, int NP, int KT, bool WIDE>
-__global__ void __launch_bounds__(64 * QW * NP, 2)
-attn_bwd_dq_tiles(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ ctx, const bf16_t* __restrict__ dctx,
-                  const float* __restrict__ lse, float* __restrict__ delta, bf16_t* __restrict__ dqkv, int s, int b, int heads,
-                  const uint8_t* __restrict__ mask) {
+// READ: delta comes from memory.
+template <int DH, bool CAUSAL, int QW, int NP, int KT, bool WIDE, bool READ>
+__device__ __forceinline__ void attn_dq_block(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ ctx, const bf16_t* __restrict__ dctx,
+                                              const float* __restrict__ lse, float* __restrict__ delta, bf16_t* __restrict__ dqkv, int s, int b,
+                                              int heads, const uint8_t* __restrict__ mask, int id, char* smem_all) {
   constexpr int NKK = DH / 16, NDT = DH / 32, kQ = 32 * QW, SUBS = KT / 32;
   constexpr uint32_t kTile = TileDma<DH, QW, KT, WIDE>::kBytes, kStage = 2 * kTile;
-  extern __shared__ __attribute__((aligned(1024))) char smem_all[];
   const int wave_all = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), grp = NP == 1 ? 0 : wave_all / QW, wave = wave_all % QW;
   const uint32_t lds0 = attn_lds_offset(smem_all) + grp * 2 * kStage;
 
   const int nqb = (s + kQ - 1) / kQ;
   int qblk, e, j;
-  if (!attn_map_tiles<CAUSAL && !WIDE>(blockIdx.x, nqb, heads, b, &qblk, &e, &j)) return;
+  if (!attn_map_tiles<CAUSAL && !WIDE>(id, nqb, heads, b, &qblk, &e, &j)) return;
   qblk = nqb - 1 - qblk;   // long rows first
   const int lane = threadIdx.x & 63, half = lane >> 5, l31 = lane & 31;
   const int hp = heads * DH;
@@ -901,21 +915,13 @@ attn_bwd_dq_tiles(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ ctx
     qf[kk] = frag_global(base + (size_t)min(my_q, s - 1) * rs, valid, kk, half);
     dof[kk] = frag_global(dctx + out_row, valid, kk, half);
   }
-  // delta = sum_d dctx * ctx: the diagonal of ctx dctx^T, summed in the order of dP below (with one visible key dP - D is
-  // exactly zero); the dK/dV kernel, launched next, reads it from memory.  In a launch of its own it took 8 to 61 us.
   float D;
-  {
-    f32x16_t x = zero16();
-#pragma unroll
-    for (int kk = 0; kk < NKK; ++kk)
-      x = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_global(ctx + out_row, valid, kk, half), dof[kk], x, 0, 0, 0);
-    // row l31 of column l31: register (l31 & 3) + 4 * (l31 >> 3) of the lane of half (l31 >> 2) & 1
-    float mine = x[0];
-#pragma unroll
-    for (int r = 1; r < 16; ++r) mine = (l31 & 3) + 4 * (l31 >> 3) == r ? x[r] : mine;
-    D = __shfl(mine, ((l31 >> 2) & 1) * 32 + l31, 64);
+  if constexpr (READ) {
+    D = valid ? delta[stat] : 0.f;
+  } else {
+    D = attn_delta_of<DH>(ctx + out_row, dof, valid, lane);
+    if (grp == 0 && half == 0 && valid) delta[stat] = D;
   }
-  if (grp == 0 && half == 0 && valid) delta[stat] = D;
   FragDirect<KT> fk, fv;
   FragTr<KT> ft;
   fk.init(lds0, l31, half);
@@ -1004,6 +1010,15 @@ attn_bwd_dq_tiles(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ ctx
   }
   if (valid) store_cols<NDT>(dqkv + (size_t)my_q * rs + (size_t)j * 3 * hp + (size_t)e * DH, acc, scale, half);
 }
+// (it also writes delta, which the dK/dV kernel, launched next, reads: in a launch of its own that took 8 to 61 us)
+template <int DH, bool CAUSAL, int QW, int NP, int KT, bool WIDE>
+__global__ void __launch_bounds__(64 * QW * NP, 2)
+attn_bwd_dq_tiles(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ ctx, const bf16_t* __restrict__ dctx,
+                  const float* __restrict__ lse, float* __restrict__ delta, bf16_t* __restrict__ dqkv, int s, int b, int heads,
+                  const uint8_t* __restrict__ mask) {
+  extern __shared__ __attribute__((aligned(1024))) char smem_all[];
+  attn_dq_block<DH, CAUSAL, QW, NP, KT, WIDE, false>(qkv, ctx, dctx, lse, delta, dqkv, s, b, heads, mask, blockIdx.x, smem_all);
+}
 
 // The hidden flags of a tile of KEYS keys x QT queries on their way to LDS as one bit each, [key][query]: a lane reads the bits of
 // its key at once.  A thread turns 8 queries x 4 keys: eight words of four keys, whose nonzero bytes' flags are shifted
@@ -1050,17 +1065,13 @@ template <int DH, bool CAUSAL, int KW, int NP, int QT, bool SPLIT> struct DkvGeo
   static constexpr int kSums = NP > 1 ? KW * 2 * (DH / 2) * 64 * (int)sizeof(float) : 0;
   static constexpr int lds_bytes(bool masked) { return NP * 2 * stage_bytes(masked) > kSums ? NP * 2 * stage_bytes(masked) : kSums; }
 };
-// Causal heads of 64 in tiles of 32: 168 registers instead of 171 (three spilled) leave three waves on a SIMD (whole backward of 32 heads x 2048 98 ->
-// 89 us, 24 heads 75, 76, 60 x 777 40.5, 38.8; in tiles of 64 30 heads x 4 x 777 83 -> 86, and without the causal mask it spills).
 template <int DH, bool CAUSAL, int KW, int NP, int QT, bool SPLIT, bool WIDE>
-__global__ void __launch_bounds__(64 * KW * (SPLIT ? 2 : 1) * NP, WIDE ? 1 : CAUSAL && DH == 64 && QT == 32 ? 3 : 2)
-attn_bwd_dkv_tiles(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ dctx, const float* __restrict__ lse,
-                   const float* __restrict__ delta, bf16_t* __restrict__ dqkv, int s, int b, int heads,
-                   const uint8_t* __restrict__ mask) {
+__device__ __forceinline__ void attn_dkv_block(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ dctx, const float* __restrict__ lse,
+                                               const float* __restrict__ delta, bf16_t* __restrict__ dqkv, int s, int b, int heads,
+                                               const uint8_t* __restrict__ mask, int id, char* smem_all) {
   using Geom = DkvGeom<DH, CAUSAL, KW, NP, QT, SPLIT>;
   constexpr int NKK = DH / 16, NDT = DH / 32, kKeys = 32 * KW, SUBS = QT / 32, GW = Geom::kWaves, kTile = Geom::kTile;
   constexpr int NR = SPLIT ? 1 : 2;   // results of a wave
-  extern __shared__ __attribute__((aligned(1024))) char smem_all[];
   const bool use_mask = !CAUSAL && mask != nullptr;
   const uint32_t stage_bytes = Geom::stage_bytes(!CAUSAL && use_mask);
   const int wave_all = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), grp = NP == 1 ? 0 : wave_all / GW, wave = wave_all % GW;
@@ -1071,10 +1082,10 @@ attn_bwd_dkv_tiles(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ dc
 
   const int nkb = (s + kKeys - 1) / kKeys;
   int kblk, e, j;   // the first key blocks see the most queries and start first
-  if (!attn_map_tiles<CAUSAL && !WIDE>(blockIdx.x, nkb, heads, b, &kblk, &e, &j)) return;
+  if (!attn_map_tiles<CAUSAL && !WIDE>(id, nkb, heads, b, &kblk, &e, &j)) return;
   static_assert(!SPLIT || KW == 2);
   // which half of a group takes dK alternates, so that every SIMD gets both
-  const bool want_dk = !SPLIT || ((wave / KW) ^ (NP == 2 ? grp : (int)(blockIdx.x >> 8))) & 1;
+  const bool want_dk = !SPLIT || ((wave / KW) ^ (NP == 2 ? grp : id >> 8)) & 1;
   const int lane = threadIdx.x & 63, half = lane >> 5, l31 = lane & 31;
   const int hp = heads * DH;
   const size_t rs = (size_t)b * 3 * hp, dors = (size_t)b * hp;
@@ -1259,6 +1270,46 @@ attn_bwd_dkv_tiles(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ dc
       store_cols<NDT>(out + hp, acc[1], scale, half);
     }
   }
+}
+// Causal heads of 64 in tiles of 32: 168 registers instead of 171 (three spilled) leave three waves on a SIMD (whole backward of 32 heads x 2048 98 ->
+// 89 us, 24 heads 75, 76, 60 x 777 40.5, 38.8; in tiles of 64 30 heads x 4 x 777 83 -> 86, and without the causal mask it spills).
+template <int DH, bool CAUSAL, int KW, int NP, int QT, bool SPLIT, bool WIDE>
+__global__ void __launch_bounds__(64 * KW * (SPLIT ? 2 : 1) * NP, WIDE ? 1 : CAUSAL && DH == 64 && QT == 32 ? 3 : 2)
+attn_bwd_dkv_tiles(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ dctx, const float* __restrict__ lse,
+                   const float* __restrict__ delta, bf16_t* __restrict__ dqkv, int s, int b, int heads,
+                   const uint8_t* __restrict__ mask) {
+  extern __shared__ __attribute__((aligned(1024))) char smem_all[];
+  attn_dkv_block<DH, CAUSAL, KW, NP, QT, SPLIT, WIDE>(qkv, dctx, lse, delta, dqkv, s, b, heads, mask, blockIdx.x, smem_all);
+}
+
+// delta in a launch of its own, in front of dQ and dK/dV side by side (3 us where those are: few workgroups)
+template <int DH>
+__global__ void __launch_bounds__(256)
+attn_delta_kernel(const bf16_t* __restrict__ ctx, const bf16_t* __restrict__ dctx, float* __restrict__ delta, int s, int b, int heads) {
+  const int lane = threadIdx.x & 63, half = lane >> 5, l31 = lane & 31, nblk = (s + 31) / 32;
+  const int unit = blockIdx.x * 4 + (threadIdx.x >> 6);   // 32 rows of a (sample, head)
+  if (unit >= nblk * heads * b) return;
+  const int blk = unit % nblk, pair = unit / nblk, e = pair % heads, j = pair / heads, row = blk * 32 + l31;
+  const bool valid = row < s;
+  const size_t at = ((size_t)min(row, s - 1) * b + j) * heads * DH + (size_t)e * DH;
+  bf16x8_t dof[DH / 16];
+#pragma unroll
+  for (int kk = 0; kk < DH / 16; ++kk) dof[kk] = frag_global(dctx + at, valid, kk, half);
+  const float D = attn_delta_of<DH>(ctx + at, dof, valid, lane);
+  if (half == 0 && valid) delta[((size_t)j * heads + e) * s + row] = D;
+}
+// dQ (64 queries to a workgroup) and dK/dV (64 keys) side by side, for few workgroups, where each alone leaves much of the chip idle and
+// takes as long as its longest walk.  Eight workgroups of one and eight of the other in turn, so that both kernels' long
+// walks start first.  Times of both ways stand at the launcher.
+template <int DH, bool CAUSAL, int NPK, int QT, bool SPLIT>
+__global__ void __launch_bounds__(128 * NPK * (SPLIT ? 2 : 1), 2)
+attn_bwd_pair_tiles(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ dctx, const float* __restrict__ lse,
+                    float* __restrict__ delta, bf16_t* __restrict__ dqkv, int s, int b, int heads, const uint8_t* __restrict__ mask) {
+  constexpr int NPQ = NPK * (SPLIT ? 2 : 1);   // dQ's groups of waves: both kernels' workgroups have the same size
+  extern __shared__ __attribute__((aligned(1024))) char smem_all[];
+  const int id = (blockIdx.x >> 4) * 8 + (blockIdx.x & 7);
+  if (!(blockIdx.x & 8)) attn_dkv_block<DH, CAUSAL, 2, NPK, QT, SPLIT, false>(qkv, dctx, lse, delta, dqkv, s, b, heads, mask, id, smem_all);
+  else attn_dq_block<DH, CAUSAL, 2, NPQ, 32, false, true>(qkv, nullptr, dctx, lse, delta, dqkv, s, b, heads, mask, id, smem_all);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -1515,7 +1566,7 @@ static AttnForm attn_dkv_form(int dh, bool causal, int s, int b, int heads) {
   if (dh > 128) f = {2, blocks64 <= 2 * ncu ? 2 : 1, 32, true, false};
   else if (attn_bwd_small(dh, causal, s, blocks64, ncu)) f = {2, 1, dh <= 64 ? 64 : 32, false, false};
   else if (blocks64 > (causal && n > 6 ? 6 : 3) * ncu) f = {4, 1, 64, false, false};
-  else if (blocks64 <= (dh == 128 ? ncu * 3 / 2 : dh == 96 ? ncu : 2 * ncu)) f = {2, 2, 64, dh == 128, false};
+  else if (dh == 128 ? !causal && blocks64 <= ncu * 3 / 2 : dh == 96 || (dh == 32 && causal) ? false : blocks64 <= 2 * ncu) f = {2, 2, 64, dh == 128, false};
   return attn_wide_or(f, {2, 1, 32, false, true}, causal, s, b, heads, dh);
 }
 template <int DH, bool CAUSAL>
@@ -1530,21 +1581,85 @@ static int attn_bwd_dkv_t(const bf16_t* qkv, const bf16_t* dctx, const float* ls
     if (f.w == 2 && f.groups == 1)
       return attn_bwd_dkv_tiles_np<DH, CAUSAL, 2, 1, DH <= 64 ? 64 : 32, false>(qkv, dctx, lse, delta, dqkv, s, b, heads, mask, stream);
     if (f.w == 4) return attn_bwd_dkv_tiles_np<DH, CAUSAL, 4, 1, 64, false>(qkv, dctx, lse, delta, dqkv, s, b, heads, mask, stream);
-    if (f.tile == 64) return attn_bwd_dkv_tiles_np<DH, CAUSAL, 2, 2, 64, DH == 128>(qkv, dctx, lse, delta, dqkv, s, b, heads, mask, stream);
+    if constexpr (DH == 64 || (DH != 96 && !CAUSAL))
+      if (f.tile == 64) return attn_bwd_dkv_tiles_np<DH, CAUSAL, 2, 2, 64, DH == 128>(qkv, dctx, lse, delta, dqkv, s, b, heads, mask, stream);
     return attn_bwd_dkv_tiles_np<DH, CAUSAL, 2, 2, 32, false>(qkv, dctx, lse, delta, dqkv, s, b, heads, mask, stream);
   }
 }
+// dQ and dK/dV side by side in one launch, behind one for delta (k_tile = 0: one after the other).  dQ: 64 queries, k_groups (split: twice as
+// many) groups of waves, tiles of 32; dK/dV: 64 keys, k_groups groups, tiles of k_tile, split by result or not.  Time of the whole
+// backward over that of the two kernels in turn, causal / without a mask, at blocks of 64 rows = 128, 256, 384, 512:
+//   dh 32 (2, 64) s = 512 .73 .78 .83 .89 / .73 .84 .83 1.04, 2048 .62 .66 .67 .73 / .64 .77 .76 1.01;   64 the same, 512 .72 .77 .97 1.06 / .73 .88 1.01 1.13,
+//   1024 .66 .73 .81 .96 / .67 .86 .95 1.07, 2048 .62 .67 .69 .85 / .63 .84 .96 1.07;   96 (2, 64) 512 .74 .96 1.13 1.38 / .76 1.12 1.14 1.35, (2, 32) 512 .76 .83 .97
+//   1.04 / .78 .96 .97 1.06, 2048 .67 .74 .76 .89 / .69 .91 .99 1.05;   128 (2, 64, split) 512 .74 .99 1.07 1.33 / .73 1.18, 1024 .69 .86 / .69 1.15, 2048 .65 .77 / .66
+//   1.12, (1, 32, split) 200 .75 .95 .82 1.07 / .72 .91 .85 1.01, 512 .81 .88 .89 1.01 / .80 1.01 .89 1.10, 2048 .88 .94 .94 .97 / .90 1.09 1.06 1.21, (2, 32) 1024 .81 .86 .85
+//   .91, 2048 .80 .86 .85 .84;   160 (2, 32, split) 512 .72 .97 1.08 / .73 1.16, 2048 .62 .76 1.03 / .67 1.19, (1, 32, split) 200 .74 .93 .80 .86 / .73 .89 .81 .89,
+//   512 .76 .84 .90 .93 / .79 .96 .89 .98, 2048 .79 .87 .92 1.02 / .84 1.07 1.04 1.11.  Heads of 64 x 512, general mask: as without.
+struct AttnPair {
+  int k_groups, k_tile;
+  bool split;
+};
+static AttnPair attn_pair_form(int dh, bool causal, bool masked, int s, int b, int heads) {
+  const int n = (s + 63) / 64;
+  const long long blocks64 = (long long)n * heads * b, ncu = attn_compute_units();
+  const bool half = blocks64 <= ncu / 2, one = blocks64 <= ncu, more = blocks64 <= ncu * 3 / 2, two = blocks64 <= 2 * ncu;
+  const AttnPair none = {0, 0, false};
+  if (dh <= 64) {
+    const bool take = one || (dh == 32 ? more || (causal && two) : causal && ((n >= 8 && more) || (n >= 16 && two)));
+    return take ? AttnPair{2, 64, false} : none;
+  }
+  if (dh == 96) return half ? AttnPair{2, 64, false} : one || (causal && n >= 8 && more) ? AttnPair{2, 32, false} : none;
+  const AttnPair split1 = {1, 32, true}, split2 = {2, dh == 128 ? 64 : 32, true}, whole = {2, 32, false};
+  const bool long_walk = causal && n >= 16;
+  if (half) return n <= 4 ? split1 : split2;
+  if (one && long_walk) return split2;
+  if (dh == 128 && long_walk) return two ? whole : none;
+  return more && (causal || (n <= 5 && !masked)) ? split1 : none;
+}
 void attn_form_query(int kernel, int causal, int masked, int s, int b, int heads, int dh, int* rows, int* groups, int* tile, int* wide) {
-  const AttnForm f = kernel == PTDP_ATTN_KERNEL_FWD ? attn_fwd_form(dh, causal != 0, !causal && masked, s, b, heads)
-                     : kernel == PTDP_ATTN_KERNEL_DQ ? attn_dq_form(dh, causal != 0, !causal && masked, s, b, heads) : attn_dkv_form(dh, causal != 0, s, b, heads);
+  AttnForm f = kernel == PTDP_ATTN_KERNEL_FWD ? attn_fwd_form(dh, causal != 0, !causal && masked, s, b, heads)
+               : kernel == PTDP_ATTN_KERNEL_DQ ? attn_dq_form(dh, causal != 0, !causal && masked, s, b, heads) : attn_dkv_form(dh, causal != 0, s, b, heads);
+  const AttnPair p = attn_pair_form(dh, causal != 0, !causal && masked, s, b, heads);
+  if (kernel != PTDP_ATTN_KERNEL_FWD && p.k_tile > 0) {
+    f = kernel == PTDP_ATTN_KERNEL_DQ ? AttnForm{2, p.split ? 2 * p.k_groups : p.k_groups, 32, false, false} : AttnForm{2, p.k_groups, p.k_tile, p.split, false};
+  }
   *rows = 32 * f.w;
   *groups = f.groups;
   *tile = f.tile;
   *wide = f.wide;
 }
+template <int DH, bool CAUSAL, int NPK, int QT, bool SPLIT>
+static int attn_bwd_pair(const bf16_t* qkv, const bf16_t* ctx, const float* lse, const bf16_t* dctx, bf16_t* dqkv, float* delta, int s, int b,
+                         int heads, const uint8_t* mask, hipStream_t stream) {
+  using Geom = DkvGeom<DH, CAUSAL, 2, NPK, QT, SPLIT>;
+  constexpr int NPQ = NPK * (SPLIT ? 2 : 1), tiles = NPQ * 4 * TileDma<DH, 2, 32, false>::kBytes, sums = DH * 64 * (int)sizeof(float);
+  constexpr int dq_smem = tiles > sums ? tiles : sums;
+  auto larger = [](int x) { return x > dq_smem ? x : dq_smem; };
+  static once_flag_t done[kMaxDevices];
+  const auto kernel = attn_bwd_pair_tiles<DH, CAUSAL, NPK, QT, SPLIT>;
+  if (set_dynamic_smem(reinterpret_cast<const void*>(kernel), larger(Geom::lds_bytes(!CAUSAL)), done) != PTDP_OK) return PTDP_E_HIP;
+  const int nblk = (s + 63) / 64;
+  const unsigned units = (unsigned)((s + 31) / 32) * heads * b;
+  hipLaunchKernelGGL(attn_delta_kernel<DH>, dim3((units + 3) / 4), dim3(256), 0, stream, ctx, dctx, delta, s, b, heads);
+  const long long grid = CAUSAL ? attn_grid_levels(nblk, heads, b) : attn_grid(nblk, heads, b);
+  hipLaunchKernelGGL(kernel, dim3(2 * grid), dim3(128 * NPQ), larger(Geom::lds_bytes(!CAUSAL && mask != nullptr)), stream, qkv, dctx, lse, delta, dqkv,
+                     s, b, heads, mask);
+  return PTDP_OK;
+}
 template <int DH, bool CAUSAL>
 static int attn_bwd_mfma_t(const bf16_t* qkv, const bf16_t* ctx, const float* lse, const bf16_t* dctx, bf16_t* dqkv,
                            float* delta, int s, int b, int heads, const uint8_t* mask, hipStream_t stream) {
+  const AttnPair p = attn_pair_form(DH, CAUSAL, !CAUSAL && mask != nullptr, s, b, heads);
+  if constexpr (DH <= 96) {
+    if (p.k_tile == 64) return attn_bwd_pair<DH, CAUSAL, 2, 64, false>(qkv, ctx, lse, dctx, dqkv, delta, s, b, heads, mask, stream);
+    if constexpr (DH == 96)
+      if (p.k_tile == 32) return attn_bwd_pair<DH, CAUSAL, 2, 32, false>(qkv, ctx, lse, dctx, dqkv, delta, s, b, heads, mask, stream);
+  } else {
+    if (p.split && p.k_groups == 2) return attn_bwd_pair<DH, CAUSAL, 2, DH == 128 ? 64 : 32, true>(qkv, ctx, lse, dctx, dqkv, delta, s, b, heads, mask, stream);
+    if (p.split) return attn_bwd_pair<DH, CAUSAL, 1, 32, true>(qkv, ctx, lse, dctx, dqkv, delta, s, b, heads, mask, stream);
+    if constexpr (DH == 128 && CAUSAL)
+      if (p.k_groups == 2) return attn_bwd_pair<DH, CAUSAL, 2, 32, false>(qkv, ctx, lse, dctx, dqkv, delta, s, b, heads, mask, stream);
+  }
   const int rc = attn_bwd_dq_t<DH, CAUSAL>(qkv, ctx, dctx, lse, delta, dqkv, s, b, heads, mask, stream);   // first: it writes delta
   if (rc != PTDP_OK) return rc;
   return attn_bwd_dkv_t<DH, CAUSAL>(qkv, dctx, lse, delta, dqkv, s, b, heads, mask, stream);

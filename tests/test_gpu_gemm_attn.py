@@ -332,7 +332,9 @@ def test_attention_forward_backward(dtype, s, b, heads, dh):
                                           (130, 3, 172, 32), (129, 4, 130, 64), (131, 2, 258, 96), (197, 4, 97, 128), (321, 1, 50, 96),
                                           (327, 1, 5, 128),
                                           # one and two blocks of 64 rows, the last of one to 33 rows
-                                          (65, 13, 31, 32), (65, 13, 31, 64), (65, 1, 403, 96), (389, 5, 13, 96), (33, 5, 103, 128)])
+                                          (65, 13, 31, 32), (65, 13, 31, 64), (65, 1, 403, 96), (389, 5, 13, 96), (33, 5, 103, 128),
+                                          # dQ and dK/dV side by side in forms that the above leave out, and one after the other
+                                          (1000, 1, 17, 128), (70, 1, 5, 160), (65, 1, 80, 96), (65, 1, 200, 160), (65, 1, 150, 64)])
 def test_attention_forms(s, b, heads, dh):
     test_attention_forward_backward(B.BF16, s, b, heads, dh)
 

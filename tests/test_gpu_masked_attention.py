@@ -87,7 +87,11 @@ def test_masked_attention_forward_backward(dtype, s, b, heads, dh, masked, empty
                                           # and of single bytes
                                           (33, 1, 1, 32), (327, 1, 3, 32), (65, 1, 257, 32), (33, 5, 103, 32), (65, 5, 103, 32), (33, 1, 1, 64),
                                           (327, 1, 3, 64), (65, 5, 103, 64), (327, 1, 3, 96), (65, 13, 31, 96), (327, 1, 3, 128),
-                                          (33, 5, 103, 128), (65, 1, 257, 128), (65, 13, 31, 128), (33, 10, 103, 160)])
+                                          (33, 5, 103, 128), (65, 1, 257, 128), (65, 13, 31, 128), (33, 10, 103, 160),
+                                          # dQ and dK/dV side by side, and with some more heads one after the other
+                                          (388, 1, 3, 128), (388, 1, 3, 160), (68, 1, 80, 96), (68, 1, 80, 160), (68, 1, 200, 32), (68, 1, 150, 64),
+                                          (65, 1, 3, 128), (65, 1, 3, 160), (65, 1, 80, 96), (65, 1, 80, 128), (65, 1, 80, 160), (65, 1, 200, 32),
+                                          (65, 1, 150, 64)])
 def test_masked_attention_forms(s, b, heads, dh):
     test_masked_attention_forward_backward(B.BF16, s, b, heads, dh, True, [(0, s - 1)])
 
@@ -97,7 +101,9 @@ def test_masked_attention_forms(s, b, heads, dh):
                                           (33, 1, 1, 64), (65, 1, 1, 64), (33, 5, 103, 64), (65, 1, 257, 64), (65, 5, 103, 64), (449, 5, 13, 64),
                                           (33, 1, 1, 96), (65, 3, 43, 96), (33, 5, 103, 96), (65, 13, 31, 96), (389, 5, 8, 96),
                                           (33, 1, 1, 128), (33, 5, 103, 128), (65, 13, 31, 128), (389, 5, 8, 128),
-                                          (33, 1, 1, 160), (33, 10, 103, 160)])
+                                          (33, 1, 1, 160), (33, 10, 103, 160),
+                                          # as above
+                                          (389, 1, 3, 160), (65, 1, 200, 160), (65, 1, 200, 32), (65, 1, 150, 64), (65, 1, 80, 96)])
 def test_unmasked_attention_forms(s, b, heads, dh):
     test_masked_attention_forward_backward(B.BF16, s, b, heads, dh, False, [])
 
