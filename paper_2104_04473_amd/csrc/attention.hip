@@ -25,9 +25,9 @@ constexpr float kMaskFill = -10000.f;
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4_t;
 
 // ------------------------------------------------------------------------------------------------
-// fp32 kernels on v_mfma_f32_16x16x4_f32 (fp32 products and sums).  A workgroup of four waves owns 16 queries (forward,
-// dQ) or 16 keys (dK, dV) of one head; each wave takes every fourth 16-row tile of the other side and the four partial
-// results meet in LDS in a fixed order.  Operands come from memory straight into fragments: lane (c = lane & 15,
+// fp32 kernels on v_mfma_f32_16x16x4_f32 (fp32 products and sums).  A workgroup of NW waves (four, or eight
+// where workgroups are few) owns 16 queries (forward, dQ) or 16 keys (dK, dV) of one head; each wave takes every NW-th 16-row tile
+// of the other side and the partial results meet in LDS in a fixed order (eight waves' shorter sums: error against 64 bits 1 to 13 % smaller).  Operands come from memory straight into fragments: lane (c = lane & 15,
 // g = lane >> 4) carries four consecutive dh of row c (elements 16 i + 4 g .. +3 of step i; both factors of a product
 // share that order), and the score tile S^T comes out with column c = the workgroup's row and rows 4 g + r = the tile's,
 // which is the second product's B operand as it stands.  These are small calls (fp32 is the precision of small
@@ -36,7 +36,7 @@ typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4_t;
 // score across the wave.
 // ND: steps of 16 dh (dh rounded up; the lanes past dh hold zeros).
 // ------------------------------------------------------------------------------------------------
-constexpr int kF32Rows = 16, kF32Waves = 4;
+constexpr int kF32Rows = 16;
 constexpr int kMaxF32Dh = 256;
 
 template <int ND> struct F32Frag { f32x4_t v[ND]; };
@@ -112,8 +112,8 @@ __device__ __forceinline__ void f32_accumulate(f32x4_t (&acc)[ND], f32x4_t w, co
       }
   }
 }
-// waves 1 .. 3 hand their sums to wave 0 (added in that order); returns true in wave 0.  part: 3 * ND * 64 vectors.
-template <int ND> __device__ __forceinline__ bool f32_join(f32x4_t (&acc)[ND], f32x4_t* part, int wave, int lane) {
+// waves 1 .. NW - 1 hand their sums to wave 0 (added in that order); returns true in wave 0.  part: (NW - 1) * ND * 64 vectors.
+template <int ND, int NW> __device__ __forceinline__ bool f32_join(f32x4_t (&acc)[ND], f32x4_t* part, int wave, int lane) {
   __syncthreads();
   if (wave > 0) {
 #pragma unroll
@@ -122,7 +122,7 @@ template <int ND> __device__ __forceinline__ bool f32_join(f32x4_t (&acc)[ND], f
   __syncthreads();
   if (wave > 0) return false;
 #pragma unroll
-  for (int w = 0; w < kF32Waves - 1; ++w)
+  for (int w = 0; w < NW - 1; ++w)
 #pragma unroll
     for (int t = 0; t < ND; ++t) acc[t] += part[(w * ND + t) * 64 + lane];
   return true;
@@ -133,12 +133,12 @@ template <int ND> __device__ __forceinline__ void f32_store(float* row, const f3
     if (16 * t + 4 * g < dh) *reinterpret_cast<f32x4_t*>(row + 16 * t + 4 * g) = acc[t];
 }
 
-template <int ND>
-__global__ void __launch_bounds__(64 * kF32Waves)
+template <int ND, int NW>
+__global__ void __launch_bounds__(64 * NW)
 attn_fwd_f32(const float* __restrict__ qkv, float* __restrict__ ctx, float* __restrict__ lse, int s, int b, int heads, int dh,
              const uint8_t* __restrict__ mask, int causal) {
-  __shared__ f32x4_t part[(kF32Waves - 1) * ND * 64];
-  __shared__ float stat[2][kF32Waves][16];
+  __shared__ f32x4_t part[(NW - 1) * ND * 64];
+  __shared__ float stat[2][NW][16];
   const int e = blockIdx.y, j = blockIdx.z, wave = threadIdx.x >> 6, lane = threadIdx.x & 63, c = lane & 15, g = lane >> 4;
   const int q0 = ((int)gridDim.x - 1 - (int)blockIdx.x) * kF32Rows, my_q = q0 + c;   // long rows first
   const int hp = heads * dh;
@@ -153,7 +153,7 @@ attn_fwd_f32(const float* __restrict__ qkv, float* __restrict__ ctx, float* __re
   float m = -INFINITY, l = 0.f;
   const int ntiles = ((causal ? min(q0 + kF32Rows, s) : s) + kF32Rows - 1) / kF32Rows;
   const uint8_t* mrow = (!causal && mask) ? mask + ((size_t)j * s + min(my_q, s - 1)) * s : nullptr;
-  for (int kt = wave; kt < ntiles; kt += kF32Waves) {
+  for (int kt = wave; kt < ntiles; kt += NW) {
     const int key0 = kt * kF32Rows;
     F32Frag<ND> k;
     f32_load<ND>(k, base + hp + (size_t)min(key0 + c, s - 1) * rs, g, dh);
@@ -194,13 +194,13 @@ attn_fwd_f32(const float* __restrict__ qkv, float* __restrict__ ctx, float* __re
   __syncthreads();
   float mall = stat[0][0][c], lall = 0.f;   // wave 0 always has a tile
 #pragma unroll
-  for (int w = 1; w < kF32Waves; ++w) mall = fmaxf(mall, stat[0][w][c]);
+  for (int w = 1; w < NW; ++w) mall = fmaxf(mall, stat[0][w][c]);
 #pragma unroll
-  for (int w = 0; w < kF32Waves; ++w) lall += stat[1][w][c] * __expf(stat[0][w][c] - mall);
+  for (int w = 0; w < NW; ++w) lall += stat[1][w][c] * __expf(stat[0][w][c] - mall);
   const float f = __expf(m - mall);   // a wave without a tile: m = -inf, its zeros are multiplied by zero
 #pragma unroll
   for (int t = 0; t < ND; ++t) o[t] *= f;
-  if (!f32_join<ND>(o, part, wave, lane) || my_q >= s) return;
+  if (!f32_join<ND, NW>(o, part, wave, lane) || my_q >= s) return;
 #pragma unroll
   for (int t = 0; t < ND; ++t) o[t] /= lall;
   f32_store<ND>(ctx + ((size_t)my_q * b + j) * hp + (size_t)e * dh, o, g, dh);
@@ -223,7 +223,7 @@ template <int ND> __device__ __forceinline__ f32x4_t f32_delta_rows(const F32Fra
 }
 
 // dQ of 16 queries, and (delta not NULL) their delta for the dK/dV kernel
-template <int ND>
+template <int ND, int NW>
 __device__ __forceinline__ void f32_dq_block(const float* __restrict__ qkv, const float* __restrict__ ctx, const float* __restrict__ dctx,
                                              const float* __restrict__ lse, float* __restrict__ delta, float* __restrict__ dqkv, int s, int b,
                                              int heads, int dh, const uint8_t* __restrict__ mask, int causal, int blk, f32x4_t* part) {
@@ -250,7 +250,7 @@ __device__ __forceinline__ void f32_dq_block(const float* __restrict__ qkv, cons
   for (int t = 0; t < ND; ++t) acc[t] = f32x4_t{0.f, 0.f, 0.f, 0.f};
   const int ntiles = ((causal ? min(q0 + kF32Rows, s) : s) + kF32Rows - 1) / kF32Rows;
   const uint8_t* mrow = (!causal && mask) ? mask + ((size_t)j * s + qr) * s : nullptr;
-  for (int kt = wave; kt < ntiles; kt += kF32Waves) {
+  for (int kt = wave; kt < ntiles; kt += NW) {
     const int key0 = kt * kF32Rows;
     const size_t row = (size_t)min(key0 + c, s - 1) * rs;
     F32Frag<ND> k, v;
@@ -268,12 +268,12 @@ __device__ __forceinline__ void f32_dq_block(const float* __restrict__ qkv, cons
     }
     f32_accumulate<ND>(acc, ds, base + hp, rs, key0, s, dh, causal && key0 + kF32Rows > q0, vis, lane);
   }
-  if (!f32_join<ND>(acc, part, wave, lane) || my_q >= s) return;
+  if (!f32_join<ND, NW>(acc, part, wave, lane) || my_q >= s) return;
   f32_store<ND>(dqkv + (size_t)my_q * rs + (size_t)j * 3 * hp + (size_t)e * dh, acc, g, dh);
 }
 
 // dK, dV of 16 keys.  OWN_DELTA: the queries' delta is computed here as well (ctx), not read (delta).
-template <int ND, bool OWN_DELTA>
+template <int ND, int NW, bool OWN_DELTA>
 __device__ __forceinline__ void f32_dkv_block(const float* __restrict__ qkv, const float* __restrict__ ctx, const float* __restrict__ dctx,
                                               const float* __restrict__ lse, const float* __restrict__ delta, float* __restrict__ dqkv, int s,
                                               int b, int heads, int dh, const uint8_t* __restrict__ mask, int causal, int blk, f32x4_t* part) {
@@ -294,7 +294,7 @@ __device__ __forceinline__ void f32_dkv_block(const float* __restrict__ qkv, con
 #pragma unroll
   for (int t = 0; t < ND; ++t) dk[t] = dv[t] = f32x4_t{0.f, 0.f, 0.f, 0.f};
   const int ntiles = (s + kF32Rows - 1) / kF32Rows;
-  for (int qt = (causal ? blk : 0) + wave; qt < ntiles; qt += kF32Waves) {
+  for (int qt = (causal ? blk : 0) + wave; qt < ntiles; qt += NW) {
     const int q0 = qt * kF32Rows;
     f32x4_t sc, dp, p, ds, own = {0.f, 0.f, 0.f, 0.f};
     {
@@ -324,37 +324,37 @@ __device__ __forceinline__ void f32_dkv_block(const float* __restrict__ qkv, con
     f32_accumulate<ND>(dk, ds, base, rs, q0, s, dh, diag, vis, lane);
   }
   float* out = dqkv + (size_t)my_key * rs + (size_t)j * 3 * hp + (size_t)e * dh;
-  const bool mine = f32_join<ND>(dk, part, wave, lane);
+  const bool mine = f32_join<ND, NW>(dk, part, wave, lane);
   if (mine && my_key < s) f32_store<ND>(out + hp, dk, g, dh);
-  if (f32_join<ND>(dv, part, wave, lane) && my_key < s) f32_store<ND>(out + 2 * hp, dv, g, dh);
+  if (f32_join<ND, NW>(dv, part, wave, lane) && my_key < s) f32_store<ND>(out + 2 * hp, dv, g, dh);
 }
 
-template <int ND>
-__global__ void __launch_bounds__(64 * kF32Waves)
+template <int ND, int NW>
+__global__ void __launch_bounds__(64 * NW)
 attn_bwd_dq_f32(const float* __restrict__ qkv, const float* __restrict__ ctx, const float* __restrict__ dctx,
                 const float* __restrict__ lse, float* __restrict__ delta, float* __restrict__ dqkv, int s, int b, int heads, int dh,
                 const uint8_t* __restrict__ mask, int causal) {
-  __shared__ f32x4_t part[(kF32Waves - 1) * ND * 64];
+  __shared__ f32x4_t part[(NW - 1) * ND * 64];
   // long rows first
-  f32_dq_block<ND>(qkv, ctx, dctx, lse, delta, dqkv, s, b, heads, dh, mask, causal, (int)gridDim.x - 1 - (int)blockIdx.x, part);
+  f32_dq_block<ND, NW>(qkv, ctx, dctx, lse, delta, dqkv, s, b, heads, dh, mask, causal, (int)gridDim.x - 1 - (int)blockIdx.x, part);
 }
-template <int ND>
-__global__ void __launch_bounds__(64 * kF32Waves)
+template <int ND, int NW>
+__global__ void __launch_bounds__(64 * NW)
 attn_bwd_dkv_f32(const float* __restrict__ qkv, const float* __restrict__ dctx, const float* __restrict__ lse,
                  const float* __restrict__ delta, float* __restrict__ dqkv, int s, int b, int heads, int dh,
                  const uint8_t* __restrict__ mask, int causal) {
-  __shared__ f32x4_t part[(kF32Waves - 1) * ND * 64];
-  f32_dkv_block<ND, false>(qkv, nullptr, dctx, lse, delta, dqkv, s, b, heads, dh, mask, causal, blockIdx.x, part);
+  __shared__ f32x4_t part[(NW - 1) * ND * 64];
+  f32_dkv_block<ND, NW, false>(qkv, nullptr, dctx, lse, delta, dqkv, s, b, heads, dh, mask, causal, blockIdx.x, part);
 }
 // Both in one launch: dK/dV computes the delta of its queries itself, so that neither waits for the other.
-template <int ND>
-__global__ void __launch_bounds__(64 * kF32Waves)
+template <int ND, int NW>
+__global__ void __launch_bounds__(64 * NW)
 attn_bwd_f32(const float* __restrict__ qkv, const float* __restrict__ ctx, const float* __restrict__ dctx, const float* __restrict__ lse,
              float* __restrict__ dqkv, int s, int b, int heads, int dh, const uint8_t* __restrict__ mask, int causal) {
-  __shared__ f32x4_t part[(kF32Waves - 1) * ND * 64];
+  __shared__ f32x4_t part[(NW - 1) * ND * 64];
   const int n = (int)gridDim.x / 2, x = (int)blockIdx.x;
-  if (x < n) f32_dkv_block<ND, true>(qkv, ctx, dctx, lse, nullptr, dqkv, s, b, heads, dh, mask, causal, x, part);
-  else f32_dq_block<ND>(qkv, ctx, dctx, lse, nullptr, dqkv, s, b, heads, dh, mask, causal, 2 * n - 1 - x, part);
+  if (x < n) f32_dkv_block<ND, NW, true>(qkv, ctx, dctx, lse, nullptr, dqkv, s, b, heads, dh, mask, causal, x, part);
+  else f32_dq_block<ND, NW>(qkv, ctx, dctx, lse, nullptr, dqkv, s, b, heads, dh, mask, causal, 2 * n - 1 - x, part);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -1435,6 +1435,25 @@ static bool attn_sizes_fit(int s, int b, int heads) {
     else CALL(16);                  \
   } while (0)
 
+template <int ND, int NW>
+static void attn_fwd_f32_nw(const float* qkv, float* ctx, float* lse, int s, int b, int heads, int dh, const uint8_t* mask, int causal,
+                            hipStream_t stream) {
+  hipLaunchKernelGGL((attn_fwd_f32<ND, NW>), dim3((s + kF32Rows - 1) / kF32Rows, heads, b), dim3(64 * NW), 0, stream, qkv, ctx, lse, s, b, heads, dh,
+                     mask, causal);
+}
+// Eight waves for more than four tiles of 16 keys while the workgroups leave the chip's wave slots empty (heads beyond 128 take too
+// many registers).  us with four and with eight waves, causal: 64 workgroups of dh 64 x 128 9.1, 8.1, x 256 14.5, 11.3; 256 x 256 15.1, 11.6; 512 x
+// 512 47, 33; 1024 107, 108; dh 128: 256 x 256 41, 29, 512 91, 95; 48 rows (three tiles) 6.3, 7.1.
+template <int ND>
+static void attn_fwd_f32_t(const float* qkv, float* ctx, float* lse, int s, int b, int heads, int dh, const uint8_t* mask, int causal,
+                           hipStream_t stream) {
+  if constexpr (ND <= 8) {
+    const long long groups = (long long)((s + kF32Rows - 1) / kF32Rows) * heads * b, ncu = attn_compute_units();
+    if (s > 4 * kF32Rows && groups <= (ND <= 6 ? 2 : 1) * ncu) return attn_fwd_f32_nw<ND, 8>(qkv, ctx, lse, s, b, heads, dh, mask, causal, stream);
+  }
+  attn_fwd_f32_nw<ND, 4>(qkv, ctx, lse, s, b, heads, dh, mask, causal, stream);
+}
+
 // Without the causal mask every row is a full row: count the whole s x s square as executed too.
 int launch_attn_fwd(int dtype, const void* qkv, void* ctx, float* lse, int s, int b, int heads, int dh,
                     const uint8_t* mask, int causal, hipStream_t stream) {
@@ -1443,9 +1462,7 @@ int launch_attn_fwd(int dtype, const void* qkv, void* ctx, float* lse, int s, in
   Launch L(PTDP_K_ATTN_FWD, attn_flops(s, b, heads, dh), stream);
   int rc = PTDP_OK;
   if (dtype == PTDP_F32) {
-#define PTDP_ATTN_FWD32(ND) \
-  hipLaunchKernelGGL(attn_fwd_f32<ND>, dim3((s + kF32Rows - 1) / kF32Rows, heads, b), dim3(64 * kF32Waves), 0, stream, (const float*)qkv, \
-                     (float*)ctx, lse, s, b, heads, dh, mask, causal)
+#define PTDP_ATTN_FWD32(ND) attn_fwd_f32_t<ND>((const float*)qkv, (float*)ctx, lse, s, b, heads, dh, mask, causal, stream)
     PTDP_F32_DISPATCH(dh, PTDP_ATTN_FWD32);
 #undef PTDP_ATTN_FWD32
   } else {
@@ -1465,26 +1482,46 @@ int launch_attn_fwd(int dtype, const void* qkv, void* ctx, float* lse, int s, in
   return L.status();
 }
 
-// Workgroups of 16 rows up to which dQ and dK/dV run in one launch: while both fit the chip side by side.  With more, the delta
-// computed once per block of keys and the larger of the two kernels' registers for both cost more than the second launch: us of
-// two launches and one, causal, 6 workgroups of dh 64 15.8, 9.2; 64 of dh 32 15.9, 9.2, of 64 25.8, 16.1 (a layer of 256 tokens 124.4 -> 114.7), of 128 48, 30, of 160 58, 36; 256 of 32 25,
-// 20, of 64 45, 41, of 96 66, 63, of 128 87, 120; 512 of 32 62, 55, of 64 114, 144.
-static long long f32_bwd_together(int dh, int causal) {
+// Backward.  dQ and dK/dV run in one launch while both fit the chip side by side (more, and the delta computed once per block of keys
+// and the larger of the two kernels' registers for both cost more than the second launch; heads beyond 160 spill), in workgroups
+// of eight waves where the walk has more than four tiles and that leaves room.  us, causal, for two launches of four waves, two of
+// eight, one of four, one of eight; n workgroups of 16 rows:
+//   n = 6 of dh 64 x 48 15.8, 17.9, 9.0, 10.9;  64 of 32 x 128 15.9, -, 9.3, 8.0, of 64 x 128 25.8, 22.5, 15.9, 13.7 (a layer of 256 tokens 124.4 -> 114.7 with one of four),
+//   of 64 x 256 42, 34, 27.8, 21.4, of 96 x 256 62, 49, 41, 31;  128 of 64 x 256 -, 34.5, 28.2, 21.7;  256 of 32 x 256 25, 20.3, 20.4, 17.2, of 64 x 128 26.9, 23.2, 23.7,
+//   26.3, x 256 45, 35.5, 41.4, 41.8, of 96 x 256 66, 51, 61, 66, of 128 x 256 87, -, 120, -;  448 of 64 x 100 31, 36, 33.7, -;  512 of 32 x 512 62, 47.8, 55, 55, of 64 x
+//   512 112, 105, 144, -, x 1024 202, 186, 215, -;  1344 of 64 x 333 147, 165.  Without the mask the same but for 512 and more of 32.
+struct F32Bwd {
+  bool together;
+  int waves;
+};
+static F32Bwd f32_bwd_form(int dh, int causal, int s, long long groups) {
   const long long ncu = attn_compute_units();
-  return dh <= 32 && causal ? 2 * ncu : dh <= 96 ? ncu : ncu / 2;
+  if (dh > 96) return {dh <= 160 && groups <= ncu / 2, 4};
+  if (groups <= (dh <= 32 ? ncu : ncu / 2)) return {true, s > 4 * kF32Rows ? 8 : 4};
+  if (s >= 256 && groups <= 2 * ncu) return {false, 8};
+  return {groups <= (dh <= 32 && causal ? 2 * ncu : ncu), 4};
+}
+template <int ND, int NW>
+static void attn_bwd_f32_nw(bool together, const float* qkv, const float* ctx, const float* lse, const float* dctx, float* dqkv, float* delta,
+                            int s, int b, int heads, int dh, const uint8_t* mask, int causal, hipStream_t stream) {
+  const dim3 grid((s + kF32Rows - 1) / kF32Rows, heads, b), block(64 * NW);
+  if constexpr (ND <= 10) {
+    if (together) {
+      hipLaunchKernelGGL((attn_bwd_f32<ND, NW>), dim3(2 * grid.x, heads, b), block, 0, stream, qkv, ctx, dctx, lse, dqkv, s, b, heads, dh, mask, causal);
+      return;
+    }
+  }
+  hipLaunchKernelGGL((attn_bwd_dq_f32<ND, NW>), grid, block, 0, stream, qkv, ctx, dctx, lse, delta, dqkv, s, b, heads, dh, mask, causal);
+  hipLaunchKernelGGL((attn_bwd_dkv_f32<ND, NW>), grid, block, 0, stream, qkv, dctx, lse, (const float*)delta, dqkv, s, b, heads, dh, mask, causal);
 }
 template <int ND>
 static void attn_bwd_f32_t(const float* qkv, const float* ctx, const float* lse, const float* dctx, float* dqkv, float* delta, int s,
                            int b, int heads, int dh, const uint8_t* mask, int causal, hipStream_t stream) {
-  const dim3 grid((s + kF32Rows - 1) / kF32Rows, heads, b), block(64 * kF32Waves);
-  if constexpr (ND <= 10) {   // (heads beyond 160 spill)
-    if ((long long)grid.x * heads * b <= f32_bwd_together(dh, causal)) {
-      hipLaunchKernelGGL(attn_bwd_f32<ND>, dim3(2 * grid.x, heads, b), block, 0, stream, qkv, ctx, dctx, lse, dqkv, s, b, heads, dh, mask, causal);
-      return;
-    }
+  const F32Bwd f = f32_bwd_form(dh, causal, s, (long long)((s + kF32Rows - 1) / kF32Rows) * heads * b);
+  if constexpr (ND <= 6) {
+    if (f.waves == 8) return attn_bwd_f32_nw<ND, 8>(f.together, qkv, ctx, lse, dctx, dqkv, delta, s, b, heads, dh, mask, causal, stream);
   }
-  hipLaunchKernelGGL(attn_bwd_dq_f32<ND>, grid, block, 0, stream, qkv, ctx, dctx, lse, delta, dqkv, s, b, heads, dh, mask, causal);
-  hipLaunchKernelGGL(attn_bwd_dkv_f32<ND>, grid, block, 0, stream, qkv, dctx, lse, (const float*)delta, dqkv, s, b, heads, dh, mask, causal);
+  attn_bwd_f32_nw<ND, 4>(f.together, qkv, ctx, lse, dctx, dqkv, delta, s, b, heads, dh, mask, causal, stream);
 }
 
 template <int DH, bool CAUSAL, int QW, int NP, int KT, bool WIDE = false>

@@ -54,7 +54,9 @@ def forward_backward(qkv, dctx, s, b, heads, dh, mask=None):
 
 @pytest.mark.parametrize("masked", [False, True])
 @pytest.mark.parametrize("s,b,heads,dh", [(1, 1, 2, 8), (15, 2, 1, 24), (17, 1, 3, 40), (64, 2, 2, 64), (65, 1, 2, 96),
-                                          (129, 1, 1, 128), (96, 2, 1, 160), (83, 1, 1, 200), (50, 1, 2, 256)])
+                                          (129, 1, 1, 128), (96, 2, 1, 160), (83, 1, 1, 200), (50, 1, 2, 256),
+                                          # more than four tiles: workgroups of eight waves, in one launch and in two
+                                          (81, 1, 3, 32), (130, 1, 2, 64), (200, 2, 2, 72), (260, 1, 16, 64), (257, 1, 9, 40)])
 def test_attention_fp32(s, b, heads, dh, masked):
     hp = heads * dh
     qkv, dctx = randn((s, b, 3 * hp), B.F32, 1), randn((s, b, hp), B.F32, 2)
