@@ -170,8 +170,9 @@ attn_fwd_f32(const float* __restrict__ qkv, float* __restrict__ ctx, float* __re
       vis |= (uint32_t)ok << r;
       mx = fmaxf(mx, p[r]);
     }
-    mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
-    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+    const LaneHalves mr = lane_rows(mx);
+    const LaneHalves mh = lane_halves(fmaxf(mr.lo, mr.hi));
+    mx = fmaxf(mh.lo, mh.hi);
     const float ref = mx == -INFINITY ? 0.f : mx;   // only scores of -inf so far: weights of zero, not exp(-inf + inf)
     const float corr = __expf(m - ref);
     m = mx;
@@ -763,7 +764,8 @@ attn_fwd_tiles(const bf16_t* __restrict__ qkv, bf16_t* __restrict__ ctx, float* 
     for (int sub = 0; sub < SUBS; ++sub)
 #pragma unroll
       for (int r = 0; r < 16; ++r) mx = fmaxf(mx, sacc[sub][r]);
-    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+    const LaneHalves mh = lane_halves(mx);
+    mx = fmaxf(mh.lo, mh.hi);
     if (__any(mx > m_run)) {   // some row's maximum moved: rescale what has been accumulated
       const float corr = __builtin_amdgcn_exp2f((m_run - mx) * c2);
       m_run = mx;

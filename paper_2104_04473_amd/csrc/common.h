@@ -54,15 +54,40 @@ template <> struct Vec16<bf16_t> {
 };
 
 // ---- reductions -------------------------------------------------------------
+// The same pairs in the same order as a butterfly of __shfl_xor over 32, 16, 8, 4, 2, 1 (no bit differs), but in the vector ALU: that
+// shuffle goes through LDS, where each of the six dependent steps waits some hundred cycles.  After the step over 8 a row of
+// sixteen lanes repeats every 8 lanes, so that a rotation by 4 brings the same value as lane ^ 4; likewise below.
+struct LaneHalves { float lo, hi; };   // what lanes l and l + 32 (halves) or l and l + 16 (rows) hold, in every lane of the pair
+__device__ __forceinline__ LaneHalves lane_halves(float v) {
+  const auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return {__uint_as_float(p[0]), __uint_as_float(p[1])};
+}
+__device__ __forceinline__ LaneHalves lane_rows(float v) {
+  const auto p = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return {__uint_as_float(p[0]), __uint_as_float(p[1])};
+}
+template <int N> __device__ __forceinline__ float row_rotate(float v) {   // by N of a row's sixteen lanes
+  return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), 0x120 + N, 0xf, 0xf, true));
+}
 __device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-  return v;
+  const LaneHalves h = lane_halves(v);
+  v = h.lo + h.hi;
+  const LaneHalves r = lane_rows(v);
+  v = r.lo + r.hi;
+  v += row_rotate<8>(v);
+  v += row_rotate<4>(v);
+  v += row_rotate<2>(v);
+  return v + row_rotate<1>(v);
 }
 __device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v = fmaxf(v, __shfl_xor(v, off, 64));
-  return v;
+  const LaneHalves h = lane_halves(v);
+  v = fmaxf(h.lo, h.hi);
+  const LaneHalves r = lane_rows(v);
+  v = fmaxf(r.lo, r.hi);
+  v = fmaxf(v, row_rotate<8>(v));
+  v = fmaxf(v, row_rotate<4>(v));
+  v = fmaxf(v, row_rotate<2>(v));
+  return fmaxf(v, row_rotate<1>(v));
 }
 // Sum over the whole block (blockDim.x a multiple of 64, at most 1024); every thread gets the result.
 // smem: at least 16 floats; safe to call repeatedly (leading barrier).
