@@ -53,8 +53,8 @@ template <bool V> struct F32Operand {
   }
 };
 constexpr int f32_most_waves(int nb) { return nb == 1 ? 8 : 4; }   // waves that share a tile's k range
-// One tile by the workgroup's first kg waves (the others only take part in the end).
-template <bool VA, bool VB, int NB>
+// One tile by the workgroup's first kg waves.  SOME: there may be more, which only take part in the end.
+template <bool VA, bool VB, int NB, bool SOME>
 __device__ __forceinline__ void gemm_f32_tile(const float* __restrict__ A, const float* __restrict__ B, float* C, const float* __restrict__ bias,
                                               int M, int N, int K, size_t a_rs, size_t a_cs, size_t b_rs, size_t b_cs, int accumulate,
                                               int tile_m, int tile_n, int kg, float* part) {
@@ -106,7 +106,7 @@ __device__ __forceinline__ void gemm_f32_tile(const float* __restrict__ A, const
           for (int j = 0; j < NB; ++j)
             acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[set][i][q][e], fb[set][j][q][e], acc[i][j], 0, 0, 0);
   };
-  int k = wave < kg ? wave * kF32Chunk : K;
+  int k = !SOME || wave < kg ? wave * kF32Chunk : K;
   load(0, k);
   for (; k < K; k += 2 * step) {
     load(1, k + step);
@@ -116,7 +116,7 @@ __device__ __forceinline__ void gemm_f32_tile(const float* __restrict__ A, const
     multiply(1);
   }
   float* mine = part + wave * (kTile * kPitch);
-  if (wave < kg) {
+  if (!SOME || wave < kg) {
 #pragma unroll
     for (int i = 0; i < NB; ++i)
 #pragma unroll
@@ -140,7 +140,7 @@ __global__ void __launch_bounds__(64 * f32_most_waves(NB))
 gemm_f32_kernel(const float* __restrict__ A, const float* __restrict__ B, float* C, const float* __restrict__ bias,
                 int M, int N, int K, size_t a_rs, size_t a_cs, size_t b_rs, size_t b_cs, int accumulate) {
   extern __shared__ __attribute__((aligned(16))) float part[];
-  gemm_f32_tile<VA, VB, NB>(A, B, C, bias, M, N, K, a_rs, a_cs, b_rs, b_cs, accumulate, blockIdx.y, blockIdx.x, blockDim.x >> 6, part);
+  gemm_f32_tile<VA, VB, NB, false>(A, B, C, bias, M, N, K, a_rs, a_cs, b_rs, b_cs, accumulate, blockIdx.y, blockIdx.x, blockDim.x >> 6, part);
 }
 
 // The same on one 16 x 16 tile (v_mfma_f32_16x16x4_f32), for outputs of fewer 32 x 32 tiles than the chip has compute units, where
@@ -245,7 +245,7 @@ gemm_f32_multi_kernel(MultiF32 a) {
   if constexpr (TINY)
     gemm_f32_tiny_tile<false, false>(A, B, C, nullptr, M, N, a.K, 1, M, N, 1, 1, t / tiles_n, t % tiles_n, reinterpret_cast<float (*)[16][17]>(part));
   else
-    gemm_f32_tile<false, false, 1>(A, B, C, nullptr, M, N, a.K, 1, M, N, 1, 1, t / tiles_n, t % tiles_n, kg, part);
+    gemm_f32_tile<false, false, 1, true>(A, B, C, nullptr, M, N, a.K, 1, M, N, 1, 1, t / tiles_n, t % tiles_n, kg, part);
 }
 
 template <bool VA, bool VB, int NB>
