@@ -169,6 +169,9 @@ layernorm_fwd_kernel(const T* __restrict__ x, const T* __restrict__ gain, const 
 // Bound by memory for wide rows, by one row's round trip for narrow ones.  us before (one row per block at a time) and
 // now, bf16 with residual: 8192 rows x 2048 58 -> 31, 2048 x 4096 26 -> 21.5, 2048 x 12288 58 -> 53, 1024 x 2048
 // 11.3 -> 9.9.
+// The groups' sums go to LDS all at once and come back four columns a thread (in three rounds of half of the groups each, with one
+// float per access: with the finishing launch 666 x 512 13.7 -> 12.8, 2048 x 1024 20.4 -> 18.2, 1024 x 2048 21.8 -> 18.9, 2048 x 4096
+// 32.3 -> 28.3, 8192 x 2048 37.3 -> 35.1).
 // DROP: the gradient dx, as stored, also goes through the dropout in front of this residual sum, din = Drop'(dx), with the
 // column sums of din (what bda_bwd_kernel does in a pass of its own): one read of dx and a launch less.  us for the two
 // passes and for one: 8192 x 2048 45 -> 38, 2048 x 12288 77 -> 62, 666 x 512 11.5 -> 5.9.
@@ -329,47 +332,43 @@ layernorm_bwd_kernel(const T* du, const T* __restrict__ x, const T* __restrict__
     m = nm;
     rs = nrs;
   }
-  // the upper half of the groups hands its sums to the lower half until one is left
+  float* prow = part + (size_t)blockIdx.x * 2 * width;
   if constexpr (NG > 1) {
+    // every group puts its sums into LDS, then all threads add them up four columns at a time, in the order of a tree
     float* sums = reinterpret_cast<float*>(ln_smem);   // [group][gain, bias (, din)][column]: the gain row is done with
+    __syncthreads();
+    float* mine = sums + (size_t)grp * SUMS * width;
 #pragma unroll
-    for (int live = NG / 2; live > 0; live /= 2) {
-      __syncthreads();
-      if (grp >= live && grp < 2 * live) {
-        float* o = sums + (size_t)(grp - live) * SUMS * width;
+    for (int i = 0; i < VPT; ++i) {
+      const int c = tid + i * GW * 64;
+      if (c < nvec) {
 #pragma unroll
-        for (int i = 0; i < VPT; ++i) {
-          const int c = tid + i * GW * 64;
-          if (c < nvec) {
-#pragma unroll
-            for (int j = 0; j < N; ++j) {
-              o[(size_t)j * nvec + c] = ag[i][j];   // [j][c]: neighbouring lanes in neighbouring banks
-              o[(size_t)(N + j) * nvec + c] = ab[i][j];
-              if constexpr (DROP) o[(size_t)(2 * N + j) * nvec + c] = ad[i][j];
-            }
-          }
-        }
-      }
-      __syncthreads();
-      if (grp < live) {
-        const float* o = sums + (size_t)grp * SUMS * width;
-#pragma unroll
-        for (int i = 0; i < VPT; ++i) {
-          const int c = tid + i * GW * 64;
-          if (c < nvec) {
-#pragma unroll
-            for (int j = 0; j < N; ++j) {
-              ag[i][j] += o[(size_t)j * nvec + c];
-              ab[i][j] += o[(size_t)(N + j) * nvec + c];
-              if constexpr (DROP) ad[i][j] += o[(size_t)(2 * N + j) * nvec + c];
-            }
-          }
+        for (int j = 0; j < N; j += 4) {
+          float* o = mine + (size_t)c * N + j;
+          *reinterpret_cast<float4*>(o) = make_float4(ag[i][j], ag[i][j + 1], ag[i][j + 2], ag[i][j + 3]);
+          *reinterpret_cast<float4*>(o + width) = make_float4(ab[i][j], ab[i][j + 1], ab[i][j + 2], ab[i][j + 3]);
+          if constexpr (DROP) *reinterpret_cast<float4*>(o + 2 * width) = make_float4(ad[i][j], ad[i][j + 1], ad[i][j + 2], ad[i][j + 3]);
         }
       }
     }
-    if (grp > 0) return;
+    __syncthreads();
+    for (int k = 4 * threadIdx.x; k < SUMS * width; k += 4 * kLnBwdThreads) {
+      float4 v[NG];
+#pragma unroll
+      for (int q = 0; q < NG; ++q) v[q] = *reinterpret_cast<const float4*>(sums + (size_t)q * SUMS * width + k);
+#pragma unroll
+      for (int live = NG / 2; live > 0; live /= 2)
+#pragma unroll
+        for (int q = 0; q < live; ++q) {
+          v[q].x += v[q + live].x;
+          v[q].y += v[q + live].y;
+          v[q].z += v[q + live].z;
+          v[q].w += v[q + live].w;
+        }
+      *reinterpret_cast<float4*>(k < 2 * width ? prow + k : drop.part + (size_t)blockIdx.x * width + (k - 2 * width)) = v[0];
+    }
+    return;
   }
-  float* prow = part + (size_t)blockIdx.x * 2 * width;
 #pragma unroll
   for (int i = 0; i < VPT; ++i) {
     const int c = tid + i * GW * 64;
@@ -886,8 +885,8 @@ template <typename T, int VPT, int GW, bool DROP>
 static int ln_bwd_launch(const void* du, const void* x, const void* gain, const float* mu, const float* rstd, const void* resid,
                          void* dx, float* part, int rows, int width, int rpb, int nblk, const LnDrop<T>& drop, hipStream_t st) {
   constexpr int NG = kLnBwdWaves / GW, SUMS = DROP ? 3 : 2;
-  const size_t gain_bytes = (size_t)width * sizeof(T), sum_bytes = (size_t)(NG / 2) * SUMS * width * sizeof(float);
-  constexpr int kMost = VPT * GW * 64 * Vec16<T>::N * (int)(NG > 1 ? (NG / 2) * SUMS * sizeof(float) : sizeof(T));   // at the widest row of this form
+  const size_t gain_bytes = (size_t)width * sizeof(T), sum_bytes = NG > 1 ? (size_t)NG * SUMS * width * sizeof(float) : 0;
+  constexpr int kMost = VPT * GW * 64 * Vec16<T>::N * (int)(NG > 1 ? NG * SUMS * sizeof(float) : sizeof(T));   // at the widest row of this form
   auto kern = layernorm_bwd_kernel<T, VPT, GW, DROP>;
   static once_flag_t done[kMaxDevices];
   if (set_dynamic_smem(reinterpret_cast<const void*>(kern), kMost, done) != PTDP_OK) return PTDP_E_HIP;
