@@ -11,7 +11,8 @@ static constexpr int kColRows = 32;  // rows per block in the column-sum produce
 // The column-sum producers (bias+GeLU backward, bias+dropout+add backward, plain column sums) run workgroups of 64
 // column groups (16 bytes each) x 16 row lanes: wave w takes rows r0 + w and r0 + w + 16 of the block's kColRows
 // rows, a whole 1 KiB run of one row per access, and width / 512 x rows / 32 workgroups per launch.  The waves' sums
-// meet in LDS and wave 0 adds them in a fixed order.  Bound by memory for large calls, by one wave's chain for small ones.
+// meet in LDS and are added in a fixed order, one column a thread (by wave 0 alone, eight columns a lane: small and masked layers
+// 0.4 % slower, bias+GeLU backward 1024 x 2048 9.2 -> 8.7).  Bound by memory for large calls, by one wave's chain for small ones.
 // A wave's two rows go one after the other: sixteen waves hide each other's trips, and both at once (or a loop unrolled for
 // more rows) take registers: bias+dropout+add backward 2048 x 12288 22.3 with both requested first, 20.3 so.
 // us with 4 row lanes of eight rows each and now, with the finishing launch: bias+GeLU backward 666 x 2048 8.7 -> 7.7, 2048 x
@@ -20,25 +21,20 @@ static constexpr int kColRows = 32;  // rows per block in the column-sum produce
 static constexpr int kColLanes = 16;
 static inline dim3 colsum_grid(int nvec, int rows) { return dim3((nvec + 63) / 64, (rows + kColRows - 1) / kColRows); }
 template <int N>
-__device__ __forceinline__ void colsum_block_store(float (&acc)[N], float* __restrict__ part, int width, int c, bool valid) {
-  __shared__ float red[kColLanes - 1][N][64];
+__device__ __forceinline__ void colsum_block_store(float (&acc)[N], float* __restrict__ part, int width) {
+  __shared__ __attribute__((aligned(16))) float red[kColLanes][64 * N];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  if (w > 0) {
 #pragma unroll
-    for (int j = 0; j < N; ++j) red[w - 1][j][lane] = acc[j];
-  }
+  for (int j = 0; j < N; j += 4) *reinterpret_cast<float4*>(&red[w][lane * N + j]) = make_float4(acc[j], acc[j + 1], acc[j + 2], acc[j + 3]);
   __syncthreads();
-  if (w == 0 && valid) {
+  const int t = threadIdx.x, c = blockIdx.x * 64 * N + t;   // one column a thread
+  if (t < 64 * N && c < width) {
+    float s[kColLanes / 4];   // four waves at a time, then the fours in order
 #pragma unroll
-    for (int j = 0; j < N; ++j) {
-      float t[kColLanes / 4];   // four waves at a time, then the fours in order
+    for (int k = 0; k < kColLanes / 4; ++k) s[k] = (red[4 * k][t] + red[4 * k + 1][t]) + (red[4 * k + 2][t] + red[4 * k + 3][t]);
 #pragma unroll
-      for (int k = 0; k < kColLanes / 4; ++k)
-        t[k] = ((k == 0 ? acc[j] : red[4 * k - 1][j][lane]) + red[4 * k][j][lane]) + (red[4 * k + 1][j][lane] + red[4 * k + 2][j][lane]);
-#pragma unroll
-      for (int k = 1; k < kColLanes / 4; ++k) t[0] += t[k];
-      part[(size_t)blockIdx.y * width + (size_t)c * N + j] = t[0];
-    }
+    for (int k = 1; k < kColLanes / 4; ++k) s[0] += s[k];
+    part[(size_t)blockIdx.y * width + c] = s[0];
   }
 }
 
@@ -675,7 +671,7 @@ bias_gelu_bwd_kernel(const T* dg, const T* __restrict__ z, const T* __restrict__
       a.store(dz + off);
     }
   }
-  colsum_block_store<N>(acc, part, width, c, valid);
+  colsum_block_store<N>(acc, part, width);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -735,7 +731,7 @@ bda_bwd_kernel(const T* __restrict__ dout, T* __restrict__ din, float* __restric
       a.store(din + off);
     }
   }
-  colsum_block_store<N>(acc, part, width, c, valid);
+  colsum_block_store<N>(acc, part, width);
 }
 
 // part[blockIdx.y][c] = sum of in[r][c] over the block's kColRows rows (first stage of a bias gradient
@@ -761,7 +757,7 @@ colsum_rows_kernel(const T* __restrict__ in, float* __restrict__ part, int rows,
       for (int j = 0; j < N; ++j) acc[j] += af[j];
     }
   }
-  colsum_block_store<N>(acc, part, width, c, valid);
+  colsum_block_store<N>(acc, part, width);
 }
 
 __global__ void dropout_mask_kernel(uint8_t* keep, int64_t n, uint64_t key, uint32_t thr) {
