@@ -1038,9 +1038,9 @@ __device__ __forceinline__ void gemm_small_tile(const GemmArgs& g, void* Cv, int
 
 // ------------------------------------------------------------------------------------------------
 // 256 x 128 tiles (NN and NT), for outputs that give about one or two of them per compute unit and too few of 256 x 256.
-// Two groups of four waves take alternate k-tiles of 64, 128 x 64 outputs to a wave as in the 256 x 256 kernel (64 x 64
-// to a wave, as in 128 x 128 tiles, reads a third more from LDS per product and cannot keep up with the MFMAs), and
-// their sums meet in LDS at the end.  A k-tile is the 256 x 256 kernel's four phases, each a memory part and an
+// Two groups of four waves take alternate k-tiles of 64, 128 x 64 outputs to a wave as in the 256 x 256 kernel (a pair of
+// 128 x 128 tiles brings 64 KiB a k-tile from L2 to LDS for the same outputs, this one 48), and their sums meet in LDS
+// at the end.  A k-tile is the 256 x 256 kernel's four phases, each a memory part and an
 // arithmetic part with a barrier behind it; the second group runs kWideLag parts behind the first, so that on every SIMD
 // one wave computes while the other reads and requests.
 // Three k-tiles of 48 KiB are in LDS; k-tile t is in stage t % 3 and belongs to group t % 2.  A half-tile's place is
