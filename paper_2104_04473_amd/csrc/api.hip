@@ -409,7 +409,8 @@ int ptdp_layer_backward(ptdp_chunk* ch, int layer, int64_t microbatch, const voi
   PTDP_TRY(launch_gemm(dt, PTDP_GEMM_NT, wf(WS_H1), P.w_o, wf(WS_CTX), nullptr, T, hp, h, 0, 0, sk, skb, st));
   PTDP_TRY(launch_attn_bwd(dt, sf(PTDP_STASH_QKV), sf(PTDP_STASH_CTX), (const float*)sf(PTDP_STASH_LSE), wf(WS_CTX),
                            wf(WS_QKV), (float*)wf(WS_DELTA), c.s, c.b, (int)d.al, (int)d.dh, ch->mask, c.causal, st));
-  PTDP_TRY(launch_colsum(dt, wf(WS_QKV), G.b_qkv, csr[4], T, 3 * hp, st, &sums));
+  const bool late = layernorm_bwd_takes_sums(dt, T, h, 3 * hp);   // b_qkv's sums in the launch of the first LayerNorm's backward
+  if (!late) PTDP_TRY(launch_colsum(dt, wf(WS_QKV), G.b_qkv, csr[4], T, 3 * hp, st, &sums));
   PTDP_TRY(launch_gemm(dt, PTDP_GEMM_NT, wf(WS_QKV), P.w_qkv, wf(WS_H2), nullptr, T, h, 3 * hp, 0, 0, sk, skb, st));
   {
     const void* A[4] = {sf(PTDP_STASH_G), sf(PTDP_STASH_U2), sf(PTDP_STASH_U), sf(PTDP_STASH_CTX)};
@@ -418,8 +419,14 @@ int ptdp_layer_backward(ptdp_chunk* ch, int layer, int64_t microbatch, const voi
     const int M[4] = {fp, h, h, hp}, N[4] = {h, fp, 3 * hp, h};
     PTDP_TRY(launch_gemm_tn_multi(dt, 4, A, B, C, M, N, T, st));
   }
-  PTDP_TRY(launch_layernorm_bwd(dt, wf(WS_H2), sf(PTDP_STASH_X), P.ln1_g, (const float*)sf(PTDP_STASH_MU1),
-                                (const float*)sf(PTDP_STASH_RSTD1), wf(WS_X1), dx, G.ln1_g, G.ln1_b, csr[5], T, h, st, &sums));
+  const float* mu1 = (const float*)sf(PTDP_STASH_MU1);
+  const float* rstd1 = (const float*)sf(PTDP_STASH_RSTD1);
+  if (late)
+    PTDP_TRY(launch_layernorm_bwd_sums(dt, wf(WS_H2), sf(PTDP_STASH_X), P.ln1_g, mu1, rstd1, wf(WS_X1), dx, G.ln1_g, G.ln1_b,
+                                       csr[5], wf(WS_QKV), G.b_qkv, csr[4], 3 * hp, T, h, st, &sums));
+  else
+    PTDP_TRY(launch_layernorm_bwd(dt, wf(WS_H2), sf(PTDP_STASH_X), P.ln1_g, mu1, rstd1, wf(WS_X1), dx, G.ln1_g, G.ln1_b, csr[5],
+                                  T, h, st, &sums));
   PTDP_TRY(launch_colsum_batch(sums, st));
   return PTDP_OK;
 }

@@ -187,6 +187,11 @@ int launch_layernorm_bwd_drop(int dtype, const void* du, const void* x, const vo
                               const void* resid, void* dx, float* dgain, float* dbias, void* scratch, void* din, float* dbias_in,
                               void* scratch_in, float p, uint64_t key, int rows, int width, hipStream_t st,
                               ColsumBatch* defer = nullptr);
+// launch_layernorm_bwd with the column sums of in[rows, in_width] (sums: fp32 +=) in one launch, for the sizes that takes_sums accepts
+bool layernorm_bwd_takes_sums(int dtype, int rows, int width, int in_width);
+int launch_layernorm_bwd_sums(int dtype, const void* du, const void* x, const void* gain, const float* mu, const float* rstd,
+                              const void* resid, void* dx, float* dgain, float* dbias, void* scratch, const void* in, float* sums,
+                              void* scratch_in, int in_width, int rows, int width, hipStream_t st, ColsumBatch* defer = nullptr);
 int launch_bias_gelu_fwd(int dtype, int mode, const void* z, const void* bias, void* g, int rows, int width,
                          hipStream_t st);
 int launch_bias_gelu_bwd(int dtype, int mode, const void* dg, const void* z, const void* bias, void* dz,

@@ -20,6 +20,16 @@ static constexpr int kColRows = 32;  // rows per block in the column-sum produce
 // 38.3 -> 36.6, 8192 x 8192 52 -> 46; one row of 1024 4.2 -> 4.4 (waves without a row).
 static constexpr int kColLanes = 16;
 static inline dim3 colsum_grid(int nvec, int rows) { return dim3((nvec + 63) / 64, (rows + kColRows - 1) / kColRows); }
+// column t of a block: the lanes' sums four at a time, then the fours in order
+template <int N>
+__device__ __forceinline__ float colsum_lanes_sum(const float (*red)[64 * N], int t) {
+  float s[kColLanes / 4];
+#pragma unroll
+  for (int k = 0; k < kColLanes / 4; ++k) s[k] = (red[4 * k][t] + red[4 * k + 1][t]) + (red[4 * k + 2][t] + red[4 * k + 3][t]);
+#pragma unroll
+  for (int k = 1; k < kColLanes / 4; ++k) s[0] += s[k];
+  return s[0];
+}
 template <int N>
 __device__ __forceinline__ void colsum_block_store(float (&acc)[N], float* __restrict__ part, int width) {
   __shared__ __attribute__((aligned(16))) float red[kColLanes][64 * N];
@@ -28,14 +38,7 @@ __device__ __forceinline__ void colsum_block_store(float (&acc)[N], float* __res
   for (int j = 0; j < N; j += 4) *reinterpret_cast<float4*>(&red[w][lane * N + j]) = make_float4(acc[j], acc[j + 1], acc[j + 2], acc[j + 3]);
   __syncthreads();
   const int t = threadIdx.x, c = blockIdx.x * 64 * N + t;   // one column a thread
-  if (t < 64 * N && c < width) {
-    float s[kColLanes / 4];   // four waves at a time, then the fours in order
-#pragma unroll
-    for (int k = 0; k < kColLanes / 4; ++k) s[k] = (red[4 * k][t] + red[4 * k + 1][t]) + (red[4 * k + 2][t] + red[4 * k + 3][t]);
-#pragma unroll
-    for (int k = 1; k < kColLanes / 4; ++k) s[0] += s[k];
-    part[(size_t)blockIdx.y * width + c] = s[0];
-  }
+  if (t < 64 * N && c < width) part[(size_t)blockIdx.y * width + c] = colsum_lanes_sum<N>(red, t);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -180,10 +183,10 @@ template <typename T> struct LnDrop {
 };
 constexpr int kLnBwdThreads = 512, kLnBwdWaves = kLnBwdThreads / 64;
 template <typename T, int VPT, int GW, bool DROP>
-__global__ void __launch_bounds__(kLnBwdThreads)
-layernorm_bwd_kernel(const T* du, const T* __restrict__ x, const T* __restrict__ gain, const float* __restrict__ mu,
-                     const float* __restrict__ rstd, const T* resid, T* dx, float* __restrict__ part, int rows, int width,
-                     int rpb, LnDrop<T> drop) {
+__device__ __forceinline__ void
+layernorm_bwd_block(const T* du, const T* __restrict__ x, const T* __restrict__ gain, const float* __restrict__ mu,
+                    const float* __restrict__ rstd, const T* resid, T* dx, float* __restrict__ part, int rows, int width,
+                    int rpb, LnDrop<T> drop) {
   constexpr int N = Vec16<T>::N, NG = kLnBwdWaves / GW, SUMS = DROP ? 3 : 2;
   extern __shared__ __attribute__((aligned(16))) char ln_smem[];
   T* gain_s = reinterpret_cast<T*>(ln_smem);   // the gain row, read twice per row of the block
@@ -377,6 +380,60 @@ layernorm_bwd_kernel(const T* du, const T* __restrict__ x, const T* __restrict__
       }
     }
   }
+}
+template <typename T, int VPT, int GW, bool DROP>
+__global__ void __launch_bounds__(kLnBwdThreads)
+layernorm_bwd_kernel(const T* du, const T* __restrict__ x, const T* __restrict__ gain, const float* __restrict__ mu,
+                     const float* __restrict__ rstd, const T* resid, T* dx, float* __restrict__ part, int rows, int width,
+                     int rpb, LnDrop<T> drop) {
+  layernorm_bwd_block<T, VPT, GW, DROP>(du, x, gain, mu, rstd, resid, dx, part, rows, width, rpb, drop);
+}
+
+// The same with the column sums of another matrix (the QKV bias gradient's first stage) in workgroups of their own behind the
+// rows': colsum_rows_kernel's blocks, the sixteen row lanes' sums made by eight waves in two turns, so that the bits are the same.
+// One launch less and the sums run beside the rows: fp32 layer 256 wide, 256 tokens 105.2 -> 102.9 us, two layers of 512, 666 tokens
+// 267.6 -> 261.7.
+template <typename T> struct LnSums {
+  const T* in;
+  float* part;
+  int width, slabs, first;   // slabs of 64 column groups; the first workgroup of the sums
+};
+template <typename T, int VPT, int GW>
+__global__ void __launch_bounds__(kLnBwdThreads)
+layernorm_bwd_sums_kernel(const T* du, const T* __restrict__ x, const T* __restrict__ gain, const float* __restrict__ mu,
+                          const float* __restrict__ rstd, const T* resid, T* dx, float* __restrict__ part, int rows, int width,
+                          int rpb, LnSums<T> q) {
+  if ((int)blockIdx.x < q.first) {
+    layernorm_bwd_block<T, VPT, GW, false>(du, x, gain, mu, rstd, resid, dx, part, rows, width, rpb, LnDrop<T>{});
+    return;
+  }
+  constexpr int N = Vec16<T>::N;
+  extern __shared__ __attribute__((aligned(16))) char ln_smem[];
+  float(*red)[64 * N] = reinterpret_cast<float(*)[64 * N]>(ln_smem);
+  const int id = (int)blockIdx.x - q.first, tile = id / q.slabs, slab = id - tile * q.slabs;
+  const int lane = threadIdx.x & 63, g = slab * 64 + lane, r1 = min(rows, (tile + 1) * kColRows);
+#pragma unroll
+  for (int k = threadIdx.x >> 6; k < kColLanes; k += kLnBwdWaves) {
+    float acc[N];
+#pragma unroll
+    for (int j = 0; j < N; ++j) acc[j] = 0.f;
+    if (g < q.width / N) {
+#pragma unroll
+      for (int r = tile * kColRows + k; r < r1; r += kColLanes) {
+        Vec16<T> a;
+        float af[N];
+        a.load(q.in + (size_t)r * q.width + (size_t)g * N);
+        a.unpack(af);
+#pragma unroll
+        for (int j = 0; j < N; ++j) acc[j] += af[j];
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < N; j += 4) *reinterpret_cast<float4*>(&red[k][lane * N + j]) = make_float4(acc[j], acc[j + 1], acc[j + 2], acc[j + 3]);
+  }
+  __syncthreads();
+  const int t = threadIdx.x, c = slab * 64 * N + t;
+  if (t < 64 * N && c < q.width) q.part[(size_t)tile * q.width + c] = colsum_lanes_sum<N>(red, t);
 }
 
 // The same for rows whose next row does not fit the registers beside the current one (more than four vectors per lane of
@@ -868,6 +925,12 @@ int launch_colsum_batch(const ColsumBatch& batch, hipStream_t st) {
   return L.status();
 }
 
+// Workgroups of column sums up to which they run in LayerNorm backward's launch: about two per compute unit.  Where they are more, the
+// launch that is saved weighs little and a kernel of their own reads at a higher rate, in the order in which its input was written.  us
+// of a pass through two layers, two launches and one (blocks): 512 wide, 512 tokens (48) 255 -> 250; 1024, 1024 (192) 462 -> 457; 2048, 1024
+// (384) 1155 -> 1150; 12288 over eight shards, 2048 (576) 5912 -> 5912; 1024, 4096 (768) 1136 -> 1138; 4096 over four, 4096 (768)
+// 2846 -> 2850; 1024, 8192 (1536) 1966 -> 1973; 2048, 8192 (3072) 5238 -> 5269.
+static constexpr int kLnSumsBlocks = 512;
 // rows walked by one block of the backward kernel: at most 256 blocks (one per compute unit of an MI355X)
 static inline int ln_bwd_rows_per_block(int rows) { return rows > 256 ? (rows + 255) / 256 : 1; }
 
@@ -890,6 +953,20 @@ static int ln_bwd_launch(const void* du, const void* x, const void* gain, const 
                      (const T*)x, (const T*)gain, mu, rstd, (const T*)resid, (T*)dx, part, rows, width, rpb, drop);
   return PTDP_OK;
 }
+template <typename T, int VPT, int GW>
+static int ln_bwd_sums_launch(const void* du, const void* x, const void* gain, const float* mu, const float* rstd, const void* resid,
+                              void* dx, float* part, int rows, int width, int rpb, int nblk, const LnSums<T>& q, hipStream_t st) {
+  constexpr int NG = kLnBwdWaves / GW, kMost = VPT * GW * 64 * Vec16<T>::N * (int)(NG > 1 ? NG * 2 * sizeof(float) : sizeof(T));
+  constexpr size_t kRed = (size_t)kColLanes * 64 * Vec16<T>::N * sizeof(float);
+  const size_t own = NG > 1 ? (size_t)NG * 2 * width * sizeof(float) : (size_t)width * sizeof(T);   // the sums need more than the gain row
+  auto kern = layernorm_bwd_sums_kernel<T, VPT, GW>;
+  static once_flag_t done[kMaxDevices];
+  if (set_dynamic_smem(reinterpret_cast<const void*>(kern), kMost > (int)kRed ? kMost : (int)kRed, done) != PTDP_OK) return PTDP_E_HIP;
+  const int blocks = q.slabs * ((rows + kColRows - 1) / kColRows);
+  hipLaunchKernelGGL(kern, dim3(nblk + blocks), dim3(kLnBwdThreads), own > kRed ? own : kRed, st, (const T*)du, (const T*)x,
+                     (const T*)gain, mu, rstd, (const T*)resid, (T*)dx, part, rows, width, rpb, q);
+  return PTDP_OK;
+}
 template <typename T, int VPT>
 static int ln_bwd_wide_launch(const void* du, const void* x, const void* gain, const float* mu, const float* rstd, const void* resid,
                               void* dx, float* part, int rows, int width, int rpb, int nblk, hipStream_t st) {
@@ -900,19 +977,21 @@ static int ln_bwd_wide_launch(const void* du, const void* x, const void* gain, c
 template <typename T>
 static int ln_bwd_t(const void* du, const void* x, const void* gain, const float* mu, const float* rstd,
                     const void* resid, void* dx, float* dgain, float* dbias, void* scratch, int rows, int width,
-                    hipStream_t st, ColsumBatch* defer, LnDrop<T>* drop = nullptr) {
+                    hipStream_t st, ColsumBatch* defer, LnDrop<T>* drop = nullptr, LnSums<T>* also = nullptr) {
   constexpr int N = Vec16<T>::N;
   const int slots = (width / N + 63) / 64;   // 64-vector pieces of a row
   if (slots > 8 * kLnBwdWaves) return PTDP_E_UNSUPPORTED;
   float* part = (float*)scratch;
   const int rpb = ln_bwd_rows_per_block(rows), nblk = (rows + rpb - 1) / rpb;
   {
-    const double bytes = (double)rows * width * sizeof(T) * ((resid ? 4 : 3) + (drop ? 1 : 0));
+    const double bytes = (double)rows * sizeof(T) * ((double)width * ((resid ? 4 : 3) + (drop ? 1 : 0)) + (also ? also->width : 0));
+    if (also) also->first = nblk;
     Launch L(PTDP_K_LN_BWD, bytes, st);
     int rc;
 #define PTDP_LN_BWD_WIDE(V) rc = ln_bwd_wide_launch<T, V>(du, x, gain, mu, rstd, resid, dx, part, rows, width, rpb, nblk, st)
 #define PTDP_LN_BWD(V, G)                                                                                                       \
   rc = drop ? ln_bwd_launch<T, V, G, true>(du, x, gain, mu, rstd, resid, dx, part, rows, width, rpb, nblk, *drop, st)          \
+       : also ? ln_bwd_sums_launch<T, V, G>(du, x, gain, mu, rstd, resid, dx, part, rows, width, rpb, nblk, *also, st)         \
             : ln_bwd_launch<T, V, G, false>(du, x, gain, mu, rstd, resid, dx, part, rows, width, rpb, nblk, LnDrop<T>{}, st)
     // Waves per row: doubled while a lane would hold more than two vectors (2048 columns, 8192 rows: four 50, two 46, one
     // 51 us with the finishing launch) and while a block has fewer rows than groups (their sums' way through LDS costs
@@ -1107,6 +1186,31 @@ int launch_bda_bwd_static(int dtype, const void* dout, void* din, float* dbias, 
   const int rc = static_scratch(&ptr);
   if (rc != PTDP_OK) return rc;
   return launch_bda_bwd(dtype, dout, din, dbias, ptr, rows, width, p, key, st, nullptr);
+}
+
+// Rows of up to 24 x 64 vectors: the forms that the launch below has.
+bool layernorm_bwd_takes_sums(int dtype, int rows, int width, int in_width) {
+  const int n = dtype == PTDP_BF16 ? 8 : 4;
+  const dim3 g = colsum_grid(in_width / n, rows);
+  return rows > 0 && width / n <= 24 * 64 && (long long)g.x * g.y <= kLnSumsBlocks;
+}
+template <typename T>
+static int ln_bwd_sums_t(const void* du, const void* x, const void* gain, const float* mu, const float* rstd, const void* resid,
+                         void* dx, float* dgain, float* dbias, void* scratch, const void* in, float* sums, void* scratch_in,
+                         int in_width, int rows, int width, hipStream_t st, ColsumBatch* defer) {
+  const dim3 g = colsum_grid(in_width / Vec16<T>::N, rows);
+  LnSums<T> also{(const T*)in, (float*)scratch_in, in_width, (int)g.x, 0};
+  const int rc = ln_bwd_t<T>(du, x, gain, mu, rstd, resid, dx, dgain, dbias, scratch, rows, width, st, defer, nullptr, &also);
+  if (rc != PTDP_OK) return rc;
+  return colsum_finish((const float*)scratch_in, g.y, in_width, sums, nullptr, in_width, st, defer);
+}
+int launch_layernorm_bwd_sums(int dtype, const void* du, const void* x, const void* gain, const float* mu, const float* rstd,
+                              const void* resid, void* dx, float* dgain, float* dbias, void* scratch, const void* in, float* sums,
+                              void* scratch_in, int in_width, int rows, int width, hipStream_t st, ColsumBatch* defer) {
+  return dtype == PTDP_BF16 ? ln_bwd_sums_t<bf16_t>(du, x, gain, mu, rstd, resid, dx, dgain, dbias, scratch, in, sums, scratch_in,
+                                                    in_width, rows, width, st, defer)
+                            : ln_bwd_sums_t<float>(du, x, gain, mu, rstd, resid, dx, dgain, dbias, scratch, in, sums, scratch_in,
+                                                   in_width, rows, width, st, defer);
 }
 
 template <typename T>

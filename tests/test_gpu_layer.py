@@ -81,6 +81,37 @@ def test_layer_rows_shared_by_few_waves(kw):
     check_layer(B.make_cfg(**kw))
 
 
+# one row, rows and columns that leave a block's last lanes empty, 1, 2, 4 and 8 waves a row; 504 and 528 workgroups of sums (the second: two launches)
+@pytest.mark.parametrize("h,a,t,s,b,dtype", [
+    (64, 2, 1, 1, 1, B.F32), (96, 3, 1, 37, 1, B.F32), (256, 4, 1, 129, 1, B.F32), (512, 4, 1, 33, 8, B.F32), (512, 8, 1, 301, 7, B.F32),
+    (256, 8, 1, 1, 1, B.BF16), (160, 1, 1, 65, 1, B.BF16), (1024, 16, 2, 301, 7, B.BF16), (2048, 16, 8, 259, 4, B.BF16), (2304, 24, 8, 259, 4, B.BF16),
+    (12288, 96, 96, 17, 2, B.BF16), (1024, 16, 1, 383, 7, B.BF16), (1024, 16, 1, 401, 7, B.BF16),
+])
+def test_qkv_bias_sums_beside_layernorm_backward(h, a, t, s, b, dtype):
+    """The QKV bias gradient's sums share a launch with the first LayerNorm's backward where they are few: every bit is that of
+    LayerNorm backward and of column sums in calls of their own with the same operands."""
+    cfg = B.make_cfg(h=h, a=a, t=t, s=s, b=b, dtype=dtype, p_hidden=0.1, seed=5)
+    rig, T, w = LayerRig(cfg), s * b, 3 * h // t
+    x, dy = randn((s, b, h), dtype, 1), randn((s, b, h), dtype, 2)
+    y, dx, dx2 = torch.empty_like(x), torch.empty_like(x), torch.empty_like(x)
+    for g in rig.grads[0].values():
+        g.fill_(0.25)   # += : the old value counts
+    B.check(rig.chunk.forward(0, x.data_ptr(), y.data_ptr(), rig.stash.data_ptr(), rig.ws.data_ptr()), "forward")
+    B.check(rig.chunk.backward(0, dy.data_ptr(), dx.data_ptr(), rig.stash.data_ptr(), rig.ws.data_ptr()), "backward")
+    at = {k: rig.ws.data_ptr() + v for k, v in B.workspace_offsets(cfg).items()}
+    st = {k: rig.stash.data_ptr() + v for k, v in rig.offsets.items()}
+    gain, bias = torch.full((h,), 0.25, device="cuda"), torch.full((h,), 0.25, device="cuda")
+    scratch = dev_bytes(max(B.ptdp_layernorm_bwd_scratch_bytes(T, h), B.ptdp_colsum_scratch_bytes(T, w)))
+    B.check(B.ptdp_layernorm_bwd(dtype, at["DU"], st["X"], rig.params[0]["ln1_g"].data_ptr(), st["MU1"], st["RSTD1"], at["DX1"],
+                                 dx2.data_ptr(), gain.data_ptr(), bias.data_ptr(), scratch.data_ptr(), T, h, stream()), "layernorm")
+    sums, out = torch.full((w,), 0.25, device="cuda"), torch.empty((T, w), dtype=tdt(dtype), device="cuda")
+    B.check(B.ptdp_bias_dropout_add_bwd(dtype, at["DQKV"], out.data_ptr(), sums.data_ptr(), scratch.data_ptr(), T, w, 0.0, 0, 0, 0, 0, stream()), "sums")
+    sync()
+    G = rig.grads[0]
+    assert torch.equal(dx, dx2) and torch.equal(G["ln1_g"], gain) and torch.equal(G["ln1_b"], bias)
+    assert torch.equal(G["b_qkv"], sums)
+
+
 def test_chunk_of_layers_and_gradient_accumulation():
     cfg = B.make_cfg(h=256, a=4, t=1, s=40, b=2, dtype=B.F32, p_hidden=0.1, seed=9)
     check_layer(cfg, n_layers=3, first_layer=4, microbatches=(0, 3))
