@@ -1584,7 +1584,7 @@ static const SmallCost kSmallCost[2][kSmallForms] = {
 constexpr int kMinStepsForGroups = 8;   // k-tiles from which two wave groups are considered: below, joining their sums costs what they save
 // k-tiles up to which 256 x 128 tiles are considered: longer products are faster on 256 x 256 tiles whose k range is split (us for
 // 256 x 128 and split: 2048 x 4096 x 12288 NT 168, 163; x 16384 NN 211, 209, NT 215, 206).  Of 1409 calls (those of
-// profiles/gemm_forms.txt and layers of 48 to 8192 tokens) they are picked in 45 and take 0.86 of the time of the form picked
+// profiles/gemm_forms.txt and layers of 48 to 8192 tokens) they are picked in 42 and take 0.85 of the time of the form picked
 // before on average, 0.985 at most.
 constexpr int kWideSteps = 120;
 // Not considered with that many workgroups per CU over that many k-tiles: the panels no longer stay in the caches and the time is
