@@ -412,24 +412,34 @@ layernorm_bwd_sums_kernel(const T* du, const T* __restrict__ x, const T* __restr
   float(*red)[64 * N] = reinterpret_cast<float(*)[64 * N]>(ln_smem);
   const int id = (int)blockIdx.x - q.first, tile = id / q.slabs, slab = id - tile * q.slabs;
   const int lane = threadIdx.x & 63, g = slab * 64 + lane, r1 = min(rows, (tile + 1) * kColRows);
+  // a wave's four rows are requested at once, at places that exist; those past the end are not added
+  constexpr int kTurns = kColLanes / kLnBwdWaves, kPer = kColRows / kColLanes;
+  const int w = threadIdx.x >> 6, r0 = tile * kColRows + w;
+  Vec16<T> a[kTurns][kPer];
+  if (g < q.width / N) {
 #pragma unroll
-  for (int k = threadIdx.x >> 6; k < kColLanes; k += kLnBwdWaves) {
+    for (int k = 0; k < kTurns; ++k)
+#pragma unroll
+      for (int u = 0; u < kPer; ++u) a[k][u].load(q.in + (size_t)min(r0 + k * kLnBwdWaves + u * kColLanes, rows - 1) * q.width + (size_t)g * N);
+  }
+#pragma unroll
+  for (int k = 0; k < kTurns; ++k) {
     float acc[N];
 #pragma unroll
     for (int j = 0; j < N; ++j) acc[j] = 0.f;
     if (g < q.width / N) {
 #pragma unroll
-      for (int r = tile * kColRows + k; r < r1; r += kColLanes) {
-        Vec16<T> a;
+      for (int u = 0; u < kPer; ++u) {
+        const bool in = r0 + k * kLnBwdWaves + u * kColLanes < r1;
         float af[N];
-        a.load(q.in + (size_t)r * q.width + (size_t)g * N);
-        a.unpack(af);
+        a[k][u].unpack(af);
 #pragma unroll
-        for (int j = 0; j < N; ++j) acc[j] += af[j];
+        for (int j = 0; j < N; ++j) acc[j] += in ? af[j] : 0.f;
       }
     }
 #pragma unroll
-    for (int j = 0; j < N; j += 4) *reinterpret_cast<float4*>(&red[k][lane * N + j]) = make_float4(acc[j], acc[j + 1], acc[j + 2], acc[j + 3]);
+    for (int j = 0; j < N; j += 4)
+      *reinterpret_cast<float4*>(&red[w + k * kLnBwdWaves][lane * N + j]) = make_float4(acc[j], acc[j + 1], acc[j + 2], acc[j + 3]);
   }
   __syncthreads();
   const int t = threadIdx.x, c = slab * 64 * N + t;
@@ -563,38 +573,47 @@ layernorm_bwd_wide_kernel(const T* du, const T* __restrict__ x, const T* __restr
 // flight, and the first wave adds the sixteen sums in order.  Bound by the latency of that chain of loads for narrow
 // layers (with four waves of four loads, 256 parts took 22 us at any width; now 5) and by reading the partial sums
 // for wide ones (h 25600: 44 -> 36 us).
+// The parts left over behind whole groups of loads are requested together as well, at places that exist, and what is too much is
+// not added: a branch for each made them a chain of up to seven trips to memory (two layers of 512, 666 tokens 262.2 -> 260.0 us, with the
+// rows' early requests in layernorm_bwd_sums_kernel; two groups of eight in flight: 260.3, fp32 layer 256 wide 103.0 -> 103.5).
 constexpr int kFinishWaves = 16, kFinishLoads = 8;
+// the next kFinishLoads (WHOLE) or n > 0 parts; p is the same for the whole wave, c the lane's column
+template <bool TWO, bool WHOLE>
+__device__ __forceinline__ void colsum_finish_step(const float* __restrict__ p, int c, int n, int stride, int width, float (&sa)[kFinishLoads],
+                                                   float (&sb)[kFinishLoads]) {
+  float va[kFinishLoads], vb[kFinishLoads];
+#pragma unroll
+  for (int u = 0; u < kFinishLoads; ++u) {
+    const float* row = p + (size_t)(WHOLE ? u : min(u, n - 1)) * stride;
+    va[u] = row[c];
+    vb[u] = TWO ? row[width + c] : 0.f;
+  }
+#pragma unroll
+  for (int u = 0; u < kFinishLoads; ++u) {
+    sa[u] += WHOLE || u < n ? va[u] : 0.f;
+    sb[u] += WHOLE || u < n ? vb[u] : 0.f;
+  }
+}
 template <bool TWO>
-__device__ __forceinline__ void colsum_finish_part(const float* __restrict__ p, int n, int stride, int width, float& a, float& b) {
+__device__ __forceinline__ void colsum_finish_part(const float* __restrict__ p, int c, int n, int stride, int width, float& a, float& b) {
   float sa[kFinishLoads], sb[kFinishLoads];
 #pragma unroll
   for (int u = 0; u < kFinishLoads; ++u) sa[u] = sb[u] = 0.f;
-  for (; n >= kFinishLoads; n -= kFinishLoads, p += (size_t)kFinishLoads * stride) {
-#pragma unroll
-    for (int u = 0; u < kFinishLoads; ++u) {
-      sa[u] += p[(size_t)u * stride];
-      if (TWO) sb[u] += p[(size_t)u * stride + width];
-    }
-  }
-#pragma unroll
-  for (int u = 0; u < kFinishLoads; ++u)
-    if (u < n) {
-      sa[u] += p[(size_t)u * stride];
-      if (TWO) sb[u] += p[(size_t)u * stride + width];
-    }
+  for (; n >= kFinishLoads; n -= kFinishLoads, p += (size_t)kFinishLoads * stride) colsum_finish_step<TWO, true>(p, c, n, stride, width, sa, sb);
+  if (n > 0) colsum_finish_step<TWO, false>(p, c, n, stride, width, sa, sb);
   a = ((sa[0] + sa[1]) + (sa[2] + sa[3])) + ((sa[4] + sa[5]) + (sa[6] + sa[7]));
   b = ((sb[0] + sb[1]) + (sb[2] + sb[3])) + ((sb[4] + sb[5]) + (sb[6] + sb[7]));
 }
 __device__ __forceinline__ void colsum_finish_block(const float* __restrict__ part, int nparts, int stride, float* out0, float* out1,
                                                     int width, int blk) {
   __shared__ float red[2][kFinishWaves][64];
-  const int lane = threadIdx.x & 63, q = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, q = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int c = blk * 64 + lane;
   const int per = (nparts + kFinishWaves - 1) / kFinishWaves, p0 = q * per, n = min(nparts, p0 + per) - p0;
   float a = 0.f, b = 0.f;
   if (c < width && n > 0) {
-    if (out1) colsum_finish_part<true>(part + (size_t)p0 * stride + c, n, stride, width, a, b);
-    else colsum_finish_part<false>(part + (size_t)p0 * stride + c, n, stride, width, a, b);
+    if (out1) colsum_finish_part<true>(part + (size_t)p0 * stride, c, n, stride, width, a, b);
+    else colsum_finish_part<false>(part + (size_t)p0 * stride, c, n, stride, width, a, b);
   }
   red[0][q][lane] = a;
   red[1][q][lane] = b;
