@@ -1090,6 +1090,7 @@ __device__ __forceinline__ void gemm_wide_tile(const GemmArgs& g, void* Cv, int 
     __builtin_amdgcn_sched_barrier(0);
   };
   auto wait_loads = [] { asm volatile("s_waitcnt vmcnt(12)" ::: "memory"); };   // all but the youngest k-tile's
+  auto wait_reads = [] { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); };
   auto request = [&](int kt, int stage) {
     char* at = smem + stage * kWideStage;
     lb[0].template issue<false>(rb, at + kB0, wave, lane, kt, g.K);
@@ -1140,6 +1141,8 @@ __device__ __forceinline__ void gemm_wide_tile(const GemmArgs& g, void* Cv, int 
   fa.move(stage * kWideStage);
   fb.move(stage * kWideStage);
   read_b(bfr[0], kB0);
+  wait_reads();   // by the whole group: phase 0 refills this place
+  barrier();
   auto tile = [&](auto parity, auto lean, int kt) {
     constexpr int S = decltype(parity)::value, O = S ^ 1;
     constexpr bool LEAN = decltype(lean)::value;
@@ -1174,7 +1177,7 @@ __device__ __forceinline__ void gemm_wide_tile(const GemmArgs& g, void* Cv, int 
     la[1].template issue<LEAN>(ra, own + kA, wave, lane, kt + 3, g.K);
     wait_loads();
     barrier();
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    wait_reads();
     compute(acc[2], bfr[S]);
     barrier();
   };
