@@ -581,7 +581,10 @@ __device__ __forceinline__ void gemm_mainloop(TileAcc& acc, const GemmArgs& g, i
   for (int j = 0; j < 2; ++j)
 #pragma unroll
     for (int ks = 0; ks < 2; ++ks) bfr[0][j][ks] = fb.template get<0>(kB0, j, ks);
-  if (wave >= 4) barrier();   // the second group runs one part behind the first
+  if (wave >= 4) {   // the second group runs one part behind the first, which refills what was read here while the second multiplies
+    wait_reads();
+    barrier();
+  }
 
   auto compute = [&](f32x4_t (&c)[4][2], const bf16x8_t (&b)[2][2]) {
     __builtin_amdgcn_s_setprio(1);

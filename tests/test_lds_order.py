@@ -52,3 +52,14 @@ def test_256x128_tiles_first_reads_are_complete_before_their_place_is_refilled(k
         first = position(code, READ)
         request, wait = position(code, REQUEST, first), position(code, WAIT, first)
         assert position(code, BARRIER, wait) < request, name
+
+
+def test_256x256_tiles_first_reads_are_complete_at_the_second_groups_first_barrier(kernels):
+    """Both groups of waves share every place.  The first refills the half-tile that all read in front of the loop two barriers after
+    those reads, while the second multiplies for the first time: the second has waited for them before its extra barrier."""
+    found = [k for k in kernels if any(x in k for x in ("gemm_bf16_dp_kernel", "gemm_bf16_dp_multi_kernel", "gemm_bf16_split_kernel"))]
+    assert len(found) > 3
+    for name in found:
+        code = kernels[name]
+        first = position(code, READ)
+        assert position(code, WAIT, first) < position(code, BARRIER, first), name
