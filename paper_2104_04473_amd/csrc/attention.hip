@@ -26,8 +26,10 @@ typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4_t;
 
 // ------------------------------------------------------------------------------------------------
 // fp32 kernels on v_mfma_f32_16x16x4_f32 (fp32 products and sums).  A workgroup of NW waves (four, or eight
-// where workgroups are few) owns 16 queries (forward, dQ) or 16 keys (dK, dV) of one head; each wave takes every NW-th 16-row tile
-// of the other side and the partial results meet in LDS in a fixed order (eight waves' shorter sums: error against 64 bits 1 to 13 % smaller).  Operands come from memory straight into fragments: lane (c = lane & 15,
+// where workgroups are few) owns 16 queries (forward, dQ) or 16 keys (dK, dV) of one head.  The walk over the other side is PARTS
+// partial sums, each over every PARTS-th 16-row tile, that meet in LDS in a fixed order (eight instead of four: error against 64
+// bits 1 to 13 % smaller).  PARTS follows from s and dh alone and a wave makes PARTS / NW of them one after the other, so that a
+// sample's results have the same bits whatever else is in the call.  Operands come from memory straight into fragments: lane (c = lane & 15,
 // g = lane >> 4) carries four consecutive dh of row c (elements 16 i + 4 g .. +3 of step i; both factors of a product
 // share that order), and the score tile S^T comes out with column c = the workgroup's row and rows 4 g + r = the tile's,
 // which is the second product's B operand as it stands.  These are small calls (fp32 is the precision of small
@@ -112,8 +114,8 @@ __device__ __forceinline__ void f32_accumulate(f32x4_t (&acc)[ND], f32x4_t w, co
       }
   }
 }
-// waves 1 .. NW - 1 hand their sums to wave 0 (added in that order); returns true in wave 0.  part: (NW - 1) * ND * 64 vectors.
-template <int ND, int NW> __device__ __forceinline__ bool f32_join(f32x4_t (&acc)[ND], f32x4_t* part, int wave, int lane) {
+// Four waves with a part each: waves 1 .. 3 hand theirs to wave 0 (added in that order); returns true in wave 0.  part: 3 * ND * 64 vectors.
+template <int ND> __device__ __forceinline__ bool f32_join(f32x4_t (&acc)[ND], f32x4_t* part, int wave, int lane) {
   __syncthreads();
   if (wave > 0) {
 #pragma unroll
@@ -122,23 +124,85 @@ template <int ND, int NW> __device__ __forceinline__ bool f32_join(f32x4_t (&acc
   __syncthreads();
   if (wave > 0) return false;
 #pragma unroll
-  for (int w = 0; w < NW - 1; ++w)
+  for (int w = 0; w < 3; ++w)
 #pragma unroll
     for (int t = 0; t < ND; ++t) acc[t] += part[(w * ND + t) * 64 + lane];
   return true;
 }
+// Eight parts: part w and part w + 4, then those four sums in order.  Four waves make two parts each: the earlier one waits in the
+// wave's own place (f32_set_aside) and f32_add_pair adds it to the later one; of eight waves the upper four hand theirs to the lower.
+// place: 4 * ND * 64 vectors per sum.
+template <int ND> __device__ __forceinline__ void f32_set_aside(f32x4_t (&acc)[ND], f32x4_t* place, int wave, int lane) {
+#pragma unroll
+  for (int t = 0; t < ND; ++t) {
+    place[(wave * ND + t) * 64 + lane] = acc[t];
+    acc[t] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  }
+}
+// (the products are rounded by themselves, or a form might fuse with the sum behind them what another does not)
+template <int ND> __device__ __forceinline__ void f32_scale(f32x4_t (&acc)[ND], float f) {
+#pragma clang fp contract(off)
+#pragma unroll
+  for (int t = 0; t < ND; ++t) acc[t] *= f;
+}
+template <int ND, int NW> __device__ __forceinline__ void f32_add_pair(f32x4_t (&acc)[ND], const f32x4_t* place, float factor, int wave, int lane) {
+  if (NW == 8 && wave >= 4) return;
+  f32x4_t other[ND];
+#pragma unroll
+  for (int t = 0; t < ND; ++t) other[t] = place[(wave * ND + t) * 64 + lane];
+  if (NW == 4) f32_scale<ND>(other, factor);
+#pragma unroll
+  for (int t = 0; t < ND; ++t) acc[t] += other[t];
+}
+// NS sums at once; sum q ends up in wave q.  factor: of the parts set aside (NW = 4)
+template <int ND, int NW, int NS>
+__device__ __forceinline__ void f32_join_eight(f32x4_t (&acc)[NS][ND], f32x4_t* place, float factor, int wave, int lane) {
+  constexpr int kSum = 4 * ND * 64;
+  if (NW == 8) {
+    if (wave >= 4) {
+#pragma unroll
+      for (int q = 0; q < NS; ++q) f32_set_aside<ND>(acc[q], place + q * kSum, wave - 4, lane);
+    }
+    __syncthreads();
+  }
+#pragma unroll
+  for (int q = 0; q < NS; ++q) {
+    f32_add_pair<ND, NW>(acc[q], place + q * kSum, factor, wave, lane);
+    if (wave < 4 && wave != q) {
+#pragma unroll
+      for (int t = 0; t < ND; ++t) place[q * kSum + (wave * ND + t) * 64 + lane] = acc[q][t];
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < NS; ++q)
+    if (wave == q) {
+#pragma unroll
+      for (int t = 0; t < ND; ++t) {
+        f32x4_t sum = q == 0 ? acc[q][t] : place[q * kSum + t * 64 + lane];
+#pragma unroll
+        for (int w = 1; w < 4; ++w) sum += w == q ? acc[q][t] : place[q * kSum + (w * ND + t) * 64 + lane];
+        acc[q][t] = sum;
+      }
+    }
+}
+// vectors of LDS for `sums` sums
+constexpr int f32_places(int nd, int parts, int sums) { return (parts == 8 ? sums * 4 : 3) * nd * 64; }
 template <int ND> __device__ __forceinline__ void f32_store(float* row, const f32x4_t (&acc)[ND], int g, int dh) {
 #pragma unroll
   for (int t = 0; t < ND; ++t)
     if (16 * t + 4 * g < dh) *reinterpret_cast<f32x4_t*>(row + 16 * t + 4 * g) = acc[t];
 }
 
-template <int ND, int NW>
-__global__ void __launch_bounds__(64 * NW)
+// Waves on a SIMD that the forward kernel's registers leave with a part to each of four waves; the walk in two turns had taken eight
+// registers more and with them one of these waves (1024 workgroups of heads of 96 x 128 30 -> 47 us).
+constexpr int f32_fwd_waves(int nd, int nw) { return nw == 8 ? 2 : nd == 2 ? 7 : nd == 4 ? 5 : nd == 6 ? 4 : nd == 8 ? 3 : 1; }
+template <int ND, int NW, int PARTS>
+__global__ void __launch_bounds__(64 * NW, f32_fwd_waves(ND, NW))
 attn_fwd_f32(const float* __restrict__ qkv, float* __restrict__ ctx, float* __restrict__ lse, int s, int b, int heads, int dh,
              const uint8_t* __restrict__ mask, int causal) {
-  __shared__ f32x4_t part[(NW - 1) * ND * 64];
-  __shared__ float stat[2][NW][16];
+  __shared__ f32x4_t part[f32_places(ND, PARTS, 1)];
+  __shared__ float stat[2][PARTS][16];
   const int e = blockIdx.y, j = blockIdx.z, wave = threadIdx.x >> 6, lane = threadIdx.x & 63, c = lane & 15, g = lane >> 4;
   const int q0 = ((int)gridDim.x - 1 - (int)blockIdx.x) * kF32Rows, my_q = q0 + c;   // long rows first
   const int hp = heads * dh;
@@ -147,61 +211,68 @@ attn_fwd_f32(const float* __restrict__ qkv, float* __restrict__ ctx, float* __re
   const float scale = rsqrtf((float)dh);
   F32Frag<ND> q;
   f32_load<ND>(q, base + (size_t)min(my_q, s - 1) * rs, g, dh);
-  f32x4_t o[ND];
+  f32x4_t acc[1][ND];
+  f32x4_t (&o)[ND] = acc[0];
 #pragma unroll
   for (int t = 0; t < ND; ++t) o[t] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-  float m = -INFINITY, l = 0.f;
+  float m;
   const int ntiles = ((causal ? min(q0 + kF32Rows, s) : s) + kF32Rows - 1) / kF32Rows;
   const uint8_t* mrow = (!causal && mask) ? mask + ((size_t)j * s + min(my_q, s - 1)) * s : nullptr;
-  for (int kt = wave; kt < ntiles; kt += NW) {
-    const int key0 = kt * kF32Rows;
-    F32Frag<ND> k;
-    f32_load<ND>(k, base + hp + (size_t)min(key0 + c, s - 1) * rs, g, dh);
-    f32x4_t p = f32_scores<ND>(k, q);
-    uint32_t vis = 0;
-    float mx = m;
+#pragma unroll 1
+  for (int pt = wave; pt < PARTS; pt += NW) {   // the wave's parts
+    float l = 0.f;
+    m = -INFINITY;
+    for (int kt = pt; kt < ntiles; kt += PARTS) {
+      const int key0 = kt * kF32Rows;
+      F32Frag<ND> k;
+      f32_load<ND>(k, base + hp + (size_t)min(key0 + c, s - 1) * rs, g, dh);
+      f32x4_t p = f32_scores<ND>(k, q);
+      uint32_t vis = 0;
+      float mx = m;
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int key = key0 + 4 * g + r;
-      p[r] *= scale;
-      if (mrow && key < s && mrow[key]) p[r] = kMaskFill;
-      const bool ok = key < s && (!causal || key <= my_q);
-      p[r] = ok ? p[r] : -INFINITY;
-      vis |= (uint32_t)ok << r;
-      mx = fmaxf(mx, p[r]);
+      for (int r = 0; r < 4; ++r) {
+        const int key = key0 + 4 * g + r;
+        p[r] *= scale;
+        if (mrow && key < s && mrow[key]) p[r] = kMaskFill;
+        const bool ok = key < s && (!causal || key <= my_q);
+        p[r] = ok ? p[r] : -INFINITY;
+        vis |= (uint32_t)ok << r;
+        mx = fmaxf(mx, p[r]);
+      }
+      const LaneHalves mr = lane_rows(mx);
+      const LaneHalves mh = lane_halves(fmaxf(mr.lo, mr.hi));
+      mx = fmaxf(mh.lo, mh.hi);
+      const float ref = mx == -INFINITY ? 0.f : mx;   // only scores of -inf so far: weights of zero, not exp(-inf + inf)
+      const float corr = __expf(m - ref);
+      m = mx;
+      l *= corr;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        p[r] = __expf(p[r] - ref);
+        l += p[r];
+      }
+#pragma unroll
+      for (int t = 0; t < ND; ++t) o[t] *= corr;
+      f32_accumulate<ND>(o, p, base + 2 * hp, rs, key0, s, dh, causal && key0 + kF32Rows > q0, vis, lane);
     }
-    const LaneHalves mr = lane_rows(mx);
-    const LaneHalves mh = lane_halves(fmaxf(mr.lo, mr.hi));
-    mx = fmaxf(mh.lo, mh.hi);
-    const float ref = mx == -INFINITY ? 0.f : mx;   // only scores of -inf so far: weights of zero, not exp(-inf + inf)
-    const float corr = __expf(m - ref);
-    m = mx;
-    l *= corr;
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      p[r] = __expf(p[r] - ref);
-      l += p[r];
+    l += __shfl_xor(l, 16, 64);
+    l += __shfl_xor(l, 32, 64);
+    if (g == 0) {
+      stat[0][pt][c] = m;
+      stat[1][pt][c] = l;
     }
-#pragma unroll
-    for (int t = 0; t < ND; ++t) o[t] *= corr;
-    f32_accumulate<ND>(o, p, base + 2 * hp, rs, key0, s, dh, causal && key0 + kF32Rows > q0, vis, lane);
-  }
-  l += __shfl_xor(l, 16, 64);
-  l += __shfl_xor(l, 32, 64);
-  if (g == 0) {
-    stat[0][wave][c] = m;
-    stat[1][wave][c] = l;
+    if (pt + NW < PARTS) f32_set_aside<ND>(o, part, wave, lane);
   }
   __syncthreads();
-  float mall = stat[0][0][c], lall = 0.f;   // wave 0 always has a tile
+  float mall = stat[0][0][c], lall = 0.f;   // the first part always has a tile
 #pragma unroll
-  for (int w = 1; w < NW; ++w) mall = fmaxf(mall, stat[0][w][c]);
+  for (int w = 1; w < PARTS; ++w) mall = fmaxf(mall, stat[0][w][c]);
 #pragma unroll
-  for (int w = 0; w < NW; ++w) lall += stat[1][w][c] * __expf(stat[0][w][c] - mall);
-  const float f = __expf(m - mall);   // a wave without a tile: m = -inf, its zeros are multiplied by zero
-#pragma unroll
-  for (int t = 0; t < ND; ++t) o[t] *= f;
-  if (!f32_join<ND, NW>(o, part, wave, lane) || my_q >= s) return;
+  for (int w = 0; w < PARTS; ++w) lall += stat[1][w][c] * __expf(stat[0][w][c] - mall);
+  f32_scale<ND>(o, __expf(m - mall));   // a part without a tile: m = -inf, its zeros are multiplied by zero
+  if constexpr (PARTS == 8) f32_join_eight<ND, NW, 1>(acc, part, __expf(stat[0][wave][c] - mall), wave, lane);
+  else f32_join<ND>(o, part, wave, lane);
+  if (wave > 0 || my_q >= s) return;
 #pragma unroll
   for (int t = 0; t < ND; ++t) o[t] /= lall;
   f32_store<ND>(ctx + ((size_t)my_q * b + j) * hp + (size_t)e * dh, o, g, dh);
@@ -224,7 +295,7 @@ template <int ND> __device__ __forceinline__ f32x4_t f32_delta_rows(const F32Fra
 }
 
 // dQ of 16 queries, and (delta not NULL) their delta for the dK/dV kernel
-template <int ND, int NW>
+template <int ND, int NW, int PARTS>
 __device__ __forceinline__ void f32_dq_block(const float* __restrict__ qkv, const float* __restrict__ ctx, const float* __restrict__ dctx,
                                              const float* __restrict__ lse, float* __restrict__ delta, float* __restrict__ dqkv, int s, int b,
                                              int heads, int dh, const uint8_t* __restrict__ mask, int causal, int blk, f32x4_t* part) {
@@ -246,35 +317,41 @@ __device__ __forceinline__ void f32_dq_block(const float* __restrict__ qkv, cons
   }
   if (delta && wave == 0 && g == 0 && my_q < s) delta[stat] = D;
   const float L = lse[stat];
-  f32x4_t acc[ND];
+  f32x4_t acc[1][ND];
 #pragma unroll
-  for (int t = 0; t < ND; ++t) acc[t] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  for (int t = 0; t < ND; ++t) acc[0][t] = f32x4_t{0.f, 0.f, 0.f, 0.f};
   const int ntiles = ((causal ? min(q0 + kF32Rows, s) : s) + kF32Rows - 1) / kF32Rows;
   const uint8_t* mrow = (!causal && mask) ? mask + ((size_t)j * s + qr) * s : nullptr;
-  for (int kt = wave; kt < ntiles; kt += NW) {
-    const int key0 = kt * kF32Rows;
-    const size_t row = (size_t)min(key0 + c, s - 1) * rs;
-    F32Frag<ND> k, v;
-    f32_load<ND>(k, base + hp + row, g, dh);
-    f32_load<ND>(v, base + 2 * hp + row, g, dh);
-    const f32x4_t sc = f32_scores<ND>(k, q), dp = f32_scores<ND>(v, dc);
-    f32x4_t ds;
-    uint32_t vis = 0;
+#pragma unroll 1
+  for (int pt = wave; pt < PARTS; pt += NW) {   // the wave's parts
+    for (int kt = pt; kt < ntiles; kt += PARTS) {
+      const int key0 = kt * kF32Rows;
+      const size_t row = (size_t)min(key0 + c, s - 1) * rs;
+      F32Frag<ND> k, v;
+      f32_load<ND>(k, base + hp + row, g, dh);
+      f32_load<ND>(v, base + 2 * hp + row, g, dh);
+      const f32x4_t sc = f32_scores<ND>(k, q), dp = f32_scores<ND>(v, dc);
+      f32x4_t ds;
+      uint32_t vis = 0;
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int key = key0 + 4 * g + r;
-      const bool ok = key < s && (causal ? key <= my_q : !(mrow && mrow[key]));
-      ds[r] = ok ? __expf(sc[r] * scale - L) * (dp[r] - D) * scale : 0.f;
-      vis |= (uint32_t)ok << r;
+      for (int r = 0; r < 4; ++r) {
+        const int key = key0 + 4 * g + r;
+        const bool ok = key < s && (causal ? key <= my_q : !(mrow && mrow[key]));
+        ds[r] = ok ? __expf(sc[r] * scale - L) * (dp[r] - D) * scale : 0.f;
+        vis |= (uint32_t)ok << r;
+      }
+      f32_accumulate<ND>(acc[0], ds, base + hp, rs, key0, s, dh, causal && key0 + kF32Rows > q0, vis, lane);
     }
-    f32_accumulate<ND>(acc, ds, base + hp, rs, key0, s, dh, causal && key0 + kF32Rows > q0, vis, lane);
+    if (pt + NW < PARTS) f32_set_aside<ND>(acc[0], part, wave, lane);
   }
-  if (!f32_join<ND, NW>(acc, part, wave, lane) || my_q >= s) return;
-  f32_store<ND>(dqkv + (size_t)my_q * rs + (size_t)j * 3 * hp + (size_t)e * dh, acc, g, dh);
+  if constexpr (PARTS == 8) f32_join_eight<ND, NW, 1>(acc, part, 1.f, wave, lane);
+  else f32_join<ND>(acc[0], part, wave, lane);
+  if (wave > 0 || my_q >= s) return;
+  f32_store<ND>(dqkv + (size_t)my_q * rs + (size_t)j * 3 * hp + (size_t)e * dh, acc[0], g, dh);
 }
 
 // dK, dV of 16 keys.  OWN_DELTA: the queries' delta is computed here as well (ctx), not read (delta).
-template <int ND, int NW, bool OWN_DELTA>
+template <int ND, int NW, int PARTS, bool OWN_DELTA>
 __device__ __forceinline__ void f32_dkv_block(const float* __restrict__ qkv, const float* __restrict__ ctx, const float* __restrict__ dctx,
                                               const float* __restrict__ lse, const float* __restrict__ delta, float* __restrict__ dqkv, int s,
                                               int b, int heads, int dh, const uint8_t* __restrict__ mask, int causal, int blk, f32x4_t* part) {
@@ -291,71 +368,87 @@ __device__ __forceinline__ void f32_dkv_block(const float* __restrict__ qkv, con
   F32Frag<ND> k, v;
   f32_load<ND>(k, base + hp + (size_t)kr * rs, g, dh);
   f32_load<ND>(v, base + 2 * hp + (size_t)kr * rs, g, dh);
-  f32x4_t dk[ND], dv[ND];
+  f32x4_t acc[2][ND];
+  f32x4_t (&dk)[ND] = acc[0], (&dv)[ND] = acc[1];
 #pragma unroll
   for (int t = 0; t < ND; ++t) dk[t] = dv[t] = f32x4_t{0.f, 0.f, 0.f, 0.f};
   const int ntiles = (s + kF32Rows - 1) / kF32Rows;
-  for (int qt = (causal ? blk : 0) + wave; qt < ntiles; qt += NW) {
-    const int q0 = qt * kF32Rows;
-    f32x4_t sc, dp, p, ds, own = {0.f, 0.f, 0.f, 0.f};
-    {
-      F32Frag<ND> q, dc;
-      f32_load<ND>(q, base + (size_t)min(q0 + c, s - 1) * rs, g, dh);
-      f32_load<ND>(dc, dobase + (size_t)min(q0 + c, s - 1) * dors, g, dh);
-      if constexpr (OWN_DELTA) {
-        F32Frag<ND> o;
-        f32_load<ND>(o, cbase + (size_t)min(q0 + c, s - 1) * dors, g, dh);
-        own = f32_delta_rows<ND>(o, dc, g);
+#pragma unroll 1
+  for (int pt = wave; pt < PARTS; pt += NW) {   // the wave's parts
+    for (int qt = (causal ? blk : 0) + pt; qt < ntiles; qt += PARTS) {
+      const int q0 = qt * kF32Rows;
+      f32x4_t sc, dp, p, ds, own = {0.f, 0.f, 0.f, 0.f};
+      {
+        F32Frag<ND> q, dc;
+        f32_load<ND>(q, base + (size_t)min(q0 + c, s - 1) * rs, g, dh);
+        f32_load<ND>(dc, dobase + (size_t)min(q0 + c, s - 1) * dors, g, dh);
+        if constexpr (OWN_DELTA) {
+          F32Frag<ND> o;
+          f32_load<ND>(o, cbase + (size_t)min(q0 + c, s - 1) * dors, g, dh);
+          own = f32_delta_rows<ND>(o, dc, g);
+        }
+        sc = f32_scores<ND>(q, k);
+        dp = f32_scores<ND>(dc, v);
       }
-      sc = f32_scores<ND>(q, k);
-      dp = f32_scores<ND>(dc, v);
-    }
-    uint32_t vis = 0;
+      uint32_t vis = 0;
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int q = q0 + 4 * g + r, qq = min(q, s - 1);
-      const bool ok = q < s && (!causal || q >= my_key);
-      const bool hidden = !causal && mask && mask[((size_t)j * s + qq) * s + kr];
-      p[r] = ok ? __expf((hidden ? kMaskFill : sc[r] * scale) - lse_h[qq]) : 0.f;
-      ds[r] = ok && !hidden ? p[r] * (dp[r] - (OWN_DELTA ? own[r] : delta_h[qq])) * scale : 0.f;
-      vis |= (uint32_t)ok << r;
+      for (int r = 0; r < 4; ++r) {
+        const int q = q0 + 4 * g + r, qq = min(q, s - 1);
+        const bool ok = q < s && (!causal || q >= my_key);
+        const bool hidden = !causal && mask && mask[((size_t)j * s + qq) * s + kr];
+        p[r] = ok ? __expf((hidden ? kMaskFill : sc[r] * scale) - lse_h[qq]) : 0.f;
+        ds[r] = ok && !hidden ? p[r] * (dp[r] - (OWN_DELTA ? own[r] : delta_h[qq])) * scale : 0.f;
+        vis |= (uint32_t)ok << r;
+      }
+      const bool diag = causal && q0 < k0 + kF32Rows;
+      f32_accumulate<ND>(dv, p, dobase, dors, q0, s, dh, diag, vis, lane);
+      f32_accumulate<ND>(dk, ds, base, rs, q0, s, dh, diag, vis, lane);
     }
-    const bool diag = causal && q0 < k0 + kF32Rows;
-    f32_accumulate<ND>(dv, p, dobase, dors, q0, s, dh, diag, vis, lane);
-    f32_accumulate<ND>(dk, ds, base, rs, q0, s, dh, diag, vis, lane);
+    if (pt + NW < PARTS) {
+      f32_set_aside<ND>(dk, part, wave, lane);
+      f32_set_aside<ND>(dv, part + 4 * ND * 64, wave, lane);
+    }
   }
   float* out = dqkv + (size_t)my_key * rs + (size_t)j * 3 * hp + (size_t)e * dh;
-  const bool mine = f32_join<ND, NW>(dk, part, wave, lane);
-  if (mine && my_key < s) f32_store<ND>(out + hp, dk, g, dh);
-  if (f32_join<ND, NW>(dv, part, wave, lane) && my_key < s) f32_store<ND>(out + 2 * hp, dv, g, dh);
+  if constexpr (PARTS == 8) {
+    f32_join_eight<ND, NW, 2>(acc, part, 1.f, wave, lane);
+    if (my_key >= s) return;
+    if (wave == 0) f32_store<ND>(out + hp, dk, g, dh);
+    if (wave == 1) f32_store<ND>(out + 2 * hp, dv, g, dh);
+  } else {
+    const bool mine = f32_join<ND>(dk, part, wave, lane);
+    if (mine && my_key < s) f32_store<ND>(out + hp, dk, g, dh);
+    if (f32_join<ND>(dv, part, wave, lane) && my_key < s) f32_store<ND>(out + 2 * hp, dv, g, dh);
+  }
 }
 
-template <int ND, int NW>
-__global__ void __launch_bounds__(64 * NW)
+constexpr int f32_dq_waves(int nd, int nw) { return nw == 8 ? 2 : nd == 2 ? 6 : nd == 4 ? 4 : nd == 6 ? 3 : nd == 8 ? 2 : 1; }   // likewise
+template <int ND, int NW, int PARTS>
+__global__ void __launch_bounds__(64 * NW, f32_dq_waves(ND, NW))
 attn_bwd_dq_f32(const float* __restrict__ qkv, const float* __restrict__ ctx, const float* __restrict__ dctx,
                 const float* __restrict__ lse, float* __restrict__ delta, float* __restrict__ dqkv, int s, int b, int heads, int dh,
                 const uint8_t* __restrict__ mask, int causal) {
-  __shared__ f32x4_t part[(NW - 1) * ND * 64];
+  __shared__ f32x4_t part[f32_places(ND, PARTS, 1)];
   // long rows first
-  f32_dq_block<ND, NW>(qkv, ctx, dctx, lse, delta, dqkv, s, b, heads, dh, mask, causal, (int)gridDim.x - 1 - (int)blockIdx.x, part);
+  f32_dq_block<ND, NW, PARTS>(qkv, ctx, dctx, lse, delta, dqkv, s, b, heads, dh, mask, causal, (int)gridDim.x - 1 - (int)blockIdx.x, part);
 }
-template <int ND, int NW>
+template <int ND, int NW, int PARTS>
 __global__ void __launch_bounds__(64 * NW)
 attn_bwd_dkv_f32(const float* __restrict__ qkv, const float* __restrict__ dctx, const float* __restrict__ lse,
                  const float* __restrict__ delta, float* __restrict__ dqkv, int s, int b, int heads, int dh,
                  const uint8_t* __restrict__ mask, int causal) {
-  __shared__ f32x4_t part[(NW - 1) * ND * 64];
-  f32_dkv_block<ND, NW, false>(qkv, nullptr, dctx, lse, delta, dqkv, s, b, heads, dh, mask, causal, blockIdx.x, part);
+  __shared__ f32x4_t part[f32_places(ND, PARTS, 2)];
+  f32_dkv_block<ND, NW, PARTS, false>(qkv, nullptr, dctx, lse, delta, dqkv, s, b, heads, dh, mask, causal, blockIdx.x, part);
 }
 // Both in one launch: dK/dV computes the delta of its queries itself, so that neither waits for the other.
-template <int ND, int NW>
+template <int ND, int NW, int PARTS>
 __global__ void __launch_bounds__(64 * NW)
 attn_bwd_f32(const float* __restrict__ qkv, const float* __restrict__ ctx, const float* __restrict__ dctx, const float* __restrict__ lse,
              float* __restrict__ dqkv, int s, int b, int heads, int dh, const uint8_t* __restrict__ mask, int causal) {
-  __shared__ f32x4_t part[(NW - 1) * ND * 64];
+  __shared__ f32x4_t part[f32_places(ND, PARTS, 2)];
   const int n = (int)gridDim.x / 2, x = (int)blockIdx.x;
-  if (x < n) f32_dkv_block<ND, NW, true>(qkv, ctx, dctx, lse, nullptr, dqkv, s, b, heads, dh, mask, causal, x, part);
-  else f32_dq_block<ND, NW>(qkv, ctx, dctx, lse, nullptr, dqkv, s, b, heads, dh, mask, causal, 2 * n - 1 - x, part);
+  if (x < n) f32_dkv_block<ND, NW, PARTS, true>(qkv, ctx, dctx, lse, nullptr, dqkv, s, b, heads, dh, mask, causal, x, part);
+  else f32_dq_block<ND, NW, PARTS>(qkv, ctx, dctx, lse, nullptr, dqkv, s, b, heads, dh, mask, causal, 2 * n - 1 - x, part);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -1437,23 +1530,28 @@ static bool attn_sizes_fit(int s, int b, int heads) {
     else CALL(16);                  \
   } while (0)
 
-template <int ND, int NW>
+template <int ND, int NW, int PARTS>
 static void attn_fwd_f32_nw(const float* qkv, float* ctx, float* lse, int s, int b, int heads, int dh, const uint8_t* mask, int causal,
                             hipStream_t stream) {
-  hipLaunchKernelGGL((attn_fwd_f32<ND, NW>), dim3((s + kF32Rows - 1) / kF32Rows, heads, b), dim3(64 * NW), 0, stream, qkv, ctx, lse, s, b, heads, dh,
+  hipLaunchKernelGGL((attn_fwd_f32<ND, NW, PARTS>), dim3((s + kF32Rows - 1) / kF32Rows, heads, b), dim3(64 * NW), 0, stream, qkv, ctx, lse, s, b, heads, dh,
                      mask, causal);
 }
 // Eight waves for more than four tiles of 16 keys while the workgroups leave the chip's wave slots empty (heads beyond 128 take too
 // many registers).  us with four and with eight waves, causal: 64 workgroups of dh 64 x 128 9.1, 8.1, x 256 14.5, 11.3; 256 x 256 15.1, 11.6; 512 x
-// 512 47, 33; 1024 107, 108; dh 128: 256 x 256 41, 29, 512 91, 95; 48 rows (three tiles) 6.3, 7.1.
+// 512 47, 33; 1024 107, 108; dh 128: 256 x 256 41, 29, 512 91, 95; 48 rows (three tiles) 6.3, 7.1.  (Four waves with four parts: that four waves make
+// the eight parts of a longer walk costs them, in the forward, 1024 workgroups of 32 x 66 7.0 -> 7.5, 32 x 256 18.2 -> 18.4, 64 x 128 20.6 -> 21.1,
+// 96 x 100 26.6 -> 27.9, 64 x 512 58.6 -> 56.9; backward -4 to +4 %.)
 template <int ND>
 static void attn_fwd_f32_t(const float* qkv, float* ctx, float* lse, int s, int b, int heads, int dh, const uint8_t* mask, int causal,
                            hipStream_t stream) {
   if constexpr (ND <= 8) {
     const long long groups = (long long)((s + kF32Rows - 1) / kF32Rows) * heads * b, ncu = attn_compute_units();
-    if (s > 4 * kF32Rows && groups <= (ND <= 6 ? 2 : 1) * ncu) return attn_fwd_f32_nw<ND, 8>(qkv, ctx, lse, s, b, heads, dh, mask, causal, stream);
+    if (s > 4 * kF32Rows) {
+      if (groups <= (ND <= 6 ? 2 : 1) * ncu) return attn_fwd_f32_nw<ND, 8, 8>(qkv, ctx, lse, s, b, heads, dh, mask, causal, stream);
+      return attn_fwd_f32_nw<ND, 4, 8>(qkv, ctx, lse, s, b, heads, dh, mask, causal, stream);
+    }
   }
-  attn_fwd_f32_nw<ND, 4>(qkv, ctx, lse, s, b, heads, dh, mask, causal, stream);
+  attn_fwd_f32_nw<ND, 4, 4>(qkv, ctx, lse, s, b, heads, dh, mask, causal, stream);
 }
 
 // Without the causal mask every row is a full row: count the whole s x s square as executed too.
@@ -1503,27 +1601,28 @@ static F32Bwd f32_bwd_form(int dh, int causal, int s, long long groups) {
   if (s >= 256 && groups <= 2 * ncu) return {false, 8};
   return {groups <= (dh <= 32 && causal ? 2 * ncu : ncu), 4};
 }
-template <int ND, int NW>
+template <int ND, int NW, int PARTS>
 static void attn_bwd_f32_nw(bool together, const float* qkv, const float* ctx, const float* lse, const float* dctx, float* dqkv, float* delta,
                             int s, int b, int heads, int dh, const uint8_t* mask, int causal, hipStream_t stream) {
   const dim3 grid((s + kF32Rows - 1) / kF32Rows, heads, b), block(64 * NW);
   if constexpr (ND <= 10) {
     if (together) {
-      hipLaunchKernelGGL((attn_bwd_f32<ND, NW>), dim3(2 * grid.x, heads, b), block, 0, stream, qkv, ctx, dctx, lse, dqkv, s, b, heads, dh, mask, causal);
+      hipLaunchKernelGGL((attn_bwd_f32<ND, NW, PARTS>), dim3(2 * grid.x, heads, b), block, 0, stream, qkv, ctx, dctx, lse, dqkv, s, b, heads, dh, mask, causal);
       return;
     }
   }
-  hipLaunchKernelGGL((attn_bwd_dq_f32<ND, NW>), grid, block, 0, stream, qkv, ctx, dctx, lse, delta, dqkv, s, b, heads, dh, mask, causal);
-  hipLaunchKernelGGL((attn_bwd_dkv_f32<ND, NW>), grid, block, 0, stream, qkv, dctx, lse, (const float*)delta, dqkv, s, b, heads, dh, mask, causal);
+  hipLaunchKernelGGL((attn_bwd_dq_f32<ND, NW, PARTS>), grid, block, 0, stream, qkv, ctx, dctx, lse, delta, dqkv, s, b, heads, dh, mask, causal);
+  hipLaunchKernelGGL((attn_bwd_dkv_f32<ND, NW, PARTS>), grid, block, 0, stream, qkv, dctx, lse, (const float*)delta, dqkv, s, b, heads, dh, mask, causal);
 }
 template <int ND>
 static void attn_bwd_f32_t(const float* qkv, const float* ctx, const float* lse, const float* dctx, float* dqkv, float* delta, int s,
                            int b, int heads, int dh, const uint8_t* mask, int causal, hipStream_t stream) {
   const F32Bwd f = f32_bwd_form(dh, causal, s, (long long)((s + kF32Rows - 1) / kF32Rows) * heads * b);
   if constexpr (ND <= 6) {
-    if (f.waves == 8) return attn_bwd_f32_nw<ND, 8>(f.together, qkv, ctx, lse, dctx, dqkv, delta, s, b, heads, dh, mask, causal, stream);
+    if (f.waves == 8) return attn_bwd_f32_nw<ND, 8, 8>(f.together, qkv, ctx, lse, dctx, dqkv, delta, s, b, heads, dh, mask, causal, stream);
+    if (s > 4 * kF32Rows) return attn_bwd_f32_nw<ND, 4, 8>(f.together, qkv, ctx, lse, dctx, dqkv, delta, s, b, heads, dh, mask, causal, stream);
   }
-  attn_bwd_f32_nw<ND, 4>(f.together, qkv, ctx, lse, dctx, dqkv, delta, s, b, heads, dh, mask, causal, stream);
+  attn_bwd_f32_nw<ND, 4, 4>(f.together, qkv, ctx, lse, dctx, dqkv, delta, s, b, heads, dh, mask, causal, stream);
 }
 
 template <int DH, bool CAUSAL, int QW, int NP, int KT, bool WIDE = false>

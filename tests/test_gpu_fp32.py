@@ -95,6 +95,23 @@ def test_attention_fp32_backward_in_one_and_in_two_launches(s, heads, dh, many, 
         assert torch.equal(alone, all_of_them[:, j:j + 1]), j
 
 
+# s > 64: eight partial sums per row, by eight waves in workgroups of few, by four that make two each in those of many; heads beyond 96
+# (backward) and 128 (forward) have four sums either way
+@pytest.mark.parametrize("causal", [True, False])
+@pytest.mark.parametrize("s,heads,dh,many", [(65, 2, 24, 60), (81, 4, 64, 40), (128, 3, 96, 30), (130, 2, 40, 33), (257, 1, 64, 35), (300, 2, 32, 20),
+                                             (97, 2, 128, 24), (70, 1, 160, 60), (67, 1, 200, 60)])
+def test_attention_fp32_sample_alone_and_among_many(s, heads, dh, many, causal):
+    """A sample's output, lse and gradients have the same bits alone and among `many`."""
+    hp = heads * dh
+    qkv, dctx = randn((s, many, 3 * hp), B.F32, 1), randn((s, many, hp), B.F32, 2)
+    mask = None if causal else torch.from_numpy((np.random.default_rng(3).random((many, s, s)) < 0.3).astype(np.uint8)).cuda()
+    ctx, lse, grads = forward_backward(qkv, dctx, s, many, heads, dh, mask)
+    for j in (0, many // 2, many - 1):
+        one = mask[j:j + 1].clone() if mask is not None else None
+        c, l, g = forward_backward(qkv[:, j:j + 1].contiguous(), dctx[:, j:j + 1].contiguous(), s, 1, heads, dh, one)
+        assert torch.equal(c, ctx[:, j:j + 1]) and torch.equal(l, lse[j:j + 1]) and torch.equal(g, grads[:, j:j + 1]), j
+
+
 # weight gradients in tiles of 16, of 32, of both sizes, of 32 with eight waves each, of 32 and 64
 @pytest.mark.parametrize("h,a,t,s,b", [(96, 3, 1, 300, 1), (64, 2, 1, 37, 3), (256, 8, 8, 300, 1), (256, 4, 1, 128, 2), (512, 8, 1, 65, 1)])
 def test_weight_gradients_fp32_together_and_one_by_one(h, a, t, s, b):
