@@ -441,12 +441,16 @@ int ptdp_attn_masked_bwd(int dtype, const void* qkv, const uint8_t* mask, const 
 int ptdp_attn_bwd(int dtype, const void* qkv, const void* ctx, const float* lse, const void* dctx, void* dqkv,
                   float* delta, int s, int b, int heads, int dh, void* stream);
 
-/* Host only: the form of the kernels that a bf16 attention call takes (causal = 0: masked tells whether there is a mask).  A workgroup owns *rows queries (dK and dV: keys); with
- * *groups = 2 two groups of its waves take alternate tiles of *tile rows of the other side, and their results are joined.
+/* Host only: the form of the kernels that a bf16 attention call takes (causal = 0: masked tells whether there is a mask).  A workgroup
+ * owns *rows queries (dK and dV: keys); *groups (1, 2 or 4) groups of its waves take the tiles of *tile rows of the other side in
+ * turn, and their results are joined.
  * *wide = 1: tiles are read with 64-bit addresses, which row pitches b * 3 * heads * dh from about 143 million on need.
  * Returns 0, PTDP_E_INVALID_ARG, PTDP_E_UNSUPPORTED or PTDP_E_NULL_PTR. */
 enum { PTDP_ATTN_KERNEL_FWD = 0, PTDP_ATTN_KERNEL_DQ = 1, PTDP_ATTN_KERNEL_DKV = 2 };
 int ptdp_attn_form(int kernel, int causal, int masked, int s, int b, int heads, int dh, int* rows, int* groups, int* tile, int* wide);
+/* Host only, the backward pass of the same call.  *together = 1: dQ and dK/dV run in one launch, behind one that computes delta; 0:
+ * dQ, which computes delta, and then dK/dV.  *split = 1: dK and dV are computed by waves of their own.  Returns as ptdp_attn_form. */
+int ptdp_attn_bwd_launch(int causal, int masked, int s, int b, int heads, int dh, int* together, int* split);
 
 /* ---------------------------------------------------------------- ceilings */
 /* What the chip is seen to do, for reading roofline fractions: a loop of

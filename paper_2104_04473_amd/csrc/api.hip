@@ -900,6 +900,14 @@ int ptdp_attn_form(int kernel, int causal, int masked, int s, int b, int heads, 
   return PTDP_OK;
 }
 
+int ptdp_attn_bwd_launch(int causal, int masked, int s, int b, int heads, int dh, int* together, int* split) {
+  if (!together || !split) return PTDP_E_NULL_PTR;
+  if (s <= 0 || b <= 0 || heads <= 0 || dh <= 0 || dh % 8) return PTDP_E_INVALID_ARG;
+  if (!attn_dh_supported(PTDP_BF16, dh)) return PTDP_E_UNSUPPORTED;
+  attn_bwd_launch_query(causal, masked, s, b, heads, dh, together, split);
+  return PTDP_OK;
+}
+
 int ptdp_attn_fwd(int dtype, const void* qkv, void* ctx, float* lse, int s, int b, int heads, int dh, void* stream) {
   PTDP_TRY(check_dtype(dtype));
   if (s < 0 || b < 0 || heads < 0 || dh <= 0 || dh % 8 != 0) return PTDP_E_INVALID_ARG;

@@ -962,7 +962,7 @@ __device__ __forceinline__ float attn_delta_of(const bf16_t* __restrict__ row, c
 }
 
 // dQ of 32 QW queries, as the forward kernel walks them: K and V stream through two LDS stages of KT keys (K is read twice,
-// as rows for S and transposed for dQ).  NP = 2: two groups take alternate tiles and their sums are added at the end.  A wave
+// as rows for S and transposed for dQ).  NP groups (1, 2 or 4) take tiles in turn and their sums are added at the end.  A wave
 // holds Q, dO and dQ and fits two to a SIMD (tiles on their way through registers had left one), so that one's
 // exponentials run under the other's products.  Error against 64 bits unchanged.
 // us before and now, causal, s = 2048 unless given: 4 x 16 heads of 128 216 -> 106; 12 heads of 128 61 -> 38; 8 heads 48 -> 34, at
@@ -1765,6 +1765,11 @@ void attn_form_query(int kernel, int causal, int masked, int s, int b, int heads
   *groups = f.groups;
   *tile = f.tile;
   *wide = f.wide;
+}
+void attn_bwd_launch_query(int causal, int masked, int s, int b, int heads, int dh, int* together, int* split) {
+  const AttnPair p = attn_pair_form(dh, causal != 0, !causal && masked, s, b, heads);
+  *together = p.k_tile > 0;
+  *split = p.k_tile > 0 ? p.split : attn_dkv_form(dh, causal != 0, s, b, heads).split;
 }
 template <int DH, bool CAUSAL, int NPK, int QT, bool SPLIT>
 static int attn_bwd_pair(const bf16_t* qkv, const bf16_t* ctx, const float* lse, const bf16_t* dctx, bf16_t* dqkv, float* delta, int s, int b,

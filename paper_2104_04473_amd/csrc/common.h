@@ -234,6 +234,7 @@ int launch_attn_bwd(int dtype, const void* qkv, const void* ctx, const float* ls
                     hipStream_t st);
 bool attn_dh_supported(int dtype, int dh);
 // the form that a bf16 call of one of the attention kernels takes (host only)
+void attn_bwd_launch_query(int causal, int masked, int s, int b, int heads, int dh, int* together, int* split);
 void attn_form_query(int kernel, int causal, int masked, int s, int b, int heads, int dh, int* rows, int* groups, int* tile, int* wide);
 // first / last stage extras (lm_stage.hip)
 int launch_embed_fwd(int dtype, const int32_t* tokens, const void* e_word, const void* e_pos, void* x, int s, int b,

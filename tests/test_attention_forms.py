@@ -17,7 +17,12 @@ KERNELS = ("forward", "dQ", "dK/dV")
 
 def form(kernel, kind, s, b, heads, dh):
     v = [C.c_int() for _ in range(4)]
-    B.check(B.ptdp_attn_form(kernel, int(kind == "causal"), int(kind.startswith("mask")), s, b, heads, dh, *[C.byref(x) for x in v]), "form")
+    call = (int(kind == "causal"), int(kind.startswith("mask")), s, b, heads, dh)
+    B.check(B.ptdp_attn_form(kernel, *call, *[C.byref(x) for x in v]), "form")
+    if kernel > 0:   # backward: also whether dQ and dK/dV share a launch, and whether dK and dV have waves of their own
+        launch = [C.c_int(), C.c_int()]
+        B.check(B.ptdp_attn_bwd_launch(*call, *[C.byref(x) for x in launch]), "launch")
+        v += launch
     return tuple(x.value for x in v)
 
 
@@ -49,7 +54,7 @@ def test_every_form_is_run(kind, dh):
             for kernel in range(3):
                 want.setdefault((kernel, kind, dh, form(kernel, kind, s, 1, p, dh)), (s, p))
     missing = sorted((KERNELS[k[0]], k[3], example) for k, example in want.items() if k not in have)
-    assert not missing, "no GPU test runs (kernel, (rows, groups, tile, wide), an example of s and heads): %s" % missing
+    assert not missing, "no GPU test runs (kernel, (rows, groups, tile, wide (, together, split)), an example of s and heads): %s" % missing
 
 
 @pytest.mark.parametrize("dh", [32, 64, 96, 128])

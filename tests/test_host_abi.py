@@ -256,6 +256,19 @@ def test_attn_form_errors():
     assert [x.value for x in v] == [-1] * 4
 
 
+def test_attn_bwd_launch():
+    together, split = C.c_int(-1), C.c_int(-1)
+    ref = [C.byref(together), C.byref(split)]
+    for args in ((1, 0, 0, 1, 1, 64), (1, 0, 8, 0, 1, 64), (1, 0, 8, 1, 0, 64), (1, 0, 8, 1, 1, 36)):
+        assert B.ptdp_attn_bwd_launch(*args, *ref) == B.E_INVALID_ARG
+    assert B.ptdp_attn_bwd_launch(1, 0, 8, 1, 1, 40, *ref) == B.E_UNSUPPORTED
+    assert B.ptdp_attn_bwd_launch(1, 0, 8, 1, 1, 64, ref[0], None) == B.E_NULL_PTR
+    assert (together.value, split.value) == (-1, -1)
+    # few workgroups side by side, many one after the other; heads of 160 always with waves of their own
+    for args, want in (((1, 0, 333, 2, 8, 64), (1, 0)), ((1, 0, 2048, 4, 16, 128), (0, 0)), ((1, 0, 2048, 1, 8, 128), (1, 1)), ((0, 0, 2048, 1, 40, 160), (0, 1))):
+        assert B.ptdp_attn_bwd_launch(*args, *ref) == B.OK and (together.value, split.value) == want, args
+
+
 @pytest.mark.parametrize("heads,dh", [(16, 32), (1, 64), (13, 96), (16, 128), (7, 160)])
 def test_attention_rows_beyond_32_bit_offsets(heads, dh):
     """A slice of 16 rows is read with 32-bit byte offsets from its first row only where every one of them fits."""
