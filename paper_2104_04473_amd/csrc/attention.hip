@@ -1733,6 +1733,7 @@ static int attn_bwd_dkv_t(const bf16_t* qkv, const bf16_t* dctx, const float* ls
 //   1.12, (1, 32, split) 200 .75 .95 .82 1.07 / .72 .91 .85 1.01, 512 .81 .88 .89 1.01 / .80 1.01 .89 1.10, 2048 .88 .94 .94 .97 / .90 1.09 1.06 1.21, (2, 32) 1024 .81 .86 .85
 //   .91, 2048 .80 .86 .85 .84;   160 (2, 32, split) 512 .72 .97 1.08 / .73 1.16, 2048 .62 .76 1.03 / .67 1.19, (1, 32, split) 200 .74 .93 .80 .86 / .73 .89 .81 .89,
 //   512 .76 .84 .90 .93 / .79 .96 .89 .98, 2048 .79 .87 .92 1.02 / .84 1.07 1.04 1.11.  Heads of 64 x 512, general mask: as without.
+// Registers: (2, 32) of 128, causal, takes all 256 and spills three (16 bytes a lane), as dK/dV does in a launch of its own; no other spills.
 struct AttnPair {
   int k_groups, k_tile;
   bool split;

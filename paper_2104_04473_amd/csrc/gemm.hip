@@ -1058,7 +1058,7 @@ __device__ __forceinline__ void gemm_small_tile(const GemmArgs& g, void* Cv, int
 // Bound by MFMA issue on few compute units (0.53 us per k-tile, operands in the caches), by the clock that power allows and
 // the way from L2 to LDS with all of them (0.73, operands from memory 0.80), against 0.83 and 1.0 for two 128 x 128 tiles.
 // us, operands from memory, before (128 x 128 tiles; the last split along k) and now: 2048 x 4096 x 4096 NN 69.4 -> 59.0, NT 67.4 -> 58.4;
-// 2048 x 3072 x 4096 67.7 -> 57.9; 1008 x 5120 x 2560 42.8 -> 36.8; 1008 x 7680 x 5120 78.4 -> 72.8.
+// 2048 x 3072 x 4096 67.7 -> 57.9; 1008 x 7680 x 5120 78.4 -> 72.8.
 // ------------------------------------------------------------------------------------------------
 constexpr int kWideM = 256, kWideN = 128, kWideLag = 3;
 constexpr int kWideStage = (kWideM + kWideN) * BK * 2, kWideSmem = 3 * kWideStage;
