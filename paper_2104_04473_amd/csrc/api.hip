@@ -390,7 +390,7 @@ int ptdp_layer_backward(ptdp_chunk* ch, int layer, int64_t microbatch, const voi
     csr[i] = cs0;
     cs0 += colsum_region_bytes(d, i);
   }
-  ColsumBatch sums;   // the six second stages run as one launch at the end
+  ColsumBatch sums;   // the six second stages run together at the end
   void* sk = wf(WS_SPLITK);
   const size_t skb = ws_field_bytes(ch->wl, WS_SPLITK);
 
@@ -412,13 +412,6 @@ int ptdp_layer_backward(ptdp_chunk* ch, int layer, int64_t microbatch, const voi
   const bool late = layernorm_bwd_takes_sums(dt, T, h, 3 * hp);   // b_qkv's sums in the launch of the first LayerNorm's backward
   if (!late) PTDP_TRY(launch_colsum(dt, wf(WS_QKV), G.b_qkv, csr[4], T, 3 * hp, st, &sums));
   PTDP_TRY(launch_gemm(dt, PTDP_GEMM_NT, wf(WS_QKV), P.w_qkv, wf(WS_H2), nullptr, T, h, 3 * hp, 0, 0, sk, skb, st));
-  {
-    const void* A[4] = {sf(PTDP_STASH_G), sf(PTDP_STASH_U2), sf(PTDP_STASH_U), sf(PTDP_STASH_CTX)};
-    const void* B[4] = {wf(WS_DMO), wf(WS_BIG), wf(WS_QKV), wf(WS_H1)};
-    float* C[4] = {G.w_2, G.w_1, G.w_qkv, G.w_o};
-    const int M[4] = {fp, h, h, hp}, N[4] = {h, fp, 3 * hp, h};
-    PTDP_TRY(launch_gemm_tn_multi(dt, 4, A, B, C, M, N, T, st));
-  }
   const float* mu1 = (const float*)sf(PTDP_STASH_MU1);
   const float* rstd1 = (const float*)sf(PTDP_STASH_RSTD1);
   if (late)
@@ -427,8 +420,11 @@ int ptdp_layer_backward(ptdp_chunk* ch, int layer, int64_t microbatch, const voi
   else
     PTDP_TRY(launch_layernorm_bwd(dt, wf(WS_H2), sf(PTDP_STASH_X), P.ln1_g, mu1, rstd1, wf(WS_X1), dx, G.ln1_g, G.ln1_b, csr[5],
                                   T, h, st, &sums));
-  PTDP_TRY(launch_colsum_batch(sums, st));
-  return PTDP_OK;
+  const void* A[4] = {sf(PTDP_STASH_G), sf(PTDP_STASH_U2), sf(PTDP_STASH_U), sf(PTDP_STASH_CTX)};
+  const void* B[4] = {wf(WS_DMO), wf(WS_BIG), wf(WS_QKV), wf(WS_H1)};
+  float* C[4] = {G.w_2, G.w_1, G.w_qkv, G.w_o};
+  const int M[4] = {fp, h, h, hp}, N[4] = {h, fp, 3 * hp, h};
+  return launch_gemm_tn_multi(dt, 4, A, B, C, M, N, T, &sums, st);
 }
 
 int ptdp_chunk_forward(ptdp_chunk* ch, int64_t microbatch, const void* x, void* y, void* stash, void* workspace,

@@ -223,9 +223,10 @@ void gemm_form_query(int mode, int M, int N, int K, int out_f32, int accumulate,
                      int* tile_n, int* groups);
 int launch_gemm(int dtype, int mode, const void* A, const void* B, void* C, const void* bias, int M, int N,
                 int K, int out_f32, int accumulate, void* ws, size_t ws_bytes, hipStream_t st);
-// up to four fp32-accumulating weight gradients C_j += A_j^T B_j with the same K (bf16: one launch)
+// up to four fp32-accumulating weight gradients C_j += A_j^T B_j with the same K (bf16: one launch); sums: column sums to finish with
+// them (may be null)
 int launch_gemm_tn_multi(int dtype, int n, const void* const* A, const void* const* B, float* const* C, const int* M,
-                         const int* N, int K, hipStream_t st);
+                         const int* N, int K, const ColsumBatch* sums, hipStream_t st);
 // mask: [b, s, s] bytes (nonzero = hidden) or null, used when causal == 0
 int launch_attn_fwd(int dtype, const void* qkv, void* ctx, float* lse, int s, int b, int heads, int dh,
                     const uint8_t* mask, int causal, hipStream_t st);

@@ -2,7 +2,7 @@
 // names the two fusions; LayerNorm is implied by the 13h term of eq. (2)) and their backward passes.
 // All of them move 16 bytes per lane per access, keep fp32 arithmetic, and reduce with wavefront
 // shuffles; column sums (bias / LayerNorm parameter gradients) are two-stage and deterministic.
-#include "common.h"
+#include "colsum.h"
 
 namespace ptdp {
 
@@ -568,89 +568,17 @@ layernorm_bwd_wide_kernel(const T* du, const T* __restrict__ x, const T* __restr
   }
 }
 
-// out[c] += sum over parts of part[p][c]  (second stage of every column sum; fixed order).
-// A workgroup owns 64 columns; each of its sixteen waves adds a sixteenth of the parts with eight loads of either sum in
-// flight, and the first wave adds the sixteen sums in order.  Bound by the latency of that chain of loads for narrow
-// layers (with four waves of four loads, 256 parts took 22 us at any width; now 5) and by reading the partial sums
-// for wide ones (h 25600: 44 -> 36 us).
-// The parts left over behind whole groups of loads are requested together as well, at places that exist, and what is too much is
-// not added: a branch for each made them a chain of up to seven trips to memory (two layers of 512, 666 tokens 262.2 -> 260.0 us, with the
-// rows' early requests in layernorm_bwd_sums_kernel; two groups of eight in flight: 260.3, fp32 layer 256 wide 103.0 -> 103.5).
-constexpr int kFinishWaves = 16, kFinishLoads = 8;
-// the next kFinishLoads (WHOLE) or n > 0 parts; p is the same for the whole wave, c the lane's column
-template <bool TWO, bool WHOLE>
-__device__ __forceinline__ void colsum_finish_step(const float* __restrict__ p, int c, int n, int stride, int width, float (&sa)[kFinishLoads],
-                                                   float (&sb)[kFinishLoads]) {
-  float va[kFinishLoads], vb[kFinishLoads];
-#pragma unroll
-  for (int u = 0; u < kFinishLoads; ++u) {
-    const float* row = p + (size_t)(WHOLE ? u : min(u, n - 1)) * stride;
-    va[u] = row[c];
-    vb[u] = TWO ? row[width + c] : 0.f;
-  }
-#pragma unroll
-  for (int u = 0; u < kFinishLoads; ++u) {
-    sa[u] += WHOLE || u < n ? va[u] : 0.f;
-    sb[u] += WHOLE || u < n ? vb[u] : 0.f;
-  }
-}
-template <bool TWO>
-__device__ __forceinline__ void colsum_finish_part(const float* __restrict__ p, int c, int n, int stride, int width, float& a, float& b) {
-  float sa[kFinishLoads], sb[kFinishLoads];
-#pragma unroll
-  for (int u = 0; u < kFinishLoads; ++u) sa[u] = sb[u] = 0.f;
-  for (; n >= kFinishLoads; n -= kFinishLoads, p += (size_t)kFinishLoads * stride) colsum_finish_step<TWO, true>(p, c, n, stride, width, sa, sb);
-  if (n > 0) colsum_finish_step<TWO, false>(p, c, n, stride, width, sa, sb);
-  a = ((sa[0] + sa[1]) + (sa[2] + sa[3])) + ((sa[4] + sa[5]) + (sa[6] + sa[7]));
-  b = ((sb[0] + sb[1]) + (sb[2] + sb[3])) + ((sb[4] + sb[5]) + (sb[6] + sb[7]));
-}
-__device__ __forceinline__ void colsum_finish_block(const float* __restrict__ part, int nparts, int stride, float* out0, float* out1,
-                                                    int width, int blk) {
-  __shared__ float red[2][kFinishWaves][64];
-  const int lane = threadIdx.x & 63, q = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int c = blk * 64 + lane;
-  const int per = (nparts + kFinishWaves - 1) / kFinishWaves, p0 = q * per, n = min(nparts, p0 + per) - p0;
-  float a = 0.f, b = 0.f;
-  if (c < width && n > 0) {
-    if (out1) colsum_finish_part<true>(part + (size_t)p0 * stride, c, n, stride, width, a, b);
-    else colsum_finish_part<false>(part + (size_t)p0 * stride, c, n, stride, width, a, b);
-  }
-  red[0][q][lane] = a;
-  red[1][q][lane] = b;
-  __syncthreads();
-  // wave 0 finishes the first sum, wave 1 the second
-  float* out = q == 0 ? out0 : out1;
-  if (q < 2 && out && c < width) {
-    float t = 0.f;
-#pragma unroll
-    for (int w = 0; w < kFinishWaves; ++w) t += red[q][w][lane];
-    out[c] += t;
-  }
-}
-
 __global__ void __launch_bounds__(64 * kFinishWaves)
 colsum_finish_kernel(const float* __restrict__ part, int nparts, int stride, float* out0, float* out1, int width) {
-  colsum_finish_block(part, nparts, stride, out0, out1, width, (int)blockIdx.x);
+  __shared__ float red[kFinishRed];
+  colsum_finish_block(ColsumJob{part, nparts, stride, width, out0, out1}, (int)blockIdx.x, kFinishWaves, red);
 }
 
-// several finishes in one launch: job j owns workgroups first[j] .. first[j+1]-1; same arithmetic as above
-struct ColsumBatchArgs {
-  ColsumJob job[kMaxColsumJobs];
-  int first[kMaxColsumJobs + 1];
-  int n;
-};
+// several finishes in one launch
 __global__ void __launch_bounds__(64 * kFinishWaves)
 colsum_finish_batch_kernel(ColsumBatchArgs a) {
-  const int id = (int)blockIdx.x;
-  ColsumJob j = a.job[0];   // constant indices only: the arguments stay in scalar registers
-  int first = 0;
-#pragma unroll
-  for (int q = 1; q < kMaxColsumJobs; ++q)
-    if (q < a.n && id >= a.first[q]) {
-      j = a.job[q];
-      first = a.first[q];
-    }
-  colsum_finish_block(j.part, j.nparts, j.stride, j.out0, j.out1, j.width, id - first);
+  __shared__ float red[kFinishRed];
+  colsum_finish_id(a, (int)blockIdx.x, kFinishWaves, red);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -926,21 +854,10 @@ static int colsum_finish(const float* part, int nparts, int stride, float* out0,
 
 int launch_colsum_batch(const ColsumBatch& batch, hipStream_t st) {
   if (batch.n == 0) return PTDP_OK;
-  ColsumBatchArgs a;
-  a.n = batch.n;
   double bytes = 0.0;
-  int at = 0;
-  for (int j = 0; j < kMaxColsumJobs; ++j) {
-    a.job[j] = batch.job[j < batch.n ? j : 0];   // unused slots repeat job 0 (never selected)
-    a.first[j] = at;
-    if (j < batch.n) {
-      at += (batch.job[j].width + 63) / 64;
-      bytes += (double)batch.job[j].nparts * batch.job[j].stride * sizeof(float);
-    }
-  }
-  a.first[kMaxColsumJobs] = at;
+  const ColsumBatchArgs a = colsum_batch_args(batch, &bytes);
   Launch L(PTDP_K_COLSUM, bytes, st);
-  hipLaunchKernelGGL(colsum_finish_batch_kernel, dim3(at), dim3(64 * kFinishWaves), 0, st, a);
+  hipLaunchKernelGGL(colsum_finish_batch_kernel, dim3(a.first[kMaxColsumJobs]), dim3(64 * kFinishWaves), 0, st, a);
   return L.status();
 }
 

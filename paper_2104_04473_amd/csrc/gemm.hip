@@ -10,7 +10,7 @@
 // reduction index is the slow memory index (B in NN, both in TN) stays in its memory order in LDS and is gathered
 // into MFMA fragments by transposing LDS reads.
 // fp32 path: v_mfma_f32_32x32x2_f32, operands straight from memory (small configurations).
-#include "common.h"
+#include "colsum.h"
 #include <type_traits>
 
 namespace ptdp {
@@ -225,12 +225,17 @@ struct MultiF32 {
   float* C[kMaxMultiF32];
   int M[kMaxMultiF32], N[kMaxMultiF32], kg[kMaxMultiF32], start[kMaxMultiF32], n, K;   // start: first workgroup
 };
+// sums: column sums that the launch's first n_sums workgroups finish, see gemm_bf16_small_multi_kernel.
 template <bool TINY>
 __global__ void __launch_bounds__(64 * f32_most_waves(1))
-gemm_f32_multi_kernel(MultiF32 a) {
+gemm_f32_multi_kernel(MultiF32 a, ColsumBatchArgs sums, int n_sums) {
   constexpr int kTile = TINY ? 16 : 32;
   extern __shared__ __attribute__((aligned(16))) float part[];
-  const int id = (int)blockIdx.x;
+  const int id = (int)blockIdx.x - n_sums;
+  if (id < 0) {
+    colsum_finish_id(sums, id + n_sums, blockDim.x >> 6, part);
+    return;
+  }
   // constant indices only: the arguments stay in scalar registers
   const float *A = a.A[0], *B = a.B[0];
   float* C = a.C[0];
@@ -297,19 +302,22 @@ static int launch_gemm_f32(const float* A, const float* B, float* C, const float
   return launch_gemm_f32_t<VA, VB, 1>(A, B, C, bias, M, N, K, a_rs, a_cs, b_rs, b_cs, accumulate, f.kg, st);
 }
 
-template <bool TINY> static int launch_f32_multi(const MultiF32& a, int blocks, hipStream_t st) {
+template <bool TINY> static int launch_f32_multi(const MultiF32& a, int blocks, const ColsumBatchArgs& sums, hipStream_t st) {
   constexpr int kPart = (TINY ? 16 * 17 : 32 * 40) * (int)sizeof(float);   // a wave's partial tile
+  constexpr int kRed = kFinishRed * (int)sizeof(float);
   static once_flag_t done[kMaxDevices];
   if (set_dynamic_smem(reinterpret_cast<const void*>(gemm_f32_multi_kernel<TINY>), f32_most_waves(1) * kPart, done) != PTDP_OK) return PTDP_E_HIP;
   int kg = 1;
   for (int j = 0; j < a.n; ++j) kg = a.kg[j] > kg ? a.kg[j] : kg;
-  hipLaunchKernelGGL(gemm_f32_multi_kernel<TINY>, dim3(blocks), dim3(64 * kg), kg * kPart, st, a);
+  const int n_sums = sums.first[kMaxColsumJobs], smem = n_sums > 0 && kg * kPart < kRed ? kRed : kg * kPart;
+  static_assert(kRed <= f32_most_waves(1) * kPart, "within the limit set above");
+  hipLaunchKernelGGL(gemm_f32_multi_kernel<TINY>, dim3(n_sums + blocks), dim3(64 * kg), smem, st, a, sums, n_sums);
   return PTDP_OK;
 }
 // Weight gradients of a layer: those of 16 x 16 tiles and those of 32 x 32 tiles as one launch each, 64 x 64 tiles (which fill the
-// chip) one by one.
+// chip) one by one.  *sums: finished in the last of the shared launches (and then empty), if there is one.
 static int launch_f32_tn_multi(int n, const void* const* A, const void* const* B, float* const* C, const int* M, const int* N, int K,
-                               hipStream_t st) {
+                               ColsumBatch* sums, hipStream_t st) {
   MultiF32 m[2];
   long long blocks[2] = {0, 0};
   for (int x = 0; x < 2; ++x) {
@@ -341,8 +349,12 @@ static int launch_f32_tn_multi(int n, const void* const* A, const void* const* B
       m[x].A[q] = m[x].A[0]; m[x].B[q] = m[x].B[0]; m[x].C[q] = m[x].C[0];
       m[x].M[q] = m[x].M[0]; m[x].N[q] = m[x].N[0]; m[x].kg[q] = m[x].kg[0]; m[x].start[q] = 0;
     }
-    const int rc = x == 0 ? launch_f32_multi<true>(m[x], (int)blocks[x], st) : launch_f32_multi<false>(m[x], (int)blocks[x], st);
+    ColsumBatch none, *take = x == 0 && m[1].n > 0 ? &none : sums;
+    double bytes = 0.0;
+    const ColsumBatchArgs finish = colsum_batch_args(*take, &bytes);
+    const int rc = x == 0 ? launch_f32_multi<true>(m[x], (int)blocks[x], finish, st) : launch_f32_multi<false>(m[x], (int)blocks[x], finish, st);
     if (rc != PTDP_OK) return rc;
+    take->n = 0;
   }
   return PTDP_OK;
 }
@@ -1286,11 +1298,19 @@ gemm_bf16_dp_multi_kernel(MultiArgs a) {
   gemm_dp_tile<TA, TB, OUT>(g, C, id - first, smem);
 }
 
+// The small tiles' form of it.  Its first n_sums workgroups (a multiple of 8) finish the column sums of the layer's backward: as a launch
+// of its own that is 5 us of a few dependent loads, here it runs beside the tiles (us per pass, same bits: one fp32 layer of 256 x 256 102.1
+// -> 97.5, two of 666 x 512 258.8 -> 250.6, of 2048 x 1024 697 -> 687, eight of 1024 x 2048 over two shards 2858 -> 2826).  With 256 x 256
+// tiles the sums are many and the launch long: they stay a launch of their own.
 template <bool TA, bool TB, int OUT, int BM, int BN, int S, int KG>
 __global__ void __launch_bounds__(KG * kSmallThreads, 2)
-gemm_bf16_small_multi_kernel(MultiArgs a) {
+gemm_bf16_small_multi_kernel(MultiArgs a, ColsumBatchArgs sums, int n_sums) {
   extern __shared__ __attribute__((aligned(1024))) char smem[];
-  const int id = (int)blockIdx.x;
+  const int id = (int)blockIdx.x - n_sums;
+  if (id < 0) {
+    if ((int)blockIdx.x < sums.first[kMaxColsumJobs]) colsum_finish_id(sums, blockIdx.x, KG * kSmallThreads / 64, reinterpret_cast<float*>(smem));
+    return;
+  }
   GemmArgs g = a.g[0];
   void* C = a.C[0];
   int first = a.start[0];
@@ -1450,7 +1470,7 @@ static int launch_small_form(int form, const GemmArgs& g, void* C, hipStream_t s
 }
 // several problems, see gemm_bf16_dp_multi_kernel; a.start is filled here
 template <int OUT, int BM, int BN, int S, int KG>
-static int launch_small_multi(MultiArgs& a, hipStream_t st) {
+static int launch_small_multi(MultiArgs& a, const ColsumBatchArgs& sums, hipStream_t st) {
   auto kern = gemm_bf16_small_multi_kernel<true, true, OUT, BM, BN, S, KG>;
   static once_flag_t done[kMaxDevices];
   constexpr int smem = SmallGeom<BM, BN, S, KG>::kSmem;
@@ -1461,7 +1481,9 @@ static int launch_small_multi(MultiArgs& a, hipStream_t st) {
     if (j < a.n) at += small_blocks<BM, BN>(a.g[j].M, a.g[j].N);
   }
   a.start[kMaxMulti] = at;
-  hipLaunchKernelGGL(kern, dim3(at), dim3(KG * kSmallThreads), smem, st, a);
+  static_assert(kFinishRed * (int)sizeof(float) <= smem, "the column sums' LDS");
+  const int n_sums = (sums.first[kMaxColsumJobs] + 7) / 8 * 8;
+  hipLaunchKernelGGL(kern, dim3(n_sums + at), dim3(KG * kSmallThreads), smem, st, a, sums, n_sums);
   return PTDP_OK;
 }
 
@@ -1756,14 +1778,20 @@ static GemmArgs tn_args(const void* A, const void* B, int M, int N, int K) {
   return g;
 }
 
-template <int OUT> static int launch_tn_multi(int form, MultiArgs& a, hipStream_t st) {
-  switch (form) {
-    case 0: return launch_small_multi<OUT, 128, 128, 2, 1>(a, st);
-    case 1: return launch_small_multi<OUT, 128, 128, 2, 2>(a, st);
-    case 2: return launch_small_multi<OUT, 128, 64, 3, 2>(a, st);
-    case 3: return launch_small_multi<OUT, 64, 64, 4, 2>(a, st);
-    case 4: return launch_small_multi<OUT, 128, 64, 2, 1>(a, st);
-    default: break;
+// *sums: finished in this launch where the tiles are small, and then empty
+template <int OUT> static int launch_tn_multi(int form, MultiArgs& a, ColsumBatch* sums, hipStream_t st) {
+  if (form >= 0) {
+    double bytes = 0.0;
+    const ColsumBatchArgs finish = colsum_batch_args(*sums, &bytes);
+    sums->n = 0;
+    switch (form) {
+      case 0: return launch_small_multi<OUT, 128, 128, 2, 1>(a, finish, st);
+      case 1: return launch_small_multi<OUT, 128, 128, 2, 2>(a, finish, st);
+      case 2: return launch_small_multi<OUT, 128, 64, 3, 2>(a, finish, st);
+      case 3: return launch_small_multi<OUT, 64, 64, 4, 2>(a, finish, st);
+      case 4: return launch_small_multi<OUT, 128, 64, 2, 1>(a, finish, st);
+      default: return PTDP_E_STATE;   // += has no other small form
+    }
   }
   auto kern = gemm_bf16_dp_multi_kernel<true, true, OUT>;
   static once_flag_t done[kMaxDevices];
@@ -1772,10 +1800,8 @@ template <int OUT> static int launch_tn_multi(int form, MultiArgs& a, hipStream_
   return PTDP_OK;
 }
 
-// C_j[M_j,N_j] += A_j^T B_j for j < n <= 4 (fp32 C, both operands [K, .]), sharing K: weight gradients whose inputs
-// are all at hand.  In bf16 they run as one launch.
-int launch_gemm_tn_multi(int dtype, int n, const void* const* A, const void* const* B, float* const* C, const int* M,
-                         const int* N, int K, hipStream_t st) {
+static int gemm_tn_multi(int dtype, int n, const void* const* A, const void* const* B, float* const* C, const int* M, const int* N, int K,
+                         ColsumBatch* sums, hipStream_t st) {
   if (n <= 0 || n > kMaxMulti) return PTDP_E_INVALID_ARG;
   bool one_by_one = false;
   double flops = 0.0;
@@ -1792,7 +1818,7 @@ int launch_gemm_tn_multi(int dtype, int n, const void* const* A, const void* con
   }
   Launch L(PTDP_K_GEMM_TN, flops, st);
   if (dtype == PTDP_F32) {
-    const int rc = launch_f32_tn_multi(n, A, B, C, M, N, K, st);
+    const int rc = launch_f32_tn_multi(n, A, B, C, M, N, K, sums, st);
     return rc != PTDP_OK ? rc : L.status();
   }
   MultiArgs a;
@@ -1818,8 +1844,18 @@ int launch_gemm_tn_multi(int dtype, int n, const void* const* A, const void* con
   const int form = small_form(1, n, M, N, K, t_large);
   bool lines = true;
   for (int j = 0; j < n; ++j) lines = lines && whole_lines(N[j]);
-  const int rc = lines ? launch_tn_multi<OUT_F32_RMW_LINES>(form, a, st) : launch_tn_multi<OUT_F32_RMW>(form, a, st);
+  const int rc = lines ? launch_tn_multi<OUT_F32_RMW_LINES>(form, a, sums, st) : launch_tn_multi<OUT_F32_RMW>(form, a, sums, st);
   return rc != PTDP_OK ? rc : L.status();
+}
+// C_j[M_j,N_j] += A_j^T B_j for j < n <= 4 (fp32 C, both operands [K, .]), sharing K: weight gradients whose inputs
+// are all at hand.  In bf16 they run as one launch.  sums (nullable): column sums to finish as well, in that launch where that costs
+// less than one of their own.
+int launch_gemm_tn_multi(int dtype, int n, const void* const* A, const void* const* B, float* const* C, const int* M,
+                         const int* N, int K, const ColsumBatch* sums, hipStream_t st) {
+  ColsumBatch left;   // what is not finished with the products
+  if (sums) left = *sums;
+  const int rc = gemm_tn_multi(dtype, n, A, B, C, M, N, K, &left, st);
+  return rc != PTDP_OK ? rc : launch_colsum_batch(left, st);
 }
 
 int launch_gemm(int dtype, int mode, const void* A, const void* B, void* C, const void* bias, int M, int N, int K,

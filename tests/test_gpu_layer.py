@@ -112,6 +112,34 @@ def test_qkv_bias_sums_beside_layernorm_backward(h, a, t, s, b, dtype):
     assert torch.equal(G["b_qkv"], sums)
 
 
+# workgroups of 2, 4 and 8 waves, fewer parts than waves and more, columns that leave a block's last lanes empty; 256 x 256 tiles (a launch of their own)
+@pytest.mark.parametrize("h,a,t,s,b,dtype", [
+    (64, 2, 1, 1, 1, B.F32), (96, 3, 1, 37, 1, B.F32), (256, 4, 1, 128, 2, B.F32), (512, 8, 1, 301, 7, B.F32),
+    (256, 8, 1, 1, 1, B.BF16), (160, 1, 1, 65, 1, B.BF16), (512, 8, 1, 333, 2, B.BF16), (1024, 16, 2, 301, 7, B.BF16), (2048, 16, 2, 1024, 1, B.BF16),
+    (4096, 32, 1, 512, 2, B.BF16),
+])
+def test_column_sums_beside_weight_gradients(h, a, t, s, b, dtype):
+    """Column sums are finished in the launch of the weight gradients where its tiles are small: the bits of a call of their own."""
+    cfg = B.make_cfg(h=h, a=a, t=t, s=s, b=b, dtype=dtype, p_hidden=0.1, seed=7)
+    rig, T = LayerRig(cfg, first_layer=3), s * b
+    x, dy = randn((s, b, h), dtype, 1), randn((s, b, h), dtype, 2)
+    y, dx, out = torch.empty_like(x), torch.empty_like(x), torch.empty_like(x)
+    for g in rig.grads[0].values():
+        g.fill_(0.25)   # += : the old value counts
+    B.check(rig.chunk.forward(1, x.data_ptr(), y.data_ptr(), rig.stash.data_ptr(), rig.ws.data_ptr()), "forward")
+    B.check(rig.chunk.backward(1, dy.data_ptr(), dx.data_ptr(), rig.stash.data_ptr(), rig.ws.data_ptr()), "backward")
+    scratch = dev_bytes(B.ptdp_colsum_scratch_bytes(T, h))
+    at = {k: rig.ws.data_ptr() + v for k, v in B.workspace_offsets(cfg).items()}
+    for name, site, grad in (("b_2", 1, dy.data_ptr()), ("b_o", 0, at["DX1"])):
+        sums = torch.full((h,), 0.25, device="cuda")
+        B.check(B.ptdp_bias_dropout_add_bwd(dtype, grad, out.data_ptr(), sums.data_ptr(), scratch.data_ptr(), T, h, 0.1, 7, 3, site, 1, stream()), name)
+        sync()
+        if name == "b_2":
+            assert torch.equal(rig.grads[0][name], sums)
+        else:   # its rows are summed in another order, by the workgroups of LayerNorm backward: fp32 sums of T terms each
+            assert_close(np64(rig.grads[0][name]), np64(sums), B.F32, name)
+
+
 def test_chunk_of_layers_and_gradient_accumulation():
     cfg = B.make_cfg(h=256, a=4, t=1, s=40, b=2, dtype=B.F32, p_hidden=0.1, seed=9)
     check_layer(cfg, n_layers=3, first_layer=4, microbatches=(0, 3))
