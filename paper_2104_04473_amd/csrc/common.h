@@ -170,6 +170,8 @@ struct ColsumBatch {
   int n = 0;
 };
 int launch_colsum_batch(const ColsumBatch& batch, hipStream_t st);
+// out0 (out1) += column sums of part[nparts][stride], now or with the batch
+int colsum_finish(const float* part, int nparts, int stride, float* out0, float* out1, int width, hipStream_t st, ColsumBatch* defer = nullptr);
 
 // kernels (defined in the .hip files; all arguments validated by the callers in api.hip)
 int launch_layernorm_fwd(int dtype, const void* x, const void* gain, const void* bias, void* u, float* mu,
@@ -223,10 +225,17 @@ void gemm_form_query(int mode, int M, int N, int K, int out_f32, int accumulate,
                      int* tile_n, int* groups);
 int launch_gemm(int dtype, int mode, const void* A, const void* B, void* C, const void* bias, int M, int N,
                 int K, int out_f32, int accumulate, void* ws, size_t ws_bytes, hipStream_t st);
+// the products next to the MLP's GeLU, with it: z = u w, g = GeLU(z + b);  dz = (dg w^T) * GeLU'(z + b), dbias += its column sums
+int launch_gemm_gelu(int dtype, int gelu_mode, const void* u, const void* w, const void* b, void* z, void* g, int M, int N, int K, void* ws,
+                     size_t ws_bytes, hipStream_t st);
+int launch_gemm_gelu_bwd(int dtype, int gelu_mode, const void* dg, const void* w, const void* z, const void* b, void* dz, float* dbias,
+                         void* scratch, int M, int N, int K, void* ws, size_t ws_bytes, hipStream_t st, ColsumBatch* defer);
 // up to four fp32-accumulating weight gradients C_j += A_j^T B_j with the same K (bf16: one launch); sums: column sums to finish with
 // them (may be null)
 int launch_gemm_tn_multi(int dtype, int n, const void* const* A, const void* const* B, float* const* C, const int* M,
                          const int* N, int K, const ColsumBatch* sums, hipStream_t st);
+// whether they finish column sums in the products' own launch
+bool gemm_tn_multi_takes_sums(int dtype, int n, const int* M, const int* N, int K);
 // mask: [b, s, s] bytes (nonzero = hidden) or null, used when causal == 0
 int launch_attn_fwd(int dtype, const void* qkv, void* ctx, float* lse, int s, int b, int heads, int dh,
                     const uint8_t* mask, int causal, hipStream_t st);

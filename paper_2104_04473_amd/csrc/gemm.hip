@@ -11,6 +11,7 @@
 // into MFMA fragments by transposing LDS reads.
 // fp32 path: v_mfma_f32_32x32x2_f32, operands straight from memory (small configurations).
 #include "colsum.h"
+#include "gelu.h"
 #include <type_traits>
 
 namespace ptdp {
@@ -53,11 +54,23 @@ template <bool V> struct F32Operand {
   }
 };
 constexpr int f32_most_waves(int nb) { return nb == 1 ? 8 : 4; }   // waves that share a tile's k range
+
+// What an output stage does beside writing C.  EPI_GELU (NN): C = A B and g = GeLU(C + b).  EPI_GELU_GRAD (NT): C = (A B^T) * GeLU'(z + b), and
+// the column sums of C over blocks of rows to part[block][N].  Both from what a kernel of its own would read: the product as it is stored.
+enum { EPI_PLAIN = 0, EPI_GELU = 1, EPI_GELU_GRAD = 2 };
+template <int KIND, int MODE = PTDP_GELU_ERF> struct Epi {   // MODE: PTDP_GELU_*
+  static constexpr int kKind = KIND, kMode = MODE;
+};
+template <typename T> struct GeluArgs {
+  const T *b, *z;
+  T* g;
+  float* part;
+};
 // One tile by the workgroup's first kg waves.  SOME: there may be more, which only take part in the end.
-template <bool VA, bool VB, int NB, bool SOME>
+template <bool VA, bool VB, int NB, bool SOME, class EPI>
 __device__ __forceinline__ void gemm_f32_tile(const float* __restrict__ A, const float* __restrict__ B, float* C, const float* __restrict__ bias,
                                               int M, int N, int K, size_t a_rs, size_t a_cs, size_t b_rs, size_t b_cs, int accumulate,
-                                              int tile_m, int tile_n, int kg, float* part) {
+                                              int tile_m, int tile_n, int kg, float* part, const GeluArgs<float>& e) {
   constexpr int kTile = 32 * NB, kPitch = kTile + 8;   // rows 4 apart (the two halves of a register) in different banks
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, l31 = lane & 31, half = lane >> 5;
   const int m0 = tile_m * kTile, n0 = tile_n * kTile;
@@ -131,16 +144,31 @@ __device__ __forceinline__ void gemm_f32_tile(const float* __restrict__ A, const
     float v = 0.f;
     for (int w = 0; w < kg; ++w) v += part[w * (kTile * kPitch) + r * kPitch + c];
     if (bias) v += bias[n];
-    float* o = C + (size_t)m * N + n;
-    *o = accumulate ? *o + v : v;
+    const size_t at = (size_t)m * N + n;
+    if (EPI::kKind == EPI_GELU_GRAD) {
+      v *= gelu_grad_f<EPI::kMode>(e.z[at] + e.b[n]);
+      part[r * kPitch + c] = v;   // in the place that this thread alone has read
+    }
+    C[at] = accumulate ? C[at] + v : v;
+    if (EPI::kKind == EPI_GELU) e.g[at] = gelu_f<EPI::kMode>(v + e.b[n]);
+  }
+  if (EPI::kKind == EPI_GELU_GRAD) {   // a column's sum over the tile's rows: one column a thread, four sums of every fourth row
+    __syncthreads();
+    const int c = threadIdx.x, rows = min(kTile, M - m0);
+    if (c < kTile && n0 + c < N) {
+      float t[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int r = 0; r < kTile; ++r) t[r & 3] += r < rows ? part[r * kPitch + c] : 0.f;
+      e.part[(size_t)tile_m * N + n0 + c] = (t[0] + t[1]) + (t[2] + t[3]);
+    }
   }
 }
-template <bool VA, bool VB, int NB>
+template <bool VA, bool VB, int NB, class EPI = Epi<EPI_PLAIN>>
 __global__ void __launch_bounds__(64 * f32_most_waves(NB))
 gemm_f32_kernel(const float* __restrict__ A, const float* __restrict__ B, float* C, const float* __restrict__ bias,
-                int M, int N, int K, size_t a_rs, size_t a_cs, size_t b_rs, size_t b_cs, int accumulate) {
+                int M, int N, int K, size_t a_rs, size_t a_cs, size_t b_rs, size_t b_cs, int accumulate, GeluArgs<float> e) {
   extern __shared__ __attribute__((aligned(16))) float part[];
-  gemm_f32_tile<VA, VB, NB, false>(A, B, C, bias, M, N, K, a_rs, a_cs, b_rs, b_cs, accumulate, blockIdx.y, blockIdx.x, blockDim.x >> 6, part);
+  gemm_f32_tile<VA, VB, NB, false, EPI>(A, B, C, bias, M, N, K, a_rs, a_cs, b_rs, b_cs, accumulate, blockIdx.y, blockIdx.x, blockDim.x >> 6, part, e);
 }
 
 // The same on one 16 x 16 tile (v_mfma_f32_16x16x4_f32), for outputs of fewer 32 x 32 tiles than the chip has compute units, where
@@ -166,10 +194,11 @@ template <bool V> struct F32Operand16 {
   }
 };
 constexpr int kF32TinyWaves = 8, kF32TinyAhead = 4;
-template <bool VA, bool VB>
+template <bool VA, bool VB, class EPI>
 __device__ __forceinline__ void gemm_f32_tiny_tile(const float* __restrict__ A, const float* __restrict__ B, float* C, const float* __restrict__ bias,
                                                    int M, int N, int K, size_t a_rs, size_t a_cs, size_t b_rs, size_t b_cs, int accumulate,
-                                                   int tile_m, int tile_n, float (*part)[16][17]) {
+                                                   int tile_m, int tile_n, float (*part)[16][17], const GeluArgs<float>& e) {
+  static_assert(EPI::kKind != EPI_GELU_GRAD, "the partial column sums have room for one row per 32 rows");
   // kg is kF32TinyWaves, read from the launch: as a constant the loops come out 1.5 % slower (a fp32 layer of 66 x 768)
   const int wave = threadIdx.x >> 6, kg = blockDim.x >> 6, lane = threadIdx.x & 63, l15 = lane & 15, q = lane >> 4;
   const int m0 = tile_m * 16, n0 = tile_n * 16;
@@ -205,15 +234,16 @@ __device__ __forceinline__ void gemm_f32_tiny_tile(const float* __restrict__ A, 
   float v = 0.f;
   for (int w = 0; w < kg; ++w) v += part[w][x >> 4][x & 15];
   if (bias) v += bias[n];
-  float* o = C + (size_t)m * N + n;
-  *o = accumulate ? *o + v : v;
+  const size_t at = (size_t)m * N + n;
+  C[at] = accumulate ? C[at] + v : v;
+  if (EPI::kKind == EPI_GELU) e.g[at] = gelu_f<EPI::kMode>(v + e.b[n]);
 }
-template <bool VA, bool VB>
+template <bool VA, bool VB, class EPI = Epi<EPI_PLAIN>>
 __global__ void __launch_bounds__(64 * kF32TinyWaves)
 gemm_f32_tiny_kernel(const float* __restrict__ A, const float* __restrict__ B, float* C, const float* __restrict__ bias,
-                     int M, int N, int K, size_t a_rs, size_t a_cs, size_t b_rs, size_t b_cs, int accumulate) {
+                     int M, int N, int K, size_t a_rs, size_t a_cs, size_t b_rs, size_t b_cs, int accumulate, GeluArgs<float> e) {
   __shared__ float part[kF32TinyWaves][16][17];
-  gemm_f32_tiny_tile<VA, VB>(A, B, C, bias, M, N, K, a_rs, a_cs, b_rs, b_cs, accumulate, blockIdx.y, blockIdx.x, part);
+  gemm_f32_tiny_tile<VA, VB, EPI>(A, B, C, bias, M, N, K, a_rs, a_cs, b_rs, b_cs, accumulate, blockIdx.y, blockIdx.x, part, e);
 }
 
 // Weight gradients of one layer (C_j[M_j, N_j] += A_j^T B_j, sharing K) whose tiles have the same size as one launch: alone each is a
@@ -248,20 +278,21 @@ gemm_f32_multi_kernel(MultiF32 a, ColsumBatchArgs sums, int n_sums) {
     }
   const int tiles_n = (N + kTile - 1) / kTile, t = id - first;
   if constexpr (TINY)
-    gemm_f32_tiny_tile<false, false>(A, B, C, nullptr, M, N, a.K, 1, M, N, 1, 1, t / tiles_n, t % tiles_n, reinterpret_cast<float (*)[16][17]>(part));
+    gemm_f32_tiny_tile<false, false, Epi<EPI_PLAIN>>(A, B, C, nullptr, M, N, a.K, 1, M, N, 1, 1, t / tiles_n, t % tiles_n,
+                                                reinterpret_cast<float (*)[16][17]>(part), {});
   else
-    gemm_f32_tile<false, false, 1, true>(A, B, C, nullptr, M, N, a.K, 1, M, N, 1, 1, t / tiles_n, t % tiles_n, kg, part);
+    gemm_f32_tile<false, false, 1, true, Epi<EPI_PLAIN>>(A, B, C, nullptr, M, N, a.K, 1, M, N, 1, 1, t / tiles_n, t % tiles_n, kg, part, {});
 }
 
-template <bool VA, bool VB, int NB>
+template <bool VA, bool VB, int NB, class EPI = Epi<EPI_PLAIN>>
 static int launch_gemm_f32_t(const float* A, const float* B, float* C, const float* bias, int M, int N, int K, size_t a_rs, size_t a_cs,
-                             size_t b_rs, size_t b_cs, int accumulate, int kg, hipStream_t st) {
-  auto kern = gemm_f32_kernel<VA, VB, NB>;
+                             size_t b_rs, size_t b_cs, int accumulate, int kg, hipStream_t st, const GeluArgs<float>& e = {}) {
+  auto kern = gemm_f32_kernel<VA, VB, NB, EPI>;
   constexpr int kTile = 32 * NB, kPart = kTile * (kTile + 8) * (int)sizeof(float);
   static once_flag_t done[kMaxDevices];
   if (set_dynamic_smem(reinterpret_cast<const void*>(kern), f32_most_waves(NB) * kPart, done) != PTDP_OK) return PTDP_E_HIP;
   hipLaunchKernelGGL(kern, dim3((N + kTile - 1) / kTile, (M + kTile - 1) / kTile), dim3(64 * kg), kg * kPart, st, A, B, C, bias, M, N, K,
-                     a_rs, a_cs, b_rs, b_cs, accumulate);
+                     a_rs, a_cs, b_rs, b_cs, accumulate, e);
   return PTDP_OK;
 }
 static int compute_units();
@@ -289,17 +320,19 @@ static F32Form f32_form(bool va, bool vb, int M, int N, int K) {
   while (kg > 1 && (kg > (K + kF32Chunk - 1) / kF32Chunk || (big ? t2 : t1) * kg > 16 * ncu)) kg /= 2;
   return {big ? 64 : 32, kg};
 }
-template <bool VA, bool VB>
+template <bool VA, bool VB, class EPI = Epi<EPI_PLAIN>>
 static int launch_gemm_f32(const float* A, const float* B, float* C, const float* bias, int M, int N, int K, size_t a_rs, size_t a_cs,
-                           size_t b_rs, size_t b_cs, int accumulate, hipStream_t st) {
+                           size_t b_rs, size_t b_cs, int accumulate, hipStream_t st, const GeluArgs<float>& e = {}) {
   const F32Form f = f32_form(VA, VB, M, N, K);
   if (f.tile == 16) {
-    hipLaunchKernelGGL((gemm_f32_tiny_kernel<VA, VB>), dim3((N + 15) / 16, (M + 15) / 16), dim3(64 * kF32TinyWaves), 0, st, A, B, C, bias, M, N, K,
-                       a_rs, a_cs, b_rs, b_cs, accumulate);
+    if constexpr (EPI::kKind == EPI_GELU_GRAD) return PTDP_E_STATE;   // the callers ask for the form first
+    else
+      hipLaunchKernelGGL((gemm_f32_tiny_kernel<VA, VB, EPI>), dim3((N + 15) / 16, (M + 15) / 16), dim3(64 * kF32TinyWaves), 0, st, A, B, C, bias, M, N,
+                         K, a_rs, a_cs, b_rs, b_cs, accumulate, e);
     return PTDP_OK;
   }
-  if (f.tile == 64) return launch_gemm_f32_t<VA, VB, 2>(A, B, C, bias, M, N, K, a_rs, a_cs, b_rs, b_cs, accumulate, f.kg, st);
-  return launch_gemm_f32_t<VA, VB, 1>(A, B, C, bias, M, N, K, a_rs, a_cs, b_rs, b_cs, accumulate, f.kg, st);
+  if (f.tile == 64) return launch_gemm_f32_t<VA, VB, 2, EPI>(A, B, C, bias, M, N, K, a_rs, a_cs, b_rs, b_cs, accumulate, f.kg, st, e);
+  return launch_gemm_f32_t<VA, VB, 1, EPI>(A, B, C, bias, M, N, K, a_rs, a_cs, b_rs, b_cs, accumulate, f.kg, st, e);
 }
 
 template <bool TINY> static int launch_f32_multi(const MultiF32& a, int blocks, const ColsumBatchArgs& sums, hipStream_t st) {
@@ -681,6 +714,23 @@ enum { OUT_BF16 = 0, OUT_F32_STORE = 1, OUT_F32_RMW = 2, OUT_F32_RMW_LINES = 3 }
 static inline bool whole_lines(size_t ldc) { return ldc * sizeof(float) % 128 == 0; }
 constexpr size_t kWideRow = (size_t)1 << 23;   // bytes; rows of C from here on take 64-bit addresses
 
+// GeluRows: z at a lane's places of the output (as gemm_epilogue leaves them with the lanes), zeros past the end.
+template <int NS, int RB> struct GeluRows {
+  typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
+  u32x4_t v[NS][RB];
+  template <int BM, int BN>
+  __device__ __forceinline__ void load(const bf16_t* z, const int (&row)[NS], const int (&col)[NS], size_t ldc, int M, int N, int m0, int n0) {
+    const int lane = threadIdx.x & 63, l15 = lane & 15, q = lane >> 4, c8 = 16 * (q & 1) + 8 * (q >> 1);
+    const uint32_t pitch = (uint32_t)ldc * 2, records = (uint32_t)(min(BM, M - m0) - 1) * pitch + (uint32_t)min(BN, N - n0) * 2;
+    const auto r = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(z) + (size_t)m0 * ldc + n0, 0, records, 0x00020000);
+#pragma unroll
+    for (int b = 0; b < NS; ++b)
+#pragma unroll
+      for (int i = 0; i < RB; ++i)
+        v[b][i] = __builtin_amdgcn_raw_buffer_load_b128(r, n0 + col[b] + c8 < N ? (uint32_t)(row[b] + l15 + i * 16) * pitch + (col[b] + c8) * 2 : kOob, 0, 0);
+  }
+};
+
 // Lane-to-memory mapping: with four consecutive columns per lane a block's store would cover 16 rows x 64 bytes (fp32)
 // or 32 bytes (bf16) of each.  bf16: the two column blocks of a 32-column group change lanes (v_permlane16_swap) so
 // that a lane ends up with eight consecutive columns (16 bytes).  fp32: lanes of rows 0-7 and 8-15 change halves (a
@@ -689,9 +739,13 @@ constexpr size_t kWideRow = (size_t)1 << 23;   // bytes; rows of C from here on 
 // with rows staged through LDS).  All accesses to C go through a buffer descriptor that ends behind the tile's last
 // row (columns past N: an offset beyond it), so the stage is free of branches.
 // row[b], col[b]: first row and column of strip b inside the BM x BN tile.
-template <int OUT, int BM, int BN, int NS, int RB>
+// EPI other than plain (OUT_BF16, rows of less than kWideRow): the exchange leaves a lane with eight consecutive columns of a row, what the
+// element-wise kernels give a lane; a block of rows of EPI_GELU_GRAD's sums is the RB * 16 rows of a wave.
+template <int OUT, int BM, int BN, int NS, int RB, class EPI = Epi<EPI_PLAIN>>
 __device__ __forceinline__ void gemm_epilogue(const StripAcc<NS, RB>& acc, const int (&row)[NS], const int (&col)[NS], void* Cv, size_t ldc,
-                                              const bf16_t* bias, int M, int N, int m0, int n0) {
+                                              const bf16_t* bias, int M, int N, int m0, int n0, const GeluArgs<bf16_t>& e = {},
+                                              const GeluRows<NS, RB>& zr = {}) {
+  static_assert(EPI::kKind == EPI_PLAIN || OUT == OUT_BF16, "from the stored product");
   typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
   typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
   constexpr uint32_t esz = OUT == OUT_BF16 ? 2 : 4;
@@ -734,10 +788,21 @@ __device__ __forceinline__ void gemm_epilogue(const StripAcc<NS, RB>& acc, const
   const auto rc = __builtin_amdgcn_make_buffer_rsrc(origin, 0, records, 0x00020000);
   if (OUT == OUT_BF16) {
     const int c8 = 16 * (q & 1) + 8 * (q >> 1);   // first of this lane's 8 columns after the exchange
+    const size_t first = (size_t)m0 * ldc + n0;
+    const auto rg = __builtin_amdgcn_make_buffer_rsrc(e.g + first, 0, EPI::kKind == EPI_GELU ? records : 0, 0x00020000);
 #pragma unroll
     for (int b = 0; b < NS; ++b) {
       const int c = col[b] + c8;
       const uint32_t off = n0 + c < N ? (uint32_t)(row[b] + l15) * pitch + c * esz : kOob;
+      float gb[8], sum[8];
+      if (EPI::kKind != EPI_PLAIN) {
+        Vec16<bf16_t> w;
+        w.raw = make_uint4(0u, 0u, 0u, 0u);
+        if (n0 + c < N) w.load(e.b + n0 + c);
+        w.unpack(gb);
+#pragma unroll
+        for (int j = 0; j < 8; ++j) sum[j] = 0.f;
+      }
 #pragma unroll
       for (int i = 0; i < RB; ++i) {
         uint32_t p[2][2];
@@ -749,7 +814,45 @@ __device__ __forceinline__ void gemm_epilogue(const StripAcc<NS, RB>& acc, const
         }
         const u32x2_t x = __builtin_amdgcn_permlane16_swap(p[0][0], p[1][0], false, false);
         const u32x2_t y = __builtin_amdgcn_permlane16_swap(p[0][1], p[1][1], false, false);
-        __builtin_amdgcn_raw_buffer_store_b128(u32x4_t{x[0], y[0], x[1], y[1]}, rc, off + i * 16 * pitch, 0, 0);
+        u32x4_t out = {x[0], y[0], x[1], y[1]};
+        if (EPI::kKind != EPI_PLAIN) {
+          Vec16<bf16_t> v, z;
+          float f[8], zf[8];
+          v.raw = __builtin_bit_cast(uint4, out);
+          v.unpack(f);
+          if (EPI::kKind == EPI_GELU) {
+#pragma unroll
+            for (int j = 0; j < 8; ++j) f[j] = gelu_f<EPI::kMode>(f[j] + gb[j]);
+            v.pack(f);
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, v.raw), rg, off + i * 16 * pitch, 0, 0);
+          } else {
+            z.raw = __builtin_bit_cast(uint4, zr.v[b][i]);
+            z.unpack(zf);
+            const bool there = m0 + row[b] + i * 16 + l15 < M;
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+              f[j] *= gelu_grad_f<EPI::kMode>(zf[j] + gb[j]);
+              sum[j] += there ? f[j] : 0.f;
+            }
+            v.pack(f);
+            out = __builtin_bit_cast(u32x4_t, v.raw);
+          }
+        }
+        __builtin_amdgcn_raw_buffer_store_b128(out, rc, off + i * 16 * pitch, 0, 0);
+      }
+      if (EPI::kKind == EPI_GELU_GRAD) {   // the sixteen rows of a block are lanes l15
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+          sum[j] += row_rotate<8>(sum[j]);
+          sum[j] += row_rotate<4>(sum[j]);
+          sum[j] += row_rotate<2>(sum[j]);
+          sum[j] += row_rotate<1>(sum[j]);
+        }
+        if (l15 == 0 && n0 + c < N && m0 + row[b] < M) {
+          float* p = e.part + (size_t)((m0 + row[b]) / (RB * 16)) * ldc + n0 + c;
+          *reinterpret_cast<float4*>(p) = make_float4(sum[0], sum[1], sum[2], sum[3]);
+          *reinterpret_cast<float4*>(p + 4) = make_float4(sum[4], sum[5], sum[6], sum[7]);
+        }
       }
     }
   } else {
@@ -942,8 +1045,8 @@ template <int BM, int BN, int S, int KG> struct SmallGeom {
   static constexpr int kThreads = KG * kSmallThreads;
 };
 
-template <bool TA, bool TB, int OUT, int BM, int BN, int S, int KG>
-__device__ __forceinline__ void gemm_small_tile(const GemmArgs& g, void* Cv, int m0, int n0, char* smem) {
+template <bool TA, bool TB, int OUT, int BM, int BN, int S, int KG, class EPI>
+__device__ __forceinline__ void gemm_small_tile(const GemmArgs& g, void* Cv, int m0, int n0, char* smem, const GeluArgs<bf16_t>& e) {
   typedef SmallGeom<BM, BN, S, KG> G;
   constexpr int NS = BN / 64, RB = BM / 32, kLoads = (BM + BN) / 32;   // strips, row blocks; loads per wave and k-tile
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) & 3;
@@ -969,6 +1072,14 @@ __device__ __forceinline__ void gemm_small_tile(const GemmArgs& g, void* Cv, int
     la.issue(ra, ring + stage * G::kStage, wave, lane, kt * KG + kg, g.K);
     lb.issue(rb, ring + stage * G::kStage + G::kA, wave, lane, kt * KG + kg, g.K);
   };
+  int row[NS], col[NS];
+#pragma unroll
+  for (int b = 0; b < NS; ++b) {
+    row[b] = wm;
+    col[b] = wn + b * 32;
+  }
+  GeluRows<NS, RB> z;   // requested ahead of everything else, waited for at the end
+  if (EPI::kKind == EPI_GELU_GRAD && kg == 0) z.template load<BM, BN>(e.z, row, col, g.ldc, g.M, g.N, m0, n0);
 #pragma unroll
   for (int i = 0; i < S; ++i) request(i, i);
   StripAcc<NS, RB> acc;
@@ -1042,13 +1153,7 @@ __device__ __forceinline__ void gemm_small_tile(const GemmArgs& g, void* Cv, int
 #pragma unroll
       for (int i = 0; i < RB * 2; ++i) acc[b][i >> 1][i & 1] += sum[(b * RB * 2 + i) * 64];
   }
-  int row[NS], col[NS];
-#pragma unroll
-  for (int b = 0; b < NS; ++b) {
-    row[b] = wm;
-    col[b] = wn + b * 32;
-  }
-  gemm_epilogue<OUT, BM, BN, NS, RB>(acc, row, col, Cv, g.ldc, g.bias, g.M, g.N, m0, n0);
+  gemm_epilogue<OUT, BM, BN, NS, RB, EPI>(acc, row, col, Cv, g.ldc, g.bias, g.M, g.N, m0, n0, e, z);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -1254,19 +1359,26 @@ gemm_bf16_wide_kernel(GemmArgs g, void* Cv) {
 // Tiles are numbered in groups of 8 row tiles, column by column inside a group; each XCD takes one contiguous run, so
 // that its workgroups share operand panels through its L2.
 template <int BM, int BN> static inline int small_blocks(int M, int N) { return 8 * ((((M + BM - 1) / BM) * ((N + BN - 1) / BN) + 7) / 8); }
-template <bool TA, bool TB, int OUT, int BM, int BN, int S, int KG>
-__device__ __forceinline__ void gemm_small_id(const GemmArgs& g, void* Cv, int id, char* smem) {
+template <bool TA, bool TB, int OUT, int BM, int BN, int S, int KG, class EPI = Epi<EPI_PLAIN>>
+__device__ __forceinline__ void gemm_small_id(const GemmArgs& g, void* Cv, int id, char* smem, const GeluArgs<bf16_t>& e = {}) {
   const int tiles_m = (g.M + BM - 1) / BM, tiles_n = (g.N + BN - 1) / BN, tiles = tiles_m * tiles_n;
   const int per_xcd = (tiles + 7) / 8, t = (id & 7) * per_xcd + (id >> 3);
   if ((id >> 3) >= per_xcd || t >= tiles) return;
   const int grp = t / (8 * tiles_n), in_grp = t - grp * 8 * tiles_n, gm = min(8, tiles_m - grp * 8);
-  gemm_small_tile<TA, TB, OUT, BM, BN, S, KG>(g, Cv, (grp * 8 + in_grp % gm) * BM, (in_grp / gm) * BN, smem);
+  gemm_small_tile<TA, TB, OUT, BM, BN, S, KG, EPI>(g, Cv, (grp * 8 + in_grp % gm) * BM, (in_grp / gm) * BN, smem, e);
 }
 template <bool TA, bool TB, int OUT, int BM, int BN, int S, int KG>
 __global__ void __launch_bounds__(KG * kSmallThreads, 2)
 gemm_bf16_small_kernel(GemmArgs g, void* Cv) {
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   gemm_small_id<TA, TB, OUT, BM, BN, S, KG>(g, Cv, blockIdx.x, smem);
+}
+// The first MLP product with the GeLU behind it (NN) and the second one's input gradient with the GeLU's (NT, TB false).
+template <bool TB, int MODE, int BM, int BN, int S, int KG>
+__global__ void __launch_bounds__(KG * kSmallThreads, 2)
+gemm_bf16_small_gelu_kernel(GemmArgs g, void* Cv, GeluArgs<bf16_t> e) {
+  extern __shared__ __attribute__((aligned(1024))) char smem[];
+  gemm_small_id<false, TB, OUT_BF16, BM, BN, S, KG, Epi<TB ? EPI_GELU : EPI_GELU_GRAD, MODE>>(g, Cv, blockIdx.x, smem, e);
 }
 
 // Up to four independent problems of the same form in one launch: each later problem's tiles fill the CUs that the
@@ -1446,6 +1558,26 @@ static int launch_small(const GemmArgs& g, void* C, hipStream_t st) {
   const int blocks = small_blocks<BM, BN>(g.M, g.N);
   hipLaunchKernelGGL(kern, dim3(blocks), dim3(KG * kSmallThreads), smem, st, g, C);
   return PTDP_OK;
+}
+template <bool TB, int MODE, int BM, int BN, int S, int KG>
+static int launch_small_gelu(const GemmArgs& g, void* C, const GeluArgs<bf16_t>& e, hipStream_t st) {
+  auto kern = gemm_bf16_small_gelu_kernel<TB, MODE, BM, BN, S, KG>;
+  static once_flag_t done[kMaxDevices];
+  constexpr int smem = SmallGeom<BM, BN, S, KG>::kSmem;
+  if (set_dynamic_smem(reinterpret_cast<const void*>(kern), smem, done) != PTDP_OK) return PTDP_E_HIP;
+  hipLaunchKernelGGL(kern, dim3(small_blocks<BM, BN>(g.M, g.N)), dim3(KG * kSmallThreads), smem, st, g, C, e);
+  return PTDP_OK;
+}
+template <bool TB, int MODE>
+static int launch_small_gelu_form(int form, const GemmArgs& g, void* C, const GeluArgs<bf16_t>& e, hipStream_t st) {
+  switch (form) {
+    case 0: return launch_small_gelu<TB, MODE, 128, 128, 2, 1>(g, C, e, st);
+    case 1: return launch_small_gelu<TB, MODE, 128, 128, 2, 2>(g, C, e, st);
+    case 2: return launch_small_gelu<TB, MODE, 128, 64, 3, 2>(g, C, e, st);
+    case 3: return launch_small_gelu<TB, MODE, 64, 64, 4, 2>(g, C, e, st);
+    case 4: return launch_small_gelu<TB, MODE, 128, 64, 2, 1>(g, C, e, st);
+    default: return PTDP_E_STATE;   // gelu_form offers no other
+  }
 }
 template <bool TB>
 static int launch_wide(const GemmArgs& g, void* C, hipStream_t st) {
@@ -1680,10 +1812,7 @@ void gemm_form_query(int mode, int M, int N, int K, int out_f32, int accumulate,
 }
 
 template <bool TA, bool TB>
-static int launch_bf16_mode(const void* A, const void* B, void* C, const void* bias, int M, int N, int K, int out_f32,
-                            int accumulate, void* ws, size_t ws_bytes, hipStream_t st) {
-  // the kernel addresses each operand through a 31-bit byte offset from the block's first row
-  if ((size_t)M * K * 2 >= 0x7fffffffull || (size_t)N * K * 2 >= 0x7fffffffull) return PTDP_E_UNSUPPORTED;
+static GemmArgs bf16_args(const void* A, const void* B, const void* bias, int M, int N, int K) {
   GemmArgs g;
   g.A = (const bf16_t*)A;
   g.B = (const bf16_t*)B;
@@ -1694,7 +1823,15 @@ static int launch_bf16_mode(const void* A, const void* B, void* C, const void* b
   g.lda = TA ? (size_t)M : (size_t)K;
   g.ldb = TB ? (size_t)N : (size_t)K;
   g.ldc = (size_t)N;
+  return g;
+}
 
+template <bool TA, bool TB>
+static int launch_bf16_mode(const void* A, const void* B, void* C, const void* bias, int M, int N, int K, int out_f32,
+                            int accumulate, void* ws, size_t ws_bytes, hipStream_t st) {
+  // the kernel addresses each operand through a 31-bit byte offset from the block's first row
+  if ((size_t)M * K * 2 >= 0x7fffffffull || (size_t)N * K * 2 >= 0x7fffffffull) return PTDP_E_UNSUPPORTED;
+  const GemmArgs g = bf16_args<TA, TB>(A, B, bias, M, N, K);
   SplitPlan P;
   const int form = choose_form(TA ? PTDP_GEMM_TN : (TB ? PTDP_GEMM_NN : PTDP_GEMM_NT), M, N, K, out_f32, accumulate, bias != nullptr,
                                ws != nullptr ? ws_bytes : 0, &P);
@@ -1764,20 +1901,6 @@ static int launch_bf16_mode(const void* A, const void* B, void* C, const void* b
   return PTDP_OK;
 }
 
-static GemmArgs tn_args(const void* A, const void* B, int M, int N, int K) {
-  GemmArgs g;
-  g.A = (const bf16_t*)A;
-  g.B = (const bf16_t*)B;
-  g.bias = nullptr;
-  g.a_end = (const char*)A + (size_t)M * K * 2;
-  g.b_end = (const char*)B + (size_t)N * K * 2;
-  g.M = M; g.N = N; g.K = K;
-  g.lda = (size_t)M;
-  g.ldb = (size_t)N;
-  g.ldc = (size_t)N;
-  return g;
-}
-
 // *sums: finished in this launch where the tiles are small, and then empty
 template <int OUT> static int launch_tn_multi(int form, MultiArgs& a, ColsumBatch* sums, hipStream_t st) {
   if (form >= 0) {
@@ -1800,6 +1923,24 @@ template <int OUT> static int launch_tn_multi(int form, MultiArgs& a, ColsumBatc
   return PTDP_OK;
 }
 
+// the form that all of a launch's bf16 weight gradients take, or -1 for 256 x 256 tiles
+static int tn_multi_form(int n, const int* M, const int* N, int K) {
+  long long tiles = 0, busiest = 0;
+  double outputs = 0.0;
+  for (int j = 0; j < n; ++j) {
+    const long long tm = (M[j] + kBM - 1) / kBM, tn = (N[j] + kBN - 1) / kBN;
+    tiles += tm * tn;
+    busiest += busiest_xcd(tm, tn);
+    outputs += (double)M[j] * N[j];
+  }
+  return small_form(1, n, M, N, K, large_time(kLargeCost[1], tiles, busiest, outputs / ((double)tiles * kBM * kBN), (K + BK - 1) / BK));
+}
+bool gemm_tn_multi_takes_sums(int dtype, int n, const int* M, const int* N, int K) {
+  if (dtype == PTDP_BF16) return tn_multi_form(n, M, N, K) >= 0;
+  for (int j = 0; j < n; ++j)
+    if (f32_form(false, false, M[j], N[j], K).tile != 64) return true;
+  return false;
+}
 static int gemm_tn_multi(int dtype, int n, const void* const* A, const void* const* B, float* const* C, const int* M, const int* N, int K,
                          ColsumBatch* sums, hipStream_t st) {
   if (n <= 0 || n > kMaxMulti) return PTDP_E_INVALID_ARG;
@@ -1826,22 +1967,13 @@ static int gemm_tn_multi(int dtype, int n, const void* const* A, const void* con
   int at = 0;
   for (int j = 0; j < kMaxMulti; ++j) {
     const int q = j < n ? j : 0;   // unused slots repeat problem 0 (never selected)
-    a.g[j] = tn_args(A[q], B[q], M[q], N[q], K);
+    a.g[j] = bf16_args<true, true>(A[q], B[q], nullptr, M[q], N[q], K);
     a.C[j] = C[q];
     a.start[j] = at;
     if (j < n) at += dp_blocks(a.g[j]);
   }
   a.start[kMaxMulti] = at;
-  long long tiles = 0, busiest = 0;
-  double outputs = 0.0;
-  for (int j = 0; j < n; ++j) {
-    const long long tm = (M[j] + kBM - 1) / kBM, tn = (N[j] + kBN - 1) / kBN;
-    tiles += tm * tn;
-    busiest += busiest_xcd(tm, tn);
-    outputs += (double)M[j] * N[j];
-  }
-  const double t_large = large_time(kLargeCost[1], tiles, busiest, outputs / ((double)tiles * kBM * kBN), (K + BK - 1) / BK);
-  const int form = small_form(1, n, M, N, K, t_large);
+  const int form = tn_multi_form(n, M, N, K);
   bool lines = true;
   for (int j = 0; j < n; ++j) lines = lines && whole_lines(N[j]);
   const int rc = lines ? launch_tn_multi<OUT_F32_RMW_LINES>(form, a, sums, st) : launch_tn_multi<OUT_F32_RMW>(form, a, sums, st);
@@ -1883,6 +2015,77 @@ int launch_gemm(int dtype, int mode, const void* A, const void* B, void* C, cons
   }
   if (rc != PTDP_OK) return rc;
   return L.status();
+}
+
+// The two products next to the MLP's GeLU, with it in their output stage where the call takes small tiles (or is fp32): what a kernel of its
+// own costs there is a launch and a trip of the product through memory, while a tile's 25 vector instructions per element are spread over
+// most of the chip.  With 256 x 256 tiles they would run with nothing beside them, 15 us a tile: see launch_bias_gelu_*.  Speed of a pass
+// against kernels of their own: one fp32 layer of 256 x 256 1.030, two of 666 x 512 1.043, of 2048 x 1024 under a mask 1.016, eight of 1024 x
+// 2048 over two shards 1.020; two of 4096 x 256 1.03, of 8192 x 512 1.00.  z requested behind the k loop instead of in front of it: 1.027,
+// 1.028, 1.003, 1.004 of the first four.
+// The form that such a call takes, or -1 for a kernel of its own.
+static int gelu_form(int mode, int M, int N, int K, size_t ws_bytes) {
+  if ((size_t)M * K * 2 >= 0x7fffffffull || (size_t)N * K * 2 >= 0x7fffffffull || (size_t)N * 2 >= kWideRow || N % 8 != 0) return -1;
+  SplitPlan P;
+  const int form = choose_form(mode, M, N, K, 0, 0, 0, ws_bytes, &P);
+  return kSmallCost[0][form >= 0 ? form : 0].bm == kWideM ? -1 : form;
+}
+
+// z[M,N] = u[M,K] w[K,N], g = GeLU(z + b)
+int launch_gemm_gelu(int dtype, int gelu_mode, const void* u, const void* w, const void* b, void* z, void* g, int M, int N, int K, void* ws,
+                     size_t ws_bytes, hipStream_t st) {
+  if (M == 0 || N == 0) return PTDP_OK;
+  const bool tanh = gelu_mode == PTDP_GELU_TANH, vec = K % 4 == 0 && ((uintptr_t)u & 15) == 0;
+  const int form = dtype == PTDP_BF16 ? gelu_form(PTDP_GEMM_NN, M, N, K, ws ? ws_bytes : 0) : (vec ? 0 : -1);
+  if (form < 0) {
+    const int rc = launch_gemm(dtype, PTDP_GEMM_NN, u, w, z, nullptr, M, N, K, 0, 0, ws, ws_bytes, st);
+    return rc != PTDP_OK ? rc : launch_bias_gelu_fwd(dtype, gelu_mode, z, b, g, M, N, st);
+  }
+  Launch L(PTDP_K_GEMM_NN, 2.0 * M * N * K, st);
+  int rc;
+  if (dtype == PTDP_BF16) {
+    const GeluArgs<bf16_t> e{(const bf16_t*)b, nullptr, (bf16_t*)g, nullptr};
+    const GemmArgs a = bf16_args<false, true>(u, w, nullptr, M, N, K);
+    rc = tanh ? launch_small_gelu_form<true, PTDP_GELU_TANH>(form, a, z, e, st) : launch_small_gelu_form<true, PTDP_GELU_ERF>(form, a, z, e, st);
+  } else {
+    const GeluArgs<float> e{(const float*)b, nullptr, (float*)g, nullptr};
+    const float *A = (const float*)u, *B = (const float*)w;
+    rc = tanh ? launch_gemm_f32<true, false, Epi<EPI_GELU, PTDP_GELU_TANH>>(A, B, (float*)z, nullptr, M, N, K, K, 1, N, 1, 0, st, e)
+              : launch_gemm_f32<true, false, Epi<EPI_GELU, PTDP_GELU_ERF>>(A, B, (float*)z, nullptr, M, N, K, K, 1, N, 1, 0, st, e);
+  }
+  return rc != PTDP_OK ? rc : L.status();
+}
+
+// dz[M,N] = (dg[M,K] w[N,K]^T) * GeLU'(z + b), dbias += its column sums (scratch: colsum_scratch_bytes)
+int launch_gemm_gelu_bwd(int dtype, int gelu_mode, const void* dg, const void* w, const void* z, const void* b, void* dz, float* dbias,
+                         void* scratch, int M, int N, int K, void* ws, size_t ws_bytes, hipStream_t st, ColsumBatch* defer) {
+  if (M == 0 || N == 0) return PTDP_OK;
+  const bool tanh = gelu_mode == PTDP_GELU_TANH, vec = K % 4 == 0 && (((uintptr_t)dg | (uintptr_t)w) & 15) == 0;
+  const F32Form f32 = f32_form(true, true, M, N, K);
+  const int form = dtype == PTDP_BF16 ? gelu_form(PTDP_GEMM_NT, M, N, K, ws ? ws_bytes : 0) : (vec && f32.tile != 16 ? 0 : -1);
+  if (form < 0) {
+    const int rc = launch_gemm(dtype, PTDP_GEMM_NT, dg, w, dz, nullptr, M, N, K, 0, 0, ws, ws_bytes, st);
+    return rc != PTDP_OK ? rc : launch_bias_gelu_bwd(dtype, gelu_mode, dz, z, b, dz, dbias, scratch, M, N, st, defer);
+  }
+  int rows;   // per row of partial sums
+  {
+    Launch L(PTDP_K_GEMM_NT, 2.0 * M * N * K, st);
+    int rc;
+    if (dtype == PTDP_BF16) {
+      rows = kSmallCost[0][form].bm / 2;
+      const GeluArgs<bf16_t> e{(const bf16_t*)b, (const bf16_t*)z, nullptr, (float*)scratch};
+      const GemmArgs a = bf16_args<false, false>(dg, w, nullptr, M, N, K);
+      rc = tanh ? launch_small_gelu_form<false, PTDP_GELU_TANH>(form, a, dz, e, st) : launch_small_gelu_form<false, PTDP_GELU_ERF>(form, a, dz, e, st);
+    } else {
+      rows = f32.tile;
+      const GeluArgs<float> e{(const float*)b, (const float*)z, nullptr, (float*)scratch};
+      const float *A = (const float*)dg, *B = (const float*)w;
+      rc = tanh ? launch_gemm_f32<true, true, Epi<EPI_GELU_GRAD, PTDP_GELU_TANH>>(A, B, (float*)dz, nullptr, M, N, K, K, 1, 1, K, 0, st, e)
+                : launch_gemm_f32<true, true, Epi<EPI_GELU_GRAD, PTDP_GELU_ERF>>(A, B, (float*)dz, nullptr, M, N, K, K, 1, 1, K, 0, st, e);
+    }
+    if (rc != PTDP_OK || (rc = L.status()) != PTDP_OK) return rc;
+  }
+  return colsum_finish((const float*)scratch, (M + rows - 1) / rows, N, dbias, nullptr, N, st, defer);
 }
 
 }  // namespace ptdp

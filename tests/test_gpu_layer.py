@@ -288,3 +288,47 @@ def test_layernorm_behind_a_residual_sum(dtype, h, a, t):
             assert torch.equal(u, rig.field(l, dst, (s, b, h)))
             assert torch.equal(mu, rig.field(l, mean, (s * b,), torch.float32))
             assert torch.equal(rs, rig.field(l, rstd, (s * b,), torch.float32))
+
+
+# every small form of both products, rows and columns that fill no tile, tanh; 256 x 256 and 16 x 16 tiles (kernels of their own)
+@pytest.mark.parametrize("h,a,t,s,b,dtype,gelu,tile", [
+    (512, 8, 1, 25, 8, B.BF16, B.GELU_TANH, (64, 64, 2)), (320, 2, 2, 200, 1, B.BF16, B.GELU_ERF, (128, 64, 1)),
+    (1536, 12, 1, 200, 1, B.BF16, B.GELU_ERF, (128, 64, 2)), (320, 2, 1, 400, 5, B.BF16, B.GELU_TANH, (128, 128, 1)),
+    (512, 8, 1, 400, 5, B.BF16, B.GELU_ERF, (128, 128, 2)), (768, 12, 1, 400, 10, B.BF16, B.GELU_ERF, (256, 256, 1)),
+    (64, 2, 1, 37, 1, B.F32, B.GELU_ERF, None), (256, 4, 1, 128, 2, B.F32, B.GELU_TANH, None), (384, 6, 1, 100, 1, B.F32, B.GELU_ERF, None),
+    (512, 8, 1, 301, 7, B.F32, B.GELU_ERF, None),
+])
+def test_gelu_in_the_products_beside_it(h, a, t, s, b, dtype, gelu, tile):
+    """GeLU and its derivative in the output stage of the products next to them: the bits of a product and a GeLU in calls of their
+    own; the bias gradient's sums take the rows in another order."""
+    cfg = B.make_cfg(h=h, a=a, t=t, s=s, b=b, dtype=dtype, p_hidden=0.1, seed=5, gelu_mode=gelu)
+    rig, T, f = LayerRig(cfg), s * b, 4 * h // t
+    if tile:
+        got = [C.c_int() for _ in range(3)]
+        for mode in (0, 1):
+            B.check(B.ptdp_gemm_form(mode, T, f, h, 0, 0, 0, B.ptdp_gemm_workspace_bytes(), *[C.byref(x) for x in got]), "form")
+            assert tuple(x.value for x in got) == tile
+    x, dy = randn((s, b, h), dtype, 1), randn((s, b, h), dtype, 2)
+    y, dx = torch.empty_like(x), torch.empty_like(x)
+    rig.grads[0]["b_1"].fill_(0.25)
+    B.check(rig.chunk.forward(0, x.data_ptr(), y.data_ptr(), rig.stash.data_ptr(), rig.ws.data_ptr()), "forward")
+    B.check(rig.chunk.backward(0, dy.data_ptr(), dx.data_ptr(), rig.stash.data_ptr(), rig.ws.data_ptr()), "backward")
+    P, at = rig.params[0], {k: rig.ws.data_ptr() + v for k, v in B.workspace_offsets(cfg).items()}
+    Z, G = rig.field(0, "Z", (T, f)), rig.field(0, "G", (T, f))
+    z, g, dz = (torch.empty((T, f), dtype=tdt(dtype), device="cuda") for _ in range(3))
+    db, scratch = torch.full((f,), 0.25, device="cuda"), dev_bytes(B.ptdp_colsum_scratch_bytes(T, f))
+    n = B.ptdp_gemm_workspace_bytes() if dtype == B.BF16 else 0
+    ws = dev_bytes(n)
+    gemm = lambda mode, A, W, out: B.check(B.ptdp_gemm(dtype, mode, A, W.data_ptr(), out.data_ptr(), None, T, f, h, 0, 0, ws.data_ptr(), n, stream()), "gemm")
+    gemm(0, rig.field(0, "U2", (T, h)).data_ptr(), P["w_1"], z)
+    B.check(B.ptdp_bias_gelu_fwd(dtype, gelu, z.data_ptr(), P["b_1"].data_ptr(), g.data_ptr(), T, f, stream()), "gelu")
+    gemm(1, at["DMO"], P["w_2"], dz)
+    B.check(B.ptdp_bias_gelu_bwd(dtype, gelu, dz.data_ptr(), Z.data_ptr(), P["b_1"].data_ptr(), dz.data_ptr(), db.data_ptr(), scratch.data_ptr(), T, f,
+                                 stream()), "gelu backward")
+    sync()
+    off = B.workspace_offsets(cfg)["DZ"]
+    got_dz = rig.ws[off:off + dz.numel() * dz.element_size()].view(dz.dtype).view(T, f)
+    assert torch.equal(Z, z) and torch.equal(G, g) and torch.equal(got_dz, dz)
+    # two fp32 sums of T terms in different orders: relative to the sum of the terms' sizes, below T * 2^-24 (here far below)
+    lim = T * 2.0 ** -24 * (got_dz.double().abs().sum(0) + 0.25)
+    assert ((rig.grads[0]["b_1"].double() - db.double()).abs() <= lim).all()
