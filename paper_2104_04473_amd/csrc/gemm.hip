@@ -478,7 +478,10 @@ constexpr int kHalfBytes = 128 * BK * 2, kStageBytes = 4 * kHalfBytes, kGemmSmem
 // are loop constants and the k advance rides in the scalar offset (which the descriptor's bounds check excludes);
 // the last, partial k-tile, tiles past the end (all lanes out of range) and operands with short rows take the
 // general form with its per-lane checks.  Either way a call issues two loads: the main loop counts them.
-template <bool KSLOW> struct HalfLoad {
+// W: rows of a half-tile that exist.  128: half h is rows h * 128 + r of the block.  96 (of 192): rows of the block (r / 48) * 96 + h * 48 + r % 48,
+// so that a wave's share of both halves is 96 neighbouring rows; the other 32 are out of range.
+template <bool KSLOW, int W = 128> struct HalfLoad {
+  __device__ __forceinline__ static int row_of_96(int h, int r) { return (r / 48) * 96 + h * 48 + r % 48; }
   uint32_t off[2][2];  // [half][load]: byte offset of the lane's chunk at k-tile 0 minus 1024 * load, or kOob if its row is out of range
   uint32_t kstep;      // byte advance per k-tile
   int kpos[2];         // k of the lane's chunk inside the k-tile
@@ -493,15 +496,20 @@ template <bool KSLOW> struct HalfLoad {
         const int chunk = (lane & 7) ^ ((row >> 1) & 7);
         kpos[i] = chunk * 8;
 #pragma unroll
-        for (int h = 0; h < 2; ++h)
-          off[h][i] = h * 128 + row < rows_left ? (uint32_t)(((size_t)(h * 128 + row) * ld + chunk * 8) * 2) - i * 1024u : kOob;
+        for (int h = 0; h < 2; ++h) {
+          if (W == 128) off[h][i] = h * 128 + row < rows_left ? (uint32_t)(((size_t)(h * 128 + row) * ld + chunk * 8) * 2) - i * 1024u : kOob;
+          else off[h][i] = row < W && row_of_96(h, row) < rows_left ? (uint32_t)(((size_t)row_of_96(h, row) * ld + chunk * 8) * 2) - i * 1024u : kOob;
+        }
       } else {
         const int k = wave * 8 + i * 4 + (lane >> 4);
         const int chunk = (lane & 15) ^ (2 * (k & 3)) ^ (8 * ((k >> 3) & 1));
         kpos[i] = k;
 #pragma unroll
-        for (int h = 0; h < 2; ++h)
-          off[h][i] = h * 128 + chunk * 8 < rows_left ? (uint32_t)(((size_t)k * ld + h * 128 + chunk * 8) * 2) - i * 1024u : kOob;
+        for (int h = 0; h < 2; ++h) {
+          const int at = row_of_96(h, chunk * 8);
+          if (W == 128) off[h][i] = h * 128 + chunk * 8 < rows_left ? (uint32_t)(((size_t)k * ld + h * 128 + chunk * 8) * 2) - i * 1024u : kOob;
+          else off[h][i] = chunk * 8 < W && at < rows_left ? (uint32_t)(((size_t)k * ld + at) * 2) - i * 1024u : kOob;
+        }
       }
     }
     kstep = KSLOW ? (uint32_t)(BK * ld * 2) : (uint32_t)(BK * 2);
@@ -948,6 +956,157 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, void* Cv, float* sl
   add.load(slab ? nullptr : g.bias, col, g.N, n0);
   if (slab) gemm_epilogue<OUT_F32_STORE, kBM, kBN, 4, 4>(acc, row, col, slab, kBN, add, kBM, kBN, 0, 0);
   else gemm_epilogue<OUT, kBM, kBN, 4, 4>(acc, row, col, Cv, g.ldc, add, g.M, g.N, m0, n0);
+}
+
+// 256 x 192 tiles (NN and NT), for outputs that give too few 256 x 256 tiles for the compute units.  Eight waves of 2 x 32 rows and 2 x 48
+// columns in the 256 x 256 kernel's two groups, with two phases to a k-tile: its four would be of twelve MFMAs each, too few for what a
+// part costs beside them.
+//   phase:     0                  1
+//   reads      A0(t), B1(t)       A1(t), B0(t+1)     (fragments; complete at the end of the memory part)
+//   requests   A1(t+1), B0(t+2)   A0(t+2), B1(t+2)   (half-tiles, two loads each)
+//   computes   A0 x B0, A0 x B1   A1 x B1, A1 x B0
+// What a phase has read may be refilled from the next phase's memory part on; a request has three phases to land, and the wait at the end of
+// a memory part leaves the eight loads in flight that are younger than what the next one reads.
+template <bool TB>
+__device__ __forceinline__ void gemm_mid_mainloop(f32x4_t (&acc)[4][2][3], const GemmArgs& g, int m0, int n0, char* smem) {
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const bf16_t* a_base = g.A + (size_t)m0 * g.lda;
+  const bf16_t* b_base = TB ? g.B + n0 : g.B + (size_t)n0 * g.ldb;
+  const size_t a_left = (size_t)(g.a_end - reinterpret_cast<const char*>(a_base));
+  const size_t b_left = (size_t)(g.b_end - reinterpret_cast<const char*>(b_base));
+  const rsrc_t ra = make_rsrc(a_base, (uint32_t)(a_left < 0x7fffffffu ? a_left : 0x7fffffffu));
+  const rsrc_t rb = make_rsrc(b_base, (uint32_t)(b_left < 0x7fffffffu ? b_left : 0x7fffffffu));
+  const int nk = (g.K + BK - 1) / BK, kend = g.K;
+  HalfLoad<false> la;
+  HalfLoad<TB, 96> lb;
+  la.init(g.lda, g.M - m0, wave, lane);
+  lb.init(g.ldb, g.N - n0, wave, lane);
+  FragRead<false, 2> fa;
+  FragRead<TB, 3> fb;
+  fa.init(smem, (wave >> 1) * 32, lane);
+  fb.init(smem, (wave & 1) * 48, lane);
+  constexpr int kA0 = 0, kA1 = kHalfBytes, kB0 = 2 * kHalfBytes, kB1 = 3 * kHalfBytes;
+  char* odd_stage = smem + kStageBytes;
+
+  // the requests of the phases in front of phase 0 of the first tile, in the loop's order
+  lb.template issue<0, false>(rb, smem + kB0, wave, 0, kend);
+  la.template issue<0, false>(ra, smem + kA0, wave, 0, kend);
+  lb.template issue<1, false>(rb, smem + kB1, wave, 0, kend);
+  la.template issue<1, false>(ra, smem + kA1, wave, 0, kend);
+  lb.template issue<0, false>(rb, odd_stage + kB0, wave, 1, kend);
+  la.template issue<0, false>(ra, odd_stage + kA0, wave, 1, kend);
+  lb.template issue<1, false>(rb, odd_stage + kB1, wave, 1, kend);
+
+  auto barrier = [] {
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("s_barrier" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  auto wait_all = [] { asm volatile("s_waitcnt vmcnt(8) lgkmcnt(0)" ::: "memory"); };
+  bf16x8_t af[2][2], b0[2][3][2], b1[3][2];   // b0[t & 1]: B0 of tile t
+  wait_all();
+  barrier();
+#pragma unroll
+  for (int j = 0; j < 3; ++j)
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) b0[0][j][ks] = fb.template get<0>(kB0, j, ks);
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // by both groups: phase 0 refills this place
+  barrier();
+  if (wave >= 4) barrier();   // the second group runs one part behind the first
+
+  auto compute = [&](f32x4_t (&c)[2][3], const bf16x8_t (&b)[3][2]) {
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 3; ++j) c[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[j][ks], af[i][ks], c[i][j], 0, 0, 0);
+  };
+  auto tile = [&](auto parity, auto lean, int t) {
+    constexpr int S = decltype(parity)::value, O = S ^ 1;
+    constexpr bool LEAN = decltype(lean)::value;
+    char* own = smem + S * kStageBytes;
+    char* other = smem + O * kStageBytes;
+    // phase 0
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) {
+#pragma unroll
+      for (int i = 0; i < 2; ++i) af[i][ks] = fa.template get<S>(kA0, i, ks);
+#pragma unroll
+      for (int j = 0; j < 3; ++j) b1[j][ks] = fb.template get<S>(kB1, j, ks);
+    }
+    la.template issue<1, LEAN>(ra, other + kA1, wave, t + 1, kend);
+    lb.template issue<0, LEAN>(rb, own + kB0, wave, t + 2, kend);
+    wait_all();
+    barrier();
+    __builtin_amdgcn_s_setprio(1);
+    compute(acc[0], b0[S]);
+    compute(acc[1], b1);
+    __builtin_amdgcn_s_setprio(0);
+    barrier();
+    // phase 1
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) {
+#pragma unroll
+      for (int i = 0; i < 2; ++i) af[i][ks] = fa.template get<S>(kA1, i, ks);
+#pragma unroll
+      for (int j = 0; j < 3; ++j) b0[O][j][ks] = fb.template get<O>(kB0, j, ks);
+    }
+    la.template issue<0, LEAN>(ra, own + kA0, wave, t + 2, kend);
+    lb.template issue<1, LEAN>(rb, own + kB1, wave, t + 2, kend);
+    wait_all();
+    barrier();
+    __builtin_amdgcn_s_setprio(1);
+    compute(acc[3], b1);
+    compute(acc[2], b0[S]);
+    __builtin_amdgcn_s_setprio(0);
+    barrier();
+  };
+  constexpr std::integral_constant<int, 0> even{};
+  constexpr std::integral_constant<int, 1> odd{};
+  int t = 0;
+  if (la.plain && lb.plain)
+    for (; (t + 4) * BK <= kend; t += 2) {   // every tile requested here (up to t + 3) lies inside K whole
+      tile(even, std::true_type{}, t);
+      tile(odd, std::true_type{}, t + 1);
+    }
+  for (; t + 1 < nk; t += 2) {
+    tile(even, std::false_type{}, t);
+    tile(odd, std::false_type{}, t + 1);
+  }
+  if (t < nk) tile(even, std::false_type{}, t);
+  if (wave < 4) barrier();
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the requests past the last k-tile (zeros) have landed
+}
+
+constexpr int kMidN = 192;
+template <bool TB>
+__device__ __forceinline__ void gemm_mid_tile(const GemmArgs& g, void* Cv, int m0, int n0, char* smem) {
+  f32x4_t acc[4][2][3];
+#pragma unroll
+  for (int q = 0; q < 4; ++q)
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 3; ++j) acc[q][i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  gemm_mid_mainloop<TB>(acc, g, m0, n0, smem);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wm = (wave >> 1) * 32, wn = (wave & 1) * 96;
+  StripAcc<6, 2> out;   // strip 3 * ha + p: rows ha * 128 + wm .., columns wn + 32 p ..
+  int row[6], col[6];
+#pragma unroll
+  for (int ha = 0; ha < 2; ++ha)
+#pragma unroll
+    for (int p = 0; p < 3; ++p) {
+      row[3 * ha + p] = ha * 128 + wm;
+      col[3 * ha + p] = wn + 32 * p;
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) out[3 * ha + p][i][j] = acc[2 * ha + (2 * p + j) / 3][i][(2 * p + j) % 3];
+    }
+  ColumnAdd<6, Epi<EPI_PLAIN>> add;
+  add.load(g.bias, col, g.N, n0);
+  gemm_epilogue<OUT_BF16, kBM, kMidN, 6, 2>(out, row, col, Cv, g.ldc, add, g.M, g.N, m0, n0);
 }
 
 // One workgroup per output tile ("data-parallel" form); `id` is the workgroup's index inside its problem.
@@ -1408,6 +1567,17 @@ gemm_bf16_wide_kernel(GemmArgs g, void* Cv) {
   gemm_wide_tile<TB>(g, Cv, (grp * 8 + in_grp % gm) * kWideM, (in_grp / gm) * kWideN, smem);
 }
 
+template <bool TB>
+__global__ void __launch_bounds__(kGemmThreads)
+gemm_bf16_mid_kernel(GemmArgs g, void* Cv) {
+  extern __shared__ __attribute__((aligned(1024))) char smem[];
+  const int tiles_m = (g.M + kBM - 1) / kBM, tiles_n = (g.N + kMidN - 1) / kMidN, tiles = tiles_m * tiles_n;
+  const int id = blockIdx.x, per_xcd = (tiles + 7) / 8, t = (id & 7) * per_xcd + (id >> 3);   // numbered as below
+  if ((id >> 3) >= per_xcd || t >= tiles) return;
+  const int grp = t / (8 * tiles_n), in_grp = t - grp * 8 * tiles_n, gm = min(8, tiles_m - grp * 8);
+  gemm_mid_tile<TB>(g, Cv, (grp * 8 + in_grp % gm) * kBM, (in_grp / gm) * kMidN, smem);
+}
+
 // Tiles are numbered in groups of 8 row tiles, column by column inside a group; each XCD takes one contiguous run, so
 // that its workgroups share operand panels through its L2.
 template <int BM, int BN> static inline int small_blocks(int M, int N) { return 8 * ((((M + BM - 1) / BM) * ((N + BN - 1) / BN) + 7) / 8); }
@@ -1639,6 +1809,15 @@ static int launch_wide(const GemmArgs& g, void* C, hipStream_t st) {
   hipLaunchKernelGGL(kern, dim3(small_blocks<kWideM, kWideN>(g.M, g.N)), dim3(kGemmThreads), kWideSmem, st, g, C);
   return PTDP_OK;
 }
+constexpr int kMidForm = 6;   // in the order of launch_small_form
+template <bool TB>
+static int launch_mid(const GemmArgs& g, void* C, hipStream_t st) {
+  auto kern = gemm_bf16_mid_kernel<TB>;
+  static once_flag_t done[kMaxDevices];
+  if (set_dynamic_smem(reinterpret_cast<const void*>(kern), kGemmSmem, done) != PTDP_OK) return PTDP_E_HIP;
+  hipLaunchKernelGGL(kern, dim3(small_blocks<kBM, kMidN>(g.M, g.N)), dim3(kGemmThreads), kGemmSmem, st, g, C);
+  return PTDP_OK;
+}
 template <bool TA, bool TB, int OUT>
 static int launch_small_form(int form, const GemmArgs& g, void* C, hipStream_t st) {
   switch (form) {
@@ -1647,10 +1826,10 @@ static int launch_small_form(int form, const GemmArgs& g, void* C, hipStream_t s
     case 2: return launch_small<TA, TB, OUT, 128, 64, 3, 2>(g, C, st);
     case 3: return launch_small<TA, TB, OUT, 64, 64, 4, 2>(g, C, st);
     case 4: return launch_small<TA, TB, OUT, 128, 64, 2, 1>(g, C, st);
-    default:
-      if constexpr (!TA) return launch_wide<TB>(g, C, st);
-      else return PTDP_E_STATE;   // small_form offers it to NN and NT alone
+    default: break;
   }
+  if constexpr (TA) return PTDP_E_STATE;   // the others are offered to NN and NT alone
+  else return form == kMidForm ? launch_mid<TB>(g, C, st) : launch_wide<TB>(g, C, st);
 }
 // several problems, see gemm_bf16_dp_multi_kernel; a.start is filled here
 template <int OUT, int BM, int BN, int S, int KG>
@@ -1779,20 +1958,22 @@ struct SmallCost {
   int bm, bn, groups, per_cu;
   double fixed, pair, single, each, per_mb;
 };
-constexpr int kSmallForms = 6;   // TN has no 256 x 128 tiles: with += they are slower than both neighbours (4096 x 4096 x 2048 90 us, 80 and 81)
-static const SmallCost kSmallCost[2][kSmallForms] = {
+constexpr int kSmallForms = 6;   // (256 x 192 tiles, kMidForm, have a model of their own: mid_time)  TN has no 256 x 128 tiles: with += they are slower than both neighbours (4096 x 4096 x 2048 90 us, 80 and 81)
+static const SmallCost kSmallCost[2][kSmallForms + 1] = {
     {{128, 128, 1, 2, 1.9, 0.741, 0.515, 2.1, 0.135},    // (most calls of 64 to 256 large tiles with short k ranges)
      {128, 128, 2, 1, 0.0, 0.0, 0.992, 3.1, 0.102},      // two wave groups share the k range: long k, at most one workgroup per CU
      {128, 64, 2, 1, 0.0, 0.0, 0.576, 3.9, 0.079},
      {64, 64, 2, 1, 0.7, 0.0, 0.372, 2.7, 0.103},        // the smallest outputs
      {128, 64, 1, 2, 2.4, 0.548, 0.422, 0.9, 0.157},
-     {256, 128, 2, 1, 2.3, 0.0, 1.48, 7.2, 0.03}},       // 80 to 128 large tiles (about one workgroup per CU), and the like in more rounds
+     {256, 128, 2, 1, 2.3, 0.0, 1.48, 7.2, 0.03},        // 80 to 128 large tiles (about one workgroup per CU), and the like in more rounds
+     {256, 192, 1, 1, 0.0, 0.0, 0.0, 0.0, 0.0}},
     {{128, 128, 1, 2, 0.0, 0.742, 0.570, 5.8, 0.163},
      {128, 128, 2, 1, 0.0, 0.0, 0.995, 6.6, 0.127},
      {128, 64, 2, 1, 0.4, 0.0, 0.573, 4.7, 0.072},
      {64, 64, 2, 1, 0.9, 0.0, 0.388, 3.4, 0.087},
      {128, 64, 1, 2, 1.4, 0.510, 0.356, 2.8, 0.159},
-     {256, 128, 2, 1, 0.0, 0.0, 0.0, 0.0, 0.0}}};
+     {256, 128, 2, 1, 0.0, 0.0, 0.0, 0.0, 0.0},
+     {256, 192, 1, 1, 0.0, 0.0, 0.0, 0.0, 0.0}}};
 constexpr int kMinStepsForGroups = 8;   // k-tiles from which two wave groups are considered: below, joining their sums costs what they save
 // k-tiles up to which 256 x 128 tiles are considered: longer products are faster on 256 x 256 tiles whose k range is split (us for
 // 256 x 128 and split: 2048 x 4096 x 12288 NT 168, 163; x 16384 NN 211, 209, NT 215, 206).  Of 1409 calls (those of
@@ -1803,7 +1984,8 @@ constexpr int kWideSteps = 120;
 // up to 1.6 times the above (128 x 64, 16 workgroups, 100 k-tiles).
 constexpr int kManyRounds = 16, kManySteps = 32;
 
-static int small_form(int rmw, int n, const int* M, const int* N, int K, double t_large) {
+// *time: of the best large form, then of the best of all
+static int small_form(int rmw, int n, const int* M, const int* N, int K, double* time) {
   const int ncu = compute_units(), nk = (K + BK - 1) / BK;
   int best = -1;
   for (int f = 0; f < (rmw ? kSmallForms - 1 : kSmallForms); ++f) {
@@ -1820,22 +2002,43 @@ static int small_form(int rmw, int n, const int* M, const int* N, int K, double 
     if (tiles > (long long)(kManyRounds - 1) * ncu && nk >= kManySteps) continue;
     const double w = (double)((tiles + ncu - 1) / ncu), steps = (nk + c.groups - 1) / c.groups;
     const double t = c.fixed + c.each * w + c.per_mb * mb + steps * (c.per_cu == 2 ? c.pair * (double)(int)(w / 2) + c.single * (w - 2 * (int)(w / 2)) : c.single * w);
-    if (t < t_large) {
-      t_large = t;
+    if (t < *time) {
+      *time = t;
       best = f;
     }
   }
   return best;
 }
 
+// 256 x 192 tiles, NN (transposing reads of B: twice the read instructions) and NT: a k-tile with all compute units and with few, a call,
+// and per round.  Fitted to 207 measured calls (rms 9 %).
+struct MidCost {
+  double step, step_alone, fixed, round, round_full;
+};
+static const MidCost kMidCost[2] = {{1.19, 0.76, 4.9, 6.0, 3.8}, {1.09, 0.70, 4.6, 6.6, 4.3}};   // [PTDP_GEMM_NN], [PTDP_GEMM_NT]
+// Taken where they promise kMidMargin, from two row tiles that are three quarters full (less: a column panel serves so few rows that its way
+// from memory counts, 204 x 25600 x 768 NN 0.91, 299 x 20096 x 8944 0.89 of the speed).  us of the form taken before and now: NT 2048 x 6144 x 12288 235 ->
+// 220, 2048 x 12288 x 1536 70 -> 65, 1001 x 10240 x 5120 103 -> 92, 860 x 18944 x 2560 109 -> 94, 745 x 25600 x 9216 361 -> 311, 632 x 14848 x 512 18.5 -> 16.6; NN 2048 x
+// 12288 x 1536 73 -> 69, 1415 x 6656 x 1280 31.6 -> 29.4.  Of 208 calls they are picked in 58, at 1.08 times the speed of the form before on average.
+constexpr double kMidMargin = 1.02;
+static double mid_time(int mode, int M, int N, int K) {
+  const int ncu = compute_units(), nk = (K + BK - 1) / BK;
+  const MidCost& c = kMidCost[mode == PTDP_GEMM_NT];
+  const long long tiles = (long long)((M + kBM - 1) / kBM) * ((N + kMidN - 1) / kMidN), rounds = (tiles + ncu - 1) / ncu;
+  const double fill = (double)(tiles - (rounds - 1) * ncu) / ncu;
+  return c.fixed + (double)(rounds - 1) * (c.step * nk + c.round) + (c.step_alone + (c.step - c.step_alone) * fill) * nk + c.round_full * fill;
+}
+
 // The whole decision for one call: a small form, or (-1) the plan of the 256 x 256 kernels.  Small forms exist for bf16
 // outputs of NN and NT and for the += of TN: what a layer's calls need.
-static int choose_form(int mode, int M, int N, int K, int out_f32, int accumulate, int has_bias, size_t ws_bytes, SplitPlan* P) {
+static int choose_form(int mode, int M, int N, int K, int out_f32, int accumulate, int has_bias, size_t ws_bytes, SplitPlan* P, bool mid = true) {
   double t;
   *P = large_plan(M, N, K, out_f32, accumulate, has_bias, ws_bytes, &t);
   const bool rmw = mode == PTDP_GEMM_TN && out_f32 && accumulate;
   if (!rmw && (mode == PTDP_GEMM_TN || out_f32)) return -1;
-  return small_form(rmw, 1, &M, &N, K, t);
+  const int form = small_form(rmw, 1, &M, &N, K, &t);
+  const int rows = (M + kBM - 1) / kBM * kBM;
+  return mid && !rmw && rows > kBM && 4 * (long long)M >= 3ll * rows && mid_time(mode, M, N, K) * kMidMargin < t ? kMidForm : form;
 }
 
 void gemm_plan_query(int M, int N, int K, int out_f32, int accumulate, int has_bias, size_t ws_bytes, int* dp_cols,
@@ -1985,7 +2188,8 @@ static int tn_multi_form(int n, const int* M, const int* N, int K) {
     busiest += busiest_xcd(tm, tn);
     outputs += (double)M[j] * N[j];
   }
-  return small_form(1, n, M, N, K, large_time(kLargeCost[1], tiles, busiest, outputs / ((double)tiles * kBM * kBN), (K + BK - 1) / BK));
+  double t = large_time(kLargeCost[1], tiles, busiest, outputs / ((double)tiles * kBM * kBN), (K + BK - 1) / BK);
+  return small_form(1, n, M, N, K, &t);
 }
 bool gemm_tn_multi_takes_sums(int dtype, int n, const int* M, const int* N, int K) {
   if (dtype == PTDP_BF16) return tn_multi_form(n, M, N, K) >= 0;
@@ -2079,7 +2283,7 @@ int launch_gemm(int dtype, int mode, const void* A, const void* B, void* C, cons
 static int gelu_form(int mode, int M, int N, int K, size_t ws_bytes) {
   if ((size_t)M * K * 2 >= 0x7fffffffull || (size_t)N * K * 2 >= 0x7fffffffull || (size_t)N * 2 >= kWideRow || N % 8 != 0) return -1;
   SplitPlan P;
-  const int form = choose_form(mode, M, N, K, 0, 0, 0, ws_bytes, &P);
+  const int form = choose_form(mode, M, N, K, 0, 0, 0, ws_bytes, &P, false);   // (what 256 x 192 tiles gain on small ones is less than the kernel)
   return kSmallCost[0][form >= 0 ? form : 0].bm == kWideM ? -1 : form;
 }
 

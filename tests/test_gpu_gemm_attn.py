@@ -405,3 +405,25 @@ def test_attention_causal_invariance_on_gpu():
     B.check(B.ptdp_attn_fwd(B.BF16, q2.data_ptr(), ctx2.data_ptr(), lse2.data_ptr(), s, b, heads, dh, stream()), "attn")
     sync()
     assert torch.equal(ctx[:131], ctx2[:131])
+
+
+# 256 x 192 tiles: whole tiles, a few rows or columns in the last one (of its first and of its second half), k-tiles odd and even, the last
+# one whole and partial, one round and two
+MID_TILES = [(B.GEMM_NT, 2048, 6144, 1536), (B.GEMM_NN, 2000, 5120, 1280), (B.GEMM_NT, 2000, 5128, 1288), (B.GEMM_NN, 2008, 5064, 1352), (B.GEMM_NT, 1304, 6152, 6144 + 8),
+             (B.GEMM_NT, 1600, 12256, 1536 - 8), (B.GEMM_NN, 2048, 12288, 1536)]
+
+
+@pytest.mark.parametrize("mode,M,N,K", MID_TILES)
+def test_gemm_mid_tiles(mode, M, N, K):
+    assert form(mode, M, N, K, 0, 0, 1, B.ptdp_gemm_workspace_bytes()) == (256, 192, 1)
+    a, b, bias = randn((M, K), B.BF16, 1), randn((K, N), B.BF16, 2), randn((N,), B.BF16, 3)
+    Bm = b.t().contiguous() if mode == B.GEMM_NT else b
+    n = B.ptdp_gemm_workspace_bytes()
+    ws = torch.empty(n, dtype=torch.uint8, device="cuda")
+    c = torch.full((M + 1, N), 9.0, dtype=torch.bfloat16, device="cuda")
+    B.check(B.ptdp_gemm(B.BF16, mode, a.data_ptr(), Bm.data_ptr(), c.data_ptr(), bias.data_ptr(), M, N, K, 0, 0, ws.data_ptr(), n, stream()), "gemm")
+    sync()
+    want = a.double() @ b.double() + bias.double()
+    # bf16 rounding of the result (2^-9 of its size) plus the fp32 sums' error
+    assert bool(((c[:M].double() - want).abs() <= 2.0 ** -8 * want.abs() + 2.0 ** -22 * K).all())
+    assert bool((c[M] == 9.0).all())

@@ -63,3 +63,14 @@ def test_256x256_tiles_first_reads_are_complete_at_the_second_groups_first_barri
         code = kernels[name]
         first = position(code, READ)
         assert position(code, WAIT, first) < position(code, BARRIER, first), name
+
+
+def test_256x192_tiles_first_reads_are_complete_before_their_place_is_refilled(kernels):
+    """The first phase refills what was read in front of the loop: both groups wait for those reads, and a barrier lies between."""
+    found = [k for k in kernels if "gemm_bf16_mid_kernel" in k]
+    assert len(found) == 2
+    for name in found:
+        code = kernels[name]
+        first = position(code, READ)
+        request, wait = position(code, REQUEST, first), position(code, WAIT, first)
+        assert position(code, BARRIER, wait) < request, name
