@@ -2021,6 +2021,7 @@ static const MidCost kMidCost[2] = {{1.19, 0.76, 4.9, 6.0, 3.8}, {1.09, 0.70, 4.
 // 220, 2048 x 12288 x 1536 70 -> 65, 1001 x 10240 x 5120 103 -> 92, 860 x 18944 x 2560 109 -> 94, 745 x 25600 x 9216 361 -> 311, 632 x 14848 x 512 18.5 -> 16.6; NN 2048 x
 // 12288 x 1536 73 -> 69, 1415 x 6656 x 1280 31.6 -> 29.4.  Of 208 calls they are picked in 58, at 1.08 times the speed of the form before on average.
 constexpr double kMidMargin = 1.02;
+constexpr int kMidShort = 448;   // shorter products are their output stages: within 7 % of small tiles either way
 static double mid_time(int mode, int M, int N, int K) {
   const int ncu = compute_units(), nk = (K + BK - 1) / BK;
   const MidCost& c = kMidCost[mode == PTDP_GEMM_NT];
@@ -2038,7 +2039,7 @@ static int choose_form(int mode, int M, int N, int K, int out_f32, int accumulat
   if (!rmw && (mode == PTDP_GEMM_TN || out_f32)) return -1;
   const int form = small_form(rmw, 1, &M, &N, K, &t);
   const int rows = (M + kBM - 1) / kBM * kBM;
-  return mid && !rmw && rows > kBM && 4 * (long long)M >= 3ll * rows && mid_time(mode, M, N, K) * kMidMargin < t ? kMidForm : form;
+  return mid && !rmw && K > kMidShort && rows > kBM && 4 * (long long)M >= 3ll * rows && mid_time(mode, M, N, K) * kMidMargin < t ? kMidForm : form;
 }
 
 void gemm_plan_query(int M, int N, int K, int out_f32, int accumulate, int has_bias, size_t ws_bytes, int* dp_cols,
