@@ -1111,24 +1111,37 @@ __device__ __forceinline__ void gemm_mid_tile(const GemmArgs& g, void* Cv, int m
 
 // One workgroup per output tile ("data-parallel" form); `id` is the workgroup's index inside its problem.
 // Workgroups are dealt round-robin to the 8 XCDs, each with its own L2.  Each XCD owns the column
-// tiles x, x+8, ... and works through them in groups of up to 8 row tiles, so that the
-// workgroups resident on one XCD share 8 A panels and 4 B panels through that L2.
+// tiles x, x+8, ... of the first 8 * (tiles_n / 8) and works through them in groups of up to 8 row tiles, so that the
+// workgroups resident on one XCD share 8 A panels and 4 B panels through that L2.  The columns left over are
+// numbered the same way and each XCD takes an eighth of their tiles: dealt out whole they gave some XCDs up to 7 % more work than
+// others (50 column tiles: 7 to two of them, 6 to the rest), with the rest idle at the end.  us: a layer of 25600 over eight
+// shards 10690 -> 10390, two of 12288 over eight 5650 -> 5540.
 template <bool TA, bool TB, int OUT>
 __device__ __forceinline__ void gemm_dp_tile(const GemmArgs& g, void* Cv, int id, char* smem) {
   const int tiles_m = (g.M + kBM - 1) / kBM, tiles_n = (g.N + kBN - 1) / kBN;
-  const int xcd = id & 7, local = id >> 3;
-  const int nx = (tiles_n + 7) / 8;                 // column tiles per XCD (some may be past the end)
-  const int per_group = 8 * nx;                     // blocks of one full group of 8 row tiles
-  const int grp = local / per_group, in_grp = local % per_group;
+  const int xcd = id & 7, nx = tiles_n / 8, own = tiles_m * nx;   // whole column tiles per XCD, their tiles
+  int t = id >> 3, cols = nx, first = xcd, step = 8;   // the tile among `cols` column tiles first, first + step, ...
+  if (t >= own) {
+    cols = tiles_n - 8 * nx;
+    first = 8 * nx;
+    step = 1;
+    const int rest = cols * tiles_m, per_xcd = (rest + 7) / 8;
+    t -= own;
+    if (t >= per_xcd) return;
+    t += xcd * per_xcd;
+    if (t >= rest) return;
+  }
+  const int per_group = 8 * cols;                   // tiles of one full group of 8 row tiles
+  const int grp = t / per_group, in_grp = t % per_group;
   const int gm = min(8, tiles_m - grp * 8);         // row tiles in this group
-  const int tile_m = grp * 8 + in_grp % gm, tile_n = (in_grp / gm) * 8 + xcd;
-  if (tile_n >= tiles_n) return;
+  const int tile_m = grp * 8 + in_grp % gm, tile_n = (in_grp / gm) * step + first;
   gemm_tile<TA, TB, OUT>(g, Cv, nullptr, tile_m * kBM, tile_n * kBN, 0, (g.K + BK - 1) / BK, smem);
 }
+// tiles of the XCD that has the most
+static inline long long busiest_xcd(long long tiles_m, long long tiles_n) { return tiles_m * (tiles_n / 8) + (tiles_n % 8 * tiles_m + 7) / 8; }
 // workgroups of one problem (a multiple of 8, so that a second problem starts on XCD 0 again)
 static inline int dp_blocks(const GemmArgs& g) {
-  const int tiles_m = (g.M + kBM - 1) / kBM, tiles_n = (g.N + kBN - 1) / kBN;
-  return 8 * tiles_m * ((tiles_n + 7) / 8);  // 8 XCD queues of equal length; surplus workgroups exit at once
+  return 8 * (int)busiest_xcd((g.M + kBM - 1) / kBM, (g.N + kBN - 1) / kBN);  // 8 XCD queues of equal length; surplus workgroups exit at once
 }
 
 template <bool TA, bool TB, int OUT>
@@ -1874,19 +1887,18 @@ struct LargeCost {
 static const LargeCost kLargeCost[2] = {{3.9, 1.28, 0.78, 8.4, 2.8, 11.5, 1.28, 0.050, 0.26, 0.020},
                                         {5.7, 1.33, 1.12, 24.4, 8.7, 3.3, 1.56, 0.023, 0.50, 0.069}};
 
-// Whole tiles: full rounds, then one that fills part of the chip.  An XCD owns the column tiles x, x + 8, .. (gemm_dp_tile): the
-// one with the most tiles (`busiest`) sets the number of rounds.  whole: the share of the tiles' outputs that exist.
+// Whole tiles: full rounds, then one that fills part of the chip.  The XCD with the most tiles (`busiest`, see gemm_dp_tile) sets the
+// number of rounds.  whole: the share of the tiles' outputs that exist.
 constexpr int kMixedRounds = 12;   // rounds from which the compute units no longer run in step and one's output overlaps another's products
+constexpr int kMixedSteps = 8;     // and k-tiles: shorter ones leave no products to overlap (a layer's weight gradients of 4096, 128 tokens: 128 x 128 tiles 331 us, 256 x 256 371)
 static double large_time(const LargeCost& c, long long tiles, long long busiest, double whole, int nk) {
   const int ncu = compute_units(), per_xcd = ncu >= 8 ? ncu / 8 : 1;
   const long long rounds = (busiest + per_xcd - 1) / per_xcd, left = tiles - (rounds - 1) * ncu;
   const double fill = left >= ncu ? 1.0 : (left > 1 ? (double)left : 1.0) / ncu;
   const double t = c.fixed + (double)(rounds - 1) * (c.step * nk + c.round * whole) + (c.step_alone + (c.step - c.step_alone) * fill) * nk +
                    (c.round_alone + (c.round - c.round_alone) * fill) * whole;
-  return rounds >= kMixedRounds ? 0.95 * t : t;
+  return rounds >= kMixedRounds && nk >= kMixedSteps ? 0.95 * t : t;
 }
-static long long busiest_xcd(long long tiles_m, long long tiles_n) { return tiles_m * ((tiles_n + 7) / 8); }
-
 // A call that is all remainder is split where that promises to be so much faster: the fit is too low for remainders of half a
 // round and more (2048 x 6144 x 12288 whole 241 us, split 256; 2048 x 6400 x 25600 497, 508).  Of the factors 1 to 1.15 the one that
 // loses least over the measured calls (438 us in 839, 464 without).  Behind whole rounds the split pays as

@@ -427,3 +427,18 @@ def test_gemm_mid_tiles(mode, M, N, K):
     # bf16 rounding of the result (2^-9 of its size) plus the fp32 sums' error
     assert bool(((c[:M].double() - want).abs() <= 2.0 ** -8 * want.abs() + 2.0 ** -22 * K).all())
     assert bool((c[M] == 9.0).all())
+
+
+# 256 x 256 tiles: fewer column tiles than XCDs, one more, one less than twice as many; row tiles that fill no group of eight
+@pytest.mark.parametrize("tiles_m,tiles_n", [(1, 1), (9, 7), (3, 9), (17, 15), (1, 23), (8, 18), (5, 12)])
+def test_gemm_column_tiles_dealt_to_xcds(tiles_m, tiles_n):
+    """Every tile is computed once, whatever is left over behind whole column tiles per XCD."""
+    M, N, K = tiles_m * 256 - 8, tiles_n * 256 - 16, 72
+    assert form(B.GEMM_TN, M, N, K, 1, 0) == (256, 256, 1)
+    a, b = randn((K, M), B.BF16, 1), randn((K, N), B.BF16, 2)
+    c = torch.full((M, N), float("nan"), dtype=torch.float32, device="cuda")
+    B.check(B.ptdp_gemm(B.BF16, B.GEMM_TN, a.data_ptr(), b.data_ptr(), c.data_ptr(), None, M, N, K, 1, 0, None, 0, stream()), "gemm")
+    sync()
+    want = a.double().t() @ b.double()
+    # fp32 sums of 72 products of two bf16 numbers
+    assert bool(((c.double() - want).abs() <= 2.0 ** -22 * (a.double().abs().t() @ b.double().abs())).all())
