@@ -1642,6 +1642,7 @@ gemm_bf16_dp_multi_kernel(MultiArgs a) {
       C = a.C[q];
       first = a.start[q];
     }
+  g.bias = nullptr;   // (known here: no sums with it in the output stage)
   gemm_dp_tile<TA, TB, OUT>(g, C, id - first, smem);
 }
 
@@ -1668,6 +1669,7 @@ gemm_bf16_small_multi_kernel(MultiArgs a, ColsumBatchArgs sums, int n_sums) {
       C = a.C[q];
       first = a.start[q];
     }
+  g.bias = nullptr;
   gemm_small_id<TA, TB, OUT, BM, BN, S, KG>(g, C, id - first, smem);
 }
 
