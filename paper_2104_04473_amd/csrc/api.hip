@@ -349,9 +349,10 @@ static int layer_forward(ptdp_chunk* ch, int layer, int64_t microbatch, const vo
                                     (float*)sf(PTDP_STASH_MU2), (float*)sf(PTDP_STASH_RSTD2), T, h, c.ln_eps, st));
   PTDP_TRY(launch_gemm_gelu(c.dtype, c.gelu_mode, sf(PTDP_STASH_U2), P.w_1, P.b_1, sf(PTDP_STASH_Z), sf(PTDP_STASH_G), T, fp, h, sk, skb, st));
   if (!y) return PTDP_OK;
-  PTDP_TRY(launch_gemm(c.dtype, PTDP_GEMM_NN, sf(PTDP_STASH_G), P.w_2, o, nullptr, T, h, fp, 0, 0, sk, skb, st));
   const uint64_t key = dropout_key(c.seed, gl, 1, (uint64_t)microbatch);
-  if (!next) return launch_bda_fwd(c.dtype, o, P.b_2, sf(PTDP_STASH_X1), y, T, h, c.p_hidden, key, st);
+  if (!next)
+    return launch_gemm_bda(c.dtype, sf(PTDP_STASH_G), P.w_2, P.b_2, sf(PTDP_STASH_X1), o, y, c.p_hidden, key, T, h, fp, sk, skb, st);
+  PTDP_TRY(launch_gemm(c.dtype, PTDP_GEMM_NN, sf(PTDP_STASH_G), P.w_2, o, nullptr, T, h, fp, 0, 0, sk, skb, st));
   auto nf = [&](int f) { return (void*)((char*)next + ch->sl.off[f]); };
   const ptdp_layer_params& Q = ch->params[layer + 1];
   return launch_bda_layernorm_fwd(c.dtype, o, P.b_2, sf(PTDP_STASH_X1), y, c.p_hidden, key, Q.ln1_g, Q.ln1_b, nf(PTDP_STASH_U),

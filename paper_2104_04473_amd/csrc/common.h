@@ -228,6 +228,9 @@ int launch_gemm(int dtype, int mode, const void* A, const void* B, void* C, cons
 // the products next to the MLP's GeLU, with it: z = u w, g = GeLU(z + b);  dz = (dg w^T) * GeLU'(z + b), dbias += its column sums
 int launch_gemm_gelu(int dtype, int gelu_mode, const void* u, const void* w, const void* b, void* z, void* g, int M, int N, int K, void* ws,
                      size_t ws_bytes, hipStream_t st);
+// out = resid + Drop(g w + b); o: scratch [M, N]
+int launch_gemm_bda(int dtype, const void* g, const void* w, const void* b, const void* resid, void* o, void* out, float p, uint64_t key, int M, int N,
+                    int K, void* ws, size_t ws_bytes, hipStream_t st);
 int launch_gemm_gelu_bwd(int dtype, int gelu_mode, const void* dg, const void* w, const void* z, const void* b, void* dz, float* dbias,
                          void* scratch, int M, int N, int K, void* ws, size_t ws_bytes, hipStream_t st, ColsumBatch* defer);
 // up to four fp32-accumulating weight gradients C_j += A_j^T B_j with the same K (bf16: one launch); sums: column sums to finish with

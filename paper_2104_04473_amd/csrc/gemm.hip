@@ -57,7 +57,8 @@ constexpr int f32_most_waves(int nb) { return nb == 1 ? 8 : 4; }   // waves that
 
 // What an output stage does beside writing C.  EPI_GELU (NN): C = A B and g = GeLU(C + b).  EPI_GELU_GRAD (NT): C = (A B^T) * GeLU'(z + b), and
 // the column sums of C over blocks of rows to part[block][N].  Both from what a kernel of its own would read: the product as it is stored.
-enum { EPI_PLAIN = 0, EPI_GELU = 1, EPI_GELU_GRAD = 2 };
+// EPI_BDA (NN, bf16): C = z + Drop(A B + b), the residual sum behind the last layer's second MLP product.
+enum { EPI_PLAIN = 0, EPI_GELU = 1, EPI_GELU_GRAD = 2, EPI_BDA = 3 };
 template <int KIND, int MODE = PTDP_GELU_ERF> struct Epi {   // MODE: PTDP_GELU_*
   static constexpr int kKind = KIND, kMode = MODE;
 };
@@ -65,6 +66,9 @@ template <typename T> struct GeluArgs {
   const T *b, *z;
   T* g;
   float* part;
+  uint64_t key;   // EPI_BDA: of the dropout
+  uint32_t thr;
+  float scale;
 };
 // One tile by the workgroup's first kg waves.  SOME: there may be more, which only take part in the end.
 template <bool VA, bool VB, int NB, bool SOME, class EPI>
@@ -869,7 +873,16 @@ __device__ __forceinline__ void gemm_epilogue(const StripAcc<NS, RB>& acc, const
           float f[8], zf[8];
           v.raw = __builtin_bit_cast(uint4, out);
           v.unpack(f);
-          if (EPI::kKind == EPI_GELU) {
+          if (EPI::kKind == EPI_BDA) {
+            bool keep[8];
+            z.raw = __builtin_bit_cast(uint4, zr.v[b][i]);
+            z.unpack(zf);
+            keep_flags<8>(e.key, (uint64_t)(m0 + row[b] + i * 16 + l15) * ldc + (uint64_t)(n0 + c), e.thr, keep);
+#pragma unroll
+            for (int j = 0; j < 8; ++j) zf[j] += keep[j] ? (f[j] + gb[j]) * e.scale : 0.f;
+            v.pack(zf);
+            out = __builtin_bit_cast(u32x4_t, v.raw);
+          } else if (EPI::kKind == EPI_GELU) {
 #pragma unroll
             for (int j = 0; j < 8; ++j) f[j] = gelu_f<EPI::kMode>(f[j] + gb[j]);
             v.pack(f);
@@ -1297,10 +1310,11 @@ __device__ __forceinline__ void gemm_small_tile(const GemmArgs& g, void* Cv, int
   // (bias, GeLU's b: layers of 200 to 2000 tokens 0.2 to 0.9 % faster)
   ColumnAdd<NS, EPI> add;
   GeluRows<NS, RB> z;
-  constexpr bool kAddAhead = EPI::kKind != EPI_GELU_GRAD || NS == 1;   // (128 x 128 tiles with z: 8 registers would spill)
+  constexpr bool kReadsZ = EPI::kKind == EPI_GELU_GRAD || EPI::kKind == EPI_BDA;
+  constexpr bool kAddAhead = !kReadsZ || NS == 1;   // (128 x 128 tiles with z: registers would spill)
   auto load_add = [&] { add.load(OUT != OUT_BF16 ? nullptr : EPI::kKind == EPI_PLAIN ? g.bias : e.b, col, g.N, n0); };
   if (kAddAhead) load_add();
-  if (EPI::kKind == EPI_GELU_GRAD && kg == 0) z.template load<BM, BN>(e.z, row, col, g.ldc, g.M, g.N, m0, n0);
+  if (kReadsZ && kg == 0) z.template load<BM, BN>(e.z, row, col, g.ldc, g.M, g.N, m0, n0);
 #pragma unroll
   for (int i = 0; i < S; ++i) request(i, i);
   StripAcc<NS, RB> acc;
@@ -1616,6 +1630,14 @@ gemm_bf16_small_gelu_kernel(GemmArgs g, void* Cv, GeluArgs<bf16_t> e) {
   gemm_small_id<false, TB, OUT_BF16, BM, BN, S, KG, Epi<TB ? EPI_GELU : EPI_GELU_GRAD, MODE>>(g, Cv, blockIdx.x, smem, e);
 }
 
+// The second MLP product with the residual sum behind it.
+template <int BM, int BN, int S, int KG>
+__global__ void __launch_bounds__(KG * kSmallThreads, 2)
+gemm_bf16_small_bda_kernel(GemmArgs g, void* Cv, GeluArgs<bf16_t> e) {
+  extern __shared__ __attribute__((aligned(1024))) char smem[];
+  gemm_small_id<false, true, OUT_BF16, BM, BN, S, KG, Epi<EPI_BDA>>(g, Cv, blockIdx.x, smem, e);
+}
+
 // Up to four independent problems of the same form in one launch: each later problem's tiles fill the CUs that the
 // last, partial round of the ones before it would leave idle.  start[j] = first workgroup index of problem j
 // (multiples of 8, so that every problem starts on XCD 0), start[n] = grid size.
@@ -1794,6 +1816,15 @@ static int launch_small(const GemmArgs& g, void* C, hipStream_t st) {
   if (set_dynamic_smem(reinterpret_cast<const void*>(kern), smem, done) != PTDP_OK) return PTDP_E_HIP;
   const int blocks = small_blocks<BM, BN>(g.M, g.N);
   hipLaunchKernelGGL(kern, dim3(blocks), dim3(KG * kSmallThreads), smem, st, g, C);
+  return PTDP_OK;
+}
+template <int BM, int BN, int S, int KG>
+static int launch_small_bda(const GemmArgs& g, void* C, const GeluArgs<bf16_t>& e, hipStream_t st) {
+  auto kern = gemm_bf16_small_bda_kernel<BM, BN, S, KG>;
+  static once_flag_t done[kMaxDevices];
+  constexpr int smem = SmallGeom<BM, BN, S, KG>::kSmem;
+  if (set_dynamic_smem(reinterpret_cast<const void*>(kern), smem, done) != PTDP_OK) return PTDP_E_HIP;
+  hipLaunchKernelGGL(kern, dim3(small_blocks<BM, BN>(g.M, g.N)), dim3(KG * kSmallThreads), smem, st, g, C, e);
   return PTDP_OK;
 }
 template <bool TB, int MODE, int BM, int BN, int S, int KG>
@@ -2315,14 +2346,39 @@ int launch_gemm_gelu(int dtype, int gelu_mode, const void* u, const void* w, con
   Launch L(PTDP_K_GEMM_NN, 2.0 * M * N * K, st);
   int rc;
   if (dtype == PTDP_BF16) {
-    const GeluArgs<bf16_t> e{(const bf16_t*)b, nullptr, (bf16_t*)g, nullptr};
+    const GeluArgs<bf16_t> e{(const bf16_t*)b, nullptr, (bf16_t*)g, nullptr, 0, 0, 0.f};
     const GemmArgs a = bf16_args<false, true>(u, w, nullptr, M, N, K);
     rc = tanh ? launch_small_gelu_form<true, PTDP_GELU_TANH>(form, a, z, e, st) : launch_small_gelu_form<true, PTDP_GELU_ERF>(form, a, z, e, st);
   } else {
-    const GeluArgs<float> e{(const float*)b, nullptr, (float*)g, nullptr};
+    const GeluArgs<float> e{(const float*)b, nullptr, (float*)g, nullptr, 0, 0, 0.f};
     const float *A = (const float*)u, *B = (const float*)w;
     rc = tanh ? launch_gemm_f32<true, false, Epi<EPI_GELU, PTDP_GELU_TANH>>(A, B, (float*)z, nullptr, M, N, K, K, 1, N, 1, 0, st, e)
               : launch_gemm_f32<true, false, Epi<EPI_GELU, PTDP_GELU_ERF>>(A, B, (float*)z, nullptr, M, N, K, K, 1, N, 1, 0, st, e);
+  }
+  return rc != PTDP_OK ? rc : L.status();
+}
+
+// out[M,N] = resid + Drop(g[M,K] w[K,N] + b); o[M,N]: scratch for the product where the sum is a kernel of its own.  Speed of a pass against that
+// everywhere: eight layers of 1024 x 2048 over two shards, one at a time, 1.010; two of 2048 x 1024 under a mask 1.012, of 666 x 512 1.005.
+int launch_gemm_bda(int dtype, const void* g, const void* w, const void* b, const void* resid, void* o, void* out, float p, uint64_t key, int M, int N,
+                    int K, void* ws, size_t ws_bytes, hipStream_t st) {
+  if (M == 0 || N == 0) return PTDP_OK;
+  const int form = dtype == PTDP_BF16 ? gelu_form(PTDP_GEMM_NN, M, N, K, ws ? ws_bytes : 0) : -1;
+  if (form < 0) {
+    const int rc = launch_gemm(dtype, PTDP_GEMM_NN, g, w, o, nullptr, M, N, K, 0, 0, ws, ws_bytes, st);
+    return rc != PTDP_OK ? rc : launch_bda_fwd(dtype, o, b, resid, out, M, N, p, key, st);
+  }
+  Launch L(PTDP_K_GEMM_NN, 2.0 * M * N * K, st);
+  const GemmArgs a = bf16_args<false, true>(g, w, nullptr, M, N, K);
+  const GeluArgs<bf16_t> e{(const bf16_t*)b, (const bf16_t*)resid, nullptr, nullptr, key, p > 0.f ? dropout_threshold(p) : 0u, 1.0f / (1.0f - p)};
+  int rc;
+  switch (form) {
+    case 0: rc = launch_small_bda<128, 128, 2, 1>(a, out, e, st); break;
+    case 1: rc = launch_small_bda<128, 128, 2, 2>(a, out, e, st); break;
+    case 2: rc = launch_small_bda<128, 64, 3, 2>(a, out, e, st); break;
+    case 3: rc = launch_small_bda<64, 64, 4, 2>(a, out, e, st); break;
+    case 4: rc = launch_small_bda<128, 64, 2, 1>(a, out, e, st); break;
+    default: rc = PTDP_E_STATE;   // gelu_form offers no other
   }
   return rc != PTDP_OK ? rc : L.status();
 }
@@ -2344,12 +2400,12 @@ int launch_gemm_gelu_bwd(int dtype, int gelu_mode, const void* dg, const void* w
     int rc;
     if (dtype == PTDP_BF16) {
       rows = kSmallCost[0][form].bm / 2;
-      const GeluArgs<bf16_t> e{(const bf16_t*)b, (const bf16_t*)z, nullptr, (float*)scratch};
+      const GeluArgs<bf16_t> e{(const bf16_t*)b, (const bf16_t*)z, nullptr, (float*)scratch, 0, 0, 0.f};
       const GemmArgs a = bf16_args<false, false>(dg, w, nullptr, M, N, K);
       rc = tanh ? launch_small_gelu_form<false, PTDP_GELU_TANH>(form, a, dz, e, st) : launch_small_gelu_form<false, PTDP_GELU_ERF>(form, a, dz, e, st);
     } else {
       rows = f32.tile;
-      const GeluArgs<float> e{(const float*)b, (const float*)z, nullptr, (float*)scratch};
+      const GeluArgs<float> e{(const float*)b, (const float*)z, nullptr, (float*)scratch, 0, 0, 0.f};
       const float *A = (const float*)dg, *B = (const float*)w;
       rc = tanh ? launch_gemm_f32<true, true, Epi<EPI_GELU_GRAD, PTDP_GELU_TANH>>(A, B, (float*)dz, nullptr, M, N, K, K, 1, 1, K, 0, st, e)
                 : launch_gemm_f32<true, true, Epi<EPI_GELU_GRAD, PTDP_GELU_ERF>>(A, B, (float*)dz, nullptr, M, N, K, K, 1, 1, K, 0, st, e);

@@ -333,3 +333,28 @@ def test_gelu_in_the_products_beside_it(h, a, t, s, b, dtype, gelu, tile):
     # two fp32 sums of T terms in different orders: relative to the sum of the terms' sizes, below T * 2^-24 (here far below)
     lim = T * 2.0 ** -24 * (got_dz.double().abs().sum(0) + 0.25)
     assert ((rig.grads[0]["b_1"].double() - db.double()).abs() <= lim).all()
+
+
+# every small form, rows that fill no tile, no dropout; 256 x 256 tiles and fp32 (a kernel of its own)
+@pytest.mark.parametrize("h,a,t,s,b,dtype,p,tile", [
+    (768, 12, 1, 41, 8, B.BF16, 0.1, (64, 64, 2)), (64, 2, 1, 8, 1, B.BF16, 0.1, (128, 64, 1)), (96, 3, 1, 8, 5, B.BF16, 0.0, (128, 64, 1)),
+    (512, 8, 1, 1500, 2, B.BF16, 0.1, (128, 64, 2)), (1536, 12, 4, 1500, 2, B.BF16, 0.25, (128, 128, 1)), (768, 12, 2, 600, 5, B.BF16, 0.1, (128, 128, 2)),
+    (2048, 16, 1, 1000, 2, B.BF16, 0.1, (256, 256, 1)), (128, 2, 1, 37, 1, B.F32, 0.1, None),
+])
+def test_residual_sum_in_the_last_product(h, a, t, s, b, dtype, p, tile):
+    """The last layer's residual sum in the output stage of its second MLP product: the bits of a product and a sum in calls of their own."""
+    cfg = B.make_cfg(h=h, a=a, t=t, s=s, b=b, dtype=dtype, p_hidden=p, seed=9)
+    rig, T, f = LayerRig(cfg, n_layers=2, first_layer=4), s * b, 4 * h // t
+    n = B.ptdp_gemm_workspace_bytes() if dtype == B.BF16 else 0
+    if tile:
+        got = [C.c_int() for _ in range(3)]
+        B.check(B.ptdp_gemm_form(0, T, h, f, 0, 0, 0, n, *[C.byref(x) for x in got]), "form")
+        assert tuple(x.value for x in got) == tile
+    x, y = randn((s, b, h), dtype, 1), torch.empty((s, b, h), dtype=tdt(dtype), device="cuda")
+    B.check(rig.chunk.forward(2, x.data_ptr(), y.data_ptr(), rig.stash.data_ptr(), rig.ws.data_ptr()), "forward")
+    o, want, ws, P = torch.empty_like(y), torch.empty_like(y), dev_bytes(n), rig.params[1]
+    B.check(B.ptdp_gemm(dtype, 0, rig.field(1, "G", (T, f)).data_ptr(), P["w_2"].data_ptr(), o.data_ptr(), None, T, h, f, 0, 0, ws.data_ptr(), n, stream()), "gemm")
+    B.check(B.ptdp_bias_dropout_add_fwd(dtype, o.data_ptr(), P["b_2"].data_ptr(), rig.field(1, "X1", (T, h)).data_ptr(), want.data_ptr(), T, h, p, 9, 5, 1, 2,
+                                        stream()), "sum")
+    sync()
+    assert torch.equal(y, want)
