@@ -1311,8 +1311,8 @@ __device__ __forceinline__ void gemm_small_tile(const GemmArgs& g, void* Cv, int
   ColumnAdd<NS, EPI> add;
   GeluRows<NS, RB> z;
   constexpr bool kReadsZ = EPI::kKind == EPI_GELU_GRAD || EPI::kKind == EPI_BDA;
-  constexpr bool kAddAhead = !kReadsZ || NS == 1;   // (128 x 128 tiles with z: registers would spill)
-  auto load_add = [&] { add.load(OUT != OUT_BF16 ? nullptr : EPI::kKind == EPI_PLAIN ? g.bias : e.b, col, g.N, n0); };
+  constexpr bool kAddAhead = OUT == OUT_BF16 && (!kReadsZ || NS == 1);   // (128 x 128 tiles with z: registers would spill; += : a bias is rare)
+  auto load_add = [&] { add.load(EPI::kKind == EPI_PLAIN ? g.bias : e.b, col, g.N, n0); };
   if (kAddAhead) load_add();
   if (kReadsZ && kg == 0) z.template load<BM, BN>(e.z, row, col, g.ldc, g.M, g.N, m0, n0);
 #pragma unroll

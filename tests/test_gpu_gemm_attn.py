@@ -113,6 +113,21 @@ def test_gemm_small_tiles(mode, tile, M, N, K):
         assert bool(((c.double() - want).abs() <= 2.0 ** -8 * want.abs() + 2.0 ** -22 * K).all())
 
 
+@pytest.mark.parametrize("tile,M,N,K", [(tile, *shapes[0]) for tile, shapes in SMALL_FORMS.items() if tile] +
+                         [((64, 64, 2), 328, 992, 2048), ((128, 128, 1), 2048, 6144, 512), ((256, 256, 1), 4096, 4096, 2048)])
+def test_gemm_bias_of_an_accumulated_product(tile, M, N, K):
+    """+= with a bias adds it too, in every form, with rows of C that are whole lines and not."""
+    assert form(B.GEMM_TN, M, N, K, 1, 1, 1) == tile
+    a, b, bias = randn((K, M), B.BF16, 1), randn((K, N), B.BF16, 2), randn((N,), B.BF16, 3)
+    acc = torch.full((M, N), 0.5, dtype=torch.float32, device="cuda")
+    for _ in range(2):
+        B.check(B.ptdp_gemm(B.BF16, B.GEMM_TN, a.data_ptr(), b.data_ptr(), acc.data_ptr(), bias.data_ptr(), M, N, K, 1, 1, None, 0, stream()), "gemm")
+    sync()
+    # fp32 sums of K products with partial sums of size sqrt(K), as above
+    want = a.double().t() @ b.double() + bias.double()
+    assert float((acc.double() - 0.5 - 2 * want).abs().max()) <= 2 * 2.0 ** -22 * K
+
+
 # 256 x 128 tiles: whole tiles, a few rows or columns in the last one, k-tiles per group of waves odd and even, the last one whole,
 # partial and missing, requests in the lean form up to the end and not
 WIDE_TILES = [(2048, 4096, 3072), (2040, 4088, 4104), (1000, 7656, 4168), (264, 16376, 1544), (264, 16376, 1736), (520, 10248, 1920 - 8)]
