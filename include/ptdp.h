@@ -402,24 +402,27 @@ enum { PTDP_GEMM_NN = 0, PTDP_GEMM_NT = 1, PTDP_GEMM_TN = 2 };
 int ptdp_gemm(int dtype, int mode, const void* A, const void* B, void* C, const void* bias, int M, int N,
               int K, int out_f32, int accumulate, void* workspace, size_t workspace_bytes, void* stream);
 size_t ptdp_gemm_workspace_bytes(void);
-/* Host only (no device work): how ptdp_gemm cuts a bf16 call (appendix: the
- * GEMMs of a layer).  *dp_columns = columns of C computed in whole rounds, one
+/* Host only (no device work): how ptdp_gemm(mode, ...) cuts a bf16 call (appendix:
+ * the GEMMs of a layer).  *dp_columns = columns of C computed in whole rounds, one
  * workgroup per 256 x 256 tile (a multiple of 256, or N when nothing is split).
  * The remaining tiles, numbered row tile fastest, form *n_groups (0..2)
  * consecutive groups: group j has group_tiles[j] tiles and gives each of them to
  * group_parts[j] workgroups, part p of which takes the 64-wide k-steps
  * [nk*p/parts, nk*(p+1)/parts) of that tile; tiles x parts never exceeds the
  * number of compute units.  group_tiles / group_parts: two ints each.
- * Calls with so few 256 x 256 tiles that smaller ones are faster split nothing:
- * *dp_columns = N, *n_groups = 0.  (out_f32 = 0: an NN or NT call, 1: a TN call.)
+ * Calls that take smaller tiles (ptdp_gemm_form) split nothing: *dp_columns = N,
+ * *n_groups = 0; NN and NT calls of one size may differ in that.
  * has_bias / workspace_bytes as in the call being planned.  Returns 0, or
  * PTDP_E_INVALID_ARG / PTDP_E_NULL_PTR. */
+int ptdp_gemm_mode_plan(int mode, int M, int N, int K, int out_f32, int accumulate, int has_bias, size_t workspace_bytes,
+                        int* dp_columns, int* n_groups, int* group_tiles, int* group_parts);
+/* The same of an NN call (out_f32 = 0) or a TN call (out_f32 = 1). */
 int ptdp_gemm_plan(int M, int N, int K, int out_f32, int accumulate, int has_bias, size_t workspace_bytes,
                    int* dp_columns, int* n_groups, int* group_tiles, int* group_parts);
 
 /* Host only: the tiles of the bf16 call ptdp_gemm(mode, ...) with these arguments.  A workgroup computes *tile_m x *tile_n
  * outputs; with *wave_groups = 2 two groups of its waves take alternate 64-wide k-steps and their sums are added at the
- * end.  256, 256, 1 for the calls that ptdp_gemm_plan describes.  Returns 0, PTDP_E_INVALID_ARG or PTDP_E_NULL_PTR. */
+ * end.  256, 256, 1 for the calls that ptdp_gemm_mode_plan describes.  Returns 0, PTDP_E_INVALID_ARG or PTDP_E_NULL_PTR. */
 int ptdp_gemm_form(int mode, int M, int N, int K, int out_f32, int accumulate, int has_bias, size_t workspace_bytes,
                    int* tile_m, int* tile_n, int* wave_groups);
 

@@ -853,14 +853,20 @@ size_t ptdp_layernorm_bwd_scratch_bytes(int rows, int width) { return layernorm_
 
 size_t ptdp_gemm_workspace_bytes(void) { return gemm_workspace_bytes(); }
 
-int ptdp_gemm_plan(int M, int N, int K, int out_f32, int accumulate, int has_bias, size_t workspace_bytes,
-                   int* dp_columns, int* n_groups, int* group_tiles, int* group_parts) {
+int ptdp_gemm_mode_plan(int mode, int M, int N, int K, int out_f32, int accumulate, int has_bias, size_t workspace_bytes,
+                        int* dp_columns, int* n_groups, int* group_tiles, int* group_parts) {
   if (!dp_columns || !n_groups || !group_tiles || !group_parts) return PTDP_E_NULL_PTR;
-  if (M <= 0 || N <= 0 || K <= 0 || M % 8 || N % 8 || K % 8) return PTDP_E_INVALID_ARG;
+  if (mode < PTDP_GEMM_NN || mode > PTDP_GEMM_TN || M <= 0 || N <= 0 || K <= 0 || M % 8 || N % 8 || K % 8) return PTDP_E_INVALID_ARG;
   int cols = 0;
-  gemm_plan_query(M, N, K, out_f32, accumulate, has_bias, workspace_bytes, &cols, n_groups, group_tiles, group_parts);
+  gemm_plan_query(mode, M, N, K, out_f32, accumulate, has_bias, workspace_bytes, &cols, n_groups, group_tiles, group_parts);
   *dp_columns = cols < (N + 255) / 256 ? cols * 256 : N;
   return PTDP_OK;
+}
+
+int ptdp_gemm_plan(int M, int N, int K, int out_f32, int accumulate, int has_bias, size_t workspace_bytes,
+                   int* dp_columns, int* n_groups, int* group_tiles, int* group_parts) {
+  return ptdp_gemm_mode_plan(out_f32 ? PTDP_GEMM_TN : PTDP_GEMM_NN, M, N, K, out_f32, accumulate, has_bias, workspace_bytes, dp_columns, n_groups,
+                             group_tiles, group_parts);
 }
 
 int ptdp_gemm_form(int mode, int M, int N, int K, int out_f32, int accumulate, int has_bias, size_t workspace_bytes, int* tile_m,

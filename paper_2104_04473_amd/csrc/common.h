@@ -218,7 +218,7 @@ int launch_colsum(int dtype, const void* in, float* out, void* scratch, int rows
 size_t gemm_workspace_bytes();
 // how a bf16 call is cut (host only): column tiles computed in whole rounds, then up to two groups of remainder
 // tiles, group j giving each of its tiles[j] tiles to parts[j] workgroups that split the k range evenly
-void gemm_plan_query(int M, int N, int K, int out_f32, int accumulate, int has_bias, size_t ws_bytes, int* dp_cols,
+void gemm_plan_query(int mode, int M, int N, int K, int out_f32, int accumulate, int has_bias, size_t ws_bytes, int* dp_cols,
                      int* n_groups, int* tiles, int* parts);
 // the tile of a bf16 call's workgroups and how many wave groups share its k range (host only)
 void gemm_form_query(int mode, int M, int N, int K, int out_f32, int accumulate, int has_bias, size_t ws_bytes, int* tile_m,

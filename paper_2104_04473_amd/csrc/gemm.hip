@@ -2087,11 +2087,11 @@ static int choose_form(int mode, int M, int N, int K, int out_f32, int accumulat
   return mid && !rmw && K > kMidShort && rows > kBM && 4 * (long long)M >= 3ll * rows && mid_time(mode, M, N, K) * kMidMargin < t ? kMidForm : form;
 }
 
-void gemm_plan_query(int M, int N, int K, int out_f32, int accumulate, int has_bias, size_t ws_bytes, int* dp_cols,
+void gemm_plan_query(int mode, int M, int N, int K, int out_f32, int accumulate, int has_bias, size_t ws_bytes, int* dp_cols,
                      int* n_groups, int* tiles, int* parts) {
   SplitPlan P;
-  if (choose_form(out_f32 ? PTDP_GEMM_TN : PTDP_GEMM_NN, M, N, K, out_f32, accumulate, has_bias, ws_bytes, &P) >= 0) {
-    P.dp_cols = (N + kBN - 1) / kBN;   // small tiles: nothing is split
+  if (choose_form(mode, M, N, K, out_f32, accumulate, has_bias, ws_bytes, &P) >= 0) {
+    P.dp_cols = (N + kBN - 1) / kBN;   // other tiles: nothing is split
     P.n_groups = 0;
   }
   *dp_cols = P.dp_cols;

@@ -19,11 +19,11 @@ def form(mode, M, N, K, out_f32, accumulate, has_bias=0, ws_bytes=0):
     return tuple(x.value for x in v)
 
 
-def split_groups(M, N, K, out_f32, accumulate, has_bias):
+def split_groups(mode, M, N, K, out_f32, accumulate, has_bias):
     cols, n = C.c_int(), C.c_int()
     tiles, parts = (C.c_int * 2)(), (C.c_int * 2)()
-    B.check(B.ptdp_gemm_plan(M, N, K, out_f32, accumulate, has_bias, B.ptdp_gemm_workspace_bytes(), C.byref(cols), C.byref(n), tiles,
-                             parts), "plan")
+    B.check(B.ptdp_gemm_mode_plan(mode, M, N, K, out_f32, accumulate, has_bias, B.ptdp_gemm_workspace_bytes(), C.byref(cols), C.byref(n), tiles,
+                                  parts), "plan")
     return n.value
 
 
@@ -258,9 +258,9 @@ SPLIT_SHAPES = [(2128, 64, 10976, True), (136, 10928, 7400, True), (536, 3592, 1
 def test_gemm_split_along_k(mode, M, N, K, split):
     """Tile counts that do not fill the compute units: the remaining tiles are split along k through the
     workspace and reduced in a fixed order (bf16 output, or += into the fp32 accumulator)."""
-    if split:   # bf16 output with a bias, and +=, in every mode (the plan of += is that of TN)
+    if split:   # bf16 output with a bias, and +=, in every mode
         for out_f32 in (0, 1):
-            assert split_groups(M, N, K, out_f32, out_f32, 1 - out_f32) > 0
+            assert split_groups(mode, M, N, K, out_f32, out_f32, 1 - out_f32) > 0
             assert form(mode, M, N, K, out_f32, out_f32, 1 - out_f32, B.ptdp_gemm_workspace_bytes()) == (256, 256, 1)
     dtype = B.BF16
     a = randn((M, K), dtype, 1)

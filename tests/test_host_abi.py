@@ -169,6 +169,13 @@ def _plan(M, N, K, out_f32=0, accumulate=0, has_bias=0, ws=None):
     return d.value, [(tiles[j], parts[j]) for j in range(n.value)]
 
 
+def _mode_plan(mode, M, N, K, out_f32=0, accumulate=0, has_bias=0):
+    d, n = C.c_int(0), C.c_int(0)
+    tiles, parts = (C.c_int * 2)(), (C.c_int * 2)()
+    assert B.ptdp_gemm_mode_plan(mode, M, N, K, out_f32, accumulate, has_bias, B.ptdp_gemm_workspace_bytes(), C.byref(d), C.byref(n), tiles, parts) == B.OK
+    return d.value, [(tiles[j], parts[j]) for j in range(n.value)]
+
+
 def test_gemm_remainder_split_covers_every_tile_and_k_step_once():
     """Tiles beyond the whole rounds go to at most two groups; every tile of a group is shared by `parts`
     workgroups with contiguous, disjoint k-ranges: replay that arithmetic on the host, also for shapes whose
@@ -236,6 +243,26 @@ def test_gemm_form_errors_and_agreement_with_the_plan():
         assert B.ptdp_gemm_form(B.GEMM_NN, M, N, K, 0, 0, 0, ws, *ref) == B.OK
         whole = [x.value for x in v] == [256, 256, 1]
         assert whole or _plan(M, N, K) == (N, []), (M, N, K)      # only 256 x 256 tiles are ever split
+
+
+def test_gemm_plan_of_each_mode_agrees_with_the_form():
+    """A call that takes smaller tiles than 256 x 256 splits nothing, in its own mode: of the first four shapes the NN
+    call is split along k and the NT call takes 256 x 192 tiles."""
+    d, n, two, v = C.c_int(-1), C.c_int(-1), (C.c_int * 2)(-1, -1), [C.c_int(-1) for _ in range(3)]
+    for mode in (-1, 3):
+        assert B.ptdp_gemm_mode_plan(mode, 8, 8, 8, 0, 0, 0, 0, C.byref(d), C.byref(n), two, two) == B.E_INVALID_ARG
+    assert B.ptdp_gemm_mode_plan(B.GEMM_NT, 8, 8, 8, 0, 0, 0, 0, C.byref(d), C.byref(n), two, None) == B.E_NULL_PTR
+    assert (d.value, n.value, list(two)) == (-1, -1, [-1, -1])
+    ws, differ = B.ptdp_gemm_workspace_bytes(), 0
+    for M, N, K in ((2048, 12288, 4608), (1016, 18664, 2800), (800, 20376, 3312), (904, 21688, 3360), (160, 232, 216), (64, 3160, 14928),
+                    (2048, 12800, 25600), (8192, 8192, 8192), (1024, 2048, 1024), (1000, 10240, 5120), (2048, 6144, 12288)):
+        for mode, out_f32 in ((B.GEMM_NN, 0), (B.GEMM_NT, 0), (B.GEMM_TN, 1), (B.GEMM_NT, 1), (B.GEMM_TN, 0)):
+            assert B.ptdp_gemm_form(mode, M, N, K, out_f32, out_f32, 0, ws, *[C.byref(x) for x in v]) == B.OK
+            whole = [x.value for x in v] == [256, 256, 1]
+            assert whole or _mode_plan(mode, M, N, K, out_f32, out_f32) == (N, []), (mode, M, N, K)
+        assert _mode_plan(B.GEMM_NN, M, N, K) == _plan(M, N, K) and _mode_plan(B.GEMM_TN, M, N, K, 1, 1) == _plan(M, N, K, 1, 1)
+        differ += _mode_plan(B.GEMM_NT, M, N, K) != _plan(M, N, K)
+    assert differ > 0
 
 
 def _attn_form(kernel, causal, s, b, heads, dh, masked=0):
