@@ -2358,12 +2358,23 @@ int launch_gemm_gelu(int dtype, int gelu_mode, const void* u, const void* w, con
   return rc != PTDP_OK ? rc : L.status();
 }
 
+// The form of that product with the residual sum, or -1 for a kernel of its own.  Where another layer follows the product is launch_gemm's, and
+// a recomputed layer may be the last of its segment: both must add k in the same order.  Tiles of any size do, as long as the same number
+// of wave groups shares the k range.
+static int bda_form(int M, int N, int K, size_t ws_bytes) {
+  const int form = gelu_form(PTDP_GEMM_NN, M, N, K, ws_bytes);
+  if (form < 0) return -1;
+  SplitPlan P;
+  const int alone = choose_form(PTDP_GEMM_NN, M, N, K, 0, 0, 0, ws_bytes, &P);
+  return alone >= 0 && kSmallCost[0][alone].groups == kSmallCost[0][form].groups ? form : -1;
+}
+
 // out[M,N] = resid + Drop(g[M,K] w[K,N] + b); o[M,N]: scratch for the product where the sum is a kernel of its own.  Speed of a pass against that
 // everywhere: eight layers of 1024 x 2048 over two shards, one at a time, 1.010; two of 2048 x 1024 under a mask 1.012, of 666 x 512 1.005.
 int launch_gemm_bda(int dtype, const void* g, const void* w, const void* b, const void* resid, void* o, void* out, float p, uint64_t key, int M, int N,
                     int K, void* ws, size_t ws_bytes, hipStream_t st) {
   if (M == 0 || N == 0) return PTDP_OK;
-  const int form = dtype == PTDP_BF16 ? gelu_form(PTDP_GEMM_NN, M, N, K, ws ? ws_bytes : 0) : -1;
+  const int form = dtype == PTDP_BF16 ? bda_form(M, N, K, ws ? ws_bytes : 0) : -1;
   if (form < 0) {
     const int rc = launch_gemm(dtype, PTDP_GEMM_NN, g, w, o, nullptr, M, N, K, 0, 0, ws, ws_bytes, st);
     return rc != PTDP_OK ? rc : launch_bda_fwd(dtype, o, b, resid, out, M, N, p, key, st);

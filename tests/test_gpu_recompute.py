@@ -81,6 +81,24 @@ def test_chunk_recompute_matches_plain_path_and_oracle(dtype, n, seg):
         assert_close(np64(got), ck[sg], dtype, "checkpoint %d" % sg)
 
 
+def test_recompute_where_the_last_product_takes_another_form():
+    """A last layer has its residual sum in its second MLP product (128 x 128 tiles here), one that another layer follows a product of its
+    own (256 x 192): the same bits."""
+    cfg = B.make_cfg(h=3648, a=114, t=6, s=561, b=8, dtype=B.BF16, p_hidden=0.1, seed=9)
+    v = [C.c_int() for _ in range(3)]
+    B.check(B.ptdp_gemm_form(B.GEMM_NN, 561 * 8, 3648, 2432, 0, 0, 0, B.ptdp_gemm_workspace_bytes(), *[C.byref(x) for x in v]), "form")
+    assert [x.value for x in v] == [256, 192, 1]
+    rig = LayerRig(cfg, 2, seed=70)
+    x = randn((cfg.s, cfg.b, cfg.h), B.BF16, 1)
+    y0, y1 = torch.empty_like(x), torch.empty_like(x)
+    B.check(rig.chunk.forward(0, x.data_ptr(), y0.data_ptr(), rig.stash.data_ptr(), rig.ws.data_ptr()), "fwd")
+    n_ck = B.ptdp_chunk_n_checkpoints(rig.chunk.handle, 1)
+    ckpt, seg_stash = dev_bytes(n_ck * B.ptdp_checkpoint_bytes(C.byref(cfg))), dev_bytes(rig.layer_stash_bytes)
+    B.check(rig.chunk.forward_ckpt(0, x.data_ptr(), y1.data_ptr(), ckpt.data_ptr(), 1, seg_stash.data_ptr(), rig.ws.data_ptr()), "fwd_ckpt")
+    sync()
+    assert torch.equal(y0, y1)
+
+
 def test_recompute_argument_errors():
     cfg = B.make_cfg(h=256, a=4, t=1, s=16, b=1, dtype=B.BF16)
     rig = LayerRig(cfg, 2)
