@@ -1607,6 +1607,10 @@ gemm_bf16_mid_kernel(GemmArgs g, void* Cv) {
 
 // Tiles are numbered in groups of 8 row tiles, column by column inside a group; each XCD takes one contiguous run, so
 // that its workgroups share operand panels through its L2.
+// TN: where these runs begin at whole or half groups, all XCDs would start in the same one or two columns, a power of two of rows apart, and
+// C (read and written) would come from few memory channels at a time: each group starts an eighth of the columns further.  us for the backward
+// of a layer of 8192 over four shards, 200 tokens: 650 -> 583, of 4096, 200 tokens, 582 -> 564, of 4096 over two shards, 1024 tokens, 622 -> 589;
+// where the runs begin at other places it would change nothing or cost 1 % (5120, 200 tokens).
 template <int BM, int BN> static inline int small_blocks(int M, int N) { return 8 * ((((M + BM - 1) / BM) * ((N + BN - 1) / BN) + 7) / 8); }
 template <bool TA, bool TB, int OUT, int BM, int BN, int S, int KG, class EPI = Epi<EPI_PLAIN>>
 __device__ __forceinline__ void gemm_small_id(const GemmArgs& g, void* Cv, int id, char* smem, const GeluArgs<bf16_t>& e = {}) {
@@ -1614,7 +1618,9 @@ __device__ __forceinline__ void gemm_small_id(const GemmArgs& g, void* Cv, int i
   const int per_xcd = (tiles + 7) / 8, t = (id & 7) * per_xcd + (id >> 3);
   if ((id >> 3) >= per_xcd || t >= tiles) return;
   const int grp = t / (8 * tiles_n), in_grp = t - grp * 8 * tiles_n, gm = min(8, tiles_m - grp * 8);
-  gemm_small_tile<TA, TB, OUT, BM, BN, S, KG, EPI>(g, Cv, (grp * 8 + in_grp % gm) * BM, (in_grp / gm) * BN, smem, e);
+  int tile_n = in_grp / gm;
+  if (TA && per_xcd % (4 * tiles_n) == 0) tile_n = (tile_n + (grp & 7) * ((tiles_n + 7) / 8)) % tiles_n;
+  gemm_small_tile<TA, TB, OUT, BM, BN, S, KG, EPI>(g, Cv, (grp * 8 + in_grp % gm) * BM, tile_n * BN, smem, e);
 }
 template <bool TA, bool TB, int OUT, int BM, int BN, int S, int KG>
 __global__ void __launch_bounds__(KG * kSmallThreads, 2)

@@ -128,6 +128,22 @@ def test_gemm_bias_of_an_accumulated_product(tile, M, N, K):
     assert float((acc.double() - 0.5 - 2 * want).abs().max()) <= 2 * 2.0 ** -22 * K
 
 
+# runs of tiles of an XCD that begin at whole groups of 8 row tiles, at half groups and elsewhere; the last group whole and not; one column tile and more
+@pytest.mark.parametrize("M,N,K", [(2048, 64, 1032), (1984, 200, 1032), (2040, 456, 1032), (4096, 520, 1032), (4096, 1096, 200), (8184, 1096, 200),
+                                   (4096, 328, 2056), (1024, 520, 1032), (12288, 392, 72)])
+def test_gemm_small_tiles_start_at_other_columns(M, N, K):
+    """Every tile of an accumulated product is computed once, wherever its group begins."""
+    tile = form(B.GEMM_TN, M, N, K, 1, 1)
+    assert tile != (256, 256, 1)
+    a, b = randn((K, M), B.BF16, 1), randn((K, N), B.BF16, 2)
+    c = torch.full((M + 1, N), 0.5, dtype=torch.float32, device="cuda")
+    B.check(B.ptdp_gemm(B.BF16, B.GEMM_TN, a.data_ptr(), b.data_ptr(), c.data_ptr(), None, M, N, K, 1, 1, None, 0, stream()), "gemm")
+    sync()
+    # fp32 sums of K products with partial sums of size sqrt(K), as for the small tiles
+    assert float((c[:M].double() - 0.5 - a.double().t() @ b.double()).abs().max()) <= 2.0 ** -22 * K
+    assert bool((c[M] == 0.5).all())
+
+
 # 256 x 128 tiles: whole tiles, a few rows or columns in the last one, k-tiles per group of waves odd and even, the last one whole,
 # partial and missing, requests in the lean form up to the end and not
 WIDE_TILES = [(2048, 4096, 3072), (2040, 4088, 4104), (1000, 7656, 4168), (264, 16376, 1544), (264, 16376, 1736), (520, 10248, 1920 - 8)]
