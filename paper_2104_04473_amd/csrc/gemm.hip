@@ -357,7 +357,10 @@ static int launch_gemm_f32(const float* A, const float* B, float* C, const float
                          K, a_rs, a_cs, b_rs, b_cs, accumulate, e);
     return PTDP_OK;
   }
-  if (f.tile == 64) return launch_gemm_f32_t<VA, VB, 2, EPI>(A, B, C, bias, M, N, K, a_rs, a_cs, b_rs, b_cs, accumulate, f.kg, st, e);
+  if (f.tile == 64) {
+    if constexpr (EPI::kKind != EPI_PLAIN) return PTDP_E_STATE;
+    else return launch_gemm_f32_t<VA, VB, 2>(A, B, C, bias, M, N, K, a_rs, a_cs, b_rs, b_cs, accumulate, f.kg, st);
+  }
   return launch_gemm_f32_t<VA, VB, 1, EPI>(A, B, C, bias, M, N, K, a_rs, a_cs, b_rs, b_cs, accumulate, f.kg, st, e);
 }
 
@@ -2327,7 +2330,9 @@ int launch_gemm(int dtype, int mode, const void* A, const void* B, void* C, cons
 
 // The two products next to the MLP's GeLU, with it in their output stage where the call takes small tiles (or is fp32): what a kernel of its
 // own costs there is a launch and a trip of the product through memory, while a tile's 25 vector instructions per element are spread over
-// most of the chip.  With 256 x 256 tiles they would run with nothing beside them, 15 us a tile: see launch_bias_gelu_*.  Speed of a pass
+// most of the chip.  With 256 x 256 tiles they would run with nothing beside them, 15 us a tile: see launch_bias_gelu_*.  So they do in fp32
+// with 64 x 64 tiles, where a thread also reads z at sixteen places one after the other: us for forward and backward of a layer of 640, 1392
+// tokens, 335 and 674 there, 327 and 652 in kernels of their own; of 1024, 2048 tokens, 721 and 1690, 704 and 1640.  Speed of a pass
 // against kernels of their own: one fp32 layer of 256 x 256 1.030, two of 666 x 512 1.043, of 2048 x 1024 under a mask 1.016, eight of 1024 x
 // 2048 over two shards 1.020; two of 4096 x 256 1.03, of 8192 x 512 1.00.  z requested behind the k loop instead of in front of it: 1.027,
 // 1.028, 1.003, 1.004 of the first four.
@@ -2344,7 +2349,7 @@ int launch_gemm_gelu(int dtype, int gelu_mode, const void* u, const void* w, con
                      size_t ws_bytes, hipStream_t st) {
   if (M == 0 || N == 0) return PTDP_OK;
   const bool tanh = gelu_mode == PTDP_GELU_TANH, vec = K % 4 == 0 && ((uintptr_t)u & 15) == 0;
-  const int form = dtype == PTDP_BF16 ? gelu_form(PTDP_GEMM_NN, M, N, K, ws ? ws_bytes : 0) : (vec ? 0 : -1);
+  const int form = dtype == PTDP_BF16 ? gelu_form(PTDP_GEMM_NN, M, N, K, ws ? ws_bytes : 0) : (vec && f32_form(true, false, M, N, K).tile != 64 ? 0 : -1);
   if (form < 0) {
     const int rc = launch_gemm(dtype, PTDP_GEMM_NN, u, w, z, nullptr, M, N, K, 0, 0, ws, ws_bytes, st);
     return rc != PTDP_OK ? rc : launch_bias_gelu_fwd(dtype, gelu_mode, z, b, g, M, N, st);
@@ -2405,8 +2410,7 @@ int launch_gemm_gelu_bwd(int dtype, int gelu_mode, const void* dg, const void* w
                          void* scratch, int M, int N, int K, void* ws, size_t ws_bytes, hipStream_t st, ColsumBatch* defer) {
   if (M == 0 || N == 0) return PTDP_OK;
   const bool tanh = gelu_mode == PTDP_GELU_TANH, vec = K % 4 == 0 && (((uintptr_t)dg | (uintptr_t)w) & 15) == 0;
-  const F32Form f32 = f32_form(true, true, M, N, K);
-  const int form = dtype == PTDP_BF16 ? gelu_form(PTDP_GEMM_NT, M, N, K, ws ? ws_bytes : 0) : (vec && f32.tile != 16 ? 0 : -1);
+  const int form = dtype == PTDP_BF16 ? gelu_form(PTDP_GEMM_NT, M, N, K, ws ? ws_bytes : 0) : (vec && f32_form(true, true, M, N, K).tile == 32 ? 0 : -1);
   if (form < 0) {
     const int rc = launch_gemm(dtype, PTDP_GEMM_NT, dg, w, dz, nullptr, M, N, K, 0, 0, ws, ws_bytes, st);
     return rc != PTDP_OK ? rc : launch_bias_gelu_bwd(dtype, gelu_mode, dz, z, b, dz, dbias, scratch, M, N, st, defer);
@@ -2421,7 +2425,7 @@ int launch_gemm_gelu_bwd(int dtype, int gelu_mode, const void* dg, const void* w
       const GemmArgs a = bf16_args<false, false>(dg, w, nullptr, M, N, K);
       rc = tanh ? launch_small_gelu_form<false, PTDP_GELU_TANH>(form, a, dz, e, st) : launch_small_gelu_form<false, PTDP_GELU_ERF>(form, a, dz, e, st);
     } else {
-      rows = f32.tile;
+      rows = 32;
       const GeluArgs<float> e{(const float*)b, (const float*)z, nullptr, (float*)scratch, 0, 0, 0.f};
       const float *A = (const float*)dg, *B = (const float*)w;
       rc = tanh ? launch_gemm_f32<true, true, Epi<EPI_GELU_GRAD, PTDP_GELU_TANH>>(A, B, (float*)dz, nullptr, M, N, K, K, 1, 1, K, 0, st, e)

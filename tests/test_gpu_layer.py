@@ -358,3 +358,25 @@ def test_residual_sum_in_the_last_product(h, a, t, s, b, dtype, p, tile):
                                         stream()), "sum")
     sync()
     assert torch.equal(y, want)
+
+
+def launches(rig, x):
+    """Launches per family of one forward and one backward."""
+    y, dx = torch.empty_like(x), torch.empty_like(x)
+    B.ptdp_prof_enable(1)
+    try:
+        B.check(rig.chunk.forward(0, x.data_ptr(), y.data_ptr(), rig.stash.data_ptr(), rig.ws.data_ptr()), "forward")
+        B.check(rig.chunk.backward(0, y.data_ptr(), dx.data_ptr(), rig.stash.data_ptr(), rig.ws.data_ptr()), "backward")
+        sync()
+        return {k: v[2] for k, v in B.prof_collect().items()}
+    finally:
+        B.ptdp_prof_enable(0)
+
+
+# 32 x 32 tiles next to the MLP's GeLU, 16 x 16 (the gradient a kernel of its own), 64 x 64 (both)
+@pytest.mark.parametrize("h,a,s,b,own", [(64, 2, 37, 1, (0, 0)), (256, 4, 128, 2, (0, 0)), (384, 6, 66, 1, (0, 1)), (256, 4, 341, 3, (1, 1)),
+                                         (640, 10, 348, 4, (1, 1))])
+def test_fp32_gelu_is_a_kernel_of_its_own_beside_large_tiles(h, a, s, b, own):
+    cfg = B.make_cfg(h=h, a=a, t=1, s=s, b=b, dtype=B.F32, p_hidden=0.1, seed=3)
+    n = launches(LayerRig(cfg), randn((s, b, h), B.F32, 1))
+    assert (n["bias_gelu_fwd"], n["bias_gelu_bwd"]) == own
