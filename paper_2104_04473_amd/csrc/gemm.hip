@@ -1932,14 +1932,17 @@ static const LargeCost kLargeCost[2] = {{3.9, 1.28, 0.78, 8.4, 2.8, 11.5, 1.28, 
 // Whole tiles: full rounds, then one that fills part of the chip.  The XCD with the most tiles (`busiest`, see gemm_dp_tile) sets the
 // number of rounds.  whole: the share of the tiles' outputs that exist.
 constexpr int kMixedRounds = 12;   // rounds from which the compute units no longer run in step and one's output overlaps another's products
-constexpr int kMixedSteps = 8;     // and k-tiles: shorter ones leave no products to overlap (a layer's weight gradients of 4096, 128 tokens: 128 x 128 tiles 331 us, 256 x 256 371)
+// and k-tiles, fewer where there are many rounds: shorter ones leave few products to overlap.  us of a layer's backward with 128 x 128 and with 256 x
+// 256 tiles for its weight gradients: 4096, 512 tokens (12 rounds of 8 k-tiles) 722, 770; 11520 over eight shards, 582 tokens (13 of 10) 866, 892;
+// 8320 over four, 804 tokens (13 of 13) 1053, 1021; 5440, 142 tokens (23 of 3) 963, 917; 7680, 435 tokens (43 of 7) 2089, 1988.
+constexpr int kMixedSteps = 12, kManyMixedRounds = 20;
 static double large_time(const LargeCost& c, long long tiles, long long busiest, double whole, int nk) {
   const int ncu = compute_units(), per_xcd = ncu >= 8 ? ncu / 8 : 1;
   const long long rounds = (busiest + per_xcd - 1) / per_xcd, left = tiles - (rounds - 1) * ncu;
   const double fill = left >= ncu ? 1.0 : (left > 1 ? (double)left : 1.0) / ncu;
   const double t = c.fixed + (double)(rounds - 1) * (c.step * nk + c.round * whole) + (c.step_alone + (c.step - c.step_alone) * fill) * nk +
                    (c.round_alone + (c.round - c.round_alone) * fill) * whole;
-  return rounds >= kMixedRounds && nk >= kMixedSteps ? 0.95 * t : t;
+  return rounds >= (nk >= kMixedSteps ? kMixedRounds : kManyMixedRounds) ? 0.95 * t : t;
 }
 // A call that is all remainder is split where that promises to be so much faster: the fit is too low for remainders of half a
 // round and more (2048 x 6144 x 12288 whole 241 us, split 256; 2048 x 6400 x 25600 497, 508).  Of the factors 1 to 1.15 the one that
@@ -2233,8 +2236,13 @@ template <int OUT> static int launch_tn_multi(int form, MultiArgs& a, ColsumBatc
   return PTDP_OK;
 }
 
-// the form that all of a launch's bf16 weight gradients take, or -1 for 256 x 256 tiles
-static int tn_multi_form(int n, const int* M, const int* N, int K) {
+// the form that all of a launch's bf16 weight gradients take, or -1 for 256 x 256 tiles; sums: with column sums to finish
+// Those take kSumsLaunch longer behind 256 x 256 tiles, in a launch of their own: 5 us (1024 wide) to 20 (9568 wide).  Over 135 layers of 480 to
+// 25600 (48 to 8192 tokens, one to eight shards) the form taken so is 0.2 % slower than the best of 256 x 256, 128 x 128 and 128 x 64 tiles
+// on average, 4.9 % at worst; not counted 0.75 and 8.1 %.  us of the backward with 256 x 256 and with 128 x 128 tiles: 2048 tokens of 1024
+// 193.0, 190.7; 596 of 2816 465, 447; 1024 of 4096 over two shards 620, 603; and where 256 x 256 stay, 1384 of 4864 over two 1008, 1037.
+constexpr double kSumsLaunch = 16.0;
+static int tn_multi_form(int n, const int* M, const int* N, int K, bool sums) {
   long long tiles = 0, busiest = 0;
   double outputs = 0.0;
   for (int j = 0; j < n; ++j) {
@@ -2244,10 +2252,11 @@ static int tn_multi_form(int n, const int* M, const int* N, int K) {
     outputs += (double)M[j] * N[j];
   }
   double t = large_time(kLargeCost[1], tiles, busiest, outputs / ((double)tiles * kBM * kBN), (K + BK - 1) / BK);
+  if (sums) t += kSumsLaunch;
   return small_form(1, n, M, N, K, &t);
 }
 bool gemm_tn_multi_takes_sums(int dtype, int n, const int* M, const int* N, int K) {
-  if (dtype == PTDP_BF16) return tn_multi_form(n, M, N, K) >= 0;
+  if (dtype == PTDP_BF16) return tn_multi_form(n, M, N, K, true) >= 0;
   for (int j = 0; j < n; ++j)
     if (f32_form(false, false, M[j], N[j], K).tile != 64) return true;
   return false;
@@ -2284,7 +2293,7 @@ static int gemm_tn_multi(int dtype, int n, const void* const* A, const void* con
     if (j < n) at += dp_blocks(a.g[j]);
   }
   a.start[kMaxMulti] = at;
-  const int form = tn_multi_form(n, M, N, K);
+  const int form = tn_multi_form(n, M, N, K, sums->n > 0);
   bool lines = true;
   for (int j = 0; j < n; ++j) lines = lines && whole_lines(N[j]);
   const int rc = lines ? launch_tn_multi<OUT_F32_RMW_LINES>(form, a, sums, st) : launch_tn_multi<OUT_F32_RMW>(form, a, sums, st);

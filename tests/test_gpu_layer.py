@@ -380,3 +380,11 @@ def test_fp32_gelu_is_a_kernel_of_its_own_beside_large_tiles(h, a, s, b, own):
     cfg = B.make_cfg(h=h, a=a, t=1, s=s, b=b, dtype=B.F32, p_hidden=0.1, seed=3)
     n = launches(LayerRig(cfg), randn((s, b, h), B.F32, 1))
     assert (n["bias_gelu_fwd"], n["bias_gelu_bwd"]) == own
+
+
+# weight gradients that 256 x 256 tiles compute faster, but not with the launch for the column sums that follows them; and (the last) with it
+@pytest.mark.parametrize("h,a,t,s,b,own", [(1024, 16, 1, 512, 4, False), (2624, 82, 2, 169, 2, False), (11520, 72, 8, 291, 2, False), (2304, 18, 1, 877, 2, True)])
+def test_column_sums_need_no_launch_where_the_forms_are_close(h, a, t, s, b, own):
+    cfg = B.make_cfg(h=h, a=a, t=t, s=s, b=b, dtype=B.BF16, p_hidden=0.1, seed=3)
+    n = launches(LayerRig(cfg), randn((s, b, h), B.BF16, 1))
+    assert (n["colsum"] > 0) == own and n["gemm_tn"] == 1
