@@ -1679,8 +1679,8 @@ gemm_bf16_dp_multi_kernel(MultiArgs a) {
 
 // The small tiles' form of it.  Its first n_sums workgroups (a multiple of 8) finish the column sums of the layer's backward: as a launch
 // of its own that is 5 us of a few dependent loads, here it runs beside the tiles (us per pass, same bits: one fp32 layer of 256 x 256 102.1
-// -> 97.5, two of 666 x 512 258.8 -> 250.6, of 2048 x 1024 697 -> 687, eight of 1024 x 2048 over two shards 2858 -> 2826).  With 256 x 256
-// tiles the sums are many and the launch long: they stay a launch of their own.
+// -> 97.5, two of 666 x 512 258.8 -> 250.6, eight of 1024 x 2048 over two shards 2858 -> 2826; of one backward, 2048 tokens of 1024 196.5 ->
+// 190.7, 512 of 4096 727 -> 722, 582 of 11520 over eight shards 865 -> 867).  With 256 x 256 tiles the sums are many and the launch long: they stay a launch of their own.
 template <bool TA, bool TB, int OUT, int BM, int BN, int S, int KG>
 __global__ void __launch_bounds__(KG * kSmallThreads, 2)
 gemm_bf16_small_multi_kernel(MultiArgs a, ColsumBatchArgs sums, int n_sums) {
@@ -1920,8 +1920,8 @@ static int compute_units() {
 // every split group stores at most one slab per compute unit
 size_t gemm_workspace_bytes() { return (size_t)compute_units() * kMaxSplitGroups * kSlabFloats * sizeof(float); }
 
-// Times in microseconds that decide how a call is cut (outputs in bf16, or += into fp32), fitted to measured calls: see
-// profiles/gemm_forms.txt for the calls, each fit's error and what picking by these numbers costs.
+// Times in microseconds that decide how a call is cut (outputs in bf16, or += into fp32), fitted to measured calls: profiles/gemm_forms.txt has
+// most of them with the present kernels, how far each form's model is off there and what picking by these numbers costs.
 struct LargeCost {
   double fixed, step, step_alone, round, round_alone;   // 256 x 256 tiles: per k-step and per round (first loads, output), full chip and one tile
   double split_fixed, split_step, split_slab, split_part, split_reduce;   // remainder groups: per k-step, per slab; reduce: per slab of one tile or, if more, of all
@@ -1946,7 +1946,7 @@ static double large_time(const LargeCost& c, long long tiles, long long busiest,
 }
 // A call that is all remainder is split where that promises to be so much faster: the fit is too low for remainders of half a
 // round and more (2048 x 6144 x 12288 whole 241 us, split 256; 2048 x 6400 x 25600 497, 508).  Of the factors 1 to 1.15 the one that
-// loses least over the measured calls (438 us in 839, 464 without).  Behind whole rounds the split pays as
+// loses least over the measured calls (1962 us in 1293, 2008 without).  Behind whole rounds the split pays as
 // computed (2048 x 12288 x 4608, 384 tiles: 191 us whole, 186 split; 2048 x 25600 x 3200 284, 271).
 constexpr double kSplitMargin = 1.06;
 
@@ -2033,9 +2033,8 @@ static const SmallCost kSmallCost[2][kSmallForms + 1] = {
      {256, 192, 1, 1, 0.0, 0.0, 0.0, 0.0, 0.0}}};
 constexpr int kMinStepsForGroups = 8;   // k-tiles from which two wave groups are considered: below, joining their sums costs what they save
 // k-tiles up to which 256 x 128 tiles are considered: longer products are faster on 256 x 256 tiles whose k range is split (us for
-// 256 x 128 and split: 2048 x 4096 x 12288 NT 168, 163; x 16384 NN 211, 209, NT 215, 206).  Of 1409 calls (those of
-// profiles/gemm_forms.txt and layers of 48 to 8192 tokens) they are picked in 42 and take 0.85 of the time of the form picked
-// before on average, 0.985 at most.
+// 256 x 128 and split: 2048 x 4096 x 12288 NT 168, 163; x 16384 NN 211, 209, NT 215, 206).  Of the 1293 NN and NT
+// calls of profiles/gemm_forms.txt they are picked in 56 and take 0.89 of the best other form's time on average, 1.08 at most.
 constexpr int kWideSteps = 120;
 // Not considered with that many workgroups per CU over that many k-tiles: the panels no longer stay in the caches and the time is
 // up to 1.6 times the above (128 x 64, 16 workgroups, 100 k-tiles).
@@ -2068,17 +2067,22 @@ static int small_form(int rmw, int n, const int* M, const int* N, int K, double*
 }
 
 // 256 x 192 tiles, NN (transposing reads of B: twice the read instructions) and NT: a k-tile with all compute units and with few, a call,
-// and per round.  Fitted to 207 measured calls (rms 9 %).
+// and per round.  Over the calls of profiles/gemm_forms.txt they are off by 13 % (rms).
 struct MidCost {
   double step, step_alone, fixed, round, round_full;
 };
 static const MidCost kMidCost[2] = {{1.19, 0.76, 4.9, 6.0, 3.8}, {1.09, 0.70, 4.6, 6.6, 4.3}};   // [PTDP_GEMM_NN], [PTDP_GEMM_NT]
 // Taken where they promise kMidMargin, from two row tiles that are three quarters full (less: a column panel serves so few rows that its way
-// from memory counts, 204 x 25600 x 768 NN 0.91, 299 x 20096 x 8944 0.89 of the speed).  us of the form taken before and now: NT 2048 x 6144 x 12288 235 ->
-// 220, 2048 x 12288 x 1536 70 -> 65, 1001 x 10240 x 5120 103 -> 92, 860 x 18944 x 2560 109 -> 94, 745 x 25600 x 9216 361 -> 311, 632 x 14848 x 512 18.5 -> 16.6; NN 2048 x
-// 12288 x 1536 73 -> 69, 1415 x 6656 x 1280 31.6 -> 29.4.  Of 208 calls they are picked in 58, at 1.08 times the speed of the form before on average.
+// from memory counts, 208 x 25600 x 768 NN 22.8 us and 21.8 so, 304 x 20096 x 8944 NT 180 and 199).  us of the best other form and so: NT 2048 x
+// 6144 x 12288 240, 209; 2048 x 12288 x 1536 80, 72; 1008 x 10240 x 5120 104, 91; 752 x 25600 x 9216 346, 302; 632 x 14848 x 512 19.0, 17.0; NN
+// 2048 x 12288 x 1536 80, 77; 1416 x 6656 x 1280 32.3, 30.8.  Of the 867 calls of profiles/gemm_forms.txt with a longer k than kMidShort they are
+// picked in 65, at 1.11 times the speed of the form picked without them on average, 6 of them slower by more than 2 % (2176 x 4224 x 2112
+// NN 0.91, 4920 x 2080 x 2080 NN 0.90).  A margin of 1.04 would leave three of those and lose as much elsewhere: calls come out 1.29 % above their
+// best form on average, 1.30 now.
 constexpr double kMidMargin = 1.02;
-constexpr int kMidShort = 448;   // shorter products are their output stages: within 7 % of small tiles either way
+// Not for products of up to seven k-tiles, which are mostly their output stages: of 164 such calls that the model would give to them 17 are
+// slower by more than 2 %, up to a fifth, and the gain, 1.06 on average, is about 1 us a call.
+constexpr int kMidShort = 448;
 static double mid_time(int mode, int M, int N, int K) {
   const int ncu = compute_units(), nk = (K + BK - 1) / BK;
   const MidCost& c = kMidCost[mode == PTDP_GEMM_NT];
