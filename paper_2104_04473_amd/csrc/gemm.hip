@@ -1925,9 +1925,14 @@ size_t gemm_workspace_bytes() { return (size_t)compute_units() * kMaxSplitGroups
 struct LargeCost {
   double fixed, step, step_alone, round, round_alone;   // 256 x 256 tiles: per k-step and per round (first loads, output), full chip and one tile
   double split_fixed, split_step, split_slab, split_part, split_reduce;   // remainder groups: per k-step, per slab; reduce: per slab of one tile or, if more, of all
+  double medium;   // factor for a few rounds of kMediumSteps[0] to [1] k-tiles
 };
-static const LargeCost kLargeCost[2] = {{3.9, 1.28, 0.78, 8.4, 2.8, 11.5, 1.28, 0.050, 0.26, 0.020},
-                                        {5.7, 1.33, 1.12, 24.4, 8.7, 3.3, 1.56, 0.023, 0.50, 0.069}};
+static const LargeCost kLargeCost[2] = {{3.9, 1.28, 0.78, 8.4, 2.8, 11.5, 1.28, 0.050, 0.26, 0.020, 1.0},
+                                        {5.7, 1.33, 1.12, 24.4, 8.7, 3.3, 1.56, 0.023, 0.50, 0.069, 1.05}};
+// With += the sums above are 2 % low there and those of 128 x 128 tiles 4 to 8 % high.  Of the TN calls of profiles/gemm_forms.txt that take another form
+// since column tiles are dealt evenly 8 of 35 were slower by more than 2 % without the factor, 2 of 31 with it; all together 1.03 and 1.06 times
+// as fast (us with 128 x 128 and with 256 x 256 tiles: 19200 x 4800 x 712 220, 241; 11008 x 2752 x 528 73, 80).
+constexpr int kMediumSteps[2] = {5, 16};
 
 // Whole tiles: full rounds, then one that fills part of the chip.  The XCD with the most tiles (`busiest`, see gemm_dp_tile) sets the
 // number of rounds.  whole: the share of the tiles' outputs that exist.
@@ -1942,7 +1947,8 @@ static double large_time(const LargeCost& c, long long tiles, long long busiest,
   const double fill = left >= ncu ? 1.0 : (left > 1 ? (double)left : 1.0) / ncu;
   const double t = c.fixed + (double)(rounds - 1) * (c.step * nk + c.round * whole) + (c.step_alone + (c.step - c.step_alone) * fill) * nk +
                    (c.round_alone + (c.round - c.round_alone) * fill) * whole;
-  return rounds >= (nk >= kMixedSteps ? kMixedRounds : kManyMixedRounds) ? 0.95 * t : t;
+  const bool medium = nk >= kMediumSteps[0] && nk <= kMediumSteps[1] && rounds > 1 && rounds < kManyMixedRounds;
+  return (rounds >= (nk >= kMixedSteps ? kMixedRounds : kManyMixedRounds) ? 0.95 * t : t) * (medium ? c.medium : 1.0);
 }
 // A call that is all remainder is split where that promises to be so much faster: the fit is too low for remainders of half a
 // round and more (2048 x 6144 x 12288 whole 241 us, split 256; 2048 x 6400 x 25600 497, 508).  Of the factors 1 to 1.15 the one that
@@ -2243,9 +2249,10 @@ template <int OUT> static int launch_tn_multi(int form, MultiArgs& a, ColsumBatc
 // the form that all of a launch's bf16 weight gradients take, or -1 for 256 x 256 tiles; sums: with column sums to finish
 // Those take kSumsLaunch longer behind 256 x 256 tiles, in a launch of their own: 5 us (1024 wide) to 20 (9568 wide).  Over 135 layers of 480 to
 // 25600 (48 to 8192 tokens, one to eight shards) the form taken so is 0.2 % slower than the best of 256 x 256, 128 x 128 and 128 x 64 tiles
-// on average, 4.9 % at worst; not counted 0.75 and 8.1 %.  us of the backward with 256 x 256 and with 128 x 128 tiles: 2048 tokens of 1024
-// 193.0, 190.7; 596 of 2816 465, 447; 1024 of 4096 over two shards 620, 603; and where 256 x 256 stay, 1384 of 4864 over two 1008, 1037.
-constexpr double kSumsLaunch = 16.0;
+// on average, 3.7 % at worst; not counted 0.24, without the medium factor of LargeCost 0.3 and 6.7 %, with neither 0.6 and 8.1 %.  us of the backward
+// with 256 x 256 and with 128 x 128 tiles: 2048 tokens of 1024 193.0, 190.7; 596 of 2816 465, 447; 1024 of 4096 over two shards 620, 603; and where
+// 256 x 256 stay, 1384 of 4864 over two 1008, 1037.
+constexpr double kSumsLaunch = 5.0;
 static int tn_multi_form(int n, const int* M, const int* N, int K, bool sums) {
   long long tiles = 0, busiest = 0;
   double outputs = 0.0;
