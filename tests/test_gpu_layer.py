@@ -290,13 +290,15 @@ def test_layernorm_behind_a_residual_sum(dtype, h, a, t):
             assert torch.equal(rs, rig.field(l, rstd, (s * b,), torch.float32))
 
 
-# every small form of both products, rows and columns that fill no tile, tanh; 256 x 192, 256 x 256 and 16 x 16 tiles (kernels of their own)
+# every small form of both products, rows and columns that fill no tile, tanh; 256 x 192, 256 x 256 and fp32's 64 x 64 tiles (kernels of their own);
+# 16 x 16 tiles (the gradient's in a kernel of its own)
 @pytest.mark.parametrize("h,a,t,s,b,dtype,gelu,tile", [
     (512, 8, 1, 25, 8, B.BF16, B.GELU_TANH, (64, 64, 2)), (320, 2, 2, 200, 1, B.BF16, B.GELU_ERF, (128, 64, 1)),
     (1536, 12, 1, 200, 1, B.BF16, B.GELU_ERF, (128, 64, 2)), (320, 2, 1, 400, 5, B.BF16, B.GELU_TANH, (128, 128, 1)),
     (512, 8, 1, 400, 5, B.BF16, B.GELU_ERF, (128, 128, 2)), (768, 12, 1, 400, 10, B.BF16, B.GELU_ERF, (256, 192, 1)),
     (1024, 16, 1, 400, 10, B.BF16, B.GELU_ERF, (256, 256, 1)),
     (64, 2, 1, 37, 1, B.F32, B.GELU_ERF, None), (256, 4, 1, 128, 2, B.F32, B.GELU_TANH, None), (384, 6, 1, 100, 1, B.F32, B.GELU_ERF, None),
+    (384, 6, 1, 66, 1, B.F32, B.GELU_ERF, None), (384, 6, 1, 66, 1, B.F32, B.GELU_TANH, None),
     (512, 8, 1, 301, 7, B.F32, B.GELU_ERF, None),
 ])
 def test_gelu_in_the_products_beside_it(h, a, t, s, b, dtype, gelu, tile):
